@@ -15,6 +15,9 @@ enum { OUT_COMPACT = 0, OUT_MAP = 1, OUT_TOKENS_T = 2, OUT_COMPACT_F32 = 3 };
 // The consumer then reads activations instead of normalising its input in a launch of its own.
 struct GnView { bf16_t* dst; const float2* ss; int dstC, c_off, silu, pad_; };
 
+// n / d as (umulhi(n, mul) + n) >> shift: exact for n < 2^31 (round-up method of Granlund and Montgomery)
+struct FastDiv { unsigned mul; int shift; };
+
 struct IgemmArgs {
     // ---- A operand: rows = B * Ma active pixels (or compact rows) x K
     const bf16_t* a0; const bf16_t* a1; int C0, C1;    // map sources [B,Hin,Win,C*] (a1 unused when C1 == 0)
@@ -45,6 +48,12 @@ struct IgemmArgs {
     int need_pix;                                       // set by the launcher: the epilogue addresses a map (else rows only)
     // ---- optional normalised copies of the output map for its consumers (one OUT_MAP section, N % 4 == 0)
     int nview; GnView view[2];
+    // ---- set by the launcher of the wave-split kernel: K steps per workgroup, divisors, arrival counters of split tiles,
+    // whether four consecutive rows are four consecutive tokens (8-byte stores into a transposed section)
+    int kper, tt, trans4; int* counters;
+    struct { const bf16_t* p; unsigned bytes, pitch; } src[4];      // A sources a0, a1, s0, s1: base, size, bytes per pixel (or row)
+    unsigned bias_bytes, bias2_bytes, temb_bytes, res_bytes;        // sizes of the epilogue operands (0: absent)
+    FastDiv d_gx, d_gy, d_Ma, d_tt, d_tw, d_tiles_w, d_spt;
 };
 
 // What a block of the UNet step keeps in the per-step cache besides its stored maps (all derived from them and from
@@ -117,9 +126,12 @@ __device__ __forceinline__ void put_views1(const GnView* view, int nview, int b,
 }
 #endif
 
-// Scratch of the launcher: GroupNorm (scale, shift) table and the parked partial sums of split-K launches.
-constexpr size_t IGEMM_PARTIAL_BYTES = 32u << 20;
-struct IgemmWorkspace { float* partial; size_t partial_bytes; };
+// Scratch of the launcher: the parked partial sums of split-K launches, then the arrival counters.
+constexpr int IGEMM_COUNTERS = 4096;     // arrival counters of split output tiles (zeroed once per call, left at zero by every launch)
+constexpr size_t IGEMM_PARTIAL_BYTES = (32u << 20) - IGEMM_COUNTERS * sizeof(int);
+struct IgemmWorkspace { float* partial; size_t partial_bytes; int* counters; mutable bool counters_zeroed; };
+bool wave_gemm_fits(const IgemmArgs& a);
+int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st);
 size_t igemm_workspace_bytes();
 // Carves the scratch out of `workspace`; with a null or too
 // small workspace `out` is left empty and every launch runs unsplit.

@@ -6,8 +6,8 @@
 namespace fise {
 
 // one kind per kernel family, so that a kind's average can be set against a profiler's per-kernel figure
-enum { PROF_IGEMM = 0,          // LDS-direct gathered GEMM, 64x64 tiles
-       PROF_IGEMM_GEGLU = 1,    // the same with the GEGLU epilogue (64x128 / 32x256 tiles)
+enum { PROF_IGEMM = 0,          // gathered GEMM over maps, K split inside the workgroup (or shared 64x64 tiles)
+       PROF_IGEMM_GEGLU = 1,    // the GEGLU epilogue
        PROF_ATTENTION = 2,      // active-query attention (without its merge launch)
        PROF_IGEMM_WIDE = 3,     // 128x128 tiles (dense-sized problems)
        PROF_REDUCE = 4,         // split-K reduce + epilogue
@@ -15,7 +15,7 @@ enum { PROF_IGEMM = 0,          // LDS-direct gathered GEMM, 64x64 tiles
        PROF_IGEMM_STAGED = 6,   // register-staged gathered GEMM (GroupNorm prologue, 32-wide K steps)
        PROF_ATTENTION_MERGE = 7,
        PROF_EMPTY = 8,          // nothing between the two events: the bracket's own cost
-       PROF_IGEMM_WSK = 9,      // wave-split gathered GEMM (per-token products, 32-row tiles, K split inside the workgroup)
+       PROF_ROWS_GEMM = 9,      // gathered GEMM over compact rows, K split inside the workgroup
        PROF_KINDS = 10 };
 
 extern bool g_profile_on;

@@ -1,0 +1,588 @@
+// Gathered GEMM for tiles of 32 or 64 rows whose K loop is split over the waves of ONE workgroup.
+//
+//   out[row, n] = epilogue( sum_k A[row, k] * W[n, k]  (+ sum_k A2[row, k] * W2[n, k]) )      (see igemm.h)
+//
+// What bounds the masked step is not bandwidth or MFMA rate but the fixed cost of ~200 dependent launches, and inside a
+// launch the round trips to memory.  So this kernel is built around them:
+//  - Every wave owns the whole 32*TM x 32*TN tile for its share of K and runs it from an LDS ring of its own, filled by
+//    LDS-direct loads: no barrier in the K loop, a wave waits for its own loads only, and 4 waves x (NST - 1) stages keep
+//    64 - 100 KB per CU in flight (32 KB are enough for the 125 GB/s a CU gets out of its L2: measured).
+//  - No row table and no barrier in front of the first load: the lanes work out their own rows (divisions by
+//    precomputed reciprocals), the weight loads of the first stages go out before the pixel of a row is known.
+//  - Everything the epilogue fetches (biases, time projection, residual, scale / shift tables) is requested before the K
+//    loop through buffer descriptors; an operand that is absent has a descriptor of size zero, so there is no branch and
+//    hence no round trip per operand.
+//  - The waves' partial tiles are summed through LDS in wave order.  Where the tiles of a launch do not fill the chip K is
+//    also split over workgroups: every workgroup parks its tile (written through to memory), counts itself on a per-tile
+//    counter, and the one that arrives last adds the parked tiles in split order and finishes.  Nobody waits for anybody,
+//    so there is nothing to deadlock, and the sum does not depend on who came last.
+// Measured against shared 64x64 tiles with a reduce launch behind every K split: step of 12 of 64 tiles 3070 -> 2590 us,
+// 2 of 70 tiles 2600 -> 1985 us, transformer block of 160 rows 92 -> 78 us.
+#include <algorithm>
+#include "igemm.h"
+#include "profile.h"
+
+namespace fise {
+
+#define FISE_AS1 __attribute__((address_space(1)))
+typedef unsigned u32x2_w __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4_w __attribute__((ext_vector_type(4)));
+typedef float f32x4_w __attribute__((ext_vector_type(4)));
+
+enum { A_ROWS = 0, A_MAP = 1 };         // compact rows / pixels of maps (taps, two sources, side product)
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// n / d for the divisor behind f, exact for n < 2^31
+__device__ __forceinline__ unsigned fdiv(unsigned n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float lo16(unsigned w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi16(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
+
+// x * Phi(x) with Phi from the complementary error function of |x| / sqrt 2 (Abramowitz & Stegun 7.1.26: absolute error
+// below 1.5e-7, and for negative x no cancellation against 1)
+__device__ __forceinline__ float gelu_f(float x) {
+    const float u = fabsf(x) * 0.70710678118654752f;
+    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, u, 1.0f));
+    const float p = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f), -0.284496736f), 0.254829592f);
+    const float e = 0.5f * p * __builtin_amdgcn_exp2f(-1.4426950408889634f * u * u);      // half of erfc(u)
+    return x * (x < 0.f ? e : 1.0f - e);
+}
+#endif
+
+template <int TM, int TN, int NW, int NST, int AM, bool GEGLU>
+__global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int BM = 32 * TM, BN = 32 * TN, NT = 64 * NW;
+    constexpr int AL = BM / 8, BL = BN / 8;             // 16-byte loads per lane and K step (one load fills 8 rows of 128 bytes)
+    constexpr int STAGE = (BM + BN) * 128;
+    constexpr int PITCH = BN + 4;                       // floats per row of a partial tile in LDS
+    constexpr int OW = GEGLU ? BN / 2 : BN;             // output columns of the tile
+    constexpr int CPR = OW / 4, ITEMS = BM * CPR / NT;  // four-column pieces per row, per thread
+    constexpr unsigned OOB = 0x80000000u;               // beyond every descriptor: the load returns zeros
+    static_assert(BM * CPR % NT == 0 && NW * NST * STAGE >= NW * BM * PITCH * 4, "tile");
+    extern __shared__ __attribute__((aligned(16))) unsigned char ring[];      // [NW][NST][STAGE], later [NW][BM][PITCH] floats
+
+    // Kernel arguments arrive through scalar loads placed where a field is first used; named here they come as one batch.
+    asm volatile("" ::"s"(a.gx), "s"(a.gy), "s"(a.splits), "s"(a.kper), "s"(a.d_gx.mul), "s"(a.d_gy.mul), "s"(a.d_Ma.mul), "s"(a.d_tt.mul),
+                 "s"(a.d_tw.mul), "s"(a.d_tiles_w.mul), "s"(a.B), "s"(a.Ma), "s"(a.K), "s"(a.K2), "s"(a.N), "s"(a.w), "s"(a.tile_idx), "s"(a.need_pix));
+    asm volatile("" ::"s"(a.Ho), "s"(a.Wo), "s"(a.tile), "s"(a.sect_n), "s"(a.out_mode[0]), "s"(a.bias), "s"(a.bias_bytes), "s"(a.temb), "s"(a.temb_bytes),
+                 "s"(a.res), "s"(a.res_bytes), "s"(a.res_compact), "s"(a.nview), "s"(a.src[0].p), "s"(a.src[0].bytes));
+    if constexpr (AM == A_MAP) asm volatile("" ::"s"(a.Hin), "s"(a.Win), "s"(a.ksize), "s"(a.stride), "s"(a.ups), "s"(a.C0), "s"(a.d_spt.mul), "s"(a.bias2), "s"(a.bias2_bytes));
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane >> 3;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // consecutive workgroups go round-robin to the 8 XCDs: give every XCD a contiguous run of (bz, by, bx), bx fastest, so
+    // that a slice of the weights is pulled into one L2
+    int bx, by, bz;
+    {
+        const int total = a.gx * a.gy * a.splits, chunk = total >> 3;
+        int w = blockIdx.x;
+        if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
+        const unsigned t = fdiv((unsigned)w, a.d_gx);
+        bx = w - (int)t * a.gx; bz = (int)fdiv(t, a.d_gy); by = (int)t - bz * a.gy;
+    }
+    const int rows = a.B * a.Ma, m0 = bx * BM;
+    const int nsteps1 = a.K >> 6, nsteps = nsteps1 + (a.K2 >> 6);
+    int kb, ke;                                         // K steps of this wave
+    {
+        const int c0 = bz * a.kper, c1 = min(nsteps, c0 + a.kper), per = (c1 - c0 + NW - 1) / NW;
+        kb = min(c1, c0 + wave * per); ke = min(c1, kb + per);
+    }
+
+    // ---- Every lane works out one row of the tile (row lane % BM); whoever needs a row's position gets it by a lane
+    // permutation.  First half: batch element and the request for the tile id.
+    const int my_row = m0 + (lane & (BM - 1));
+    const unsigned gm = (unsigned)min(my_row, rows - 1);
+    const unsigned rb = fdiv(gm, a.d_Ma), rm = gm - __umul24(rb, (unsigned)a.Ma);
+    const bool pixels = AM == A_MAP || (a.need_pix && a.tile_idx);      // rows are pixels of active tiles
+    unsigned rp = 0; int rtile = 0;
+    if (pixels) {
+        const unsigned t = fdiv(rm, a.d_tt);
+        rp = rm - __umul24(t, (unsigned)a.tt);
+        rtile = ((const FISE_AS1 int*)a.tile_idx)[t];
+    }
+
+    // ---- weights: first stages.  LDS slot p of row r holds segment p ^ ((r >> 1) & 7) (conflict-free operand reads); a load
+    // fills 8 rows, so between odd and even loads only bit 2 of the segment flips.
+    const unsigned wrows = (unsigned)(GEGLU ? 2 * a.N : a.N);
+    const unsigned seg0 = (unsigned)(((lane & 7) ^ (lr >> 1)) * 16);
+    unsigned vb[BL], soff_b, bytes_b;
+    const bf16_t* ptr_b;
+    auto set_weights = [&](bool side, int kstep) {
+        const unsigned pitch = (unsigned)(side ? a.K2 : a.K) * 2u;
+        ptr_b = side ? a.w2 : a.w; bytes_b = __umul24(wrows, pitch); soff_b = (unsigned)kstep * 128u;
+        const unsigned row0 = __umul24((unsigned)(by * (GEGLU ? OW : BN) + lr), pitch);
+#pragma unroll
+        for (int j = 0; j < BL; ++j) {                  // GEGLU: value rows, then the gate rows N further down
+            unsigned jr = j * 8u;
+            if (GEGLU && j >= BL / 2) jr += (unsigned)(a.N - OW);
+            vb[j] = row0 + (j & 1 ? seg0 ^ 64u : seg0) + jr * pitch;      // rows past the matrix lie past the descriptor
+        }
+    };
+    unsigned char* const my_ring = ring + wave * (NST * STAGE);
+    int kw = kb;                                        // weight cursor
+    set_weights(kb >= nsteps1, kb >= nsteps1 ? kb - nsteps1 : kb);
+    auto issue_b = [&](int st) {                        // steps past the range: a descriptor of size zero, no traffic
+        const __amdgpu_buffer_rsrc_t rs = buf(ptr_b, kw < ke ? bytes_b : 0u);
+        unsigned char* base = my_ring + st * STAGE + BM * 128;
+#pragma unroll
+        for (int j = 0; j < BL; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + j * 1024), 16, vb[j], soff_b, 0, 0);
+        ++kw; soff_b += 128u;
+        if (AM == A_MAP && kw == nsteps1 && kw < ke) set_weights(true, 0);
+    };
+    // Where many row tiles share a slice of the weights they walk it in step, and each of its lines is cold for all of them at
+    // once: the CU's ~16 KB of loads in flight then wait for memory instead of L2 (85 GB/s per CU instead of 110).  So the
+    // row tiles first touch the slice, each a share of its lines (one dword per line, into a stage that is filled later).
+    // 1536 x 320 x 2880: K loop 6.4 -> 5.0 us; short K ranges do not earn it back.
+    if (a.gx >= 12 && a.kper >= 32) {
+        const int c0 = bz * a.kper, c1 = min(nsteps1, c0 + a.kper);
+        const int half = BN == 32 ? lane >> 5 : 0;
+        const __amdgpu_buffer_rsrc_t rs = buf(a.w, bytes_b);
+        const unsigned off = __umul24((unsigned)(by * (GEGLU ? OW : BN) + (lane & (BN - 1)) + (GEGLU && lane >= OW ? a.N - OW : 0)), (unsigned)a.K * 2u);
+        constexpr int PER = BN == 32 ? 2 : 1;
+        for (int q = c0 + (bx * NW + wave) * PER; q < c1; q += a.gx * NW * PER)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(ring + wave * (NST * STAGE)), 4, off + (q + half) * 128, 0, 0, 0);
+    }
+#pragma unroll
+    for (int s = 0; s < NST; ++s) issue_b(s);
+
+    // ---- second half of the row: position on the output map
+    unsigned ryx = rm, rpix = 0; int ry = 0, rx = 0;
+    if (pixels) {
+        const unsigned py = fdiv(rp, a.d_tw), ty = fdiv((unsigned)rtile, a.d_tiles_w);
+        ry = (int)(__umul24(ty, (unsigned)a.tile) + py);
+        rx = (int)(__umul24((unsigned)rtile - __umul24(ty, (unsigned)a.tiles_w), (unsigned)a.tile_w) + (rp - __umul24(py, (unsigned)a.tile_w)));
+        ryx = __umul24((unsigned)ry, (unsigned)a.Wo) + rx;
+    }
+    rpix = __umul24(rb, __umul24((unsigned)a.Ho, (unsigned)a.Wo)) + ryx;
+
+    // ---- this thread's pieces of the finished tile (four columns of a row, or four rows of a column) and their operands
+    const int col0 = by * OW;
+    const int sect = (col0 >= a.sect_n) + (col0 >= 2 * a.sect_n);      // a column tile lies in one section (checked by the launcher)
+    const int omode = sect == 0 ? a.out_mode[0] : sect == 1 ? a.out_mode[1] : a.out_mode[2];
+    const bool trans = omode == OUT_TOKENS_T && a.trans4;
+    int e_r[ITEMS], e_c[ITEMS], e_b[ITEMS]; unsigned e_pix[ITEMS]; bool e_ok[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int item = tid + it * NT;
+        e_r[it] = trans ? (item % (BM / 4)) * 4 : item / CPR;
+        e_c[it] = trans ? item / (BM / 4) : (item % CPR) * 4;
+        e_ok[it] = m0 + e_r[it] < rows && col0 + e_c[it] < a.N;
+        e_b[it] = __shfl((int)rb, e_r[it]);
+        e_pix[it] = (unsigned)__shfl((int)rpix, e_r[it]);
+    }
+    constexpr bool AHEAD = ITEMS <= 2;                  // more pieces per thread: fetched after the K loop, all together
+    u32x2_w e_bias[ITEMS], e_bias2[ITEMS], e_gate[ITEMS]; u32x4_w e_temb[ITEMS], e_res[ITEMS], e_ss[ITEMS][2][2];
+    auto fetch_operands = [&]() {                       // an absent operand has a descriptor of size zero: no branches, no waits
+        const __amdgpu_buffer_rsrc_t s_bias = buf(a.bias, a.bias_bytes), s_bias2 = buf(a.bias2, a.bias2_bytes),
+                                     s_temb = buf(a.temb, a.temb_bytes), s_res = buf(a.res, a.res_bytes);
+        const int res_shift = a.res_compact == 2 ? 2 : 1;       // float rows / bf16 (16 bytes are fetched either way, 8 of them used)
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const unsigned no = e_ok[it] && !trans ? 0u : OOB, col = (unsigned)(col0 + e_c[it]);
+            e_bias[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, (col * 2u) | no, 0, 0));
+            if constexpr (GEGLU) {
+                e_gate[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, ((col + a.N) * 2u) | no, 0, 0));
+            } else {
+                const unsigned r = __umul24(a.res_compact ? (unsigned)(m0 + e_r[it]) : e_pix[it], (unsigned)a.N) + col;
+                e_res[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_res, (r << res_shift) | no, 0, 0));
+                if constexpr (AM == A_MAP) {
+                    e_bias2[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias2, (col * 2u) | no, 0, 0));
+                    e_temb[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_temb, ((__umul24((unsigned)e_b[it], (unsigned)a.temb_stride) + col) * 4u) | no, 0, 0));
+                }
+            }
+        }
+        if constexpr (!GEGLU)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+                if (v < a.nview) {
+                    const __amdgpu_buffer_rsrc_t s = buf(a.view[v].ss, (unsigned)a.B * a.view[v].dstC * 8u);
+#pragma unroll
+                    for (int it = 0; it < ITEMS; ++it) {
+                        const unsigned no = e_ok[it] && !trans ? 0u : OOB;
+                        const unsigned off = ((__umul24((unsigned)e_b[it], (unsigned)a.view[v].dstC) + a.view[v].c_off + col0 + e_c[it]) * 8u) | no;
+                        e_ss[it][v][0] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s, off, 0, 0));
+                        e_ss[it][v][1] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s, off, 16, 0));
+                    }
+                }
+    };
+    if constexpr (AHEAD) fetch_operands();
+
+    // ---- A operand
+    unsigned va[AL], soff_a, bytes_a = a.src[0].bytes;
+    const bf16_t* ptr_a = a.src[0].p;
+    int ka = kb;                                        // cursor: K step, source, tap, channel within the source, channels of the source
+    int si = 0, tap = 0, cc = 0, cn = a.C0;
+    unsigned in0[AL], valid[AL], out0[AL];              // pixel under tap (0, 0) (wraps at the border), taps inside the image | parities << 16; output pixel
+    if constexpr (AM == A_ROWS) {
+        soff_a = (unsigned)kb * 128u;
+        const unsigned row0 = (unsigned)(m0 + lr) * a.src[0].pitch;
+#pragma unroll
+        for (int j = 0; j < AL; ++j) va[j] = row0 + (j & 1 ? seg0 ^ 64u : seg0) + (unsigned)(j * 8) * a.src[0].pitch;     // past the last row: past the descriptor
+    }
+    auto set_source = [&]() {                           // base and offsets of the cursor position
+        si = __builtin_amdgcn_readfirstlane(si);
+        ptr_a = a.src[si].p; bytes_a = a.src[si].bytes;
+        const unsigned pitch = a.src[si].pitch;
+        soff_a = (unsigned)cc * 2u; cn = (int)(pitch >> 1);
+        if (si >= 2) {                                  // side product: the output pixel itself
+#pragma unroll
+            for (int j = 0; j < AL; ++j) va[j] = (__umul24(out0[j], pitch) + (j & 1 ? seg0 ^ 64u : seg0)) | (out0[j] & OOB);
+            return;
+        }
+        const int ky = a.ksize == 1 ? 0 : (tap * 11) >> 5, kx = tap - ky * a.ksize;
+        unsigned px[AL];
+        if (a.ups) {                                    // nearest neighbour: taps step from one input pixel to the next by parity
+#pragma unroll
+            for (int j = 0; j < AL; ++j) px[j] = in0[j] + __umul24((((valid[j] >> 16) & 1u) + ky) >> 1, (unsigned)a.Win) + ((((valid[j] >> 17) & 1u) + kx) >> 1);
+        } else {
+            const unsigned delta = (unsigned)(ky * a.Win + kx);
+#pragma unroll
+            for (int j = 0; j < AL; ++j) px[j] = in0[j] + delta;
+        }
+#pragma unroll
+        for (int j = 0; j < AL; ++j) va[j] = (__umul24(px[j], pitch) + (j & 1 ? seg0 ^ 64u : seg0)) | ((~valid[j] >> tap) << 31);
+    };
+    if constexpr (AM == A_MAP) {
+        // pixel under tap (0, 0) and which taps lie inside the image, worked out for this lane's row, then dealt out
+        const int pad = a.ksize >> 1, iy = ry * a.stride - pad, ix = rx * a.stride - pad;
+        const int hh = a.Hin << a.ups, ww = a.Win << a.ups;
+        unsigned vx = 0, v = 0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) vx |= (k < a.ksize && (unsigned)(ix + k) < (unsigned)ww ? 1u : 0u) << k;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v |= (k < a.ksize && (unsigned)(iy + k) < (unsigned)hh ? vx : 0u) << (k * a.ksize);
+        if (my_row >= rows) v = 0;
+        v |= ((unsigned)iy & 1u) << 16 | ((unsigned)ix & 1u) << 17;
+        const unsigned p0 = (unsigned)((int)rb * a.Hin + (iy >> a.ups)) * (unsigned)a.Win + (unsigned)(ix >> a.ups);
+        const unsigned o0 = my_row < rows ? rpix : OOB;
+#pragma unroll
+        for (int j = 0; j < AL; ++j) {
+            in0[j] = (unsigned)__shfl((int)p0, j * 8 + lr);
+            valid[j] = (unsigned)__shfl((int)v, j * 8 + lr);
+            out0[j] = (unsigned)__shfl((int)o0, j * 8 + lr);
+        }
+        const int Cin = a.C0 + a.C1;
+        if (kb < nsteps1) {
+            tap = (int)fdiv((unsigned)kb, a.d_spt); cc = kb * 64 - tap * Cin;
+            if (cc >= a.C0) { si = 1; cc -= a.C0; }
+        } else {
+            cc = (kb - nsteps1) * 64; si = 2;
+            if (cc >= a.S0) { si = 3; cc -= a.S0; }
+        }
+        set_source();
+    }
+    auto issue_a = [&](int st) {
+        const __amdgpu_buffer_rsrc_t rs = buf(ptr_a, ka < ke ? bytes_a : 0u);
+        unsigned char* base = my_ring + st * STAGE;
+#pragma unroll
+        for (int j = 0; j < AL; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + j * 1024), 16, va[j], soff_a, 0, 0);
+        ++ka; soff_a += 128u;
+        if constexpr (AM == A_MAP) {
+            cc += 64;
+            if (cc >= cn) {                             // next source (a0 -> a1 -> a0 of the next tap ... -> s0 -> s1)
+                cc = 0;
+                if (si == 0 && a.C1) si = 1;
+                else if (si < 2) { si = ka == nsteps1 ? 2 : 0; ++tap; }
+                else si = 3;
+                if (ka < ke) set_source();
+            }
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < NST; ++s) issue_a(s);
+
+    // ---- K loop.  The accumulators hold the transposed product (lane = row, four consecutive columns per register group).
+    // One copy of the body with a rotating stage offset: the launch is short, so the code it has to fetch counts.
+    unsigned rd[4];                                     // LDS offset of this lane's operand fragments within 32 rows of a stage
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) rd[ks] = (unsigned)((lane & 31) * 128 + (((ks * 2) ^ (lane >> 5) ^ ((lane >> 1) & 7)) * 16));
+    f32x16_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    int st = 0;
+#pragma unroll 1
+    for (int k = kb; k < ke; ++k) {
+        // The stage's loads have landed when at most the younger ones are in flight.  The first stages were filled weights
+        // first, so behind the A loads of stage i come (NST - 1 - i) stages of A loads and i whole stages.
+        if (k == kb) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * AL) : "memory");
+        else if (NST > 2 && k == kb + 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * AL + AL + BL) : "memory");
+        else if (NST > 3 && k == kb + 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NST > 3 ? (NST - 3) * AL + 2 * (AL + BL) : 0) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * (AL + BL)) : "memory");
+        const unsigned char* stage = my_ring + st * STAGE;
+        bf16x8_t fa[4][TM], fb[4][TN];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const unsigned char* p = stage + rd[ks];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[ks][i] = *reinterpret_cast<const bf16x8_t*>(p + i * 4096);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[ks][j] = *reinterpret_cast<const bf16x8_t*>(p + (BM + j * 32) * 128);
+        }
+        // The stage is refilled as soon as its fragments are in registers: NST stages stay in flight while the matrix
+        // pipe works (refilled one step later, a two-stage ring leaves the memory idle while a stage is read).
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        issue_a(st);
+        issue_b(st);
+        st = st == NST - 1 ? 0 : st + 1;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // the loads past the end of the range still target the ring
+    __syncthreads();
+    if constexpr (!AHEAD) fetch_operands();
+    float* const part = reinterpret_cast<float*>(ring);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4_w*>(&part[(wave * BM + i * 32 + (lane & 31)) * PITCH + j * 32 + q * 8 + (lane >> 5) * 4]) =
+                    f32x4_w{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    __syncthreads();
+    f32x4_w v[ITEMS], g[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) v[it] = g[it] = f32x4_w{0.f, 0.f, 0.f, 0.f};
+    if (trans) {
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float* p = &part[(w * BM + e_r[it]) * PITCH + e_c[it]];
+                v[it] += f32x4_w{p[0], p[PITCH], p[2 * PITCH], p[3 * PITCH]};
+            }
+    } else {
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float* p = &part[(w * BM + e_r[it]) * PITCH + e_c[it]];
+                v[it] += *reinterpret_cast<const f32x4_w*>(p);
+                if (GEGLU) g[it] += *reinterpret_cast<const f32x4_w*>(p + OW);
+            }
+    }
+    if (a.splits > 1) {
+        // park the tile (16 bytes per lane, written through to memory), count this workgroup; the last one goes on
+        constexpr int SLOT = (GEGLU ? 2 : 1) * BM * OW * 4;
+        const unsigned tile = (unsigned)(by * a.gx + bx), base = tile * a.splits;
+        const __amdgpu_buffer_rsrc_t s_part = buf(a.partial, (unsigned)IGEMM_PARTIAL_BYTES);
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const unsigned off = (base + bz) * SLOT + (unsigned)(it * NT + tid) * 16u;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_w, v[it]), s_part, off, 0, 17);
+            if (GEGLU) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_w, g[it]), s_part, off + BM * OW * 4, 0, 17);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        int* const flag = reinterpret_cast<int*>(ring + NW * BM * PITCH * 4 - 4);      // the last pad word of the partial tiles
+        if (tid == 0) {
+            const int old = __hip_atomic_fetch_add(a.counters + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (old == a.splits - 1) __hip_atomic_store(a.counters + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *flag = old;
+        }
+        __syncthreads();
+        if (*flag != a.splits - 1) return;
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) v[it] = g[it] = f32x4_w{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int z = 0; z < a.splits; ++z) {            // split order, whoever is last
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) {
+                const unsigned off = (base + z) * SLOT + (unsigned)(it * NT + tid) * 16u;
+                v[it] += __builtin_bit_cast(f32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_part, off, 0, 17));
+                if (GEGLU) g[it] += __builtin_bit_cast(f32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_part, off + BM * OW * 4, 0, 17));
+            }
+        }
+    }
+
+    // ---- epilogue: sum, biases, gate, then time projection + residual as one term; stores
+    bf16_t* const outp = sect == 0 ? a.out[0] : sect == 1 ? a.out[1] : a.out[2];
+    const int scol0 = col0 - sect * a.sect_n;
+    if (trans) {
+        const unsigned HW = (unsigned)(a.Ho * a.Wo);
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            if (!e_ok[it]) continue;
+            FISE_AS1 bf16_t* q = (FISE_AS1 bf16_t*)(outp + ((size_t)e_b[it] * a.sect_n + scol0 + e_c[it]) * HW + (e_pix[it] - (unsigned)e_b[it] * HW));
+            *(FISE_AS1 u32x2_w*)q = u32x2_w{f2bf2(v[it][0], v[it][1]), f2bf2(v[it][2], v[it][3])};
+        }
+        return;
+    }
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        float x[4] = {v[it][0] + lo16(e_bias[it][0]), v[it][1] + hi16(e_bias[it][0]), v[it][2] + lo16(e_bias[it][1]), v[it][3] + hi16(e_bias[it][1])};
+        if constexpr (GEGLU) {
+            x[0] *= gelu_f(g[it][0] + lo16(e_gate[it][0])); x[1] *= gelu_f(g[it][1] + hi16(e_gate[it][0]));
+            x[2] *= gelu_f(g[it][2] + lo16(e_gate[it][1])); x[3] *= gelu_f(g[it][3] + hi16(e_gate[it][1]));
+        } else {
+            const u32x4_w w = e_res[it];
+            f32x4_w r = a.res_compact == 2 ? __builtin_bit_cast(f32x4_w, w) : f32x4_w{lo16(w[0]), hi16(w[0]), lo16(w[1]), hi16(w[1])};
+            if constexpr (AM == A_MAP) {
+                x[0] += lo16(e_bias2[it][0]); x[1] += hi16(e_bias2[it][0]); x[2] += lo16(e_bias2[it][1]); x[3] += hi16(e_bias2[it][1]);
+                r += __builtin_bit_cast(f32x4_w, e_temb[it]);
+            }
+            x[0] += r[0]; x[1] += r[1]; x[2] += r[2]; x[3] += r[3];
+        }
+        if (!e_ok[it]) continue;
+        const int scol = scol0 + e_c[it];
+        const size_t gm = (size_t)(m0 + e_r[it]);
+        if (omode == OUT_TOKENS_T) {
+            const size_t HW = (size_t)a.Ho * a.Wo;
+            FISE_AS1 bf16_t* q = (FISE_AS1 bf16_t*)(outp + ((size_t)e_b[it] * a.sect_n + scol) * HW + (e_pix[it] - (unsigned)e_b[it] * (unsigned)HW));
+#pragma unroll
+            for (int t = 0; t < 4; ++t) q[t * HW] = f2bf(x[t]);
+            continue;
+        }
+        const u32x2_w packed = {f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
+        if (omode == OUT_COMPACT_F32) {
+            if (outp) *(FISE_AS1 f32x4_w*)(reinterpret_cast<float*>(outp) + gm * a.sect_n + scol) = f32x4_w{x[0], x[1], x[2], x[3]};
+            if (a.mirror) *(FISE_AS1 u32x2_w*)(a.mirror + gm * a.sect_n + scol) = packed;
+        } else if (omode == OUT_COMPACT) {
+            *(FISE_AS1 u32x2_w*)(outp + gm * a.sect_n + scol) = packed;
+        } else {
+            *(FISE_AS1 u32x2_w*)(outp + (size_t)e_pix[it] * a.sect_n + scol) = packed;
+            if (!GEGLU && a.nview) {
+                ViewSS ss;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) { ss.s[i][q] = __uint_as_float(e_ss[it][i][0][q]); ss.s[i][4 + q] = __uint_as_float(e_ss[it][i][1][q]); }
+                put_views4(a.view, a.nview, e_pix[it], scol, x, ss);
+            }
+        }
+    }
+#endif
+}
+
+__global__ void zero_ints_kernel(int* p, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) p[i] = 0;
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+static FastDiv fast_div(int d) {
+    FastDiv f{1u, 0};
+    while ((1ll << f.shift) < d) ++f.shift;
+    f.mul = (unsigned)((((unsigned long long)1 << 32) * (((unsigned long long)1 << f.shift) - (unsigned)d)) / (unsigned)d + 1);
+    return f;
+}
+
+// Derived fields of the argument block: divisors, operand sizes, what the epilogue addresses.
+static void prepare(IgemmArgs& a, int ncols) {
+    const int rows = a.B * a.Ma;
+    if (a.tile_w <= 0) a.tile_w = a.tile;
+    a.need_pix = a.res && a.res_compact == 0;
+    bool tokens_t = false;
+    for (int s = 0; s < a.nsect; ++s) { a.need_pix |= a.out_mode[s] == OUT_MAP || a.out_mode[s] == OUT_TOKENS_T; tokens_t |= a.out_mode[s] == OUT_TOKENS_T; }
+    // four consecutive rows are four consecutive pixels of a map row (or tokens) at an offset that is a multiple of 4
+    const bool runs = a.tile_idx ? a.tile_w % 4 == 0 && a.Wo % 4 == 0 : a.Ma % 4 == 0 && (a.Ho * a.Wo) % 4 == 0;
+    a.trans4 = tokens_t && runs && a.Ma % 4 == 0 && !a.bias && !a.bias2 && !a.temb && !a.res && !a.geglu;
+    a.tt = a.tile * a.tile_w;
+    a.d_gx = fast_div(a.gx); a.d_gy = fast_div(a.gy); a.d_Ma = fast_div(a.Ma); a.d_tt = fast_div(a.tt); a.d_tw = fast_div(a.tile_w);
+    a.d_tiles_w = fast_div(a.tiles_w); a.d_spt = fast_div((a.C0 + a.C1) / 64);
+    const unsigned n_in = a.a_compact ? (unsigned)rows : (unsigned)(a.B * a.Hin * a.Win), n_out = (unsigned)(a.B * a.Ho * a.Wo);
+    a.src[0].p = a.a0; a.src[0].pitch = 2u * a.C0; a.src[1].p = a.a1; a.src[1].pitch = 2u * a.C1;
+    a.src[2].p = a.s0; a.src[2].pitch = 2u * a.S0; a.src[3].p = a.s1; a.src[3].pitch = 2u * a.S1;
+    a.bias_bytes = a.bias ? 2u * ncols : 0u; a.bias2_bytes = a.bias2 ? 2u * a.N : 0u;
+    a.temb_bytes = a.temb ? 4u * ((a.B - 1) * a.temb_stride + a.N) : 0u;
+    a.res_bytes = !a.res ? 0u : (a.res_compact == 0 ? n_out : (unsigned)rows) * (unsigned)a.N * (a.res_compact == 2 ? 4u : 2u);
+    for (int i = 0; i < 4; ++i) a.src[i].bytes = (i < 2 ? n_in : n_out) * a.src[i].pitch;
+}
+
+template <int TM, int TN, int NST, int AM, bool GEGLU>
+static int launch_tile(const IgemmArgs& a, hipStream_t st) {
+    constexpr int NW = 4, lds = NW * NST * (32 * TM + 32 * TN) * 128;
+    // raised once per instantiation (initialisation of a function-local static is thread safe)
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return fail(FISE_ERR_HIP, "wave gemm: cannot raise the dynamic LDS limit");
+    const double rows = (double)a.B * a.Ma, ncols = a.geglu ? 2.0 * a.N : a.N, K = (double)a.K + a.K2;
+    {
+        ProfileScope prof(GEGLU ? PROF_IGEMM_GEGLU : AM == A_MAP ? PROF_IGEMM : PROF_ROWS_GEMM, 2.0 * rows * ncols * K, 2.0 * (ncols * K + rows * (a.C0 + a.C1 + a.S0 + a.S1) + rows * a.N), st);
+        hipLaunchKernelGGL((wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU>), dim3((unsigned)(a.gx * a.gy * a.splits)), dim3(64 * NW), lds, st, a);
+    }
+    FISE_CHECK_LAUNCH("wave gemm");
+    return FISE_OK;
+}
+
+bool wave_gemm_fits(const IgemmArgs& a) {
+    const int rows = a.B * a.Ma;
+    constexpr size_t kLim = (size_t)1 << 31;            // 32-bit buffer offsets, top bit reserved for "no such row"
+    if (a.pro != PRO_NONE || a.C0 % 64 || a.C1 % 64 || a.S0 % 64 || a.S1 % 64 || a.N % 4) return false;
+    if (a.nsect > 1 && a.sect_n % 64) return false;     // a column tile has one destination
+    if (a.geglu && (!a.a_compact || a.nsect != 1 || a.temb || a.res || a.nview || a.bias2)) return false;
+    if (!a.a_compact && !a.tile_idx) return false;
+    const size_t npix_in = a.a_compact ? (size_t)rows : (size_t)a.B * a.Hin * a.Win, npix_out = (size_t)a.B * a.Ho * a.Wo;
+    const size_t ncols = a.geglu ? 2 * (size_t)a.N : (size_t)a.N;
+    if (npix_in >= 1u << 24 || npix_out >= 1u << 24 || rows >= 1 << 24) return false;   // 24-bit multiplies
+    if (a.a_compact && (a.temb || a.bias2)) return false;      // epilogue terms of the convolutions only
+    return npix_in * std::max(a.C0, a.C1) * 2 < kLim && npix_out * std::max({a.S0, a.S1, a.N}) * 2 < kLim &&
+           ncols * std::max(a.K, a.K2) * 2 < kLim && (size_t)rows * a.N * 4 < kLim;
+}
+
+// Tile and K split of a launch: the cheapest of the combinations under the times measured per part of a launch (us, from
+// time stamps inside the kernel over the shapes of a step).  `fixed`: start, row positions, first loads, sum over the
+// waves, epilogue, and the gap to the launch before.  `iter`: one K step of all four waves (its operands at the 85 GB/s
+// a CU reaches here).  A K split over workgroups adds parking, counting and re-reading the tiles.  256 workgroups run at
+// once: the rings take most of a CU's LDS.
+int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
+    const int rows = a.B * a.Ma, ncols = a.geglu ? 2 * a.N : a.N, nsteps = (a.K + a.K2) / 64;
+    int best_tm = 1, best_tn = 1, best_s = 1; double best = 1e30;
+    const int max_s = ws && ws->counters && ws->partial ? 8 : 1;
+    struct { int tm, tn; double fixed, iter, park; } shapes[] = {{1, 1, 4.3, 0.39, 2.0}, {1, 2, 4.8, 0.56, 2.3}, {2, 2, 5.8, 0.92, 3.2}};
+    for (const auto& sh : shapes) {
+        if (a.geglu && sh.tn == 1) continue;
+        const int gx = ceil_div(rows, 32 * sh.tm), gy = ceil_div(ncols, 32 * sh.tn);
+        for (int s = 1; s <= max_s; ++s) {
+            const int per = ceil_div(nsteps, s);
+            if (s > 1 && (per < 4 || ceil_div(nsteps, per) != s)) continue;
+            if (s > 1 && (gx * gy > IGEMM_COUNTERS || (size_t)gx * gy * s * 32 * sh.tm * 32 * sh.tn * 4 > ws->partial_bytes)) break;
+            const double t = ceil_div(gx * gy * s, 256) * (sh.fixed + ceil_div(per, 4) * sh.iter) + (s > 1 ? sh.park + 0.15 * s * sh.tm * sh.tn : 0.0);
+            if (t < best) { best = t; best_tm = sh.tm; best_tn = sh.tn; best_s = s; }
+        }
+    }
+    a.splits = best_s; a.kper = ceil_div(nsteps, best_s);
+    a.gx = ceil_div(rows, 32 * best_tm); a.gy = ceil_div(ncols, 32 * best_tn);
+    prepare(a, ncols);
+    if (a.splits > 1) {
+        a.partial = ws->partial; a.counters = ws->counters;
+        if (!ws->counters_zeroed) {                     // once per call: every launch leaves its counters at zero
+            hipLaunchKernelGGL(zero_ints_kernel, dim3(ceil_div(IGEMM_COUNTERS, 256)), dim3(256), 0, st, ws->counters, IGEMM_COUNTERS);
+            FISE_CHECK_LAUNCH("zero counters");
+            ws->counters_zeroed = true;
+        }
+    }
+    int e;
+    if (a.geglu) e = best_tm == 1 ? launch_tile<1, 2, 2, A_ROWS, true>(a, st) : launch_tile<2, 2, 2, A_ROWS, true>(a, st);
+    else if (a.a_compact)
+        e = best_tm == 2 ? launch_tile<2, 2, 2, A_ROWS, false>(a, st) : best_tn == 2 ? launch_tile<1, 2, 2, A_ROWS, false>(a, st) : launch_tile<1, 1, 2, A_ROWS, false>(a, st);
+    else
+        e = best_tm == 2 ? launch_tile<2, 2, 2, A_MAP, false>(a, st) : best_tn == 2 ? launch_tile<1, 2, 2, A_MAP, false>(a, st) : launch_tile<1, 1, 2, A_MAP, false>(a, st);
+    if (e) return e;
+    if (a.ln_out) {
+        if (a.nsect != 1 || a.out_mode[0] != OUT_COMPACT_F32 || a.geglu || !a.ln_gamma || !a.ln_beta)
+            return fail(FISE_ERR_SHAPE, "igemm: LayerNorm output needs one float compact section");
+        return launch_ln_rows(a.out[0], 1, rows, a.N, a.ln_gamma, a.ln_beta, a.ln_eps, a.ln_out, nullptr, 1, 1, 1, 1, 1, st);
+    }
+    return FISE_OK;
+}
+
+}  // namespace fise

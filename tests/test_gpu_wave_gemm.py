@@ -1,0 +1,64 @@
+"""GPU parity of the wave-split gathered GEMM at the sizes where its tiles, K shares and splits can go wrong, against the oracle's
+masked convolution."""
+import math
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import fise_oracle as fo
+from paper_2305_17423_amd import workloads as wl
+from helpers import DEV, TOL, dev, host, idx_dev, active_mask, check_map
+
+pytestmark = pytest.mark.gpu
+DT = "bf16"
+
+
+@pytest.fixture(scope="module")
+def fb():
+    from paper_2305_17423_amd import binding
+    binding.lib()
+    assert torch.cuda.is_available()
+    return binding
+
+
+CASES = [
+    # name, B, H(out), W(out), C0, C1, Cout, k, stride, ups, tile, tiles, temb, res
+    ("one-row-one-step", 1, 8, 8, 64, 0, 4, 1, 1, 0, 1, 1, False, False),              # three of four waves without work
+    ("32-rows-exact", 2, 8, 8, 64, 64, 32, 1, 1, 0, 4, 1, False, True),
+    ("33-rows-ragged-columns", 1, 8, 8, 192, 0, 68, 3, 1, 0, 1, 33, True, True),
+    ("source-change-inside-a-share", 2, 8, 8, 64, 128, 96, 3, 1, 0, 2, 5, False, False),
+    ("uneven-shares", 1, 8, 8, 320, 0, 64, 1, 1, 0, 2, 3, False, True),                # 5 steps: shares of 2, 2, 1, 0
+    ("split-over-workgroups", 2, 8, 8, 640, 0, 36, 3, 1, 0, 2, 2, True, True),
+    ("split-stride-2", 1, 8, 8, 320, 320, 64, 3, 2, 0, 4, 2, False, False),
+    ("split-upsample", 1, 16, 16, 640, 0, 64, 3, 1, 1, 4, 3, False, False),
+    ("many-row-tiles-long-k", 1, 32, 32, 320, 0, 64, 3, 1, 0, 4, 39, True, False),     # row tiles fetch the weight slice together
+    ("64-row-tiles", 2, 64, 32, 128, 0, 324, 1, 1, 0, 8, 31, False, True),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_wave_gemm_edges(fb, case):
+    name, B, Ho, Wo, C0, C1, Co, k, stride, ups, t, n, use_temb, use_res = case
+    rng = np.random.default_rng(zlib.crc32(name.encode()))
+    H, W = (Ho // 2, Wo // 2) if ups else (Ho * stride, Wo * stride)
+    x0 = wl.normal(rng, (B, H, W, C0), 1.0, DT)
+    x1 = wl.normal(rng, (B, H, W, C1), 1.0, DT) if C1 else None
+    w = wl.normal(rng, (Co, k, k, C0 + C1), 1 / math.sqrt(k * k * (C0 + C1)), DT)
+    bias = wl.normal(rng, (Co,), 0.1, DT)
+    temb = wl.normal(rng, (B, Co), 0.3) if use_temb else None
+    res = wl.normal(rng, (B, Ho, Wo, Co), 1.0, DT) if use_res else None
+    cache = wl.normal(rng, (B, Ho, Wo, Co), 1.0, DT)
+    ix = np.sort(rng.choice((Ho // t) * (Wo // t), n, replace=False)).astype(np.int32)
+    want = fo.masked_conv([x0, x1] if C1 else x0, w, bias, ix, t, cache.astype(np.float64).copy(), DT, stride=stride, upsample=bool(ups),
+                          temb=temb, residual=res)
+    y, xd, x1d, wd, bd, ixd = dev(cache, DT), dev(x0, DT), dev(x1, DT) if C1 else None, dev(w, DT), dev(bias, DT), idx_dev(ix)
+    tembd, resd = dev(temb) if use_temb else None, dev(res, DT) if use_res else None
+    a = fb.conv_args(xd, wd, bd, ixd, n, t, y, x1=x1d, ksize=k, stride=stride, upsample=ups, temb=tembd, residual=resd)
+    ws = torch.full((fb.fise_masked_conv_workspace_bytes(a),), 0xA5, dtype=torch.uint8, device=DEV)
+    fb.fise_masked_conv(a, ws)
+    got = host(y)
+    check_map(got, want, cache.astype(np.float64), active_mask(ix, t, Ho, Wo), TOL[DT], name)
+    fb.fise_masked_conv(a, ws)                       # arrival counters are back at zero, the sum does not depend on who came last
+    assert np.array_equal(host(y), got)
