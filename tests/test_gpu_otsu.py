@@ -1,0 +1,40 @@
+"""GPU parity of the Otsu threshold at the sizes where its chunks and bins can go wrong: counts and sums of every bin bit for bit
+in index order, threshold and mask against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fise_oracle as fo
+from helpers import DEV, dev
+
+pytestmark = pytest.mark.gpu
+BINS = 257
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 1023, 1024, 1025, 4096, 9216])
+@pytest.mark.parametrize("shape", ["uniform", "one-bin-and-one", "two-clusters"])
+def test_otsu_bins_in_index_order(n, shape):
+    from paper_2305_17423_amd import binding as fb
+    rng = np.random.default_rng(n)
+    if shape == "uniform":
+        d = rng.random(n)
+    elif shape == "one-bin-and-one":                    # all but one value in the lowest bin: one chain of n additions
+        d = rng.random(n) * 1e-3
+        d[n // 2] = 1.0
+    else:
+        d = np.where(rng.random(n) < 0.3, 0.8, 0.1) + 0.05 * rng.random(n)
+    d = d.astype(np.float32)
+    eps, pix = torch.full((1,), -1.0, device=DEV), torch.full((n,), 7, dtype=torch.uint8, device=DEV)
+    ws = torch.full((fb.fise_otsu_workspace_bytes(),), 0xA5, dtype=torch.uint8, device=DEV)
+    fb.fise_otsu_mask(dev(d), eps, pix, ws)
+    v = fo.normalize_minmax(d.astype(np.float64))
+    cnt, tot = np.zeros(BINS), np.zeros(BINS)
+    for x in v:
+        k = int(np.floor(x * 256.0))
+        cnt[k] += 1.0
+        tot[k] += x
+    got = ws.cpu().numpy()[:8 * (2 + 2 * BINS)].view(np.float64)
+    assert np.array_equal(got[2:2 + BINS], cnt) and np.array_equal(got[2 + BINS:], tot)
+    want, mask = fo.otsu_threshold(v)
+    assert float(eps.item()) == np.float32(want)
+    assert np.array_equal(pix.cpu().numpy(), mask.reshape(-1).astype(np.uint8))
