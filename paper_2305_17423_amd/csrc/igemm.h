@@ -130,7 +130,7 @@ __device__ __forceinline__ void put_views1(const GnView* view, int nview, int b,
 constexpr int IGEMM_COUNTERS = 4096;     // arrival counters of split output tiles (zeroed once per call, left at zero by every launch)
 constexpr size_t IGEMM_PARTIAL_BYTES = (32u << 20) - IGEMM_COUNTERS * sizeof(int);
 struct IgemmWorkspace { float* partial; size_t partial_bytes; int* counters; mutable bool counters_zeroed; };
-bool wave_gemm_fits(const IgemmArgs& a);
+bool wave_gemm_takes(const IgemmArgs& a);
 int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st);
 size_t igemm_workspace_bytes();
 // Carves the scratch out of `workspace`; with a null or too

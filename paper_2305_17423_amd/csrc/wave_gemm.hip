@@ -52,18 +52,22 @@ __device__ __forceinline__ float gelu_f(float x) {
 }
 #endif
 
-template <int TM, int TN, int NW, int NST, int AM, bool GEGLU>
+// SHARED: one ring for the workgroup instead of one per wave, see the block tile below.
+template <int TM, int TN, int NW, int NST, int AM, bool GEGLU, bool SHARED>
 __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 32 * TM, BN = 32 * TN, NT = 64 * NW;
-    constexpr int AL = BM / 8, BL = BN / 8;             // 16-byte loads per lane and K step (one load fills 8 rows of 128 bytes)
+    constexpr int RB = SHARED ? 8 * NW : 8;             // rows between two loads of a lane (one load of a wave fills 8 rows of 128 bytes)
+    constexpr int AL = BM / RB, BL = BN / RB;           // 16-byte loads per lane and K step
     constexpr int STAGE = (BM + BN) * 128;
     constexpr int PITCH = BN + 4;                       // floats per row of a partial tile in LDS
     constexpr int OW = GEGLU ? BN / 2 : BN;             // output columns of the tile
-    constexpr int CPR = OW / 4, ITEMS = BM * CPR / NT;  // four-column pieces per row, per thread
+    constexpr int GROUPS = SHARED ? TM : 1, GROWS = BM / GROUPS;       // the waves' sums are finished in groups of rows: what fits in the ring
+    constexpr int CPR = OW / 4, IPG = GROWS * CPR / NT, ITEMS = GROUPS * IPG;      // four-column pieces per row, per thread and group, per thread
     constexpr unsigned OOB = 0x80000000u;               // beyond every descriptor: the load returns zeros
-    static_assert(BM * CPR % NT == 0 && NW * NST * STAGE >= NW * BM * PITCH * 4, "tile");
-    extern __shared__ __attribute__((aligned(16))) unsigned char ring[];      // [NW][NST][STAGE], later [NW][BM][PITCH] floats
+    static_assert(GROWS * CPR % NT == 0 && (SHARED ? 1 : NW) * NST * STAGE >= NW * GROWS * PITCH * 4, "tile");
+    static_assert(!SHARED || (NW == 4 && NST >= 3 && !GEGLU), "a shared stage has one 16-deep slice of K per wave");
+    extern __shared__ __attribute__((aligned(16))) unsigned char ring[];      // [NW or 1][NST][STAGE], later [NW][GROWS][PITCH] floats
 
     // Kernel arguments arrive through scalar loads placed where a field is first used; named here they come as one batch.
     asm volatile("" ::"s"(a.gx), "s"(a.gy), "s"(a.splits), "s"(a.kper), "s"(a.d_gx.mul), "s"(a.d_gy.mul), "s"(a.d_Ma.mul), "s"(a.d_tt.mul),
@@ -88,7 +92,7 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
     int kb, ke;                                         // K steps of this wave
     {
         const int c0 = bz * a.kper, c1 = min(nsteps, c0 + a.kper), per = (c1 - c0 + NW - 1) / NW;
-        kb = min(c1, c0 + wave * per); ke = min(c1, kb + per);
+        kb = SHARED ? c0 : min(c1, c0 + wave * per); ke = SHARED ? c1 : min(c1, kb + per);
     }
 
     // ---- Every lane works out one row of the tile (row lane % BM); whoever needs a row's position gets it by a lane
@@ -107,21 +111,22 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
     // ---- weights: first stages.  LDS slot p of row r holds segment p ^ ((r >> 1) & 7) (conflict-free operand reads); a load
     // fills 8 rows, so between odd and even loads only bit 2 of the segment flips.
     const unsigned wrows = (unsigned)(GEGLU ? 2 * a.N : a.N);
-    const unsigned seg0 = (unsigned)(((lane & 7) ^ (lr >> 1)) * 16);
+    const int lrow = SHARED ? wave * 8 + lr : lr;       // this lane's row of a load
+    const unsigned seg0 = (unsigned)(((lane & 7) ^ ((lrow >> 1) & 7)) * 16), seg1 = SHARED ? seg0 : seg0 ^ 64u;
     unsigned vb[BL], soff_b, bytes_b;
     const bf16_t* ptr_b;
     auto set_weights = [&](bool side, int kstep) {
         const unsigned pitch = (unsigned)(side ? a.K2 : a.K) * 2u;
         ptr_b = side ? a.w2 : a.w; bytes_b = __umul24(wrows, pitch); soff_b = (unsigned)kstep * 128u;
-        const unsigned row0 = __umul24((unsigned)(by * (GEGLU ? OW : BN) + lr), pitch);
+        const unsigned row0 = __umul24((unsigned)(by * (GEGLU ? OW : BN) + lrow), pitch);
 #pragma unroll
         for (int j = 0; j < BL; ++j) {                  // GEGLU: value rows, then the gate rows N further down
-            unsigned jr = j * 8u;
+            unsigned jr = (unsigned)(j * RB);
             if (GEGLU && j >= BL / 2) jr += (unsigned)(a.N - OW);
-            vb[j] = row0 + (j & 1 ? seg0 ^ 64u : seg0) + jr * pitch;      // rows past the matrix lie past the descriptor
+            vb[j] = row0 + (j & 1 ? seg1 : seg0) + jr * pitch;      // rows past the matrix lie past the descriptor
         }
     };
-    unsigned char* const my_ring = ring + wave * (NST * STAGE);
+    unsigned char* const my_ring = ring + wave * (SHARED ? 1024 : NST * STAGE);      // where this wave's loads go
     int kw = kb;                                        // weight cursor
     set_weights(kb >= nsteps1, kb >= nsteps1 ? kb - nsteps1 : kb);
     auto issue_b = [&](int st) {                        // steps past the range: a descriptor of size zero, no traffic
@@ -129,7 +134,7 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
         unsigned char* base = my_ring + st * STAGE + BM * 128;
 #pragma unroll
         for (int j = 0; j < BL; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + j * 1024), 16, vb[j], soff_b, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + j * (RB * 128)), 16, vb[j], soff_b, 0, 0);
         ++kw; soff_b += 128u;
         if (AM == A_MAP && kw == nsteps1 && kw < ke) set_weights(true, 0);
     };
@@ -139,12 +144,20 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
     // 1536 x 320 x 2880: K loop 6.4 -> 5.0 us; short K ranges do not earn it back.
     if (a.gx >= 12 && a.kper >= 32) {
         const int c0 = bz * a.kper, c1 = min(nsteps1, c0 + a.kper);
-        const int half = BN == 32 ? lane >> 5 : 0;
         const __amdgpu_buffer_rsrc_t rs = buf(a.w, bytes_b);
+        if constexpr (SHARED) {
+            for (int q = c0 + bx * NW + wave; q < c1; q += a.gx * NW)
+#pragma unroll
+                for (int r = 0; r < BN; r += 64)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)my_ring, 4,
+                                                             r + lane < BN ? __umul24((unsigned)(by * BN + r + lane), (unsigned)a.K * 2u) + q * 128 : OOB, 0, 0, 0);
+        } else {
+        const int half = BN == 32 ? lane >> 5 : 0;
         const unsigned off = __umul24((unsigned)(by * (GEGLU ? OW : BN) + (lane & (BN - 1)) + (GEGLU && lane >= OW ? a.N - OW : 0)), (unsigned)a.K * 2u);
         constexpr int PER = BN == 32 ? 2 : 1;
         for (int q = c0 + (bx * NW + wave) * PER; q < c1; q += a.gx * NW * PER)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(ring + wave * (NST * STAGE)), 4, off + (q + half) * 128, 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)my_ring, 4, off + (q + half) * 128, 0, 0, 0);
+        }
     }
 #pragma unroll
     for (int s = 0; s < NST; ++s) issue_b(s);
@@ -165,33 +178,35 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
     const int omode = sect == 0 ? a.out_mode[0] : sect == 1 ? a.out_mode[1] : a.out_mode[2];
     const bool trans = omode == OUT_TOKENS_T && a.trans4;
     int e_r[ITEMS], e_c[ITEMS], e_b[ITEMS]; unsigned e_pix[ITEMS]; bool e_ok[ITEMS];
+    auto place_items = [&]() {
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
-        const int item = tid + it * NT;
-        e_r[it] = trans ? (item % (BM / 4)) * 4 : item / CPR;
-        e_c[it] = trans ? item / (BM / 4) : (item % CPR) * 4;
+        const int item = tid + it % IPG * NT, g0 = it / IPG * GROWS;
+        e_r[it] = g0 + (trans ? (item % (GROWS / 4)) * 4 : item / CPR);
+        e_c[it] = trans ? item / (GROWS / 4) : (item % CPR) * 4;
         e_ok[it] = m0 + e_r[it] < rows && col0 + e_c[it] < a.N;
         e_b[it] = __shfl((int)rb, e_r[it]);
         e_pix[it] = (unsigned)__shfl((int)rpix, e_r[it]);
     }
-    constexpr bool AHEAD = ITEMS <= 2;                  // more pieces per thread: fetched after the K loop, all together
-    u32x2_w e_bias[ITEMS], e_bias2[ITEMS], e_gate[ITEMS]; u32x4_w e_temb[ITEMS], e_res[ITEMS], e_ss[ITEMS][2][2];
-    auto fetch_operands = [&]() {                       // an absent operand has a descriptor of size zero: no branches, no waits
+    };
+    constexpr bool AHEAD = ITEMS <= 2;                  // more pieces per thread: placed and fetched after the K loop, all together
+    u32x2_w e_bias[IPG], e_bias2[IPG], e_gate[IPG]; u32x4_w e_temb[IPG], e_res[IPG], e_ss[IPG][2][2];
+    auto fetch_operands = [&](int grp) {                       // an absent operand has a descriptor of size zero: no branches, no waits
         const __amdgpu_buffer_rsrc_t s_bias = buf(a.bias, a.bias_bytes), s_bias2 = buf(a.bias2, a.bias2_bytes),
                                      s_temb = buf(a.temb, a.temb_bytes), s_res = buf(a.res, a.res_bytes);
         const int res_shift = a.res_compact == 2 ? 2 : 1;       // float rows / bf16 (16 bytes are fetched either way, 8 of them used)
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it) {
-            const unsigned no = e_ok[it] && !trans ? 0u : OOB, col = (unsigned)(col0 + e_c[it]);
+        for (int it = 0; it < IPG; ++it) {
+            const unsigned no = e_ok[grp * IPG + it] && !trans ? 0u : OOB, col = (unsigned)(col0 + e_c[grp * IPG + it]);
             e_bias[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, (col * 2u) | no, 0, 0));
             if constexpr (GEGLU) {
                 e_gate[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, ((col + a.N) * 2u) | no, 0, 0));
             } else {
-                const unsigned r = __umul24(a.res_compact ? (unsigned)(m0 + e_r[it]) : e_pix[it], (unsigned)a.N) + col;
+                const unsigned r = __umul24(a.res_compact ? (unsigned)(m0 + e_r[grp * IPG + it]) : e_pix[grp * IPG + it], (unsigned)a.N) + col;
                 e_res[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_res, (r << res_shift) | no, 0, 0));
                 if constexpr (AM == A_MAP) {
                     e_bias2[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias2, (col * 2u) | no, 0, 0));
-                    e_temb[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_temb, ((__umul24((unsigned)e_b[it], (unsigned)a.temb_stride) + col) * 4u) | no, 0, 0));
+                    e_temb[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_temb, ((__umul24((unsigned)e_b[grp * IPG + it], (unsigned)a.temb_stride) + col) * 4u) | no, 0, 0));
                 }
             }
         }
@@ -201,15 +216,15 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
                 if (v < a.nview) {
                     const __amdgpu_buffer_rsrc_t s = buf(a.view[v].ss, (unsigned)a.B * a.view[v].dstC * 8u);
 #pragma unroll
-                    for (int it = 0; it < ITEMS; ++it) {
-                        const unsigned no = e_ok[it] && !trans ? 0u : OOB;
-                        const unsigned off = ((__umul24((unsigned)e_b[it], (unsigned)a.view[v].dstC) + a.view[v].c_off + col0 + e_c[it]) * 8u) | no;
+                    for (int it = 0; it < IPG; ++it) {
+                        const unsigned no = e_ok[grp * IPG + it] && !trans ? 0u : OOB;
+                        const unsigned off = ((__umul24((unsigned)e_b[grp * IPG + it], (unsigned)a.view[v].dstC) + a.view[v].c_off + col0 + e_c[grp * IPG + it]) * 8u) | no;
                         e_ss[it][v][0] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s, off, 0, 0));
                         e_ss[it][v][1] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s, off, 16, 0));
                     }
                 }
     };
-    if constexpr (AHEAD) fetch_operands();
+    if constexpr (AHEAD) { place_items(); fetch_operands(0); }
 
     // ---- A operand
     unsigned va[AL], soff_a, bytes_a = a.src[0].bytes;
@@ -219,9 +234,9 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
     unsigned in0[AL], valid[AL], out0[AL];              // pixel under tap (0, 0) (wraps at the border), taps inside the image | parities << 16; output pixel
     if constexpr (AM == A_ROWS) {
         soff_a = (unsigned)kb * 128u;
-        const unsigned row0 = (unsigned)(m0 + lr) * a.src[0].pitch;
+        const unsigned row0 = (unsigned)(m0 + lrow) * a.src[0].pitch;
 #pragma unroll
-        for (int j = 0; j < AL; ++j) va[j] = row0 + (j & 1 ? seg0 ^ 64u : seg0) + (unsigned)(j * 8) * a.src[0].pitch;     // past the last row: past the descriptor
+        for (int j = 0; j < AL; ++j) va[j] = row0 + (j & 1 ? seg1 : seg0) + (unsigned)(j * RB) * a.src[0].pitch;     // past the last row: past the descriptor
     }
     auto set_source = [&]() {                           // base and offsets of the cursor position
         si = __builtin_amdgcn_readfirstlane(si);
@@ -230,7 +245,7 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
         soff_a = (unsigned)cc * 2u; cn = (int)(pitch >> 1);
         if (si >= 2) {                                  // side product: the output pixel itself
 #pragma unroll
-            for (int j = 0; j < AL; ++j) va[j] = (__umul24(out0[j], pitch) + (j & 1 ? seg0 ^ 64u : seg0)) | (out0[j] & OOB);
+            for (int j = 0; j < AL; ++j) va[j] = (__umul24(out0[j], pitch) + (j & 1 ? seg1 : seg0)) | (out0[j] & OOB);
             return;
         }
         const int ky = a.ksize == 1 ? 0 : (tap * 11) >> 5, kx = tap - ky * a.ksize;
@@ -244,7 +259,7 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
             for (int j = 0; j < AL; ++j) px[j] = in0[j] + delta;
         }
 #pragma unroll
-        for (int j = 0; j < AL; ++j) va[j] = (__umul24(px[j], pitch) + (j & 1 ? seg0 ^ 64u : seg0)) | ((~valid[j] >> tap) << 31);
+        for (int j = 0; j < AL; ++j) va[j] = (__umul24(px[j], pitch) + (j & 1 ? seg1 : seg0)) | ((~valid[j] >> tap) << 31);
     };
     if constexpr (AM == A_MAP) {
         // pixel under tap (0, 0) and which taps lie inside the image, worked out for this lane's row, then dealt out
@@ -261,9 +276,9 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
         const unsigned o0 = my_row < rows ? rpix : OOB;
 #pragma unroll
         for (int j = 0; j < AL; ++j) {
-            in0[j] = (unsigned)__shfl((int)p0, j * 8 + lr);
-            valid[j] = (unsigned)__shfl((int)v, j * 8 + lr);
-            out0[j] = (unsigned)__shfl((int)o0, j * 8 + lr);
+            in0[j] = (unsigned)__shfl((int)p0, j * RB + lrow);
+            valid[j] = (unsigned)__shfl((int)v, j * RB + lrow);
+            out0[j] = (unsigned)__shfl((int)o0, j * RB + lrow);
         }
         const int Cin = a.C0 + a.C1;
         if (kb < nsteps1) {
@@ -280,7 +295,7 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
         unsigned char* base = my_ring + st * STAGE;
 #pragma unroll
         for (int j = 0; j < AL; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + j * 1024), 16, va[j], soff_a, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + j * (RB * 128)), 16, va[j], soff_a, 0, 0);
         ++ka; soff_a += 128u;
         if constexpr (AM == A_MAP) {
             cc += 64;
@@ -299,6 +314,7 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
     // ---- K loop.  The accumulators hold the transposed product (lane = row, four consecutive columns per register group).
     // One copy of the body with a rotating stage offset: the launch is short, so the code it has to fetch counts.
     unsigned rd[4];                                     // LDS offset of this lane's operand fragments within 32 rows of a stage
+    const unsigned rd_own = (unsigned)((lane & 31) * 128 + (((wave * 2) ^ (lane >> 5) ^ ((lane >> 1) & 7)) * 16));     // SHARED: this wave's slice of K
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) rd[ks] = (unsigned)((lane & 31) * 128 + (((ks * 2) ^ (lane >> 5) ^ ((lane >> 1) & 7)) * 16));
     f32x16_t acc[TM][TN];
@@ -309,6 +325,44 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
     int st = 0;
+    if constexpr (SHARED) {
+        // Step k: the fragments of step k + 1 are requested behind the barrier that says its stage has landed for all
+        // waves, the stage of step k (in registers everywhere by then) is refilled, and the matrix pipe works on step k.
+        bf16x8_t f0[TM + TN], f1[TM + TN];
+        auto read = [&](bf16x8_t (&f)[TM + TN], int slot) {
+            const unsigned char* p = ring + slot * STAGE + rd_own;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) f[i] = *reinterpret_cast<const bf16x8_t*>(p + i * 4096);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) f[TM + j] = *reinterpret_cast<const bf16x8_t*>(p + (BM + j * 32) * 128);
+        };
+        auto step = [&](bf16x8_t (&cur)[TM + TN], bf16x8_t (&next)[TM + TN], int k) {
+            const int after = st == NST - 1 ? 0 : st + 1;
+            // the first NST stages were filled weights first: behind the A loads of stage i come (NST - 1 - i) stages of A loads
+            if (k == kb) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NST - 2) * AL) : "memory");
+            else if (NST > 3 && k == kb + 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NST > 3 ? (NST - 3) * AL + AL + BL : 0) : "memory");
+            else if (NST > 4 && k == kb + 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NST > 4 ? (NST - 4) * AL + 2 * (AL + BL) : 0) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NST - 2) * (AL + BL)) : "memory");
+            read(next, after);                          // past the range: zeros (loads through a descriptor of size zero)
+            issue_a(st);
+            issue_b(st);
+            st = after;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur[TM + j], cur[i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NST - 1) * AL) : "memory");
+        read(f0, 0);
+#pragma unroll 1
+        for (int k = kb; k < ke; k += 2) {              // always in pairs (an exit between the two costs copies of all
+            step(f0, f1, k);                            // accumulators): a stage past the range holds zeros
+            step(f1, f0, k + 1);
+        }
+    } else
 #pragma unroll 1
     for (int k = kb; k < ke; ++k) {
         // The stage's loads have landed when at most the younger ones are in flight.  The first stages were filled weights
@@ -345,37 +399,43 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // the loads past the end of the range still target the ring
     __syncthreads();
-    if constexpr (!AHEAD) fetch_operands();
+    if constexpr (!AHEAD) { place_items(); fetch_operands(0); }
     float* const part = reinterpret_cast<float*>(ring);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<f32x4_w*>(&part[(wave * BM + i * 32 + (lane & 31)) * PITCH + j * 32 + q * 8 + (lane >> 5) * 4]) =
-                    f32x4_w{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-    __syncthreads();
     f32x4_w v[ITEMS], g[ITEMS];
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) v[it] = g[it] = f32x4_w{0.f, 0.f, 0.f, 0.f};
-    if (trans) {
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it)
+    for (int grp = 0; grp < GROUPS; ++grp) {
+        if (grp) __syncthreads();
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const float* p = &part[(w * BM + e_r[it]) * PITCH + e_c[it]];
-                v[it] += f32x4_w{p[0], p[PITCH], p[2 * PITCH], p[3 * PITCH]};
-            }
-    } else {
+        for (int i = 0; i < TM / GROUPS; ++i)
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it)
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const float* p = &part[(w * BM + e_r[it]) * PITCH + e_c[it]];
-                v[it] += *reinterpret_cast<const f32x4_w*>(p);
-                if (GEGLU) g[it] += *reinterpret_cast<const f32x4_w*>(p + OW);
-            }
+                for (int q = 0; q < 4; ++q) {
+                    const f32x16_t& c = acc[grp * (TM / GROUPS) + i][j];
+                    *reinterpret_cast<f32x4_w*>(&part[(wave * GROWS + i * 32 + (lane & 31)) * PITCH + j * 32 + q * 8 + (lane >> 5) * 4]) =
+                        f32x4_w{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+                }
+        __syncthreads();
+        if (trans) {
+#pragma unroll
+            for (int it = grp * IPG; it < (grp + 1) * IPG; ++it)
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    const float* p = &part[(w * GROWS + e_r[it] - grp * GROWS) * PITCH + e_c[it]];
+                    v[it] += f32x4_w{p[0], p[PITCH], p[2 * PITCH], p[3 * PITCH]};
+                }
+        } else {
+#pragma unroll
+            for (int it = grp * IPG; it < (grp + 1) * IPG; ++it)
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    const float* p = &part[(w * GROWS + e_r[it] - grp * GROWS) * PITCH + e_c[it]];
+                    v[it] += *reinterpret_cast<const f32x4_w*>(p);
+                    if (GEGLU) g[it] += *reinterpret_cast<const f32x4_w*>(p + OW);
+                }
+        }
     }
     if (a.splits > 1) {
         // park the tile (16 bytes per lane, written through to memory), count this workgroup; the last one goes on
@@ -390,7 +450,7 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        int* const flag = reinterpret_cast<int*>(ring + NW * BM * PITCH * 4 - 4);      // the last pad word of the partial tiles
+        int* const flag = reinterpret_cast<int*>(ring + NW * GROWS * PITCH * 4 - 4);      // the last pad word of the partial tiles
         if (tid == 0) {
             const int old = __hip_atomic_fetch_add(a.counters + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (old == a.splits - 1) __hip_atomic_store(a.counters + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -426,16 +486,18 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
     }
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
-        float x[4] = {v[it][0] + lo16(e_bias[it][0]), v[it][1] + hi16(e_bias[it][0]), v[it][2] + lo16(e_bias[it][1]), v[it][3] + hi16(e_bias[it][1])};
+        const int gi = it % IPG;
+        if (GROUPS > 1 && it && gi == 0) fetch_operands(it / IPG);
+        float x[4] = {v[it][0] + lo16(e_bias[gi][0]), v[it][1] + hi16(e_bias[gi][0]), v[it][2] + lo16(e_bias[gi][1]), v[it][3] + hi16(e_bias[gi][1])};
         if constexpr (GEGLU) {
-            x[0] *= gelu_f(g[it][0] + lo16(e_gate[it][0])); x[1] *= gelu_f(g[it][1] + hi16(e_gate[it][0]));
-            x[2] *= gelu_f(g[it][2] + lo16(e_gate[it][1])); x[3] *= gelu_f(g[it][3] + hi16(e_gate[it][1]));
+            x[0] *= gelu_f(g[it][0] + lo16(e_gate[gi][0])); x[1] *= gelu_f(g[it][1] + hi16(e_gate[gi][0]));
+            x[2] *= gelu_f(g[it][2] + lo16(e_gate[gi][1])); x[3] *= gelu_f(g[it][3] + hi16(e_gate[gi][1]));
         } else {
-            const u32x4_w w = e_res[it];
+            const u32x4_w w = e_res[gi];
             f32x4_w r = a.res_compact == 2 ? __builtin_bit_cast(f32x4_w, w) : f32x4_w{lo16(w[0]), hi16(w[0]), lo16(w[1]), hi16(w[1])};
             if constexpr (AM == A_MAP) {
-                x[0] += lo16(e_bias2[it][0]); x[1] += hi16(e_bias2[it][0]); x[2] += lo16(e_bias2[it][1]); x[3] += hi16(e_bias2[it][1]);
-                r += __builtin_bit_cast(f32x4_w, e_temb[it]);
+                x[0] += lo16(e_bias2[gi][0]); x[1] += hi16(e_bias2[gi][0]); x[2] += lo16(e_bias2[gi][1]); x[3] += hi16(e_bias2[gi][1]);
+                r += __builtin_bit_cast(f32x4_w, e_temb[gi]);
             }
             x[0] += r[0]; x[1] += r[1]; x[2] += r[2]; x[3] += r[3];
         }
@@ -462,7 +524,7 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) { ss.s[i][q] = __uint_as_float(e_ss[it][i][0][q]); ss.s[i][4 + q] = __uint_as_float(e_ss[it][i][1][q]); }
+                    for (int q = 0; q < 4; ++q) { ss.s[i][q] = __uint_as_float(e_ss[gi][i][0][q]); ss.s[i][4 + q] = __uint_as_float(e_ss[gi][i][1][q]); }
                 put_views4(a.view, a.nview, e_pix[it], scol, x, ss);
             }
         }
@@ -507,23 +569,25 @@ static void prepare(IgemmArgs& a, int ncols) {
     for (int i = 0; i < 4; ++i) a.src[i].bytes = (i < 2 ? n_in : n_out) * a.src[i].pitch;
 }
 
-template <int TM, int TN, int NST, int AM, bool GEGLU>
+template <int TM, int TN, int NST, int AM, bool GEGLU, bool SHARED = false>
 static int launch_tile(const IgemmArgs& a, hipStream_t st) {
-    constexpr int NW = 4, lds = NW * NST * (32 * TM + 32 * TN) * 128;
+    constexpr int NW = 4, lds = (SHARED ? 1 : NW) * NST * (32 * TM + 32 * TN) * 128;
     // raised once per instantiation (initialisation of a function-local static is thread safe)
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU, SHARED>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return fail(FISE_ERR_HIP, "wave gemm: cannot raise the dynamic LDS limit");
     const double rows = (double)a.B * a.Ma, ncols = a.geglu ? 2.0 * a.N : a.N, K = (double)a.K + a.K2;
     {
         ProfileScope prof(GEGLU ? PROF_IGEMM_GEGLU : AM == A_MAP ? PROF_IGEMM : PROF_ROWS_GEMM, 2.0 * rows * ncols * K, 2.0 * (ncols * K + rows * (a.C0 + a.C1 + a.S0 + a.S1) + rows * a.N), st);
-        hipLaunchKernelGGL((wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU>), dim3((unsigned)(a.gx * a.gy * a.splits)), dim3(64 * NW), lds, st, a);
+        hipLaunchKernelGGL((wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU, SHARED>), dim3((unsigned)(a.gx * a.gy * a.splits)), dim3(64 * NW), lds, st, a);
     }
     FISE_CHECK_LAUNCH("wave gemm");
     return FISE_OK;
 }
 
-bool wave_gemm_fits(const IgemmArgs& a) {
+constexpr int BLOCK_ROWS = 2048;        // from here on the tiles of a wave of its own re-read too much: the block tile or igemm.hip
+
+static bool wave_gemm_fits(const IgemmArgs& a) {
     const int rows = a.B * a.Ma;
     constexpr size_t kLim = (size_t)1 << 31;            // 32-bit buffer offsets, top bit reserved for "no such row"
     if (a.pro != PRO_NONE || a.C0 % 64 || a.C1 % 64 || a.S0 % 64 || a.S1 % 64 || a.N % 4) return false;
@@ -538,6 +602,17 @@ bool wave_gemm_fits(const IgemmArgs& a) {
            ncols * std::max(a.K, a.K2) * 2 < kLim && (size_t)rows * a.N * 4 < kLim;
 }
 
+// Block tile of 64 x 160: one LDS ring for the workgroup, every wave multiplies a 16-deep slice of each K step over the whole
+// tile.  All CUs together stream operands at ~18 TB/s whatever the tile (70 GB/s each), so what counts is the bytes per
+// product: 1/46 of an operand row instead of 1/32 (64 x 64) or 1/43 on LDS reads that took twice as long (64 x 128, 8
+// waves).  Widths of a 320-channel UNet are multiples of 160: no columns to spare.  Its start and its epilogue of ten pieces
+// per thread take 13 us with one wave per SIMD, which only a long K earns back: 8192 x 320 x 2880 36.4 -> 31 us, 2048 x 640
+// x 5760 44.4 -> 38 us, but 8192 x 320 x 320 13 -> 18 us.
+static bool block_gemm_fits(const IgemmArgs& a) {
+    return !a.a_compact && a.N % 160 == 0 && a.nsect == 1 && (a.K + a.K2) / 64 >= 24;
+}
+bool wave_gemm_takes(const IgemmArgs& a) { return wave_gemm_fits(a) && (a.B * a.Ma < BLOCK_ROWS || block_gemm_fits(a)); }
+
 // Tile and K split of a launch: the cheapest of the combinations under the times measured per part of a launch (us, from
 // time stamps inside the kernel over the shapes of a step).  `fixed`: start, row positions, first loads, sum over the
 // waves, epilogue, and the gap to the launch before.  `iter`: one K step of all four waves (its operands at the 85 GB/s
@@ -547,9 +622,11 @@ int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
     const int rows = a.B * a.Ma, ncols = a.geglu ? 2 * a.N : a.N, nsteps = (a.K + a.K2) / 64;
     int best_tm = 1, best_tn = 1, best_s = 1; double best = 1e30;
     const int max_s = ws && ws->counters && ws->partial ? 8 : 1;
-    struct { int tm, tn; double fixed, iter, park; } shapes[] = {{1, 1, 4.3, 0.39, 2.0}, {1, 2, 4.8, 0.56, 2.3}, {2, 2, 5.8, 0.92, 3.2}};
+    struct { int tm, tn; double fixed, iter, park; } shapes[] = {{1, 1, 4.3, 0.39, 2.0}, {1, 2, 4.8, 0.56, 2.3}, {2, 2, 5.8, 0.92, 3.2}, {2, 5, 13.0, 1.6, 4.0}};
     for (const auto& sh : shapes) {
         if (a.geglu && sh.tn == 1) continue;
+        if (sh.tn == 5 && !block_gemm_fits(a)) continue;
+        if (rows >= BLOCK_ROWS && sh.tn != 5) continue;
         const int gx = ceil_div(rows, 32 * sh.tm), gy = ceil_div(ncols, 32 * sh.tn);
         for (int s = 1; s <= max_s; ++s) {
             const int per = ceil_div(nsteps, s);
@@ -572,6 +649,7 @@ int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
     }
     int e;
     if (a.geglu) e = best_tm == 1 ? launch_tile<1, 2, 2, A_ROWS, true>(a, st) : launch_tile<2, 2, 2, A_ROWS, true>(a, st);
+    else if (best_tn == 5) e = launch_tile<2, 5, 4, A_MAP, false, true>(a, st);
     else if (a.a_compact)
         e = best_tm == 2 ? launch_tile<2, 2, 2, A_ROWS, false>(a, st) : best_tn == 2 ? launch_tile<1, 2, 2, A_ROWS, false>(a, st) : launch_tile<1, 1, 2, A_ROWS, false>(a, st);
     else

@@ -35,6 +35,14 @@ CASES = [
     ("split-upsample", 1, 16, 16, 640, 0, 64, 3, 1, 1, 4, 3, False, False),
     ("many-row-tiles-long-k", 1, 32, 32, 320, 0, 64, 3, 1, 0, 4, 39, True, False),     # row tiles fetch the weight slice together
     ("64-row-tiles", 2, 64, 32, 128, 0, 324, 1, 1, 0, 8, 31, False, True),
+    # block tile of 64 x 160 (from 2048 rows on, and where it is the cheapest)
+    ("block-one-step", 2, 64, 40, 64, 0, 160, 1, 1, 0, 8, 16, False, False),           # one K step, the second of the pair is zeros
+    ("block-ragged-rows", 1, 64, 64, 64, 0, 160, 3, 1, 0, 4, 129, True, True),         # 2064 rows, 9 steps
+    ("block-sources", 2, 64, 40, 64, 128, 320, 3, 1, 0, 8, 17, True, False),
+    ("block-long-k", 2, 64, 40, 320, 0, 160, 3, 1, 0, 8, 19, False, True),             # row tiles fetch the weight slice together
+    ("block-stride-2", 1, 64, 40, 64, 0, 160, 3, 2, 0, 8, 33, False, False),
+    ("block-upsample", 1, 64, 40, 128, 0, 160, 3, 1, 1, 8, 33, False, True),
+    ("block-split", 2, 32, 32, 640, 0, 320, 3, 1, 0, 4, 32, True, True),               # 1024 rows
 ]
 
 
@@ -62,3 +70,37 @@ def test_wave_gemm_edges(fb, case):
     check_map(got, want, cache.astype(np.float64), active_mask(ix, t, Ho, Wo), TOL[DT], name)
     fb.fise_masked_conv(a, ws)                       # arrival counters are back at zero, the sum does not depend on who came last
     assert np.array_equal(host(y), got)
+
+
+def test_block_tile_rows_and_transposed_columns(fb):
+    """Compact rows in, rows / scattered rows / transposed columns out: an attention layer of more than 2048 queries."""
+    B, H, W, C, heads, t = 2, 48, 56, 320, 8, 4
+    rng = np.random.default_rng(41)
+    x = wl.normal(rng, (B, H, W, C), 1.0, DT)
+    Kc, Vc = (wl.normal(rng, (B, H * W, C), 1.0, DT) for _ in range(2))
+    Wq, Wk, Wv, Wo = (wl.normal(rng, (C, C), C ** -0.5, DT) for _ in range(4))
+    bo, gamma, beta = wl.normal(rng, (C,), 0.1, DT), np.ones(C, np.float32), np.zeros(C, np.float32)
+    y0 = wl.normal(rng, (B, H, W, C), 1.0, DT)
+    ix = np.sort(rng.choice((H // t) * (W // t), 67, replace=False)).astype(np.int32)
+    y, Kd, Vtd = dev(y0, DT), dev(Kc, DT), dev(np.ascontiguousarray(Vc.transpose(0, 2, 1)), DT)
+    ws = torch.zeros(fb.fise_masked_attention_workspace_bytes(B, C, ix.size, t), dtype=torch.uint8, device=DEV)
+    ws_args = [dev(v, DT) for v in (x, gamma, beta, Wq, Wk, Wv, Wo, bo)]
+    fb.fise_masked_attention(*ws_args, heads, Kd, Vtd, None, None, 0, idx_dev(ix), ix.size, t, y, ws)
+    act = active_mask(ix, t, H, W)
+    n = np.asarray(x, np.float64)[:, act]                     # [B, active, C]; rows normalised in float64, rounded once
+    n = (n - n.mean(-1, keepdims=True)) / np.sqrt(n.var(-1, keepdims=True) + 1e-5)
+    for got, w, cache in ((host(Kd), Wk, Kc), (host(Vtd).transpose(0, 2, 1), Wv, Vc)):
+        got, cache = got.reshape(B, H, W, C), np.asarray(cache, np.float64).reshape(B, H, W, C)
+        want = cache.copy()
+        want[:, act] = n @ np.asarray(w, np.float64).T
+        check_map(got, want, cache, act, TOL[DT], "keys or values")
+    K64, V64 = host(Kd).astype(np.float64), host(Vtd).astype(np.float64).transpose(0, 2, 1)
+    q, d, o = n @ np.asarray(Wq, np.float64).T, C // heads, []
+    for h in range(heads):
+        c = slice(h * d, (h + 1) * d)
+        s = q[..., c] @ K64[..., c].transpose(0, 2, 1) / math.sqrt(d)
+        p = np.exp(s - s.max(-1, keepdims=True))
+        o.append(p @ V64[..., c] / p.sum(-1, keepdims=True))
+    want = np.asarray(y0, np.float64).copy()
+    want[:, act] = np.concatenate(o, -1) @ np.asarray(Wo, np.float64).T + np.asarray(bo, np.float64) + np.asarray(x, np.float64)[:, act]
+    check_map(host(y), want, np.asarray(y0, np.float64), act, TOL[DT], "layer output")
