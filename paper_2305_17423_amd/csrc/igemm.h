@@ -17,6 +17,12 @@ struct GnView { bf16_t* dst; const float2* ss; int dstC, c_off, silu, pad_; };
 
 // n / d as (umulhi(n, mul) + n) >> shift: exact for n < 2^31 (round-up method of Granlund and Montgomery)
 struct FastDiv { unsigned mul; int shift; };
+inline FastDiv fast_div(int d) {
+    FastDiv f{1u, 0};
+    while ((1ll << f.shift) < d) ++f.shift;
+    f.mul = (unsigned)((((unsigned long long)1 << 32) * (((unsigned long long)1 << f.shift) - (unsigned)d)) / (unsigned)d + 1);
+    return f;
+}
 
 struct IgemmArgs {
     // ---- A operand: rows = B * Ma active pixels (or compact rows) x K
@@ -67,6 +73,7 @@ struct BlockDerived {
 };
 
 #if defined(__HIPCC__)
+__device__ __forceinline__ unsigned fdiv(unsigned n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
 // Four consecutive channels col .. col + 3 of pixel `pix` (batch element b): every view gets its activation.
 // In two halves, so that an epilogue can request the table entries of all its items together with its other
 // operands and use them later (loaded where they are used, each item pays a round trip of its own in front of

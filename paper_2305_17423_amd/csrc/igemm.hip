@@ -1182,7 +1182,7 @@ int launch_igemm(const IgemmArgs& a, const IgemmWorkspace* ws, hipStream_t st) {
     for (int i = 0; i < a.nview; ++i)
         if (!a.view[i].dst || !a.view[i].ss || a.view[i].dstC % 4 || a.view[i].c_off % 4 || a.view[i].c_off + a.N > a.view[i].dstC)
             return fail(FISE_ERR_SHAPE, "igemm: normalised copy %d: channels %d + %d of %d", i, a.view[i].c_off, a.N, a.view[i].dstC);
-    // below 2048 rows the fixed cost of a launch decides, from there on the operands that small tiles re-read (wave_gemm.hip)
+    // all but compact rows of one section from 2048 rows on, and what is not made of 64-channel pieces
     if (wave_gemm_takes(a)) return launch_wave_gemm(a, ws, st);
     const bool wide = rows >= 4096 && a.N >= 128;          // dense-sized problems: 64x128 tiles, 8 waves
     if (a.geglu) {

@@ -32,9 +32,6 @@ typedef float f32x4_w __attribute__((ext_vector_type(4)));
 enum { A_ROWS = 0, A_MAP = 1 };         // compact rows / pixels of maps (taps, two sources, side product)
 
 #if defined(__HIP_DEVICE_COMPILE__)
-// n / d for the divisor behind f, exact for n < 2^31
-__device__ __forceinline__ unsigned fdiv(unsigned n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
-
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
@@ -52,9 +49,9 @@ __device__ __forceinline__ float gelu_f(float x) {
 }
 #endif
 
-// SHARED: one ring for the workgroup instead of one per wave, see the block tile below.
+// SHARED: one ring for the workgroup instead of one per wave, see the launcher.
 template <int TM, int TN, int NW, int NST, int AM, bool GEGLU, bool SHARED>
-__global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
+__global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_kernel(const IgemmArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 32 * TM, BN = 32 * TN, NT = 64 * NW;
     constexpr int RB = SHARED ? 8 * NW : 8;             // rows between two loads of a lane (one load of a wave fills 8 rows of 128 bytes)
@@ -66,7 +63,7 @@ __global__ __launch_bounds__(64 * NW) void wave_gemm_kernel(const IgemmArgs a) {
     constexpr int CPR = OW / 4, IPG = GROWS * CPR / NT, ITEMS = GROUPS * IPG;      // four-column pieces per row, per thread and group, per thread
     constexpr unsigned OOB = 0x80000000u;               // beyond every descriptor: the load returns zeros
     static_assert(GROWS * CPR % NT == 0 && (SHARED ? 1 : NW) * NST * STAGE >= NW * GROWS * PITCH * 4, "tile");
-    static_assert(!SHARED || (NW == 4 && NST >= 3 && !GEGLU), "a shared stage has one 16-deep slice of K per wave");
+    static_assert(!SHARED || (NW == 4 && NST >= 3), "a shared stage has one 16-deep slice of K per wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];      // [NW or 1][NST][STAGE], later [NW][GROWS][PITCH] floats
 
     // Kernel arguments arrive through scalar loads placed where a field is first used; named here they come as one batch.
@@ -540,13 +537,6 @@ __global__ void zero_ints_kernel(int* p, int n) {
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-static FastDiv fast_div(int d) {
-    FastDiv f{1u, 0};
-    while ((1ll << f.shift) < d) ++f.shift;
-    f.mul = (unsigned)((((unsigned long long)1 << 32) * (((unsigned long long)1 << f.shift) - (unsigned)d)) / (unsigned)d + 1);
-    return f;
-}
-
 // Derived fields of the argument block: divisors, operand sizes, what the epilogue addresses.
 static void prepare(IgemmArgs& a, int ncols) {
     const int rows = a.B * a.Ma;
@@ -585,8 +575,6 @@ static int launch_tile(const IgemmArgs& a, hipStream_t st) {
     return FISE_OK;
 }
 
-constexpr int BLOCK_ROWS = 2048;        // from here on the tiles of a wave of its own re-read too much: the block tile or igemm.hip
-
 static bool wave_gemm_fits(const IgemmArgs& a) {
     const int rows = a.B * a.Ma;
     constexpr size_t kLim = (size_t)1 << 31;            // 32-bit buffer offsets, top bit reserved for "no such row"
@@ -602,38 +590,50 @@ static bool wave_gemm_fits(const IgemmArgs& a) {
            ncols * std::max(a.K, a.K2) * 2 < kLim && (size_t)rows * a.N * 4 < kLim;
 }
 
-// Block tile of 64 x 160: one LDS ring for the workgroup, every wave multiplies a 16-deep slice of each K step over the whole
-// tile.  All CUs together stream operands at ~18 TB/s whatever the tile (70 GB/s each), so what counts is the bytes per
-// product: 1/46 of an operand row instead of 1/32 (64 x 64) or 1/43 on LDS reads that took twice as long (64 x 128, 8
-// waves).  Widths of a 320-channel UNet are multiples of 160: no columns to spare.  Its start and its epilogue of ten pieces
-// per thread take 13 us with one wave per SIMD, which only a long K earns back: 8192 x 320 x 2880 36.4 -> 31 us, 2048 x 640
-// x 5760 44.4 -> 38 us, but 8192 x 320 x 320 13 -> 18 us.
-static bool block_gemm_fits(const IgemmArgs& a) {
-    return !a.a_compact && a.N % 160 == 0 && a.nsect == 1 && (a.K + a.K2) / 64 >= 24;
+// Compact rows of one section from here on: igemm.hip's 64 x 128 and 64 x 64 tiles (8192 x 320 x 320 12.8 against 14.3 us,
+// 2048 x 640 x 640 12.7 against 13.3 us on shared tiles).
+constexpr int BLOCK_ROWS = 2048;
+bool wave_gemm_takes(const IgemmArgs& a) {
+    return wave_gemm_fits(a) && (a.B * a.Ma < BLOCK_ROWS || !a.a_compact || a.geglu || a.nsect > 1);
 }
-bool wave_gemm_takes(const IgemmArgs& a) { return wave_gemm_fits(a) && (a.B * a.Ma < BLOCK_ROWS || block_gemm_fits(a)); }
 
-// Tile and K split of a launch: the cheapest of the combinations under the times measured per part of a launch (us, from
-// time stamps inside the kernel over the shapes of a step).  `fixed`: start, row positions, first loads, sum over the
-// waves, epilogue, and the gap to the launch before.  `iter`: one K step of all four waves (its operands at the 85 GB/s
-// a CU reaches here).  A K split over workgroups adds parking, counting and re-reading the tiles.  256 workgroups run at
-// once: the rings take most of a CU's LDS.
+// Tile and K split of a launch: the cheapest of the combinations under times measured per part of a launch (us, from time
+// stamps inside the kernel and kernel traces over the shapes of steps and dense builds).
+//  - PRIVATE, a ring per wave, 256 workgroups at once.  `fixed`: start, row positions, first loads, sum over the waves,
+//    epilogue, and the gap to the launch before.  `iter`: four K steps, one per wave (operands at the 70 - 85 GB/s a CU gets).
+//  - SHARED, 64 x 64 on one ring of 48 KB: every wave multiplies a 16-deep slice of each K step over the whole tile, so a
+//    staged byte is read once, and three workgroups per CU hide each other's start and epilogue, which many tiles of
+//    a short K consist of: `tile` + `iter` per K step of a tile and CU.  5504 x 320 x 2880 36 -> 24 us (64 x 128 tiles of
+//    eight waves that read a staged byte 2.7 times), 1376 x 1920 x 640 23 -> 15, with GEGLU 1376 x 5120 x 640 39 -> 26 us.
+//    Beyond ~96 K steps (`iter_long`) the workgroups of an XCD drift apart and fall out of its L2.
+//  - BLOCK, 64 x 160 on one ring of 112 KB: 1/46 of an operand row per product instead of 1/32, one workgroup per CU and a
+//    long epilogue (ten pieces per thread): 8192 x 320 x 9600 105 (SHARED) -> 64 us, 2048 x 640 x 11520 with 1x1 side product 76
+//    -> 54 us.  Widths of a 320-channel UNet are multiples of 160: no columns to spare.
+// A K split over workgroups adds parking, counting and re-reading the tiles (`park`, `park_s` per split).
+enum { PRIVATE = 0, SHARED_RING = 1, BLOCK = 2 };
+struct TileShape { int kind, tm, tn; double fixed, tile, iter, iter_long, park, park_s; };
+static const TileShape kShapes[] = {
+    {PRIVATE, 1, 1, 4.3, 0.0, 0.39, 0.39, 2.0, 0.15}, {PRIVATE, 1, 2, 4.8, 0.0, 0.56, 0.56, 2.3, 0.3}, {PRIVATE, 2, 2, 5.8, 0.0, 0.92, 0.92, 3.2, 0.6},
+    {SHARED_RING, 2, 2, 5.2, 1.2, 0.235, 0.32, 3.2, 0.6}, {BLOCK, 2, 5, 13.0, 0.0, 0.4, 0.4, 4.0, 1.5}};
+
 int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
     const int rows = a.B * a.Ma, ncols = a.geglu ? 2 * a.N : a.N, nsteps = (a.K + a.K2) / 64;
-    int best_tm = 1, best_tn = 1, best_s = 1; double best = 1e30;
+    int kind = PRIVATE, best_tm = 1, best_tn = 1, best_s = 1; double best = 1e30;
     const int max_s = ws && ws->counters && ws->partial ? 8 : 1;
-    struct { int tm, tn; double fixed, iter, park; } shapes[] = {{1, 1, 4.3, 0.39, 2.0}, {1, 2, 4.8, 0.56, 2.3}, {2, 2, 5.8, 0.92, 3.2}, {2, 5, 13.0, 1.6, 4.0}};
-    for (const auto& sh : shapes) {
+    for (const TileShape& sh : kShapes) {
         if (a.geglu && sh.tn == 1) continue;
-        if (sh.tn == 5 && !block_gemm_fits(a)) continue;
-        if (rows >= BLOCK_ROWS && sh.tn != 5) continue;
+        if (sh.kind == BLOCK && (a.a_compact || a.N % 160 || a.nsect > 1)) continue;
         const int gx = ceil_div(rows, 32 * sh.tm), gy = ceil_div(ncols, 32 * sh.tn);
         for (int s = 1; s <= max_s; ++s) {
             const int per = ceil_div(nsteps, s);
             if (s > 1 && (per < 4 || ceil_div(nsteps, per) != s)) continue;
-            if (s > 1 && (gx * gy > IGEMM_COUNTERS || (size_t)gx * gy * s * 32 * sh.tm * 32 * sh.tn * 4 > ws->partial_bytes)) break;
-            const double t = ceil_div(gx * gy * s, 256) * (sh.fixed + ceil_div(per, 4) * sh.iter) + (s > 1 ? sh.park + 0.15 * s * sh.tm * sh.tn : 0.0);
-            if (t < best) { best = t; best_tm = sh.tm; best_tn = sh.tn; best_s = s; }
+            if (s > 1 && ((long long)gx * gy > IGEMM_COUNTERS || (size_t)gx * gy * s * 32 * sh.tm * 32 * sh.tn * 4 > ws->partial_bytes)) break;
+            const long long n = (long long)gx * gy * s;
+            const double iter = nsteps > 96 ? sh.iter_long : sh.iter;
+            double t = s > 1 ? sh.park + sh.park_s * s : 0.0;
+            if (sh.kind == SHARED_RING) t += sh.fixed + std::max(1.0, n / 256.0) * (sh.tile + per * iter);
+            else t += (double)((n + 255) / 256) * (sh.fixed + (sh.kind == PRIVATE ? ceil_div(per, 4) : per) * iter);
+            if (t < best) { best = t; kind = sh.kind; best_tm = sh.tm; best_tn = sh.tn; best_s = s; }
         }
     }
     a.splits = best_s; a.kper = ceil_div(nsteps, best_s);
@@ -648,8 +648,10 @@ int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
         }
     }
     int e;
-    if (a.geglu) e = best_tm == 1 ? launch_tile<1, 2, 2, A_ROWS, true>(a, st) : launch_tile<2, 2, 2, A_ROWS, true>(a, st);
-    else if (best_tn == 5) e = launch_tile<2, 5, 4, A_MAP, false, true>(a, st);
+    if (kind == BLOCK) e = launch_tile<2, 5, 4, A_MAP, false, true>(a, st);
+    else if (kind == SHARED_RING)
+        e = a.geglu ? launch_tile<2, 2, 3, A_ROWS, true, true>(a, st) : a.a_compact ? launch_tile<2, 2, 3, A_ROWS, false, true>(a, st) : launch_tile<2, 2, 3, A_MAP, false, true>(a, st);
+    else if (a.geglu) e = best_tm == 1 ? launch_tile<1, 2, 2, A_ROWS, true>(a, st) : launch_tile<2, 2, 2, A_ROWS, true>(a, st);
     else if (a.a_compact)
         e = best_tm == 2 ? launch_tile<2, 2, 2, A_ROWS, false>(a, st) : best_tn == 2 ? launch_tile<1, 2, 2, A_ROWS, false>(a, st) : launch_tile<1, 1, 2, A_ROWS, false>(a, st);
     else

@@ -35,7 +35,7 @@ CASES = [
     ("split-upsample", 1, 16, 16, 640, 0, 64, 3, 1, 1, 4, 3, False, False),
     ("many-row-tiles-long-k", 1, 32, 32, 320, 0, 64, 3, 1, 0, 4, 39, True, False),     # row tiles fetch the weight slice together
     ("64-row-tiles", 2, 64, 32, 128, 0, 324, 1, 1, 0, 8, 31, False, True),
-    # block tile of 64 x 160 (from 2048 rows on, and where it is the cheapest)
+    # tiles on a ring shared by the workgroup: many tiles, odd and even numbers of K steps, every source change
     ("block-one-step", 2, 64, 40, 64, 0, 160, 1, 1, 0, 8, 16, False, False),           # one K step, the second of the pair is zeros
     ("block-ragged-rows", 1, 64, 64, 64, 0, 160, 3, 1, 0, 4, 129, True, True),         # 2064 rows, 9 steps
     ("block-sources", 2, 64, 40, 64, 128, 320, 3, 1, 0, 8, 17, True, False),
@@ -43,6 +43,8 @@ CASES = [
     ("block-stride-2", 1, 64, 40, 64, 0, 160, 3, 2, 0, 8, 33, False, False),
     ("block-upsample", 1, 64, 40, 128, 0, 160, 3, 1, 1, 8, 33, False, True),
     ("block-split", 2, 32, 32, 640, 0, 320, 3, 1, 0, 4, 32, True, True),               # 1024 rows
+    ("block-ragged-columns", 1, 64, 64, 64, 0, 324, 3, 1, 0, 4, 131, True, True),
+    ("block-160-wide", 1, 64, 64, 640, 640, 320, 3, 1, 0, 8, 33, True, False),         # 64 x 160 tiles, split, 180 steps
 ]
 
 
