@@ -27,6 +27,7 @@ template <int KD, int DB>          // KD: 16-wide steps over the head dim; DB: 3
 __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K,
                                                         const bf16_t* __restrict__ Vt, int B, int M, int n_keys, int n_stride,
                                                         int C, int d, float scale_log2e, int splits, int nqt, int heads,
+                                                        FastDiv d_nqt, FastDiv d_heads, FastDiv d_splits, int chunk_mul,
                                                         bf16_t* __restrict__ out, float* __restrict__ part_o, float* __restrict__ part_ml) {
     constexpr int DP = KD * 16;
     constexpr int KP = DP + 8;            // K tile pitch (bf16)
@@ -47,9 +48,9 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
         const int total = nqt * heads * B * splits, chunk = total >> 3;
         int w = blockIdx.x;
         if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
-        qt = w % nqt; int t = w / nqt;
-        h = t % heads; t /= heads;
-        sp = t % splits; b = t / splits;
+        const int t = (int)fdiv(w, d_nqt), u = (int)fdiv(t, d_heads);
+        qt = w - t * nqt; h = t - u * heads;
+        b = (int)fdiv(u, d_splits); sp = u - b * splits;
     }
     const int qrow = qt * AT_BQ + wave * AT_QW + l32;
     const bool qok = qrow < M;
@@ -80,9 +81,10 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
     // ---- register staging of key blocks.  Thread slot j covers chunk e = tid + 256 j of the block's real data:
     // K rows of d / 8 chunks (key e / dchunks, chunk e % dchunks), V^T rows of 8 chunks (row e / 8 < d, keys
     // (e % 8) * 8 ..).  Everything that depends only on the slot is worked out once; a block costs one pointer
-    // bump and one load per slot.  The padding of the LDS tiles (head-dim columns / rows past d) is zeroed once
-    // and never written again.  Keys that do not exist can only occur in the last block of the whole range: that
-    // block alone takes the guarded path (keys past n_keys read nothing and are stored as zeros).
+    // bump and one load per slot.  The head-dim columns of the K tile past d are zeroed once and never written
+    // again (V^T rows past d only reach output rows that are not stored).  Keys that do not exist can only occur in the last block of the whole range: its loads go
+    // to the nearest key that exists (all of them unconditional: behind a branch each, they were a round trip each) and
+    // what they bring is replaced by zeros on the way into the LDS tiles.
     constexpr int PFD = (KL + VL <= 6) ? 2 : 1;       // key blocks in flight (small heads can afford two in registers)
     uint4 rk[PFD][KL], rv[PFD][VL];
     const bf16_t* pk[KL]; const bf16_t* pv[VL];        // source of the slot in key block 0
@@ -91,7 +93,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
 #pragma unroll
     for (int j = 0; j < KL; ++j) {
         const int e = tid + 256 * j;
-        const int kk = e / dchunks, c8 = e - kk * dchunks;
+        const int kk = (e * chunk_mul) >> 16, c8 = e - kk * dchunks;      // e / dchunks: e < 1280, dchunks <= 20
         const bool used = e < AT_BKV * dchunks;
         kkey[j] = used ? kk : -1;
         pk[j] = K + (used ? ((size_t)b * n_keys + kk) * C + h * d + c8 * 8 : 0);
@@ -106,15 +108,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
         pv[j] = Vt + (used ? ((size_t)b * C + h * d + r) * n_stride + c8 * 8 : 0);
         sv[j] = &Vs[used ? r : 0][used ? c8 * 8 : 0];
     }
-    for (int e = tid; e < AT_BKV * KP / 8; e += 256) reinterpret_cast<uint4*>(&Ks[0][0])[e] = make_uint4(0, 0, 0, 0);
-    for (int e = tid; e < DB * 32 * VP / 8; e += 256) reinterpret_cast<uint4*>(&Vs[0][0])[e] = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-    // The query fragments must have ARRIVED before the key loop is entered: while their loads are still counted as
-    // outstanding at the loop head, the compiler's wait-count bookkeeping (merged over the loop's paths) puts a
-    // wait for ALL loads in front of the first MFMA of every iteration, i.e. right behind the prefetch of the next
-    // key block, which then never overlaps anything.  Naming the fragments as operands here places that wait once.
-#pragma unroll
-    for (int ks = 0; ks < KD; ++ks) asm volatile("" ::"v"(qf[ks]));
+    for (int e = tid; e < AT_BKV * (DP / 8 - dchunks); e += 256) *reinterpret_cast<uint4*>(&Ks[e % AT_BKV][d + e / AT_BKV * 8]) = make_uint4(0, 0, 0, 0);
     auto fetch = [&](int blk, int slot) {
         const int k0 = blk * AT_BKV;
         if (k0 + AT_BKV <= n_keys) {                     // uniform: a block of existing keys
@@ -123,31 +117,27 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
 #pragma unroll
             for (int j = 0; j < VL; ++j) rv[slot][j] = *reinterpret_cast<const uint4*>(pv[j] + k0);
         } else {
+            const int last = n_keys - 1 - k0;            // last key of the block
 #pragma unroll
-            for (int j = 0; j < KL; ++j) {
-                const bool ok = kkey[j] >= 0 && k0 + kkey[j] < n_keys;
-                rk[slot][j] = ok ? *reinterpret_cast<const uint4*>(pk[j] + (size_t)k0 * C) : make_uint4(0, 0, 0, 0);
-            }
+            for (int j = 0; j < KL; ++j) rk[slot][j] = *reinterpret_cast<const uint4*>(pk[j] + ((long long)k0 + min(0, last - kkey[j])) * C);
 #pragma unroll
-            for (int j = 0; j < VL; ++j) {
-                const int key = k0 + vkey[j];
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (vkey[j] >= 0 && key < n_keys) {
-                    v = *reinterpret_cast<const uint4*>(pv[j] + k0);
-                    const int nvalid = n_keys - key;          // keys of this chunk that exist; the rest become zeros
-                    if (nvalid < 8) {
-                        unsigned w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                        for (int t = 0; t < 8; ++t)
-                            if (t >= nvalid) w4[t >> 1] &= (t & 1) ? 0x0000ffffu : 0xffff0000u;
-                        v = make_uint4(w4[0], w4[1], w4[2], w4[3]);
-                    }
-                }
-                rv[slot][j] = v;
-            }
+            for (int j = 0; j < VL; ++j) rv[slot][j] = *reinterpret_cast<const uint4*>(pv[j] + (vkey[j] <= last ? k0 : 0));
         }
     };
-    auto stash = [&](int slot) {
+    auto stash = [&](int blk, int slot) {
+        const int nk = n_keys - blk * AT_BKV;            // keys of this block that exist
+        if (__builtin_amdgcn_readfirstlane(nk < AT_BKV)) {
+#pragma unroll
+            for (int j = 0; j < KL; ++j)
+                if (kkey[j] >= nk) rk[slot][j] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < VL; ++j) {
+                const int nv = nk - vkey[j];             // keys of this chunk that exist
+                auto keep = [&](unsigned w, int t) { return nv > t + 1 ? w : nv > t ? w & 0xffffu : 0u; };
+                const uint4 v = rv[slot][j];
+                rv[slot][j] = make_uint4(keep(v.x, 0), keep(v.y, 2), keep(v.z, 4), keep(v.w, 6));
+            }
+        }
 #pragma unroll
         for (int j = 0; j < KL; ++j)
             if (kkey[j] >= 0) *reinterpret_cast<uint4*>(sk[j]) = rk[slot][j];
@@ -160,6 +150,12 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
 #pragma unroll
         for (int s = 0; s < PFD; ++s) fetch(min(blk0 + s, blk1 - 1), s);
     }
+    // The query fragments must have ARRIVED before the key loop is entered: while their loads are still counted as
+    // outstanding at the loop head, the compiler's wait-count bookkeeping (merged over the loop's paths) puts a
+    // wait for ALL loads in front of the first MFMA of every iteration, i.e. right behind the prefetch of the next
+    // key block, which then never overlaps anything.  Naming the fragments as operands here, behind the first key blocks' loads, places that wait once.
+#pragma unroll
+    for (int ks = 0; ks < KD; ++ks) asm volatile("" ::"v"(qf[ks]));
     for (int blk0u = blk0; blk0u < blk1; blk0u += PFD) {
 #pragma unroll
       for (int slot = 0; slot < PFD; ++slot) {
@@ -167,7 +163,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
         if (blk >= blk1) break;                            // uniform across the workgroup
         const int k0 = blk * AT_BKV;
         at_lds_barrier();                                  // previous block fully consumed
-        stash(slot);
+        stash(blk, slot);
         fetch(min(blk + PFD, blk1 - 1), slot);             // PFD blocks ahead, in flight during the MFMAs below
         at_lds_barrier();
 
@@ -309,12 +305,16 @@ static void launch_at(const void* q, const void* K, const void* Vt, int B, int M
     dim3 grid((unsigned)(nqt * heads * B * splits));
     hipLaunchKernelGGL((attention_kernel<KD, DB>), grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)K,
                        (const bf16_t*)Vt, B, M, n_keys, n_stride, C, d, scale * 1.4426950408889634f, splits, nqt, heads,
+                       fast_div(nqt), fast_div(heads), fast_div(splits), 65536 / (d / 8) + 1,
                        (bf16_t*)out, part_o, part_ml);
 }
 
+// A split pays a second launch of ~5 us for the merge; a key block takes 0.6 - 1 us, so a handful of them is streamed in one go
+// (192 x 256 keys of 1280 channels: 10 + 4.5 us with two splits, 13 us without, and one launch less).
 static int attention_splits(int B, int M, int n_keys, int heads) {
     const int wgs = ceil_div(M, AT_BQ) * heads * B;
     const int nblocks = ceil_div(n_keys, AT_BKV);
+    if (nblocks < 8) return 1;
     int s = ceil_div(640, wgs);
     s = std::min(s, nblocks / 2);
     return std::max(1, std::min(s, 32));
@@ -343,7 +343,8 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
     else if (kd == 2) FISE_AT(2, 1);
     else if (kd == 3) FISE_AT(3, 2);
     else if (kd == 4) FISE_AT(4, 2);
-    else if (kd <= 6 && db <= 3) FISE_AT(6, 3);
+    else if (kd == 5) FISE_AT(5, 3);
+    else if (kd == 6) FISE_AT(6, 3);
     else if (kd <= 8) FISE_AT(8, 4);
     else if (kd <= 10) FISE_AT(10, 5);
     else return fail(FISE_ERR_SHAPE, "attention: head dim %d > 160", d);
