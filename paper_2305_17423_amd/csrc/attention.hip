@@ -23,10 +23,12 @@ constexpr int AT_BQ = AT_QW * AT_WAVES;
 
 __device__ __forceinline__ void at_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int KD, int DB>          // KD: 16-wide steps over the head dim; DB: 32-row blocks of the output head dim
+// KD: 16-wide steps over the head dim; DB: 32-row blocks of the output head dim; EXACT: the head dim is 16 KD (80, 160: the set-up
+// of a short launch is instructions, and most of its conditions and address terms are constants then)
+template <int KD, int DB, bool EXACT>
 __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K,
                                                         const bf16_t* __restrict__ Vt, int B, int M, int n_keys, int n_stride,
-                                                        int C, int d, float scale_log2e, int splits, int nqt, int heads,
+                                                        int C, int d_arg, float scale_log2e, int splits, int nqt, int heads,
                                                         FastDiv d_nqt, FastDiv d_heads, FastDiv d_splits, int chunk_mul,
                                                         bf16_t* __restrict__ out, float* __restrict__ part_o, float* __restrict__ part_ml) {
     constexpr int DP = KD * 16;
@@ -54,7 +56,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
     }
     const int qrow = qt * AT_BQ + wave * AT_QW + l32;
     const bool qok = qrow < M;
-    const int dchunks = d / 8;
+    const int d = EXACT ? DP : d_arg, dchunks = d / 8;
 
     // key blocks of this split
     const int nblocks = (n_keys + AT_BKV - 1) / AT_BKV;
@@ -93,7 +95,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
 #pragma unroll
     for (int j = 0; j < KL; ++j) {
         const int e = tid + 256 * j;
-        const int kk = (e * chunk_mul) >> 16, c8 = e - kk * dchunks;      // e / dchunks: e < 1280, dchunks <= 20
+        const int kk = EXACT ? e / (DP / 8) : (e * chunk_mul) >> 16, c8 = e - kk * dchunks;      // e / dchunks: e < 1280, dchunks <= 20
         const bool used = e < AT_BKV * dchunks;
         kkey[j] = used ? kk : -1;
         pk[j] = K + (used ? ((size_t)b * n_keys + kk) * C + h * d + c8 * 8 : 0);
@@ -298,12 +300,12 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
     *reinterpret_cast<uint2*>(out + ((size_t)b * M + m) * C + c) = make_uint2(f2bf2(num.x * inv, num.y * inv), f2bf2(num.z * inv, num.w * inv));
 }
 
-template <int KD, int DB>
+template <int KD, int DB, bool EXACT>
 static void launch_at(const void* q, const void* K, const void* Vt, int B, int M, int n_keys, int n_stride, int C, int heads,
                       int d, float scale, int splits, void* out, float* part_o, float* part_ml, hipStream_t st) {
     const int nqt = ceil_div(M, AT_BQ);
     dim3 grid((unsigned)(nqt * heads * B * splits));
-    hipLaunchKernelGGL((attention_kernel<KD, DB>), grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)K,
+    hipLaunchKernelGGL((attention_kernel<KD, DB, EXACT>), grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)K,
                        (const bf16_t*)Vt, B, M, n_keys, n_stride, C, d, scale * 1.4426950408889634f, splits, nqt, heads,
                        fast_div(nqt), fast_div(heads), fast_div(splits), 65536 / (d / 8) + 1,
                        (bf16_t*)out, part_o, part_ml);
@@ -338,17 +340,21 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
     {
     ProfileScope prof(PROF_ATTENTION, 4.0 * B * (double)M * n_keys * C,
                       2.0 * ((double)B * n_keys * C * 2 + 2.0 * B * M * C), st);
-#define FISE_AT(KDV, DBV) launch_at<KDV, DBV>(q, K, Vt, B, M, n_keys, n_stride, C, heads, d, scale, splits, out, part_o, part_ml, st)
+#define FISE_AT(KDV, DBV) launch_at<KDV, DBV, false>(q, K, Vt, B, M, n_keys, n_stride, C, heads, d, scale, splits, out, part_o, part_ml, st)
+#define FISE_AT_EXACT(KDV, DBV) launch_at<KDV, DBV, true>(q, K, Vt, B, M, n_keys, n_stride, C, heads, d, scale, splits, out, part_o, part_ml, st)
     if (kd <= 1) FISE_AT(1, 1);
     else if (kd == 2) FISE_AT(2, 1);
     else if (kd == 3) FISE_AT(3, 2);
     else if (kd == 4) FISE_AT(4, 2);
+    else if (d == 80) FISE_AT_EXACT(5, 3);
     else if (kd == 5) FISE_AT(5, 3);
     else if (kd == 6) FISE_AT(6, 3);
     else if (kd <= 8) FISE_AT(8, 4);
+    else if (d == 160) FISE_AT_EXACT(10, 5);
     else if (kd <= 10) FISE_AT(10, 5);
     else return fail(FISE_ERR_SHAPE, "attention: head dim %d > 160", d);
 #undef FISE_AT
+#undef FISE_AT_EXACT
     }
     FISE_CHECK_LAUNCH("attention");
     if (splits > 1) {
