@@ -63,6 +63,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
     constexpr int CPR = OW / 4, IPG = GROWS * CPR / NT, ITEMS = GROUPS * IPG;      // four-column pieces per row, per thread and group, per thread
     constexpr unsigned OOB = 0x80000000u;               // beyond every descriptor: the load returns zeros
     static_assert(GROWS * CPR % NT == 0 && (SHARED ? 1 : NW) * NST * STAGE >= NW * GROWS * PITCH * 4, "tile");
+    constexpr bool CONV = TN == 5;                      // the block tile: one map out, bf16 map as residual
     static_assert(!SHARED || (NW == 4 && NST >= 3), "a shared stage has one 16-deep slice of K per wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];      // [NW or 1][NST][STAGE], later [NW][GROWS][PITCH] floats
 
@@ -171,9 +172,9 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
 
     // ---- this thread's pieces of the finished tile (four columns of a row, or four rows of a column) and their operands
     const int col0 = by * OW;
-    const int sect = (col0 >= a.sect_n) + (col0 >= 2 * a.sect_n);      // a column tile lies in one section (checked by the launcher)
-    const int omode = sect == 0 ? a.out_mode[0] : sect == 1 ? a.out_mode[1] : a.out_mode[2];
-    const bool trans = omode == OUT_TOKENS_T && a.trans4;
+    const int sect = CONV ? 0 : (col0 >= a.sect_n) + (col0 >= 2 * a.sect_n);      // a column tile lies in one section (checked by the launcher)
+    const int omode = CONV ? OUT_MAP : sect == 0 ? a.out_mode[0] : sect == 1 ? a.out_mode[1] : a.out_mode[2];
+    const bool trans = !CONV && omode == OUT_TOKENS_T && a.trans4;
     int e_r[ITEMS], e_c[ITEMS], e_b[ITEMS]; unsigned e_pix[ITEMS]; bool e_ok[ITEMS];
     auto place_items = [&]() {
 #pragma unroll
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
     auto fetch_operands = [&](int grp) {                       // an absent operand has a descriptor of size zero: no branches, no waits
         const __amdgpu_buffer_rsrc_t s_bias = buf(a.bias, a.bias_bytes), s_bias2 = buf(a.bias2, a.bias2_bytes),
                                      s_temb = buf(a.temb, a.temb_bytes), s_res = buf(a.res, a.res_bytes);
-        const int res_shift = a.res_compact == 2 ? 2 : 1;       // float rows / bf16 (16 bytes are fetched either way, 8 of them used)
+        const int res_compact = CONV ? 0 : a.res_compact, res_shift = res_compact == 2 ? 2 : 1;       // float rows / bf16 (16 bytes are fetched either way, 8 of them used)
 #pragma unroll
         for (int it = 0; it < IPG; ++it) {
             const unsigned no = e_ok[grp * IPG + it] && !trans ? 0u : OOB, col = (unsigned)(col0 + e_c[grp * IPG + it]);
@@ -199,8 +200,9 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
             if constexpr (GEGLU) {
                 e_gate[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, ((col + a.N) * 2u) | no, 0, 0));
             } else {
-                const unsigned r = __umul24(a.res_compact ? (unsigned)(m0 + e_r[grp * IPG + it]) : e_pix[grp * IPG + it], (unsigned)a.N) + col;
-                e_res[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_res, (r << res_shift) | no, 0, 0));
+                const unsigned r = __umul24(res_compact ? (unsigned)(m0 + e_r[grp * IPG + it]) : e_pix[grp * IPG + it], (unsigned)a.N) + col;
+                if constexpr (CONV) e_res[it].xy = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_res, (r << 1) | no, 0, 0));
+                else e_res[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_res, (r << res_shift) | no, 0, 0));
                 if constexpr (AM == A_MAP) {
                     e_bias2[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias2, (col * 2u) | no, 0, 0));
                     e_temb[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_temb, ((__umul24((unsigned)e_b[grp * IPG + it], (unsigned)a.temb_stride) + col) * 4u) | no, 0, 0));
@@ -471,6 +473,54 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
     // ---- epilogue: sum, biases, gate, then time projection + residual as one term; stores
     bf16_t* const outp = sect == 0 ? a.out[0] : sect == 1 ? a.out[1] : a.out[2];
     const int scol0 = col0 - sect * a.sect_n;
+    if constexpr (CONV) {
+        // A group's results are packed in registers, the next group's operands requested, and only then stored: behind the
+        // stores the loads would wait for them.
+#pragma unroll
+        for (int grp = 0; grp < GROUPS; ++grp) {
+            u32x2_w y[IPG], yv[IPG][2];
+#pragma unroll
+            for (int it = 0; it < IPG; ++it) {
+                const f32x4_w sum = v[grp * IPG + it];
+                float x[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    auto part = [q](const u32x2_w& w) { return q & 1 ? hi16(w[q >> 1]) : lo16(w[q >> 1]); };
+                    const float res = part(u32x2_w{e_res[it][0], e_res[it][1]});
+                    x[q] = sum[q] + part(e_bias[it]);
+                    x[q] += part(e_bias2[it]);
+                    x[q] += res + __uint_as_float(e_temb[it][q]);
+                }
+                y[it] = u32x2_w{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (i < a.nview) {                  // as put_views4
+                        float u[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const u32x4_w& ss = e_ss[it][i][q >> 1];
+                            u[q] = fmaf(q & 1 ? hi16(y[it][q >> 1]) : lo16(y[it][q >> 1]), __uint_as_float(ss[(q & 1) * 2]), __uint_as_float(ss[(q & 1) * 2 + 1]));
+                        }
+                        if (a.view[i].silu) {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) u[q] = silu_f(u[q]);
+                        }
+                        yv[it][i] = u32x2_w{f2bf2(u[0], u[1]), f2bf2(u[2], u[3])};
+                    }
+            }
+            if (grp + 1 < GROUPS) fetch_operands(grp + 1);
+#pragma unroll
+            for (int it = 0; it < IPG; ++it) {
+                const int e = grp * IPG + it;
+                if (!e_ok[e]) continue;
+                *(FISE_AS1 u32x2_w*)(outp + (size_t)e_pix[e] * a.N + col0 + e_c[e]) = y[it];
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (i < a.nview) *(FISE_AS1 u32x2_w*)(a.view[i].dst + (size_t)e_pix[e] * a.view[i].dstC + a.view[i].c_off + col0 + e_c[e]) = yv[it][i];
+            }
+        }
+        return;
+    }
     if (trans) {
         const unsigned HW = (unsigned)(a.Ho * a.Wo);
 #pragma unroll
@@ -622,7 +672,7 @@ int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
     const int max_s = ws && ws->counters && ws->partial ? 8 : 1;
     for (const TileShape& sh : kShapes) {
         if (a.geglu && sh.tn == 1) continue;
-        if (sh.kind == BLOCK && (a.a_compact || a.N % 160 || a.nsect > 1)) continue;
+        if (sh.kind == BLOCK && (a.a_compact || a.N % 160 || a.nsect > 1 || a.out_mode[0] != OUT_MAP || (a.res && a.res_compact))) continue;
         const int gx = ceil_div(rows, 32 * sh.tm), gy = ceil_div(ncols, 32 * sh.tn);
         for (int s = 1; s <= max_s; ++s) {
             const int per = ceil_div(nsteps, s);
