@@ -214,7 +214,8 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
 #pragma unroll
         for (int i = 0; i < DB; ++i)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) oacc[i][e] *= alpha;
+            for (int e = 0; e < 16; ++e)
+                if (i * 32 + (e >> 2) * 8 < DP) oacc[i][e] *= alpha;      // (rows past the head dim are not stored)
 
         // ---- O^T += V^T P^T : four 16-key steps; the key order inside a step follows the accumulator layout
 #pragma unroll
