@@ -38,15 +38,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned by
 __device__ __forceinline__ float lo16(unsigned w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi16(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
 
-// x * Phi(x) with Phi from the complementary error function of |x| / sqrt 2 (Abramowitz & Stegun 7.1.26: absolute error
-// below 1.5e-7, and for negative x no cancellation against 1)
-__device__ __forceinline__ float gelu_f(float x) {
-    const float u = fabsf(x) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, u, 1.0f));
-    const float p = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f), -0.284496736f), 0.254829592f);
-    const float e = 0.5f * p * __builtin_amdgcn_exp2f(-1.4426950408889634f * u * u);      // half of erfc(u)
-    return x * (x < 0.f ? e : 1.0f - e);
-}
+__device__ __forceinline__ float gelu_f(float x) { return x * (0.5f * (1.0f + erff(x * 0.70710678118654752f))); }
 #endif
 
 // SHARED: one ring for the workgroup instead of one per wave, see the launcher.
