@@ -333,7 +333,7 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
                      float scale, void* out, void* ws, size_t ws_bytes, hipStream_t st) {
     if (M <= 0) return FISE_OK;
     const int d = C / heads;
-    const int kd = ceil_div(d, 16), db = ceil_div(d, 32);
+    const int kd = ceil_div(d, 16);
     int splits = attention_splits(B, M, n_keys, heads);
     if (splits > 1 && (!ws || ws_bytes < attention_workspace_bytes(B, M, n_keys, C, heads))) splits = 1;
     float* part_o = (float*)ws;

@@ -1,0 +1,44 @@
+"""GPU parity of the fp32 convolution of a few tiles (K range shared by the waves of a workgroup) at the edges of its tiles, of its
+batches of K units and of the rule that chooses it, against the oracle's masked convolution."""
+import math
+import zlib
+
+import numpy as np
+import pytest
+
+from oracle import fise_oracle as fo
+from paper_2305_17423_amd import workloads as wl
+from helpers import dev, host, idx_dev, active_mask, check_map
+
+pytestmark = pytest.mark.gpu
+CASES = [
+    # name, B, H(out), W(out), Cin, Cout, k, stride, ups, tile, tiles, temb, res
+    ("one-row-two-units", 1, 8, 8, 16, 4, 1, 1, 0, 1, 1, False, False),               # six of eight waves without work
+    ("33-rows-ragged-columns", 1, 8, 8, 48, 36, 3, 1, 0, 1, 33, True, True),           # 54 units: batches end inside
+    ("border-tiles", 2, 8, 8, 64, 64, 3, 1, 0, 4, 4, False, True),                     # 72 units, one more than a batch of eight waves
+    ("stride-2", 2, 8, 8, 128, 32, 3, 2, 0, 2, 5, True, False),
+    ("upsample", 1, 16, 16, 32, 68, 3, 1, 1, 4, 7, False, False),
+    ("256-tiles", 2, 64, 32, 16, 64, 3, 1, 0, 8, 32, False, False),                    # 128 x 2 tiles: the last launch shape of this kernel
+    ("258-tiles", 1, 64, 72, 16, 36, 3, 1, 0, 4, 258, False, True),                    # the staged kernel
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_conv_f32_few_tiles(case):
+    from paper_2305_17423_amd import binding as fb
+    name, B, Ho, Wo, Ci, Co, k, stride, ups, t, n, use_temb, use_res = case
+    rng = np.random.default_rng(zlib.crc32(name.encode()))
+    H, W = (Ho // 2, Wo // 2) if ups else (Ho * stride, Wo * stride)
+    x = wl.normal(rng, (B, H, W, Ci), 1.0)
+    w = wl.normal(rng, (Co, k, k, Ci), 1 / math.sqrt(k * k * Ci))
+    bias = wl.normal(rng, (Co,), 0.1)
+    temb = wl.normal(rng, (B, Co), 0.3) if use_temb else None
+    res = wl.normal(rng, (B, Ho, Wo, Co), 1.0) if use_res else None
+    cache = wl.normal(rng, (B, Ho, Wo, Co), 1.0)
+    ix = np.sort(rng.choice((Ho // t) * (Wo // t), n, replace=False)).astype(np.int32)
+    want = fo.masked_conv(x, w, bias, ix, t, cache.astype(np.float64).copy(), "f32", stride=stride, upsample=bool(ups), temb=temb, residual=res)
+    y, xd, wd, bd, ixd = dev(cache), dev(x), dev(w), dev(bias), idx_dev(ix)
+    tembd, resd = dev(temb) if use_temb else None, dev(res) if use_res else None
+    fb.fise_masked_conv(fb.conv_args(xd, wd, bd, ixd, n, t, y, ksize=k, stride=stride, upsample=ups, temb=tembd, residual=resd), None)
+    # K <= 1152 float products and sums: K 2^-24 = 7e-5 of the largest term at worst, 1e-5 as the sums here go
+    check_map(host(y), want, cache.astype(np.float64), active_mask(ix, t, Ho, Wo), 1e-5, name)
