@@ -80,7 +80,7 @@ int run_resnet(const fise_resnet_args* a, void* ws, const IgemmWorkspace* iw, hi
     // the normalised + activated input (active tiles and their ring) is written once, then convolved
     if (!have_acts)
         if (int e = launch_gn_act_halo(a->x0, a->x1, a->C0, a->C1, B, H, W, a->gn1_mean, a->gn1_rstd, a->gn1_gamma, a->gn1_beta, a->G, 1,
-                                       a->tile_idx, a->n_active, a->tile, act1, st)) return e;
+                                       a->tile_idx, a->n_active, a->tile, act1, st, iw)) return e;
     IgemmArgs c1 = conv_args(act1, nullptr, Ci, 0, B, H, W, H, W, 3, 1, 0, a->conv1_w, a->conv1_b, Co, a->tile_idx,
                              a->n_active, a->tile, a->h1_cache);
     c1.temb = a->temb; c1.temb_stride = a->temb_stride;

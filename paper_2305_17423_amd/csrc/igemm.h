@@ -164,9 +164,10 @@ int launch_gn_scale_shift(const float* mean, const float* rstd, const void* gamm
 int launch_gn_stats_table(const void* x0, const void* x1, int B, int H, int W, int C0, int C1, int G, float eps, float* mean, float* rstd,
                           const void* gamma, const void* beta, float2* ss, void* workspace, hipStream_t st);
 // act[B,H,W,C0+C1] = GroupNorm(x0|x1) (+SiLU) with the given statistics at the active tiles and their one-pixel ring.
+// iw: scratch of the GEMMs that follow on the stream; its arrival counters are zeroed on the way if they are not yet.
 int launch_gn_act_halo(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, const float* mean, const float* rstd,
                        const void* gamma, const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act,
-                       hipStream_t st);
+                       hipStream_t st, const IgemmWorkspace* iw = nullptr);
 // ws: scratch for the key-split partials (attention_workspace_bytes; null or too small = no key split)
 size_t attention_workspace_bytes(int B, int M, int n_keys, int C, int heads);
 int launch_attention(const void* q, const void* K, const void* Vt, int B, int M, int n_keys, int n_stride, int C,

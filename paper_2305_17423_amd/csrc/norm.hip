@@ -154,7 +154,9 @@ __global__ __launch_bounds__(256) void gn_act_halo_kernel(const bf16_t* __restri
                                                           int C1, int H, int W, const float* __restrict__ mean,
                                                           const float* __restrict__ rstd, const bf16_t* __restrict__ gamma,
                                                           const bf16_t* __restrict__ beta, int G, int silu,
-                                                          const int* __restrict__ tile_idx, int tile, bf16_t* __restrict__ act) {
+                                                          const int* __restrict__ tile_idx, int tile, bf16_t* __restrict__ act,
+                                                          int* __restrict__ zero, int n_zero) {
+    for (int i = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < n_zero; i += gridDim.x * gridDim.y * gridDim.z * 256) zero[i] = 0;
     const int C = C0 + C1, chunks = C / 8, side = tile + 2;
     const int t = tile_idx[blockIdx.x], b = blockIdx.y;
     const int tiles_w = W / tile;
@@ -218,13 +220,17 @@ int launch_gn_scale_shift(const float* mean, const float* rstd, const void* gamm
 
 int launch_gn_act_halo(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, const float* mean, const float* rstd,
                        const void* gamma, const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act,
-                       hipStream_t st) {
+                       hipStream_t st, const IgemmWorkspace* iw) {
     if (n_active <= 0) return FISE_OK;
+    // a launch of its own for the counters costs 2.7 us (a ResNet block of 160 rows x 1280 channels takes 67)
+    const bool zero = iw && iw->counters && !iw->counters_zeroed;
     const int items = (tile + 2) * (tile + 2) * ((C0 + C1) / 8);
     const int z = std::max(1, std::min(64, ceil_div(items, 512)));
     hipLaunchKernelGGL(gn_act_halo_kernel, dim3(n_active, B, z), dim3(256), 0, st, (const bf16_t*)x0, (const bf16_t*)x1, C0, C1, H, W,
-                       mean, rstd, (const bf16_t*)gamma, (const bf16_t*)beta, G, silu, tile_idx, tile, (bf16_t*)act);
+                       mean, rstd, (const bf16_t*)gamma, (const bf16_t*)beta, G, silu, tile_idx, tile, (bf16_t*)act,
+                       zero ? iw->counters : nullptr, zero ? IGEMM_COUNTERS : 0);
     FISE_CHECK_LAUNCH("gn activation with halo");
+    if (zero) iw->counters_zeroed = true;
     return FISE_OK;
 }
 
