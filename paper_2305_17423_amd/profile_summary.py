@@ -52,11 +52,12 @@ def short(name: str) -> str:
 def kind_of(name: str):
     """The fise_profile_read kind (as bench.py names it) a profiler kernel name belongs to, or None."""
     n = short(name)
-    if "wave_gemm_kernel" in n and "true>" in n or "igemm_dma_kernel<64, 128, 2, 2" in n or "igemm_dma_kernel<32, 256" in n:
+    wave = re.search(r"wave_gemm_kernel<\d+, \d+, \d+, \d+, (\d), (true|false), (?:true|false)>", n)      # A operand, GEGLU, ring
+    if wave and wave[2] == "true" or "igemm_dma_kernel<64, 128, 2, 2" in n or "igemm_dma_kernel<32, 256" in n:
         return "wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>"
-    if "wave_gemm_kernel" in n and ", 0, false>" in n:
+    if wave and wave[1] == "0":
         return "wave_gemm_kernel<*,A_ROWS>"
-    if "wave_gemm_kernel" in n or "igemm_dma_kernel<64, 64, 2, 2" in n:
+    if wave or "igemm_dma_kernel<64, 64, 2, 2" in n:
         return "wave_gemm_kernel<*,A_MAP> / igemm_dma_kernel<64,64,*>"
     if "igemm_dma_kernel<64, 128, 2, 4" in n:
         return "igemm_dma_kernel<64,128,2,4,3,*>"
