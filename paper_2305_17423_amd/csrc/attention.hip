@@ -11,12 +11,12 @@
 // one is being multiplied; the LDS hand-over uses a barrier that does not wait for
 // those loads.
 #include <algorithm>
+#include "attention_keys.h"
 #include "igemm.h"
 #include "profile.h"
 
 namespace fise {
 
-constexpr int AT_BKV = 64;        // keys per block
 constexpr int AT_QW = 32;         // queries per wave
 constexpr int AT_WAVES = 4;
 constexpr int AT_BQ = AT_QW * AT_WAVES;
@@ -84,9 +84,10 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
     // K rows of d / 8 chunks (key e / dchunks, chunk e % dchunks), V^T rows of 8 chunks (row e / 8 < d, keys
     // (e % 8) * 8 ..).  Everything that depends only on the slot is worked out once; a block costs one pointer
     // bump and one load per slot.  The head-dim columns of the K tile past d are zeroed once and never written
-    // again (V^T rows past d only reach output rows that are not stored).  Keys that do not exist can only occur in the last block of the whole range: its loads go
-    // to the nearest key that exists (all of them unconditional: behind a branch each, they were a round trip each) and
-    // what they bring is replaced by zeros on the way into the LDS tiles.
+    // again (V^T rows past d only reach output rows that are not stored).  Keys that do not exist can only occur in the
+    // last block of the whole range, which may be the first: its loads go to the last key, or chunk of eight, that exists
+    // (attention_keys.h; all of them unconditional: behind a branch each, they were a round trip each) and what
+    // they bring is replaced by zeros on the way into the LDS tiles.
     constexpr int PFD = (KL + VL <= 6) ? 2 : 1;       // key blocks in flight (small heads can afford two in registers)
     uint4 rk[PFD][KL], rv[PFD][VL];
     const bf16_t* pk[KL]; const bf16_t* pv[VL];        // source of the slot in key block 0
@@ -121,9 +122,9 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
         } else {
             const int last = n_keys - 1 - k0;            // last key of the block
 #pragma unroll
-            for (int j = 0; j < KL; ++j) rk[slot][j] = *reinterpret_cast<const uint4*>(pk[j] + ((long long)k0 + min(0, last - kkey[j])) * C);
+            for (int j = 0; j < KL; ++j) rk[slot][j] = *reinterpret_cast<const uint4*>(pk[j] + (long long)at_key_shift(k0, last, kkey[j]) * C);
 #pragma unroll
-            for (int j = 0; j < VL; ++j) rv[slot][j] = *reinterpret_cast<const uint4*>(pv[j] + (vkey[j] <= last ? k0 : 0));
+            for (int j = 0; j < VL; ++j) rv[slot][j] = *reinterpret_cast<const uint4*>(pv[j] + at_value_shift(k0, last, vkey[j]));
         }
     };
     auto stash = [&](int blk, int slot) {
