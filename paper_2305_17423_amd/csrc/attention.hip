@@ -24,7 +24,11 @@ constexpr int AT_BQ = AT_QW * AT_WAVES;
 __device__ __forceinline__ void at_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // KD: 16-wide steps over the head dim; DB: 32-row blocks of the output head dim; EXACT: the head dim is 16 KD (80, 160: the set-up
-// of a short launch is instructions, and most of its conditions and address terms are constants then)
+// of a short launch is instructions, and most of its conditions and address terms are constants then).
+// What bounds it: few queries, the round trips of the key blocks (~0.9 us each with two blocks in flight, heads up to 96; ~2 us
+// with one); many queries, the exponentials and the other ~100 vector instructions per 64 keys.  The wide heads sit right below
+// 256 registers, where a CU still holds two workgroups: 2 x 4096 queries and keys of 8 x 160 channels 226 us, at 262
+// registers 325.
 template <int KD, int DB, bool EXACT>
 __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K,
                                                         const bf16_t* __restrict__ Vt, int B, int M, int n_keys, int n_stride,
@@ -91,25 +95,24 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
     constexpr int PFD = (KL + VL <= 6) ? 2 : 1;       // key blocks in flight (small heads can afford two in registers)
     uint4 rk[PFD][KL], rv[PFD][VL];
     const bf16_t* pk[KL]; const bf16_t* pv[VL];        // source of the slot in key block 0
-    int kkey[KL], vkey[VL];                            // first key of the slot within a block (-1: slot unused)
+    int kkey[KL];                                      // key of the K slot within a block (-1: slot unused)
+    const int vkey = (tid & 7) * 8;                    // first key of the V^T slots (256 threads: whole rows of 8 chunks)
     bf16_t* sk[KL]; bf16_t* sv[VL];                    // destination in the LDS tiles
+    auto v_used = [&](int j) { return (EXACT && VCH == 256 * VL && DB * 32 == DP) || ((tid + 256 * j) >> 3) < d; };
 #pragma unroll
     for (int j = 0; j < KL; ++j) {
         const int e = tid + 256 * j;
         const int kk = EXACT ? e / (DP / 8) : (e * chunk_mul) >> 16, c8 = e - kk * dchunks;      // e / dchunks: e < 1280, dchunks <= 20
-        const bool used = e < AT_BKV * dchunks;
+        const bool used = (EXACT && KCH == 256 * KL) || e < AT_BKV * dchunks;
         kkey[j] = used ? kk : -1;
         pk[j] = K + (used ? ((size_t)b * n_keys + kk) * C + h * d + c8 * 8 : 0);
         sk[j] = &Ks[used ? kk : 0][used ? c8 * 8 : 0];
     }
 #pragma unroll
-    for (int j = 0; j < VL; ++j) {
-        const int e = tid + 256 * j;
-        const int r = e >> 3, c8 = e & 7;
-        const bool used = r < d;
-        vkey[j] = used ? c8 * 8 : -1;
-        pv[j] = Vt + (used ? ((size_t)b * C + h * d + r) * n_stride + c8 * 8 : 0);
-        sv[j] = &Vs[used ? r : 0][used ? c8 * 8 : 0];
+    for (int j = 0; j < VL; ++j) {                     // (unused: the chunk of the same keys in the first row)
+        const int r = (tid + 256 * j) >> 3;
+        pv[j] = Vt + (v_used(j) ? ((size_t)b * C + h * d + r) * n_stride : 0) + vkey;
+        sv[j] = &Vs[v_used(j) ? r : 0][vkey];
     }
     for (int e = tid; e < AT_BKV * (DP / 8 - dchunks); e += 256) *reinterpret_cast<uint4*>(&Ks[e % AT_BKV][d + e / AT_BKV * 8]) = make_uint4(0, 0, 0, 0);
     auto fetch = [&](int blk, int slot) {
@@ -124,7 +127,10 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
 #pragma unroll
             for (int j = 0; j < KL; ++j) rk[slot][j] = *reinterpret_cast<const uint4*>(pk[j] + (long long)at_key_shift(k0, last, kkey[j]) * C);
 #pragma unroll
-            for (int j = 0; j < VL; ++j) rv[slot][j] = *reinterpret_cast<const uint4*>(pv[j] + at_value_shift(k0, last, vkey[j]));
+            for (int j = 0; j < VL; ++j) rv[slot][j] = *reinterpret_cast<const uint4*>(pv[j] + at_value_shift(k0, last, vkey));
+            // keeps the loads of the two branches apart: merged, every whole block pays for selecting its shifts (2 x 4096
+            // queries and keys of 8 x 160 channels 229 -> 226 us, 2 x 192 queries 256 keys 14.2 -> 13.5)
+            asm volatile("");
         }
     };
     auto stash = [&](int blk, int slot) {
@@ -135,7 +141,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
                 if (kkey[j] >= nk) rk[slot][j] = make_uint4(0, 0, 0, 0);
 #pragma unroll
             for (int j = 0; j < VL; ++j) {
-                const int nv = nk - vkey[j];             // keys of this chunk that exist
+                const int nv = nk - vkey;             // keys of this chunk that exist
                 auto keep = [&](unsigned w, int t) { return nv > t + 1 ? w : nv > t ? w & 0xffffu : 0u; };
                 const uint4 v = rv[slot][j];
                 rv[slot][j] = make_uint4(keep(v.x, 0), keep(v.y, 2), keep(v.z, 4), keep(v.w, 6));
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
             if (kkey[j] >= 0) *reinterpret_cast<uint4*>(sk[j]) = rk[slot][j];
 #pragma unroll
         for (int j = 0; j < VL; ++j)
-            if (vkey[j] >= 0) *reinterpret_cast<uint4*>(sv[j]) = rv[slot][j];
+            if (v_used(j)) *reinterpret_cast<uint4*>(sv[j]) = rv[slot][j];
     };
 
     if (blk0 < blk1) {

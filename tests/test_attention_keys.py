@@ -9,7 +9,8 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "paper_2305_17423_amd", "csrc", "attention_keys.h")
 N_KEYS = 200
-# one line per (number of keys, block, key of the slot): both shifts; slots that hold nothing carry key -1
+# one line per (number of keys, block, key of the slot): both shifts; K slots that hold nothing carry key -1, V^T slots the
+# chunk of their keys in the first row
 PROGRAM = r"""
 #include <cstdio>
 #include "%s"
@@ -44,9 +45,9 @@ def test_key_rows_stay_inside(shifts):
 
 
 def test_value_chunks_stay_inside_the_shortest_row(shifts):
-    s = shifts[(shifts[:, 2] % 8 == 0) | (shifts[:, 2] < 0)]
+    s = shifts[(shifts[:, 2] >= 0) & (shifts[:, 2] % 8 == 0)]
     n, k0, key, _, vs = s.T
-    first = np.maximum(key, 0) + vs
+    first = key + vs
     stride = (n + 7) // 8 * 8                           # the smallest row an entry point accepts
     over = first + 8 - stride
     assert (first >= 0).all() and (over <= 0).all(), f"up to {over.max()} elements past a row, first at {n[over > 0][:1]} keys"
