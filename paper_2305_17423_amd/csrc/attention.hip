@@ -319,19 +319,23 @@ static void launch_at(const void* q, const void* K, const void* Vt, int B, int M
                        (bf16_t*)out, part_o, part_ml);
 }
 
-// A split pays a second launch of ~5 us for the merge; a key block takes 0.6 - 1 us, so a handful of them is streamed in one go
-// (192 x 256 keys of 1280 channels: 10 + 4.5 us with two splits, 13 us without, and one launch less).
-static int attention_splits(int B, int M, int n_keys, int heads) {
+// A split pays a second launch for the merge and, with it, ~2 us per million parked elements (rows x channels x splits); it saves
+// key blocks, which cost a workgroup 0.9 us (head dim 40) to 2 us (160).  Below six blocks that never pays (four blocks of
+// 8 x 160 channels: 2 x 32 queries 11.4 us, two splits 10.8; 2 x 192 13.8 against 14.8; head dim 40 6.4 against 7.8).  Six and
+// seven blocks are four less with three splits: that is worth (d - 64) / 24 us without the parked elements (160: 4.1, 128:
+// 2.4, 80: 0.7, 64 and 40: nothing), so the line lies where both are equal (six blocks of 8 x 160 channels: 2 x 32 queries 15.5
+// us unsplit, 11.4 split; 2 x 256 17.9 and 17.5; 2 x 384 18.0 and 19.8).
+static int attention_splits(int B, int M, int n_keys, int C, int heads) {
     const int wgs = ceil_div(M, AT_BQ) * heads * B;
     const int nblocks = ceil_div(n_keys, AT_BKV);
-    if (nblocks < 8) return 1;
+    if (nblocks < 6 || (nblocks < 8 && (long long)B * M * C > (C / heads - 64) * 7000LL)) return 1;
     int s = ceil_div(640, wgs);
     s = std::min(s, nblocks / 2);
     return std::max(1, std::min(s, 32));
 }
 
 size_t attention_workspace_bytes(int B, int M, int n_keys, int C, int heads) {
-    const int s = attention_splits(B, M, n_keys, heads);
+    const int s = attention_splits(B, M, n_keys, C, heads);
     if (s <= 1) return 0;
     return align256((size_t)s * B * M * C * sizeof(float)) + align256((size_t)s * B * heads * M * 2 * sizeof(float));
 }
@@ -341,7 +345,7 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
     if (M <= 0) return FISE_OK;
     const int d = C / heads;
     const int kd = ceil_div(d, 16);
-    int splits = attention_splits(B, M, n_keys, heads);
+    int splits = attention_splits(B, M, n_keys, C, heads);
     if (splits > 1 && (!ws || ws_bytes < attention_workspace_bytes(B, M, n_keys, C, heads))) splits = 1;
     float* part_o = (float*)ws;
     float* part_ml = splits > 1 ? (float*)((char*)ws + align256((size_t)splits * B * M * C * sizeof(float))) : nullptr;

@@ -39,6 +39,8 @@ def vt_dev(V, n_stride=None, poison=False):
     (2, 16, 64, 32, 4),          # d = 8
     (1, 130, 200, 128, 4),       # d = 32, keys not a multiple of 64
     (1, 1, 8, 64, 4),            # one query, one partial block
+    (2, 16, 448, 1280, 8),       # seven blocks of wide heads, few queries: three key splits, the last of one block
+    (1, 40, 330, 1024, 8),       # d = 128, six blocks in three splits, the last partial
 ])
 def test_attention_active(fb, B, M, N, C, heads):
     rng = np.random.default_rng(4000 + M + N)
