@@ -60,6 +60,21 @@ def test_attention_active(fb, B, M, N, C, heads):
     assert err2 <= TOL["bf16"], err2
 
 
+@pytest.mark.parametrize("d", [40, 72, 80, 128, 136, 160])
+@pytest.mark.parametrize("N", [1, 9, 31, 33, 56, 57, 63, 64, 65, 120])
+def test_attention_partial_key_blocks(fb, d, N):
+    """The partial block is the first one (up to 63 keys) or a later one; head dims of the constant instantiations (80, 160), of the
+    same tiles with the head dim as an argument (72, 136) and of padded tiles; key padding of V^T holds NaN."""
+    rng = np.random.default_rng(4050 + 200 * d + N)
+    B, M, heads = 2, 35, 2
+    C = d * heads
+    q = wl.normal(rng, (B, M, C), 1.0, "bf16"); K = wl.normal(rng, (B, N, C), 1.0, "bf16"); V = wl.normal(rng, (B, N, C), 1.0, "bf16")
+    want = fo.attention_active(q, K, V, heads)
+    out = torch.zeros((B, M, C), dtype=torch.bfloat16, device=DEV)
+    fb.fise_attention_active(dev(q, "bf16"), dev(K, "bf16"), vt_dev(V, (N + 7) // 8 * 8, poison=True), heads, 1 / math.sqrt(d), out, n_keys=N)
+    assert rel_err(host(out), want) <= TOL["bf16"]
+
+
 def test_attention_closed_forms_on_device(fb):
     rng = np.random.default_rng(4100)
     B, M, N, C, heads = 1, 40, 300, 320, 8
