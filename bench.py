@@ -26,7 +26,8 @@ if ROOT not in sys.path:
 MFMA_BF16_PEAK_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 HBM_PEAK_GBS = 8000.0
 
-# fise_profile_read kinds -> the kernel a profiler lists for them
+# fise_profile_read kinds -> the kernel a profiler lists for them (behind a slash: what runs where wave_gemm does not take a launch,
+# 64x64 tiles for 2048 - 4095 compact rows, the others for odd widths only)
 KIND_NAMES = {0: "wave_gemm_kernel<*,A_MAP> / igemm_dma_kernel<64,64,*>", 1: "wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>",
               2: "attention_kernel", 3: "igemm_dma_kernel<64,128,2,4,3,*>", 4: "igemm_reduce_kernel / igemm_reduce_ln_kernel",
               5: "igemm_dma_kernel<32,128,1,4,3,*>", 6: "igemm_kernel<...> (GroupNorm prologue)", 7: "attention_merge_kernel",

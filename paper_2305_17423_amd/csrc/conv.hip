@@ -236,8 +236,8 @@ __global__ __launch_bounds__(256) void conv_f32_tile_kernel(const float* __restr
 // The same product for a few tiles, where its chain of stages and barriers is all the time there is: eight waves share the K
 // range of one 32 x 32 tile in units of (tap, 8 channels), operands go from memory into the matrix registers (a lane
 // loads four consecutive channels of its row and of its column, the two halves of a wave eight), a batch of eight units
-// is requested at once, and the waves' sums meet in LDS.  One barrier.  It reads 32-byte pieces, so from one tile per CU on the
-// staged kernel takes over.  160 rows x 64 x 576: 19.4 -> 8.9 us.
+// is requested at once, and the waves' sums meet in LDS.  One barrier.  What bounds it is the round trips of its batches (32-byte
+// pieces).  160 rows x 64 x 576: 19.4 -> 8.9 us.
 __global__ __launch_bounds__(512) void conv_f32_wave_kernel(const float* __restrict__ x, int Cin, int B, int Hin, int Win,
                                                             const float* __restrict__ w, const float* __restrict__ bias, int Cout,
                                                             int ksize, int stride, int ups, const float* __restrict__ temb,
@@ -366,7 +366,10 @@ int conv_dispatch(const fise_conv_args* a, void* workspace, size_t workspace_byt
         if (a->dtype == FISE_F32 && a->C1 == 0 && !a->gn_mean && a->C0 % 16 == 0 && a->Cout % 4 == 0) {
             const int Ma = a->n_active * a->tile * tile_cols(a), rows = a->B * Ma;
             const dim3 grid(ceil_div(rows, 32), ceil_div(a->Cout, 64)), wgrid(ceil_div(rows, 32), ceil_div(a->Cout, 32));
-            // up to one 32 x 32 tile per CU its single round trip is the shorter way; pixel numbers of the output have 32 bits
+            // Up to one 32 x 32 tile per CU it is the faster one at every size measured (8 - 256 tiles; us here / staged at 256): 3x3 of 16
+            // channels 5.3 / 8.8, 64 9.2 / 20.1, 320 27 / 84, 1280 101 / 324; 1x1 of 16 4.3 / 4.4, 64 5.2 / 5.7, 1280 15 / 39.  A second tile per CU
+            // costs a second round: at 320 tiles 1x1 of 64 channels 7.3 / 5.8, of 128 7.7 / 7.5, though 3x3 of 64 still 15 / 20.
+            // Pixel numbers of the output have 32 bits.
             if ((long long)wgrid.x * wgrid.y <= 256 && (long long)a->B * Ho * Wo < (1ll << 31)) {
                 hipLaunchKernelGGL(conv_f32_wave_kernel, wgrid, dim3(512), 0, st, (const float*)a->x0, a->C0, a->B, a->H, a->W, (const float*)a->w,
                                    (const float*)a->bias, a->Cout, a->ksize, a->stride, a->upsample ? 1 : 0, a->temb, (const float*)a->residual,

@@ -1,6 +1,10 @@
-// Gathered implicit GEMM on bf16 MFMA: the one contraction kernel behind masked
-// convolutions (3x3 / 1x1, stride 2, nearest-2x upsample, two concatenated
-// sources) and the per-token linears of the transformer blocks.  Internal.
+// Gathered implicit GEMM on bf16 MFMA behind masked convolutions (3x3 / 1x1,
+// stride 2, nearest-2x upsample, two concatenated sources) and the per-token
+// linears of the transformer blocks: one argument block, three kernels.
+// launch_igemm gives what is made of 64-channel pieces to wave_gemm_kernel
+// (wave_gemm.hip) except compact rows of one section from 2048 rows on, which
+// igemm_dma_kernel takes; a GroupNorm prologue and 32-channel pieces go to
+// igemm_kernel (both igemm.hip).  Internal.
 #pragma once
 #include "common.h"
 

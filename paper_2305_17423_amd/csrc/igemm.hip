@@ -7,6 +7,9 @@
 // is packed in HBM.  The optional second product is a 1x1 convolution of other
 // maps at the same pixel (the ResNet shortcut), accumulated into the same tile.
 //
+// Most launches of a step go to wave_gemm.hip; here are the linears of dense-sized row
+// counts (igemm_dma_kernel), what has a GroupNorm prologue or 32-channel pieces
+// (igemm_kernel), and the few shapes that wave_gemm_takes refuses.
 // The masked problems are small (a few GFLOP, often a few dozen rows against tens
 // of MB of weights), so both kernels here are built to keep memory requests in
 // flight rather than to maximise MFMA issue: the K loop moves 64 elements per step,
@@ -1184,6 +1187,9 @@ int launch_igemm(const IgemmArgs& a, const IgemmWorkspace* ws, hipStream_t st) {
             return fail(FISE_ERR_SHAPE, "igemm: normalised copy %d: channels %d + %d of %d", i, a.view[i].c_off, a.N, a.view[i].dstC);
     // all but compact rows of one section from 2048 rows on, and what is not made of 64-channel pieces
     if (wave_gemm_takes(a)) return launch_wave_gemm(a, ws, st);
+    // The LDS-direct kernel then runs linears of 64 x 64 (below 4096 rows) and 64 x 128 tiles; its other tiles, and any tile over maps, only
+    // where the output width is no multiple of 4, several outputs are no multiples of 64 wide, an array has 2^24 pixels or float rows
+    // fill 2 GiB.  The register-staged kernel uses them all.
     const bool wide = rows >= 4096 && a.N >= 128;          // dense-sized problems: 64x128 tiles, 8 waves
     if (a.geglu) {
         if (rows <= 32) return launch_cfg<32, 256, 1, 4>(a, ws, PROF_IGEMM_GEGLU, st);

@@ -2,11 +2,14 @@
 //
 //   out[row, n] = epilogue( sum_k A[row, k] * W[n, k]  (+ sum_k A2[row, k] * W2[n, k]) )      (see igemm.h)
 //
-// What bounds the masked step is not bandwidth or MFMA rate but the fixed cost of ~200 dependent launches, and inside a
-// launch the round trips to memory.  So this kernel is built around them:
+// What bounds the masked step is not bandwidth or MFMA rate but the fixed cost of 277 dependent launches (178 of them this
+// kernel), and inside a launch the round trips to memory.  So this kernel is built around them.  What a CU gets through LDS-direct
+// loads depends on who else is at it (operand bytes over time, tiles of 32 x 32 to 64 x 160): 71 - 88 GB/s over a launch with all
+// 256 CUs busy (18 - 22 TB/s together), 110 in the K loop of 240 workgroups whose lines are in L2 (85 where they are not), 125
+// alone out of its L2.
 //  - Every wave owns the whole 32*TM x 32*TN tile for its share of K and runs it from an LDS ring of its own, filled by
-//    LDS-direct loads: no barrier in the K loop, a wave waits for its own loads only, and 4 waves x (NST - 1) stages keep
-//    64 - 100 KB per CU in flight (32 KB are enough for the 125 GB/s a CU gets out of its L2: measured).
+//    LDS-direct loads: no barrier in the K loop, a wave waits for its own loads only, and 4 waves x 2 stages of 8 - 16 KB keep
+//    32 - 128 KB per CU in flight (32 KB are enough for the 125 GB/s of a CU alone).
 //  - No row table and no barrier in front of the first load: the lanes work out their own rows (divisions by
 //    precomputed reciprocals), the weight loads of the first stages go out before the pixel of a row is known.
 //  - Everything the epilogue fetches (biases, time projection, residual, scale / shift tables) is requested before the K
@@ -129,9 +132,9 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
         if (AM == A_MAP && kw == nsteps1 && kw < ke) set_weights(true, 0);
     };
     // Where many row tiles share a slice of the weights they walk it in step, and each of its lines is cold for all of them at
-    // once: the CU's ~16 KB of loads in flight then wait for memory instead of L2 (85 GB/s per CU instead of 110).  So the
-    // row tiles first touch the slice, each a share of its lines (one dword per line, into a stage that is filled later).
-    // 1536 x 320 x 2880: K loop 6.4 -> 5.0 us; short K ranges do not earn it back.
+    // once: their loads then wait for memory instead of L2.  So the row tiles first touch the slice, each a share of its lines
+    // (one dword per line, into a stage that is filled later).  1536 x 320 x 2880 in 240 tiles: K loop 6.4 -> 5.0 us (85 -> 110
+    // GB/s per CU); short K ranges do not earn it back.
     if (a.gx >= 12 && a.kper >= 32) {
         const int c0 = bz * a.kper, c1 = min(nsteps1, c0 + a.kper);
         const __amdgpu_buffer_rsrc_t rs = buf(a.w, bytes_b);
@@ -642,7 +645,7 @@ bool wave_gemm_takes(const IgemmArgs& a) {
 // Tile and K split of a launch: the cheapest of the combinations under times measured per part of a launch (us, from time
 // stamps inside the kernel and kernel traces over the shapes of steps and dense builds).
 //  - PRIVATE, a ring per wave, 256 workgroups at once.  `fixed`: start, row positions, first loads, sum over the waves,
-//    epilogue, and the gap to the launch before.  `iter`: four K steps, one per wave (operands at the 70 - 85 GB/s a CU gets).
+//    epilogue, and the gap to the launch before.  `iter`: four K steps, one per wave (operands at the 71 - 88 GB/s a CU gets with all busy).
 //  - SHARED, 64 x 64 on one ring of 48 KB: every wave multiplies a 16-deep slice of each K step over the whole tile, so a
 //    staged byte is read once, and three workgroups per CU hide each other's start and epilogue, which many tiles of
 //    a short K consist of: `tile` + `iter` per K step of a tile and CU.  5504 x 320 x 2880 36 -> 24 us (64 x 128 tiles of
@@ -652,6 +655,10 @@ bool wave_gemm_takes(const IgemmArgs& a) {
 //    long epilogue (ten pieces per thread): 8192 x 320 x 9600 105 (SHARED) -> 64 us, 2048 x 640 x 11520 with 1x1 side product 76
 //    -> 54 us.  Widths of a 320-channel UNet are multiples of 160: no columns to spare.
 // A K split over workgroups adds parking, counting and re-reading the tiles (`park`, `park_s` per split).
+// Held against every tile and split on the 164 ResNet convolutions of a 64 x 64 x 320 / 32 x 32 x 640 / 16 x 16 x 1280 UNet with
+// 32 to 8192 rows and cold weights, the choice is 4 % from the best on average.  It is furthest off at 90 - 180 K steps and ~160 tiles
+// of 64 x 64, where it takes BLOCK in four splits or SHARED in two (2048 x 320 x 8640: 39 us, PRIVATE unsplit 29; 512 x 1280 x 5760:
+// 34 and 27): fewer than 256 workgroups get more per CU than `iter` says, and four parked BLOCK tiles cost more than `park`.
 enum { PRIVATE = 0, SHARED_RING = 1, BLOCK = 2 };
 struct TileShape { int kind, tm, tn; double fixed, tile, iter, iter_long, park, park_s; };
 static const TileShape kShapes[] = {
