@@ -60,7 +60,8 @@ struct IgemmArgs {
     int nview; GnView view[2];
     // ---- set by the launcher of the wave-split kernel: K steps per workgroup, divisors, arrival counters of split tiles,
     // whether four consecutive rows are four consecutive tokens (8-byte stores into a transposed section)
-    int kper, tt, trans4; int* counters;
+    // (PATCH: kper chunks of 64 channels and kper2 K steps of the side product)
+    int kper, kper2, touch, tt, trans4; int* counters;
     struct { const bf16_t* p; unsigned bytes, pitch; } src[4];      // A sources a0, a1, s0, s1: base, size, bytes per pixel (or row)
     unsigned bias_bytes, bias2_bytes, temb_bytes, res_bytes;        // sizes of the epilogue operands (0: absent)
     FastDiv d_gx, d_gy, d_Ma, d_tt, d_tw, d_tiles_w, d_spt;

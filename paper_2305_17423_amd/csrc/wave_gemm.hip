@@ -22,6 +22,7 @@
 // Measured against shared 64x64 tiles with a reduce launch behind every K split: step of 12 of 64 tiles 3070 -> 2590 us,
 // 2 of 70 tiles 2600 -> 1985 us, transformer block of 160 rows 92 -> 78 us.
 #include <algorithm>
+#include <type_traits>
 #include "igemm.h"
 #include "profile.h"
 
@@ -34,6 +35,41 @@ typedef float f32x4_w __attribute__((ext_vector_type(4)));
 
 enum { A_ROWS = 0, A_MAP = 1 };         // compact rows / pixels of maps (taps, two sources, side product)
 
+// ---- PATCH form (3x3, stride 1, square tiles of edge 2, 4 or 8): the pixels of a tile and their ring are brought into LDS once for 64
+// channels and read under all nine taps; the weights run through a ring of their own, a kernel row at a time.  Bound by the LDS-direct
+// loads (36 KB of weights and 8 - 32 KB of patches per chunk and column tile of 32; 0.42 us at the 125 GB/s of a CU, 0.6 - 0.7 measured)
+// and, from 20 chunks of 1280 wide layers on, by their cold weights.
+// Geometry of the patches behind the BM rows of a workgroup: strips of H x T pixels with their one-pixel ring.
+template <int BM, int T> struct Patch {
+    static constexpr int H = BM / T < T ? BM / T : T, PIX = (H + 2) * (T + 2), STRIPS = BM / (H * T);
+    static constexpr int SLOTS = (STRIPS * PIX + 31) / 32;      // 16-byte loads per lane and chunk of 64 channels
+    static constexpr int BYTES = SLOTS * 32 * 128;
+    // Segment of 16 bytes that slot 0 of patch row p holds.  The LDS serves sixteen lanes at once (0-3, 12-15, 20-23, 24-27 and so
+    // on); under every tap their sixteen pixels lie in different (row parity, segment) pairs.
+    static __device__ __forceinline__ int swizzle(int p) {
+        const int strip = p / PIX, q = p % PIX;
+        return (q % (T + 2) / 2 + T / 2 * (q / (T + 2)) + T * T / 2 * strip) & 7;
+    }
+};
+// Loads a lane issues in the steps u0 <= u < u1 (three per chunk): every step LB weight loads, the first one before them SLOTS patch loads.
+constexpr int patch_loads(int u0, int u1, int LB, int SLOTS) {
+    int n = 0;
+    for (int u = u0; u < u1; ++u) n += LB + ((u + 3000) % 3 == 0 ? SLOTS : 0);
+    return n;
+}
+constexpr int patch_min(int a, int b) { return a < b ? a : b; }
+// Loads that may be in flight when the operands of step s + 1 have to be there (s = ky of any chunk): the weights of step t went
+// out in step t - AHEAD, the patch of chunk c in step 3 (c - NPB + 1) in front of that step's weights.
+constexpr int patch_flight(int s, int AHEAD, int NPB, int LB, int SLOTS) {
+    const int w = patch_loads(s + 2 - AHEAD, s, LB, SLOTS);
+    return (s + 1) % 3 ? w : patch_min(w, LB + patch_loads(s + 5 - 3 * NPB, s, LB, SLOTS));
+}
+// The same in front of step 0, when the steps below 0 have gone out (those below -AHEAD without weights).
+constexpr int patch_flight0(int AHEAD, int NPB, int LB, int SLOTS) {
+    const int a0 = 3 - 3 * NPB, a = a0 >= -AHEAD ? LB + patch_loads(a0 + 1, 0, LB, SLOTS) : patch_loads(-AHEAD, 0, LB, SLOTS);
+    return patch_min(patch_loads(1 - AHEAD, 0, LB, SLOTS), a);
+}
+
 #if defined(__HIP_DEVICE_COMPILE__)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
@@ -45,8 +81,8 @@ __device__ __forceinline__ float gelu_f(float x) { return x * (0.5f * (1.0f + er
 #endif
 
 // SHARED: one ring for the workgroup instead of one per wave, see the launcher.
-template <int TM, int TN, int NW, int NST, int AM, bool GEGLU, bool SHARED>
-__global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_kernel(const IgemmArgs a) {
+template <int TM, int TN, int NW, int NST, int AM, bool GEGLU, bool SHARED, int PATCH = 0, int NPB = 0>
+__global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void wave_gemm_kernel(const IgemmArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 32 * TM, BN = 32 * TN, NT = 64 * NW;
     constexpr int RB = SHARED ? 8 * NW : 8;             // rows between two loads of a lane (one load of a wave fills 8 rows of 128 bytes)
@@ -54,11 +90,14 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
     constexpr int STAGE = (BM + BN) * 128;
     constexpr int PITCH = BN + 4;                       // floats per row of a partial tile in LDS
     constexpr int OW = GEGLU ? BN / 2 : BN;             // output columns of the tile
-    constexpr int GROUPS = SHARED ? TM : 1, GROWS = BM / GROUPS;       // the waves' sums are finished in groups of rows: what fits in the ring
+    constexpr int GROUPS = SHARED && !PATCH ? TM : 1, GROWS = BM / GROUPS;       // the waves' sums are finished in groups of rows: what fits in the ring
     constexpr int CPR = OW / 4, IPG = GROWS * CPR / NT, ITEMS = GROUPS * IPG;      // four-column pieces per row, per thread and group, per thread
     constexpr unsigned OOB = 0x80000000u;               // beyond every descriptor: the load returns zeros
-    static_assert(GROWS * CPR % NT == 0 && (SHARED ? 1 : NW) * NST * STAGE >= NW * GROWS * PITCH * 4, "tile");
-    constexpr bool CONV = TN == 5;                      // the block tile: one map out, bf16 map as residual
+    using PG = Patch<BM, PATCH ? PATCH : 8>;
+    constexpr int LB = 3 * BL, WSTAGE = 3 * BN * 128, NB = NST;       // PATCH: weight loads per lane and step, bytes of a step's weights, steps in LDS
+    static_assert(GROWS * CPR % NT == 0 && (PATCH ? NPB * PG::BYTES + NB * WSTAGE : (SHARED ? 1 : NW) * NST * STAGE) >= NW * GROWS * PITCH * 4, "tile");
+    static_assert(!PATCH || (SHARED && AM == A_MAP && BM <= 64 && TM + BL <= LB && NB >= 4 && NPB >= 2 && NPB <= 3), "patch form");
+    constexpr bool CONV = TN == 5 || PATCH;             // one map out, bf16 map as residual
     static_assert(!SHARED || (NW == 4 && NST >= 3), "a shared stage has one 16-deep slice of K per wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];      // [NW or 1][NST][STAGE], later [NW][GROWS][PITCH] floats
 
@@ -121,7 +160,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
     };
     unsigned char* const my_ring = ring + wave * (SHARED ? 1024 : NST * STAGE);      // where this wave's loads go
     int kw = kb;                                        // weight cursor
-    set_weights(kb >= nsteps1, kb >= nsteps1 ? kb - nsteps1 : kb);
+    if constexpr (PATCH) set_weights(false, 0); else set_weights(kb >= nsteps1, kb >= nsteps1 ? kb - nsteps1 : kb);
     auto issue_b = [&](int st) {                        // steps past the range: a descriptor of size zero, no traffic
         const __amdgpu_buffer_rsrc_t rs = buf(ptr_b, kw < ke ? bytes_b : 0u);
         unsigned char* base = my_ring + st * STAGE + BM * 128;
@@ -135,7 +174,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
     // once: their loads then wait for memory instead of L2.  So the row tiles first touch the slice, each a share of its lines
     // (one dword per line, into a stage that is filled later).  1536 x 320 x 2880 in 240 tiles: K loop 6.4 -> 5.0 us (85 -> 110
     // GB/s per CU); short K ranges do not earn it back.
-    if (a.gx >= 12 && a.kper >= 32) {
+    if (!PATCH && a.gx >= 12 && a.kper >= 32) {
         const int c0 = bz * a.kper, c1 = min(nsteps1, c0 + a.kper);
         const __amdgpu_buffer_rsrc_t rs = buf(a.w, bytes_b);
         if constexpr (SHARED) {
@@ -152,8 +191,67 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)my_ring, 4, off + (q + half) * 128, 0, 0, 0);
         }
     }
+    // PATCH: chunks of 64 channels [ch0, ch1) of the main product, K steps [sd0, sd1) of the side product; a step is the three
+    // taps of a kernel row or one K step of the side product.
+    const int nchunk = nsteps1 / 9;
+    const int ch0 = min(nchunk, bz * a.kper), ch1 = min(nchunk, ch0 + a.kper), nmain = 3 * (ch1 - ch0);
+    const int sd0 = min(nsteps - nsteps1, bz * a.kper2), nside = min(nsteps - nsteps1, sd0 + a.kper2) - sd0;
+    unsigned char* const wring = ring + NPB * PG::BYTES;       // [NB][WSTAGE] behind the patches [NPB][PG::BYTES]
+    unsigned va_s[TM], vb_s[BL], out_s[TM]; const bf16_t* ptr_s = nullptr; unsigned bytes_s = 0, soff_s = 0, end_s = 0, soff_w2 = 0;    // side product: rows, weights, cursor
+    int vstep = 0, vky = 0; unsigned wslot = 0;                // next step to request, its kernel row, its place in the ring
+    const unsigned tap_bytes = (unsigned)(a.C0 + a.C1) * 2u;
+    if constexpr (PATCH) {
+        soff_b = (unsigned)ch0 * 128u;
+        // The same first touch as above: line q of a row of W is tap q / chunks, chunk q % chunks of this range.
+        if (a.touch) {
+            const __amdgpu_buffer_rsrc_t rs = buf(a.w, bytes_b);
+            const int nch = ch1 - ch0, lines = 9 * nch;
+            const unsigned off = __umul24((unsigned)(by * BN + (lane & (BN - 1))), (unsigned)a.K * 2u) + soff_b;
+            constexpr int PER = 64 / BN;
+            for (int q = (bx * NW + wave) * PER; q < lines; q += a.gx * NW * PER) {
+                const int l = q + (PER == 2 ? lane >> 5 : 0), t = l / nch;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(wring + wave * 1024), 4, l < lines ? off + t * tap_bytes + (l - t * nch) * 128 : OOB, 0, 0, 0);
+            }
+        }
+    }
+    auto set_side = [&](int cc2) {                             // source of the side product that holds channel cc2
+        const int i = cc2 >= a.S0 ? 3 : 2;
+        ptr_s = a.src[i].p; bytes_s = a.src[i].bytes; end_s = a.src[i].pitch; soff_s = (unsigned)(cc2 - (i == 3 ? a.S0 : 0)) * 2u;
 #pragma unroll
-    for (int s = 0; s < NST; ++s) issue_b(s);
+        for (int l = 0; l < TM; ++l) va_s[l] = (__umul24(out_s[l], end_s) + seg0) | (out_s[l] & OOB);
+    };
+    // weights of the next step into its ring slot; behind the main product the rows of A and W of a side step.  LB loads always.
+    auto issue_step = [&]() {
+        unsigned char* base = wring + wslot + wave * 1024;
+        if (vstep < nmain) {
+            const __amdgpu_buffer_rsrc_t rs = buf(a.w, bytes_b);
+#pragma unroll
+            for (int l = 0; l < LB; ++l)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + l * 4096), 16, vb[l % BL], soff_b + (l / BL) * tap_bytes, 0, 0);
+            soff_b += 3 * tap_bytes;
+            if (++vky == 3) { vky = 0; soff_b += 128u - 9 * tap_bytes; }
+        } else {
+            const bool live = vstep < nmain + nside;
+            const __amdgpu_buffer_rsrc_t rs = buf(ptr_s, live ? bytes_s : 0u), rw = buf(a.w2, live ? __umul24((unsigned)a.N, (unsigned)a.K2 * 2u) : 0u);
+#pragma unroll
+            for (int l = 0; l < LB; ++l) {
+                if (l < TM) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + l * 4096), 16, va_s[l], soff_s, 0, 0);
+                else __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(base + l * 4096), 16, l < TM + BL ? vb_s[(l - TM) % BL] : OOB, soff_w2, 0, 0);
+            }
+            soff_s += 128u; soff_w2 += 128u;
+            if (soff_s == end_s && vstep + 1 < nmain + nside) set_side(a.S0);
+        }
+        ++vstep;
+        wslot = wslot == (NB - 1) * WSTAGE ? 0u : wslot + WSTAGE;
+    };
+    constexpr int FIRST_A = 3 - 3 * NPB, WAHEAD = NB - 1;      // step (before the first) in which the first patch goes out; steps the weights run ahead
+    if constexpr (PATCH) {
+#pragma unroll
+        for (int s = -WAHEAD; s < FIRST_A; ++s) issue_step();
+    } else {
+#pragma unroll
+        for (int s = 0; s < NST; ++s) issue_b(s);
+    }
 
     // ---- second half of the row: position on the output map
     unsigned ryx = rm, rpix = 0; int ry = 0, rx = 0;
@@ -255,7 +353,52 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
 #pragma unroll
         for (int j = 0; j < AL; ++j) va[j] = (__umul24(px[j], pitch) + (j & 1 ? seg1 : seg0)) | ((~valid[j] >> tap) << 31);
     };
-    if constexpr (AM == A_MAP) {
+    // PATCH: pixel (24 bits), segment (3 bits above) of every patch row this lane loads, address in the current source; cursor: chunk, place in LDS
+    unsigned px_p[PG::SLOTS], va_p[PG::SLOTS], soff_p = 0, end_p = 0, pslot = 0; int chunk_p = ch0;
+    const bf16_t* ptr_p = nullptr; unsigned bytes_p = 0;
+    auto set_patch_source = [&](int cc0) {
+        const int i = cc0 >= a.C0 ? 1 : 0;
+        ptr_p = a.src[i].p; bytes_p = a.src[i].bytes; end_p = a.src[i].pitch; soff_p = (unsigned)(cc0 - (i ? a.C0 : 0)) * 2u;
+#pragma unroll
+        for (int j = 0; j < PG::SLOTS; ++j) va_p[j] = (__umul24(px_p[j], end_p) + (px_p[j] >> 20 & 0x70u)) | (px_p[j] & OOB);
+    };
+    auto issue_patch = [&]() {                                 // SLOTS loads always
+        const __amdgpu_buffer_rsrc_t rs = buf(ptr_p, chunk_p < ch1 ? bytes_p : 0u);
+        unsigned char* base = ring + pslot + wave * 1024;
+#pragma unroll
+        for (int j = 0; j < PG::SLOTS; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + j * 4096), 16, va_p[j], soff_p, 0, 0);
+        ++chunk_p; soff_p += 128u;
+        pslot = pslot == (NPB - 1) * PG::BYTES ? 0u : pslot + PG::BYTES;
+        if (soff_p == end_p && chunk_p < ch1) set_patch_source(a.C0);
+    };
+    if constexpr (PATCH) {
+        // lane's patch rows: strip, row and column in the ringed strip; the strip's first output pixel is known to the lane of its row
+#pragma unroll
+        for (int j = 0; j < PG::SLOTS; ++j) {
+            const int p = j * 32 + lrow, strip = p / PG::PIX, q = p - strip * PG::PIX, r0 = strip * (PG::H * PATCH);
+            const int iy = __shfl(ry, r0 & (BM - 1)) - 1 + q / (PATCH + 2), ix = __shfl(rx, r0 & (BM - 1)) - 1 + q % (PATCH + 2), b = __shfl((int)rb, r0 & (BM - 1));
+            const bool in = strip < PG::STRIPS && m0 + r0 < rows && (unsigned)iy < (unsigned)a.Hin && (unsigned)ix < (unsigned)a.Win;
+            const unsigned pix = __umul24(__umul24((unsigned)b, (unsigned)a.Hin) + iy, (unsigned)a.Win) + ix;
+            px_p[j] = in ? pix | (unsigned)((lane & 7) ^ PG::swizzle(p)) << 24 : OOB;
+        }
+        set_patch_source(ch0 * 64);
+        if (nside > 0) {
+            const unsigned o0 = my_row < rows ? rpix : OOB;
+#pragma unroll
+            for (int l = 0; l < TM; ++l) out_s[l] = (unsigned)__shfl((int)o0, l * 32 + lrow);
+            const unsigned pitch2 = (unsigned)a.K2 * 2u;
+#pragma unroll
+            for (int l = 0; l < BL; ++l) vb_s[l] = __umul24((unsigned)(by * BN + l * 32 + lrow), pitch2) + seg0;
+            soff_w2 = (unsigned)sd0 * 128u;
+            set_side(sd0 * 64);
+        }
+#pragma unroll
+        for (int s = FIRST_A; s < 0; ++s) {
+            if (s % 3 == 0) issue_patch();
+            if (s >= -WAHEAD) issue_step();
+        }
+    } else if constexpr (AM == A_MAP) {
         // pixel under tap (0, 0) and which taps lie inside the image, worked out for this lane's row, then dealt out
         const int pad = a.ksize >> 1, iy = ry * a.stride - pad, ix = rx * a.stride - pad;
         const int hh = a.Hin << a.ups, ww = a.Win << a.ups;
@@ -302,6 +445,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
             }
         }
     };
+    if constexpr (!PATCH)
 #pragma unroll
     for (int s = 0; s < NST; ++s) issue_a(s);
 
@@ -319,7 +463,82 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 ? 3 : 1) void wave_gemm_
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
     int st = 0;
-    if constexpr (SHARED) {
+    if constexpr (PATCH) {
+        // Every wave multiplies its 16-deep slice of 64 channels over the whole tile.  Behind each product of step s its registers
+        // take the operands of step s + 1, which have landed in LDS for all waves (the barrier says so); that barrier
+        // also says that every wave is done with what step s - 1 read, which is refilled.
+        const int slice = wave * 2 + (lane >> 5);
+        unsigned rp[9][TM];                             // operand A under each tap: place in a patch
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int r = i * 32 + (lane & 31), q = r / (PG::H * PATCH) * PG::PIX + r % (PG::H * PATCH) / PATCH * (PATCH + 2) + r % PATCH;
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                const int p = q + t / 3 * (PATCH + 2) + t % 3;
+                rp[t][i] = (unsigned)(p * 128 + ((slice ^ PG::swizzle(p)) * 16));
+            }
+        }
+        bf16x8_t fa[3][TM], fb[3][TN];
+        auto read_b = [&](bf16x8_t (&f)[TN], unsigned slot, int row) {
+#pragma unroll
+            for (int n = 0; n < TN; ++n) f[n] = *reinterpret_cast<const bf16x8_t*>(wring + slot + rd_own + (row + n * 32) * 128);
+        };
+        auto read_a = [&](bf16x8_t (&f)[TM], unsigned patch, int tap) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) f[i] = *reinterpret_cast<const bf16x8_t*>(ring + patch + rp[tap][i]);
+        };
+        auto multiply = [&](const bf16x8_t (&x)[TM], const bf16x8_t (&w)[TN]) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int n = 0; n < TN; ++n) acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[n], x[i], acc[i][n], 0, 0, 0);
+        };
+        auto next_slot = [&](unsigned s) { return s == (NB - 1) * WSTAGE ? 0u : s + WSTAGE; };
+        unsigned rslot = 0, rpatch = 0;                 // where the step whose operands are read next lies
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(patch_flight0(WAHEAD, NPB, LB, PG::SLOTS)) : "memory");
+#pragma unroll
+        for (int j = 0; j < 3; ++j) { read_a(fa[j], 0, j); read_b(fb[j], 0, j * BN); }
+#pragma unroll 1
+        for (int c = ch0; c < ch1; ++c) {
+            auto step = [&](auto ky_) {
+                constexpr int ky = decltype(ky_)::value, after = (ky + 1) % 3;
+                asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(patch_flight(ky, WAHEAD, NPB, LB, PG::SLOTS)) : "memory");
+                if (ky == 2) rpatch = rpatch == (NPB - 1) * PG::BYTES ? 0u : rpatch + PG::BYTES;
+                rslot = next_slot(rslot);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    multiply(fa[j], fb[j]);
+                    read_a(fa[j], rpatch, after * 3 + j); read_b(fb[j], rslot, j * BN);     // behind the last chunk: not used
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (j == 0) {
+                        if (ky == 0) issue_patch();
+                        issue_step();
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            };
+            step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{}); step(std::integral_constant<int, 2>{});
+        }
+        // side product: a ring slot holds BM rows of A, then BN rows of W
+        if (nside > 0) {
+            auto read_side = [&]() {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) fa[0][i] = *reinterpret_cast<const bf16x8_t*>(wring + rslot + rd_own + i * 4096);
+                read_b(fb[0], rslot, BM);
+            };
+            read_side();
+#pragma unroll 1
+            for (int e = 0; e < nside; ++e) {
+                asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((WAHEAD - 2) * LB) : "memory");
+                rslot = next_slot(rslot);
+                multiply(fa[0], fb[0]);
+                read_side();
+                __builtin_amdgcn_sched_barrier(0);
+                issue_step();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    } else if constexpr (SHARED) {
         // Step k: the fragments of step k + 1 are requested behind the barrier that says its stage has landed for all
         // waves, the stage of step k (in registers everywhere by then) is refilled, and the matrix pipe works on step k.
         bf16x8_t f0[TM + TN], f1[TM + TN];
@@ -604,17 +823,18 @@ static void prepare(IgemmArgs& a, int ncols) {
     for (int i = 0; i < 4; ++i) a.src[i].bytes = (i < 2 ? n_in : n_out) * a.src[i].pitch;
 }
 
-template <int TM, int TN, int NST, int AM, bool GEGLU, bool SHARED = false>
+template <int TM, int TN, int NST, int AM, bool GEGLU, bool SHARED = false, int PATCH = 0, int NPB = 0>
 static int launch_tile(const IgemmArgs& a, hipStream_t st) {
-    constexpr int NW = 4, lds = (SHARED ? 1 : NW) * NST * (32 * TM + 32 * TN) * 128;
+    constexpr int NW = 4, lds = PATCH ? NPB * Patch<32 * TM, PATCH ? PATCH : 8>::BYTES + NST * 3 * 32 * TN * 128 : (SHARED ? 1 : NW) * NST * (32 * TM + 32 * TN) * 128;
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
     // raised once per instantiation (initialisation of a function-local static is thread safe)
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU, SHARED>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU, SHARED, PATCH, NPB>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return fail(FISE_ERR_HIP, "wave gemm: cannot raise the dynamic LDS limit");
     const double rows = (double)a.B * a.Ma, ncols = a.geglu ? 2.0 * a.N : a.N, K = (double)a.K + a.K2;
     {
         ProfileScope prof(GEGLU ? PROF_IGEMM_GEGLU : AM == A_MAP ? PROF_IGEMM : PROF_ROWS_GEMM, 2.0 * rows * ncols * K, 2.0 * (ncols * K + rows * (a.C0 + a.C1 + a.S0 + a.S1) + rows * a.N), st);
-        hipLaunchKernelGGL((wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU, SHARED>), dim3((unsigned)(a.gx * a.gy * a.splits)), dim3(64 * NW), lds, st, a);
+        hipLaunchKernelGGL((wave_gemm_kernel<TM, TN, NW, NST, AM, GEGLU, SHARED, PATCH, NPB>), dim3((unsigned)(a.gx * a.gy * a.splits)), dim3(64 * NW), lds, st, a);
     }
     FISE_CHECK_LAUNCH("wave gemm");
     return FISE_OK;
@@ -659,35 +879,78 @@ bool wave_gemm_takes(const IgemmArgs& a) {
 // 32 to 8192 rows and cold weights, the choice is 4 % from the best on average.  It is furthest off at 90 - 180 K steps and ~160 tiles
 // of 64 x 64, where it takes BLOCK in four splits or SHARED in two (2048 x 320 x 8640: 39 us, PRIVATE unsplit 29; 512 x 1280 x 5760:
 // 34 and 27): fewer than 256 workgroups get more per CU than `iter` says, and four parked BLOCK tiles cost more than `park`.
-enum { PRIVATE = 0, SHARED_RING = 1, BLOCK = 2 };
-struct TileShape { int kind, tm, tn; double fixed, tile, iter, iter_long, park, park_s; };
+//  - PATCHES, 3x3 convolutions of stride 1 over square tiles of edge 2, 4 or 8, `iter` per chunk of 64 channels (times `small` at edge 2,
+//    whose patches are four times the tile): the other forms bring a pixel into LDS once per tap, this one brings the tiles' patches
+//    in once, 1/5 (edge 8) to 1/2 (edge 2) of the bytes.  1376 x 640 x 5760: 23.3 -> 18.8 us, 1536 x 320 x 8640 21.7 -> 17.2, 344 x
+//    1280 x 11520 29.5 -> 23.  It loses where few rows leave a launch its fixed cost (64 rows), its set-up being longer.
+// These launches have their own table: fitted to every form and split of 127 convolutions (320 / 640 / 1280 wide, 4 to 18432 rows, tiles
+// of edge 2 to 8, cold weights), where the choice is 0.6 % from the best on average, at worst 9 %, and 10 % faster than without PATCHES.
+enum { PRIVATE = 0, SHARED_RING = 1, BLOCK = 2, PATCHES = 3 };
+struct TileShape { int kind, tm, tn; double fixed, tile, iter, iter_long, park, park_s, small; };
 static const TileShape kShapes[] = {
-    {PRIVATE, 1, 1, 4.3, 0.0, 0.39, 0.39, 2.0, 0.15}, {PRIVATE, 1, 2, 4.8, 0.0, 0.56, 0.56, 2.3, 0.3}, {PRIVATE, 2, 2, 5.8, 0.0, 0.92, 0.92, 3.2, 0.6},
-    {SHARED_RING, 2, 2, 5.2, 1.2, 0.235, 0.32, 3.2, 0.6}, {BLOCK, 2, 5, 13.0, 0.0, 0.4, 0.4, 4.0, 1.5}};
+    {PRIVATE, 1, 1, 4.3, 0.0, 0.39, 0.39, 2.0, 0.15, 1}, {PRIVATE, 1, 2, 4.8, 0.0, 0.56, 0.56, 2.3, 0.3, 1}, {PRIVATE, 2, 2, 5.8, 0.0, 0.92, 0.92, 3.2, 0.6, 1},
+    {SHARED_RING, 2, 2, 5.2, 1.2, 0.235, 0.32, 3.2, 0.6, 1}, {BLOCK, 2, 5, 13.0, 0.0, 0.4, 0.4, 4.0, 1.5, 1}};
+static const TileShape kPatchShapes[] = {
+    {PRIVATE, 1, 1, 4.4, 0.0, 0.25, 0.39, 2.0, 0.15, 1}, {PRIVATE, 1, 2, 4.8, 0.0, 0.56, 0.56, 2.5, 0.3, 1}, {PRIVATE, 2, 2, 5.8, 0.0, 0.92, 0.92, 3.2, 0.6, 1},
+    {SHARED_RING, 2, 2, 5.2, 1.2, 0.25, 0.32, 3.2, 0.6, 1}, {BLOCK, 2, 5, 11.8, 0.0, 0.4, 0.365, 4.0, 1.5, 1},
+    {PATCHES, 1, 1, 4.9, 0.0, 0.52, 0.6, 4.0, 0.15, 1}, {PATCHES, 2, 1, 6.6, 0.0, 0.69, 0.69, 3.1, 0.3, 1.1}, {PATCHES, 2, 2, 7.0, 0.0, 1.05, 1.0, 4.3, 0.6, 1.2}};
+constexpr double PATCH_SIDE = 0.25;          // a K step of the side product behind the chunks
+
+// 3x3 products over pixels of square tiles whose strips have a patch form, into one map (wider tiles, rectangles, stride 2 and upsampling
+// keep the forms that gather a tap at a time).
+static bool patch_fits(const IgemmArgs& a) {
+    return !a.a_compact && a.ksize == 3 && a.stride == 1 && !a.ups && (a.tile_w == 0 || a.tile_w == a.tile) && (a.tile == 2 || a.tile == 4 || a.tile == 8) &&
+           a.nsect == 1 && a.out_mode[0] == OUT_MAP && !(a.res && a.res_compact);
+}
+
+struct TileChoice { int kind, tm, tn, splits; };
+static TileChoice choose_tile(const IgemmArgs& a, const IgemmWorkspace* ws) {
+    const int rows = a.B * a.Ma, ncols = a.geglu ? 2 * a.N : a.N, nsteps = (a.K + a.K2) / 64;
+    TileChoice c{PRIVATE, 1, 1, 1}; double best = 1e30;
+    const int max_s = ws && ws->counters && ws->partial ? 8 : 1;
+    const bool patches = patch_fits(a);
+    const TileShape* const table = patches ? kPatchShapes : kShapes;
+    for (int i = 0; i < (int)(patches ? sizeof kPatchShapes : sizeof kShapes) / (int)sizeof(TileShape); ++i) {
+        const TileShape& sh = table[i];
+        if (a.geglu && sh.tn == 1) continue;
+        if (sh.kind == BLOCK && (a.a_compact || a.N % 160 || a.nsect > 1 || a.out_mode[0] != OUT_MAP || (a.res && a.res_compact))) continue;
+        if (sh.kind == PATCHES && sh.tm == 1 && a.tile == 2) continue;      // never the cheapest
+        const int gx = ceil_div(rows, 32 * sh.tm), gy = ceil_div(ncols, 32 * sh.tn), pieces = sh.kind == PATCHES ? a.K / 576 : nsteps;
+        for (int s = 1; s <= max_s; ++s) {
+            const int per = ceil_div(pieces, s);
+            if (s > 1 && ((sh.kind != PATCHES && per < 4) || ceil_div(pieces, per) != s)) continue;
+            if (s > 1 && ((long long)gx * gy > IGEMM_COUNTERS || (size_t)gx * gy * s * 32 * sh.tm * 32 * sh.tn * 4 > ws->partial_bytes)) break;
+            const long long n = (long long)gx * gy * s;
+            const double iter = (nsteps > 96 ? sh.iter_long : sh.iter) * (a.tile == 2 ? sh.small : 1);
+            double t = s > 1 ? sh.park + sh.park_s * s : 0.0;
+            if (sh.kind == SHARED_RING) t += sh.fixed + std::max(1.0, n / 256.0) * (sh.tile + per * iter);
+            else t += (double)((n + 255) / 256) * (sh.fixed + (sh.kind == PRIVATE ? ceil_div(per, 4) : per) * iter + (sh.kind == PATCHES ? ceil_div(a.K2 / 64, s) * PATCH_SIDE : 0.0));
+            if (t < best) { best = t; c = {sh.kind, sh.tm, sh.tn, s}; }
+        }
+    }
+    return c;
+}
+
+// Stages in LDS: as many as it holds (a chunk's weights for a column tile of 32 are 36 KB, its patch 8 - 32 KB).
+template <int T>
+static int launch_patches(const IgemmArgs& a, int tm, int tn, hipStream_t st) {
+    if constexpr (T > 2)
+        if (tm == 1) return launch_tile<1, 1, 9, A_MAP, false, true, T, 3>(a, st);
+    if (tn == 1) return launch_tile<2, 1, T == 8 ? 9 : T == 4 ? 8 : 5, A_MAP, false, true, T, 3>(a, st);
+    return launch_tile<2, 2, T == 8 ? 5 : 4, A_MAP, false, true, T, 2>(a, st);
+}
 
 int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
     const int rows = a.B * a.Ma, ncols = a.geglu ? 2 * a.N : a.N, nsteps = (a.K + a.K2) / 64;
-    int kind = PRIVATE, best_tm = 1, best_tn = 1, best_s = 1; double best = 1e30;
-    const int max_s = ws && ws->counters && ws->partial ? 8 : 1;
-    for (const TileShape& sh : kShapes) {
-        if (a.geglu && sh.tn == 1) continue;
-        if (sh.kind == BLOCK && (a.a_compact || a.N % 160 || a.nsect > 1 || a.out_mode[0] != OUT_MAP || (a.res && a.res_compact))) continue;
-        const int gx = ceil_div(rows, 32 * sh.tm), gy = ceil_div(ncols, 32 * sh.tn);
-        for (int s = 1; s <= max_s; ++s) {
-            const int per = ceil_div(nsteps, s);
-            if (s > 1 && (per < 4 || ceil_div(nsteps, per) != s)) continue;
-            if (s > 1 && ((long long)gx * gy > IGEMM_COUNTERS || (size_t)gx * gy * s * 32 * sh.tm * 32 * sh.tn * 4 > ws->partial_bytes)) break;
-            const long long n = (long long)gx * gy * s;
-            const double iter = nsteps > 96 ? sh.iter_long : sh.iter;
-            double t = s > 1 ? sh.park + sh.park_s * s : 0.0;
-            if (sh.kind == SHARED_RING) t += sh.fixed + std::max(1.0, n / 256.0) * (sh.tile + per * iter);
-            else t += (double)((n + 255) / 256) * (sh.fixed + (sh.kind == PRIVATE ? ceil_div(per, 4) : per) * iter);
-            if (t < best) { best = t; kind = sh.kind; best_tm = sh.tm; best_tn = sh.tn; best_s = s; }
-        }
-    }
-    a.splits = best_s; a.kper = ceil_div(nsteps, best_s);
-    a.gx = ceil_div(rows, 32 * best_tm); a.gy = ceil_div(ncols, 32 * best_tn);
+    const TileChoice c = choose_tile(a, ws);
+    a.splits = c.splits;
+    if (c.kind == PATCHES) { a.kper = ceil_div(a.K / 576, c.splits); a.kper2 = ceil_div(a.K2 / 64, c.splits); }
+    else a.kper = ceil_div(nsteps, c.splits);
+    a.gx = ceil_div(rows, 32 * c.tm); a.gy = ceil_div(ncols, 32 * c.tn);
     prepare(a, ncols);
+    // 384 x 640 x 11520 in 12 row tiles: 21.9 -> 18.4 us, 512 x 1280 x 11520 in eight 38.9 -> 34.9; three row tiles, which have four times
+    // the lines each, 26.1 -> 28.4
+    a.touch = a.gx >= 8;
     if (a.splits > 1) {
         a.partial = ws->partial; a.counters = ws->counters;
         if (!ws->counters_zeroed) {                     // once per call: every launch leaves its counters at zero
@@ -697,14 +960,15 @@ int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
         }
     }
     int e;
-    if (kind == BLOCK) e = launch_tile<2, 5, 4, A_MAP, false, true>(a, st);
-    else if (kind == SHARED_RING)
+    if (c.kind == PATCHES) e = a.tile == 8 ? launch_patches<8>(a, c.tm, c.tn, st) : a.tile == 4 ? launch_patches<4>(a, c.tm, c.tn, st) : launch_patches<2>(a, c.tm, c.tn, st);
+    else if (c.kind == BLOCK) e = launch_tile<2, 5, 4, A_MAP, false, true>(a, st);
+    else if (c.kind == SHARED_RING)
         e = a.geglu ? launch_tile<2, 2, 3, A_ROWS, true, true>(a, st) : a.a_compact ? launch_tile<2, 2, 3, A_ROWS, false, true>(a, st) : launch_tile<2, 2, 3, A_MAP, false, true>(a, st);
-    else if (a.geglu) e = best_tm == 1 ? launch_tile<1, 2, 2, A_ROWS, true>(a, st) : launch_tile<2, 2, 2, A_ROWS, true>(a, st);
+    else if (a.geglu) e = c.tm == 1 ? launch_tile<1, 2, 2, A_ROWS, true>(a, st) : launch_tile<2, 2, 2, A_ROWS, true>(a, st);
     else if (a.a_compact)
-        e = best_tm == 2 ? launch_tile<2, 2, 2, A_ROWS, false>(a, st) : best_tn == 2 ? launch_tile<1, 2, 2, A_ROWS, false>(a, st) : launch_tile<1, 1, 2, A_ROWS, false>(a, st);
+        e = c.tm == 2 ? launch_tile<2, 2, 2, A_ROWS, false>(a, st) : c.tn == 2 ? launch_tile<1, 2, 2, A_ROWS, false>(a, st) : launch_tile<1, 1, 2, A_ROWS, false>(a, st);
     else
-        e = best_tm == 2 ? launch_tile<2, 2, 2, A_MAP, false>(a, st) : best_tn == 2 ? launch_tile<1, 2, 2, A_MAP, false>(a, st) : launch_tile<1, 1, 2, A_MAP, false>(a, st);
+        e = c.tm == 2 ? launch_tile<2, 2, 2, A_MAP, false>(a, st) : c.tn == 2 ? launch_tile<1, 2, 2, A_MAP, false>(a, st) : launch_tile<1, 1, 2, A_MAP, false>(a, st);
     if (e) return e;
     if (a.ln_out) {
         if (a.nsect != 1 || a.out_mode[0] != OUT_COMPACT_F32 || a.geglu || !a.ln_gamma || !a.ln_beta)

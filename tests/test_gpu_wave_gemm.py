@@ -45,6 +45,19 @@ CASES = [
     ("block-split", 2, 32, 32, 640, 0, 320, 3, 1, 0, 4, 32, True, True),               # 1024 rows
     ("block-ragged-columns", 1, 64, 64, 64, 0, 324, 3, 1, 0, 4, 131, True, True),
     ("block-160-wide", 1, 64, 64, 640, 640, 320, 3, 1, 0, 8, 33, True, False),         # 64 x 160 tiles, split, 180 steps
+    # patches of the tiles and their rings in LDS (which form a case takes is the launcher's choice; at these sizes it is this one):
+    # tiles at corners and edges, strips that are half a tile, row tiles with absent strips, ragged columns, source changes, splits
+    ("patch8-32x32", 2, 32, 64, 320, 320, 324, 3, 1, 0, 8, 4, True, True),             # half tiles of four rows
+    ("patch8-64x32", 2, 64, 40, 320, 0, 320, 3, 1, 0, 8, 7, True, True),
+    ("patch8-64x64", 1, 64, 80, 256, 64, 320, 3, 1, 0, 8, 41, False, True),            # source change behind four chunks
+    ("patch8-odd-tiles", 2, 40, 64, 192, 128, 320, 3, 1, 0, 8, 9, True, False),
+    ("patch4-32x32", 2, 24, 40, 640, 0, 260, 3, 1, 0, 4, 19, True, True),
+    ("patch4-64x32-tail", 1, 48, 32, 640, 64, 320, 3, 1, 0, 4, 45, False, True),       # 720 rows: the last row tile has one strip of four
+    ("patch4-64x64", 2, 48, 48, 320, 320, 640, 3, 1, 0, 4, 43, True, False),
+    ("patch4-split", 2, 16, 40, 640, 640, 640, 3, 1, 0, 4, 7, True, True),
+    ("patch2-64x32-split", 2, 16, 16, 1280, 0, 1280, 3, 1, 0, 2, 21, False, True),
+    ("patch2-64x64", 2, 24, 24, 640, 0, 640, 3, 1, 0, 2, 101, True, False),            # 808 rows: ten strips in the last row tile
+    ("patch2-all-tiles", 1, 16, 24, 640, 64, 1280, 3, 1, 0, 2, 96, False, False),
 ]
 
 
