@@ -271,12 +271,10 @@ extern "C" int fise_context_kv(const void* ctx, const void* Wk, const void* Wv, 
     if (Dc % 32 || C % 8) return fail(FISE_ERR_ALIGN, "fise_context_kv: Dc=%d must be a multiple of 32, C=%d of 8", Dc, C);
     if (n_stride < n_ctx || n_stride % 8) return fail(FISE_ERR_ALIGN, "fise_context_kv: n_stride %d", n_stride);
     hipStream_t st = as_stream(stream);
-    const IgemmWorkspace* iw = nullptr;
-    IgemmArgs g = linear_args(ctx, n_ctx, B, Dc, Wk, nullptr, C);
-    g.out[0] = (bf16_t*)K_ctx;
-    if (int e = launch_igemm(g, iw, st)) return e;
-    g.w = (const bf16_t*)Wv; g.out[0] = (bf16_t*)Vt_ctx; g.out_mode[0] = OUT_TOKENS_T; g.Ho = 1; g.Wo = n_stride;
-    return launch_igemm(g, iw, st);
+    IgemmArgs g = linear_args(ctx, n_ctx, B, Dc, nullptr, nullptr, C);
+    g.Ho = 1; g.Wo = n_stride;
+    const GemmProduct kv[2] = {{(const bf16_t*)Wk, C, (bf16_t*)K_ctx, OUT_COMPACT}, {(const bf16_t*)Wv, C, (bf16_t*)Vt_ctx, OUT_TOKENS_T}};
+    return launch_igemm_group(g, kv, 2, st);
 }
 
 extern "C" size_t fise_masked_attention_workspace_bytes(int B, int C, int n_active, int tile) {
@@ -320,13 +318,9 @@ extern "C" int fise_masked_attention(const void* x, const void* ln_gamma, const 
     if (int e = launch_ln_rows(x, 0, rows, C, ln_gamma, ln_beta, 1e-5f, nbuf, tile_idx, tile, W / tile, H, W, Ma, st)) return e;
     IgemmArgs g = linear_args(nbuf, Ma, B, C, Wq, nullptr, C);
     g.tile_idx = tile_idx; g.tile = tile; g.tiles_w = W / tile; g.Ho = H; g.Wo = W;
-    g.out[0] = qbuf;
-    if (int e = launch_igemm(g, iw, st)) return e;
+    const GemmProduct qkv[3] = {{(const bf16_t*)Wq, C, qbuf, OUT_COMPACT}, {(const bf16_t*)Wk, C, (bf16_t*)K_cache, OUT_MAP}, {(const bf16_t*)Wv, C, (bf16_t*)Vt_cache, OUT_TOKENS_T}};
+    if (int e = launch_igemm_group(g, qkv, self ? 3 : 1, st)) return e;
     if (self) {
-        g.w = (const bf16_t*)Wk; g.out[0] = (bf16_t*)K_cache; g.out_mode[0] = OUT_MAP;
-        if (int e = launch_igemm(g, iw, st)) return e;
-        g.w = (const bf16_t*)Wv; g.out[0] = (bf16_t*)Vt_cache; g.out_mode[0] = OUT_TOKENS_T;
-        if (int e = launch_igemm(g, iw, st)) return e;
         if (int e = launch_attention(qbuf, K_cache, Vt_cache, B, Ma, H * W, H * W, C, heads, scale, obuf, ws + 3 * buf, workspace_bytes - 3 * buf, st)) return e;
     } else {
         if (int e = launch_attention(qbuf, K_ctx, Vt_ctx, B, Ma, n_ctx, n_ctx_stride, C, heads, scale, obuf, nullptr, 0, st)) return e;
@@ -383,12 +377,9 @@ extern "C" int fise_masked_attention_restricted(const void* x, const void* ln_ga
     // Q, K as compact rows; V as compact transposed columns [B, C, vstride] (row r of batch b -> column r): these
     // launches address rows only, so they carry no tile list
     IgemmArgs g = linear_args(nbuf, Ma, B, C, Wq, nullptr, C);
-    g.out[0] = qbuf;
-    if (int e = launch_igemm(g, iw, st)) return e;
-    g.w = (const bf16_t*)Wk; g.out[0] = kbuf;
-    if (int e = launch_igemm(g, iw, st)) return e;
-    g.w = (const bf16_t*)Wv; g.out[0] = vtbuf; g.out_mode[0] = OUT_TOKENS_T; g.Ho = 1; g.Wo = vstride;
-    if (int e = launch_igemm(g, iw, st)) return e;
+    g.Ho = 1; g.Wo = vstride;
+    const GemmProduct qkv[3] = {{(const bf16_t*)Wq, C, qbuf, OUT_COMPACT}, {(const bf16_t*)Wk, C, kbuf, OUT_COMPACT}, {(const bf16_t*)Wv, C, vtbuf, OUT_TOKENS_T}};
+    if (int e = launch_igemm_group(g, qkv, 3, st)) return e;
     if (int e = launch_attention(qbuf, kbuf, vtbuf, B, Ma, Ma, vstride, C, heads, scale, obuf, atws,
                                  workspace_bytes - (size_t)(atws - ws), st)) return e;
     IgemmArgs o = linear_args(obuf, Ma, B, C, Wo, bo, C);

@@ -142,6 +142,12 @@ __device__ __forceinline__ void put_views1(const GnView* view, int nview, int b,
 constexpr int IGEMM_COUNTERS = 4096;     // arrival counters of split output tiles (zeroed once per call, left at zero by every launch)
 constexpr size_t IGEMM_PARTIAL_BYTES = (32u << 20) - IGEMM_COUNTERS * sizeof(int);
 struct IgemmWorkspace { float* partial; size_t partial_bytes; int* counters; mutable bool counters_zeroed; };
+// One of several products of the same rows: weights [N, K], destination and its OUT_ mode.
+struct GemmProduct { const bf16_t* w; int N; bf16_t* out; int mode; };
+constexpr int GEMM_GROUP = 32;           // products of one launch
+struct GemmGroup { int first[GEMM_GROUP], N[GEMM_GROUP], mode[GEMM_GROUP]; const bf16_t* w[GEMM_GROUP]; bf16_t* out[GEMM_GROUP]; };    // first: column tile where a product starts
+// base: compact rows, K and geometry; its weights, width and destinations are the products'.  One launch where the sizes allow it.
+int launch_igemm_group(const IgemmArgs& base, const GemmProduct* p, int n, hipStream_t st);
 bool wave_gemm_takes(const IgemmArgs& a);
 int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st);
 size_t igemm_workspace_bytes();

@@ -321,16 +321,17 @@ extern "C" int fise_unet_context_kv(const fise_unet* u, const void* weights, con
     const fise_unet_desc& d = u->d;
     const bf16_t* Wt = (const bf16_t*)weights;
     hipStream_t st = as_stream(stream);
+    // the products of all blocks read the same rows and depend on nothing else
+    IgemmArgs g = linear_args(ctx, d.n_ctx, d.B, d.ctx_dim, nullptr, nullptr, 64);
+    g.Ho = 1; g.Wo = u->n_stride;
+    std::vector<GemmProduct> products;
     for (const Module& m : u->mods) {
         if (m.kind != K_TR) continue;
-        const int C = m.cout;
-        // k.w and v.w are adjacent: one launch, two output sections
-        IgemmArgs g = linear_args(ctx, d.n_ctx, d.B, d.ctx_dim, Wt + u->off(0, m.name + ".a2.k.w"), nullptr, 2 * C);
-        g.nsect = 2; g.sect_n = C; g.Ho = 1; g.Wo = u->n_stride;
-        g.out[0] = (bf16_t*)((char*)ctxkv + u->off(2, m.name + ".ctx_k")); g.out_mode[0] = OUT_COMPACT;
-        g.out[1] = (bf16_t*)((char*)ctxkv + u->off(2, m.name + ".ctx_vt")); g.out_mode[1] = OUT_TOKENS_T;
-        if (int e = launch_igemm(g, nullptr, st)) return e;
+        products.push_back({Wt + u->off(0, m.name + ".a2.k.w"), m.cout, (bf16_t*)((char*)ctxkv + u->off(2, m.name + ".ctx_k")), OUT_COMPACT});
+        products.push_back({Wt + u->off(0, m.name + ".a2.v.w"), m.cout, (bf16_t*)((char*)ctxkv + u->off(2, m.name + ".ctx_vt")), OUT_TOKENS_T});
     }
+    for (size_t i = 0; i < products.size(); i += GEMM_GROUP)
+        if (int e = launch_igemm_group(g, products.data() + i, (int)std::min<size_t>(GEMM_GROUP, products.size() - i), st)) return e;
     return FISE_OK;
 }
 

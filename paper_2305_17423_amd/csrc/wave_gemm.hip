@@ -81,8 +81,11 @@ __device__ __forceinline__ float gelu_f(float x) { return x * (0.5f * (1.0f + er
 #endif
 
 // SHARED: one ring for the workgroup instead of one per wave, see the launcher.
+// What the products of a group differ in.
+struct Product { const bf16_t* w; int N, sect_n; bf16_t* out0; int mode0; };
+
 template <int TM, int TN, int NW, int NST, int AM, bool GEGLU, bool SHARED, int PATCH = 0, int NPB = 0>
-__global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void wave_gemm_kernel(const IgemmArgs a) {
+__device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product& pr, const int bx, const int by, const int bz) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 32 * TM, BN = 32 * TN, NT = 64 * NW;
     constexpr int RB = SHARED ? 8 * NW : 8;             // rows between two loads of a lane (one load of a wave fills 8 rows of 128 bytes)
@@ -102,23 +105,13 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];      // [NW or 1][NST][STAGE], later [NW][GROWS][PITCH] floats
 
     // Kernel arguments arrive through scalar loads placed where a field is first used; named here they come as one batch.
-    asm volatile("" ::"s"(a.gx), "s"(a.gy), "s"(a.splits), "s"(a.kper), "s"(a.d_gx.mul), "s"(a.d_gy.mul), "s"(a.d_Ma.mul), "s"(a.d_tt.mul),
-                 "s"(a.d_tw.mul), "s"(a.d_tiles_w.mul), "s"(a.B), "s"(a.Ma), "s"(a.K), "s"(a.K2), "s"(a.N), "s"(a.w), "s"(a.tile_idx), "s"(a.need_pix));
-    asm volatile("" ::"s"(a.Ho), "s"(a.Wo), "s"(a.tile), "s"(a.sect_n), "s"(a.out_mode[0]), "s"(a.bias), "s"(a.bias_bytes), "s"(a.temb), "s"(a.temb_bytes),
+    asm volatile("" ::"s"(a.kper), "s"(a.d_Ma.mul), "s"(a.d_tt.mul),
+                 "s"(a.d_tw.mul), "s"(a.d_tiles_w.mul), "s"(a.B), "s"(a.Ma), "s"(a.K), "s"(a.K2), "s"(pr.N), "s"(pr.w), "s"(a.tile_idx), "s"(a.need_pix));
+    asm volatile("" ::"s"(a.Ho), "s"(a.Wo), "s"(a.tile), "s"(pr.sect_n), "s"(pr.mode0), "s"(a.bias), "s"(a.bias_bytes), "s"(a.temb), "s"(a.temb_bytes),
                  "s"(a.res), "s"(a.res_bytes), "s"(a.res_compact), "s"(a.nview), "s"(a.src[0].p), "s"(a.src[0].bytes));
     if constexpr (AM == A_MAP) asm volatile("" ::"s"(a.Hin), "s"(a.Win), "s"(a.ksize), "s"(a.stride), "s"(a.ups), "s"(a.C0), "s"(a.d_spt.mul), "s"(a.bias2), "s"(a.bias2_bytes));
     const int tid = threadIdx.x, lane = tid & 63, lr = lane >> 3;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // consecutive workgroups go round-robin to the 8 XCDs: give every XCD a contiguous run of (bz, by, bx), bx fastest, so
-    // that a slice of the weights is pulled into one L2
-    int bx, by, bz;
-    {
-        const int total = a.gx * a.gy * a.splits, chunk = total >> 3;
-        int w = blockIdx.x;
-        if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
-        const unsigned t = fdiv((unsigned)w, a.d_gx);
-        bx = w - (int)t * a.gx; bz = (int)fdiv(t, a.d_gy); by = (int)t - bz * a.gy;
-    }
     const int rows = a.B * a.Ma, m0 = bx * BM;
     const int nsteps1 = a.K >> 6, nsteps = nsteps1 + (a.K2 >> 6);
     int kb, ke;                                         // K steps of this wave
@@ -142,19 +135,19 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
 
     // ---- weights: first stages.  LDS slot p of row r holds segment p ^ ((r >> 1) & 7) (conflict-free operand reads); a load
     // fills 8 rows, so between odd and even loads only bit 2 of the segment flips.
-    const unsigned wrows = (unsigned)(GEGLU ? 2 * a.N : a.N);
+    const unsigned wrows = (unsigned)(GEGLU ? 2 * pr.N : pr.N);
     const int lrow = SHARED ? wave * 8 + lr : lr;       // this lane's row of a load
     const unsigned seg0 = (unsigned)(((lane & 7) ^ ((lrow >> 1) & 7)) * 16), seg1 = SHARED ? seg0 : seg0 ^ 64u;
     unsigned vb[BL], soff_b, bytes_b;
     const bf16_t* ptr_b;
     auto set_weights = [&](bool side, int kstep) {
         const unsigned pitch = (unsigned)(side ? a.K2 : a.K) * 2u;
-        ptr_b = side ? a.w2 : a.w; bytes_b = __umul24(wrows, pitch); soff_b = (unsigned)kstep * 128u;
+        ptr_b = side ? a.w2 : pr.w; bytes_b = __umul24(wrows, pitch); soff_b = (unsigned)kstep * 128u;
         const unsigned row0 = __umul24((unsigned)(by * (GEGLU ? OW : BN) + lrow), pitch);
 #pragma unroll
         for (int j = 0; j < BL; ++j) {                  // GEGLU: value rows, then the gate rows N further down
             unsigned jr = (unsigned)(j * RB);
-            if (GEGLU && j >= BL / 2) jr += (unsigned)(a.N - OW);
+            if (GEGLU && j >= BL / 2) jr += (unsigned)(pr.N - OW);
             vb[j] = row0 + (j & 1 ? seg1 : seg0) + jr * pitch;      // rows past the matrix lie past the descriptor
         }
     };
@@ -176,7 +169,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
     // GB/s per CU); short K ranges do not earn it back.
     if (!PATCH && a.gx >= 12 && a.kper >= 32) {
         const int c0 = bz * a.kper, c1 = min(nsteps1, c0 + a.kper);
-        const __amdgpu_buffer_rsrc_t rs = buf(a.w, bytes_b);
+        const __amdgpu_buffer_rsrc_t rs = buf(pr.w, bytes_b);
         if constexpr (SHARED) {
             for (int q = c0 + bx * NW + wave; q < c1; q += a.gx * NW)
 #pragma unroll
@@ -185,7 +178,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
                                                              r + lane < BN ? __umul24((unsigned)(by * BN + r + lane), (unsigned)a.K * 2u) + q * 128 : OOB, 0, 0, 0);
         } else {
         const int half = BN == 32 ? lane >> 5 : 0;
-        const unsigned off = __umul24((unsigned)(by * (GEGLU ? OW : BN) + (lane & (BN - 1)) + (GEGLU && lane >= OW ? a.N - OW : 0)), (unsigned)a.K * 2u);
+        const unsigned off = __umul24((unsigned)(by * (GEGLU ? OW : BN) + (lane & (BN - 1)) + (GEGLU && lane >= OW ? pr.N - OW : 0)), (unsigned)a.K * 2u);
         constexpr int PER = BN == 32 ? 2 : 1;
         for (int q = c0 + (bx * NW + wave) * PER; q < c1; q += a.gx * NW * PER)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)my_ring, 4, off + (q + half) * 128, 0, 0, 0);
@@ -204,7 +197,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
         soff_b = (unsigned)ch0 * 128u;
         // The same first touch as above: line q of a row of W is tap q / chunks, chunk q % chunks of this range.
         if (a.touch) {
-            const __amdgpu_buffer_rsrc_t rs = buf(a.w, bytes_b);
+            const __amdgpu_buffer_rsrc_t rs = buf(pr.w, bytes_b);
             const int nch = ch1 - ch0, lines = 9 * nch;
             const unsigned off = __umul24((unsigned)(by * BN + (lane & (BN - 1))), (unsigned)a.K * 2u) + soff_b;
             constexpr int PER = 64 / BN;
@@ -224,7 +217,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
     auto issue_step = [&]() {
         unsigned char* base = wring + wslot + wave * 1024;
         if (vstep < nmain) {
-            const __amdgpu_buffer_rsrc_t rs = buf(a.w, bytes_b);
+            const __amdgpu_buffer_rsrc_t rs = buf(pr.w, bytes_b);
 #pragma unroll
             for (int l = 0; l < LB; ++l)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + l * 4096), 16, vb[l % BL], soff_b + (l / BL) * tap_bytes, 0, 0);
@@ -232,7 +225,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
             if (++vky == 3) { vky = 0; soff_b += 128u - 9 * tap_bytes; }
         } else {
             const bool live = vstep < nmain + nside;
-            const __amdgpu_buffer_rsrc_t rs = buf(ptr_s, live ? bytes_s : 0u), rw = buf(a.w2, live ? __umul24((unsigned)a.N, (unsigned)a.K2 * 2u) : 0u);
+            const __amdgpu_buffer_rsrc_t rs = buf(ptr_s, live ? bytes_s : 0u), rw = buf(a.w2, live ? __umul24((unsigned)pr.N, (unsigned)a.K2 * 2u) : 0u);
 #pragma unroll
             for (int l = 0; l < LB; ++l) {
                 if (l < TM) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + l * 4096), 16, va_s[l], soff_s, 0, 0);
@@ -265,8 +258,8 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
 
     // ---- this thread's pieces of the finished tile (four columns of a row, or four rows of a column) and their operands
     const int col0 = by * OW;
-    const int sect = CONV ? 0 : (col0 >= a.sect_n) + (col0 >= 2 * a.sect_n);      // a column tile lies in one section (checked by the launcher)
-    const int omode = CONV ? OUT_MAP : sect == 0 ? a.out_mode[0] : sect == 1 ? a.out_mode[1] : a.out_mode[2];
+    const int sect = CONV ? 0 : (col0 >= pr.sect_n) + (col0 >= 2 * pr.sect_n);      // a column tile lies in one section (checked by the launcher)
+    const int omode = CONV ? OUT_MAP : sect == 0 ? pr.mode0 : sect == 1 ? a.out_mode[1] : a.out_mode[2];
     const bool trans = !CONV && omode == OUT_TOKENS_T && a.trans4;
     int e_r[ITEMS], e_c[ITEMS], e_b[ITEMS]; unsigned e_pix[ITEMS]; bool e_ok[ITEMS];
     auto place_items = [&]() {
@@ -275,7 +268,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
         const int item = tid + it % IPG * NT, g0 = it / IPG * GROWS;
         e_r[it] = g0 + (trans ? (item % (GROWS / 4)) * 4 : item / CPR);
         e_c[it] = trans ? item / (GROWS / 4) : (item % CPR) * 4;
-        e_ok[it] = m0 + e_r[it] < rows && col0 + e_c[it] < a.N;
+        e_ok[it] = m0 + e_r[it] < rows && col0 + e_c[it] < pr.N;
         e_b[it] = __shfl((int)rb, e_r[it]);
         e_pix[it] = (unsigned)__shfl((int)rpix, e_r[it]);
     }
@@ -291,9 +284,9 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
             const unsigned no = e_ok[grp * IPG + it] && !trans ? 0u : OOB, col = (unsigned)(col0 + e_c[grp * IPG + it]);
             e_bias[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, (col * 2u) | no, 0, 0));
             if constexpr (GEGLU) {
-                e_gate[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, ((col + a.N) * 2u) | no, 0, 0));
+                e_gate[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, ((col + pr.N) * 2u) | no, 0, 0));
             } else {
-                const unsigned r = __umul24(res_compact ? (unsigned)(m0 + e_r[grp * IPG + it]) : e_pix[grp * IPG + it], (unsigned)a.N) + col;
+                const unsigned r = __umul24(res_compact ? (unsigned)(m0 + e_r[grp * IPG + it]) : e_pix[grp * IPG + it], (unsigned)pr.N) + col;
                 if constexpr (CONV) e_res[it].xy = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_res, (r << 1) | no, 0, 0));
                 else e_res[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_res, (r << res_shift) | no, 0, 0));
                 if constexpr (AM == A_MAP) {
@@ -685,8 +678,8 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
     }
 
     // ---- epilogue: sum, biases, gate, then time projection + residual as one term; stores
-    bf16_t* const outp = sect == 0 ? a.out[0] : sect == 1 ? a.out[1] : a.out[2];
-    const int scol0 = col0 - sect * a.sect_n;
+    bf16_t* const outp = sect == 0 ? pr.out0 : sect == 1 ? a.out[1] : a.out[2];
+    const int scol0 = col0 - sect * pr.sect_n;
     if constexpr (CONV) {
         // A group's results are packed in registers, the next group's operands requested, and only then stored: behind the
         // stores the loads would wait for them.
@@ -727,7 +720,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
             for (int it = 0; it < IPG; ++it) {
                 const int e = grp * IPG + it;
                 if (!e_ok[e]) continue;
-                *(FISE_AS1 u32x2_w*)(outp + (size_t)e_pix[e] * a.N + col0 + e_c[e]) = y[it];
+                *(FISE_AS1 u32x2_w*)(outp + (size_t)e_pix[e] * pr.N + col0 + e_c[e]) = y[it];
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
                     if (i < a.nview) *(FISE_AS1 u32x2_w*)(a.view[i].dst + (size_t)e_pix[e] * a.view[i].dstC + a.view[i].c_off + col0 + e_c[e]) = yv[it][i];
@@ -740,7 +733,7 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) {
             if (!e_ok[it]) continue;
-            FISE_AS1 bf16_t* q = (FISE_AS1 bf16_t*)(outp + ((size_t)e_b[it] * a.sect_n + scol0 + e_c[it]) * HW + (e_pix[it] - (unsigned)e_b[it] * HW));
+            FISE_AS1 bf16_t* q = (FISE_AS1 bf16_t*)(outp + ((size_t)e_b[it] * pr.sect_n + scol0 + e_c[it]) * HW + (e_pix[it] - (unsigned)e_b[it] * HW));
             *(FISE_AS1 u32x2_w*)q = u32x2_w{f2bf2(v[it][0], v[it][1]), f2bf2(v[it][2], v[it][3])};
         }
         return;
@@ -767,19 +760,19 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
         const size_t gm = (size_t)(m0 + e_r[it]);
         if (omode == OUT_TOKENS_T) {
             const size_t HW = (size_t)a.Ho * a.Wo;
-            FISE_AS1 bf16_t* q = (FISE_AS1 bf16_t*)(outp + ((size_t)e_b[it] * a.sect_n + scol) * HW + (e_pix[it] - (unsigned)e_b[it] * (unsigned)HW));
+            FISE_AS1 bf16_t* q = (FISE_AS1 bf16_t*)(outp + ((size_t)e_b[it] * pr.sect_n + scol) * HW + (e_pix[it] - (unsigned)e_b[it] * (unsigned)HW));
 #pragma unroll
             for (int t = 0; t < 4; ++t) q[t * HW] = f2bf(x[t]);
             continue;
         }
         const u32x2_w packed = {f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
         if (omode == OUT_COMPACT_F32) {
-            if (outp) *(FISE_AS1 f32x4_w*)(reinterpret_cast<float*>(outp) + gm * a.sect_n + scol) = f32x4_w{x[0], x[1], x[2], x[3]};
-            if (a.mirror) *(FISE_AS1 u32x2_w*)(a.mirror + gm * a.sect_n + scol) = packed;
+            if (outp) *(FISE_AS1 f32x4_w*)(reinterpret_cast<float*>(outp) + gm * pr.sect_n + scol) = f32x4_w{x[0], x[1], x[2], x[3]};
+            if (a.mirror) *(FISE_AS1 u32x2_w*)(a.mirror + gm * pr.sect_n + scol) = packed;
         } else if (omode == OUT_COMPACT) {
-            *(FISE_AS1 u32x2_w*)(outp + gm * a.sect_n + scol) = packed;
+            *(FISE_AS1 u32x2_w*)(outp + gm * pr.sect_n + scol) = packed;
         } else {
-            *(FISE_AS1 u32x2_w*)(outp + (size_t)e_pix[it] * a.sect_n + scol) = packed;
+            *(FISE_AS1 u32x2_w*)(outp + (size_t)e_pix[it] * pr.sect_n + scol) = packed;
             if (!GEGLU && a.nview) {
                 ViewSS ss;
 #pragma unroll
@@ -791,6 +784,33 @@ __global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void 
         }
     }
 #endif
+}
+
+// Place of this workgroup in the order in which its XCD should work: consecutive workgroups go round-robin to the 8 XCDs; every XCD
+// gets a contiguous run of (bz, by, bx), bx fastest, so that a slice of the weights is pulled into one L2.
+__device__ __forceinline__ int xcd_order(int total) {
+    const int w = blockIdx.x, chunk = total >> 3;
+    return w < (chunk << 3) ? (w & 7) * chunk + (w >> 3) : w;
+}
+
+template <int TM, int TN, int NW, int NST, int AM, bool GEGLU, bool SHARED, int PATCH = 0, int NPB = 0>
+__global__ __launch_bounds__(64 * NW, SHARED && TN == 2 && !PATCH ? 3 : 1) void wave_gemm_kernel(const IgemmArgs a) {
+    asm volatile("" ::"s"(a.gx), "s"(a.gy), "s"(a.splits), "s"(a.d_gx.mul), "s"(a.d_gy.mul));
+    const int w = xcd_order(a.gx * a.gy * a.splits);
+    const unsigned t = fdiv((unsigned)w, a.d_gx);
+    const int bz = (int)fdiv(t, a.d_gy);
+    wave_gemm_tile<TM, TN, NW, NST, AM, GEGLU, SHARED, PATCH, NPB>(a, Product{a.w, a.N, a.sect_n, a.out[0], a.out_mode[0]}, w - (int)t * a.gx, (int)t - bz * a.gy, bz);
+}
+
+// Several products of the same compact rows, each with weights, width and destination of its own, as one launch.
+template <int TM, int TN, int NW, int NST, bool SHARED>
+__global__ __launch_bounds__(64 * NW, SHARED ? 3 : 1) void wave_gemm_group_kernel(const IgemmArgs a, const GemmGroup grp) {
+    const int w = xcd_order(a.gx * a.gy);
+    const int t = (int)fdiv((unsigned)w, a.d_gx);
+    int g = 0;
+#pragma unroll
+    for (int i = 1; i < GEMM_GROUP; ++i) g += t >= grp.first[i];        // column tiles of all products, one behind the other
+    wave_gemm_tile<TM, TN, NW, NST, A_ROWS, false, SHARED>(a, Product{grp.w[g], grp.N[g], grp.N[g], grp.out[g], grp.mode[g]}, w - t * a.gx, t - grp.first[g], 0);
 }
 
 __global__ void zero_ints_kernel(int* p, int n) {
@@ -938,6 +958,60 @@ static int launch_patches(const IgemmArgs& a, int tm, int tn, hipStream_t st) {
         if (tm == 1) return launch_tile<1, 1, 9, A_MAP, false, true, T, 3>(a, st);
     if (tn == 1) return launch_tile<2, 1, T == 8 ? 9 : T == 4 ? 8 : 5, A_MAP, false, true, T, 3>(a, st);
     return launch_tile<2, 2, T == 8 ? 5 : 4, A_MAP, false, true, T, 2>(a, st);
+}
+
+// The products of a group as one launch (no K split).  One by one they are a few dozen workgroups each that wait for one another's
+// launch: keys and values of 154 context tokens for 16 blocks (24960 columns) 85.3 -> 24.0 us, queries,
+// keys and values of 640 rows of 320 channels three launches of 4.7 -> one of 6.
+template <int TM, int TN, int NST, bool SHARED>
+static int launch_group_tile(const IgemmArgs& a, const GemmGroup& g, hipStream_t st) {
+    constexpr int NW = 4, lds = (SHARED ? 1 : NW) * NST * (32 * TM + 32 * TN) * 128;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&wave_gemm_group_kernel<TM, TN, NW, NST, SHARED>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return fail(FISE_ERR_HIP, "wave gemm group: cannot raise the dynamic LDS limit");
+    {
+        const double rows = (double)a.B * a.Ma;
+        ProfileScope prof(PROF_ROWS_GEMM, 2.0 * rows * a.N * a.K, 2.0 * ((double)a.N * a.K + rows * a.K + rows * a.N), st);
+        hipLaunchKernelGGL((wave_gemm_group_kernel<TM, TN, NW, NST, SHARED>), dim3((unsigned)(a.gx * a.gy)), dim3(64 * NW), lds, st, a, g);
+    }
+    FISE_CHECK_LAUNCH("wave gemm group");
+    return FISE_OK;
+}
+
+int launch_igemm_group(const IgemmArgs& base, const GemmProduct* p, int n, hipStream_t st) {
+    IgemmArgs a = base;
+    a.nsect = 1; a.sect_n = a.N; a.splits = 1;
+    bool grouped = n > 1 && n <= GEMM_GROUP && !a.bias && !a.temb && !a.res && !a.nview && !a.geglu && !a.ln_out && a.a_compact && a.C0 == a.K;
+    int cols = 0; bool pix = false, tokens = false;
+    for (int i = 0; i < n; ++i) {
+        IgemmArgs b = a;
+        b.N = b.sect_n = p[i].N;
+        grouped &= wave_gemm_fits(b) && p[i].N % 64 == 0;
+        cols += p[i].N; pix |= p[i].mode != OUT_COMPACT; tokens |= p[i].mode == OUT_TOKENS_T;
+    }
+    if (!grouped || a.B * a.Ma <= 0) {                  // one by one
+        for (int i = 0; i < n; ++i) {
+            a.w = p[i].w; a.N = a.sect_n = p[i].N; a.out[0] = p[i].out; a.out_mode[0] = p[i].mode;
+            if (int e = launch_igemm(a, nullptr, st)) return e;
+        }
+        return FISE_OK;
+    }
+    a.N = cols;
+    const TileChoice c = choose_tile(a, nullptr);
+    GemmGroup g{};
+    int tiles = 0;
+    for (int i = 0; i < GEMM_GROUP; ++i) {
+        g.first[i] = i < n ? tiles : 1 << 30;
+        if (i >= n) continue;
+        g.w[i] = p[i].w; g.out[i] = p[i].out; g.N[i] = p[i].N; g.mode[i] = p[i].mode;
+        tiles += p[i].N / (32 * c.tn);
+    }
+    a.out_mode[0] = tokens ? OUT_TOKENS_T : pix ? OUT_MAP : OUT_COMPACT;
+    a.gx = ceil_div(a.B * a.Ma, 32 * c.tm); a.gy = tiles; a.kper = a.K / 64;
+    prepare(a, a.N);
+    if (c.kind == SHARED_RING) return launch_group_tile<2, 2, 3, true>(a, g, st);
+    if (c.tm == 2) return launch_group_tile<2, 2, 2, false>(a, g, st);
+    return c.tn == 2 ? launch_group_tile<1, 2, 2, false>(a, g, st) : launch_group_tile<1, 1, 2, false>(a, g, st);
 }
 
 int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {

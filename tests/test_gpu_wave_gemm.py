@@ -119,3 +119,18 @@ def test_block_tile_rows_and_transposed_columns(fb):
     want = np.asarray(y0, np.float64).copy()
     want[:, act] = np.concatenate(o, -1) @ np.asarray(Wo, np.float64).T + np.asarray(bo, np.float64) + np.asarray(x, np.float64)[:, act]
     check_map(host(y), want, np.asarray(y0, np.float64), act, TOL[DT], "layer output")
+
+
+@pytest.mark.parametrize("B,n,Dc,C", [(1, 1, 64, 64), (2, 77, 768, 320), (1, 8, 768, 1280), (4, 154, 768, 640), (2, 33, 128, 192), (2, 77, 96, 320)])
+def test_products_of_one_launch(fb, B, n, Dc, C):
+    """Keys and values of a context: two products of the same rows, rows out and transposed columns out (the last size one by one)."""
+    rng = np.random.default_rng(B * 1000 + n)
+    ctx, wk, wv = wl.normal(rng, (B, n, Dc), 1.0, DT), wl.normal(rng, (C, Dc), Dc ** -0.5, DT), wl.normal(rng, (C, Dc), Dc ** -0.5, DT)
+    stride = (n + 7) // 8 * 8
+    K = torch.full((B, n, C), 7.0, dtype=torch.bfloat16, device=DEV)
+    Vt = torch.full((B, C, stride), 7.0, dtype=torch.bfloat16, device=DEV)
+    fb.fise_context_kv(dev(ctx, DT), dev(wk, DT), dev(wv, DT), K, Vt)
+    for got, w in ((host(K), wk), (host(Vt)[:, :, :n].transpose(0, 2, 1), wv)):
+        want = np.asarray(ctx, np.float64) @ np.asarray(w, np.float64).T
+        assert np.abs(got - want).max() <= TOL[DT] * max(1.0, np.sqrt((want ** 2).mean()))
+    assert (host(Vt)[:, :, n:] == 7.0).all()         # columns past the context stay as they are
