@@ -8,21 +8,28 @@
 namespace fise {
 
 // ---------------------------------------------------------------------------
-// d = mean_{b,c} |fresh - cached| with a fixed summation order (b outermost, c
-// ascending, float adds), one pixel per lane of the first wave.  The workgroup
-// stages [64 pixels x CH channels] slabs through LDS so that global reads are
-// coalesced along channels while each pixel's channels are still added in
-// ascending order by one lane.
+// d = mean_{b,c} |fresh - cached| with a fixed summation order (b outermost, c ascending, float adds), one pixel per lane.
+//  - slab form: the workgroup stages [PIX pixels x DET_CH channels] through LDS so that global reads are coalesced along channels
+//    while each pixel's channels are still added in ascending order by one lane.  Bound by the round trip of the loads and the chain of
+//    additions; maps of few pixels are cut into groups of 16 to reach more CUs (32 x 32 x 64 fp32: 6.7 -> 3.3 us).
+//  - vector form (4, 8, 12 or 16 channels, which a lane reads as vectors of four): no LDS, every load of two batch elements in
+//    flight at once (64 x 64 x 4 bf16, batch 2: 4.0 -> 2.4 us).
 // ---------------------------------------------------------------------------
-constexpr int DET_PIX = 64;         // pixels per workgroup
 constexpr int DET_CH = 64;          // channels staged per slab
 constexpr int DET_THREADS = 256;    // all four waves load the slab; the first sums it, one pixel per lane
 
-template <typename T>
+__device__ __forceinline__ void pixel_put(float s, int p, int terms, float* __restrict__ d_out, int accumulate, float threshold,
+                                          uint8_t* __restrict__ pix) {
+    const float d = s / (float)terms;
+    if (d_out) d_out[p] = accumulate ? d_out[p] + d : d;
+    if (pix) pix[p] = d > threshold ? 1 : 0;
+}
+
+template <typename T, int DET_PIX>
 __global__ __launch_bounds__(DET_THREADS) void pixel_diff_kernel(const T* __restrict__ cached, const T* __restrict__ fresh,
                                                                  int B, int HW, int C, float* __restrict__ d_out,
                                                                  int accumulate, float threshold, uint8_t* __restrict__ pix) {
-    __shared__ float slab[DET_PIX][DET_CH + 1];
+    __shared__ __attribute__((aligned(16))) float slab[DET_PIX][DET_CH + 4];
     const int p0 = blockIdx.x * DET_PIX;
     const int tid = threadIdx.x;
     float s = 0.f;
@@ -52,23 +59,74 @@ __global__ __launch_bounds__(DET_THREADS) void pixel_diff_kernel(const T* __rest
                 for (int e = tid; e < DET_PIX * nc; e += DET_THREADS) slab[e / nc][e % nc] = absdiff(b, e / nc, c0 + e % nc);
             }
             __syncthreads();
-            if (tid < DET_PIX)
-                for (int cc = 0; cc < nc; ++cc) s = s + slab[tid][cc];
+            if (tid < DET_PIX) {
+                if (nc == DET_CH) {
+#pragma unroll
+                    for (int cc = 0; cc < DET_CH; cc += 4) {
+                        const float4 v = *reinterpret_cast<const float4*>(&slab[tid][cc]);
+                        s = s + v.x; s = s + v.y; s = s + v.z; s = s + v.w;
+                    }
+                } else
+                    for (int cc = 0; cc < nc; ++cc) s = s + slab[tid][cc];
+            }
             __syncthreads();
         }
     }
-    const int p = p0 + tid;
-    if (tid < DET_PIX && p < HW) {
-        const float d = s / (float)(B * C);
-        if (d_out) d_out[p] = accumulate ? d_out[p] + d : d;
-        if (pix) pix[p] = d > threshold ? 1 : 0;
+    if (tid < DET_PIX && p0 + tid < HW) pixel_put(s, p0 + tid, B * C, d_out, accumulate, threshold, pix);
+}
+
+// four consecutive channels as floats
+__device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ float4 load4(const bf16_t* p) {
+    const uint2 v = *reinterpret_cast<const uint2*>(p);
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+}
+
+template <typename T, int C4>
+__global__ __launch_bounds__(64) void pixel_diff_vec_kernel(const T* __restrict__ cached, const T* __restrict__ fresh, int B, int HW,
+                                                            float* __restrict__ d_out, int accumulate, float threshold,
+                                                            uint8_t* __restrict__ pix) {
+    const int p = blockIdx.x * 64 + threadIdx.x;
+    if (p >= HW) return;
+    float s = 0.f;
+#pragma unroll 2
+    for (int b = 0; b < B; ++b) {
+        const size_t off = ((size_t)b * HW + p) * (4 * C4);
+        float4 x[C4], y[C4];
+#pragma unroll
+        for (int q = 0; q < C4; ++q) { x[q] = load4(cached + off + 4 * q); y[q] = load4(fresh + off + 4 * q); }
+#pragma unroll
+        for (int q = 0; q < C4; ++q) {
+            s = s + fabsf(y[q].x - x[q].x); s = s + fabsf(y[q].y - x[q].y); s = s + fabsf(y[q].z - x[q].z); s = s + fabsf(y[q].w - x[q].w);
+        }
     }
+    pixel_put(s, p, B * 4 * C4, d_out, accumulate, threshold, pix);
+}
+
+template <typename T>
+static void launch_pixel_diff(const void* cached, const void* fresh, int B, int HW, int C, float* d_out, int accumulate, float threshold,
+                              uint8_t* pix, hipStream_t st) {
+    const T* a = (const T*)cached; const T* b = (const T*)fresh;
+    // vectors of four channels lie on multiples of their size where the maps do
+    const bool vec = C % 4 == 0 && C <= 16 && (reinterpret_cast<uintptr_t>(cached) | reinterpret_cast<uintptr_t>(fresh)) % (4 * sizeof(T)) == 0;
+    const dim3 vgrid(ceil_div(HW, 64)), vblock(64);
+    if (vec && C == 4) hipLaunchKernelGGL((pixel_diff_vec_kernel<T, 1>), vgrid, vblock, 0, st, a, b, B, HW, d_out, accumulate, threshold, pix);
+    else if (vec && C == 8) hipLaunchKernelGGL((pixel_diff_vec_kernel<T, 2>), vgrid, vblock, 0, st, a, b, B, HW, d_out, accumulate, threshold, pix);
+    else if (vec && C == 12) hipLaunchKernelGGL((pixel_diff_vec_kernel<T, 3>), vgrid, vblock, 0, st, a, b, B, HW, d_out, accumulate, threshold, pix);
+    else if (vec) hipLaunchKernelGGL((pixel_diff_vec_kernel<T, 4>), vgrid, vblock, 0, st, a, b, B, HW, d_out, accumulate, threshold, pix);
+    else if (HW <= 64 * 128)
+        hipLaunchKernelGGL((pixel_diff_kernel<T, 16>), dim3(ceil_div(HW, 16)), dim3(DET_THREADS), 0, st, a, b, B, HW, C, d_out, accumulate, threshold, pix);
+    else
+        hipLaunchKernelGGL((pixel_diff_kernel<T, 64>), dim3(ceil_div(HW, 64)), dim3(DET_THREADS), 0, st, a, b, B, HW, C, d_out, accumulate, threshold, pix);
 }
 
 // ---------------------------------------------------------------------------
 // tile OR + ordered compaction, one workgroup; tiles are taken 256 at a time,
 // the running base keeps ids ascending across chunks.
 // ---------------------------------------------------------------------------
+// Word: what a row of a tile is read in (8, 4 or 1 pixels).  One pixel at a time an 8 x 8 tile is a chain of 64 byte loads (64 x 64
+// pixels: 4.5 -> 1.9 us).
+template <typename Word>
 __global__ __launch_bounds__(256) void tile_compact_kernel(const uint8_t* __restrict__ pix, int H, int W, int tile_h, int tile_w,
                                                            uint8_t* __restrict__ tile_mask, int* __restrict__ idx,
                                                            int capacity, int* __restrict__ n_active) {
@@ -81,8 +139,15 @@ __global__ __launch_bounds__(256) void tile_compact_kernel(const uint8_t* __rest
         bool act = false;
         if (t < nt) {
             const int y0 = (t / tw) * tile_h, x0 = (t % tw) * tile_w;
-            for (int yy = 0; yy < tile_h; ++yy)
-                for (int xx = 0; xx < tile_w; ++xx) act |= pix[(y0 + yy) * W + x0 + xx] != 0;
+            Word any = 0;
+            if (tile_h == 8 && tile_w == (int)sizeof(Word)) {           // all rows in flight at once
+#pragma unroll
+                for (int yy = 0; yy < 8; ++yy) any |= *reinterpret_cast<const Word*>(pix + (y0 + yy) * W + x0);
+            } else {
+                for (int yy = 0; yy < tile_h; ++yy)
+                    for (int xx = 0; xx < tile_w; xx += (int)sizeof(Word)) any |= *reinterpret_cast<const Word*>(pix + (y0 + yy) * W + x0 + xx);
+            }
+            act = any != 0;
             tile_mask[t] = act ? 1 : 0;
         }
         const unsigned long long bal = __ballot(act);
@@ -104,6 +169,17 @@ __global__ __launch_bounds__(256) void tile_compact_kernel(const uint8_t* __rest
     if (threadIdx.x == 0) *n_active = base;
 }
 
+static void launch_tile_compact(const uint8_t* pix, int H, int W, int tile_h, int tile_w, uint8_t* tile_mask, int* idx, int capacity,
+                                int* n_active, hipStream_t st) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(pix);              // W is a multiple of tile_w: rows of tiles start on multiples of the word
+    if (tile_w % 8 == 0 && at % 8 == 0)
+        hipLaunchKernelGGL(tile_compact_kernel<unsigned long long>, dim3(1), dim3(256), 0, st, pix, H, W, tile_h, tile_w, tile_mask, idx, capacity, n_active);
+    else if (tile_w % 4 == 0 && at % 4 == 0)
+        hipLaunchKernelGGL(tile_compact_kernel<unsigned>, dim3(1), dim3(256), 0, st, pix, H, W, tile_h, tile_w, tile_mask, idx, capacity, n_active);
+    else
+        hipLaunchKernelGGL(tile_compact_kernel<uint8_t>, dim3(1), dim3(256), 0, st, pix, H, W, tile_h, tile_w, tile_mask, idx, capacity, n_active);
+}
+
 __global__ void or_pool_kernel(const uint8_t* __restrict__ m, int H, int W, uint8_t* __restrict__ out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int Ho = H / 2, Wo = W / 2;
@@ -117,101 +193,135 @@ __global__ void or_pool_kernel(const uint8_t* __restrict__ m, int H, int W, uint
 // Otsu in two launches.  Values are min-max normalised in double; bin k of 257 holds values with floor(256 v) == k, so
 // class A of threshold k/256 is exactly bins [0, k).  Every bin's sum is taken in index order: the order is part of the
 // result, so the longest chain of dependent additions (the fullest bin) is what bounds this.
-//  - otsu_bins_kernel: one wave per bin.  The workgroup normalises 1024 values at a time into LDS; a wave packs those of
-//    its bin behind one another (ballot + popcount prefix) and adds them up from LDS, where the reads run ahead of the
-//    additions.  Normalising costs a double division per value and workgroup, not one per value and bin.
-//  - otsu_apply_kernel: every workgroup finds the threshold for itself (one serial pass of 257 additions, the objectives in
-//    parallel) and thresholds its share of the values.
-// One thread per bin walking all values in one workgroup: 650 us; this: 30 us for 64 x 64 values, and
-// five accumulated differences and their mask 680 -> 57 us.
+//  - otsu_bins_kernel: four bins per workgroup of sixteen waves.  The waves normalise 4096 values in registers (a double
+//    division per value and workgroup), pack those of each bin behind one another in LDS (ballot + popcount prefix, the waves' counts
+//    in between), and one wave per bin adds them up from there, where the reads run ahead of the additions.
+//  - otsu_apply_kernel: every workgroup finds the threshold for itself (the sums below a bin one chain of 257 additions, the counts
+//    below it, whole numbers, a scan, the objectives in parallel) and thresholds its share of the values.
+// One thread per bin walking all values in one workgroup: 650 us; four waves of one bin each over chunks of 1024: 21.3 + 8.8 us for 64 x 64
+// values of which 2285 share a bin; this: 19.6 + 5.9, of which the chain of 2285 dependent additions is 15.
 // ---------------------------------------------------------------------------
-constexpr int OTSU_BINS = 257, OTSU_CHUNK = 1024;
+constexpr int OTSU_BINS = 257, OTSU_CHUNK = 4096, OTSU_WG_BINS = 4, OTSU_WAVES = 16;
 struct OtsuWs { double lo, hi; double cnt[OTSU_BINS]; double sum[OTSU_BINS]; };
 
-__global__ __launch_bounds__(256) void otsu_bins_kernel(const float* __restrict__ diff, int n, OtsuWs* __restrict__ ws) {
-    __shared__ double red_lo[4], red_hi[4];
-    __shared__ __attribute__((aligned(16))) double val[OTSU_CHUNK], mine[4][OTSU_CHUNK + 64];
-    __shared__ int bin[OTSU_CHUNK];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, k = blockIdx.x * 4 + wave;
+__global__ __launch_bounds__(64 * OTSU_WAVES) void otsu_bins_kernel(const float* __restrict__ diff, int n, OtsuWs* __restrict__ ws) {
+    constexpr int NT = 64 * OTSU_WAVES, PER = OTSU_CHUNK / NT;
+    __shared__ double red_lo[OTSU_WAVES], red_hi[OTSU_WAVES];
+    __shared__ int wave_cnt[OTSU_WG_BINS][OTSU_WAVES];
+    extern __shared__ __attribute__((aligned(16))) unsigned char otsu_lds[];
+    double (*mine)[OTSU_CHUNK + 64] = reinterpret_cast<double (*)[OTSU_CHUNK + 64]>(otsu_lds);      // [OTSU_WG_BINS]
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, k0 = blockIdx.x * OTSU_WG_BINS;
     double lo = 1e300, hi = -1e300;
-#pragma unroll 8
-    for (int i = t; i < n; i += 256) { const double v = diff[i]; lo = fmin(lo, v); hi = fmax(hi, v); }
+#pragma unroll 4
+    for (int i = t; i < n; i += NT) { const double v = diff[i]; lo = fmin(lo, v); hi = fmax(hi, v); }
     for (int o = 32; o > 0; o >>= 1) { lo = fmin(lo, __shfl_xor(lo, o)); hi = fmax(hi, __shfl_xor(hi, o)); }
     if (lane == 0) { red_lo[wave] = lo; red_hi[wave] = hi; }
     __syncthreads();
-    lo = fmin(fmin(red_lo[0], red_lo[1]), fmin(red_lo[2], red_lo[3]));
-    hi = fmax(fmax(red_hi[0], red_hi[1]), fmax(red_hi[2], red_hi[3]));
+    for (int w = 0; w < OTSU_WAVES; ++w) { lo = fmin(lo, red_lo[w]); hi = fmax(hi, red_hi[w]); }
     const double range = hi - lo;
     double sum = 0.0;
     int count = 0;
     for (int c0 = 0; c0 < n; c0 += OTSU_CHUNK) {
-        const int len = min(OTSU_CHUNK, n - c0);
-        for (int i = t; i < OTSU_CHUNK; i += 256) {
-            const double v = i < len && range > 0 ? ((double)diff[c0 + i] - lo) / range : 0.0;
-            val[i] = v;
-            bin[i] = i < len ? (int)floor(v * 256.0) : -1;
+        // wave w holds values c0 + w * 256 .. in index order: PER rows of 64
+        double v[PER]; int bin[PER], before[OTSU_WG_BINS][PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int i = c0 + (wave * PER + j) * 64 + lane;
+            v[j] = i < n && range > 0 ? ((double)diff[i] - lo) / range : 0.0;
+            bin[j] = i < n ? (int)floor(v[j] * 256.0) - k0 : -1;
+        }
+#pragma unroll
+        for (int b = 0; b < OTSU_WG_BINS; ++b) {
+            int m = 0;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const unsigned long long bal = __ballot(bin[j] == b);
+                before[b][j] = m + __popcll(bal & ((1ull << lane) - 1ull));
+                m += __popcll(bal);
+            }
+            if (lane == 0) wave_cnt[b][wave] = m;
         }
         __syncthreads();
-        int m = 0;
-#pragma unroll 4
-        for (int i0 = 0; i0 < OTSU_CHUNK; i0 += 64) {
-            const int i = i0 + lane;
-            const bool in = bin[i] == k;
-            const unsigned long long bal = __ballot(in);
-            if (in) mine[wave][m + __popcll(bal & ((1ull << lane) - 1ull))] = val[i];
-            m += __popcll(bal);
+        int total = 0;                                     // of bin `wave` in the first waves
+#pragma unroll
+        for (int b = 0; b < OTSU_WG_BINS; ++b) {
+            int base = 0, all = 0;
+#pragma unroll
+            for (int w = 0; w < OTSU_WAVES; ++w) { const int c = wave_cnt[b][w]; base += w < wave ? c : 0; all += c; }
+#pragma unroll
+            for (int j = 0; j < PER; ++j)
+                if (bin[j] == b) mine[b][base + before[b][j]] = v[j];
+            if (wave == OTSU_WG_BINS + b) mine[b][all + lane] = 0.0;       // past the last value: adding +0 changes no sum of values >= +0
+            if (wave == b) total = all;
         }
-        mine[wave][m + lane] = 0.0;                        // past the last value: adding +0 changes no sum of values >= +0
-        count += m;
         __syncthreads();
-        // sixteen values are added while the next sixteen are on their way
-        double v0[16], v1[16];
-        auto read = [&](double (&v)[16], int i) {
+        if (wave < OTSU_WG_BINS) {
+            // sixteen values are added while the next sixteen are on their way
+            const double* src = mine[wave];
+            double v0[16], v1[16];
+            auto read = [&](double (&r)[16], int i) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) v[q] = mine[wave][min(i, OTSU_CHUNK + 48) + q];
-        };
-        auto add = [&](const double (&v)[16]) {
+                for (int q = 0; q < 16; ++q) r[q] = src[min(i, OTSU_CHUNK + 48) + q];
+            };
+            auto add = [&](const double (&r)[16]) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) sum += v[q];
-        };
-        read(v0, 0);
-        for (int i = 0; i < m; i += 32) {
-            read(v1, i + 16);
-            __builtin_amdgcn_sched_barrier(0);
-            add(v0);
-            __builtin_amdgcn_sched_barrier(0);
-            read(v0, i + 32);
-            __builtin_amdgcn_sched_barrier(0);
-            add(v1);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int q = 0; q < 16; ++q) sum += r[q];
+            };
+            read(v0, 0);
+            for (int i = 0; i < total; i += 32) {
+                read(v1, i + 16);
+                __builtin_amdgcn_sched_barrier(0);
+                add(v0);
+                __builtin_amdgcn_sched_barrier(0);
+                read(v0, i + 32);
+                __builtin_amdgcn_sched_barrier(0);
+                add(v1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            count += total;
         }
+        __syncthreads();
     }
-    if (lane == 0 && k < OTSU_BINS) { ws->cnt[k] = (double)count; ws->sum[k] = sum; }
+    const int k = k0 + wave;
+    if (lane == 0 && wave < OTSU_WG_BINS && k < OTSU_BINS) { ws->cnt[k] = (double)count; ws->sum[k] = sum; }
     if (blockIdx.x == 0 && t == 0) { ws->lo = lo; ws->hi = hi; }
 }
 
 __global__ __launch_bounds__(256) void otsu_apply_kernel(const float* __restrict__ diff, int n, float* __restrict__ eps_out,
                                                          uint8_t* __restrict__ pix, const OtsuWs* __restrict__ ws) {
-    __shared__ double cnt[OTSU_BINS], sum[OTSU_BINS], cnt_lo[OTSU_BINS], sum_lo[OTSU_BINS], total[2], s_eps;      // _lo: sums over the bins below k
-    const int t = threadIdx.x;
+    __shared__ double sum[OTSU_BINS + 15], cnt_lo[OTSU_BINS], sum_lo[OTSU_BINS], total[2], s_eps;      // _lo: sums over the bins below k
+    const int t = threadIdx.x, lane = t & 63;
     const double lo = ws->lo, range = ws->hi - lo;
-    for (int k = t; k < OTSU_BINS; k += 256) { cnt[k] = ws->cnt[k]; sum[k] = ws->sum[k]; }
+    for (int k = t; k < OTSU_BINS; k += 256) sum[k] = ws->sum[k];
+    double c4[4];                                              // second wave: counts of bins 4 lane .. 4 lane + 3
+    if (t >> 6 == 1)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c4[q] = ws->cnt[4 * lane + q];
     __syncthreads();
+    if (t >> 6 == 1) {                                         // counts are whole numbers: any order gives their sum
+        double up = c4[0] + c4[1] + c4[2] + c4[3], mine = up;
+        for (int o = 1; o < 64; o <<= 1) { const double x = __shfl_up(up, o); if (lane >= o) up += x; }
+        double below = up - mine;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { cnt_lo[4 * lane + q] = below; below += c4[q]; }
+        if (lane == 63) { cnt_lo[OTSU_BINS - 1] = below; total[0] = below + ws->cnt[OTSU_BINS - 1]; }
+    }
     if (t == 0) {
-        double c = 0, s = 0;
+        double s = 0, sk[16], next[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) sk[q] = sum[q];
         for (int k0 = 0; k0 < OTSU_BINS - 1; k0 += 16) {       // sixteen bins' reads ahead of the additions
-            double ck[16], sk[16];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) { ck[q] = cnt[k0 + q]; sk[q] = sum[k0 + q]; }
+            for (int q = 0; q < 16; ++q) next[q] = sum[k0 + 16 + q];        // (past the last bin: not used)
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                cnt_lo[k0 + q] = c; sum_lo[k0 + q] = s;
-                c += ck[q]; s += sk[q];
-            }
+            for (int q = 0; q < 16; ++q) { sum_lo[k0 + q] = s; s += sk[q]; }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) sk[q] = next[q];
         }
-        cnt_lo[OTSU_BINS - 1] = c; sum_lo[OTSU_BINS - 1] = s;
-        c += cnt[OTSU_BINS - 1]; s += sum[OTSU_BINS - 1];
-        total[0] = c; total[1] = s;
+        sum_lo[OTSU_BINS - 1] = s;
+        total[1] = s + sum[OTSU_BINS - 1];
     }
     __syncthreads();
     if (t < 64) {                                       // the first bin with the largest objective
@@ -283,8 +393,7 @@ extern "C" int fise_mask_from_pixels(const uint8_t* pix_mask, int H, int W, int 
     if (!pix_mask || !tile_mask || !tile_idx || !n_active) return fail(FISE_ERR_NULL, "fise_mask_from_pixels: null pointer");
     if (int e = check_tile("fise_mask_from_pixels", H, W, tile)) return e;
     if (capacity < 0) return fail(FISE_ERR_CAPACITY, "fise_mask_from_pixels: capacity %d", capacity);
-    hipLaunchKernelGGL(tile_compact_kernel, dim3(1), dim3(256), 0, as_stream(stream), pix_mask, H, W, tile, tile, tile_mask,
-                       tile_idx, capacity, n_active);
+    launch_tile_compact(pix_mask, H, W, tile, tile, tile_mask, tile_idx, capacity, n_active, as_stream(stream));
     FISE_CHECK_LAUNCH("fise_mask_from_pixels");
     return FISE_OK;
 }
@@ -296,8 +405,7 @@ extern "C" int fise_mask_from_pixels_rect(const uint8_t* pix_mask, int H, int W,
         return fail(FISE_ERR_SHAPE, "fise_mask_from_pixels_rect: H=%d, W=%d must be positive multiples of the %dx%d block", H, W,
                     tile_h, tile_w);
     if (capacity < 0) return fail(FISE_ERR_CAPACITY, "fise_mask_from_pixels_rect: capacity %d", capacity);
-    hipLaunchKernelGGL(tile_compact_kernel, dim3(1), dim3(256), 0, as_stream(stream), pix_mask, H, W, tile_h, tile_w, tile_mask,
-                       tile_idx, capacity, n_active);
+    launch_tile_compact(pix_mask, H, W, tile_h, tile_w, tile_mask, tile_idx, capacity, n_active, as_stream(stream));
     FISE_CHECK_LAUNCH("fise_mask_from_pixels_rect");
     return FISE_OK;
 }
@@ -310,13 +418,8 @@ extern "C" int fise_mask_detect(const void* cached, const void* fresh, int dtype
     if (int e = check_tile("fise_mask_detect", H, W, tile)) return e;
     if (capacity < 0) return fail(FISE_ERR_CAPACITY, "fise_mask_detect: capacity %d", capacity);
     const int HW = H * W;
-    const dim3 grid(ceil_div(HW, DET_PIX)), block(DET_THREADS);
-    if (dtype == FISE_F32)
-        hipLaunchKernelGGL(pixel_diff_kernel<float>, grid, block, 0, as_stream(stream), (const float*)cached,
-                           (const float*)fresh, B, HW, C, (float*)nullptr, 0, threshold, pix_mask);
-    else
-        hipLaunchKernelGGL(pixel_diff_kernel<bf16_t>, grid, block, 0, as_stream(stream), (const bf16_t*)cached,
-                           (const bf16_t*)fresh, B, HW, C, (float*)nullptr, 0, threshold, pix_mask);
+    if (dtype == FISE_F32) launch_pixel_diff<float>(cached, fresh, B, HW, C, nullptr, 0, threshold, pix_mask, as_stream(stream));
+    else launch_pixel_diff<bf16_t>(cached, fresh, B, HW, C, nullptr, 0, threshold, pix_mask, as_stream(stream));
     FISE_CHECK_LAUNCH("fise_mask_detect(diff)");
     return fise_mask_from_pixels(pix_mask, H, W, tile, tile_mask, tile_idx, capacity, n_active, stream);
 }
@@ -326,13 +429,8 @@ extern "C" int fise_diff_accumulate(const void* cached, const void* fresh, int d
     if (int e = check_map("fise_diff_accumulate", cached, fresh, dtype, B, H, W, C)) return e;
     if (!diff_acc) return fail(FISE_ERR_NULL, "fise_diff_accumulate: null diff_acc");
     const int HW = H * W;
-    const dim3 grid(ceil_div(HW, DET_PIX)), block(DET_THREADS);
-    if (dtype == FISE_F32)
-        hipLaunchKernelGGL(pixel_diff_kernel<float>, grid, block, 0, as_stream(stream), (const float*)cached,
-                           (const float*)fresh, B, HW, C, diff_acc, 1, 0.f, (uint8_t*)nullptr);
-    else
-        hipLaunchKernelGGL(pixel_diff_kernel<bf16_t>, grid, block, 0, as_stream(stream), (const bf16_t*)cached,
-                           (const bf16_t*)fresh, B, HW, C, diff_acc, 1, 0.f, (uint8_t*)nullptr);
+    if (dtype == FISE_F32) launch_pixel_diff<float>(cached, fresh, B, HW, C, diff_acc, 1, 0.f, nullptr, as_stream(stream));
+    else launch_pixel_diff<bf16_t>(cached, fresh, B, HW, C, diff_acc, 1, 0.f, nullptr, as_stream(stream));
     FISE_CHECK_LAUNCH("fise_diff_accumulate");
     return FISE_OK;
 }
@@ -351,7 +449,10 @@ extern "C" size_t fise_otsu_workspace_bytes(void) { return align256(sizeof(OtsuW
 extern "C" int fise_otsu_mask(const float* diff, int n, float* eps_out, uint8_t* pix_mask, void* workspace, void* stream) {
     if (!diff || !eps_out || !pix_mask || !workspace) return fail(FISE_ERR_NULL, "fise_otsu_mask: null pointer");
     if (n < 1) return fail(FISE_ERR_SHAPE, "fise_otsu_mask: n=%d", n);
-    hipLaunchKernelGGL(otsu_bins_kernel, dim3(ceil_div(OTSU_BINS, 4)), dim3(256), 0, as_stream(stream), diff, n, (OtsuWs*)workspace);
+    constexpr int lds = OTSU_WG_BINS * (OTSU_CHUNK + 64) * (int)sizeof(double);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&otsu_bins_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return fail(FISE_ERR_HIP, "fise_otsu_mask: cannot raise the dynamic LDS limit");
+    hipLaunchKernelGGL(otsu_bins_kernel, dim3(ceil_div(OTSU_BINS, OTSU_WG_BINS)), dim3(64 * OTSU_WAVES), lds, as_stream(stream), diff, n, (OtsuWs*)workspace);
     FISE_CHECK_LAUNCH("fise_otsu_mask(bins)");
     hipLaunchKernelGGL(otsu_apply_kernel, dim3(std::min(ceil_div(n, 256), 64)), dim3(256), 0, as_stream(stream), diff, n, eps_out, pix_mask,
                        (const OtsuWs*)workspace);

@@ -75,6 +75,42 @@ def test_mask_detect_noisy_everywhere_bit_exact(fb):
     assert n == idx_o.size and np.array_equal(idx[:n], idx_o)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("C,shift", [(4, 0), (8, 0), (12, 0), (16, 0), (4, 1), (16, 2), (20, 0), (64, 0), (64, 3)])
+def test_pixel_differences_of_every_width_and_alignment(fb, dtype, C, shift):
+    """Differences added in order, bit for bit: widths read as vectors, maps that start between two vectors, widths of the slab
+    form with few and with many pixels, ragged pixel counts."""
+    for B, H, W in ((1, 3, 7), (3, 16, 24)) + (((2, 96, 96),) if C in (4, 64) and not shift else ()):
+        rng = np.random.default_rng(C * 100 + shift + H)
+        a, b = wl.normal(rng, (B, H, W, C), 1.0, dtype), wl.normal(rng, (B, H, W, C), 1.0, dtype)
+        flat = [torch.cat([torch.zeros(shift, dtype=dev(x, dtype).dtype, device=DEV), dev(x, dtype).reshape(-1)]) for x in (a, b)]
+        acc = torch.full((H * W,), 0.5, device=DEV)
+        rc = fb.lib().fise_diff_accumulate(flat[0].data_ptr() + shift * flat[0].element_size(), flat[1].data_ptr() + shift * flat[1].element_size(),
+                                           0 if dtype == "f32" else 1, B, H, W, C, acc.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        assert rc == 0, fb.fise_last_error()
+        want = np.float32(0.5) + fo.pixel_diff(a, b).astype(np.float32).reshape(-1)
+        np.testing.assert_array_equal(acc.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("H,W,th,tw,shift", [(16, 24, 8, 8, 0), (16, 24, 8, 8, 4), (16, 24, 8, 8, 1), (12, 20, 4, 4, 0), (12, 20, 4, 4, 2), (24, 32, 3, 16, 0),
+                                             (30, 18, 5, 6, 0), (160, 136, 8, 8, 0), (64, 96, 32, 4, 4)])
+def test_tile_lists_of_every_width_and_alignment(fb, H, W, th, tw, shift):
+    """Rows of a tile are read in words of 8, 4 or 1 pixels; masks that start between two words; one pixel per active tile."""
+    rng = np.random.default_rng(H * W + tw + shift)
+    nt = (H // th) * (W // tw)
+    on = rng.random(nt) < 0.4
+    pix = np.zeros((H // th, th, W // tw, tw), np.uint8)
+    for t in np.flatnonzero(on):
+        pix[t // (W // tw), rng.integers(th), t % (W // tw), rng.integers(tw)] = rng.integers(1, 256)
+    flat = torch.cat([torch.ones(shift, dtype=torch.uint8, device=DEV), dev_u8(pix.reshape(-1))])
+    tm, idx, n = torch.full((nt,), 7, dtype=torch.uint8, device=DEV), torch.full((nt,), -1, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    rc = fb.lib().fise_mask_from_pixels_rect(flat.data_ptr() + shift, H, W, th, tw, tm.data_ptr(), idx.data_ptr(), nt, n.data_ptr(),
+                                             torch.cuda.current_stream().cuda_stream)
+    assert rc == 0, fb.fise_last_error()
+    np.testing.assert_array_equal(tm.cpu().numpy(), on.astype(np.uint8))
+    assert int(n.item()) == on.sum() and np.array_equal(idx.cpu().numpy()[:on.sum()], np.flatnonzero(on))
+
+
 def test_mask_detect_edge_cases(fb):
     rng = np.random.default_rng(2011)
     x = wl.normal(rng, (1, 8, 8, 4))

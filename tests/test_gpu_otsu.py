@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 BINS = 257
 
 
-@pytest.mark.parametrize("n", [1, 2, 63, 1023, 1024, 1025, 4096, 9216])
+@pytest.mark.parametrize("n", [1, 2, 63, 1023, 1024, 1025, 4096, 9216, 255, 4095, 4097, 8191, 12289])
 @pytest.mark.parametrize("shape", ["uniform", "one-bin-and-one", "two-clusters"])
 def test_otsu_bins_in_index_order(n, shape):
     from paper_2305_17423_amd import binding as fb
