@@ -159,6 +159,9 @@ def _dt(t):
 
 def _stream(stream):
     if stream is None:
+        # the handle alone: the Stream object around it costs 2.9 us a call, more than the launch (a mask detection 6.9 -> 4 us)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 
