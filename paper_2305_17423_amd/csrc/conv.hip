@@ -235,15 +235,15 @@ __global__ __launch_bounds__(256) void conv_f32_tile_kernel(const float* __restr
 
 // The same product for a few tiles, where its chain of stages and barriers is all the time there is: eight waves share the K
 // range of one 32 x 32 tile in units of (tap, 8 channels), operands go from memory into the matrix registers (a lane
-// loads four consecutive channels of its row and of its column, the two halves of a wave eight), a batch of eight units
+// loads four consecutive channels of its row and of its column, the two halves of a wave eight), a batch of nine units
 // is requested at once, and the waves' sums meet in LDS.  One barrier.  What bounds it is the round trips of its batches (32-byte
-// pieces).  160 rows x 64 x 576: 19.4 -> 8.9 us.
+// pieces); nine a batch are the one trip that 64 channels under 3x3 need (80 rows x 64 x 576: 9.0 -> 8.3 us, 19.4 on the staged kernel).
 __global__ __launch_bounds__(512) void conv_f32_wave_kernel(const float* __restrict__ x, int Cin, int B, int Hin, int Win,
                                                             const float* __restrict__ w, const float* __restrict__ bias, int Cout,
                                                             int ksize, int stride, int ups, const float* __restrict__ temb,
                                                             const float* residual, const int* __restrict__ tile_idx, int Ma, int tile,
                                                             int tile_w, int Ho, int Wo, FastDiv d_units, float* y) {
-    constexpr int NW = 8, BATCH = 8;
+    constexpr int NW = 8, BATCH = 9;
     __shared__ float part[NW][32][33];
     __shared__ int rb[32], rpix[32];
     const int t = threadIdx.x, lane = t & 63, l32 = lane & 31, hl = lane >> 5, rows = B * Ma;
