@@ -77,16 +77,29 @@ int run_resnet(const fise_resnet_args* a, void* ws, const IgemmWorkspace* iw, hi
                                               a->gn1_beta, dv->ss_in, ws, st)) return e;
         } else if (int e = fise_groupnorm_stats(a->x0, a->x1, FISE_BF16, B, H, W, a->C0, a->C1, a->G, 1e-5f, a->gn1_mean, a->gn1_rstd, ws, st)) return e;
     }
+    // Given statistics, no maps kept: both convolutions' activated inputs in one launch, conv1's epilogue completes the second.  The table
+    // it needs lies at the end of the K splits' scratch.
+    IgemmWorkspace cut;
+    float2* ss2 = nullptr;
+    const size_t ss_bytes = align256((size_t)B * Co * sizeof(float2));
+    if (!dv && !a->stats_fresh && iw && iw->partial && iw->partial_bytes >= 2 * ss_bytes) {
+        cut = *iw;
+        cut.partial_bytes = (cut.partial_bytes - ss_bytes) / 256 * 256;
+        ss2 = (float2*)((char*)cut.partial + cut.partial_bytes);
+        iw = &cut;
+    }
     // the normalised + activated input (active tiles and their ring) is written once, then convolved
-    if (!have_acts)
+    if (ss2) {
+        if (int e = launch_resnet_acts(a, act1, act2, ss2, st, iw)) return e;
+    } else if (!have_acts)
         if (int e = launch_gn_act_halo(a->x0, a->x1, a->C0, a->C1, B, H, W, a->gn1_mean, a->gn1_rstd, a->gn1_gamma, a->gn1_beta, a->G, 1,
                                        a->tile_idx, a->n_active, a->tile, act1, st, iw)) return e;
     IgemmArgs c1 = conv_args(act1, nullptr, Ci, 0, B, H, W, H, W, 3, 1, 0, a->conv1_w, a->conv1_b, Co, a->tile_idx,
                              a->n_active, a->tile, a->h1_cache);
     c1.temb = a->temb; c1.temb_stride = a->temb_stride;
-    if (dv && !a->stats_fresh) {       // conv2's input: SiLU(GN2(h1)) under the cached statistics, from conv1's epilogue
+    if (ss2 || (dv && !a->stats_fresh)) {       // conv2's input: SiLU(GN2(h1)) under the cached statistics, from conv1's epilogue
         c1.nview = 1;
-        c1.view[0] = GnView{(bf16_t*)dv->act_mid, dv->ss_mid, Co, 0, 1, 0};
+        c1.view[0] = GnView{(bf16_t*)act2, ss2 ? ss2 : dv->ss_mid, Co, 0, 1, 0};
     }
     if (int e = launch_igemm(c1, iw, st)) return e;
     if (a->stats_fresh) {
@@ -95,7 +108,7 @@ int run_resnet(const fise_resnet_args* a, void* ws, const IgemmWorkspace* iw, hi
                                               a->gn2_beta, dv->ss_mid, ws, st)) return e;
         } else if (int e = fise_groupnorm_stats(a->h1_cache, nullptr, FISE_BF16, B, H, W, Co, 0, a->G, 1e-5f, a->gn2_mean, a->gn2_rstd, ws, st)) return e;
     }
-    if (!have_acts)
+    if (!have_acts && !ss2)
         if (int e = launch_gn_act_halo(a->h1_cache, nullptr, Co, 0, B, H, W, a->gn2_mean, a->gn2_rstd, a->gn2_gamma, a->gn2_beta, a->G, 1,
                                        a->tile_idx, a->n_active, a->tile, act2, st)) return e;
     IgemmArgs c2 = conv_args(act2, nullptr, Co, 0, B, H, W, H, W, 3, 1, 0, a->conv2_w, a->conv2_b, Co, a->tile_idx,

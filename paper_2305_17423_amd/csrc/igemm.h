@@ -179,6 +179,9 @@ int launch_gn_stats_table(const void* x0, const void* x1, int B, int H, int W, i
 int launch_gn_act_halo(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, const float* mean, const float* rstd,
                        const void* gamma, const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act,
                        hipStream_t st, const IgemmWorkspace* iw = nullptr);
+// A ResNet block's two activated inputs under given statistics in one launch: act1 as above, of act2 (from h1_cache) the ring only, and the
+// scale / shift table ss2 [B, Cout] with which conv1's epilogue writes act2 at the active pixels.
+int launch_resnet_acts(const fise_resnet_args* a, void* act1, void* act2, float2* ss2, hipStream_t st, const IgemmWorkspace* iw);
 // ws: scratch for the key-split partials (attention_workspace_bytes; null or too small = no key split)
 size_t attention_workspace_bytes(int B, int M, int n_keys, int C, int heads);
 int launch_attention(const void* q, const void* K, const void* Vt, int B, int M, int n_keys, int n_stride, int C,

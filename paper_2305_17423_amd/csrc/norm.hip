@@ -150,34 +150,42 @@ __global__ void masked_gn_silu_kernel(const T* __restrict__ x, const float* __re
 // convolution that follows reads plain activations instead of re-evaluating the nonlinearity for
 // each of its nine taps and each of its column tiles.  Neighbouring tiles write identical values
 // to their shared ring.  One thread per (pixel, 8 channels).
-__global__ __launch_bounds__(256) void gn_act_halo_kernel(const bf16_t* __restrict__ x0, const bf16_t* __restrict__ x1, int C0,
-                                                          int C1, int H, int W, const float* __restrict__ mean,
-                                                          const float* __restrict__ rstd, const bf16_t* __restrict__ gamma,
-                                                          const bf16_t* __restrict__ beta, int G, int silu,
-                                                          const int* __restrict__ tile_idx, int tile, bf16_t* __restrict__ act,
-                                                          int* __restrict__ zero, int n_zero) {
-    for (int i = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < n_zero; i += gridDim.x * gridDim.y * gridDim.z * 256) zero[i] = 0;
-    const int C = C0 + C1, chunks = C / 8, side = tile + 2;
-    const int t = tile_idx[blockIdx.x], b = blockIdx.y;
-    const int tiles_w = W / tile;
-    const int y0 = (t / tiles_w) * tile - 1, x0p = (t % tiles_w) * tile - 1;
-    const int items = side * side * chunks;
-    const int cpg = C / G;
-    for (int it = blockIdx.z * 256 + threadIdx.x; it < items; it += gridDim.z * 256) {
-        const int p = it / chunks, ch = it % chunks;
-        const int y = y0 + p / side, x = x0p + p % side;
+// Two maps share a launch: of the second one, whose active pixels the convolution of the first rewrites, only the ring is
+// written here (that convolution's epilogue adds its active pixels through the scale / shift table that the launch also writes).
+// ResNet block of 1024 rows x 320 channels: two activation launches of 4.5 us -> one of 5.3, the block 27.4 -> 24.5 us; 160 rows, 2560 to
+// 1280 channels 56.8 -> 53.7.
+struct ActMap {
+    const bf16_t* x0; const bf16_t* x1; int C0, C1; const float* mean; const float* rstd; const bf16_t* gamma; const bf16_t* beta; int G, silu;
+    bf16_t* act; float2* ss;                             // ss: table to write (null: none)
+    int z, cpg; FastDiv d_chunks, d_cpg;                 // workgroups per tile (0: no such map), channels per group; divisors
+};
+
+template <bool RING>
+__device__ __forceinline__ void act_tile(const ActMap& a, int zi, int H, int W, int t, int tile, FastDiv d_side, FastDiv d_tiles_w) {
+    const int b = blockIdx.y, C = a.C0 + a.C1, chunks = C / 8, side = tile + 2, tiles_w = W / tile;
+    const int ty = (int)fdiv((unsigned)t, d_tiles_w), y0 = ty * tile - 1, x0 = (t - ty * tiles_w) * tile - 1;
+    const int items = (RING ? 4 * (tile + 1) : side * side) * chunks;
+    for (int it = zi * 256 + threadIdx.x; it < items; it += a.z * 256) {
+        const int p = (int)fdiv((unsigned)it, a.d_chunks), c = (it - p * chunks) * 8;
+        int py, px;
+        if (RING) {                                      // top row, bottom row, then the two sides
+            const int q = p - 2 * side;
+            py = q >= 0 ? 1 + (q >> 1) : p >= side ? side - 1 : 0;
+            px = q >= 0 ? (q & 1) * (side - 1) : p >= side ? p - side : p;
+        } else {
+            py = (int)fdiv((unsigned)p, d_side); px = p - py * side;
+        }
+        const int y = y0 + py, x = x0 + px;
         if (y < 0 || y >= H || x < 0 || x >= W) continue;
-        const int c = ch * 8;
         const size_t pix = ((size_t)b * H + y) * W + x;
-        const uint4 v = c < C0 ? *reinterpret_cast<const uint4*>(x0 + pix * C0 + c)
-                               : *reinterpret_cast<const uint4*>(x1 + pix * C1 + (c - C0));
-        const uint4 gv = *reinterpret_cast<const uint4*>(gamma + c), bv = *reinterpret_cast<const uint4*>(beta + c);
+        const uint4 v = c < a.C0 ? *reinterpret_cast<const uint4*>(a.x0 + pix * a.C0 + c) : *reinterpret_cast<const uint4*>(a.x1 + pix * a.C1 + (c - a.C0));
+        const uint4 gv = *reinterpret_cast<const uint4*>(a.gamma + c), bv = *reinterpret_cast<const uint4*>(a.beta + c);
         const unsigned xw[4] = {v.x, v.y, v.z, v.w}, gw[4] = {gv.x, gv.y, gv.z, gv.w}, bw[4] = {bv.x, bv.y, bv.z, bv.w};
         unsigned ow[4];
         // the 8 channels of a chunk lie in one group or straddle one boundary (cpg >= 8 here; else divide per channel)
-        const int g0 = c / cpg, edge = (g0 + 1) * cpg;
-        const int g1 = min(g0 + 1, G - 1);
-        const float mu0 = mean[b * G + g0], rs0 = rstd[b * G + g0], mu1 = mean[b * G + g1], rs1 = rstd[b * G + g1];
+        const int g0 = (int)fdiv((unsigned)c, a.d_cpg), edge = (g0 + 1) * a.cpg;
+        const int g1 = min(g0 + 1, a.G - 1);
+        const float mu0 = a.mean[b * a.G + g0], rs0 = a.rstd[b * a.G + g0], mu1 = a.mean[b * a.G + g1], rs1 = a.rstd[b * a.G + g1];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             float r[2];
@@ -185,20 +193,35 @@ __global__ __launch_bounds__(256) void gn_act_halo_kernel(const bf16_t* __restri
             for (int q = 0; q < 2; ++q) {
                 const int cc = c + 2 * e + q;
                 float mu, rs;
-                if (cpg >= 8) { const bool hi = cc >= edge; mu = hi ? mu1 : mu0; rs = hi ? rs1 : rs0; }
-                else { const int g = cc / cpg; mu = mean[b * G + g]; rs = rstd[b * G + g]; }
+                if (a.cpg >= 8) { const bool hi = cc >= edge; mu = hi ? mu1 : mu0; rs = hi ? rs1 : rs0; }
+                else { const int g = (int)fdiv((unsigned)cc, a.d_cpg); mu = a.mean[b * a.G + g]; rs = a.rstd[b * a.G + g]; }
                 const float xv = q ? __uint_as_float(xw[e] & 0xffff0000u) : __uint_as_float(xw[e] << 16);
                 const float ga = q ? __uint_as_float(gw[e] & 0xffff0000u) : __uint_as_float(gw[e] << 16);
                 const float be = q ? __uint_as_float(bw[e] & 0xffff0000u) : __uint_as_float(bw[e] << 16);
                 const float sc = rs * ga;
                 float u = fmaf(xv, sc, fmaf(-mu, sc, be));      // the same two operations as the scale / shift table form
-                if (silu) u = silu_f(u);
+                if (a.silu) u = silu_f(u);
                 r[q] = u;
             }
             ow[e] = f2bf2(r[0], r[1]);
         }
-        *reinterpret_cast<uint4*>(act + pix * C + c) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
+        *reinterpret_cast<uint4*>(a.act + pix * C + c) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
     }
+}
+
+template <bool PAIR>
+__global__ __launch_bounds__(256) void gn_act_halo_kernel(const ActMap first, const ActMap second, int H, int W, const int* __restrict__ tile_idx,
+                                                          int tile, FastDiv d_side, FastDiv d_tiles_w, int* __restrict__ zero, int n_zero) {
+    const int t = tile_idx[blockIdx.x];
+    for (int i = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < n_zero; i += gridDim.x * gridDim.y * gridDim.z * 256) zero[i] = 0;
+    if (!PAIR || (int)blockIdx.z < first.z) { act_tile<false>(first, blockIdx.z, H, W, t, tile, d_side, d_tiles_w); return; }
+    const int zi = (int)blockIdx.z - first.z, b = blockIdx.y;
+    for (int c = (blockIdx.x * second.z + zi) * 256 + threadIdx.x; c < second.C0; c += gridDim.x * second.z * 256) {
+        const int g = (int)fdiv((unsigned)c, second.d_cpg);
+        const float sc = second.rstd[b * second.G + g] * bf2f(second.gamma[c]);
+        second.ss[b * second.C0 + c] = make_float2(sc, fmaf(-second.mean[b * second.G + g], sc, bf2f(second.beta[c])));
+    }
+    act_tile<true>(second, zi, H, W, t, tile, d_side, d_tiles_w);
 }
 
 __global__ void gn_scale_shift_kernel(const float* __restrict__ mean, const float* __restrict__ rstd, const bf16_t* __restrict__ gamma,
@@ -218,20 +241,37 @@ int launch_gn_scale_shift(const float* mean, const float* rstd, const void* gamm
     return FISE_OK;
 }
 
+static ActMap act_map(const void* x0, const void* x1, int C0, int C1, const float* mean, const float* rstd, const void* gamma, const void* beta, int G,
+                      int silu, int tile, bool ring_only, void* act, float2* ss) {
+    const int npix = ring_only ? 4 * (tile + 1) : (tile + 2) * (tile + 2), chunks = (C0 + C1) / 8, cpg = (C0 + C1) / G;
+    return ActMap{(const bf16_t*)x0, (const bf16_t*)x1, C0, C1, mean, rstd, (const bf16_t*)gamma, (const bf16_t*)beta, G, silu, (bf16_t*)act, ss,
+                  std::max(1, std::min(64, ceil_div(npix * chunks, 512))), cpg, fast_div(chunks), fast_div(cpg)};
+}
+
+static int launch_act(const ActMap& first, const ActMap* second, int B, int H, int W, const int* tile_idx, int n_active, int tile, hipStream_t st, const IgemmWorkspace* iw) {
+    // a launch of its own for the counters costs 2.7 us (a ResNet block of 160 rows x 1280 channels takes 55)
+    const bool zero = iw && iw->counters && !iw->counters_zeroed;
+    const dim3 grid(n_active, B, first.z + (second ? second->z : 0));
+    int* const zp = zero ? iw->counters : nullptr; const int nz = zero ? IGEMM_COUNTERS : 0;
+    if (second) hipLaunchKernelGGL(gn_act_halo_kernel<true>, grid, dim3(256), 0, st, first, *second, H, W, tile_idx, tile, fast_div(tile + 2), fast_div(W / tile), zp, nz);
+    else hipLaunchKernelGGL(gn_act_halo_kernel<false>, grid, dim3(256), 0, st, first, first, H, W, tile_idx, tile, fast_div(tile + 2), fast_div(W / tile), zp, nz);
+    FISE_CHECK_LAUNCH("gn activation with halo");
+    if (zero) iw->counters_zeroed = true;
+    return FISE_OK;
+}
+
 int launch_gn_act_halo(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, const float* mean, const float* rstd,
                        const void* gamma, const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act,
                        hipStream_t st, const IgemmWorkspace* iw) {
     if (n_active <= 0) return FISE_OK;
-    // a launch of its own for the counters costs 2.7 us (a ResNet block of 160 rows x 1280 channels takes 67)
-    const bool zero = iw && iw->counters && !iw->counters_zeroed;
-    const int items = (tile + 2) * (tile + 2) * ((C0 + C1) / 8);
-    const int z = std::max(1, std::min(64, ceil_div(items, 512)));
-    hipLaunchKernelGGL(gn_act_halo_kernel, dim3(n_active, B, z), dim3(256), 0, st, (const bf16_t*)x0, (const bf16_t*)x1, C0, C1, H, W,
-                       mean, rstd, (const bf16_t*)gamma, (const bf16_t*)beta, G, silu, tile_idx, tile, (bf16_t*)act,
-                       zero ? iw->counters : nullptr, zero ? IGEMM_COUNTERS : 0);
-    FISE_CHECK_LAUNCH("gn activation with halo");
-    if (zero) iw->counters_zeroed = true;
-    return FISE_OK;
+    return launch_act(act_map(x0, x1, C0, C1, mean, rstd, gamma, beta, G, silu, tile, false, act, nullptr), nullptr, B, H, W, tile_idx, n_active, tile, st, iw);
+}
+
+int launch_resnet_acts(const fise_resnet_args* a, void* act1, void* act2, float2* ss2, hipStream_t st, const IgemmWorkspace* iw) {
+    if (a->n_active <= 0) return FISE_OK;
+    const ActMap h1 = act_map(a->h1_cache, nullptr, a->Cout, 0, a->gn2_mean, a->gn2_rstd, a->gn2_gamma, a->gn2_beta, a->G, 1, a->tile, true, act2, ss2);
+    return launch_act(act_map(a->x0, a->x1, a->C0, a->C1, a->gn1_mean, a->gn1_rstd, a->gn1_gamma, a->gn1_beta, a->G, 1, a->tile, false, act1, nullptr), &h1,
+                      a->B, a->H, a->W, a->tile_idx, a->n_active, a->tile, st, iw);
 }
 
 // LayerNorm of rows -> compact out[rows, C] (bf16).  General form: one wave per row held in

@@ -51,6 +51,9 @@ RES_CASES = [
     ("cfg4-16x16-1280", 2, 16, 16, 1280, 0, 1280, 4, 0.25, 0.02),
     ("up-concat-960-to-320", 2, 32, 32, 640, 320, 320, 4, 0.05, 0.02),
     ("down-320-to-640", 2, 16, 16, 320, 0, 640, 2, 0.5, 0.03),
+    # rings of the second activation map: three channels per group, tiles of one pixel; tiles that all touch, at every border
+    ("rings-tile-1-96", 2, 12, 8, 96, 0, 96, 1, 0.3, 0.05),
+    ("rings-touching-128-to-64", 1, 16, 24, 64, 64, 64, 4, 0.7, 0.05),
 ]
 
 
