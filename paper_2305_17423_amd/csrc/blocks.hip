@@ -167,35 +167,71 @@ int run_transformer(const fise_transformer_args* a, void* workspace, const Igemm
     if (dv && !(dv->trust && !a->stats_fresh))
         if (int e = launch_gn_act_halo(a->x, nullptr, C, 0, B, H, W, a->gn_mean, a->gn_rstd, a->gn_gamma, a->gn_beta, a->G, 0,
                                        a->tile_idx, a->n_active, a->tile, dv->act_in, st)) return e;
-    IgemmArgs pin = conv_args(dv ? dv->act_in : a->x, nullptr, C, 0, B, H, W, H, W, 1, 1, 0, a->pin_w, a->pin_b, C, a->tile_idx, a->n_active,
-                              a->tile, hb);
-    if (!dv) set_gn(pin, a->gn_mean, a->gn_rstd, a->gn_gamma, a->gn_beta, a->G, false);
-    pin.out_mode[0] = OUT_COMPACT_F32;
-    // every GEMM that completes the residual stream also emits the LayerNorm the next sub-block starts with
+    // the products behind a LayerNorm normalise the residual stream themselves; where their kernel does not take the width, every GEMM
+    // that completes the stream emits the normalised rows
+    const bool fused = norm_gemm_takes(NG_ROWS_LN, C, B, Ma, H, W);
     auto with_ln = [&](IgemmArgs& g, const void* gamma, const void* beta) {
+        if (fused) return;
         g.ln_gamma = (const bf16_t*)gamma; g.ln_beta = (const bf16_t*)beta; g.ln_eps = 1e-5f; g.ln_out = nb;
     };
-    with_ln(pin, a->ln1_g, a->ln1_b);
-    if (int e = launch_igemm(pin, iw, st)) return e;
+    auto normed = [&](const void* gamma, const void* beta, const void* w, int N, bf16_t* out) {
+        NormGemmArgs g{};
+        g.x = hb; g.src = NG_ROWS_LN; g.K = C; g.gamma = (const bf16_t*)gamma; g.beta = (const bf16_t*)beta; g.eps = 1e-5f;
+        g.tile_idx = a->tile_idx; g.tile = a->tile; g.tiles_w = W / a->tile; g.Ho = H; g.Wo = W; g.B = B; g.Ma = Ma;
+        g.w[0] = (const bf16_t*)w; g.N = g.sect_n = N; g.out[0] = out; g.mode[0] = OUT_COMPACT;
+        return g;
+    };
+    const int in_src = dv ? NG_MAP_RAW : NG_MAP_GN;
+    if (fused && norm_gemm_takes(in_src, C, B, Ma, H, W)) {
+        NormGemmArgs g = normed(a->gn_gamma, a->gn_beta, a->pin_w, C, (bf16_t*)hb);
+        g.x = dv ? dv->act_in : a->x; g.src = in_src; g.gn_mean = a->gn_mean; g.gn_rstd = a->gn_rstd; g.G = a->G;
+        g.bias = (const bf16_t*)a->pin_b; g.mode[0] = OUT_COMPACT_F32;
+        if (int e = launch_norm_gemm(g, st)) return e;
+    } else {
+        IgemmArgs pin = conv_args(dv ? dv->act_in : a->x, nullptr, C, 0, B, H, W, H, W, 1, 1, 0, a->pin_w, a->pin_b, C, a->tile_idx, a->n_active,
+                                  a->tile, hb);
+        if (!dv) set_gn(pin, a->gn_mean, a->gn_rstd, a->gn_gamma, a->gn_beta, a->G, false);
+        pin.out_mode[0] = OUT_COMPACT_F32;
+        with_ln(pin, a->ln1_g, a->ln1_b);
+        if (int e = launch_igemm(pin, iw, st)) return e;
+    }
     // self-attention: LN -> stacked QKV (K, V rows scattered into the caches) -> attention -> out-proj + residual
-    IgemmArgs qkv = lin(nb, C, a->qkv_w, nullptr, 3 * C);
-    qkv.nsect = 3; qkv.sect_n = C;
-    qkv.out[0] = qb; qkv.out_mode[0] = OUT_COMPACT;
-    qkv.out[1] = (bf16_t*)a->K_cache; qkv.out_mode[1] = OUT_MAP;
-    qkv.out[2] = (bf16_t*)a->Vt_cache; qkv.out_mode[2] = OUT_TOKENS_T;
-    if (int e = launch_igemm(qkv, iw, st)) return e;
+    if (fused) {
+        NormGemmArgs g = normed(a->ln1_g, a->ln1_b, a->qkv_w, 3 * C, qb);
+        g.sect_n = C;
+        g.w[1] = g.w[0] + (size_t)C * C; g.out[1] = (bf16_t*)a->K_cache; g.mode[1] = OUT_MAP;
+        g.w[2] = g.w[1] + (size_t)C * C; g.out[2] = (bf16_t*)a->Vt_cache; g.mode[2] = OUT_TOKENS_T;
+        if (int e = launch_norm_gemm(g, st)) return e;
+    } else {
+        IgemmArgs qkv = lin(nb, C, a->qkv_w, nullptr, 3 * C);
+        qkv.nsect = 3; qkv.sect_n = C;
+        qkv.out[0] = qb; qkv.out_mode[0] = OUT_COMPACT;
+        qkv.out[1] = (bf16_t*)a->K_cache; qkv.out_mode[1] = OUT_MAP;
+        qkv.out[2] = (bf16_t*)a->Vt_cache; qkv.out_mode[2] = OUT_TOKENS_T;
+        if (int e = launch_igemm(qkv, iw, st)) return e;
+    }
     if (int e = launch_attention(qb, a->K_cache, a->Vt_cache, B, Ma, H * W, H * W, C, a->heads, scale, ob, ws + wl.at, wl.at_bytes, st)) return e;
     IgemmArgs o1 = lin(ob, C, a->o1_w, a->o1_b, C); into_h(o1); with_ln(o1, a->ln2_g, a->ln2_b);
     if (int e = launch_igemm(o1, iw, st)) return e;
     // cross-attention against the context K/V
-    IgemmArgs q2 = lin(nb, C, a->q2_w, nullptr, C); q2.out[0] = qb;
-    if (int e = launch_igemm(q2, iw, st)) return e;
+    if (fused) {
+        if (int e = launch_norm_gemm(normed(a->ln2_g, a->ln2_b, a->q2_w, C, qb), st)) return e;
+    } else {
+        IgemmArgs q2 = lin(nb, C, a->q2_w, nullptr, C); q2.out[0] = qb;
+        if (int e = launch_igemm(q2, iw, st)) return e;
+    }
     if (int e = launch_attention(qb, a->K_ctx, a->Vt_ctx, B, Ma, a->n_ctx, a->n_ctx_stride, C, a->heads, scale, ob, nullptr, 0, st)) return e;
     IgemmArgs o2 = lin(ob, C, a->o2_w, a->o2_b, C); into_h(o2); with_ln(o2, a->ln3_g, a->ln3_b);
     if (int e = launch_igemm(o2, iw, st)) return e;
     // feed-forward: LN -> first GEMM with the GEGLU gate in its epilogue -> second GEMM + residual
-    IgemmArgs f1 = lin(nb, C, a->ff1_w, a->ff1_b, 4 * C); f1.geglu = 1; f1.out[0] = fb;
-    if (int e = launch_igemm(f1, iw, st)) return e;
+    if (fused) {
+        NormGemmArgs g = normed(a->ln3_g, a->ln3_b, a->ff1_w, 4 * C, fb);
+        g.geglu = 1; g.bias = (const bf16_t*)a->ff1_b;
+        if (int e = launch_norm_gemm(g, st)) return e;
+    } else {
+        IgemmArgs f1 = lin(nb, C, a->ff1_w, a->ff1_b, 4 * C); f1.geglu = 1; f1.out[0] = fb;
+        if (int e = launch_igemm(f1, iw, st)) return e;
+    }
     IgemmArgs f2 = lin(fb, 4 * C, a->ff2_w, a->ff2_b, C); into_h(f2);
     f2.mirror = (bf16_t*)(ws + wl.h16);               // bf16 copy of the final residual stream: A operand of the 1x1 out
     if (int e = launch_igemm(f2, iw, st)) return e;
@@ -328,11 +364,21 @@ extern "C" int fise_masked_attention(const void* x, const void* ln_gamma, const 
     bf16_t* nbuf = (bf16_t*)ws; bf16_t* qbuf = (bf16_t*)(ws + buf); bf16_t* obuf = (bf16_t*)(ws + 2 * buf);
     const float scale = 1.0f / sqrtf((float)d);
 
-    if (int e = launch_ln_rows(x, 0, rows, C, ln_gamma, ln_beta, 1e-5f, nbuf, tile_idx, tile, W / tile, H, W, Ma, st)) return e;
-    IgemmArgs g = linear_args(nbuf, Ma, B, C, Wq, nullptr, C);
-    g.tile_idx = tile_idx; g.tile = tile; g.tiles_w = W / tile; g.Ho = H; g.Wo = W;
     const GemmProduct qkv[3] = {{(const bf16_t*)Wq, C, qbuf, OUT_COMPACT}, {(const bf16_t*)Wk, C, (bf16_t*)K_cache, OUT_MAP}, {(const bf16_t*)Wv, C, (bf16_t*)Vt_cache, OUT_TOKENS_T}};
-    if (int e = launch_igemm_group(g, qkv, self ? 3 : 1, st)) return e;
+    const int nprod = self ? 3 : 1;
+    if (norm_gemm_takes(NG_MAP_LN, C, B, Ma, H, W)) {
+        NormGemmArgs g{};
+        g.x = x; g.src = NG_MAP_LN; g.K = C; g.gamma = (const bf16_t*)ln_gamma; g.beta = (const bf16_t*)ln_beta; g.eps = 1e-5f;
+        g.tile_idx = tile_idx; g.tile = tile; g.tiles_w = W / tile; g.Ho = H; g.Wo = W; g.B = B; g.Ma = Ma;
+        g.N = nprod * C; g.sect_n = C;
+        for (int i = 0; i < nprod; ++i) { g.w[i] = qkv[i].w; g.out[i] = qkv[i].out; g.mode[i] = qkv[i].mode; }
+        if (int e = launch_norm_gemm(g, st)) return e;
+    } else {
+        if (int e = launch_ln_rows(x, 0, rows, C, ln_gamma, ln_beta, 1e-5f, nbuf, tile_idx, tile, W / tile, H, W, Ma, st)) return e;
+        IgemmArgs g = linear_args(nbuf, Ma, B, C, Wq, nullptr, C);
+        g.tile_idx = tile_idx; g.tile = tile; g.tiles_w = W / tile; g.Ho = H; g.Wo = W;
+        if (int e = launch_igemm_group(g, qkv, nprod, st)) return e;
+    }
     if (self) {
         if (int e = launch_attention(qbuf, K_cache, Vt_cache, B, Ma, H * W, H * W, C, heads, scale, obuf, ws + 3 * buf, workspace_bytes - 3 * buf, st)) return e;
     } else {

@@ -150,6 +150,20 @@ struct GemmGroup { int first[GEMM_GROUP], N[GEMM_GROUP], mode[GEMM_GROUP]; const
 int launch_igemm_group(const IgemmArgs& base, const GemmProduct* p, int n, hipStream_t st);
 bool wave_gemm_takes(const IgemmArgs& a);
 int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st);
+// Normalised rows times weights (norm_gemm.hip).  Rows of K channels: compact float rows under a LayerNorm, or the active pixels of a bf16 map
+// [B, Ho*Wo, K] under a LayerNorm, under a GroupNorm with given statistics, or as they are.  N columns in sections of sect_n, section s with
+// weights w[s] [sect_n, K] to out[s] (only the last one transposed; geglu: one section, w[0] [2N, K]); a bias belongs to one section.
+enum { NG_ROWS_LN = 0, NG_MAP_LN = 1, NG_MAP_GN = 2, NG_MAP_RAW = 3 };
+struct NormGemmArgs {
+    const void* x; int src, K;
+    const bf16_t* gamma; const bf16_t* beta; float eps;
+    const float* gn_mean; const float* gn_rstd; int G;
+    const int* tile_idx; int tile, tiles_w, Ho, Wo, B, Ma;
+    const bf16_t* w[3]; const bf16_t* bias; int N, sect_n, geglu;
+    bf16_t* out[3]; int mode[3];
+};
+bool norm_gemm_takes(int src, int K, int B, int Ma, int H, int W);
+int launch_norm_gemm(const NormGemmArgs& a, hipStream_t st);
 size_t igemm_workspace_bytes();
 // Carves the scratch out of `workspace`; with a null or too
 // small workspace `out` is left empty and every launch runs unsplit.

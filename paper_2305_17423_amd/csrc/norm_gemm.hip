@@ -1,0 +1,492 @@
+// Normalisation and the product behind it as one launch:
+//
+//   out[row, n] = epilogue( sum_k N(x[row])[k] * W[n, k] ),   N = LayerNorm of the row, or GroupNorm with given statistics
+//
+// the query / key / value products, the cross-attention queries and the first feed-forward product (GEGLU gate) of a transformer
+// block, and its input product where no normalised copy of the map is kept.  Widths 320, 640 and 1280.
+//  - A workgroup of eight waves normalises its 16*RT rows once, straight from the float residual stream (or the map) into LDS as bf16:
+//    20 - 90 KB, all of K.  No launch writes normalised rows and no launch reads them back.
+//  - Every wave owns 16*CT columns at a time and streams their weights through an LDS ring of its own (LDS-direct loads, eight rows of 128 bytes
+//    each, ND stages of 64 channels): behind the barrier of the rows there is none.  The ring runs on over the end of a column
+//    tile, so the next tile's weights travel under the epilogue.
+//  - 16 x 16 x 32 products: a lane ends up with four consecutive columns of a row, or, with the operands exchanged, four consecutive
+//    rows of a column (the transposed values); results go from registers to memory, there is no sum over waves.
+// Bound by the LDS (operands of both sides, 2 RT + 4 CT KB a wave and stage) and the rate of LDS-direct loads for many rows, by its start, the rows and the
+// first weights (5 - 6 us) for few.  Against a LayerNorm launch and the gathered GEMM (us): GEGLU 1536 x 2560 x 320 18 -> 9, 8192 x 2560 x
+// 320 60 -> 24, 2048 x 5120 x 640 44 -> 27, 96 x 10240 x 1280 20 -> 16; queries, keys and values 1536 x 960 x 320 13.5 -> 7.8, 96 x 3840 x
+// 1280 13.5 -> 11.3; one product 1536 x 320 x 320 8 -> 5.7, 24 x 1280 x 1280 10 -> 8.1.  Weights straight into matrix registers (16 rows of 64 bytes a load, no
+// LDS) were up to 1.6 times slower from 100 KB of weights a workgroup on: 37 GB/s per CU instead of 60.
+#include <algorithm>
+#include "igemm.h"
+#include "profile.h"
+
+namespace fise {
+
+#define FISE_AS1 __attribute__((address_space(1)))
+typedef unsigned u32x2_n __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4_n __attribute__((ext_vector_type(4)));
+typedef float f32x4_n __attribute__((ext_vector_type(4)));
+
+constexpr int NG_WAVES = 8;
+struct NormGemmDev {
+    NormGemmArgs a;
+    int gx, per, units, t_tokens, trans4, pixels, touch, ks;
+    FastDiv d_gx, d_Ma, d_tt, d_tile, d_tiles_w, d_cpg;
+};
+
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t ng_buf(const void* p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float ng_lo(unsigned w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float ng_gelu(float x) { return x * (0.5f * (1.0f + erff(x * 0.70710678118654752f))); }
+__device__ __forceinline__ float ng_hi(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
+// Sum over aligned groups of 16, 32 or 64 lanes, in every lane of the group (data paths of the vector unit: a shuffle through the LDS costs
+// ~130 cycles a step, and a row's mean and variance are ten to twelve of them in a row).
+template <int CTRL> __device__ __forceinline__ float ng_dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int N> __device__ __forceinline__ float ng_sum(float x) {
+    x += ng_dpp<0xB1>(x);                                 // quad_perm 1 0 3 2
+    x += ng_dpp<0x4E>(x);                                 // quad_perm 2 3 0 1
+    x += ng_dpp<0x141>(x);                                // row_half_mirror
+    x += ng_dpp<0x140>(x);                                // row_mirror
+    if constexpr (N >= 32) {
+        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+    if constexpr (N >= 64) {
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+    return x;
+}
+#endif
+
+// LDS of a workgroup: rows of K bf16 whose 16-byte segments are XOR-swizzled with (row >> 1) & 7, at a pitch of 128 bytes modulo 256,
+// so that sixteen rows' operand reads meet no bank twice; then the rows' positions; then (GroupNorm) the scale / shift table.
+template <int KM> constexpr int ng_pitch() { return 640 * KM + (KM == 1 ? 0 : 128); }
+
+template <int KM, int RT, int CT, int ND, bool GEGLU>
+__global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormGemmDev g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int NW = NG_WAVES, K = 320 * KM, BM = 16 * RT, PITCH = ng_pitch<KM>(), LPR = 16 * KM, RPW = 64 / LPR, P = BM / (NW * RPW);
+    constexpr int OC = GEGLU ? 16 : 16 * CT, NK = 5 * KM;      // output columns of a unit, stages of 64 channels
+    static_assert(P >= 1 && BM % (NW * RPW) == 0 && (!GEGLU || CT == 2), "rows per wave");
+    const NormGemmArgs& a = g.a;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    int2* const rowpos = reinterpret_cast<int2*>(lds + BM * PITCH);
+    constexpr int WST = CT * 2048;                        // bytes of a stage of weights in LDS
+    unsigned char* const wring = lds + BM * PITCH + BM * 8;
+    float2* const table = reinterpret_cast<float2*>(wring + NW * ND * WST);
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // consecutive workgroups go round-robin to the 8 XCDs: each gets a contiguous run of (columns, rows), rows fastest
+    const int total = gridDim.x, chunk = total >> 3;
+    int w = blockIdx.x;
+    if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
+    const int cs = (int)fdiv((unsigned)w, g.d_gx), bx = w - cs * g.gx;
+    const int rows = a.B * a.Ma, m0 = bx * BM;
+    const int t0 = cs * g.per, t1 = min(g.units, t0 + g.per);
+
+    // ---- rows: LPR lanes a row, five pieces of four channels each, all rows of the wave requested together
+    const int l = lane % LPR;
+    f32x4_n v[P][5];
+    const int b_first = (int)fdiv((unsigned)m0, g.d_Ma);
+    unsigned rb[P], rm[P], rt[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const unsigned gm = (unsigned)min(m0 + p * (NW * RPW) + wave * RPW + lane / LPR, rows - 1);
+        rb[p] = fdiv(gm, g.d_Ma); rm[p] = gm - rb[p] * (unsigned)a.Ma; rt[p] = 0;
+    }
+    if (g.pixels)
+#pragma unroll
+        for (int p = 0; p < P; ++p) rt[p] = (unsigned)((const FISE_AS1 int*)a.tile_idx)[fdiv(rm[p], g.d_tt)];
+    if (a.src == NG_ROWS_LN)
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const FISE_AS1 f32x4_n* q = (const FISE_AS1 f32x4_n*)((const float*)a.x + (size_t)(rb[p] * (unsigned)a.Ma + rm[p]) * K) + l;
+#pragma unroll
+            for (int j = 0; j < 5; ++j) v[p][j] = q[j * LPR];
+        }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        if (g.pixels) {                                  // position on the map, from here on in place of the row
+            const unsigned rp = rm[p] - fdiv(rm[p], g.d_tt) * (unsigned)(a.tile * a.tile), py = fdiv(rp, g.d_tile), ty = fdiv(rt[p], g.d_tiles_w);
+            rm[p] = (ty * a.tile + py) * (unsigned)a.Wo + (rt[p] - ty * a.tiles_w) * a.tile + (rp - py * a.tile);
+        }
+        if (l == 0) rowpos[p * (NW * RPW) + wave * RPW + lane / LPR] = make_int2((int)rb[p], (int)rm[p]);
+    }
+    if (a.src != NG_ROWS_LN)
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const FISE_AS1 u32x2_n* q = (const FISE_AS1 u32x2_n*)((const bf16_t*)a.x + ((size_t)rb[p] * (a.Ho * a.Wo) + rm[p]) * K) + l;
+#pragma unroll
+            for (int j = 0; j < 5; ++j) { const u32x2_n u = q[j * LPR]; v[p][j] = f32x4_n{__uint_as_float(u.x), __uint_as_float(u.y), 0.f, 0.f}; }
+        }
+    u32x2_n gam[5], bet[5];
+    if (a.src == NG_ROWS_LN || a.src == NG_MAP_LN)
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            gam[j] = ((const FISE_AS1 u32x2_n*)a.gamma)[j * LPR + l];
+            bet[j] = ((const FISE_AS1 u32x2_n*)a.beta)[j * LPR + l];
+        }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // Where a workgroup has at most four units the waves also split K: 2^ks of them a unit, part `part` of its stages each.
+    const int part = wave & ((1 << g.ks) - 1), step = NW >> g.ks;
+    const int per_k = (NK + (1 << g.ks) - 1) >> g.ks, k0 = min(NK, part * per_k), kn = min(NK, k0 + per_k) - k0;
+    // ---- weights: unit t is 16*CT weight rows (GEGLU: 16 of the values, 16 of the gates N further down)
+    const bf16_t* wp = nullptr; unsigned wbytes = 0, wrow = 0;
+    auto set_unit = [&](int t) {                          // past the range: a descriptor of size zero, no traffic
+        const int col = t * OC, s = GEGLU ? 0 : (col >= a.sect_n) + (col >= 2 * a.sect_n);
+        wp = s == 0 ? a.w[0] : s == 1 ? a.w[1] : a.w[2];
+        wbytes = t < t1 ? (unsigned)((GEGLU ? 2 * a.N : a.sect_n) * (2 * K)) : 0u;
+        wrow = (unsigned)(col - s * a.sect_n) * (2u * K) + k0 * 128u;
+    };
+    // LDS ring: slot p of row r holds segment p ^ ((r >> 1) & 7); a load fills eight rows
+    const unsigned seg = (unsigned)((lane & 7) ^ ((lane >> 4) & 7)) * 16u;
+    const unsigned vd0 = (unsigned)(lane >> 3) * (2u * K) + seg, vd1 = (unsigned)(8 + (lane >> 3)) * (2u * K) + (seg ^ 64u);
+    unsigned char* const my_ring = wring + __builtin_amdgcn_readfirstlane(wave) * (ND * WST);
+    auto load = [&](int u) {                              // the unit's next stage into ring slot u
+        const __amdgpu_buffer_rsrc_t rs = ng_buf(wp, wbytes);
+#pragma unroll
+        for (int q = 0; q < 2 * CT; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(my_ring + u * WST + q * 1024), 16,
+                                                     q & 1 ? vd1 : vd0, wrow + (q < 2 ? 0u : GEGLU ? (unsigned)a.N * (2u * K) : 16u * (2u * K)), 0, 0);
+        wrow += 128u;
+    };
+    auto load_bias = [&](int t, u32x2_n (&o)[CT]) {
+        const __amdgpu_buffer_rsrc_t rs = ng_buf(a.bias, a.bias && t < t1 ? (unsigned)((GEGLU ? 2 : 1) * a.N) * 2u : 0u);
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+            o[c] = __builtin_bit_cast(u32x2_n, __builtin_amdgcn_raw_buffer_load_b64(rs, (unsigned)(t * OC + lq * 4) * 2u + (c == 0 ? 0u : GEGLU ? 2u * a.N : 32u), 0, 0));
+    };
+    // Row tiles that share a slice of the weights walk it in step, so each of its lines is cold for all of them at once: they first touch
+    // the slice, each a share of its lines (one dword a line, into the ring before it is filled).  512 x 10240 x 1280 38 -> 30.4 us, 96 rows
+    // 18.4 -> 16.0; slices under 200 KB or two row tiles lose 0.3 - 1 us.
+    if (g.touch) {
+        const int col0 = t0 * OC, s = GEGLU ? 0 : (col0 >= a.sect_n) + (col0 >= 2 * a.sect_n), n = GEGLU ? 32 * (t1 - t0) : min(t1 * OC, (s + 1) * a.sect_n) - col0;
+        const __amdgpu_buffer_rsrc_t rs = ng_buf(s == 0 ? a.w[0] : s == 1 ? a.w[1] : a.w[2], (unsigned)((GEGLU ? 2 * a.N : a.sect_n) * (2 * K)));
+        for (int q = (bx * NW + wave) * 64 + lane; q < n * NK; q += g.gx * NW * 64) {
+            const int r = q / NK, row = GEGLU ? (r & 1 ? a.N : 0) + col0 + (r >> 1) : col0 - s * a.sect_n + r;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)my_ring, 4, (unsigned)row * (2u * K) + (unsigned)(q - r * NK) * 128u, 0, 0, 0);
+        }
+    }
+    int t = t0 + (wave >> g.ks);
+    u32x2_n bias[CT], bias_next[CT];
+    load_bias(t, bias_next);
+    set_unit(t);
+#pragma unroll
+    for (int u = 0; u < ND; ++u) {
+        if (u == kn) set_unit(t + step);
+        load(u);
+    }
+    int slot = 0, pos = ND <= kn ? ND : ND - kn;                               // next stage to read, stages of the unit that have been requested
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- normalise into LDS
+    if (a.src == NG_MAP_GN) {                             // (scale, shift) of the tile's batch elements (two at most: Ma >= BM)
+        for (int e = tid; e < 2 * K; e += 64 * NW) {
+            const int bb = min(a.B - 1, b_first + (e >= K)), c = e >= K ? e - K : e, gi = bb * a.G + (int)fdiv((unsigned)c, g.d_cpg);
+            const float sc = a.gn_rstd[gi] * bf2f(a.gamma[c]);
+            table[e] = make_float2(sc, bf2f(a.beta[c]) - a.gn_mean[gi] * sc);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int r = p * (NW * RPW) + wave * RPW + lane / LPR;
+        f32x4_n x[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            x[j] = v[p][j];
+            if (a.src != NG_ROWS_LN) {
+                const unsigned w0 = __float_as_uint(v[p][j].x), w1 = __float_as_uint(v[p][j].y);
+                x[j] = f32x4_n{ng_lo(w0), ng_hi(w0), ng_lo(w1), ng_hi(w1)};
+            }
+        }
+        if (a.src == NG_MAP_GN) {
+            const float2* ss = table + ((int)fdiv((unsigned)min(m0 + r, rows - 1), g.d_Ma) - b_first) * K;
+#pragma unroll
+            for (int j = 0; j < 5; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { const float2 s = ss[(j * LPR + l) * 4 + q]; x[j][q] = x[j][q] * s.x + s.y; }
+        } else if (a.src != NG_MAP_RAW) {
+            float s = 0.f;
+#pragma unroll
+            for (int j = 0; j < 5; ++j) s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
+            const float mu = ng_sum<LPR>(s) / K;
+            float q = 0.f;
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {
+                const f32x4_n d = x[j] - mu;
+                q += (d.x * d.x + d.y * d.y) + (d.z * d.z + d.w * d.w);
+            }
+            const float rs = rsqrtf(ng_sum<LPR>(q) / K + a.eps);
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {
+                x[j].x = (x[j].x - mu) * rs * ng_lo(gam[j].x) + ng_lo(bet[j].x);
+                x[j].y = (x[j].y - mu) * rs * ng_hi(gam[j].x) + ng_hi(bet[j].x);
+                x[j].z = (x[j].z - mu) * rs * ng_lo(gam[j].y) + ng_lo(bet[j].y);
+                x[j].w = (x[j].w - mu) * rs * ng_hi(gam[j].y) + ng_hi(bet[j].y);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            const int c4 = j * LPR + l, seg = c4 >> 1;   // piece of four channels, 16-byte segment
+            *reinterpret_cast<u32x2_n*>(lds + r * PITCH + (seg >> 3) * 128 + ((seg & 7) ^ ((r >> 1) & 7)) * 16 + (c4 & 1) * 8) =
+                u32x2_n{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // not the loads of the weights
+
+    // ---- column tiles
+    const unsigned rd0 = (unsigned)(l16 * PITCH + ((lq ^ ((l16 >> 1) & 7)) * 16)), rd1 = rd0 ^ 64u, rw = (unsigned)(l16 * 128) + ((lq ^ ((l16 >> 1) & 7)) * 16);     // operand of channels 0 - 31 / 32 - 63 of a stage
+    auto column_tile = [&](auto tokens) {
+        constexpr bool TOKENS = decltype(tokens)::value;
+        f32x4_n acc[RT][CT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[i][c] = f32x4_n{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < CT; ++c) bias[c] = bias_next[c];
+        load_bias(t + step, bias_next);
+        const int col = t * OC, sect = GEGLU ? 0 : (col >= a.sect_n) + (col >= 2 * a.sect_n);
+        const int mode = GEGLU ? OUT_COMPACT : sect == 0 ? a.mode[0] : sect == 1 ? a.mode[1] : a.mode[2];
+        auto run = [&]() {
+            bf16x8_t fa[2][2][RT], fb[2][2][CT];
+            unsigned r0 = rd0 + k0 * 128u, r1 = rd1 + k0 * 128u;
+            auto read = [&](bf16x8_t (&x)[2][RT], bf16x8_t (&w)[2][CT]) {       // the oldest stage, which has landed
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ND - 1) * 2 * CT) : "memory");
+                const unsigned char* const stage = my_ring + slot * WST;
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) w[ks][c] = *reinterpret_cast<const bf16x8_t*>(stage + (ks ? rw ^ 64u : rw) + c * 2048);
+#pragma unroll
+                    for (int i = 0; i < RT; ++i) x[ks][i] = *reinterpret_cast<const bf16x8_t*>(lds + (ks ? r1 : r0) + i * (16 * PITCH));
+                }
+                r0 += 128u; r1 += 128u;
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            // the stage's operands are in registers: its place is refilled, the next stage's are requested, then the products
+            auto stage = [&](const bf16x8_t (&x)[2][RT], const bf16x8_t (&w)[2][CT], bf16x8_t (&xn)[2][RT], bf16x8_t (&wn)[2][CT], bool more) {
+                __builtin_amdgcn_s_waitcnt(0xc07f);       // lgkmcnt(0), in a form that the compiler counts too
+                __builtin_amdgcn_sched_barrier(0);
+                if (pos == kn) { set_unit(t + step); pos = 0; }
+                load(slot); ++pos;
+                slot = slot == ND - 1 ? 0 : slot + 1;
+                __builtin_amdgcn_sched_barrier(0);
+                if (more) read(xn, wn);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int c = 0; c < CT; ++c)
+#pragma unroll
+                        for (int i = 0; i < RT; ++i)
+                            acc[i][c] = TOKENS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[ks][i], w[ks][c], acc[i][c], 0, 0, 0)
+                                               : __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][c], x[ks][i], acc[i][c], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if (kn > 0) read(fa[0], fb[0]);
+#pragma unroll 1
+            for (int k = 0; k < kn; k += 2) {
+                stage(fa[0], fb[0], fa[1], fb[1], k + 1 < kn);
+                if (k + 1 < kn) stage(fa[1], fb[1], fa[0], fb[0], k + 2 < kn);
+            }
+        };
+        // positions and addresses of the rows are worked out per column tile, not kept in registers over the products
+        int e16 = l16, eq = lq;
+        auto place = [&]() { asm volatile("" : "+v"(e16), "+v"(eq)::"memory"); };
+        bf16_t* const out = sect == 0 ? a.out[0] : sect == 1 ? a.out[1] : a.out[2];
+        const int scol = col - sect * a.sect_n;
+        run();
+        if (g.ks) {                                       // the parts' sums meet in the place of the rows; the first part's wave goes on
+            f32x4_n* const sums = reinterpret_cast<f32x4_n*>(lds);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (part)
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) sums[(wave * (RT * CT) + i * CT + c) * 64 + lane] = acc[i][c];
+            __syncthreads();
+            if (part) { t = t1; return; }
+            for (int o = 1; o < 1 << g.ks; ++o)
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) acc[i][c] += sums[((wave + o) * (RT * CT) + i * CT + c) * 64 + lane];
+        }
+        place();
+        if constexpr (GEGLU) {
+            const float bv[4] = {ng_lo(bias[0].x), ng_hi(bias[0].x), ng_lo(bias[0].y), ng_hi(bias[0].y)};
+            const float bg[4] = {ng_lo(bias[1].x), ng_hi(bias[1].x), ng_lo(bias[1].y), ng_hi(bias[1].y)};
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                const int gm = m0 + i * 16 + e16;
+                float y[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) y[q] = (acc[i][0][q] + bv[q]) * ng_gelu(acc[i][CT - 1][q] + bg[q]);
+                if (gm < rows) *(FISE_AS1 u32x2_n*)(out + (size_t)gm * a.N + col + eq * 4) = u32x2_n{f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
+            }
+        } else if constexpr (TOKENS) {
+            const size_t HW = (size_t)a.Ho * a.Wo;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                const int r = i * 16 + eq * 4;
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    const unsigned n = (unsigned)(scol + c * 16 + e16);
+                    if (g.trans4) {                       // four tokens in a row
+                        const int2 pos = rowpos[r];
+                        if (m0 + r < rows)
+                            *(FISE_AS1 u32x2_n*)(out + ((size_t)pos.x * a.sect_n + n) * HW + pos.y) = u32x2_n{f2bf2(acc[i][c][0], acc[i][c][1]), f2bf2(acc[i][c][2], acc[i][c][3])};
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int2 pos = rowpos[r + q];
+                            if (m0 + r + q < rows) *(FISE_AS1 bf16_t*)(out + ((size_t)pos.x * a.sect_n + n) * HW + pos.y) = f2bf(acc[i][c][q]);
+                        }
+                    }
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                const int r = i * 16 + e16;
+                const int2 pos = rowpos[r];
+                const size_t row = mode == OUT_MAP ? (size_t)pos.x * (a.Ho * a.Wo) + pos.y : (size_t)(m0 + r);
+                if (m0 + r >= rows) continue;
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    const f32x4_n y = acc[i][c] + f32x4_n{ng_lo(bias[c].x), ng_hi(bias[c].x), ng_lo(bias[c].y), ng_hi(bias[c].y)};
+                    const size_t off = row * a.sect_n + scol + c * 16 + eq * 4;
+                    if (mode == OUT_COMPACT_F32) *(FISE_AS1 f32x4_n*)(reinterpret_cast<float*>(out) + off) = y;
+                    else *(FISE_AS1 u32x2_n*)(out + off) = u32x2_n{f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
+                }
+            }
+        }
+        t += step;
+    };
+    // the transposed section is the last one: two loops instead of a choice in one, which costs copies of the ring
+    const bool idle = t >= t1;
+    while (t < min(t1, g.t_tokens)) column_tile(std::false_type{});
+    if constexpr (!GEGLU)
+        while (t < t1) column_tile(std::true_type{});
+    if (g.ks && idle) {                                   // every wave meets the two barriers of a split unit
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        __syncthreads();
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the loads past the range still write to this workgroup's LDS
+#endif
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+template <int KM, int RT, int CT, int ND> constexpr int ng_lds(bool table) {
+    return 16 * RT * (ng_pitch<KM>() + 8) + NG_WAVES * ND * CT * 2048 + (table ? 2 * 320 * KM * 8 : 0);
+}
+constexpr int NG_LDS_MAX = 160 * 1024;
+
+// Logarithm of the waves that share a unit: all there are, where their sums find room in the place of the rows (320 channels of 32 columns: not).  1280 channels,
+// 24 rows: one product 8.1 -> 7.0 us, queries, keys and values 10.1 -> 8.5; 640 channels 384 rows 7.5 -> 7.2.
+static int waves_per_unit(int KM, int CT, int per) {
+    int ks = 0;
+    if (CT * 512 <= 640 * KM + (KM == 1 ? 0 : 128))
+        while ((per << (ks + 1)) <= NG_WAVES && (2 << ks) <= 5 * KM) ++ks;
+    return ks;
+}
+
+template <int KM, int RT, int CT, int ND, bool GEGLU>
+static int launch_cfg(NormGemmDev g, int per, hipStream_t st) {
+    const NormGemmArgs& a = g.a;
+    constexpr int lds_max = ng_lds<KM, RT, CT, ND>(true) <= NG_LDS_MAX ? ng_lds<KM, RT, CT, ND>(true) : ng_lds<KM, RT, CT, ND>(false);
+    static_assert(lds_max <= NG_LDS_MAX, "LDS of a CU");
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&norm_gemm_kernel<KM, RT, CT, ND, GEGLU>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
+    if (attr != hipSuccess) return fail(FISE_ERR_HIP, "norm gemm: cannot raise the dynamic LDS limit");
+    const int rows = a.B * a.Ma;
+    g.gx = ceil_div(rows, 16 * RT); g.units = a.N / (GEGLU ? 16 : 16 * CT); g.per = per;
+    g.t_tokens = a.mode[a.N / a.sect_n - 1] == OUT_TOKENS_T ? (a.N - a.sect_n) / (16 * CT) : g.units;
+    g.touch = g.gx >= 3 && per * CT * KM * 10 >= 200;      // kernel comment
+    g.ks = waves_per_unit(KM, CT, per);
+    g.d_gx = fast_div(g.gx);
+    {
+        const double K = 320.0 * KM, ncols = GEGLU ? 2.0 * a.N : a.N;
+        ProfileScope prof(GEGLU ? PROF_IGEMM_GEGLU : PROF_ROWS_GEMM, 2.0 * rows * ncols * K,
+                          2.0 * (ncols * K + (double)rows * a.N) + (a.src == NG_ROWS_LN ? 4.0 : 2.0) * rows * K, st);
+        hipLaunchKernelGGL((norm_gemm_kernel<KM, RT, CT, ND, GEGLU>), dim3((unsigned)(g.gx * ceil_div(g.units, per))), dim3(64 * NG_WAVES),
+                           (ng_lds<KM, RT, CT, ND>(a.src == NG_MAP_GN)), st, g);
+    }
+    FISE_CHECK_LAUNCH("norm gemm");
+    return FISE_OK;
+}
+
+// Rows and columns of a workgroup's tile per width, with the launch function of that instantiation.
+struct NormTile { int K, geglu, rt, ct, nd; int (*launch)(NormGemmDev, int, hipStream_t); };
+static const NormTile kTiles[] = {
+    {320, 1, 4, 2, 2, launch_cfg<1, 4, 2, 2, true>},   {320, 1, 2, 2, 3, launch_cfg<1, 2, 2, 3, true>},
+    {640, 1, 4, 2, 2, launch_cfg<2, 4, 2, 2, true>},   {640, 1, 2, 2, 3, launch_cfg<2, 2, 2, 3, true>},
+    {1280, 1, 2, 2, 2, launch_cfg<4, 2, 2, 2, true>},  {1280, 1, 1, 2, 3, launch_cfg<4, 1, 2, 3, true>},
+    {320, 0, 4, 2, 3, launch_cfg<1, 4, 2, 3, false>},  {320, 0, 2, 1, 4, launch_cfg<1, 2, 1, 4, false>},
+    {640, 0, 2, 2, 3, launch_cfg<2, 2, 2, 3, false>},  {640, 0, 2, 1, 4, launch_cfg<2, 2, 1, 4, false>},
+    {1280, 0, 2, 2, 2, launch_cfg<4, 2, 2, 2, false>}, {1280, 0, 2, 1, 4, launch_cfg<4, 2, 1, 4, false>},
+    {1280, 0, 1, 1, 4, launch_cfg<4, 1, 1, 4, false>}};
+
+// A GroupNorm's table holds two batch elements, and the smallest row tile is 32 (16 at 1280 channels).
+static bool table_fits(const NormGemmArgs& a, int rt) { return a.src != NG_MAP_GN || a.B == 1 || a.Ma >= 16 * rt; }
+
+// The row tile and column units per workgroup of a launch: the cheapest under times (us) fitted to 800 combinations of tile and split over the
+// products of 320 / 640 / 1280 channels with 16 to 8192 rows and cold weights, where the choice is 0.6 % from the best on average, at worst
+// 10 %.  One workgroup runs per CU; a round of 256 pays for its rows (16 rows of 320 channels 0.66), for the LDS traffic of its units
+// (2 RT + 4 CT KB a wave and stage of 64 channels) and for the stages a wave goes through; what all workgroups read of the weights comes on top.
+struct NormChoice { const NormTile* tile; int per; };
+static NormChoice choose(const NormGemmArgs& a) {
+    static const short kPer[] = {1, 2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 40, 64, 80};
+    const int rows = a.B * a.Ma, NK = a.K / 64, KM = a.K / 320;
+    NormChoice c{nullptr, 1}; double best = 1e30;
+    for (const NormTile& t : kTiles) {
+        if (t.K != a.K || t.geglu != (a.geglu != 0) || !table_fits(a, t.rt)) continue;
+        if (a.src == NG_MAP_GN && 16 * t.rt * (640 * KM + 136) + NG_WAVES * t.nd * t.ct * 2048 + 2 * a.K * 8 > NG_LDS_MAX) continue;
+        const int units = a.N / (a.geglu ? 16 : 16 * t.ct), gx = ceil_div(rows, 16 * t.rt);
+        for (const int per : kPer) {
+            if (per > units) break;
+            const long long wgs = (long long)gx * ceil_div(units, per);
+            const int ks = waves_per_unit(KM, t.ct, per), stages = ks ? (NK + (1 << ks) - 1) >> ks : ceil_div(per, NG_WAVES) * NK;
+            const double us = 1.8 + (double)((wgs + 255) / 256) * (2.0 + 0.66 * t.rt * KM + 0.0031 * per * NK * (2 * t.rt + 4 * t.ct) + 0.026 * stages + (ks ? 0.26 : 0.0)) +
+                              0.024e-3 * wgs * per * NK * t.ct + 0.12 * NK * (t.ct - 1) / (1 << ks);
+            if (us < best) { best = us; c = {&t, per}; }
+        }
+    }
+    return c;
+}
+
+bool norm_gemm_takes(int src, int K, int B, int Ma, int H, int W) {
+    if ((K != 320 && K != 640 && K != 1280) || Ma < 1) return false;
+    if (src == NG_MAP_GN && B > 1 && Ma < (K == 1280 ? 16 : 32)) return false;
+    return (long long)B * Ma < 1 << 24 && (long long)B * H * W < 1 << 24;       // 32-bit products of row and pixel numbers
+}
+
+int launch_norm_gemm(const NormGemmArgs& a, hipStream_t st) {
+    NormGemmDev g{};
+    g.a = a;
+    const int nsect = a.N / a.sect_n;
+    bool map = a.src != NG_ROWS_LN, tokens = false;
+    for (int s = 0; s < nsect; ++s) { map |= a.mode[s] == OUT_MAP; tokens |= a.mode[s] == OUT_TOKENS_T; if (a.mode[s] == OUT_TOKENS_T && s + 1 < nsect) return fail(FISE_ERR_SHAPE, "norm gemm: a transposed section is the last one"); }
+    if (!norm_gemm_takes(a.src, a.K, a.B, a.Ma, a.Ho, a.Wo) || a.sect_n % 32 || nsect * a.sect_n != a.N || nsect > 3 || (a.geglu && nsect != 1) || (a.bias && nsect != 1))
+        return fail(FISE_ERR_SHAPE, "norm gemm: %d channels, %d columns in sections of %d", a.K, a.N, a.sect_n);
+    g.pixels = a.tile_idx && (map || tokens);
+    g.trans4 = a.Ma % 4 == 0 && (a.tile_idx ? a.tile % 4 == 0 && a.Wo % 4 == 0 : a.Ho * a.Wo % 4 == 0);
+    g.d_Ma = fast_div(a.Ma); g.d_tt = fast_div(a.tile * a.tile); g.d_tile = fast_div(a.tile); g.d_tiles_w = fast_div(a.tiles_w);
+    g.d_cpg = fast_div(a.src == NG_MAP_GN ? a.K / a.G : 1);
+    const NormChoice c = choose(a);
+    if (!c.tile) return fail(FISE_ERR_SHAPE, "norm gemm: no tile");
+    return c.tile->launch(g, c.per, st);
+}
+
+}  // namespace fise
