@@ -11,6 +11,7 @@
 // one is being multiplied; the LDS hand-over uses a barrier that does not wait for
 // those loads.
 #include <algorithm>
+#include <type_traits>
 #include "attention_keys.h"
 #include "igemm.h"
 #include "profile.h"
@@ -278,6 +279,217 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
     }
 }
 
+// Few queries: a workgroup of eight waves takes 32 queries of one (batch, head), and the waves deal the keys out among themselves, 32 at
+// a time, so 256 keys are one trip to memory for all of them and no second launch merges key splits.  Nothing is shared between
+// the waves before the end: each brings its keys into LDS of its own (LDS-direct loads, rows of 2 d contiguous bytes) and reads its values straight
+// into matrix registers (16 rows of 64 bytes a load); the next keys are requested once the scores of these stand, their values once the
+// products do.  The waves' partial sums meet in LDS, in wave order.
+// 16 x 16 x 32 products; LDS row r of a wave holds key 8 (r / 4 % 4) + 4 (r / 16) + r % 4, so a lane's eight scores of a query are eight
+// consecutive keys: the operand of the second product as they stand.
+// Bound by the vector memory path, ~4 cycles per 128-byte line that a load instruction touches, and the start and the merge: see attention_few.
+constexpr int AF_WAVES = 8;
+
+template <int KD> struct FewTile {                      // KD: 16-wide steps over the head dim
+    static constexpr int KS = (KD + 1) / 2, PS = 4 * KS, ITEMS = 2 * KD, SLICE = ITEMS < 10 ? ITEMS : 10;      // 32-wide steps, 16-byte segments of an LDS row; pieces of the output, summed at a time
+    static constexpr int KBYTES = 32 * PS * 16;         // keys of a wave
+    static constexpr int LDS = AF_WAVES * (KBYTES > SLICE * 1024 ? KBYTES : SLICE * 1024);
+    // Segment p of row r holds segment p ^ swizzle(r) of its key: sixteen lanes that the LDS serves at once (rows 0-3, 12-15 of one segment, 4-11
+    // of the next) meet in no bank.
+    static __device__ __forceinline__ int swizzle(int r) {
+        if (PS == 8) return (r >> 1) & 7;
+        if (PS == 16) return r & 15;
+        return ((r >> 2 ^ r >> 3) & 1) << 1 | (r >> 3 & 1);
+    }
+};
+
+template <int KD, bool EXACT>
+__global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K,
+                                                                         const bf16_t* __restrict__ Vt, int B, int M, int n_keys, int n_stride,
+                                                                         int C, int d_arg, float scale_log2e, int nqt, int heads,
+                                                                         FastDiv d_nqt, FastDiv d_heads, bf16_t* __restrict__ out) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    using T = FewTile<KD>;
+    constexpr int KS = T::KS, PS = T::PS, NK = PS / 2;  // LDS-direct loads of 32 keys
+    constexpr unsigned OOB = 0x80000000u;
+    typedef unsigned u32x4_a __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) unsigned char keys[T::LDS];      // later the partial sums [waves][SLICE][64 lanes]
+    __shared__ float2 ml[AF_WAVES][32];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // as above: the query tiles of a (batch, head) one behind the other, on one XCD
+    int qt, h, b;
+    {
+        const int total = nqt * heads * B, chunk = total >> 3;
+        int w = blockIdx.x;
+        if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
+        const int t = (int)fdiv(w, d_nqt);
+        b = (int)fdiv(t, d_heads);
+        qt = w - t * nqt; h = t - b * heads;
+    }
+    const int d = EXACT ? KD * 16 : d_arg;
+    const int nsb = (n_keys + 31) / 32;
+    // queries and keys past the last one and channels past the head lie outside these: zeros
+    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(q + (size_t)b * M * C + h * d), 0, (M * C - h * d) * 2, 0x00020000);
+    bf16_t* const kp = const_cast<bf16_t*>(K + (size_t)b * n_keys * C + h * d);
+    bf16_t* const vp = const_cast<bf16_t*>(Vt + ((size_t)b * C + h * d) * n_stride);
+    unsigned char* const my_keys = keys + wave * T::KBYTES;
+    unsigned ok[NK];
+#pragma unroll
+    for (int j = 0; j < NK; ++j) {
+        const int slot = j * 64 + lane, r = slot / PS, seg = (slot % PS) ^ T::swizzle(r);
+        const int key = 8 * ((r >> 2) & 3) + 4 * (r >> 4) + (r & 3);
+        ok[j] = seg * 8 < d ? (unsigned)(key * C + seg * 8) * 2u : OOB;
+    }
+    // Requests for keys behind the last ones go out through descriptors of size zero, not behind branches: the compiler counts the loads
+    // in flight by the path that has fewest, and each wait for values would wait for the next keys too.
+    auto fetch_k = [&](int sb) {
+        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(kp, 0, sb < nsb ? (n_keys * C - h * d) * 2 : 0, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < NK; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (__attribute__((address_space(3))) void*)(my_keys + j * 1024), 16, ok[j], (unsigned)(sb * 64) * (unsigned)C, 0, 0);
+    };
+    u32x4_a vf[KD];
+    const unsigned ov = (unsigned)(l16 * n_stride + lq * 8) * 2u;
+    auto fetch_v = [&](int sb) {
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(vp, 0, sb < nsb ? d * n_stride * 2 : 0, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < KD; ++i)
+            vf[i] = __builtin_bit_cast(u32x4_a, __builtin_amdgcn_raw_buffer_load_b128(rv, ov + (unsigned)(sb * 64), (unsigned)(i * 32) * (unsigned)n_stride, 0));
+    };
+    bf16x8_t qf[2][KS];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int c = ks * 32 + lq * 8;
+            qf[t][ks] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rq, c < d ? (unsigned)((qt * 32 + t * 16 + l16) * C + c) * 2u : OOB, 0, 0));
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_k(wave);
+    fetch_v(wave);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" ::"v"(qf[t][ks]));      // arrived before the loop, as above
+
+    f32x4_t o[2][KD];
+    float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < KD; ++i) o[t][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const unsigned rd = (unsigned)((l16 * PS + (lq ^ (T::swizzle(l16) & 3))) * 16), rx = (unsigned)(T::swizzle(l16) >> 2);      // place of segment 4 ks + lq: 64 (ks ^ rx) behind rd
+#pragma unroll 1
+    for (int sb = wave; sb < nsb; sb += AF_WAVES) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KD) : "memory");      // the keys have landed (the values were requested after them)
+        f32x4_t s[2][2];
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) s[t][kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                // rows 16 apart have the same swizzle
+                const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(my_keys + rd + ((unsigned)ks ^ rx) * 64 + kt * (16 * PS * 16));
+#pragma unroll
+                for (int t = 0; t < 2; ++t) s[t][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[t][ks], s[t][kt], 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0): the keys are in registers
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_k(sb + AF_WAVES);
+        __builtin_amdgcn_sched_barrier(0);
+        const int left = n_keys - sb * 32 - lq * 8;      // keys that exist from this lane's first one on
+        const bool partial = sb * 32 + 32 > n_keys;      // uniform
+        if (partial)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (kt * 4 + e >= left) s[t][kt][e] = -INFINITY;
+        bf16x8_t pf[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            float mraw = fmaxf(fmaxf(fmaxf(s[t][0][0], s[t][0][1]), fmaxf(s[t][0][2], s[t][0][3])), fmaxf(fmaxf(s[t][1][0], s[t][1][1]), fmaxf(s[t][1][2], s[t][1][3])));
+            mraw = fmaxf(mraw, __shfl_xor(mraw, 16));
+            mraw = fmaxf(mraw, __shfl_xor(mraw, 32));
+            const float mx = fmaxf(m_run[t], mraw * scale_log2e), alpha = __builtin_amdgcn_exp2f(m_run[t] - mx);
+            float psum = 0.f;
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(s[t][kt][e], scale_log2e, -mx));
+                    s[t][kt][e] = p;
+                    psum += p;
+                }
+            psum += __shfl_xor(psum, 16);
+            psum += __shfl_xor(psum, 32);
+            l_run[t] = l_run[t] * alpha + psum;
+            m_run[t] = mx;
+#pragma unroll
+            for (int i = 0; i < KD; ++i) o[t][i] *= alpha;
+            uint4 pw = make_uint4(f2bf2(s[t][0][0], s[t][0][1]), f2bf2(s[t][0][2], s[t][0][3]), f2bf2(s[t][1][0], s[t][1][1]), f2bf2(s[t][1][2], s[t][1][3]));
+            pf[t] = *reinterpret_cast<bf16x8_t*>(&pw);
+        }
+        if (partial) {                                   // values of absent keys may be anything
+            auto keep = [&](unsigned w, int t) { return left > t + 1 ? w : left > t ? w & 0xffffu : 0u; };
+#pragma unroll
+            for (int i = 0; i < KD; ++i) vf[i] = u32x4_a{keep(vf[i].x, 0), keep(vf[i].y, 2), keep(vf[i].z, 4), keep(vf[i].w, 6)};
+        }
+#pragma unroll
+        for (int i = 0; i < KD; ++i)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) o[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vf[i]), pf[t], o[t][i], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_v(sb + AF_WAVES);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // ---- sums of the waves that had keys: weights 2^(m_w - max m), then O in wave order
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // requests behind the last keys still write zeros into the wave's LDS
+    if (lq == 0)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) ml[wave][t * 16 + l16] = make_float2(m_run[t], l_run[t]);
+    __syncthreads();
+    f32x4_t* const part = reinterpret_cast<f32x4_t*>(keys);
+    auto finish = [&](auto waves) {                      // of the first four waves or all
+        constexpr int W = decltype(waves)::value;
+        float own[2], inv[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            float2 v[W];
+            float mx = -INFINITY, den = 0.f;
+#pragma unroll
+            for (int w = 0; w < W; ++w) { v[w] = ml[w][t * 16 + l16]; mx = fmaxf(mx, v[w].x); }
+#pragma unroll
+            for (int w = 0; w < W; ++w) den += __builtin_amdgcn_exp2f(v[w].x - mx) * v[w].y;      // a wave without keys: weight 0
+            own[t] = __builtin_amdgcn_exp2f(m_run[t] - mx); inv[t] = 1.0f / den;
+        }
+#pragma unroll
+        for (int g0 = 0; g0 < T::ITEMS; g0 += T::SLICE) {       // piece g: 16 channels g / 2 of query tile g % 2
+            if (g0) __syncthreads();
+            if (wave < W)
+#pragma unroll
+                for (int g = g0; g < g0 + T::SLICE && g < T::ITEMS; ++g) part[(wave * T::SLICE + g - g0) * 64 + lane] = o[g & 1][g >> 1] * own[g & 1];
+            __syncthreads();
+            for (int g = g0 + wave; g < g0 + T::SLICE && g < T::ITEMS; g += AF_WAVES) {
+                f32x4_t v = part[(g - g0) * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < W; ++w) v += part[(w * T::SLICE + g - g0) * 64 + lane];
+                const int m = qt * 32 + (g & 1) * 16 + l16, c = (g >> 1) * 16 + lq * 4;
+                const float iv = g & 1 ? inv[1] : inv[0];
+                if (m < M && c < d) *reinterpret_cast<uint2*>(out + ((size_t)b * M + m) * C + h * d + c) = make_uint2(f2bf2(v[0] * iv, v[1] * iv), f2bf2(v[2] * iv, v[3] * iv));
+            }
+        }
+    };
+    if (nsb <= 4) finish(std::integral_constant<int, 4>{}); else finish(std::integral_constant<int, AF_WAVES>{});
+#endif
+}
+
 // out[b,m,c] = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max_s m_s), splits visited in index order.
 // One thread per four channels (d is a multiple of 8: the four share a head, hence the weights).
 __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
@@ -311,6 +523,13 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 template <int KD, int DB, bool EXACT>
 static void launch_at(const void* q, const void* K, const void* Vt, int B, int M, int n_keys, int n_stride, int C, int heads,
                       int d, float scale, int splits, void* out, float* part_o, float* part_ml, hipStream_t st) {
+    if (splits == 0) {
+        const int nqt = ceil_div(M, 32);
+        hipLaunchKernelGGL((attention_few_kernel<KD, EXACT>), dim3((unsigned)(nqt * heads * B)), dim3(64 * AF_WAVES), 0, st, (const bf16_t*)q,
+                           (const bf16_t*)K, (const bf16_t*)Vt, B, M, n_keys, n_stride, C, d, scale * 1.4426950408889634f, nqt, heads, fast_div(nqt),
+                           fast_div(heads), (bf16_t*)out);
+        return;
+    }
     const int nqt = ceil_div(M, AT_BQ);
     dim3 grid((unsigned)(nqt * heads * B * splits));
     hipLaunchKernelGGL((attention_kernel<KD, DB, EXACT>), grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)K,
@@ -334,6 +553,25 @@ static int attention_splits(int B, int M, int n_keys, int C, int heads) {
     return std::max(1, std::min(s, 32));
 }
 
+// Which kernel: the one whose time is smaller by lines fitted to both over 175 launches (1 to 4096 queries, 16 to 4096 keys, heads of 8 to
+// 160, cold keys; the choice is 0.1 % from the better one on average, 5 % at worst).  Us, d = head dim:
+//  - few queries: 2.8 + 0.019 d, 0.32 + 0.02 d per 256 keys and round of 256 workgroups, 0.037 d per further round;
+//  - the other: 2.2 + 0.007 d, 0.57 + 0.01 d per key block of a workgroup (more where more than two share a CU), 0.47 + 0.004 d for a partial block,
+//    and for split keys 3.9 and 3.3 per million parked elements.
+// 2 x 48 queries, 256 keys of 8 x 160 channels 12.0 -> 10.4 us; 2 x 192 x 77 keys of 8 x 80 6.6 -> 5.4; 2 x 384 x 1024 21.5 -> 12.7; 2 x
+// 192 x 2304 of 8 x 40 17.9 -> 14.0; 2 x 768 x 4096 of 8 x 40 stays (34 against 36).
+static bool attention_few(int B, int M, int n_keys, int n_stride, int C, int heads, int splits) {
+    const double lim = 1u << 30;                         // 32-bit offsets into a batch element
+    if ((double)n_keys * C >= lim || (double)C * n_stride >= lim || (double)M * C >= lim) return false;
+    const int d = C / heads, few_wgs = ceil_div(M, 32) * heads * B, rounds = ceil_div(few_wgs, 256);
+    const double few = 2.8 + 0.019 * d + rounds * (ceil_div(n_keys, 32) / 8.0) * (0.32 + 0.02 * d) + (rounds - 1) * 0.037 * d;
+    const double wgs = (double)ceil_div(M, AT_BQ) * heads * B * splits;
+    const int per = ceil_div(ceil_div(n_keys, AT_BKV), splits);
+    const double many = 2.2 + 0.0068 * d + (n_keys % AT_BKV ? 0.47 + 0.0036 * d : 0.0) + per * std::max(1.0, wgs / 512.0) * (0.57 + 0.0095 * d) +
+                        (splits > 1 ? 3.9 + 3.3e-6 * splits * B * M * C : 0.0);
+    return few < (splits > 1 ? 0.93 : 1.0) * many;       // with warm keys the key splits gain more: 2 x 80 queries, 1024 keys of 8 x 80 11.0 against 12.2
+}
+
 size_t attention_workspace_bytes(int B, int M, int n_keys, int C, int heads) {
     const int s = attention_splits(B, M, n_keys, C, heads);
     if (s <= 1) return 0;
@@ -347,6 +585,7 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
     const int kd = ceil_div(d, 16);
     int splits = attention_splits(B, M, n_keys, C, heads);
     if (splits > 1 && (!ws || ws_bytes < attention_workspace_bytes(B, M, n_keys, C, heads))) splits = 1;
+    if (attention_few(B, M, n_keys, n_stride, C, heads, splits)) splits = 0;       // one launch whatever the key range
     float* part_o = (float*)ws;
     float* part_ml = splits > 1 ? (float*)((char*)ws + align256((size_t)splits * B * M * C * sizeof(float))) : nullptr;
     {
