@@ -24,6 +24,7 @@
 #include <algorithm>
 #include <type_traits>
 #include "igemm.h"
+#include "patch.h"
 #include "profile.h"
 
 namespace fise {
@@ -39,18 +40,6 @@ enum { A_ROWS = 0, A_MAP = 1 };         // compact rows / pixels of maps (taps, 
 // channels and read under all nine taps; the weights run through a ring of their own, a kernel row at a time.  Bound by the LDS-direct
 // loads (36 KB of weights and 8 - 32 KB of patches per chunk and column tile of 32; 0.42 us at the 125 GB/s of a CU, 0.6 - 0.7 measured)
 // and, from 20 chunks of 1280 wide layers on, by their cold weights.
-// Geometry of the patches behind the BM rows of a workgroup: strips of H x T pixels with their one-pixel ring.
-template <int BM, int T> struct Patch {
-    static constexpr int H = BM / T < T ? BM / T : T, PIX = (H + 2) * (T + 2), STRIPS = BM / (H * T);
-    static constexpr int SLOTS = (STRIPS * PIX + 31) / 32;      // 16-byte loads per lane and chunk of 64 channels
-    static constexpr int BYTES = SLOTS * 32 * 128;
-    // Segment of 16 bytes that slot 0 of patch row p holds.  The LDS serves sixteen lanes at once (0-3, 12-15, 20-23, 24-27 and so
-    // on); under every tap their sixteen pixels lie in different (row parity, segment) pairs.
-    static __device__ __forceinline__ int swizzle(int p) {
-        const int strip = p / PIX, q = p % PIX;
-        return (q % (T + 2) / 2 + T / 2 * (q / (T + 2)) + T * T / 2 * strip) & 7;
-    }
-};
 // Loads a lane issues in the steps u0 <= u < u1 (three per chunk): every step LB weight loads, the first one before them SLOTS patch loads.
 constexpr int patch_loads(int u0, int u1, int LB, int SLOTS) {
     int n = 0;
@@ -905,7 +894,10 @@ bool wave_gemm_takes(const IgemmArgs& a) {
 //    1280 x 11520 29.5 -> 23.  It loses where few rows leave a launch its fixed cost (64 rows), its set-up being longer.
 // These launches have their own table: fitted to every form and split of 127 convolutions (320 / 640 / 1280 wide, 4 to 18432 rows, tiles
 // of edge 2 to 8, cold weights), where the choice is 0.6 % from the best on average, at worst 9 %, and 10 % faster than without PATCHES.
-enum { PRIVATE = 0, SHARED_RING = 1, BLOCK = 2, PATCHES = 3 };
+//  - WIDE, the same over 64 or 128 rows x 80 columns (conv_patch.hip), edge 4 (64 rows) or 8: fewest bytes per product, one workgroup per CU, for
+// launches that give most CUs one of its tiles.  8192 x 320 x 2880 29 -> 21.5 us, x 8640 67 -> 47; 4096 x 320 x 5760 37 -> 22.7; 2048 x 640 x 5760
+// 35 -> 24.3, x 17280 76 -> 58; not for 2432 x 320 x 2880 (152 tiles: 14 against 12.7) or 4608 x 640 x 5760 (576: 62 against 54).
+enum { PRIVATE = 0, SHARED_RING = 1, BLOCK = 2, PATCHES = 3, WIDE = 4 };
 struct TileShape { int kind, tm, tn; double fixed, tile, iter, iter_long, park, park_s, small; };
 static const TileShape kShapes[] = {
     {PRIVATE, 1, 1, 4.3, 0.0, 0.39, 0.39, 2.0, 0.15, 1}, {PRIVATE, 1, 2, 4.8, 0.0, 0.56, 0.56, 2.3, 0.3, 1}, {PRIVATE, 2, 2, 5.8, 0.0, 0.92, 0.92, 3.2, 0.6, 1},
@@ -913,7 +905,8 @@ static const TileShape kShapes[] = {
 static const TileShape kPatchShapes[] = {
     {PRIVATE, 1, 1, 4.4, 0.0, 0.25, 0.39, 2.0, 0.15, 1}, {PRIVATE, 1, 2, 4.8, 0.0, 0.56, 0.56, 2.5, 0.3, 1}, {PRIVATE, 2, 2, 5.8, 0.0, 0.92, 0.92, 3.2, 0.6, 1},
     {SHARED_RING, 2, 2, 5.2, 1.2, 0.25, 0.32, 3.2, 0.6, 1}, {BLOCK, 2, 5, 11.8, 0.0, 0.4, 0.365, 4.0, 1.5, 1},
-    {PATCHES, 1, 1, 4.9, 0.0, 0.52, 0.6, 4.0, 0.15, 1}, {PATCHES, 2, 1, 6.6, 0.0, 0.69, 0.69, 3.1, 0.3, 1.1}, {PATCHES, 2, 2, 7.0, 0.0, 1.05, 1.0, 4.3, 0.6, 1.2}};
+    {PATCHES, 1, 1, 4.9, 0.0, 0.52, 0.6, 4.0, 0.15, 1}, {PATCHES, 2, 1, 6.6, 0.0, 0.69, 0.69, 3.1, 0.3, 1.1}, {PATCHES, 2, 2, 7.0, 0.0, 1.05, 1.0, 4.3, 0.6, 1.2},
+    {WIDE, 2, 0, 6.6, 0.0, 1.68, 1.68, 0.0, 0.0, 1}, {WIDE, 4, 0, 8.9, 0.0, 2.5, 2.5, 0.0, 0.0, 1}};
 constexpr double PATCH_SIDE = 0.25;          // a K step of the side product behind the chunks
 
 // 3x3 products over pixels of square tiles whose strips have a patch form, into one map (wider tiles, rectangles, stride 2 and upsampling
@@ -935,16 +928,18 @@ static TileChoice choose_tile(const IgemmArgs& a, const IgemmWorkspace* ws) {
         if (a.geglu && sh.tn == 1) continue;
         if (sh.kind == BLOCK && (a.a_compact || a.N % 160 || a.nsect > 1 || a.out_mode[0] != OUT_MAP || (a.res && a.res_compact))) continue;
         if (sh.kind == PATCHES && sh.tm == 1 && a.tile == 2) continue;      // never the cheapest
-        const int gx = ceil_div(rows, 32 * sh.tm), gy = ceil_div(ncols, 32 * sh.tn), pieces = sh.kind == PATCHES ? a.K / 576 : nsteps;
+        if (sh.kind == WIDE && (a.N % 80 || !(a.tile == 8 || (a.tile == 4 && sh.tm == 2)))) continue;
+        const bool chunks = sh.kind == PATCHES || sh.kind == WIDE;
+        const int gx = ceil_div(rows, 32 * sh.tm), gy = sh.kind == WIDE ? a.N / 80 : ceil_div(ncols, 32 * sh.tn), pieces = chunks ? a.K / 576 : nsteps;
         for (int s = 1; s <= max_s; ++s) {
             const int per = ceil_div(pieces, s);
-            if (s > 1 && ((sh.kind != PATCHES && per < 4) || ceil_div(pieces, per) != s)) continue;
+            if (s > 1 && (sh.kind == WIDE || (sh.kind != PATCHES && per < 4) || ceil_div(pieces, per) != s)) continue;
             if (s > 1 && ((long long)gx * gy > IGEMM_COUNTERS || (size_t)gx * gy * s * 32 * sh.tm * 32 * sh.tn * 4 > ws->partial_bytes)) break;
             const long long n = (long long)gx * gy * s;
             const double iter = (nsteps > 96 ? sh.iter_long : sh.iter) * (a.tile == 2 ? sh.small : 1);
             double t = s > 1 ? sh.park + sh.park_s * s : 0.0;
             if (sh.kind == SHARED_RING) t += sh.fixed + std::max(1.0, n / 256.0) * (sh.tile + per * iter);
-            else t += (double)((n + 255) / 256) * (sh.fixed + (sh.kind == PRIVATE ? ceil_div(per, 4) : per) * iter + (sh.kind == PATCHES ? ceil_div(a.K2 / 64, s) * PATCH_SIDE : 0.0));
+            else t += (double)((n + 255) / 256) * (sh.fixed + (sh.kind == PRIVATE ? ceil_div(per, 4) : per) * iter + (chunks ? ceil_div(a.K2 / 64, s) * PATCH_SIDE * (sh.kind == WIDE ? 0.5 * sh.tm : 1.0) : 0.0));
             if (t < best) { best = t; c = {sh.kind, sh.tm, sh.tn, s}; }
         }
     }
@@ -1020,7 +1015,7 @@ int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
     a.splits = c.splits;
     if (c.kind == PATCHES) { a.kper = ceil_div(a.K / 576, c.splits); a.kper2 = ceil_div(a.K2 / 64, c.splits); }
     else a.kper = ceil_div(nsteps, c.splits);
-    a.gx = ceil_div(rows, 32 * c.tm); a.gy = ceil_div(ncols, 32 * c.tn);
+    a.gx = ceil_div(rows, 32 * c.tm); a.gy = c.kind == WIDE ? a.N / 80 : ceil_div(ncols, 32 * c.tn);
     prepare(a, ncols);
     // 384 x 640 x 11520 in 12 row tiles: 21.9 -> 18.4 us, 512 x 1280 x 11520 in eight 38.9 -> 34.9; three row tiles, which have four times
     // the lines each, 26.1 -> 28.4
@@ -1035,6 +1030,7 @@ int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st) {
     }
     int e;
     if (c.kind == PATCHES) e = a.tile == 8 ? launch_patches<8>(a, c.tm, c.tn, st) : a.tile == 4 ? launch_patches<4>(a, c.tm, c.tn, st) : launch_patches<2>(a, c.tm, c.tn, st);
+    else if (c.kind == WIDE) e = launch_conv_patch(a, c.tm, st);
     else if (c.kind == BLOCK) e = launch_tile<2, 5, 4, A_MAP, false, true>(a, st);
     else if (c.kind == SHARED_RING)
         e = a.geglu ? launch_tile<2, 2, 3, A_ROWS, true, true>(a, st) : a.a_compact ? launch_tile<2, 2, 3, A_ROWS, false, true>(a, st) : launch_tile<2, 2, 3, A_MAP, false, true>(a, st);
