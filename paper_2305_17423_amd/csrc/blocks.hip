@@ -71,12 +71,6 @@ int run_resnet(const fise_resnet_args* a, void* ws, const IgemmWorkspace* iw, hi
     // With cached statistics and a trusted cache, the producers of x0 / x1 have already written this block's
     // activated input at the active pixels (the ring outside them is unchanged), and conv1 writes conv2's.
     const bool have_acts = dv && dv->trust && !a->stats_fresh;
-    if (a->stats_fresh) {
-        if (dv) {
-            if (int e = launch_gn_stats_table(a->x0, a->x1, B, H, W, a->C0, a->C1, a->G, 1e-5f, a->gn1_mean, a->gn1_rstd, a->gn1_gamma,
-                                              a->gn1_beta, dv->ss_in, ws, st)) return e;
-        } else if (int e = fise_groupnorm_stats(a->x0, a->x1, FISE_BF16, B, H, W, a->C0, a->C1, a->G, 1e-5f, a->gn1_mean, a->gn1_rstd, ws, st)) return e;
-    }
     // Given statistics, no maps kept: both convolutions' activated inputs in one launch, conv1's epilogue completes the second.  The table
     // it needs lies at the end of the K splits' scratch.
     IgemmWorkspace cut;
@@ -91,6 +85,9 @@ int run_resnet(const fise_resnet_args* a, void* ws, const IgemmWorkspace* iw, hi
     // the normalised + activated input (active tiles and their ring) is written once, then convolved
     if (ss2) {
         if (int e = launch_resnet_acts(a, act1, act2, ss2, st, iw)) return e;
+    } else if (a->stats_fresh) {
+        if (int e = launch_gn_stats_act(a->x0, a->x1, a->C0, a->C1, B, H, W, 1e-5f, a->gn1_mean, a->gn1_rstd, a->gn1_gamma, a->gn1_beta, a->G, 1,
+                                        a->tile_idx, a->n_active, a->tile, act1, dv ? dv->ss_in : nullptr, ws, st, iw)) return e;
     } else if (!have_acts)
         if (int e = launch_gn_act_halo(a->x0, a->x1, a->C0, a->C1, B, H, W, a->gn1_mean, a->gn1_rstd, a->gn1_gamma, a->gn1_beta, a->G, 1,
                                        a->tile_idx, a->n_active, a->tile, act1, st, iw)) return e;
@@ -103,12 +100,9 @@ int run_resnet(const fise_resnet_args* a, void* ws, const IgemmWorkspace* iw, hi
     }
     if (int e = launch_igemm(c1, iw, st)) return e;
     if (a->stats_fresh) {
-        if (dv) {
-            if (int e = launch_gn_stats_table(a->h1_cache, nullptr, B, H, W, Co, 0, a->G, 1e-5f, a->gn2_mean, a->gn2_rstd, a->gn2_gamma,
-                                              a->gn2_beta, dv->ss_mid, ws, st)) return e;
-        } else if (int e = fise_groupnorm_stats(a->h1_cache, nullptr, FISE_BF16, B, H, W, Co, 0, a->G, 1e-5f, a->gn2_mean, a->gn2_rstd, ws, st)) return e;
-    }
-    if (!have_acts && !ss2)
+        if (int e = launch_gn_stats_act(a->h1_cache, nullptr, Co, 0, B, H, W, 1e-5f, a->gn2_mean, a->gn2_rstd, a->gn2_gamma, a->gn2_beta, a->G, 1,
+                                        a->tile_idx, a->n_active, a->tile, act2, dv ? dv->ss_mid : nullptr, ws, st)) return e;
+    } else if (!have_acts && !ss2)
         if (int e = launch_gn_act_halo(a->h1_cache, nullptr, Co, 0, B, H, W, a->gn2_mean, a->gn2_rstd, a->gn2_gamma, a->gn2_beta, a->G, 1,
                                        a->tile_idx, a->n_active, a->tile, act2, st)) return e;
     IgemmArgs c2 = conv_args(act2, nullptr, Co, 0, B, H, W, H, W, 3, 1, 0, a->conv2_w, a->conv2_b, Co, a->tile_idx,
@@ -158,13 +152,13 @@ int run_transformer(const fise_transformer_args* a, void* workspace, const Igemm
 
     if (a->stats_fresh) {
         if (dv) {
-            if (int e = launch_gn_stats_table(a->x, nullptr, B, H, W, C, 0, a->G, 1e-6f, a->gn_mean, a->gn_rstd, a->gn_gamma, a->gn_beta,
-                                              dv->ss_in, ws + wl.gn, st)) return e;
+            if (int e = launch_gn_stats_act(a->x, nullptr, C, 0, B, H, W, 1e-6f, a->gn_mean, a->gn_rstd, a->gn_gamma, a->gn_beta, a->G, 0, a->tile_idx,
+                                            a->n_active, a->tile, dv->act_in, dv->ss_in, ws + wl.gn, st)) return e;
         } else if (int e = fise_groupnorm_stats(a->x, nullptr, FISE_BF16, B, H, W, C, 0, a->G, 1e-6f, a->gn_mean, a->gn_rstd, ws + wl.gn, st)) return e;
     }
     // With a derived map the 1x1 in reads the normalised input (written by the producer of x under the cached
     // statistics, or here); without one it normalises in its own prologue.
-    if (dv && !(dv->trust && !a->stats_fresh))
+    if (dv && !dv->trust && !a->stats_fresh)
         if (int e = launch_gn_act_halo(a->x, nullptr, C, 0, B, H, W, a->gn_mean, a->gn_rstd, a->gn_gamma, a->gn_beta, a->G, 0,
                                        a->tile_idx, a->n_active, a->tile, dv->act_in, st)) return e;
     // the products behind a LayerNorm normalise the residual stream themselves; where their kernel does not take the width, every GEMM

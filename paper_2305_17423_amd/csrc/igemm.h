@@ -186,15 +186,16 @@ int launch_iota(int* p, int n, hipStream_t st);
 // ss[B, C] = (rstd * gamma, beta - mean * rstd * gamma): the scale / shift form of a GroupNorm with given statistics.
 int launch_gn_scale_shift(const float* mean, const float* rstd, const void* gamma, const void* beta, int B, int C, int G, float2* ss,
                           hipStream_t st);
-// mean / rstd [B, G] of the bf16 map x0 | x1 and the scale / shift table built from them (workspace as for
-// fise_groupnorm_stats).
-int launch_gn_stats_table(const void* x0, const void* x1, int B, int H, int W, int C0, int C1, int G, float eps, float* mean, float* rstd,
-                          const void* gamma, const void* beta, float2* ss, void* workspace, hipStream_t st);
 // act[B,H,W,C0+C1] = GroupNorm(x0|x1) (+SiLU) with the given statistics at the active tiles and their one-pixel ring.
 // iw: scratch of the GEMMs that follow on the stream; its arrival counters are zeroed on the way if they are not yet.
 int launch_gn_act_halo(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, const float* mean, const float* rstd,
                        const void* gamma, const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act,
                        hipStream_t st, const IgemmWorkspace* iw = nullptr);
+// The same with fresh statistics, in two launches: those of x0 | x1 to mean / rstd (and the scale / shift table ss [B, C], if given), and act with them
+// (workspace as for fise_groupnorm_stats).
+int launch_gn_stats_act(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, float eps, float* mean, float* rstd, const void* gamma,
+                        const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act, float2* ss, void* workspace,
+                        hipStream_t st, const IgemmWorkspace* iw = nullptr);
 // A ResNet block's two activated inputs under given statistics in one launch: act1 as above, of act2 (from h1_cache) the ring only, and the
 // scale / shift table ss2 [B, Cout] with which conv1's epilogue writes act2 at the active pixels.
 int launch_resnet_acts(const fise_resnet_args* a, void* act1, void* act2, float2* ss2, hipStream_t st, const IgemmWorkspace* iw);

@@ -70,6 +70,7 @@ __global__ __launch_bounds__(256) void gn_partial_vec_kernel(const bf16_t* __res
             float s[8], q[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) { s[j] = 0.f; q[j] = 0.f; }
+#pragma unroll 4                                         // (the loads go out together: one round trip, not one each)
             for (int p = p0 + ps; p < p1; p += PS) {
                 const uint4 v = *reinterpret_cast<const uint4*>(src + (size_t)p * pitch);
                 const unsigned w[4] = {v.x, v.y, v.z, v.w};
@@ -85,6 +86,7 @@ __global__ __launch_bounds__(256) void gn_partial_vec_kernel(const bf16_t* __res
         __syncthreads();
         for (int i = tid; i < CH * 8; i += 256) {
             double ds = 0, dq = 0;
+#pragma unroll 8
             for (int k = 0; k < PS; ++k) { const float2 v = stripe[k * CH * 8 + i]; ds += (double)v.x; dq += (double)v.y; }
             chan[pc * 8 + i] = make_double2(ds, dq);
         }
@@ -92,6 +94,7 @@ __global__ __launch_bounds__(256) void gn_partial_vec_kernel(const bf16_t* __res
     }
     for (int g = g0 + tid; g < g1; g += 256) {
         double s = 0, q = 0;
+#pragma unroll 10
         for (int c = g * cpg - c_lo; c < (g + 1) * cpg - c_lo; ++c) { s += chan[c].x; q += chan[c].y; }
         partial[((size_t)b * nchunk + chunk) * G + g] = make_double2(s, q);
     }
@@ -160,8 +163,9 @@ struct ActMap {
     int z, cpg; FastDiv d_chunks, d_cpg;                 // workgroups per tile (0: no such map), channels per group; divisors
 };
 
-template <bool RING>
-__device__ __forceinline__ void act_tile(const ActMap& a, int zi, int H, int W, int t, int tile, FastDiv d_side, FastDiv d_tiles_w) {
+// stat(g): mean and rstd of group g of this workgroup's batch element.
+template <bool RING, typename Stat>
+__device__ __forceinline__ void act_tile(const ActMap& a, Stat stat, int zi, int H, int W, int t, int tile, FastDiv d_side, FastDiv d_tiles_w) {
     const int b = blockIdx.y, C = a.C0 + a.C1, chunks = C / 8, side = tile + 2, tiles_w = W / tile;
     const int ty = (int)fdiv((unsigned)t, d_tiles_w), y0 = ty * tile - 1, x0 = (t - ty * tiles_w) * tile - 1;
     const int items = (RING ? 4 * (tile + 1) : side * side) * chunks;
@@ -185,7 +189,7 @@ __device__ __forceinline__ void act_tile(const ActMap& a, int zi, int H, int W, 
         // the 8 channels of a chunk lie in one group or straddle one boundary (cpg >= 8 here; else divide per channel)
         const int g0 = (int)fdiv((unsigned)c, a.d_cpg), edge = (g0 + 1) * a.cpg;
         const int g1 = min(g0 + 1, a.G - 1);
-        const float mu0 = a.mean[b * a.G + g0], rs0 = a.rstd[b * a.G + g0], mu1 = a.mean[b * a.G + g1], rs1 = a.rstd[b * a.G + g1];
+        const float2 st0 = stat(g0), st1 = stat(g1);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             float r[2];
@@ -193,8 +197,8 @@ __device__ __forceinline__ void act_tile(const ActMap& a, int zi, int H, int W, 
             for (int q = 0; q < 2; ++q) {
                 const int cc = c + 2 * e + q;
                 float mu, rs;
-                if (a.cpg >= 8) { const bool hi = cc >= edge; mu = hi ? mu1 : mu0; rs = hi ? rs1 : rs0; }
-                else { const int g = (int)fdiv((unsigned)cc, a.d_cpg); mu = a.mean[b * a.G + g]; rs = a.rstd[b * a.G + g]; }
+                if (a.cpg >= 8) { const bool hi = cc >= edge; mu = hi ? st1.x : st0.x; rs = hi ? st1.y : st0.y; }
+                else { const float2 sg = stat((int)fdiv((unsigned)cc, a.d_cpg)); mu = sg.x; rs = sg.y; }
                 const float xv = q ? __uint_as_float(xw[e] & 0xffff0000u) : __uint_as_float(xw[e] << 16);
                 const float ga = q ? __uint_as_float(gw[e] & 0xffff0000u) : __uint_as_float(gw[e] << 16);
                 const float be = q ? __uint_as_float(bw[e] & 0xffff0000u) : __uint_as_float(bw[e] << 16);
@@ -213,15 +217,61 @@ template <bool PAIR>
 __global__ __launch_bounds__(256) void gn_act_halo_kernel(const ActMap first, const ActMap second, int H, int W, const int* __restrict__ tile_idx,
                                                           int tile, FastDiv d_side, FastDiv d_tiles_w, int* __restrict__ zero, int n_zero) {
     const int t = tile_idx[blockIdx.x];
+    auto given = [](const ActMap& m) { return [&m](int g) { const int i = blockIdx.y * m.G + g; return make_float2(m.mean[i], m.rstd[i]); }; };
     for (int i = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < n_zero; i += gridDim.x * gridDim.y * gridDim.z * 256) zero[i] = 0;
-    if (!PAIR || (int)blockIdx.z < first.z) { act_tile<false>(first, blockIdx.z, H, W, t, tile, d_side, d_tiles_w); return; }
+    if (!PAIR || (int)blockIdx.z < first.z) { act_tile<false>(first, given(first), blockIdx.z, H, W, t, tile, d_side, d_tiles_w); return; }
     const int zi = (int)blockIdx.z - first.z, b = blockIdx.y;
     for (int c = (blockIdx.x * second.z + zi) * 256 + threadIdx.x; c < second.C0; c += gridDim.x * second.z * 256) {
         const int g = (int)fdiv((unsigned)c, second.d_cpg);
         const float sc = second.rstd[b * second.G + g] * bf2f(second.gamma[c]);
         second.ss[b * second.C0 + c] = make_float2(sc, fmaf(-second.mean[b * second.G + g], sc, bf2f(second.beta[c])));
     }
-    act_tile<true>(second, zi, H, W, t, tile, d_side, d_tiles_w);
+    act_tile<true>(second, given(second), zi, H, W, t, tile, d_side, d_tiles_w);
+}
+
+// The same with statistics that are still partial sums (gn_partial_vec_kernel): every workgroup adds up its batch element's chunks, one of them
+// stores the statistics and the scale / shift table.  A dense pass with fresh statistics ran a launch of 4.3 us between the two for that (60 of
+// them); here it is 32 KB of partial sums (a 64 x 64 map), from L2, in front of the pixels: 5.5 -> 6.6 us.  Whole pass 5377 -> 5207 us.
+// 256 / GP lanes a group (GP: the groups, rounded up to a power of two) add every (256 / GP)-th chunk, then one adds the lanes' sums in order.
+constexpr int GN_MAX_G = 256;
+__global__ __launch_bounds__(256) void gn_finish_act_kernel(const ActMap a, const double2* __restrict__ partial, int nchunk, int log_gp, double count, float eps,
+                                                            float* __restrict__ mean, float* __restrict__ rstd, int H, int W, const int* __restrict__ tile_idx, int tile,
+                                                            FastDiv d_side, FastDiv d_tiles_w, int* __restrict__ zero, int n_zero) {
+    __shared__ double2 sums[256];
+    __shared__ float2 stats[GN_MAX_G];
+    const int tid = threadIdx.x, b = blockIdx.y, gp = 1 << log_gp, lanes = 256 >> log_gp;
+    const int t = tile_idx[blockIdx.x];
+    for (int i = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256 + tid; i < n_zero; i += gridDim.x * gridDim.y * gridDim.z * 256) zero[i] = 0;
+    {
+        const int g = tid & (gp - 1);
+        double s = 0, q = 0;
+        if (g < a.G) {
+            const double2* p = partial + (size_t)b * nchunk * a.G + g;
+#pragma unroll 8
+            for (int k = tid >> log_gp; k < nchunk; k += lanes) { const double2 v = p[(size_t)k * a.G]; s += v.x; q += v.y; }
+        }
+        sums[tid] = make_double2(s, q);
+    }
+    __syncthreads();
+    if (tid < a.G) {
+        double s = 0, q = 0;
+        for (int k = 0; k < lanes; ++k) { const double2 v = sums[(k << log_gp) + tid]; s += v.x; q += v.y; }
+        const double m = s / count;
+        double var = q / count - m * m;
+        if (var < 0) var = 0;
+        const float2 st = make_float2((float)m, (float)(1.0 / sqrt(var + (double)eps)));
+        stats[tid] = st;
+        if (blockIdx.x == 0 && blockIdx.z == 0) { mean[b * a.G + tid] = st.x; rstd[b * a.G + tid] = st.y; }
+    }
+    __syncthreads();
+    const int C = a.C0 + a.C1;
+    if (a.ss && blockIdx.x == 0 && blockIdx.z == 0)
+        for (int c = tid; c < C; c += 256) {
+            const float2 st = stats[fdiv((unsigned)c, a.d_cpg)];
+            const float sc = st.y * bf2f(a.gamma[c]);
+            a.ss[(size_t)b * C + c] = make_float2(sc, fmaf(-st.x, sc, bf2f(a.beta[c])));
+        }
+    act_tile<false>(a, [&](int g) { return stats[g]; }, blockIdx.z, H, W, t, tile, d_side, d_tiles_w);
 }
 
 __global__ void gn_scale_shift_kernel(const float* __restrict__ mean, const float* __restrict__ rstd, const bf16_t* __restrict__ gamma,
@@ -454,7 +504,7 @@ extern "C" size_t fise_groupnorm_stats_workspace_bytes(int B, int H, int W, int 
 // gamma / beta / ss (all or none): the finish launch also writes the GroupNorm's (scale, shift) table.
 static int gn_stats_run(const char* fn, const void* x, const void* x1, int dtype, int B, int H, int W, int C0, int C1, int G,
                         float eps, float* mean, float* rstd, double2* partial, hipStream_t st, const void* gamma = nullptr,
-                        const void* beta = nullptr, float2* ss = nullptr) {
+                        const void* beta = nullptr, float2* ss = nullptr, bool finish = true) {
     const int C = C0 + C1;
     const int HW = H * W, nchunk = ceil_div(HW, GS_PIX);
     const size_t shmem = (size_t)C * sizeof(double2);
@@ -480,6 +530,7 @@ static int gn_stats_run(const char* fn, const void* x, const void* x1, int dtype
     else
         hipLaunchKernelGGL(gn_partial_kernel<bf16_t>, dim3(nchunk, B), dim3(256), shmem, st, (const bf16_t*)x, (const bf16_t*)x1, HW, C0, C1, G, partial);
     FISE_CHECK_LAUNCH("fise_groupnorm_stats(partial)");
+    if (!finish) return FISE_OK;
     hipLaunchKernelGGL(gn_finish_kernel, dim3(B * G), dim3(64), 0, st, partial, nchunk, B * G, G,
                        (double)HW * (C / G), eps, mean, rstd, (const bf16_t*)gamma, (const bf16_t*)beta, C, ss);
     FISE_CHECK_LAUNCH("fise_groupnorm_stats(finish)");
@@ -495,13 +546,29 @@ static int gn_stats_check(const char* fn, const void* x, const void* x1, int dty
     return FISE_OK;
 }
 
-// Statistics of a bf16 map (or two concatenated ones) and, in the same two launches, the GroupNorm's scale / shift table.
-int fise::launch_gn_stats_table(const void* x0, const void* x1, int B, int H, int W, int C0, int C1, int G, float eps, float* mean, float* rstd,
-                          const void* gamma, const void* beta, float2* ss, void* workspace, hipStream_t st) {
-    const char* fn = "groupnorm statistics + table";
-    if (!workspace || !gamma || !beta || !ss) return fail(FISE_ERR_NULL, "%s: null pointer", fn);
+int fise::launch_gn_stats_act(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, float eps, float* mean, float* rstd, const void* gamma,
+                              const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act, float2* ss, void* workspace,
+                              hipStream_t st, const IgemmWorkspace* iw) {
+    const char* fn = "groupnorm statistics + activation";
+    if (!workspace || !gamma || !beta || !act) return fail(FISE_ERR_NULL, "%s: null pointer", fn);
     if (int e = gn_stats_check(fn, x0, x1, FISE_BF16, B, H, W, C0, C1, G, mean, rstd)) return e;
-    return gn_stats_run(fn, x0, x1, FISE_BF16, B, H, W, C0, C1, G, eps, mean, rstd, (double2*)workspace, st, gamma, beta, ss);
+    const int C = C0 + C1;
+    if (n_active <= 0 || G > GN_MAX_G) {                 // one after the other
+        if (int e = gn_stats_run(fn, x0, x1, FISE_BF16, B, H, W, C0, C1, G, eps, mean, rstd, (double2*)workspace, st, ss ? gamma : nullptr, ss ? beta : nullptr, ss)) return e;
+        return launch_gn_act_halo(x0, x1, C0, C1, B, H, W, mean, rstd, gamma, beta, G, silu, tile_idx, n_active, tile, act, st, iw);
+    }
+    if (int e = gn_stats_run(fn, x0, x1, FISE_BF16, B, H, W, C0, C1, G, eps, mean, rstd, (double2*)workspace, st, nullptr, nullptr, nullptr, false)) return e;
+    ActMap a = act_map(x0, x1, C0, C1, mean, rstd, gamma, beta, G, silu, tile, false, act, ss);
+    a.z = std::max(1, std::min(a.z, 1024 / (n_active * B)));      // each workgroup reads the partial sums: four to a CU at most
+    int log_gp = 0;
+    while ((1 << log_gp) < G) ++log_gp;
+    const bool zero = iw && iw->counters && !iw->counters_zeroed;
+    hipLaunchKernelGGL(gn_finish_act_kernel, dim3(n_active, B, a.z), dim3(256), 0, st, a, (const double2*)workspace, ceil_div(H * W, GS_PIX), log_gp,
+                       (double)H * W * (C / G), eps, mean, rstd, H, W, tile_idx, tile, fast_div(tile + 2), fast_div(W / tile), zero ? iw->counters : nullptr,
+                       zero ? IGEMM_COUNTERS : 0);
+    FISE_CHECK_LAUNCH("gn statistics and activation with halo");
+    if (zero) iw->counters_zeroed = true;
+    return FISE_OK;
 }
 
 extern "C" int fise_groupnorm_stats(const void* x, const void* x1, int dtype, int B, int H, int W, int C0, int C1, int G,
