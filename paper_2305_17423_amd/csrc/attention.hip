@@ -553,23 +553,43 @@ static int attention_splits(int B, int M, int n_keys, int C, int heads) {
     return std::max(1, std::min(s, 32));
 }
 
-// Which kernel: the one whose time is smaller by lines fitted to both over 175 launches (1 to 4096 queries, 16 to 4096 keys, heads of 8 to
-// 160, cold keys; the choice is 0.1 % from the better one on average, 5 % at worst).  Us, d = head dim:
-//  - few queries: 2.8 + 0.019 d, 0.32 + 0.02 d per 256 keys and round of 256 workgroups, 0.037 d per further round;
-//  - the other: 2.2 + 0.007 d, 0.57 + 0.01 d per key block of a workgroup (more where more than two share a CU), 0.47 + 0.004 d for a partial block,
-//    and for split keys 3.9 and 3.3 per million parked elements.
-// 2 x 48 queries, 256 keys of 8 x 160 channels 12.0 -> 10.4 us; 2 x 192 x 77 keys of 8 x 80 6.6 -> 5.4; 2 x 384 x 1024 21.5 -> 12.7; 2 x
-// 192 x 2304 of 8 x 40 17.9 -> 14.0; 2 x 768 x 4096 of 8 x 40 stays (34 against 36).
+// What a launch costs in us, by lines fitted to 500 of them (32 to 4096 queries, 128 to 9216 keys, heads of 40, 80 and 160, cold keys, every
+// split that the scratch allows); d = head dim.  A workgroup spends 0.52 + 0.009 d on each of its key blocks and 0.44 more for every further
+// workgroup on its CU, which holds three of heads up to 64 and two of wider ones; more workgroups than that go round again.  A split costs
+// 3.5 for the merge and 2.6 per million parked elements (rows x channels x splits).
+static double attention_us(int B, int M, int n_keys, int C, int heads, int splits) {
+    const int d = C / heads, resident = d <= 64 ? 3 : 2;
+    const double wgs = (double)ceil_div(M, AT_BQ) * heads * B * splits;
+    const double on_cu = std::min(std::ceil(wgs / 256.0), (double)resident);
+    const int per = ceil_div(ceil_div(n_keys, AT_BKV), splits);
+    return 2.2 + 0.0068 * d + (n_keys % AT_BKV ? 0.47 + 0.0036 * d : 0.0) +
+           per * std::max(1.0, wgs / (256.0 * resident)) * (0.52 + 0.0086 * d + 0.44 * (on_cu - 1.0)) +
+           (splits > 1 ? 3.5 + 2.6e-6 * splits * B * M * C : 0.0);
+}
+
+// Splits of a launch, of the `most` that its scratch holds (2.5 workgroups per CU): as many as pay for what they park.  1.1 % from the best
+// one on average over 90 shapes, 12 % at worst; all of `most` 11 % and 43 %.  2 x 1024 queries and keys of 8 x 80 channels: 5 splits 30.0
+// us, none 22.2; of 8 x 40 5 splits 22.1, two 17.5; 2 x 384 x 1024 keys of 8 x 80 8 splits 21.1, four 17.0; 2 x 4096 x 4096 of 8 x 40 two
+// splits 101, none 95; 2 x 2752 x 9216 stays at two.
+static int attention_launch_splits(int B, int M, int n_keys, int C, int heads, int most) {
+    int best = 1;
+    double us = attention_us(B, M, n_keys, C, heads, 1);
+    for (int s = 2; s <= most; ++s) {
+        const double t = attention_us(B, M, n_keys, C, heads, s);
+        if (t < us) { us = t; best = s; }
+    }
+    return best;
+}
+
+// Which kernel: the one whose time is smaller, 0.6 % from the better one on average over 105 shapes, 14 % at worst.  Few queries: 2.8 + 0.019
+// d us, 0.32 + 0.02 d per 256 keys and round of 256 workgroups, 0.037 d per further round.  2 x 48 queries, 256 keys of 8 x 160 channels
+// 12.0 -> 10.4 us; 2 x 192 x 77 keys of 8 x 80 6.6 -> 5.4; 2 x 384 x 1024 17.0 -> 12.7; 2 x 768 x 4096 of 8 x 40 stays (31 against 36).
 static bool attention_few(int B, int M, int n_keys, int n_stride, int C, int heads, int splits) {
     const double lim = 1u << 30;                         // 32-bit offsets into a batch element
     if ((double)n_keys * C >= lim || (double)C * n_stride >= lim || (double)M * C >= lim) return false;
     const int d = C / heads, few_wgs = ceil_div(M, 32) * heads * B, rounds = ceil_div(few_wgs, 256);
     const double few = 2.8 + 0.019 * d + rounds * (ceil_div(n_keys, 32) / 8.0) * (0.32 + 0.02 * d) + (rounds - 1) * 0.037 * d;
-    const double wgs = (double)ceil_div(M, AT_BQ) * heads * B * splits;
-    const int per = ceil_div(ceil_div(n_keys, AT_BKV), splits);
-    const double many = 2.2 + 0.0068 * d + (n_keys % AT_BKV ? 0.47 + 0.0036 * d : 0.0) + per * std::max(1.0, wgs / 512.0) * (0.57 + 0.0095 * d) +
-                        (splits > 1 ? 3.9 + 3.3e-6 * splits * B * M * C : 0.0);
-    return few < (splits > 1 ? 0.93 : 1.0) * many;       // with warm keys the key splits gain more: 2 x 80 queries, 1024 keys of 8 x 80 11.0 against 12.2
+    return few < attention_us(B, M, n_keys, C, heads, splits);
 }
 
 size_t attention_workspace_bytes(int B, int M, int n_keys, int C, int heads) {
@@ -583,8 +603,9 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
     if (M <= 0) return FISE_OK;
     const int d = C / heads;
     const int kd = ceil_div(d, 16);
-    int splits = attention_splits(B, M, n_keys, C, heads);
+    int splits = attention_splits(B, M, n_keys, C, heads);                         // what the scratch is laid out for
     if (splits > 1 && (!ws || ws_bytes < attention_workspace_bytes(B, M, n_keys, C, heads))) splits = 1;
+    splits = attention_launch_splits(B, M, n_keys, C, heads, splits);
     if (attention_few(B, M, n_keys, n_stride, C, heads, splits)) splits = 0;       // one launch whatever the key range
     float* part_o = (float*)ws;
     float* part_ml = splits > 1 ? (float*)((char*)ws + align256((size_t)splits * B * M * C * sizeof(float))) : nullptr;
