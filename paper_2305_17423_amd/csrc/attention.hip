@@ -24,18 +24,30 @@ constexpr int AT_BQ = AT_QW * AT_WAVES;
 
 __device__ __forceinline__ void at_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// A query's two lanes: the swap leaves the lower half's value in one result and the upper half's in the other.  An instruction where a shuffle
+// is a trip to the LDS between the scores and their exponentials (and the sums meet once, behind the last block): 2 x 9216 queries and keys of
+// 8 x 40 channels 436 -> 421 us, 2 x 4096 of 8 x 160 216 -> 212, 2 x 1024 of 8 x 160 37.8 -> 35.9, 2 x 768 x 4096 keys of 8 x 40 unchanged.
+__device__ __forceinline__ float2 at_halves(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return make_float2(__uint_as_float(p[0]), __uint_as_float(p[1]));
+#else
+    return make_float2(x, x);
+#endif
+}
+
 // KD: 16-wide steps over the head dim; DB: 32-row blocks of the output head dim; EXACT: the head dim is 16 KD (80, 160: the set-up
 // of a short launch is instructions, and most of its conditions and address terms are constants then).
 // What bounds it: few queries, the round trips of the key blocks (~0.9 us each with two blocks in flight, heads up to 96; ~2 us
 // with one); many queries, the exponentials and the other ~100 vector instructions per 64 keys.  The wide heads sit right below
-// 256 registers, where a CU still holds two workgroups: 2 x 4096 queries and keys of 8 x 160 channels 226 us, at 262
-// registers 325.
+// 256 registers, where a CU still holds two workgroups: 2 x 4096 queries and keys of 8 x 160 channels 212 us, at 262
+// registers half as fast again (325 when it was 226).
 template <int KD, int DB, bool EXACT>
-__global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K,
-                                                        const bf16_t* __restrict__ Vt, int B, int M, int n_keys, int n_stride,
-                                                        int C, int d_arg, float scale_log2e, int splits, int nqt, int heads,
-                                                        FastDiv d_nqt, FastDiv d_heads, FastDiv d_splits, int chunk_mul,
-                                                        bf16_t* __restrict__ out, float* __restrict__ part_o, float* __restrict__ part_ml) {
+__global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K,
+                                                           const bf16_t* __restrict__ Vt, int B, int M, int n_keys, int n_stride,
+                                                           int C, int d_arg, float scale_log2e, int splits, int nqt, int heads,
+                                                           FastDiv d_nqt, FastDiv d_heads, FastDiv d_splits, int chunk_mul,
+                                                           bf16_t* __restrict__ out, float* __restrict__ part_o, float* __restrict__ part_ml) {
     constexpr int DP = KD * 16;
     constexpr int KP = DP + 8;            // K tile pitch (bf16)
     constexpr int VP = AT_BKV + 8;        // V^T tile pitch
@@ -83,7 +95,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
     for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e) oacc[i][e] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;                // l: of this lane's half of the keys until the end
 
     // ---- register staging of key blocks.  Thread slot j covers chunk e = tid + 256 j of the block's real data:
     // K rows of d / 8 chunks (key e / dchunks, chunk e % dchunks), V^T rows of 8 chunks (row e / 8 < d, keys
@@ -204,8 +216,8 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int e = 0; e < 16; ++e) mraw = fmaxf(mraw, s[kb][e]);
-        mraw = fmaxf(mraw, __shfl_xor(mraw, 32));
-        const float mx = fmaxf(m_run, mraw * scale_log2e);
+        const float2 mh = at_halves(mraw);
+        const float mx = fmaxf(m_run, fmaxf(mh.x, mh.y) * scale_log2e);
         const float alpha = __builtin_amdgcn_exp2f(m_run - mx);   // first block: exp2(-inf) = 0
         float psum = 0.f;
 #pragma unroll
@@ -216,7 +228,6 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
                 s[kb][e] = p;
                 psum += p;
             }
-        psum += __shfl_xor(psum, 32);
         l_run = l_run * alpha + psum;
         m_run = mx;
 #pragma unroll
@@ -248,6 +259,8 @@ __global__ __launch_bounds__(256) void attention_kernel(const bf16_t* __restrict
 
     // ---- store: lane holds query l32, head-dim rows i*32 + (e/4)*8 + hl*4 + e%4: four consecutive elements of e are
     // four consecutive channels (d is a multiple of 8, so a group of four is inside the head or outside it as a whole)
+    const float2 lh = at_halves(l_run);
+    l_run = lh.x + lh.y;
     if (!qok) return;
     if (splits == 1) {
         const float inv = 1.0f / l_run;
