@@ -152,6 +152,10 @@ bool wave_gemm_takes(const IgemmArgs& a);
 int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st);
 // 3x3 convolution on tiles of 32 * tm rows x 80 columns (conv_patch.hip; tm 2 or 4, tiles of edge 4 or 8, N a multiple of 80); called with the launcher's fields set.
 int launch_conv_patch(const IgemmArgs& a, int tm, hipStream_t st);
+
+// Linears of many compact rows into float rows (linear_wide.hip).
+bool linear_wide_takes(const IgemmArgs& a);
+int launch_linear_wide(const IgemmArgs& a, hipStream_t st);
 // Normalised rows times weights (norm_gemm.hip).  Rows of K channels: compact float rows under a LayerNorm, or the active pixels of a bf16 map
 // [B, Ho*Wo, K] under a LayerNorm, under a GroupNorm with given statistics, or as they are.  N columns in sections of sect_n, section s with
 // weights w[s] [sect_n, K] to out[s] (only the last one transposed; geglu: one section, w[0] [2N, K]); a bias belongs to one section.

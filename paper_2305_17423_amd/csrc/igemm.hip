@@ -1185,9 +1185,10 @@ int launch_igemm(const IgemmArgs& a, const IgemmWorkspace* ws, hipStream_t st) {
     for (int i = 0; i < a.nview; ++i)
         if (!a.view[i].dst || !a.view[i].ss || a.view[i].dstC % 4 || a.view[i].c_off % 4 || a.view[i].c_off + a.N > a.view[i].dstC)
             return fail(FISE_ERR_SHAPE, "igemm: normalised copy %d: channels %d + %d of %d", i, a.view[i].c_off, a.N, a.view[i].dstC);
+    if (linear_wide_takes(a)) return launch_linear_wide(a, st);      // float rows from 2048 on, one tile per CU
     // all but compact rows of one section from 2048 rows on, and what is not made of 64-channel pieces
     if (wave_gemm_takes(a)) return launch_wave_gemm(a, ws, st);
-    // The LDS-direct kernel then runs linears of 64 x 64 (below 4096 rows) and 64 x 128 tiles; its other tiles, and any tile over maps, only
+    // The LDS-direct kernel then runs the other linears of 64 x 64 (below 4096 rows) and 64 x 128 tiles; its other tiles, and any tile over maps, only
     // where the output width is no multiple of 4, several outputs are no multiples of 64 wide, an array has 2^24 pixels or float rows
     // fill 2 GiB.  The register-staged kernel uses them all.
     const bool wide = rows >= 4096 && a.N >= 128;          // dense-sized problems: 64x128 tiles, 8 waves

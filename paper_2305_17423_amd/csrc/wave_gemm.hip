@@ -864,7 +864,7 @@ static bool wave_gemm_fits(const IgemmArgs& a) {
            ncols * std::max(a.K, a.K2) * 2 < kLim && (size_t)rows * a.N * 4 < kLim;
 }
 
-// Compact rows of one section from here on: igemm.hip's 64 x 128 and 64 x 64 tiles (8192 x 320 x 320 12.8 against 14.3 us,
+// Compact rows of one section from here on: linear_wide.hip (float rows) and igemm.hip's 64 x 128 and 64 x 64 tiles (8192 x 320 x 320 12.8 against 14.3 us,
 // 2048 x 640 x 640 12.7 against 13.3 us on shared tiles).
 constexpr int BLOCK_ROWS = 2048;
 bool wave_gemm_takes(const IgemmArgs& a) {
