@@ -26,12 +26,13 @@ if ROOT not in sys.path:
 MFMA_BF16_PEAK_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 HBM_PEAK_GBS = 8000.0
 
-# fise_profile_read kinds -> the kernel a profiler lists for them (behind a slash: what runs where wave_gemm does not take a launch,
-# 64x64 tiles for 2048 - 4095 compact rows, the others for odd widths only)
-KIND_NAMES = {0: "wave_gemm_kernel<*,A_MAP> / igemm_dma_kernel<64,64,*>", 1: "wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>",
-              2: "attention_kernel", 3: "igemm_dma_kernel<64,128,2,4,3,*>", 4: "igemm_reduce_kernel / igemm_reduce_ln_kernel",
+# fise_profile_read kinds -> the kernels a profiler lists for them (igemm_dma_kernel: 64x64 tiles for 2048 - 4095 compact rows,
+# 64x128 from there on, where linear_wide does not take them; its other tiles for odd widths only)
+KIND_NAMES = {0: "wave_gemm_kernel<*,A_MAP> / conv_patch_kernel / igemm_dma_kernel<64,64,*>",
+              1: "norm_gemm_kernel<*,GEGLU> / wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>",
+              2: "attention_kernel / attention_few_kernel", 3: "linear_wide_kernel / igemm_dma_kernel<64,128,2,4,3,*>", 4: "igemm_reduce_kernel",
               5: "igemm_dma_kernel<32,128,1,4,3,*>", 6: "igemm_kernel<...> (GroupNorm prologue)", 7: "attention_merge_kernel",
-              8: "(empty bracket)", 9: "wave_gemm_kernel<*,A_ROWS>"}
+              8: "(empty bracket)", 9: "norm_gemm_kernel / wave_gemm_kernel<*,A_ROWS>"}
 # HBM bytes per launch (read + written) of the library's kernels from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of
 # this bench on the headline workload: profiles/masked_unet_step_sd15_10pct_traffic.json, written by
 # `python -m paper_2305_17423_amd.profile_summary` together with the sha1 of the kernel sources it was measured

@@ -29,7 +29,7 @@ __device__ __forceinline__ float cp_hi(unsigned w) { return __uint_as_float(w & 
 #endif
 
 constexpr int CP_TAP = 80 * 128, CP_STEP = 3 * CP_TAP;       // bytes of a tap's weights, of a kernel row's
-constexpr int CP_LW = 8;                // loads of a kernel row's weights per wave: 30 of 1 KB, dealt out (two are loads of nothing)
+[[maybe_unused]] constexpr int CP_LW = 8;   // loads of a kernel row's weights per wave: 30 of 1 KB, dealt out (two are loads of nothing)
 template <int RT, int T> struct ConvPatch {
     static constexpr int BM = 32 * RT, SIDE = (BM + 80) * 128, RING = 2 * Patch<BM, T>::BYTES + 3 * CP_STEP, NS = RING / SIDE < 4 ? RING / SIDE : 4;
     static constexpr int LDS = RING + 1024 + BM * 8;    // patches, weights, a place for loads of nothing, the rows' positions

@@ -1,10 +1,12 @@
 // Gathered implicit GEMM on bf16 MFMA behind masked convolutions (3x3 / 1x1,
 // stride 2, nearest-2x upsample, two concatenated sources) and the per-token
-// linears of the transformer blocks: one argument block, three kernels.
-// launch_igemm gives what is made of 64-channel pieces to wave_gemm_kernel
-// (wave_gemm.hip) except compact rows of one section from 2048 rows on, which
-// igemm_dma_kernel takes; a GroupNorm prologue and 32-channel pieces go to
-// igemm_kernel (both igemm.hip).  Internal.
+// linears of the transformer blocks: one argument block.
+// launch_igemm gives what is made of 64-channel pieces to wave_gemm.hip (and from
+// there 3x3 convolutions of many rows to conv_patch.hip) except compact rows of one
+// section from 2048 rows on: those go to linear_wide.hip (float rows, one tile per
+// CU) or igemm_dma_kernel; a GroupNorm prologue and 32-channel pieces go to
+// igemm_kernel (both igemm.hip).  Products behind a normalisation of 320, 640 or
+// 1280 channels have norm_gemm.hip and arguments of their own.  Internal.
 #pragma once
 #include "common.h"
 
@@ -46,8 +48,7 @@ struct IgemmArgs {
     int nsect, sect_n;                                  // N = nsect * sect_n; section s goes to out[s]
     bf16_t* out[3]; int out_mode[3];
     bf16_t* mirror;                                     // OUT_COMPACT_F32 only: also store a bf16 copy here (may be null)
-    // ---- optional LayerNorm of the finished rows (one OUT_COMPACT_F32 section, N = sect_n): ln_out[rows, N] bf16.
-    // Fused into the split-K reduce launch where the shape allows, otherwise a separate launch.
+    // ---- optional LayerNorm of the finished rows (one OUT_COMPACT_F32 section, N = sect_n): ln_out[rows, N] bf16, in a launch of its own.
     const bf16_t* ln_gamma; const bf16_t* ln_beta; float ln_eps; bf16_t* ln_out;
     // ---- optional side product accumulated into the same tile: 1x1 conv of the raw maps s0 | s1
     // [B,Ho,Wo,S*] at the output pixel with weights w2 [N, K2] and bias2 (K2 = S0 + S1, 0 = none)

@@ -7,7 +7,8 @@
 // is packed in HBM.  The optional second product is a 1x1 convolution of other
 // maps at the same pixel (the ResNet shortcut), accumulated into the same tile.
 //
-// Most launches of a step go to wave_gemm.hip; here are the linears of dense-sized row
+// Most launches of a step go to wave_gemm.hip, norm_gemm.hip (behind a normalisation) and
+// linear_wide.hip (float rows); here are the other linears of dense-sized row
 // counts (igemm_dma_kernel), what has a GroupNorm prologue or 32-channel pieces
 // (igemm_kernel), and the few shapes that wave_gemm_takes refuses.
 // The masked problems are small (a few GFLOP, often a few dozen rows against tens
@@ -955,94 +956,6 @@ __global__ __launch_bounds__(256) void igemm_reduce_kernel(const IgemmArgs a) {
     epilogue_put4(a, osel, gm, pos, col, r, a.nview ? &vss : nullptr);
 }
 
-// Split-K reduce fused with the LayerNorm that follows a residual-stream GEMM: LPR lanes share a row of
-// N = 20 * LPR columns (320 / 640 / 1280), each lane owns 20 consecutive columns as 5 x float4.  The
-// lanes sum the partials in split order on top of bias and residual, store the float row (the new
-// residual stream), then normalise it in registers (two passes, fp32) and store the bf16 LayerNorm row.
-template <int LPR>
-__global__ __launch_bounds__(256) void igemm_reduce_ln_kernel(const IgemmArgs a) {
-    asm volatile("" ::"s"(a.B), "s"(a.Ma), "s"(a.partial), "s"(a.splits), "s"(a.bias), "s"(a.res), "s"(a.out[0]), "s"(a.mirror),
-                 "s"(a.ln_gamma), "s"(a.ln_beta), "s"(a.ln_eps), "s"(a.ln_out));    // one batch of argument loads
-    constexpr int C = 20 * LPR, RPB = 256 / LPR;
-    const int rows = a.B * a.Ma;
-    const int row = blockIdx.x * RPB + threadIdx.x / LPR;
-    const int l = threadIdx.x % LPR;
-    if (row >= rows) return;                      // whole LPR-lane groups leave together
-    const size_t off = (size_t)row * C + l * 20;
-    // LayerNorm scale and shift of this lane's channels: requested here with everything else (read in the store loop
-    // they would each wait behind the previous store, which the compiler must assume may alias them)
-    uint2 gv[5], bv[5];
-    {
-        const uint2* g2 = reinterpret_cast<const uint2*>(a.ln_gamma + l * 20);
-        const uint2* b2 = reinterpret_cast<const uint2*>(a.ln_beta + l * 20);
-#pragma unroll
-        for (int j = 0; j < 5; ++j) { gv[j] = g2[j]; bv[j] = b2[j]; }
-    }
-    float4 v[5];
-    {
-        // residual and bias: each as one batch of loads behind one uniform test (tested per element they became
-        // five load - wait - add rounds)
-        uint2 bb[5];
-#pragma unroll
-        for (int j = 0; j < 5; ++j) { v[j] = make_float4(0.f, 0.f, 0.f, 0.f); bb[j] = make_uint2(0u, 0u); }
-        if (a.res) {
-            const float4* r4 = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(a.res) + off);
-#pragma unroll
-            for (int j = 0; j < 5; ++j) v[j] = r4[j];
-        }
-        if (a.bias) {
-            const uint2* b2 = reinterpret_cast<const uint2*>(a.bias + l * 20);
-#pragma unroll
-            for (int j = 0; j < 5; ++j) bb[j] = b2[j];
-        }
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            v[j].x += __uint_as_float(bb[j].x << 16); v[j].y += __uint_as_float(bb[j].x & 0xffff0000u);
-            v[j].z += __uint_as_float(bb[j].y << 16); v[j].w += __uint_as_float(bb[j].y & 0xffff0000u);
-        }
-    }
-    const float4* P = reinterpret_cast<const float4*>(a.partial + off);
-    const size_t stride4 = (size_t)rows * C / 4;
-#pragma unroll 4
-    for (int z = 0; z < a.splits; ++z) {
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            const float4 p = P[z * stride4 + j];
-            v[j].x += p.x; v[j].y += p.y; v[j].z += p.z; v[j].w += p.w;
-        }
-    }
-    float4* h4 = reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out[0]) + off);
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) { h4[j] = v[j]; s += (v[j].x + v[j].y) + (v[j].z + v[j].w); }
-    if (a.mirror) {
-        uint2* m2 = reinterpret_cast<uint2*>(a.mirror + off);
-#pragma unroll
-        for (int j = 0; j < 5; ++j) m2[j] = make_uint2(f2bf2(v[j].x, v[j].y), f2bf2(v[j].z, v[j].w));
-    }
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    const float mu = s / C;
-    float q = 0.f;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-        const float a0 = v[j].x - mu, a1 = v[j].y - mu, a2 = v[j].z - mu, a3 = v[j].w - mu;
-        q += (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
-    }
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) q += __shfl_xor(q, o);
-    const float rs = rsqrtf(q / C + a.ln_eps);
-    uint2* o2 = reinterpret_cast<uint2*>(a.ln_out + off);
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-        const float y0 = (v[j].x - mu) * rs * __uint_as_float(gv[j].x << 16) + __uint_as_float(bv[j].x << 16);
-        const float y1 = (v[j].y - mu) * rs * __uint_as_float(gv[j].x & 0xffff0000u) + __uint_as_float(bv[j].x & 0xffff0000u);
-        const float y2 = (v[j].z - mu) * rs * __uint_as_float(gv[j].y << 16) + __uint_as_float(bv[j].y << 16);
-        const float y3 = (v[j].w - mu) * rs * __uint_as_float(gv[j].y & 0xffff0000u) + __uint_as_float(bv[j].y & 0xffff0000u);
-        o2[j] = make_uint2(f2bf2(y0, y1), f2bf2(y2, y3));
-    }
-}
-
 
 // ---------------------------------------------------------------------------
 // host side: tile shape and K split per problem
@@ -1136,21 +1049,9 @@ static int launch_bk(IgemmArgs a, const IgemmWorkspace* ws, int prof_kind, hipSt
         else hipLaunchKernelGGL((igemm_kernel<BM, BN, WGM, WGN, BK, false>), grid, dim3(64 * WGM * WGN), 0, st, a);
     }
     FISE_CHECK_LAUNCH("igemm");
-    // LayerNorm of the finished rows: inside the reduce launch when there is one and the row shape is one the
-    // fused kernel is built for, otherwise as a launch of its own after the rows are complete
-    const bool ln = a.ln_out != nullptr;
+    const bool ln = a.ln_out != nullptr;                // LayerNorm of the finished rows
     if (ln && (a.nsect != 1 || a.out_mode[0] != OUT_COMPACT_F32 || a.geglu || !a.ln_gamma || !a.ln_beta))
         return fail(FISE_ERR_SHAPE, "igemm: LayerNorm output needs one float compact section");
-    const bool ln_fused = ln && a.splits > 1 && !a.temb && !a.bias2 && (!a.res || a.res_compact == 2) &&
-                          (a.N == 320 || a.N == 640 || a.N == 1280);
-    if (ln_fused) {
-        ProfileScope prof(PROF_REDUCE, 0.0, (double)a.splits * rows * ncols * 4.0 + 10.0 * rows * a.N, st);
-        if (a.N == 320) hipLaunchKernelGGL(igemm_reduce_ln_kernel<16>, dim3(ceil_div(rows, 16)), dim3(256), 0, st, a);
-        else if (a.N == 640) hipLaunchKernelGGL(igemm_reduce_ln_kernel<32>, dim3(ceil_div(rows, 8)), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(igemm_reduce_ln_kernel<64>, dim3(ceil_div(rows, 4)), dim3(256), 0, st, a);
-        FISE_CHECK_LAUNCH("igemm reduce + layernorm");
-        return FISE_OK;
-    }
     if (a.splits > 1) {
         const dim3 rgrid((unsigned)ceil_div(a.N / 4, 64), (unsigned)ceil_div(rows, 4));
         ProfileScope prof(PROF_REDUCE, 0.0, (double)a.splits * rows * ncols * 4.0 + 2.0 * rows * a.N, st);

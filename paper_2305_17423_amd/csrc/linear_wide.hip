@@ -159,7 +159,7 @@ static int launch_lw(const LinearWide& a, hipStream_t st) {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_wide_kernel<RT>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return fail(FISE_ERR_HIP, "linear: cannot raise the dynamic LDS limit");
     {
-        ProfileScope prof(PROF_IGEMM, 2.0 * a.rows * a.N * (double)a.K, 2.0 * ((double)a.N * a.K + (double)a.rows * a.K) + 8.0 * a.rows * a.N, st);
+        ProfileScope prof(PROF_IGEMM_WIDE, 2.0 * a.rows * a.N * (double)a.K, 2.0 * ((double)a.N * a.K + (double)a.rows * a.K) + 8.0 * a.rows * a.N, st);
         hipLaunchKernelGGL((linear_wide_kernel<RT>), dim3((unsigned)(ceil_div(a.rows, 32 * RT) * a.gy)), dim3(256), lds, st, a);
     }
     FISE_CHECK_LAUNCH("linear");

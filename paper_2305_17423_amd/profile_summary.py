@@ -52,25 +52,26 @@ def short(name: str) -> str:
 def kind_of(name: str):
     """The fise_profile_read kind (as bench.py names it) a profiler kernel name belongs to, or None."""
     n = short(name)
-    wave = re.search(r"wave_gemm_kernel<\d+, \d+, \d+, \d+, (\d), (true|false), (?:true|false)>", n)      # A operand, GEGLU, ring
-    if wave and wave[2] == "true" or "igemm_dma_kernel<64, 128, 2, 2" in n or "igemm_dma_kernel<32, 256" in n:
-        return "wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>"
-    if wave and wave[1] == "0":
-        return "wave_gemm_kernel<*,A_ROWS>"
-    if wave or "igemm_dma_kernel<64, 64, 2, 2" in n:
-        return "wave_gemm_kernel<*,A_MAP> / igemm_dma_kernel<64,64,*>"
-    if "igemm_dma_kernel<64, 128, 2, 4" in n:
-        return "igemm_dma_kernel<64,128,2,4,3,*>"
+    wave = re.search(r"wave_gemm_(?:group_)?kernel<\d+, \d+, \d+, \d+, (\d), (true|false), ", n)      # A operand, GEGLU
+    norm = re.search(r"norm_gemm_kernel<\d+, \d+, \d+, \d+, (true|false)>", n)                      # GEGLU
+    if wave and wave[2] == "true" or norm and norm[1] == "true" or "igemm_dma_kernel<64, 128, 2, 2" in n or "igemm_dma_kernel<32, 256" in n:
+        return "norm_gemm_kernel<*,GEGLU> / wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>"
+    if norm or "wave_gemm_group" in n or wave and wave[1] == "0":
+        return "norm_gemm_kernel / wave_gemm_kernel<*,A_ROWS>"
+    if wave or "conv_patch_kernel" in n or "igemm_dma_kernel<64, 64, 2, 2" in n:
+        return "wave_gemm_kernel<*,A_MAP> / conv_patch_kernel / igemm_dma_kernel<64,64,*>"
+    if "linear_wide_kernel" in n or "igemm_dma_kernel<64, 128, 2, 4" in n:
+        return "linear_wide_kernel / igemm_dma_kernel<64,128,2,4,3,*>"
     if "igemm_dma_kernel<32, 128" in n:
         return "igemm_dma_kernel<32,128,1,4,3,*>"
     if "igemm_reduce" in n:
-        return "igemm_reduce_kernel / igemm_reduce_ln_kernel"
+        return "igemm_reduce_kernel"
     if "igemm_kernel" in n:
         return "igemm_kernel<...> (GroupNorm prologue)"
     if "attention_merge" in n:
         return "attention_merge_kernel"
-    if "attention_kernel" in n:
-        return "attention_kernel"
+    if "attention_kernel" in n or "attention_few_kernel" in n:
+        return "attention_kernel / attention_few_kernel"
     return None
 
 
