@@ -85,7 +85,7 @@ def _rows(d, pattern):
 def _steps(rows, key_start="Start_Timestamp"):
     """Index ranges of whole steps: each begins with the mask-detection kernel."""
     rows.sort(key=lambda r: int(r[key_start]))
-    starts = [i for i, r in enumerate(rows) if "pixel_diff_kernel" in r["Kernel_Name"]]
+    starts = [i for i, r in enumerate(rows) if "pixel_diff" in r["Kernel_Name"]]
     return [(a, b) for a, b in zip(starts[:-1], starts[1:])]
 
 
@@ -147,7 +147,7 @@ def _pmc(d, counter):
 def _steady_steps(rows):
     """Index ranges of the steady-state masked steps (each begins with the mask-detection kernel; the most common
     launch count is the masked step's)."""
-    starts = [i for i, r in enumerate(rows) if "pixel_diff_kernel" in r["Kernel_Name"]]
+    starts = [i for i, r in enumerate(rows) if "pixel_diff" in r["Kernel_Name"]]
     steps = [(a, b) for a, b in zip(starts[:-1], starts[1:])]
     n_launch = collections.Counter(b - a for a, b in steps).most_common(1)[0][0]
     return [(a, b) for a, b in steps if b - a == n_launch][1:]
