@@ -323,7 +323,6 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
 #if defined(__HIP_DEVICE_COMPILE__)
     using T = FewTile<KD>;
     constexpr int KS = T::KS, PS = T::PS, NK = PS / 2;  // LDS-direct loads of 32 keys
-    constexpr unsigned OOB = 0x80000000u;
     typedef unsigned u32x4_a __attribute__((ext_vector_type(4)));
     __shared__ __attribute__((aligned(16))) unsigned char keys[T::LDS];      // later the partial sums [waves][SLICE][64 lanes]
     __shared__ float2 ml[AF_WAVES][32];
@@ -340,10 +339,10 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
         qt = w - t * nqt; h = t - b * heads;
     }
     const int d = EXACT ? KD * 16 : d_arg;
-    const int nsb = (n_keys + 31) / 32;
-    // queries and keys past the last one and channels past the head lie outside these: zeros
+    const int nsb = (n_keys + AF_BKV - 1) / AF_BKV;
+    // queries, keys and channels that do not exist lie outside the descriptors: zeros (attention_keys.h)
     const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(q + (size_t)b * M * C + h * d), 0, (M * C - h * d) * 2, 0x00020000);
-    bf16_t* const kp = const_cast<bf16_t*>(K + (size_t)b * n_keys * C + h * d);
+    unsigned char* const kp = reinterpret_cast<unsigned char*>(const_cast<bf16_t*>(K + (size_t)b * n_keys * C));
     bf16_t* const vp = const_cast<bf16_t*>(Vt + ((size_t)b * C + h * d) * n_stride);
     unsigned char* const my_keys = keys + wave * T::KBYTES;
     unsigned ok[NK];
@@ -351,23 +350,23 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
     for (int j = 0; j < NK; ++j) {
         const int slot = j * 64 + lane, r = slot / PS, seg = (slot % PS) ^ T::swizzle(r);
         const int key = 8 * ((r >> 2) & 3) + 4 * (r >> 4) + (r & 3);
-        ok[j] = seg * 8 < d ? (unsigned)(key * C + seg * 8) * 2u : OOB;
+        ok[j] = af_key_offset(key, seg, C, d);
     }
     // Requests for keys behind the last ones go out through descriptors of size zero, not behind branches: the compiler counts the loads
     // in flight by the path that has fewest, and each wait for values would wait for the next keys too.
     auto fetch_k = [&](int sb) {
-        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(kp, 0, sb < nsb ? (n_keys * C - h * d) * 2 : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(kp + af_key_base(C, h, d, sb), 0, (int)af_key_size(n_keys, C, h, d, sb), 0x00020000);
 #pragma unroll
         for (int j = 0; j < NK; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (__attribute__((address_space(3))) void*)(my_keys + j * 1024), 16, ok[j], (unsigned)(sb * 64) * (unsigned)C, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (__attribute__((address_space(3))) void*)(my_keys + j * 1024), 16, ok[j], 0, 0, 0);
     };
     u32x4_a vf[KD];
-    const unsigned ov = (unsigned)(l16 * n_stride + lq * 8) * 2u;
+    const unsigned ov = af_value_row(l16, lq * 8, n_stride);
     auto fetch_v = [&](int sb) {
-        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(vp, 0, sb < nsb ? d * n_stride * 2 : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(vp, 0, (int)af_value_size(n_keys, n_stride, d, sb), 0x00020000);
 #pragma unroll
         for (int i = 0; i < KD; ++i)
-            vf[i] = __builtin_bit_cast(u32x4_a, __builtin_amdgcn_raw_buffer_load_b128(rv, ov + (unsigned)(sb * 64), (unsigned)(i * 32) * (unsigned)n_stride, 0));
+            vf[i] = __builtin_bit_cast(u32x4_a, __builtin_amdgcn_raw_buffer_load_b128(rv, af_value_offset(ov, i, n_stride, sb), 0, 0));
     };
     bf16x8_t qf[2][KS];
 #pragma unroll
@@ -375,7 +374,7 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const int c = ks * 32 + lq * 8;
-            qf[t][ks] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rq, c < d ? (unsigned)((qt * 32 + t * 16 + l16) * C + c) * 2u : OOB, 0, 0));
+            qf[t][ks] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rq, c < d ? (unsigned)((qt * 32 + t * 16 + l16) * C + c) * 2u : AF_OOB, 0, 0));
         }
     __builtin_amdgcn_sched_barrier(0);
     fetch_k(wave);
