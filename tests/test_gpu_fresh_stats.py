@@ -22,7 +22,9 @@ def fb():
     return binding
 
 
-@pytest.mark.parametrize("B,H,W,C,G,tile,tiles", [(1, 8, 8, 96, 24, 4, 1), (2, 24, 40, 96, 6, 4, 9), (2, 64, 72, 64, 64, 8, 3), (3, 16, 16, 160, 5, 2, 64)])
+@pytest.mark.parametrize("B,H,W,C,G,tile,tiles", [(1, 8, 8, 96, 24, 4, 1), (2, 24, 40, 96, 6, 4, 9), (2, 64, 72, 64, 64, 8, 3), (3, 16, 16, 160, 5, 2, 64),
+                                                  # the most groups that the one launch holds, and more: statistics, then activation
+                                                  (1, 8, 16, 512, 256, 4, 5), (2, 16, 16, 576, 288, 4, 9)])
 def test_resnet_block_with_fresh_statistics(fb, B, H, W, C, G, tile, tiles):
     rng = np.random.default_rng(C + G + H)
     P = wl.params_from_shapes(rng, res_shapes("r", C, C, 64), 0.05, DT)

@@ -354,6 +354,29 @@ def test_sd15_96x96_unet_module_by_module(fb, capsys):
     run_module_by_module(fb, uo.sd15_desc(H=96, W=96), 5030, 0.02, 8, 0.1, say)
 
 
+@pytest.mark.parametrize("layers,products", [(2, 32), (3, 44)])
+def test_context_products_of_one_launch_and_more(fb, layers, products):
+    """Keys and values of the context for every transformer block: as many products as one launch holds, and more."""
+    d = uo.tiny_desc(base=64, layers=layers)
+    blocks = [m for m in uo.unet_modules(d) if m["kind"] == "tr"]
+    assert 2 * len(blocks) == products
+    rng = np.random.default_rng(7900 + layers)
+    u = fb.fise_unet_create(d)
+    P = wl.params_from_shapes(rng, uo.param_shapes(d), 0.04, "bf16")
+    ctx = wl.normal(rng, (d["B"], d["n_ctx"], d["ctx_dim"]), 1.0, "bf16")
+    kv = torch.full((fb.fise_unet_ctxkv_bytes(u),), 0x7F, dtype=torch.uint8, device=DEV)
+    fb.fise_unet_context_kv(u, pack_weights(fb, u, P), dev(ctx, "bf16"), kv)
+    host_kv, want = kv.cpu(), uo.context_kv_all(P, d, ctx, "bf16")
+    where = {name: host_kv[off:off + n].view(torch.bfloat16).to(torch.float64).numpy() for name, off, n in fb.fise_unet_tensors(u, 2)}
+    for m in blocks:
+        K, V = want[m["name"]]
+        shape = (d["B"], d["n_ctx"], K.shape[-1])
+        got_v = where[m["name"] + ".ctx_vt"].reshape(d["B"], K.shape[-1], -1)[:, :, :d["n_ctx"]].transpose(0, 2, 1)
+        assert rel_err(where[m["name"] + ".ctx_k"].reshape(shape), K) <= 2e-2, m["name"]
+        assert rel_err(got_v, V) <= 2e-2, m["name"]
+    fb.fise_unet_destroy(u)
+
+
 def test_masked_step_under_graph_capture(fb):
     """The step allocates nothing, clears nothing with a memset node and never synchronises, so a caller can capture
     it into a HIP graph.  Each replay (with eager work and synchronisations of the test in between, and the cache
