@@ -12,6 +12,7 @@
 // those loads.
 #include <algorithm>
 #include <type_traits>
+#include "attention_choice.h"
 #include "attention_keys.h"
 #include "igemm.h"
 #include "profile.h"
@@ -19,8 +20,7 @@
 namespace fise {
 
 constexpr int AT_QW = 32;         // queries per wave
-constexpr int AT_WAVES = 4;
-constexpr int AT_BQ = AT_QW * AT_WAVES;
+static_assert(AT_BQ == 4 * AT_QW, "four waves");
 
 __device__ __forceinline__ void at_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -536,7 +536,7 @@ template <int KD, int DB, bool EXACT>
 static void launch_at(const void* q, const void* K, const void* Vt, int B, int M, int n_keys, int n_stride, int C, int heads,
                       int d, float scale, int splits, void* out, float* part_o, float* part_ml, hipStream_t st) {
     if (splits == 0) {
-        const int nqt = ceil_div(M, 32);
+        const int nqt = ceil_div(M, AF_BQ);
         hipLaunchKernelGGL((attention_few_kernel<KD, EXACT>), dim3((unsigned)(nqt * heads * B)), dim3(64 * AF_WAVES), 0, st, (const bf16_t*)q,
                            (const bf16_t*)K, (const bf16_t*)Vt, B, M, n_keys, n_stride, C, d, scale * 1.4426950408889634f, nqt, heads, fast_div(nqt),
                            fast_div(heads), (bf16_t*)out);
@@ -550,60 +550,6 @@ static void launch_at(const void* q, const void* K, const void* Vt, int B, int M
                        (bf16_t*)out, part_o, part_ml);
 }
 
-// A split pays a second launch for the merge and, with it, ~2 us per million parked elements (rows x channels x splits); it saves
-// key blocks, which cost a workgroup 0.9 us (head dim 40) to 2 us (160).  Below six blocks that never pays (four blocks of
-// 8 x 160 channels: 2 x 32 queries 11.4 us, two splits 10.8; 2 x 192 13.8 against 14.8; head dim 40 6.4 against 7.8).  Six and
-// seven blocks are four less with three splits: that is worth (d - 64) / 24 us without the parked elements (160: 4.1, 128:
-// 2.4, 80: 0.7, 64 and 40: nothing), so the line lies where both are equal (six blocks of 8 x 160 channels: 2 x 32 queries 15.5
-// us unsplit, 11.4 split; 2 x 256 17.9 and 17.5; 2 x 384 18.0 and 19.8).
-static int attention_splits(int B, int M, int n_keys, int C, int heads) {
-    const int wgs = ceil_div(M, AT_BQ) * heads * B;
-    const int nblocks = ceil_div(n_keys, AT_BKV);
-    if (nblocks < 6 || (nblocks < 8 && (long long)B * M * C > (C / heads - 64) * 7000LL)) return 1;
-    int s = ceil_div(640, wgs);
-    s = std::min(s, nblocks / 2);
-    return std::max(1, std::min(s, 32));
-}
-
-// What a launch costs in us, by lines fitted to 500 of them (32 to 4096 queries, 128 to 9216 keys, heads of 40, 80 and 160, cold keys, every
-// split that the scratch allows); d = head dim.  A workgroup spends 0.52 + 0.009 d on each of its key blocks and 0.44 more for every further
-// workgroup on its CU, which holds three of heads up to 64 and two of wider ones; more workgroups than that go round again.  A split costs
-// 3.5 for the merge and 2.6 per million parked elements (rows x channels x splits).
-static double attention_us(int B, int M, int n_keys, int C, int heads, int splits) {
-    const int d = C / heads, resident = d <= 64 ? 3 : 2;
-    const double wgs = (double)ceil_div(M, AT_BQ) * heads * B * splits;
-    const double on_cu = std::min(std::ceil(wgs / 256.0), (double)resident);
-    const int per = ceil_div(ceil_div(n_keys, AT_BKV), splits);
-    return 2.2 + 0.0068 * d + (n_keys % AT_BKV ? 0.47 + 0.0036 * d : 0.0) +
-           per * std::max(1.0, wgs / (256.0 * resident)) * (0.52 + 0.0086 * d + 0.44 * (on_cu - 1.0)) +
-           (splits > 1 ? 3.5 + 2.6e-6 * splits * B * M * C : 0.0);
-}
-
-// Splits of a launch, of the `most` that its scratch holds (2.5 workgroups per CU): as many as pay for what they park.  1.1 % from the best
-// one on average over 90 shapes, 12 % at worst; all of `most` 11 % and 43 %.  2 x 1024 queries and keys of 8 x 80 channels: 5 splits 30.0
-// us, none 22.2; of 8 x 40 5 splits 22.1, two 17.5; 2 x 384 x 1024 keys of 8 x 80 8 splits 21.1, four 17.0; 2 x 4096 x 4096 of 8 x 40 two
-// splits 101, none 95; 2 x 2752 x 9216 stays at two.
-static int attention_launch_splits(int B, int M, int n_keys, int C, int heads, int most) {
-    int best = 1;
-    double us = attention_us(B, M, n_keys, C, heads, 1);
-    for (int s = 2; s <= most; ++s) {
-        const double t = attention_us(B, M, n_keys, C, heads, s);
-        if (t < us) { us = t; best = s; }
-    }
-    return best;
-}
-
-// Which kernel: the one whose time is smaller, 0.6 % from the better one on average over 105 shapes, 14 % at worst.  Few queries: 2.8 + 0.019
-// d us, 0.32 + 0.02 d per 256 keys and round of 256 workgroups, 0.037 d per further round.  2 x 48 queries, 256 keys of 8 x 160 channels
-// 12.0 -> 10.4 us; 2 x 192 x 77 keys of 8 x 80 6.6 -> 5.4; 2 x 384 x 1024 17.0 -> 12.7; 2 x 768 x 4096 of 8 x 40 stays (31 against 36).
-static bool attention_few(int B, int M, int n_keys, int n_stride, int C, int heads, int splits) {
-    const double lim = 1u << 30;                         // 32-bit offsets into a batch element
-    if ((double)n_keys * C >= lim || (double)C * n_stride >= lim || (double)M * C >= lim) return false;
-    const int d = C / heads, few_wgs = ceil_div(M, 32) * heads * B, rounds = ceil_div(few_wgs, 256);
-    const double few = 2.8 + 0.019 * d + rounds * (ceil_div(n_keys, 32) / 8.0) * (0.32 + 0.02 * d) + (rounds - 1) * 0.037 * d;
-    return few < attention_us(B, M, n_keys, C, heads, splits);
-}
-
 size_t attention_workspace_bytes(int B, int M, int n_keys, int C, int heads) {
     const int s = attention_splits(B, M, n_keys, C, heads);
     if (s <= 1) return 0;
@@ -615,10 +561,7 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
     if (M <= 0) return FISE_OK;
     const int d = C / heads;
     const int kd = ceil_div(d, 16);
-    int splits = attention_splits(B, M, n_keys, C, heads);                         // what the scratch is laid out for
-    if (splits > 1 && (!ws || ws_bytes < attention_workspace_bytes(B, M, n_keys, C, heads))) splits = 1;
-    splits = attention_launch_splits(B, M, n_keys, C, heads, splits);
-    if (attention_few(B, M, n_keys, n_stride, C, heads, splits)) splits = 0;       // one launch whatever the key range
+    const int splits = attention_form(B, M, n_keys, n_stride, C, heads, ws && ws_bytes >= attention_workspace_bytes(B, M, n_keys, C, heads));
     float* part_o = (float*)ws;
     float* part_ml = splits > 1 ? (float*)((char*)ws + align256((size_t)splits * B * M * C * sizeof(float))) : nullptr;
     {

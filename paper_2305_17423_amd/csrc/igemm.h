@@ -9,6 +9,7 @@
 // 1280 channels have norm_gemm.hip and arguments of their own.  Internal.
 #pragma once
 #include "common.h"
+#include "gemm_choice.h"
 
 namespace fise {
 
@@ -139,9 +140,6 @@ __device__ __forceinline__ void put_views1(const GnView* view, int nview, int b,
 }
 #endif
 
-// Scratch of the launcher: the parked partial sums of split-K launches, then the arrival counters.
-constexpr int IGEMM_COUNTERS = 4096;     // arrival counters of split output tiles (zeroed once per call, left at zero by every launch)
-constexpr size_t IGEMM_PARTIAL_BYTES = (32u << 20) - IGEMM_COUNTERS * sizeof(int);
 struct IgemmWorkspace { float* partial; size_t partial_bytes; int* counters; mutable bool counters_zeroed; };
 // One of several products of the same rows: weights [N, K], destination and its OUT_ mode.
 struct GemmProduct { const bf16_t* w; int N; bf16_t* out; int mode; };

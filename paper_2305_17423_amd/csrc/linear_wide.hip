@@ -166,17 +166,6 @@ static int launch_lw(const LinearWide& a, hipStream_t st) {
     return FISE_OK;
 }
 
-// Row tiles of 32 of a launch, 0: igemm.hip's tiles.  One tile for each CU at most: 64 rows while that suffices, else 128 (several rounds of them
-// fall behind 64 x 128 tiles, of which a CU holds two: 9216 x 320 x 320 11.7 us there, 12.0 and 14.4 here; 9216 x 640 x 2560 57, 63 and 67).
-// Fewer than 2048 rows belong to wave_gemm.hip, which splits K over more waves.  Before and now, us: 2048 x 320 x 1280 14.0, 8.3; 2048 x 640 x 640
-// 9.9, 6.9; x 2560 23.2, 13.7; 4096 x 320 x 320 8.0, 5.5; 5504 x 320 x 1280 19.0, 13.4; 8192 x 320 x 320 11.2, 8.9; x 1280 20.7, 14.5; 2048 x 1280 x 5120
-// 64, 42.
-static int linear_tile(int rows, int N) {
-    const long long columns = N / 80;
-    if (rows < 2048 || ceil_div(rows, 128) * columns > 256) return 0;
-    return ceil_div(rows, 64) * columns <= 256 ? 2 : 4;
-}
-
 bool linear_wide_takes(const IgemmArgs& a) {
     const long long rows = (long long)a.B * a.Ma, lim = 1ll << 31;
     return a.a_compact && a.ksize == 1 && a.C1 == 0 && a.K == a.C0 && a.K % 64 == 0 && a.N % 80 == 0 && a.K2 == 0 && a.pro == PRO_NONE && a.nsect == 1 && !a.geglu &&

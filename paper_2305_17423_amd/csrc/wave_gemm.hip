@@ -871,44 +871,6 @@ bool wave_gemm_takes(const IgemmArgs& a) {
     return wave_gemm_fits(a) && (a.B * a.Ma < BLOCK_ROWS || !a.a_compact || a.geglu || a.nsect > 1);
 }
 
-// Tile and K split of a launch: the cheapest of the combinations under times measured per part of a launch (us, from time
-// stamps inside the kernel and kernel traces over the shapes of steps and dense builds).
-//  - PRIVATE, a ring per wave, 256 workgroups at once.  `fixed`: start, row positions, first loads, sum over the waves,
-//    epilogue, and the gap to the launch before.  `iter`: four K steps, one per wave (operands at the 71 - 88 GB/s a CU gets with all busy).
-//  - SHARED, 64 x 64 on one ring of 48 KB: every wave multiplies a 16-deep slice of each K step over the whole tile, so a
-//    staged byte is read once, and three workgroups per CU hide each other's start and epilogue, which many tiles of
-//    a short K consist of: `tile` + `iter` per K step of a tile and CU.  5504 x 320 x 2880 36 -> 24 us (64 x 128 tiles of
-//    eight waves that read a staged byte 2.7 times), 1376 x 1920 x 640 23 -> 15, with GEGLU 1376 x 5120 x 640 39 -> 26 us.
-//    Beyond ~96 K steps (`iter_long`) the workgroups of an XCD drift apart and fall out of its L2.
-//  - BLOCK, 64 x 160 on one ring of 112 KB: 1/46 of an operand row per product instead of 1/32, one workgroup per CU and a
-//    long epilogue (ten pieces per thread): 8192 x 320 x 9600 105 (SHARED) -> 64 us, 2048 x 640 x 11520 with 1x1 side product 76
-//    -> 54 us.  Widths of a 320-channel UNet are multiples of 160: no columns to spare.
-// A K split over workgroups adds parking, counting and re-reading the tiles (`park`, `park_s` per split).
-// Held against every tile and split on the 164 ResNet convolutions of a 64 x 64 x 320 / 32 x 32 x 640 / 16 x 16 x 1280 UNet with
-// 32 to 8192 rows and cold weights, the choice is 4 % from the best on average.  It is furthest off at 90 - 180 K steps and ~160 tiles
-// of 64 x 64, where it takes BLOCK in four splits or SHARED in two (2048 x 320 x 8640: 39 us, PRIVATE unsplit 29; 512 x 1280 x 5760:
-// 34 and 27): fewer than 256 workgroups get more per CU than `iter` says, and four parked BLOCK tiles cost more than `park`.
-//  - PATCHES, 3x3 convolutions of stride 1 over square tiles of edge 2, 4 or 8, `iter` per chunk of 64 channels (times `small` at edge 2,
-//    whose patches are four times the tile): the other forms bring a pixel into LDS once per tap, this one brings the tiles' patches
-//    in once, 1/5 (edge 8) to 1/2 (edge 2) of the bytes.  1376 x 640 x 5760: 23.3 -> 18.8 us, 1536 x 320 x 8640 21.7 -> 17.2, 344 x
-//    1280 x 11520 29.5 -> 23.  It loses where few rows leave a launch its fixed cost (64 rows), its set-up being longer.
-// These launches have their own table: fitted to every form and split of 127 convolutions (320 / 640 / 1280 wide, 4 to 18432 rows, tiles
-// of edge 2 to 8, cold weights), where the choice is 0.6 % from the best on average, at worst 9 %, and 10 % faster than without PATCHES.
-//  - WIDE, the same over 64 or 128 rows x 80 columns (conv_patch.hip), edge 4 (64 rows) or 8: fewest bytes per product, one workgroup per CU, for
-// launches that give most CUs one of its tiles.  8192 x 320 x 2880 29 -> 21.5 us, x 8640 67 -> 47; 4096 x 320 x 5760 37 -> 22.7; 2048 x 640 x 5760
-// 35 -> 24.3, x 17280 76 -> 58; not for 2432 x 320 x 2880 (152 tiles: 14 against 12.7) or 4608 x 640 x 5760 (576: 62 against 54).
-enum { PRIVATE = 0, SHARED_RING = 1, BLOCK = 2, PATCHES = 3, WIDE = 4 };
-struct TileShape { int kind, tm, tn; double fixed, tile, iter, iter_long, park, park_s, small; };
-static const TileShape kShapes[] = {
-    {PRIVATE, 1, 1, 4.3, 0.0, 0.39, 0.39, 2.0, 0.15, 1}, {PRIVATE, 1, 2, 4.8, 0.0, 0.56, 0.56, 2.3, 0.3, 1}, {PRIVATE, 2, 2, 5.8, 0.0, 0.92, 0.92, 3.2, 0.6, 1},
-    {SHARED_RING, 2, 2, 5.2, 1.2, 0.235, 0.32, 3.2, 0.6, 1}, {BLOCK, 2, 5, 13.0, 0.0, 0.4, 0.4, 4.0, 1.5, 1}};
-static const TileShape kPatchShapes[] = {
-    {PRIVATE, 1, 1, 4.4, 0.0, 0.25, 0.39, 2.0, 0.15, 1}, {PRIVATE, 1, 2, 4.8, 0.0, 0.56, 0.56, 2.5, 0.3, 1}, {PRIVATE, 2, 2, 5.8, 0.0, 0.92, 0.92, 3.2, 0.6, 1},
-    {SHARED_RING, 2, 2, 5.2, 1.2, 0.25, 0.32, 3.2, 0.6, 1}, {BLOCK, 2, 5, 11.8, 0.0, 0.4, 0.365, 4.0, 1.5, 1},
-    {PATCHES, 1, 1, 4.9, 0.0, 0.52, 0.6, 4.0, 0.15, 1}, {PATCHES, 2, 1, 6.6, 0.0, 0.69, 0.69, 3.1, 0.3, 1.1}, {PATCHES, 2, 2, 7.0, 0.0, 1.05, 1.0, 4.3, 0.6, 1.2},
-    {WIDE, 2, 0, 6.6, 0.0, 1.68, 1.68, 0.0, 0.0, 1}, {WIDE, 4, 0, 8.9, 0.0, 2.5, 2.5, 0.0, 0.0, 1}};
-constexpr double PATCH_SIDE = 0.25;          // a K step of the side product behind the chunks
-
 // 3x3 products over pixels of square tiles whose strips have a patch form, into one map (wider tiles, rectangles, stride 2 and upsampling
 // keep the forms that gather a tap at a time).
 static bool patch_fits(const IgemmArgs& a) {
@@ -916,34 +878,11 @@ static bool patch_fits(const IgemmArgs& a) {
            a.nsect == 1 && a.out_mode[0] == OUT_MAP && !(a.res && a.res_compact);
 }
 
-struct TileChoice { int kind, tm, tn, splits; };
 static TileChoice choose_tile(const IgemmArgs& a, const IgemmWorkspace* ws) {
-    const int rows = a.B * a.Ma, ncols = a.geglu ? 2 * a.N : a.N, nsteps = (a.K + a.K2) / 64;
-    TileChoice c{PRIVATE, 1, 1, 1}; double best = 1e30;
-    const int max_s = ws && ws->counters && ws->partial ? 8 : 1;
-    const bool patches = patch_fits(a);
-    const TileShape* const table = patches ? kPatchShapes : kShapes;
-    for (int i = 0; i < (int)(patches ? sizeof kPatchShapes : sizeof kShapes) / (int)sizeof(TileShape); ++i) {
-        const TileShape& sh = table[i];
-        if (a.geglu && sh.tn == 1) continue;
-        if (sh.kind == BLOCK && (a.a_compact || a.N % 160 || a.nsect > 1 || a.out_mode[0] != OUT_MAP || (a.res && a.res_compact))) continue;
-        if (sh.kind == PATCHES && sh.tm == 1 && a.tile == 2) continue;      // never the cheapest
-        if (sh.kind == WIDE && (a.N % 80 || !(a.tile == 8 || (a.tile == 4 && sh.tm == 2)))) continue;
-        const bool chunks = sh.kind == PATCHES || sh.kind == WIDE;
-        const int gx = ceil_div(rows, 32 * sh.tm), gy = sh.kind == WIDE ? a.N / 80 : ceil_div(ncols, 32 * sh.tn), pieces = chunks ? a.K / 576 : nsteps;
-        for (int s = 1; s <= max_s; ++s) {
-            const int per = ceil_div(pieces, s);
-            if (s > 1 && (sh.kind == WIDE || (sh.kind != PATCHES && per < 4) || ceil_div(pieces, per) != s)) continue;
-            if (s > 1 && ((long long)gx * gy > IGEMM_COUNTERS || (size_t)gx * gy * s * 32 * sh.tm * 32 * sh.tn * 4 > ws->partial_bytes)) break;
-            const long long n = (long long)gx * gy * s;
-            const double iter = (nsteps > 96 ? sh.iter_long : sh.iter) * (a.tile == 2 ? sh.small : 1);
-            double t = s > 1 ? sh.park + sh.park_s * s : 0.0;
-            if (sh.kind == SHARED_RING) t += sh.fixed + std::max(1.0, n / 256.0) * (sh.tile + per * iter);
-            else t += (double)((n + 255) / 256) * (sh.fixed + (sh.kind == PRIVATE ? ceil_div(per, 4) : per) * iter + (chunks ? ceil_div(a.K2 / 64, s) * PATCH_SIDE * (sh.kind == WIDE ? 0.5 * sh.tm : 1.0) : 0.0));
-            if (t < best) { best = t; c = {sh.kind, sh.tm, sh.tn, s}; }
-        }
-    }
-    return c;
+    GemmShape g;
+    g.rows = a.B * a.Ma; g.N = a.N; g.K = a.K; g.K2 = a.K2; g.tile = a.tile; g.geglu = a.geglu; g.patches = patch_fits(a);
+    g.one_map = !a.a_compact && a.nsect == 1 && a.out_mode[0] == OUT_MAP && !(a.res && a.res_compact);
+    return choose_tile(g, ws && ws->counters && ws->partial ? ws->partial_bytes : 0);
 }
 
 // Stages in LDS: as many as it holds (a chunk's weights for a column tile of 32 are 36 KB, its patch 8 - 32 KB).

@@ -1,7 +1,11 @@
-"""Where the key range of the attention is split over workgroups: the scratch size tells, on the host."""
+"""Where the key range of the attention is split over workgroups: the scratch size tells, on the host.  Which kernel and how many splits the cases of the
+GPU tests run: the launcher's own rule (csrc/attention_choice.h), compiled for the host."""
+import subprocess
+
 import pytest
 
-from paper_2305_17423_amd import binding as fb
+import test_gpu_attention as attention
+from paper_2305_17423_amd import binding as fb, build
 
 
 @pytest.mark.parametrize("B,M,n_keys,C,splits", [
@@ -25,3 +29,45 @@ def test_key_splits(B, M, n_keys, C, splits):
         return (n + 255) // 256 * 256
     need = up(splits * B * M * C * 4) + up(splits * B * 8 * M * 8) if splits > 1 else 0
     assert fb.fise_attention_active_workspace_bytes(B, M, n_keys, C, 8) == need
+
+
+PROGRAM = r"""
+#include <cstdio>
+#include "%s/attention_choice.h"
+int main() {
+    int B, M, n, C, heads;
+    while (std::scanf("%%d %%d %%d %%d %%d", &B, &M, &n, &C, &heads) == 5)
+        std::printf("%%d %%d\n", fise::attention_form(B, M, n, (n + 7) / 8 * 8, C, heads, false), fise::attention_form(B, M, n, (n + 7) / 8 * 8, C, heads, true));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def forms(tmp_path_factory):
+    """[(B, queries, keys, channels, heads)] -> [(without scratch, with it)]: 0 the kernel for few queries, else the splits of the one for many"""
+    d = tmp_path_factory.mktemp("attention_forms")
+    (d / "forms.cpp").write_text(PROGRAM % build.CSRC)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(d / "forms"), str(d / "forms.cpp")], check=True)
+
+    def run(shapes):
+        r = subprocess.run([str(d / "forms")], input="\n".join(" ".join(map(str, s)) for s in shapes), check=True, capture_output=True, text=True)
+        return [tuple(map(int, l.split())) for l in r.stdout.splitlines()]
+    return run
+
+
+def test_forms_of_the_gpu_cases(forms):
+    assert forms([c[:5] for c in attention.ACTIVE]) == [c[5:] for c in attention.ACTIVE]
+    few = {c[3] // c[4] for c in attention.ACTIVE if c[6] == 0}
+    assert {-(-d // 16) for d in few} >= {1, 2, 3, 4, 5, 6, 7, 8, 9, 10}, sorted(few)       # every padding of the head dim
+    split = {c[3] // c[4] for c in attention.ACTIVE if c[6] > 1}
+    assert split >= {40, 64, 80, 104, 128, 160}, sorted(split)
+
+
+def test_forms_of_the_partial_key_blocks(forms):
+    """The kernel for many queries has a partial block at every head dim, as the first one and behind a whole one; so has the one for few."""
+    def of(M, heads, d, N):
+        return forms([(2, M, N, d * heads, heads)])[0][0]
+    for d in attention.PARTIAL_D:
+        for N in attention.PARTIAL_N:
+            assert of(520, 8, d, N) == 1, (d, N)
+        assert of(35, 2, d, 65) == 0 and of(35, 2, d, 120) == 0 and (d == 160 or of(35, 2, d, 9) == 0), d

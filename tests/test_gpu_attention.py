@@ -31,17 +31,48 @@ def vt_dev(V, n_stride=None, poison=False):
     return dev(buf, "bf16")
 
 
-@pytest.mark.parametrize("B,M,N,C,heads", [
-    (2, 200, 4096, 320, 8),      # config 3 shape: d = 40, ragged query count
-    (2, 64, 1024, 640, 8),       # d = 80
-    (1, 37, 256, 1280, 8),       # d = 160
-    (2, 33, 77, 320, 8),         # cross-attention: 77 keys (tail block), stride 80
-    (2, 16, 64, 32, 4),          # d = 8
-    (1, 130, 200, 128, 4),       # d = 32, keys not a multiple of 64
-    (1, 1, 8, 64, 4),            # one query, one partial block
-    (2, 16, 448, 1280, 8),       # seven blocks of wide heads, few queries: three key splits, the last of one block
-    (1, 40, 330, 1024, 8),       # d = 128, six blocks in three splits, the last partial
-])
+# B, queries, keys, channels, heads, form without scratch, form with it: 0 the kernel for few queries, else the key splits of the one for many
+# (test_attention_splits.py asks the launcher for both)
+ACTIVE = [
+    (2, 200, 4096, 320, 8, 0, 8),     # config 3 shape: d = 40, ragged query count
+    (2, 64, 1024, 640, 8, 0, 8),      # d = 80
+    (1, 37, 256, 1280, 8, 0, 0),      # d = 160
+    (2, 33, 77, 320, 8, 0, 0),        # cross-attention: 77 keys (tail block), stride 80
+    (2, 16, 64, 32, 4, 1, 1),         # d = 8
+    (1, 130, 200, 128, 4, 0, 0),      # d = 32, keys not a multiple of 64
+    (1, 1, 8, 64, 4, 0, 0),           # one query, one partial block
+    (2, 16, 448, 1280, 8, 0, 0),      # seven blocks of wide heads, few queries: scratch for three key splits, not used
+    (1, 40, 330, 1024, 8, 0, 0),      # d = 128, six blocks, the last partial
+    # few queries (one launch, the keys dealt out among the waves of a workgroup): key counts around 32 and around one and two turns of the
+    # waves, query counts around the tile of 32, every head dim that has a padding of its own
+    (1, 1, 1, 64, 8, 0, 0),           # one query, one key, d = 8
+    (2, 31, 31, 96, 4, 0, 0),         # d = 24
+    (1, 32, 32, 320, 8, 0, 0),        # d = 40
+    (2, 33, 33, 384, 8, 0, 0),        # d = 48
+    (2, 64, 95, 256, 4, 0, 0),        # d = 64
+    (2, 64, 63, 256, 4, 1, 1),
+    (1, 65, 65, 640, 8, 0, 0),        # d = 80
+    (2, 5, 129, 768, 8, 0, 0),        # d = 96, five waves with keys
+    (1, 40, 255, 416, 4, 0, 0),       # d = 104
+    (2, 48, 256, 1024, 8, 0, 0),      # d = 128, one turn of the waves
+    (1, 17, 257, 1088, 8, 0, 0),      # d = 136, a second turn of one key
+    (2, 100, 289, 1280, 8, 0, 0),     # d = 160
+    (2, 300, 520, 320, 8, 0, 0),      # more workgroups than CUs, three turns
+    (4, 12, 77, 1280, 8, 0, 0),
+    # many queries: launches that use fewer key splits than their scratch is laid out for, or none, around the lines where the count changes and
+    # with last splits of one partial key block
+    (2, 700, 800, 640, 8, 1, 1),      # six splits fit, one is used
+    (2, 576, 576, 1280, 8, 1, 1),     # four, one
+    (1, 130, 2000, 256, 4, 0, 16),    # sixteen, all
+    (1, 700, 1500, 416, 4, 0, 6),     # twelve, six
+    (2, 384, 4033, 320, 8, 0, 5),     # fourteen, five, the last block one key
+    (2, 688, 1281, 640, 8, 0, 2),     # seven, between
+    (1, 3, 577, 1280, 8, 0, 5),       # d = 160, ten blocks in fives of two, the last partial
+    (2, 130, 1000, 1024, 8, 0, 8),    # d = 128, a second query tile of two
+]
+
+
+@pytest.mark.parametrize("B,M,N,C,heads", [c[:5] for c in ACTIVE])
 def test_attention_active(fb, B, M, N, C, heads):
     rng = np.random.default_rng(4000 + M + N)
     q = wl.normal(rng, (B, M, C), 1.0, "bf16"); K = wl.normal(rng, (B, N, C), 1.0, "bf16"); V = wl.normal(rng, (B, N, C), 1.0, "bf16")
@@ -60,13 +91,19 @@ def test_attention_active(fb, B, M, N, C, heads):
     assert err2 <= TOL["bf16"], err2
 
 
-@pytest.mark.parametrize("d", [40, 72, 80, 128, 136, 160])
-@pytest.mark.parametrize("N", [1, 9, 31, 33, 56, 57, 63, 64, 65, 120])
-def test_attention_partial_key_blocks(fb, d, N):
-    """The partial block is the first one (up to 63 keys) or a later one; head dims of the constant instantiations (80, 160), of the
-    same tiles with the head dim as an argument (72, 136) and of padded tiles; key padding of V^T holds NaN."""
+# The partial block is the first one (up to 63 keys) or a later one.  35 queries of two heads run on either kernel, by d and N; 520 of eight on that for
+# many queries at every d and N (test_attention_splits.py says so).
+PARTIAL_D, PARTIAL_N, PARTIAL_QUERIES = [40, 72, 80, 128, 136, 160], [1, 9, 31, 33, 56, 57, 63, 64, 65, 120], [(35, 2), (520, 8)]
+
+
+@pytest.mark.parametrize("M,heads", PARTIAL_QUERIES)
+@pytest.mark.parametrize("d", PARTIAL_D)
+@pytest.mark.parametrize("N", PARTIAL_N)
+def test_attention_partial_key_blocks(fb, d, N, M, heads):
+    """Head dims of the constant instantiations (80, 160), of the same tiles with the head dim as an argument (72, 136) and of padded tiles; key padding
+    of V^T holds NaN."""
     rng = np.random.default_rng(4050 + 200 * d + N)
-    B, M, heads = 2, 35, 2
+    B = 2
     C = d * heads
     q = wl.normal(rng, (B, M, C), 1.0, "bf16"); K = wl.normal(rng, (B, N, C), 1.0, "bf16"); V = wl.normal(rng, (B, N, C), 1.0, "bf16")
     want = fo.attention_active(q, K, V, heads)
@@ -96,7 +133,10 @@ def test_attention_closed_forms_on_device(fb):
 
 @pytest.mark.parametrize("C,heads,H,W,t,frac,cross", [(320, 8, 64, 64, 4, 0.05, False), (320, 8, 64, 64, 4, 0.2, False),
                                                        (320, 8, 64, 64, 4, 0.1, True), (640, 8, 32, 32, 4, 0.1, False),
-                                                       (64, 4, 8, 8, 2, 0.3, False)])
+                                                       (64, 4, 8, 8, 2, 0.3, False),
+                                                       # queries, keys and values behind the LayerNorm in one launch, see test_gpu_blocks.TR_CASES
+                                                       (1280, 8, 8, 8, 1, 0.1, False), (640, 8, 12, 12, 3, 0.3, False), (320, 8, 24, 16, 1, 0.05, True),
+                                                       (1280, 8, 16, 16, 4, 0.8, False), (640, 8, 16, 8, 2, 0.3, True), (320, 8, 48, 56, 4, 0.6, False)])
 def test_masked_attention_layer(fb, C, heads, H, W, t, frac, cross):
     rng = np.random.default_rng(4200 + C + int(frac * 100) + cross)
     B, dt, Dc, n_ctx = 2, "bf16", 768, 77

@@ -54,21 +54,32 @@ RES_CASES = [
     # rings of the second activation map: three channels per group, tiles of one pixel; tiles that all touch, at every border
     ("rings-tile-1-96", 2, 12, 8, 96, 0, 96, 1, 0.3, 0.05),
     ("rings-touching-128-to-64", 1, 16, 24, 64, 64, 64, 4, 0.7, 0.05),
+    # both convolutions on tiles of 64 or 128 rows x 80 columns, the second with the shortcut's side product (test_launch_forms.py says so)
+    ("wide8-64-shortcut", 2, 32, 32, 320, 64, 640, 8, 0.9, 0.02),
+    ("wide8-128-shortcut", 2, 64, 64, 64, 128, 320, 8, 0.7, 0.03),
+    ("wide4-64-shortcut", 2, 32, 32, 128, 192, 640, 4, 0.8, 0.02),
 ]
 
 
-@pytest.mark.parametrize("case", RES_CASES, ids=[c[0] for c in RES_CASES])
-def test_resnet_block(fb, case):
+def res_inputs(case):
+    """Weights, old and new input, skip source, embedding and the active tiles of a case."""
     name, B, H, W, C0, C1, Co, t, frac, std = case
     rng = np.random.default_rng(6000 + H + C0 + C1)
-    te, G, n = 1280, 32, "r"
+    te, n = 1280, "r"
     P = wl.params_from_shapes(rng, res_shapes(n, C0 + C1, Co, te), std, DT)
     x_old = wl.normal(rng, (B, H, W, C0), 1.0, DT)
     skip = wl.normal(rng, (B, H, W, C1), 1.0, DT) if C1 else None
     emb = wl.normal(rng, (B, te), 1.0)
     pixm = wl.ellipse_pixels(rng, H, W, frac)
     x_new = wl.perturb(rng, x_old, pixm, 1.0, DT)
-    _, idx = fo.tiles_from_pixels(pixm, t)
+    return P, x_old, x_new, skip, emb, fo.tiles_from_pixels(pixm, t)[1]
+
+
+@pytest.mark.parametrize("case", RES_CASES, ids=[c[0] for c in RES_CASES])
+def test_resnet_block(fb, case):
+    name, B, H, W, C0, C1, Co, t, frac, std = case
+    G, n = 32, "r"
+    P, x_old, x_new, skip, emb, idx = res_inputs(case)
     full = fo.full_index(H, W, t)
     cache = {f"{n}.h1": np.zeros((B, H, W, Co)), f"{n}.out": np.zeros((B, H, W, Co))}
     uo.resnet_block(P, n, [x_old, skip] if C1 else x_old, emb, cache, full, t, DT, G, stats="fresh")     # old generation
@@ -116,19 +127,52 @@ TR_CASES = [
     ("cfg4-32x32-640", 32, 32, 640, 4, 0.10),
     ("cfg4-16x16-1280", 16, 16, 1280, 4, 0.25),
     ("tile1-8x8-1280", 8, 8, 1280, 1, 0.3),
+    # products behind a normalisation as one launch (widths 320, 640 and 1280), where the rows or columns of a workgroup's tile run out: a handful of
+    # rows, tiles whose pixels are no runs of four, batch elements that end inside a row tile, as many rows as make several column tiles a workgroup
+    ("a-few-pixels-320", 8, 8, 320, 1, 0.05),
+    ("tile3-320", 12, 18, 320, 3, 0.3),
+    ("tile2-320", 16, 24, 320, 2, 0.2),
+    ("rows-past-2048-320", 64, 64, 320, 8, 0.5),
+    ("tile5-640", 20, 20, 640, 5, 0.1),
+    ("a-few-pixels-640", 8, 16, 640, 1, 0.05),
+    ("most-of-a-map-640", 32, 32, 640, 4, 0.8),
+    ("tile3-1280", 12, 6, 1280, 3, 0.2),
+    ("a-few-pixels-1280", 8, 8, 1280, 1, 0.05),
+    ("most-of-a-map-1280", 16, 16, 1280, 2, 0.8),
+    # linears of many rows into float rows on tiles of 64 or 128 rows x 80 columns: last row tile partial, full or one batch element's end, both tile
+    # heights and both sides of the rule (test_launch_forms.py holds rows and tile)
+    ("rows-2124-320", 48, 48, 320, 3, 0.4),              # 64 rows, the last tile of 12
+    ("rows-2048-640", 32, 32, 640, 8, 1.0),              # 64 rows, one tile for each CU
+    ("rows-4230-320", 66, 72, 320, 3, 0.4),              # 128 rows, the last tile of 6
+    ("rows-2368-640", 40, 40, 640, 4, 0.6),              # 128 rows
+    ("rows-1854-320", 48, 48, 320, 3, 0.35),             # below the line
+    # widths that the one-launch products do not take: QKV and the gated product on the tiles of wave_gemm.hip (test_launch_forms.py says which)
+    ("general-192", 24, 24, 192, 4, 0.3),
+    ("general-384", 32, 24, 384, 4, 0.7),
 ]
+
+
+def tr_inputs(case, rng):
+    """Weights, old and new input and the active tiles of a case."""
+    name, H, W, C, t, frac = case
+    P = wl.params_from_shapes(rng, tr_shapes("t", C, 768), 0.02, DT)
+    x_old = wl.normal(rng, (2, H, W, C), 1.0, DT)
+    pixm = wl.ellipse_pixels(rng, H, W, frac)
+    x_new = wl.perturb(rng, x_old, pixm, 1.0, DT)
+    return P, x_old, x_new, fo.tiles_from_pixels(pixm, t)[1]
+
+
+def tr_rng(case):
+    name, H, W, C, t, frac = case
+    return np.random.default_rng(7000 + H + C + int(frac * 100))
 
 
 @pytest.mark.parametrize("case", TR_CASES, ids=[c[0] for c in TR_CASES])
 def test_transformer_block(fb, case):
     name, H, W, C, t, frac = case
-    rng = np.random.default_rng(7000 + H + C + int(frac * 100))
     B, G, heads, cd, n_ctx, n = 2, 32, 8, 768, 77, "t"
-    P = wl.params_from_shapes(rng, tr_shapes(n, C, cd), 0.02, DT)
-    x_old = wl.normal(rng, (B, H, W, C), 1.0, DT)
-    pixm = wl.ellipse_pixels(rng, H, W, frac)
-    x_new = wl.perturb(rng, x_old, pixm, 1.0, DT)
-    _, idx = fo.tiles_from_pixels(pixm, t)
+    rng = tr_rng(case)
+    P, x_old, x_new, idx = tr_inputs(case, rng)
     full = fo.full_index(H, W, t)
     ctx_old, ctx_new = wl.normal(rng, (B, n_ctx, cd), 1.0, DT), wl.normal(rng, (B, n_ctx, cd), 1.0, DT)
     Ko, Vo = fo.context_kv(ctx_old, P[f"{n}.a2.k.w"], P[f"{n}.a2.v.w"], DT)

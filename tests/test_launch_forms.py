@@ -1,0 +1,100 @@
+"""Which kernel and tile the cases of the GPU tests run on: the launchers' own rules (csrc/gemm_choice.h), compiled for the host and asked with the
+sizes of those cases.  A case that was made for a form and no longer runs it fails here, and so does a form that has lost its last case."""
+import os
+import subprocess
+
+import pytest
+
+import test_gpu_blocks as blocks
+import test_gpu_wave_gemm as gemm
+from paper_2305_17423_amd import build
+
+PROGRAM = r"""
+#include <cstdio>
+#include "%s/gemm_choice.h"
+using namespace fise;
+int main() {
+    const char* kinds[] = {"private", "ring", "block", "patch", "wide"};
+    int what, v[9];
+    while (std::scanf("%%d %%d %%d", &what, &v[0], &v[1]) == 3) {       // 0 rows N: a linear of many rows
+        if (what == 0) { std::printf("%%d\n", 32 * linear_tile(v[0], v[1])); continue; }
+        for (int i = 2; i < 9; ++i) if (std::scanf("%%d", &v[i]) != 1) return 1;     // 1 rows N K K2 tile geglu patches one_map scratch
+        const GemmShape g{v[0], v[1], v[2], v[3], v[4], v[5] != 0, v[6] != 0, v[7] != 0};
+        const TileChoice c = choose_tile(g, v[8] ? IGEMM_PARTIAL_BYTES : 0);
+        std::printf("%%s %%dx%%d", kinds[c.kind], 32 * c.tm, c.kind == WIDE ? 80 : 32 * c.tn);
+        if (c.splits > 1) std::printf(" in %%d", c.splits);
+        std::puts("");
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("forms")
+    (d / "forms.cpp").write_text(PROGRAM % build.CSRC)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(d / "forms"), str(d / "forms.cpp")], check=True)
+
+    def run(questions):
+        r = subprocess.run([str(d / "forms")], input="\n".join(" ".join(str(int(v)) for v in q) for q in questions), check=True, capture_output=True, text=True)
+        return r.stdout.splitlines()
+    return run
+
+
+def conv(rows, N, K, K2, k, stride, ups, tile):
+    return 1, rows, N, K, K2, tile, 0, k == 3 and stride == 1 and not ups and tile in (2, 4, 8), 1, 1
+
+
+def rows_gemm(rows, N, K, geglu=0, scratch=1):
+    return 1, rows, N, K, 0, 4, geglu, 0, 0, scratch
+
+
+def test_convolution_cases(ask):
+    cases = gemm.CASES
+    got = ask([conv(B * n * t * t, Co, k * k * (C0 + C1), 0, k, stride, ups, t) for _, _, B, _, _, C0, C1, Co, k, stride, ups, t, n, _, _ in cases])
+    assert {c[0]: f for c, f in zip(cases, got)} == {c[0]: c[1] for c in cases}
+    for name, _, _, Ho, Wo, *_, t, n, _, _ in cases:
+        assert n <= (Ho // t) * (Wo // t), name
+    forms = {c[1].split(" in ")[0] + (" in" if " in " in c[1] else "") for c in cases}
+    assert forms == {"private 32x32", "private 32x32 in", "private 32x64", "private 32x64 in", "private 64x64", "private 64x64 in", "ring 64x64", "ring 64x64 in",
+                     "block 64x160", "block 64x160 in", "patch 32x32", "patch 32x32 in", "patch 64x32", "patch 64x32 in", "patch 64x64", "patch 64x64 in",
+                     "wide 64x80", "wide 128x80"}
+    for edge, tiles in ((2, {"64x32", "64x64"}), (4, {"32x32", "64x32", "64x64"}), (8, {"32x32", "64x32", "64x64"})):
+        assert {c[1].split()[1] for c in cases if c[1].startswith("patch") and c[11] == edge} == tiles
+    assert {c[11] for c in cases if c[1] == "wide 64x80"} == {4, 8}
+
+
+def test_product_group_cases(ask):
+    """Without scratch; the last one is no multiple of 64 deep and runs product by product."""
+    got = ask([rows_gemm(B * n, 2 * C, Dc, scratch=0) for B, n, Dc, C in gemm.PRODUCTS[:-1]])
+    assert set(got) == {"private 32x32", "private 32x64", "private 64x64", "ring 64x64"}, got
+    assert gemm.PRODUCTS[-1][2] % 64
+
+
+def test_shortcut_cases(ask):
+    for case in blocks.RES_CASES:
+        name, B, H, W, C0, C1, Co, t, *_ = case
+        if not name.startswith("wide"):
+            continue
+        rows = B * blocks.res_inputs(case)[5].size * t * t
+        want = "wide %sx80" % name.split("-")[1]
+        assert ask([conv(rows, Co, 9 * (C0 + C1), 0, 3, 1, 0, t), conv(rows, Co, 9 * Co, C0 + C1, 3, 1, 0, t)]) == [want, want], name
+
+
+LINEARS = {"rows-2124-320": (2124, 64), "rows-2048-640": (2048, 64), "rows-4230-320": (4230, 128), "rows-2368-640": (2368, 128), "rows-1854-320": (1854, 0)}
+GENERAL = {"general-192": (608, "private 32x64", "private 64x64"), "general-384": (1088, "ring 64x64", "ring 64x64")}      # rows, QKV, gated product
+
+
+def test_transformer_cases(ask):
+    seen = set()
+    for case in blocks.TR_CASES:
+        name, H, W, C, t, _ = case
+        if name not in LINEARS and name not in GENERAL:
+            continue
+        rows = 2 * blocks.tr_inputs(case, blocks.tr_rng(case))[3].size * t * t
+        if name in LINEARS:
+            assert (rows, int(ask([(0, rows, C)])[0])) == LINEARS[name], name
+        else:
+            assert (rows, *ask([rows_gemm(rows, 3 * C, C), rows_gemm(rows, 4 * C, C, geglu=1)])) == GENERAL[name], name
+        seen.add(name)
+    assert seen == set(LINEARS) | set(GENERAL)
