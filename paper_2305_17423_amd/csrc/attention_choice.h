@@ -10,12 +10,11 @@ namespace fise {
 constexpr int AT_BQ = 128, AF_BQ = 32;        // queries of a workgroup of attention_kernel, of attention_few_kernel
 constexpr int at_ceil(int a, int b) { return (a + b - 1) / b; }
 
-// A split pays a second launch for the merge and, with it, ~2 us per million parked elements (rows x channels x splits); it saves
-// key blocks, which cost a workgroup 0.9 us (head dim 40) to 2 us (160).  Below six blocks that never pays (four blocks of
-// 8 x 160 channels: 2 x 32 queries 11.4 us, two splits 10.8; 2 x 192 13.8 against 14.8; head dim 40 6.4 against 7.8).  Six and
-// seven blocks are four less with three splits: that is worth (d - 64) / 24 us without the parked elements (160: 4.1, 128:
-// 2.4, 80: 0.7, 64 and 40: nothing), so the line lies where both are equal (six blocks of 8 x 160 channels: 2 x 32 queries 15.5
-// us unsplit, 11.4 split; 2 x 256 17.9 and 17.5; 2 x 384 18.0 and 19.8).
+// Key splits that the scratch of a launch is laid out for; how many it uses is attention_launch_splits' choice.  A split pays a second launch for the
+// merge and, with it, ~2 us per million parked elements (rows x channels x splits); it saves key blocks, which cost a workgroup 0.9 us (head
+// dim 40) to 2 us (160).  Below six blocks that never pays (four blocks of 8 x 160 channels: 2 x 32 queries 11.4 us, two splits 10.8; 2 x 192 13.8
+// against 14.8; head dim 40 6.4 against 7.8).  Six and seven blocks of wide heads were worth three splits with few queries (2 x 32 queries of 8 x
+// 160 channels 15.5 us unsplit, 11.4 split) before attention_few_kernel, which has those launches now: none uses that scratch, whose size callers see.
 inline int attention_splits(int B, int M, int n_keys, int C, int heads) {
     const int wgs = at_ceil(M, AT_BQ) * heads * B;
     const int nblocks = at_ceil(n_keys, AT_BKV);

@@ -16,22 +16,24 @@ constexpr size_t IGEMM_PARTIAL_BYTES = (32u << 20) - IGEMM_COUNTERS * sizeof(int
 //    epilogue, and the gap to the launch before.  `iter`: four K steps, one per wave (operands at the 71 - 88 GB/s a CU gets with all busy).
 //  - SHARED, 64 x 64 on one ring of 48 KB: every wave multiplies a 16-deep slice of each K step over the whole tile, so a
 //    staged byte is read once, and three workgroups per CU hide each other's start and epilogue, which many tiles of
-//    a short K consist of: `tile` + `iter` per K step of a tile and CU.  5504 x 320 x 2880 36 -> 24 us (64 x 128 tiles of
-//    eight waves that read a staged byte 2.7 times), 1376 x 1920 x 640 23 -> 15, with GEGLU 1376 x 5120 x 640 39 -> 26 us.
-//    Beyond ~96 K steps (`iter_long`) the workgroups of an XCD drift apart and fall out of its L2.
+//    a short K consist of: `tile` + `iter` per K step of a tile and CU.  4096 x 320 x 2880, stride 2, 24 us (PRIVATE 28), 8192 x 640 x 5760,
+//    upsampling, 76 (93); with GEGLU 1376 x 5120 x 640 39 -> 26 us.  Beyond ~96 K steps (`iter_long`) the workgroups of an XCD drift apart and fall
+//    out of its L2.
 //  - BLOCK, 64 x 160 on one ring of 112 KB: 1/46 of an operand row per product instead of 1/32, one workgroup per CU and a
-//    long epilogue (ten pieces per thread): 8192 x 320 x 9600 105 (SHARED) -> 64 us, 2048 x 640 x 11520 with 1x1 side product 76
-//    -> 54 us.  Widths of a 320-channel UNet are multiples of 160: no columns to spare.
+//    long epilogue (ten pieces per thread): 4096 x 640 x 5760, stride 2, 44 us (SHARED 74), 2048 x 1280 x 11520, stride 2, 87 (139).  Widths of a
+//    320-channel UNet are multiples of 160: no columns to spare.
 // A K split over workgroups adds parking, counting and re-reading the tiles (`park`, `park_s` per split).
-// Held against every tile and split on the 164 ResNet convolutions of a 64 x 64 x 320 / 32 x 32 x 640 / 16 x 16 x 1280 UNet with
-// 32 to 8192 rows and cold weights, the choice is 4 % from the best on average.  It is furthest off at 90 - 180 K steps and ~160 tiles
-// of 64 x 64, where it takes BLOCK in four splits or SHARED in two (2048 x 320 x 8640: 39 us, PRIVATE unsplit 29; 512 x 1280 x 5760:
-// 34 and 27): fewer than 256 workgroups get more per CU than `iter` says, and four parked BLOCK tiles cost more than `park`.
+// kShapes serves what the forms below do not take: stride 2, upsampling, tiles of edge 1, 1x1 over maps, compact rows.  Its constants come from time
+// stamps and from 3x3 convolutions that kPatchShapes has now.  Held against every tile and split on 173 launches of its own (widths
+// 320 / 640 / 1280, K up to 23040, 2 to 8192 rows, cold weights), the choice is 4 % from the best on average over stride 2, 7 % over upsampling, 3 % over
+// edge 1 and 1 % over compact rows.  It is furthest off at 90 - 180 K steps and 80 - 320 tiles: 1376 x 1280 x 11520, upsampling, 80 us (BLOCK; SHARED
+// 61); 512 x 1280 x 11520, upsampling, 41 (BLOCK in four; SHARED in three 34); 2048 x 640 x 5760, stride 2, 43 (SHARED; BLOCK in two 32).  The same
+// form is up to 1.7 times as slow under stride 2 as under upsampling (8192 x 640 x 5760 on SHARED 134 us and 76), which one `iter` does not tell apart.
 //  - PATCHES, 3x3 convolutions of stride 1 over square tiles of edge 2, 4 or 8, `iter` per chunk of 64 channels (times `small` at edge 2,
 //    whose patches are four times the tile): the other forms bring a pixel into LDS once per tap, this one brings the tiles' patches
 //    in once, 1/5 (edge 8) to 1/2 (edge 2) of the bytes.  1376 x 640 x 5760: 23.3 -> 18.8 us, 1536 x 320 x 8640 21.7 -> 17.2, 344 x
 //    1280 x 11520 29.5 -> 23.  It loses where few rows leave a launch its fixed cost (64 rows), its set-up being longer.
-// These launches have their own table: fitted to every form and split of 127 convolutions (320 / 640 / 1280 wide, 4 to 18432 rows, tiles
+// These launches have a table of their own, kPatchShapes: fitted to every form and split of 127 convolutions (320 / 640 / 1280 wide, 4 to 18432 rows, tiles
 // of edge 2 to 8, cold weights), where the choice is 0.6 % from the best on average, at worst 9 %, and 10 % faster than without PATCHES.
 //  - WIDE, the same over 64 or 128 rows x 80 columns (conv_patch.hip), edge 4 (64 rows) or 8: fewest bytes per product, one workgroup per CU, for
 // launches that give most CUs one of its tiles.  8192 x 320 x 2880 29 -> 21.5 us, x 8640 67 -> 47; 4096 x 320 x 5760 37 -> 22.7; 2048 x 640 x 5760
