@@ -323,7 +323,6 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
 #if defined(__HIP_DEVICE_COMPILE__)
     using T = FewTile<KD>;
     constexpr int KS = T::KS, PS = T::PS, NK = PS / 2;  // LDS-direct loads of 32 keys
-    typedef unsigned u32x4_a __attribute__((ext_vector_type(4)));
     __shared__ __attribute__((aligned(16))) unsigned char keys[T::LDS];      // later the partial sums [waves][SLICE][64 lanes]
     __shared__ float2 ml[AF_WAVES][32];
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
@@ -341,9 +340,9 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
     const int d = EXACT ? KD * 16 : d_arg;
     const int nsb = (n_keys + AF_BKV - 1) / AF_BKV;
     // queries, keys and channels that do not exist lie outside the descriptors: zeros (attention_keys.h)
-    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(q + (size_t)b * M * C + h * d), 0, (M * C - h * d) * 2, 0x00020000);
-    unsigned char* const kp = reinterpret_cast<unsigned char*>(const_cast<bf16_t*>(K + (size_t)b * n_keys * C));
-    bf16_t* const vp = const_cast<bf16_t*>(Vt + ((size_t)b * C + h * d) * n_stride);
+    const __amdgpu_buffer_rsrc_t rq = buf(q + (size_t)b * M * C + h * d, (unsigned)(M * C - h * d) * 2u);
+    const unsigned char* const kp = reinterpret_cast<const unsigned char*>(K + (size_t)b * n_keys * C);
+    const bf16_t* const vp = Vt + ((size_t)b * C + h * d) * n_stride;
     unsigned char* const my_keys = keys + wave * T::KBYTES;
     unsigned ok[NK];
 #pragma unroll
@@ -355,18 +354,18 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
     // Requests for keys behind the last ones go out through descriptors of size zero, not behind branches: the compiler counts the loads
     // in flight by the path that has fewest, and each wait for values would wait for the next keys too.
     auto fetch_k = [&](int sb) {
-        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(kp + af_key_base(C, h, d, sb), 0, (int)af_key_size(n_keys, C, h, d, sb), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rk = buf(kp + af_key_base(C, h, d, sb), af_key_size(n_keys, C, h, d, sb));
 #pragma unroll
         for (int j = 0; j < NK; ++j)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (__attribute__((address_space(3))) void*)(my_keys + j * 1024), 16, ok[j], 0, 0, 0);
     };
-    u32x4_a vf[KD];
+    u32x4_t vf[KD];
     const unsigned ov = af_value_row(l16, lq * 8, n_stride);
     auto fetch_v = [&](int sb) {
-        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(vp, 0, (int)af_value_size(n_keys, n_stride, d, sb), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = buf(vp, af_value_size(n_keys, n_stride, d, sb));
 #pragma unroll
         for (int i = 0; i < KD; ++i)
-            vf[i] = __builtin_bit_cast(u32x4_a, __builtin_amdgcn_raw_buffer_load_b128(rv, af_value_offset(ov, i, n_stride, sb), 0, 0));
+            vf[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rv, af_value_offset(ov, i, n_stride, sb), 0, 0));
     };
     bf16x8_t qf[2][KS];
 #pragma unroll
@@ -450,7 +449,7 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
         if (partial) {                                   // values of absent keys may be anything
             auto keep = [&](unsigned w, int t) { return left > t + 1 ? w : left > t ? w & 0xffffu : 0u; };
 #pragma unroll
-            for (int i = 0; i < KD; ++i) vf[i] = u32x4_a{keep(vf[i].x, 0), keep(vf[i].y, 2), keep(vf[i].z, 4), keep(vf[i].w, 6)};
+            for (int i = 0; i < KD; ++i) vf[i] = u32x4_t{keep(vf[i].x, 0), keep(vf[i].y, 2), keep(vf[i].z, 4), keep(vf[i].w, 6)};
         }
 #pragma unroll
         for (int i = 0; i < KD; ++i)

@@ -29,6 +29,12 @@ typedef __attribute__((ext_vector_type(8))) short bf16x8_t;   // MFMA operand (8
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
+// plain vectors: the HIP vector classes cannot be assigned through an address-space pointer
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+#define FISE_AS1 __attribute__((address_space(1)))
+#define FISE_AS3 __attribute__((address_space(3)))
+
 typedef __bf16 hw_bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float hw_f32x2_t __attribute__((ext_vector_type(2)));
 
@@ -40,8 +46,19 @@ __device__ __forceinline__ unsigned f2bf2(float lo, float hi) {
     return *reinterpret_cast<unsigned*>(&r);
 }
 __device__ __forceinline__ bf16_t f2bf(float f) { return (bf16_t)(f2bf2(f, 0.f) & 0xffffu); }
+// the two floats of a packed pair
+__device__ __forceinline__ float lo16(unsigned w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi16(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
+__device__ __forceinline__ float gelu_f(float x) { return x * (0.5f * (1.0f + erff(x * 0.70710678118654752f))); }
 // x * sigmoid(x); the reciprocal is the hardware approximation (1 ulp), far below bf16 resolution
 __device__ __forceinline__ float silu_f(float u) { return u * __builtin_amdgcn_rcpf(1.0f + __expf(-u)); }
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// Raw buffer: loads whose byte offset is not below `bytes` return zeros (with bytes 0 all of them), stores there are dropped.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+#endif
 
 template <typename T> struct Elem;
 template <> struct Elem<float> {

@@ -82,8 +82,8 @@ __global__ __launch_bounds__(256) void conv_latent3x3_kernel(const bf16_t* __res
         const int iy = oy + t / 3 - 1, ix = ox + t % 3 - 1;
         uint2 v = make_uint2(0u, 0u);
         if (iy >= 0 && iy < H && ix >= 0 && ix < W) v = *(const uint2*)(x + (((size_t)b * H + iy) * W + ix) * 4);
-        xin[t * 4 + 0] = __uint_as_float(v.x << 16); xin[t * 4 + 1] = __uint_as_float(v.x & 0xffff0000u);
-        xin[t * 4 + 2] = __uint_as_float(v.y << 16); xin[t * 4 + 3] = __uint_as_float(v.y & 0xffff0000u);
+        xin[t * 4 + 0] = lo16(v.x); xin[t * 4 + 1] = hi16(v.x);
+        xin[t * 4 + 2] = lo16(v.y); xin[t * 4 + 3] = hi16(v.y);
     }
     const size_t o = (((size_t)b * H + oy) * W + ox) * Cout + co;
     float acc[4];
@@ -94,10 +94,10 @@ __global__ __launch_bounds__(256) void conv_latent3x3_kernel(const bf16_t* __res
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
             const uint2 v = wr[t];
-            a = fmaf(xin[t * 4 + 0], __uint_as_float(v.x << 16), a);
-            a = fmaf(xin[t * 4 + 1], __uint_as_float(v.x & 0xffff0000u), a);
-            a = fmaf(xin[t * 4 + 2], __uint_as_float(v.y << 16), a);
-            a = fmaf(xin[t * 4 + 3], __uint_as_float(v.y & 0xffff0000u), a);
+            a = fmaf(xin[t * 4 + 0], lo16(v.x), a);
+            a = fmaf(xin[t * 4 + 1], hi16(v.x), a);
+            a = fmaf(xin[t * 4 + 2], lo16(v.y), a);
+            a = fmaf(xin[t * 4 + 3], hi16(v.y), a);
         }
         if (bias) a += Elem<bf16_t>::ld(bias + co + j);
         if (temb) a += temb[b * Cout + co + j];

@@ -15,19 +15,6 @@
 
 namespace fise {
 
-#define FISE_AS1 __attribute__((address_space(1)))
-typedef unsigned u32x2_c __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4_c __attribute__((ext_vector_type(4)));
-typedef float f32x4_c __attribute__((ext_vector_type(4)));
-
-#if defined(__HIP_DEVICE_COMPILE__)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t cp_buf(const void* p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ float cp_lo(unsigned w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float cp_hi(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
-#endif
-
 constexpr int CP_TAP = 80 * 128, CP_STEP = 3 * CP_TAP;       // bytes of a tap's weights, of a kernel row's
 [[maybe_unused]] constexpr int CP_LW = 8;   // loads of a kernel row's weights per wave: 30 of 1 KB, dealt out (two are loads of nothing)
 template <int RT, int T> struct ConvPatch {
@@ -84,7 +71,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const IgemmArgs a) {
     }
     const unsigned wbytes = __umul24((unsigned)a.N, pitch_w);
     auto issue_w = [&](int chunk, int ky) {              // into slot ky; chunks past the last: a descriptor of size zero, no traffic
-        const __amdgpu_buffer_rsrc_t rs = cp_buf(a.w, chunk < nchunk ? wbytes : 0u);
+        const __amdgpu_buffer_rsrc_t rs = buf(a.w, chunk < nchunk ? wbytes : 0u);
         const unsigned soff = (unsigned)chunk * 128u + (unsigned)ky * 3u * tap_bytes;
 #pragma unroll
         for (int l = 0; l < CP_LW; ++l)
@@ -92,7 +79,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const IgemmArgs a) {
     };
     // the row tiles of a column first touch its weights, each a share of the lines (as in wave_gemm.hip)
     if (a.touch) {
-        const __amdgpu_buffer_rsrc_t rs = cp_buf(a.w, wbytes);
+        const __amdgpu_buffer_rsrc_t rs = buf(a.w, wbytes);
         const int lines = a.K >> 6;                      // of 128 bytes in a row
         for (int q = (bx * 4 + wave) * 64 + lane; q < 80 * lines; q += a.gx * 256) {
             const int r = q / lines;
@@ -121,7 +108,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const IgemmArgs a) {
         for (int j = 0; j < PG::SLOTS; ++j) va[j] = (__umul24(px[j], end_p) + (px[j] >> 20 & 0x70u)) | (px[j] & OOB);
     };
     auto issue_patch = [&]() {
-        const __amdgpu_buffer_rsrc_t rs = cp_buf(ptr_p, chunk_p < nchunk ? bytes_p : 0u);
+        const __amdgpu_buffer_rsrc_t rs = buf(ptr_p, chunk_p < nchunk ? bytes_p : 0u);
         unsigned char* const base = lds + (chunk_p & 1) * PG::BYTES + wave * 1024;
 #pragma unroll
         for (int j = 0; j < PG::SLOTS; ++j) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + j * 4096), 16, va[j], soff_p, 0, 0);
@@ -136,11 +123,11 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const IgemmArgs a) {
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- K loop
-    f32x4_c acc[RT][CT];
+    f32x4_t acc[RT][CT];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int c = 0; c < CT; ++c) acc[i][c] = f32x4_c{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < CT; ++c) acc[i][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     unsigned rp[9][RT];                                  // operand A under each tap: place in a patch
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
@@ -230,7 +217,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const IgemmArgs a) {
         };
         auto issue = [&]() {
             const bool live = issued < nside;
-            const __amdgpu_buffer_rsrc_t rs = cp_buf(ptr, live ? bytes : 0u), r2 = cp_buf(a.w2, live ? w2bytes : 0u);
+            const __amdgpu_buffer_rsrc_t rs = buf(ptr, live ? bytes : 0u), r2 = buf(a.w2, live ? w2bytes : 0u);
             unsigned char* const base = lds + slot;
 #pragma unroll
             for (int l = 0; l < RT; ++l) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(base + (wave + 4 * l) * 1024), 16, vs[l], soff, 0, 0);
@@ -264,79 +251,70 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const IgemmArgs a) {
 
     // ---- the K halves: each wave finishes RT / 2 of its row tiles and hands over the others
     constexpr int HT = RT / 2;
-    f32x4_c* const hand = reinterpret_cast<f32x4_c*>(lds);
+    f32x4_t* const hand = reinterpret_cast<f32x4_t*>(lds);
 #pragma unroll
     for (int i = 0; i < HT; ++i)
 #pragma unroll
         for (int c = 0; c < CT; ++c) hand[((wave * HT + i) * CT + c) * 64 + lane] = kh ? acc[i][c] : acc[HT + i][c];
     __syncthreads();
-    u32x2_c e_bias[CT], e_bias2[CT];
+    u32x2_t e_bias[CT], e_bias2[CT];
     {
-        const __amdgpu_buffer_rsrc_t s1 = cp_buf(a.bias, a.bias_bytes), s2 = cp_buf(a.bias2, a.bias2_bytes);
+        const __amdgpu_buffer_rsrc_t s1 = buf(a.bias, a.bias_bytes), s2 = buf(a.bias2, a.bias2_bytes);
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const unsigned col = (unsigned)(by * 80 + c * 16 + lq * 4);
-            e_bias[c] = __builtin_bit_cast(u32x2_c, __builtin_amdgcn_raw_buffer_load_b64(s1, col * 2u, 0, 0));
-            e_bias2[c] = __builtin_bit_cast(u32x2_c, __builtin_amdgcn_raw_buffer_load_b64(s2, col * 2u, 0, 0));
+            e_bias[c] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(s1, col * 2u, 0, 0));
+            e_bias2[c] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(s2, col * 2u, 0, 0));
         }
     }
-    const __amdgpu_buffer_rsrc_t s_temb = cp_buf(a.temb, a.temb_bytes), s_res = cp_buf(a.res, a.res_bytes);
+    const __amdgpu_buffer_rsrc_t s_temb = buf(a.temb, a.temb_bytes), s_res = buf(a.res, a.res_bytes);
 #pragma unroll
     for (int i = 0; i < HT; ++i) {
         const int2 pos = rowpos[(mw * RT + kh * HT + i) * 16 + l16];
         const unsigned no = pos.y < 0 ? OOB : 0u, pix = (unsigned)max(pos.y, 0);
-        u32x2_c e_res[CT]; f32x4_c e_temb[CT]; u32x4_c ss[2][CT][2];
+        u32x2_t e_res[CT]; f32x4_t e_temb[CT]; u32x4_t ss[2][CT][2];
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const unsigned col = (unsigned)(by * 80 + c * 16 + lq * 4);
-            e_res[c] = __builtin_bit_cast(u32x2_c, __builtin_amdgcn_raw_buffer_load_b64(s_res, ((__umul24(pix, (unsigned)a.N) + col) * 2u) | no, 0, 0));
-            e_temb[c] = __builtin_bit_cast(f32x4_c, __builtin_amdgcn_raw_buffer_load_b128(s_temb, (__umul24((unsigned)pos.x, (unsigned)a.temb_stride) + col) * 4u, 0, 0));
+            e_res[c] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(s_res, ((__umul24(pix, (unsigned)a.N) + col) * 2u) | no, 0, 0));
+            e_temb[c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s_temb, (__umul24((unsigned)pos.x, (unsigned)a.temb_stride) + col) * 4u, 0, 0));
         }
 #pragma unroll
         for (int v = 0; v < 2; ++v)
             if (v < a.nview) {
-                const __amdgpu_buffer_rsrc_t s = cp_buf(a.view[v].ss, (unsigned)a.B * a.view[v].dstC * 8u);
+                const __amdgpu_buffer_rsrc_t s = buf(a.view[v].ss, (unsigned)a.B * a.view[v].dstC * 8u);
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
                     const unsigned off = (__umul24((unsigned)pos.x, (unsigned)a.view[v].dstC) + a.view[v].c_off + by * 80 + c * 16 + lq * 4) * 8u;
-                    ss[v][c][0] = __builtin_bit_cast(u32x4_c, __builtin_amdgcn_raw_buffer_load_b128(s, off, 0, 0));
-                    ss[v][c][1] = __builtin_bit_cast(u32x4_c, __builtin_amdgcn_raw_buffer_load_b128(s, off, 16, 0));
+                    ss[v][c][0] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s, off, 0, 0));
+                    ss[v][c][1] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s, off, 16, 0));
                 }
             }
-        u32x2_c y[CT], u[2][CT];
+        u32x2_t y[CT], u[2][CT];
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            const f32x4_c own = kh ? acc[HT + i][c] : acc[i][c], sum = own + hand[(((wave ^ 1) * HT + i) * CT + c) * 64 + lane];
+            const f32x4_t own = kh ? acc[HT + i][c] : acc[i][c], sum = own + hand[(((wave ^ 1) * HT + i) * CT + c) * 64 + lane];
             float x[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                auto part = [q](const u32x2_c& v) { return q & 1 ? cp_hi(v[q >> 1]) : cp_lo(v[q >> 1]); };
+                auto part = [q](const u32x2_t& v) { return q & 1 ? hi16(v[q >> 1]) : lo16(v[q >> 1]); };
                 x[q] = sum[q] + part(e_bias[c]);
                 x[q] += part(e_bias2[c]);
                 x[q] += part(e_res[c]) + e_temb[c][q];
             }
-            y[c] = u32x2_c{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
+            y[c] = u32x2_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
 #pragma unroll
             for (int v = 0; v < 2; ++v)
-                if (v < a.nview) {                       // as put_views4
-                    float z[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        z[q] = fmaf(q & 1 ? cp_hi(y[c][q >> 1]) : cp_lo(y[c][q >> 1]), __uint_as_float(ss[v][c][q >> 1][(q & 1) * 2]), __uint_as_float(ss[v][c][q >> 1][(q & 1) * 2 + 1]));
-                    if (a.view[v].silu)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) z[q] = silu_f(z[q]);
-                    u[v][c] = u32x2_c{f2bf2(z[0], z[1]), f2bf2(z[2], z[3])};
-                }
+                if (v < a.nview) u[v][c] = view_act4(y[c], __builtin_bit_cast(f32x4_t, ss[v][c][0]), __builtin_bit_cast(f32x4_t, ss[v][c][1]), a.view[v].silu);
         }
         if (pos.y >= 0)
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
                 const unsigned col = (unsigned)(by * 80 + c * 16 + lq * 4);
-                *(FISE_AS1 u32x2_c*)(a.out[0] + (size_t)pix * a.N + col) = y[c];
+                *(FISE_AS1 u32x2_t*)(a.out[0] + (size_t)pix * a.N + col) = y[c];
 #pragma unroll
                 for (int v = 0; v < 2; ++v)
-                    if (v < a.nview) *(FISE_AS1 u32x2_c*)(a.view[v].dst + (size_t)pix * a.view[v].dstC + a.view[v].c_off + col) = u[v][c];
+                    if (v < a.nview) *(FISE_AS1 u32x2_t*)(a.view[v].dst + (size_t)pix * a.view[v].dstC + a.view[v].c_off + col) = u[v][c];
             }
     }
 #endif

@@ -85,39 +85,35 @@ __device__ __forceinline__ unsigned fdiv(unsigned n, FastDiv f) { return (__umul
 // In two halves, so that an epilogue can request the table entries of all its items together with its other
 // operands and use them later (loaded where they are used, each item pays a round trip of its own in front of
 // its stores): view_ss_load fetches the four (scale, shift) pairs per view, put_views4 applies them.
-struct ViewSS { float s[2][8]; };
+struct ViewSS { f32x4_t s[2][2]; };      // (scale, shift) of two channels each
 __device__ __forceinline__ void view_ss_load(const GnView* view, int nview, int b, int col, ViewSS& o) {
-    typedef float f32x4v __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        f32x4v s01 = {0.f, 0.f, 0.f, 0.f}, s23 = s01;
+        o.s[i][0] = o.s[i][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         if (i < nview) {
             const GnView w = view[i];
-            auto sp = (const __attribute__((address_space(1))) f32x4v*)(w.ss + (size_t)b * w.dstC + w.c_off + col);
-            s01 = sp[0]; s23 = sp[1];
+            auto sp = (const FISE_AS1 f32x4_t*)(w.ss + (size_t)b * w.dstC + w.c_off + col);
+            o.s[i][0] = sp[0]; o.s[i][1] = sp[1];
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { o.s[i][q] = s01[q]; o.s[i][4 + q] = s23[q]; }
     }
 }
+// One view of four channels, from the values as stored.
+__device__ __forceinline__ u32x2_t view_act4(u32x2_t stored, f32x4_t ss01, f32x4_t ss23, int silu) {
+    float u[4] = {fmaf(lo16(stored[0]), ss01[0], ss01[1]), fmaf(hi16(stored[0]), ss01[2], ss01[3]), fmaf(lo16(stored[1]), ss23[0], ss23[1]),
+                  fmaf(hi16(stored[1]), ss23[2], ss23[3])};
+    if (silu) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = silu_f(u[q]);
+    }
+    return u32x2_t{f2bf2(u[0], u[1]), f2bf2(u[2], u[3])};
+}
 __device__ __forceinline__ void put_views4(const GnView* view, int nview, unsigned pix, int col, const float (&v)[4], const ViewSS& ss) {
-    typedef unsigned u32x2v __attribute__((ext_vector_type(2)));
-    const unsigned p01 = f2bf2(v[0], v[1]), p23 = f2bf2(v[2], v[3]);      // the values as stored
-    const float x[4] = {__uint_as_float(p01 << 16), __uint_as_float(p01 & 0xffff0000u), __uint_as_float(p23 << 16),
-                        __uint_as_float(p23 & 0xffff0000u)};
+    const u32x2_t stored = {f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         if (i >= nview) break;
         const GnView w = view[i];
-        float u[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) u[q] = fmaf(x[q], ss.s[i][2 * q], ss.s[i][2 * q + 1]);
-        if (w.silu) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) u[q] = silu_f(u[q]);
-        }
-        auto dp = (__attribute__((address_space(1))) u32x2v*)(w.dst + (size_t)pix * w.dstC + w.c_off + col);
-        *dp = u32x2v{f2bf2(u[0], u[1]), f2bf2(u[2], u[3])};
+        *(FISE_AS1 u32x2_t*)(w.dst + (size_t)pix * w.dstC + w.c_off + col) = view_act4(stored, ss.s[i][0], ss.s[i][1], w.silu);
     }
 }
 __device__ __forceinline__ void put_views4(const GnView* view, int nview, int b, unsigned pix, int col, const float (&v)[4]) {

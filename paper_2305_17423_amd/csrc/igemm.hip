@@ -48,8 +48,6 @@ template <typename T>
 __device__ __forceinline__ __attribute__((address_space(1))) T* as_global(T* p) {   // a pointer rebuilt from integers has
     return (__attribute__((address_space(1))) T*)p;                                  // to be told it is global again
 }
-typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));       // plain vectors: the HIP vector classes cannot be
-typedef float f32x4v_t __attribute__((ext_vector_type(4)));         // assigned through an address-space pointer
 // Epilogue terms that depend on the output position: time projection and residual for output element
 // (row gm = (b, y, x), column col).
 __device__ __forceinline__ float epilogue_terms(const IgemmArgs& a, int gm, int b, int y, int x, int col) {
@@ -83,13 +81,13 @@ __device__ __forceinline__ void epilogue_terms4(const IgemmArgs& a, int gm, cons
     }
     if (a.res) {
         if (a.res_compact == 2) {
-            const f32x4v_t r = *as_global(reinterpret_cast<const f32x4v_t*>(reinterpret_cast<const float*>(a.res) + (size_t)gm * a.N + col));
+            const f32x4_t r = *as_global(reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(a.res) + (size_t)gm * a.N + col));
             t[0] += r[0]; t[1] += r[1]; t[2] += r[2]; t[3] += r[3];
         } else {
             const size_t row = a.res_compact ? (size_t)gm : (size_t)p.pix;
             const u32x2_t r = *as_global(reinterpret_cast<const u32x2_t*>(a.res + row * a.N + col));
-            t[0] += __uint_as_float(r[0] << 16); t[1] += __uint_as_float(r[0] & 0xffff0000u);
-            t[2] += __uint_as_float(r[1] << 16); t[3] += __uint_as_float(r[1] & 0xffff0000u);
+            t[0] += lo16(r[0]); t[1] += hi16(r[0]);
+            t[2] += lo16(r[1]); t[3] += hi16(r[1]);
         }
     }
 }
@@ -128,8 +126,8 @@ __device__ __forceinline__ void epilogue_put4(const IgemmArgs& a, const OutSel& 
     }
     const u32x2_t packed = {f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
     if (omode == OUT_COMPACT_F32) {
-        const f32x4v_t full = {v[0], v[1], v[2], v[3]};
-        *as_global(reinterpret_cast<f32x4v_t*>(reinterpret_cast<float*>(outp) + (size_t)gm * o.sect_n + scol)) = full;
+        const f32x4_t full = {v[0], v[1], v[2], v[3]};
+        *as_global(reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(outp) + (size_t)gm * o.sect_n + scol)) = full;
         if (a.mirror) *as_global(reinterpret_cast<u32x2_t*>(a.mirror + (size_t)gm * o.sect_n + scol)) = packed;
     } else if (omode == OUT_COMPACT) {
         *as_global(reinterpret_cast<u32x2_t*>(outp + (size_t)gm * o.sect_n + scol)) = packed;
@@ -229,7 +227,7 @@ __device__ __forceinline__ void finish_tile(const IgemmArgs& a, f32x16_t (&acc)[
                     float v = acc[i][j][e] + bias_v;
                     if (a.geglu) {
                         const float g = acc[i][(j + TN / 2) % TN][e] + bias_g;
-                        v = v * (0.5f * g * (1.0f + erff(g * 0.70710678118654752f)));
+                        v *= gelu_f(g);
                     }
                     stage[r * pitch + c] = v;
                 }
@@ -264,9 +262,9 @@ __device__ __forceinline__ void finish_tile(const IgemmArgs& a, f32x16_t (&acc)[
             const bool out_map = osel.mode0 == OUT_MAP, out_f32 = osel.mode0 == OUT_COMPACT_F32;
             const int resk = !a.res ? 0 : (a.res_compact == 2 ? 2 : 1);
             const bool res_map = a.res_compact == 0;
-            u32x2_t rh[MAXI]; f32x4v_t rf[MAXI];
+            u32x2_t rh[MAXI]; f32x4_t rf[MAXI];
 #pragma unroll
-            for (int it = 0; it < MAXI; ++it) { rh[it] = u32x2_t{0u, 0u}; rf[it] = f32x4v_t{0.f, 0.f, 0.f, 0.f}; }
+            for (int it = 0; it < MAXI; ++it) { rh[it] = u32x2_t{0u, 0u}; rf[it] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
             // residual loads without a branch each (a masked-off item reads element 0 instead: valid memory, value
             // unused), so that they all go out back to back
             if (resk == 1) {
@@ -277,7 +275,7 @@ __device__ __forceinline__ void finish_tile(const IgemmArgs& a, f32x16_t (&acc)[
                     rh[it] = src[ok[it] ? e4 : 0];
                 }
             } else if (resk == 2) {
-                auto src = as_global(reinterpret_cast<const f32x4v_t*>(a.res));
+                auto src = as_global(reinterpret_cast<const f32x4_t*>(a.res));
 #pragma unroll
                 for (int it = 0; it < MAXI; ++it) {
                     const size_t e4 = ((size_t)(m0 + rowv[it]) * a.N + colv[it]) >> 2;
@@ -293,18 +291,18 @@ __device__ __forceinline__ void finish_tile(const IgemmArgs& a, f32x16_t (&acc)[
                 for (int it = 0; it < MAXI; ++it) view_ss_load(a.view, a.nview, ok[it] ? pos[it].b : 0, ok[it] ? colv[it] : 0, vss[it]);
             }
             auto dst16 = as_global(reinterpret_cast<u32x2_t*>(out_f32 ? reinterpret_cast<unsigned long long>(a.mirror) : osel.base));
-            auto dst32 = as_global(reinterpret_cast<f32x4v_t*>(osel.base));
+            auto dst32 = as_global(reinterpret_cast<f32x4_t*>(osel.base));
             const bool put16 = !out_f32 || a.mirror != nullptr;
 #pragma unroll
             for (int it = 0; it < MAXI; ++it) {
                 if (!ok[it]) continue;
                 // the residual is added as one term, as everywhere else: value + (0 + residual)
-                const float v0 = sv[it].x + (rf[it][0] + __uint_as_float(rh[it][0] << 16));
-                const float v1 = sv[it].y + (rf[it][1] + __uint_as_float(rh[it][0] & 0xffff0000u));
-                const float v2 = sv[it].z + (rf[it][2] + __uint_as_float(rh[it][1] << 16));
-                const float v3 = sv[it].w + (rf[it][3] + __uint_as_float(rh[it][1] & 0xffff0000u));
+                const float v0 = sv[it].x + (rf[it][0] + lo16(rh[it][0]));
+                const float v1 = sv[it].y + (rf[it][1] + hi16(rh[it][0]));
+                const float v2 = sv[it].z + (rf[it][2] + lo16(rh[it][1]));
+                const float v3 = sv[it].w + (rf[it][3] + hi16(rh[it][1]));
                 const size_t e4 = ((out_map ? (size_t)pos[it].pix : (size_t)(m0 + rowv[it])) * a.N + colv[it]) >> 2;
-                if (out_f32) dst32[e4] = f32x4v_t{v0, v1, v2, v3};
+                if (out_f32) dst32[e4] = f32x4_t{v0, v1, v2, v3};
                 if (put16) dst16[e4] = u32x2_t{f2bf2(v0, v1), f2bf2(v2, v3)};
                 if (out_map && a.nview) {
                     const float vv[4] = {v0, v1, v2, v3};
@@ -366,7 +364,7 @@ __device__ __forceinline__ void finish_tile(const IgemmArgs& a, f32x16_t (&acc)[
                 float v = acc[i][j][e] + bias_v;
                 if (a.geglu) {
                     const float g = acc[i][(j + TN / 2) % TN][e] + bias_g;
-                    v = v * (0.5f * g * (1.0f + erff(g * 0.70710678118654752f)));
+                    v *= gelu_f(g);
                 }
                 v += t[e];
                 const size_t gm = (size_t)(m0 + r);
@@ -574,8 +572,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_kernel(const IgemmArgs a
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float2 s0 = ss[2 * e], s1 = ss[2 * e + 1];
-                    float u0 = __uint_as_float(w4[e] << 16) * s0.x + s0.y;
-                    float u1 = __uint_as_float(w4[e] & 0xffff0000u) * s1.x + s1.y;
+                    float u0 = lo16(w4[e]) * s0.x + s0.y;
+                    float u1 = hi16(w4[e]) * s1.x + s1.y;
                     if (a.pro == PRO_GN_SILU) { u0 = silu_f(u0); u1 = silu_f(u1); }
                     w4[e] = f2bf2(u0, u1);
                 }
@@ -670,7 +668,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN >= 8 ? 4 : 1)) void igem
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
     constexpr int STAGE = (BM + BN) * 128;              // bytes
     constexpr unsigned OOB = 0x80000000u;               // beyond any descriptor (sizes are below 2 GiB)
-    constexpr int SRD_FLAGS = 0x00020000;               // raw buffer, 32-bit data format
 
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
     __shared__ RowInfo rinfo[BM];
@@ -702,13 +699,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN >= 8 ? 4 : 1)) void igem
     // ---- descriptors of the operand arrays
     const unsigned npix_in = a.a_compact ? (unsigned)rows : (unsigned)(a.B * a.Hin * a.Win);
     const unsigned npix_out = (unsigned)(a.B * a.Ho * a.Wo);
-    const __amdgpu_buffer_rsrc_t srd_a0 = __builtin_amdgcn_make_buffer_rsrc((void*)a.a0, 0, (int)(npix_in * a.C0 * 2u), SRD_FLAGS);
-    const __amdgpu_buffer_rsrc_t srd_a1 = __builtin_amdgcn_make_buffer_rsrc((void*)a.a1, 0, (int)(a.a1 ? npix_in * a.C1 * 2u : 0u), SRD_FLAGS);
-    const __amdgpu_buffer_rsrc_t srd_s0 = __builtin_amdgcn_make_buffer_rsrc((void*)a.s0, 0, (int)(a.s0 ? npix_out * a.S0 * 2u : 0u), SRD_FLAGS);
-    const __amdgpu_buffer_rsrc_t srd_s1 = __builtin_amdgcn_make_buffer_rsrc((void*)a.s1, 0, (int)(a.s1 ? npix_out * a.S1 * 2u : 0u), SRD_FLAGS);
+    const __amdgpu_buffer_rsrc_t srd_a0 = buf(a.a0, npix_in * a.C0 * 2u);
+    const __amdgpu_buffer_rsrc_t srd_a1 = buf(a.a1, a.a1 ? npix_in * a.C1 * 2u : 0u);
+    const __amdgpu_buffer_rsrc_t srd_s0 = buf(a.s0, a.s0 ? npix_out * a.S0 * 2u : 0u);
+    const __amdgpu_buffer_rsrc_t srd_s1 = buf(a.s1, a.s1 ? npix_out * a.S1 * 2u : 0u);
     const unsigned wrows = (unsigned)(a.geglu ? 2 * a.N : a.N);
-    const __amdgpu_buffer_rsrc_t srd_w = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, (int)(wrows * (unsigned)a.K * 2u), SRD_FLAGS);
-    const __amdgpu_buffer_rsrc_t srd_w2 = __builtin_amdgcn_make_buffer_rsrc((void*)a.w2, 0, (int)(a.w2 ? wrows * (unsigned)a.K2 * 2u : 0u), SRD_FLAGS);
+    const __amdgpu_buffer_rsrc_t srd_w = buf(a.w, wrows * (unsigned)a.K * 2u);
+    const __amdgpu_buffer_rsrc_t srd_w2 = buf(a.w2, a.w2 ? wrows * (unsigned)a.K2 * 2u : 0u);
 
     // ---- per-thread load slots: slot j of this wave fills tile rows j * RB + wave * 8 .. + 8
     const int lr = lane >> 3;                           // row within the 8
@@ -939,18 +936,16 @@ __global__ __launch_bounds__(256) void igemm_reduce_kernel(const IgemmArgs a) {
     }
     const OutPos pos = out_pos(a, b, y, x);
     if (a.res && a.res_compact == 0) res_raw = *reinterpret_cast<const uint2*>(a.res + (size_t)pos.pix * a.N + col);
-    auto lo = [](unsigned w) { return __uint_as_float(w << 16); };
-    auto hi = [](unsigned w) { return __uint_as_float(w & 0xffff0000u); };
     // same order of additions as the unsplit epilogue: sum, biases, (gate), time projection, residual
-    float r[4] = {v.x + (lo(bias_raw.x) + lo(bias2_raw.x)), v.y + (hi(bias_raw.x) + hi(bias2_raw.x)),
-                  v.z + (lo(bias_raw.y) + lo(bias2_raw.y)), v.w + (hi(bias_raw.y) + hi(bias2_raw.y))};
+    float r[4] = {v.x + (lo16(bias_raw.x) + lo16(bias2_raw.x)), v.y + (hi16(bias_raw.x) + hi16(bias2_raw.x)),
+                  v.z + (lo16(bias_raw.y) + lo16(bias2_raw.y)), v.w + (hi16(bias_raw.y) + hi16(bias2_raw.y))};
     if (GEGLU) {
-        const float gg[4] = {g.x + lo(gate_raw.x), g.y + hi(gate_raw.x), g.z + lo(gate_raw.y), g.w + hi(gate_raw.y)};
+        const float gg[4] = {g.x + lo16(gate_raw.x), g.y + hi16(gate_raw.x), g.z + lo16(gate_raw.y), g.w + hi16(gate_raw.y)};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) r[q] = r[q] * (0.5f * gg[q] * (1.0f + erff(gg[q] * 0.70710678118654752f)));
+        for (int q = 0; q < 4; ++q) r[q] *= gelu_f(gg[q]);
     }
-    const float post[4] = {temb_v.x + (res_v.x + lo(res_raw.x)), temb_v.y + (res_v.y + hi(res_raw.x)),
-                           temb_v.z + (res_v.z + lo(res_raw.y)), temb_v.w + (res_v.w + hi(res_raw.y))};
+    const float post[4] = {temb_v.x + (res_v.x + lo16(res_raw.x)), temb_v.y + (res_v.y + hi16(res_raw.x)),
+                           temb_v.z + (res_v.z + lo16(res_raw.y)), temb_v.w + (res_v.w + hi16(res_raw.y))};
 #pragma unroll
     for (int q = 0; q < 4; ++q) r[q] += post[q];
     epilogue_put4(a, osel, gm, pos, col, r, a.nview ? &vss : nullptr);

@@ -13,12 +13,6 @@
 
 namespace fise {
 
-#define FISE_AS1 __attribute__((address_space(1)))
-#define FISE_AS3 __attribute__((address_space(3)))
-typedef unsigned u32x2_l __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4_l __attribute__((ext_vector_type(4)));
-typedef float f32x4_l __attribute__((ext_vector_type(4)));
-
 struct LinearWide {
     const bf16_t *x, *w, *bias;
     const float* res;
@@ -47,7 +41,6 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(const LinearWide a)
     int u = blockIdx.x;
     if (u < (run << 3)) u = (u & 7) * run + (u >> 3);
     const int bx = (int)fdiv((unsigned)u, a.d_gy), by = u - bx * a.gy, m0 = bx * BM, n0 = by * 80;
-    auto buf = [](const void* p, unsigned bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000); };
 
     // ---- stages: pieces of eight rows of 128 bytes, wave v loads the pieces v, v + 4 ... of x and of w; segments swizzled with (row >> 1) & 7
     const unsigned pitch = (unsigned)a.K * 2u;
@@ -79,17 +72,17 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(const LinearWide a)
     };
     issue();
     // ---- what the epilogue adds, ahead of the other stages
-    u32x2_l e_bias[CT]; f32x4_l e_res[HT][CT];
+    u32x2_t e_bias[CT]; f32x4_t e_res[HT][CT];
     {
         const __amdgpu_buffer_rsrc_t sb = buf(a.bias, a.bias_bytes), sr = buf(a.res, a.res_bytes);
 #pragma unroll
-        for (int c = 0; c < CT; ++c) e_bias[c] = __builtin_bit_cast(u32x2_l, __builtin_amdgcn_raw_buffer_load_b64(sb, (unsigned)(n0 + c * 16 + lq * 4) * 2u, 0, 0));
+        for (int c = 0; c < CT; ++c) e_bias[c] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(sb, (unsigned)(n0 + c * 16 + lq * 4) * 2u, 0, 0));
 #pragma unroll
         for (int i = 0; i < HT; ++i) {
             const int m = m0 + (mw * RT + kh * HT + i) * 16 + l16;
 #pragma unroll
             for (int c = 0; c < CT; ++c)
-                e_res[i][c] = __builtin_bit_cast(f32x4_l, __builtin_amdgcn_raw_buffer_load_b128(sr, m < a.rows ? ((unsigned)m * (unsigned)a.N + (unsigned)(n0 + c * 16 + lq * 4)) * 4u : OOB, 0, 0));
+                e_res[i][c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(sr, m < a.rows ? ((unsigned)m * (unsigned)a.N + (unsigned)(n0 + c * 16 + lq * 4)) * 4u : OOB, 0, 0));
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -97,11 +90,11 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(const LinearWide a)
     for (int s = 1; s < NS - 1; ++s) issue();
     __builtin_amdgcn_sched_barrier(0);
 
-    f32x4_l acc[RT][CT];
+    f32x4_t acc[RT][CT];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int c = 0; c < CT; ++c) acc[i][c] = f32x4_l{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < CT; ++c) acc[i][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const unsigned rd = (unsigned)(l16 * 128 + (((kh * 4 + lq) ^ ((l16 >> 1) & 7)) * 16));      // an operand within 16 rows
     unsigned rs = 0;
 #pragma unroll 1
@@ -125,7 +118,7 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(const LinearWide a)
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
     // ---- the K halves: each wave finishes half of its row tiles and hands over the others
-    f32x4_l* const hand = reinterpret_cast<f32x4_l*>(lds);
+    f32x4_t* const hand = reinterpret_cast<f32x4_t*>(lds);
 #pragma unroll
     for (int i = 0; i < HT; ++i)
 #pragma unroll
@@ -136,16 +129,16 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(const LinearWide a)
         const int m = m0 + (mw * RT + kh * HT + i) * 16 + l16;
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            f32x4_l y = (kh ? acc[HT + i][c] : acc[i][c]) + hand[(((wave ^ 1) * HT + i) * CT + c) * 64 + lane];
+            f32x4_t y = (kh ? acc[HT + i][c] : acc[i][c]) + hand[(((wave ^ 1) * HT + i) * CT + c) * 64 + lane];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                y[q] += __uint_as_float(q & 1 ? e_bias[c][q >> 1] & 0xffff0000u : e_bias[c][q >> 1] << 16);
+                y[q] += q & 1 ? hi16(e_bias[c][q >> 1]) : lo16(e_bias[c][q >> 1]);
                 y[q] += e_res[i][c][q];
             }
             if (m < a.rows) {
                 const size_t o = (size_t)m * a.N + n0 + c * 16 + lq * 4;
-                *(FISE_AS1 f32x4_l*)(a.out + o) = y;
-                if (a.mirror) *(FISE_AS1 u32x2_l*)(a.mirror + o) = u32x2_l{f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
+                *(FISE_AS1 f32x4_t*)(a.out + o) = y;
+                if (a.mirror) *(FISE_AS1 u32x2_t*)(a.mirror + o) = u32x2_t{f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
             }
         }
     }

@@ -79,7 +79,7 @@ __global__ __launch_bounds__(DET_THREADS) void pixel_diff_kernel(const T* __rest
 __device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ float4 load4(const bf16_t* p) {
     const uint2 v = *reinterpret_cast<const uint2*>(p);
-    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+    return make_float4(lo16(v.x), hi16(v.x), lo16(v.y), hi16(v.y));
 }
 
 template <typename T, int C4>

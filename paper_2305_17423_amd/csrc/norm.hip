@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void gn_partial_vec_kernel(const bf16_t* __res
                 const unsigned w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float lo = __uint_as_float(w[j] << 16), hi = __uint_as_float(w[j] & 0xffff0000u);
+                    const float lo = lo16(w[j]), hi = hi16(w[j]);
                     s[2 * j] += lo; q[2 * j] += lo * lo; s[2 * j + 1] += hi; q[2 * j + 1] += hi * hi;
                 }
             }
@@ -199,9 +199,9 @@ __device__ __forceinline__ void act_tile(const ActMap& a, Stat stat, int zi, int
                 float mu, rs;
                 if (a.cpg >= 8) { const bool hi = cc >= edge; mu = hi ? st1.x : st0.x; rs = hi ? st1.y : st0.y; }
                 else { const float2 sg = stat((int)fdiv((unsigned)cc, a.d_cpg)); mu = sg.x; rs = sg.y; }
-                const float xv = q ? __uint_as_float(xw[e] & 0xffff0000u) : __uint_as_float(xw[e] << 16);
-                const float ga = q ? __uint_as_float(gw[e] & 0xffff0000u) : __uint_as_float(gw[e] << 16);
-                const float be = q ? __uint_as_float(bw[e] & 0xffff0000u) : __uint_as_float(bw[e] << 16);
+                const float xv = q ? hi16(xw[e]) : lo16(xw[e]);
+                const float ga = q ? hi16(gw[e]) : lo16(gw[e]);
+                const float be = q ? hi16(bw[e]) : lo16(bw[e]);
                 const float sc = rs * ga;
                 float u = fmaf(xv, sc, fmaf(-mu, sc, be));      // the same two operations as the scale / shift table form
                 if (a.silu) u = silu_f(u);
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256) void small_linear_kernel(const float* __restri
         const unsigned w4[4] = {wv.x, wv.y, wv.z, wv.w};
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float wf = (e & 1) ? __uint_as_float(w4[e >> 1] & 0xffff0000u) : __uint_as_float(w4[e >> 1] << 16);
+            const float wf = (e & 1) ? hi16(w4[e >> 1]) : lo16(w4[e >> 1]);
 #pragma unroll
             for (int b = 0; b < NB; ++b) acc[b] = fmaf(in[(size_t)b * K + k + e], wf, acc[b]);
         }

@@ -22,11 +22,6 @@
 
 namespace fise {
 
-#define FISE_AS1 __attribute__((address_space(1)))
-typedef unsigned u32x2_n __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4_n __attribute__((ext_vector_type(4)));
-typedef float f32x4_n __attribute__((ext_vector_type(4)));
-
 constexpr int NG_WAVES = 8;
 struct NormGemmDev {
     NormGemmArgs a;
@@ -35,12 +30,6 @@ struct NormGemmDev {
 };
 
 #if defined(__HIP_DEVICE_COMPILE__)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t ng_buf(const void* p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ float ng_lo(unsigned w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float ng_gelu(float x) { return x * (0.5f * (1.0f + erff(x * 0.70710678118654752f))); }
-__device__ __forceinline__ float ng_hi(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
 // Sum over aligned groups of 16, 32 or 64 lanes, in every lane of the group (data paths of the vector unit: a shuffle through the LDS costs
 // ~130 cycles a step, and a row's mean and variance are ten to twelve of them in a row).
 template <int CTRL> __device__ __forceinline__ float ng_dpp(float x) {
@@ -91,7 +80,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
 
     // ---- rows: LPR lanes a row, five pieces of four channels each, all rows of the wave requested together
     const int l = lane % LPR;
-    f32x4_n v[P][5];
+    f32x4_t v[P][5];
     const int b_first = (int)fdiv((unsigned)m0, g.d_Ma);
     unsigned rb[P], rm[P], rt[P];
 #pragma unroll
@@ -105,7 +94,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
     if (a.src == NG_ROWS_LN)
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const FISE_AS1 f32x4_n* q = (const FISE_AS1 f32x4_n*)((const float*)a.x + (size_t)(rb[p] * (unsigned)a.Ma + rm[p]) * K) + l;
+            const FISE_AS1 f32x4_t* q = (const FISE_AS1 f32x4_t*)((const float*)a.x + (size_t)(rb[p] * (unsigned)a.Ma + rm[p]) * K) + l;
 #pragma unroll
             for (int j = 0; j < 5; ++j) v[p][j] = q[j * LPR];
         }
@@ -120,16 +109,16 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
     if (a.src != NG_ROWS_LN)
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const FISE_AS1 u32x2_n* q = (const FISE_AS1 u32x2_n*)((const bf16_t*)a.x + ((size_t)rb[p] * (a.Ho * a.Wo) + rm[p]) * K) + l;
+            const FISE_AS1 u32x2_t* q = (const FISE_AS1 u32x2_t*)((const bf16_t*)a.x + ((size_t)rb[p] * (a.Ho * a.Wo) + rm[p]) * K) + l;
 #pragma unroll
-            for (int j = 0; j < 5; ++j) { const u32x2_n u = q[j * LPR]; v[p][j] = f32x4_n{__uint_as_float(u.x), __uint_as_float(u.y), 0.f, 0.f}; }
+            for (int j = 0; j < 5; ++j) { const u32x2_t u = q[j * LPR]; v[p][j] = f32x4_t{__uint_as_float(u.x), __uint_as_float(u.y), 0.f, 0.f}; }
         }
-    u32x2_n gam[5], bet[5];
+    u32x2_t gam[5], bet[5];
     if (a.src == NG_ROWS_LN || a.src == NG_MAP_LN)
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
-            gam[j] = ((const FISE_AS1 u32x2_n*)a.gamma)[j * LPR + l];
-            bet[j] = ((const FISE_AS1 u32x2_n*)a.beta)[j * LPR + l];
+            gam[j] = ((const FISE_AS1 u32x2_t*)a.gamma)[j * LPR + l];
+            bet[j] = ((const FISE_AS1 u32x2_t*)a.beta)[j * LPR + l];
         }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -149,32 +138,32 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
     const unsigned vd0 = (unsigned)(lane >> 3) * (2u * K) + seg, vd1 = (unsigned)(8 + (lane >> 3)) * (2u * K) + (seg ^ 64u);
     unsigned char* const my_ring = wring + __builtin_amdgcn_readfirstlane(wave) * (ND * WST);
     auto load = [&](int u) {                              // the unit's next stage into ring slot u
-        const __amdgpu_buffer_rsrc_t rs = ng_buf(wp, wbytes);
+        const __amdgpu_buffer_rsrc_t rs = buf(wp, wbytes);
 #pragma unroll
         for (int q = 0; q < 2 * CT; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(my_ring + u * WST + q * 1024), 16,
                                                      q & 1 ? vd1 : vd0, wrow + (q < 2 ? 0u : GEGLU ? (unsigned)a.N * (2u * K) : 16u * (2u * K)), 0, 0);
         wrow += 128u;
     };
-    auto load_bias = [&](int t, u32x2_n (&o)[CT]) {
-        const __amdgpu_buffer_rsrc_t rs = ng_buf(a.bias, a.bias && t < t1 ? (unsigned)((GEGLU ? 2 : 1) * a.N) * 2u : 0u);
+    auto load_bias = [&](int t, u32x2_t (&o)[CT]) {
+        const __amdgpu_buffer_rsrc_t rs = buf(a.bias, a.bias && t < t1 ? (unsigned)((GEGLU ? 2 : 1) * a.N) * 2u : 0u);
 #pragma unroll
         for (int c = 0; c < CT; ++c)
-            o[c] = __builtin_bit_cast(u32x2_n, __builtin_amdgcn_raw_buffer_load_b64(rs, (unsigned)(t * OC + lq * 4) * 2u + (c == 0 ? 0u : GEGLU ? 2u * a.N : 32u), 0, 0));
+            o[c] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, (unsigned)(t * OC + lq * 4) * 2u + (c == 0 ? 0u : GEGLU ? 2u * a.N : 32u), 0, 0));
     };
     // Row tiles that share a slice of the weights walk it in step, so each of its lines is cold for all of them at once: they first touch
     // the slice, each a share of its lines (one dword a line, into the ring before it is filled).  512 x 10240 x 1280 38 -> 30.4 us, 96 rows
     // 18.4 -> 16.0; slices under 200 KB or two row tiles lose 0.3 - 1 us.
     if (g.touch) {
         const int col0 = t0 * OC, s = GEGLU ? 0 : (col0 >= a.sect_n) + (col0 >= 2 * a.sect_n), n = GEGLU ? 32 * (t1 - t0) : min(t1 * OC, (s + 1) * a.sect_n) - col0;
-        const __amdgpu_buffer_rsrc_t rs = ng_buf(s == 0 ? a.w[0] : s == 1 ? a.w[1] : a.w[2], (unsigned)((GEGLU ? 2 * a.N : a.sect_n) * (2 * K)));
+        const __amdgpu_buffer_rsrc_t rs = buf(s == 0 ? a.w[0] : s == 1 ? a.w[1] : a.w[2], (unsigned)((GEGLU ? 2 * a.N : a.sect_n) * (2 * K)));
         for (int q = (bx * NW + wave) * 64 + lane; q < n * NK; q += g.gx * NW * 64) {
             const int r = q / NK, row = GEGLU ? (r & 1 ? a.N : 0) + col0 + (r >> 1) : col0 - s * a.sect_n + r;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)my_ring, 4, (unsigned)row * (2u * K) + (unsigned)(q - r * NK) * 128u, 0, 0, 0);
         }
     }
     int t = t0 + (wave >> g.ks);
-    u32x2_n bias[CT], bias_next[CT];
+    u32x2_t bias[CT], bias_next[CT];
     load_bias(t, bias_next);
     set_unit(t);
 #pragma unroll
@@ -197,13 +186,13 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const int r = p * (NW * RPW) + wave * RPW + lane / LPR;
-        f32x4_n x[5];
+        f32x4_t x[5];
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             x[j] = v[p][j];
             if (a.src != NG_ROWS_LN) {
                 const unsigned w0 = __float_as_uint(v[p][j].x), w1 = __float_as_uint(v[p][j].y);
-                x[j] = f32x4_n{ng_lo(w0), ng_hi(w0), ng_lo(w1), ng_hi(w1)};
+                x[j] = f32x4_t{lo16(w0), hi16(w0), lo16(w1), hi16(w1)};
             }
         }
         if (a.src == NG_MAP_GN) {
@@ -220,23 +209,23 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
             float q = 0.f;
 #pragma unroll
             for (int j = 0; j < 5; ++j) {
-                const f32x4_n d = x[j] - mu;
+                const f32x4_t d = x[j] - mu;
                 q += (d.x * d.x + d.y * d.y) + (d.z * d.z + d.w * d.w);
             }
             const float rs = rsqrtf(ng_sum<LPR>(q) / K + a.eps);
 #pragma unroll
             for (int j = 0; j < 5; ++j) {
-                x[j].x = (x[j].x - mu) * rs * ng_lo(gam[j].x) + ng_lo(bet[j].x);
-                x[j].y = (x[j].y - mu) * rs * ng_hi(gam[j].x) + ng_hi(bet[j].x);
-                x[j].z = (x[j].z - mu) * rs * ng_lo(gam[j].y) + ng_lo(bet[j].y);
-                x[j].w = (x[j].w - mu) * rs * ng_hi(gam[j].y) + ng_hi(bet[j].y);
+                x[j].x = (x[j].x - mu) * rs * lo16(gam[j].x) + lo16(bet[j].x);
+                x[j].y = (x[j].y - mu) * rs * hi16(gam[j].x) + hi16(bet[j].x);
+                x[j].z = (x[j].z - mu) * rs * lo16(gam[j].y) + lo16(bet[j].y);
+                x[j].w = (x[j].w - mu) * rs * hi16(gam[j].y) + hi16(bet[j].y);
             }
         }
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             const int c4 = j * LPR + l, seg = c4 >> 1;   // piece of four channels, 16-byte segment
-            *reinterpret_cast<u32x2_n*>(lds + r * PITCH + (seg >> 3) * 128 + ((seg & 7) ^ ((r >> 1) & 7)) * 16 + (c4 & 1) * 8) =
-                u32x2_n{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
+            *reinterpret_cast<u32x2_t*>(lds + r * PITCH + (seg >> 3) * 128 + ((seg & 7) ^ ((r >> 1) & 7)) * 16 + (c4 & 1) * 8) =
+                u32x2_t{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
         }
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // not the loads of the weights
@@ -245,11 +234,11 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
     const unsigned rd0 = (unsigned)(l16 * PITCH + ((lq ^ ((l16 >> 1) & 7)) * 16)), rd1 = rd0 ^ 64u, rw = (unsigned)(l16 * 128) + ((lq ^ ((l16 >> 1) & 7)) * 16);     // operand of channels 0 - 31 / 32 - 63 of a stage
     auto column_tile = [&](auto tokens) {
         constexpr bool TOKENS = decltype(tokens)::value;
-        f32x4_n acc[RT][CT];
+        f32x4_t acc[RT][CT];
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) acc[i][c] = f32x4_n{0.f, 0.f, 0.f, 0.f};
+            for (int c = 0; c < CT; ++c) acc[i][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < CT; ++c) bias[c] = bias_next[c];
         load_bias(t + step, bias_next);
@@ -304,7 +293,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
         const int scol = col - sect * a.sect_n;
         run();
         if (g.ks) {                                       // the parts' sums meet in the place of the rows; the first part's wave goes on
-            f32x4_n* const sums = reinterpret_cast<f32x4_n*>(lds);
+            f32x4_t* const sums = reinterpret_cast<f32x4_t*>(lds);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             if (part)
@@ -322,15 +311,15 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
         }
         place();
         if constexpr (GEGLU) {
-            const float bv[4] = {ng_lo(bias[0].x), ng_hi(bias[0].x), ng_lo(bias[0].y), ng_hi(bias[0].y)};
-            const float bg[4] = {ng_lo(bias[1].x), ng_hi(bias[1].x), ng_lo(bias[1].y), ng_hi(bias[1].y)};
+            const float bv[4] = {lo16(bias[0].x), hi16(bias[0].x), lo16(bias[0].y), hi16(bias[0].y)};
+            const float bg[4] = {lo16(bias[1].x), hi16(bias[1].x), lo16(bias[1].y), hi16(bias[1].y)};
 #pragma unroll
             for (int i = 0; i < RT; ++i) {
                 const int gm = m0 + i * 16 + e16;
                 float y[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) y[q] = (acc[i][0][q] + bv[q]) * ng_gelu(acc[i][CT - 1][q] + bg[q]);
-                if (gm < rows) *(FISE_AS1 u32x2_n*)(out + (size_t)gm * a.N + col + eq * 4) = u32x2_n{f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
+                for (int q = 0; q < 4; ++q) y[q] = (acc[i][0][q] + bv[q]) * gelu_f(acc[i][CT - 1][q] + bg[q]);
+                if (gm < rows) *(FISE_AS1 u32x2_t*)(out + (size_t)gm * a.N + col + eq * 4) = u32x2_t{f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
             }
         } else if constexpr (TOKENS) {
             const size_t HW = (size_t)a.Ho * a.Wo;
@@ -343,7 +332,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
                     if (g.trans4) {                       // four tokens in a row
                         const int2 pos = rowpos[r];
                         if (m0 + r < rows)
-                            *(FISE_AS1 u32x2_n*)(out + ((size_t)pos.x * a.sect_n + n) * HW + pos.y) = u32x2_n{f2bf2(acc[i][c][0], acc[i][c][1]), f2bf2(acc[i][c][2], acc[i][c][3])};
+                            *(FISE_AS1 u32x2_t*)(out + ((size_t)pos.x * a.sect_n + n) * HW + pos.y) = u32x2_t{f2bf2(acc[i][c][0], acc[i][c][1]), f2bf2(acc[i][c][2], acc[i][c][3])};
                     } else {
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
@@ -362,10 +351,10 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
                 if (m0 + r >= rows) continue;
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
-                    const f32x4_n y = acc[i][c] + f32x4_n{ng_lo(bias[c].x), ng_hi(bias[c].x), ng_lo(bias[c].y), ng_hi(bias[c].y)};
+                    const f32x4_t y = acc[i][c] + f32x4_t{lo16(bias[c].x), hi16(bias[c].x), lo16(bias[c].y), hi16(bias[c].y)};
                     const size_t off = row * a.sect_n + scol + c * 16 + eq * 4;
-                    if (mode == OUT_COMPACT_F32) *(FISE_AS1 f32x4_n*)(reinterpret_cast<float*>(out) + off) = y;
-                    else *(FISE_AS1 u32x2_n*)(out + off) = u32x2_n{f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
+                    if (mode == OUT_COMPACT_F32) *(FISE_AS1 f32x4_t*)(reinterpret_cast<float*>(out) + off) = y;
+                    else *(FISE_AS1 u32x2_t*)(out + off) = u32x2_t{f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
                 }
             }
         }

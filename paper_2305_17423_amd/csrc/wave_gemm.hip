@@ -29,11 +29,6 @@
 
 namespace fise {
 
-#define FISE_AS1 __attribute__((address_space(1)))
-typedef unsigned u32x2_w __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4_w __attribute__((ext_vector_type(4)));
-typedef float f32x4_w __attribute__((ext_vector_type(4)));
-
 enum { A_ROWS = 0, A_MAP = 1 };         // compact rows / pixels of maps (taps, two sources, side product)
 
 // ---- PATCH form (3x3, stride 1, square tiles of edge 2, 4 or 8): the pixels of a tile and their ring are brought into LDS once for 64
@@ -58,16 +53,6 @@ constexpr int patch_flight0(int AHEAD, int NPB, int LB, int SLOTS) {
     const int a0 = 3 - 3 * NPB, a = a0 >= -AHEAD ? LB + patch_loads(a0 + 1, 0, LB, SLOTS) : patch_loads(-AHEAD, 0, LB, SLOTS);
     return patch_min(patch_loads(1 - AHEAD, 0, LB, SLOTS), a);
 }
-
-#if defined(__HIP_DEVICE_COMPILE__)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ float lo16(unsigned w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float hi16(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
-
-__device__ __forceinline__ float gelu_f(float x) { return x * (0.5f * (1.0f + erff(x * 0.70710678118654752f))); }
-#endif
 
 // SHARED: one ring for the workgroup instead of one per wave, see the launcher.
 // What the products of a group differ in.
@@ -263,7 +248,7 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
     }
     };
     constexpr bool AHEAD = ITEMS <= 2;                  // more pieces per thread: placed and fetched after the K loop, all together
-    u32x2_w e_bias[IPG], e_bias2[IPG], e_gate[IPG]; u32x4_w e_temb[IPG], e_res[IPG], e_ss[IPG][2][2];
+    u32x2_t e_bias[IPG], e_bias2[IPG], e_gate[IPG]; u32x4_t e_temb[IPG], e_res[IPG], e_ss[IPG][2][2];
     auto fetch_operands = [&](int grp) {                       // an absent operand has a descriptor of size zero: no branches, no waits
         const __amdgpu_buffer_rsrc_t s_bias = buf(a.bias, a.bias_bytes), s_bias2 = buf(a.bias2, a.bias2_bytes),
                                      s_temb = buf(a.temb, a.temb_bytes), s_res = buf(a.res, a.res_bytes);
@@ -271,16 +256,16 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
 #pragma unroll
         for (int it = 0; it < IPG; ++it) {
             const unsigned no = e_ok[grp * IPG + it] && !trans ? 0u : OOB, col = (unsigned)(col0 + e_c[grp * IPG + it]);
-            e_bias[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, (col * 2u) | no, 0, 0));
+            e_bias[it] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(s_bias, (col * 2u) | no, 0, 0));
             if constexpr (GEGLU) {
-                e_gate[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias, ((col + pr.N) * 2u) | no, 0, 0));
+                e_gate[it] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(s_bias, ((col + pr.N) * 2u) | no, 0, 0));
             } else {
                 const unsigned r = __umul24(res_compact ? (unsigned)(m0 + e_r[grp * IPG + it]) : e_pix[grp * IPG + it], (unsigned)pr.N) + col;
-                if constexpr (CONV) e_res[it].xy = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_res, (r << 1) | no, 0, 0));
-                else e_res[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_res, (r << res_shift) | no, 0, 0));
+                if constexpr (CONV) e_res[it].xy = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(s_res, (r << 1) | no, 0, 0));
+                else e_res[it] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s_res, (r << res_shift) | no, 0, 0));
                 if constexpr (AM == A_MAP) {
-                    e_bias2[it] = __builtin_bit_cast(u32x2_w, __builtin_amdgcn_raw_buffer_load_b64(s_bias2, (col * 2u) | no, 0, 0));
-                    e_temb[it] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_temb, ((__umul24((unsigned)e_b[grp * IPG + it], (unsigned)a.temb_stride) + col) * 4u) | no, 0, 0));
+                    e_bias2[it] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(s_bias2, (col * 2u) | no, 0, 0));
+                    e_temb[it] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s_temb, ((__umul24((unsigned)e_b[grp * IPG + it], (unsigned)a.temb_stride) + col) * 4u) | no, 0, 0));
                 }
             }
         }
@@ -293,8 +278,8 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
                     for (int it = 0; it < IPG; ++it) {
                         const unsigned no = e_ok[grp * IPG + it] && !trans ? 0u : OOB;
                         const unsigned off = ((__umul24((unsigned)e_b[grp * IPG + it], (unsigned)a.view[v].dstC) + a.view[v].c_off + col0 + e_c[grp * IPG + it]) * 8u) | no;
-                        e_ss[it][v][0] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s, off, 0, 0));
-                        e_ss[it][v][1] = __builtin_bit_cast(u32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s, off, 16, 0));
+                        e_ss[it][v][0] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s, off, 0, 0));
+                        e_ss[it][v][1] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s, off, 16, 0));
                     }
                 }
     };
@@ -596,9 +581,9 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
     __syncthreads();
     if constexpr (!AHEAD) { place_items(); fetch_operands(0); }
     float* const part = reinterpret_cast<float*>(ring);
-    f32x4_w v[ITEMS], g[ITEMS];
+    f32x4_t v[ITEMS], g[ITEMS];
 #pragma unroll
-    for (int it = 0; it < ITEMS; ++it) v[it] = g[it] = f32x4_w{0.f, 0.f, 0.f, 0.f};
+    for (int it = 0; it < ITEMS; ++it) v[it] = g[it] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int grp = 0; grp < GROUPS; ++grp) {
         if (grp) __syncthreads();
@@ -609,8 +594,8 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const f32x16_t& c = acc[grp * (TM / GROUPS) + i][j];
-                    *reinterpret_cast<f32x4_w*>(&part[(wave * GROWS + i * 32 + (lane & 31)) * PITCH + j * 32 + q * 8 + (lane >> 5) * 4]) =
-                        f32x4_w{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+                    *reinterpret_cast<f32x4_t*>(&part[(wave * GROWS + i * 32 + (lane & 31)) * PITCH + j * 32 + q * 8 + (lane >> 5) * 4]) =
+                        f32x4_t{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
                 }
         __syncthreads();
         if (trans) {
@@ -619,7 +604,7 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
                     const float* p = &part[(w * GROWS + e_r[it] - grp * GROWS) * PITCH + e_c[it]];
-                    v[it] += f32x4_w{p[0], p[PITCH], p[2 * PITCH], p[3 * PITCH]};
+                    v[it] += f32x4_t{p[0], p[PITCH], p[2 * PITCH], p[3 * PITCH]};
                 }
         } else {
 #pragma unroll
@@ -627,8 +612,8 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
                     const float* p = &part[(w * GROWS + e_r[it] - grp * GROWS) * PITCH + e_c[it]];
-                    v[it] += *reinterpret_cast<const f32x4_w*>(p);
-                    if (GEGLU) g[it] += *reinterpret_cast<const f32x4_w*>(p + OW);
+                    v[it] += *reinterpret_cast<const f32x4_t*>(p);
+                    if (GEGLU) g[it] += *reinterpret_cast<const f32x4_t*>(p + OW);
                 }
         }
     }
@@ -640,8 +625,8 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) {
             const unsigned off = (base + bz) * SLOT + (unsigned)(it * NT + tid) * 16u;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_w, v[it]), s_part, off, 0, 17);
-            if (GEGLU) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_w, g[it]), s_part, off + BM * OW * 4, 0, 17);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v[it]), s_part, off, 0, 17);
+            if (GEGLU) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, g[it]), s_part, off + BM * OW * 4, 0, 17);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
@@ -654,14 +639,14 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
         __syncthreads();
         if (*flag != a.splits - 1) return;
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it) v[it] = g[it] = f32x4_w{0.f, 0.f, 0.f, 0.f};
+        for (int it = 0; it < ITEMS; ++it) v[it] = g[it] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
         for (int z = 0; z < a.splits; ++z) {            // split order, whoever is last
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
                 const unsigned off = (base + z) * SLOT + (unsigned)(it * NT + tid) * 16u;
-                v[it] += __builtin_bit_cast(f32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_part, off, 0, 17));
-                if (GEGLU) g[it] += __builtin_bit_cast(f32x4_w, __builtin_amdgcn_raw_buffer_load_b128(s_part, off + BM * OW * 4, 0, 17));
+                v[it] += __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s_part, off, 0, 17));
+                if (GEGLU) g[it] += __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s_part, off + BM * OW * 4, 0, 17));
             }
         }
     }
@@ -674,45 +659,34 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
         // stores the loads would wait for them.
 #pragma unroll
         for (int grp = 0; grp < GROUPS; ++grp) {
-            u32x2_w y[IPG], yv[IPG][2];
+            u32x2_t y[IPG], yv[IPG][2];
 #pragma unroll
             for (int it = 0; it < IPG; ++it) {
-                const f32x4_w sum = v[grp * IPG + it];
+                const f32x4_t sum = v[grp * IPG + it];
                 float x[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    auto part = [q](const u32x2_w& w) { return q & 1 ? hi16(w[q >> 1]) : lo16(w[q >> 1]); };
-                    const float res = part(u32x2_w{e_res[it][0], e_res[it][1]});
+                    auto part = [q](const u32x2_t& w) { return q & 1 ? hi16(w[q >> 1]) : lo16(w[q >> 1]); };
+                    const float res = part(u32x2_t{e_res[it][0], e_res[it][1]});
                     x[q] = sum[q] + part(e_bias[it]);
                     x[q] += part(e_bias2[it]);
                     x[q] += res + __uint_as_float(e_temb[it][q]);
                 }
-                y[it] = u32x2_w{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
+                y[it] = u32x2_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
-                    if (i < a.nview) {                  // as put_views4
-                        float u[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const u32x4_w& ss = e_ss[it][i][q >> 1];
-                            u[q] = fmaf(q & 1 ? hi16(y[it][q >> 1]) : lo16(y[it][q >> 1]), __uint_as_float(ss[(q & 1) * 2]), __uint_as_float(ss[(q & 1) * 2 + 1]));
-                        }
-                        if (a.view[i].silu) {
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) u[q] = silu_f(u[q]);
-                        }
-                        yv[it][i] = u32x2_w{f2bf2(u[0], u[1]), f2bf2(u[2], u[3])};
-                    }
+                    if (i < a.nview)
+                        yv[it][i] = view_act4(y[it], __builtin_bit_cast(f32x4_t, e_ss[it][i][0]), __builtin_bit_cast(f32x4_t, e_ss[it][i][1]), a.view[i].silu);
             }
             if (grp + 1 < GROUPS) fetch_operands(grp + 1);
 #pragma unroll
             for (int it = 0; it < IPG; ++it) {
                 const int e = grp * IPG + it;
                 if (!e_ok[e]) continue;
-                *(FISE_AS1 u32x2_w*)(outp + (size_t)e_pix[e] * pr.N + col0 + e_c[e]) = y[it];
+                *(FISE_AS1 u32x2_t*)(outp + (size_t)e_pix[e] * pr.N + col0 + e_c[e]) = y[it];
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
-                    if (i < a.nview) *(FISE_AS1 u32x2_w*)(a.view[i].dst + (size_t)e_pix[e] * a.view[i].dstC + a.view[i].c_off + col0 + e_c[e]) = yv[it][i];
+                    if (i < a.nview) *(FISE_AS1 u32x2_t*)(a.view[i].dst + (size_t)e_pix[e] * a.view[i].dstC + a.view[i].c_off + col0 + e_c[e]) = yv[it][i];
             }
         }
         return;
@@ -723,7 +697,7 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
         for (int it = 0; it < ITEMS; ++it) {
             if (!e_ok[it]) continue;
             FISE_AS1 bf16_t* q = (FISE_AS1 bf16_t*)(outp + ((size_t)e_b[it] * pr.sect_n + scol0 + e_c[it]) * HW + (e_pix[it] - (unsigned)e_b[it] * HW));
-            *(FISE_AS1 u32x2_w*)q = u32x2_w{f2bf2(v[it][0], v[it][1]), f2bf2(v[it][2], v[it][3])};
+            *(FISE_AS1 u32x2_t*)q = u32x2_t{f2bf2(v[it][0], v[it][1]), f2bf2(v[it][2], v[it][3])};
         }
         return;
     }
@@ -736,11 +710,11 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
             x[0] *= gelu_f(g[it][0] + lo16(e_gate[gi][0])); x[1] *= gelu_f(g[it][1] + hi16(e_gate[gi][0]));
             x[2] *= gelu_f(g[it][2] + lo16(e_gate[gi][1])); x[3] *= gelu_f(g[it][3] + hi16(e_gate[gi][1]));
         } else {
-            const u32x4_w w = e_res[gi];
-            f32x4_w r = a.res_compact == 2 ? __builtin_bit_cast(f32x4_w, w) : f32x4_w{lo16(w[0]), hi16(w[0]), lo16(w[1]), hi16(w[1])};
+            const u32x4_t w = e_res[gi];
+            f32x4_t r = a.res_compact == 2 ? __builtin_bit_cast(f32x4_t, w) : f32x4_t{lo16(w[0]), hi16(w[0]), lo16(w[1]), hi16(w[1])};
             if constexpr (AM == A_MAP) {
                 x[0] += lo16(e_bias2[gi][0]); x[1] += hi16(e_bias2[gi][0]); x[2] += lo16(e_bias2[gi][1]); x[3] += hi16(e_bias2[gi][1]);
-                r += __builtin_bit_cast(f32x4_w, e_temb[gi]);
+                r += __builtin_bit_cast(f32x4_t, e_temb[gi]);
             }
             x[0] += r[0]; x[1] += r[1]; x[2] += r[2]; x[3] += r[3];
         }
@@ -754,20 +728,18 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
             for (int t = 0; t < 4; ++t) q[t * HW] = f2bf(x[t]);
             continue;
         }
-        const u32x2_w packed = {f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
+        const u32x2_t packed = {f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
         if (omode == OUT_COMPACT_F32) {
-            if (outp) *(FISE_AS1 f32x4_w*)(reinterpret_cast<float*>(outp) + gm * pr.sect_n + scol) = f32x4_w{x[0], x[1], x[2], x[3]};
-            if (a.mirror) *(FISE_AS1 u32x2_w*)(a.mirror + gm * pr.sect_n + scol) = packed;
+            if (outp) *(FISE_AS1 f32x4_t*)(reinterpret_cast<float*>(outp) + gm * pr.sect_n + scol) = f32x4_t{x[0], x[1], x[2], x[3]};
+            if (a.mirror) *(FISE_AS1 u32x2_t*)(a.mirror + gm * pr.sect_n + scol) = packed;
         } else if (omode == OUT_COMPACT) {
-            *(FISE_AS1 u32x2_w*)(outp + gm * pr.sect_n + scol) = packed;
+            *(FISE_AS1 u32x2_t*)(outp + gm * pr.sect_n + scol) = packed;
         } else {
-            *(FISE_AS1 u32x2_w*)(outp + (size_t)e_pix[it] * pr.sect_n + scol) = packed;
+            *(FISE_AS1 u32x2_t*)(outp + (size_t)e_pix[it] * pr.sect_n + scol) = packed;
             if (!GEGLU && a.nview) {
                 ViewSS ss;
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) { ss.s[i][q] = __uint_as_float(e_ss[gi][i][0][q]); ss.s[i][4 + q] = __uint_as_float(e_ss[gi][i][1][q]); }
+                for (int i = 0; i < 2; ++i) { ss.s[i][0] = __builtin_bit_cast(f32x4_t, e_ss[gi][i][0]); ss.s[i][1] = __builtin_bit_cast(f32x4_t, e_ss[gi][i][1]); }
                 put_views4(a.view, a.nview, e_pix[it], scol, x, ss);
             }
         }
