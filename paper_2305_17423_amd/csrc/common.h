@@ -54,7 +54,8 @@ __device__ __forceinline__ float gelu_f(float x) { return x * (0.5f * (1.0f + er
 __device__ __forceinline__ float silu_f(float u) { return u * __builtin_amdgcn_rcpf(1.0f + __expf(-u)); }
 
 #if defined(__HIP_DEVICE_COMPILE__)
-// Raw buffer: loads whose byte offset is not below `bytes` return zeros (with bytes 0 all of them), stores there are dropped.
+// Raw buffer: loads whose lane offset is not below `bytes` return zeros (with bytes 0 all of them), stores there are dropped.  Scalar offsets are
+// for steps inside what the lane offset has shown to exist: that they take part in this comparison is relied on nowhere.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }

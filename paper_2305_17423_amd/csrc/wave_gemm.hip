@@ -54,9 +54,10 @@ constexpr int patch_flight0(int AHEAD, int NPB, int LB, int SLOTS) {
     return patch_min(patch_loads(1 - AHEAD, 0, LB, SLOTS), a);
 }
 
-// SHARED: one ring for the workgroup instead of one per wave, see the launcher.
 // What the products of a group differ in.
 struct Product { const bf16_t* w; int N, sect_n; bf16_t* out0; int mode0; };
+
+// SHARED: one ring for the workgroup instead of one per wave; which form a launch takes is gemm_choice.h's rule.
 
 template <int TM, int TN, int NW, int NST, int AM, bool GEGLU, bool SHARED, int PATCH = 0, int NPB = 0>
 __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product& pr, const int bx, const int by, const int bz) {
