@@ -106,11 +106,11 @@ def summarize_trace(d, out):
             dur = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
             e[0] += 1; e[1] += dur; e[2] = min(e[2], dur); e[3] = max(e[3], dur)
     ns = len(steady)
-    total = sum(v[1] for v in agg.values()) / ns
+    total, n_lib = sum(v[1] for v in agg.values()) / ns, round(sum(v[0] for v in agg.values()) / ns)
     lines = ["# Masked UNet step (SD-1.5 shapes, batch 2, 64x64 latent, 10 % blob = 12 of 64 tiles): per-kernel times", "",
              "Command (on the MI355X box, from the repository root, after `cd /tmp && export TMPDIR=/tmp`):", "", "```", TRACE_CMD.format(d=os.path.normpath(d)), "```", "",
-             f"Steady state: {ns} consecutive masked steps of `run_kernel_trace.csv`, {n_launch} launches per step "
-             f"(mask detection + UNet step), summed kernel durations {total / 1e3:.3f} ms per step, start-to-start "
+             f"Steady state: {ns} consecutive masked steps of `run_kernel_trace.csv`, {n_lib} library launches per step "
+             f"(mask detection + UNet step; {n_launch - n_lib} torch launches of the sampler update between two steps are left out), summed kernel durations {total / 1e3:.3f} ms per step, start-to-start "
              f"{span / ns / 1e3:.3f} ms per step under the profiler.", "",
              "| kernel | launches/step | average us | min us | max us | ms/step | % of step |", "|---|---:|---:|---:|---:|---:|---:|"]
     for k, v in sorted(agg.items(), key=lambda kv: -kv[1][1]):
