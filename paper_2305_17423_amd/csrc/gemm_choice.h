@@ -1,5 +1,5 @@
-// Which tile and K split a launch of wave_gemm.hip takes, and which row tile one of linear_wide.hip: plain C++, so that a host program can ask for
-// the form of any size.  Internal.
+// Which tile and K split a launch of wave_gemm.hip takes, which row tile one of linear_wide.hip, which tile and column units one of norm_gemm.hip: plain C++,
+// so that a host program can ask for the form of any size.  Internal.
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -93,6 +93,57 @@ inline int linear_tile(int rows, int N) {
     const long long columns = N / 80;
     if (rows < 2048 || (rows + 127) / 128 * columns > 256) return 0;
     return (rows + 63) / 64 * columns <= 256 ? 2 : 4;
+}
+
+// ---- norm_gemm.hip
+constexpr int NG_WAVES = 8, NG_LDS_MAX = 160 * 1024;
+
+// Logarithm of the waves that share a unit: all there are, where their sums find room in the place of the rows (320 channels of 32 columns: not).  1280 channels,
+// 24 rows: one product 8.1 -> 7.0 us, queries, keys and values 10.1 -> 8.5; 640 channels 384 rows 7.5 -> 7.2.
+inline int waves_per_unit(int KM, int CT, int per) {
+    int ks = 0;
+    if (CT * 512 <= 640 * KM + (KM == 1 ? 0 : 128))
+        while ((per << (ks + 1)) <= NG_WAVES && (2 << ks) <= 5 * KM) ++ks;
+    return ks;
+}
+
+// Rows (16 rt) and columns (16 ct) of a workgroup's tile per width, stages of the weights in LDS.
+#define FISE_NORM_TILES(T) /* K, GEGLU, rt, ct, stages */                                                                        \
+    T(320, 1, 4, 2, 2) T(320, 1, 2, 2, 3) T(640, 1, 4, 2, 2) T(640, 1, 2, 2, 3) T(1280, 1, 2, 2, 2) T(1280, 1, 1, 2, 3)           \
+    T(320, 0, 4, 2, 3) T(320, 0, 2, 1, 4) T(640, 0, 2, 2, 3) T(640, 0, 2, 1, 4) T(1280, 0, 2, 2, 2) T(1280, 0, 2, 1, 4) T(1280, 0, 1, 1, 4)
+struct NormTile { int K, geglu, rt, ct, nd; };
+#define FISE_NORM_TILE(K, GEGLU, RT, CT, ND) {K, GEGLU, RT, CT, ND},
+inline constexpr NormTile kNormTiles[] = {FISE_NORM_TILES(FISE_NORM_TILE)};
+#undef FISE_NORM_TILE
+
+struct NormShape { int B, Ma, K, N; bool geglu, gn; };     // gn: a GroupNorm's (scale, shift) table in LDS
+struct NormChoice { int tile, per; };                      // in kNormTiles (-1: none), column units of a workgroup
+// The row tile and column units per workgroup of a launch: the cheapest under times (us) fitted to 800 combinations of tile and split over the
+// products of 320 / 640 / 1280 channels with 16 to 8192 rows and cold weights, where the choice is 0.6 % from the best on average, at worst
+// 10 %.  One workgroup runs per CU; a round of 256 pays for its rows (16 rows of 320 channels 0.66), for the LDS traffic of its units
+// (2 RT + 4 CT KB a wave and stage of 64 channels) and for the stages a wave goes through; what all workgroups read of the weights comes on top.
+inline NormChoice choose_norm_tile(const NormShape& a) {
+    constexpr int kPer[] = {1, 2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 40, 64, 80};
+    auto up = [](int n, int d) { return (n + d - 1) / d; };
+    const int rows = a.B * a.Ma, NK = a.K / 64, KM = a.K / 320;
+    NormChoice c{-1, 1}; double best = 1e30;
+    for (int i = 0; i < (int)(sizeof kNormTiles / sizeof(NormTile)); ++i) {
+        const NormTile& t = kNormTiles[i];
+        if (t.K != a.K || t.geglu != (int)a.geglu) continue;
+        // the table holds two batch elements, and the smallest row tile is 32 (16 at 1280 channels)
+        if (a.gn && a.B > 1 && a.Ma < 16 * t.rt) continue;
+        if (a.gn && 16 * t.rt * (640 * KM + 136) + NG_WAVES * t.nd * t.ct * 2048 + 2 * a.K * 8 > NG_LDS_MAX) continue;
+        const int units = a.N / (a.geglu ? 16 : 16 * t.ct), gx = up(rows, 16 * t.rt);
+        for (const int per : kPer) {
+            if (per > units) break;
+            const long long wgs = (long long)gx * up(units, per);
+            const int ks = waves_per_unit(KM, t.ct, per), stages = ks ? (NK + (1 << ks) - 1) >> ks : up(per, NG_WAVES) * NK;
+            const double us = 1.8 + (double)((wgs + 255) / 256) * (2.0 + 0.66 * t.rt * KM + 0.0031 * per * NK * (2 * t.rt + 4 * t.ct) + 0.026 * stages + (ks ? 0.26 : 0.0)) +
+                              0.024e-3 * wgs * per * NK * t.ct + 0.12 * NK * (t.ct - 1) / (1 << ks);
+            if (us < best) { best = us; c = {i, per}; }
+        }
+    }
+    return c;
 }
 
 }  // namespace fise

@@ -22,7 +22,6 @@
 
 namespace fise {
 
-constexpr int NG_WAVES = 8;
 struct NormGemmDev {
     NormGemmArgs a;
     int gx, per, units, t_tokens, trans4, pixels, touch, ks;
@@ -380,16 +379,6 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
 template <int KM, int RT, int CT, int ND> constexpr int ng_lds(bool table) {
     return 16 * RT * (ng_pitch<KM>() + 8) + NG_WAVES * ND * CT * 2048 + (table ? 2 * 320 * KM * 8 : 0);
 }
-constexpr int NG_LDS_MAX = 160 * 1024;
-
-// Logarithm of the waves that share a unit: all there are, where their sums find room in the place of the rows (320 channels of 32 columns: not).  1280 channels,
-// 24 rows: one product 8.1 -> 7.0 us, queries, keys and values 10.1 -> 8.5; 640 channels 384 rows 7.5 -> 7.2.
-static int waves_per_unit(int KM, int CT, int per) {
-    int ks = 0;
-    if (CT * 512 <= 640 * KM + (KM == 1 ? 0 : 128))
-        while ((per << (ks + 1)) <= NG_WAVES && (2 << ks) <= 5 * KM) ++ks;
-    return ks;
-}
 
 template <int KM, int RT, int CT, int ND, bool GEGLU>
 static int launch_cfg(NormGemmDev g, int per, hipStream_t st) {
@@ -416,44 +405,9 @@ static int launch_cfg(NormGemmDev g, int per, hipStream_t st) {
     return FISE_OK;
 }
 
-// Rows and columns of a workgroup's tile per width, with the launch function of that instantiation.
-struct NormTile { int K, geglu, rt, ct, nd; int (*launch)(NormGemmDev, int, hipStream_t); };
-static const NormTile kTiles[] = {
-    {320, 1, 4, 2, 2, launch_cfg<1, 4, 2, 2, true>},   {320, 1, 2, 2, 3, launch_cfg<1, 2, 2, 3, true>},
-    {640, 1, 4, 2, 2, launch_cfg<2, 4, 2, 2, true>},   {640, 1, 2, 2, 3, launch_cfg<2, 2, 2, 3, true>},
-    {1280, 1, 2, 2, 2, launch_cfg<4, 2, 2, 2, true>},  {1280, 1, 1, 2, 3, launch_cfg<4, 1, 2, 3, true>},
-    {320, 0, 4, 2, 3, launch_cfg<1, 4, 2, 3, false>},  {320, 0, 2, 1, 4, launch_cfg<1, 2, 1, 4, false>},
-    {640, 0, 2, 2, 3, launch_cfg<2, 2, 2, 3, false>},  {640, 0, 2, 1, 4, launch_cfg<2, 2, 1, 4, false>},
-    {1280, 0, 2, 2, 2, launch_cfg<4, 2, 2, 2, false>}, {1280, 0, 2, 1, 4, launch_cfg<4, 2, 1, 4, false>},
-    {1280, 0, 1, 1, 4, launch_cfg<4, 1, 1, 4, false>}};
-
-// A GroupNorm's table holds two batch elements, and the smallest row tile is 32 (16 at 1280 channels).
-static bool table_fits(const NormGemmArgs& a, int rt) { return a.src != NG_MAP_GN || a.B == 1 || a.Ma >= 16 * rt; }
-
-// The row tile and column units per workgroup of a launch: the cheapest under times (us) fitted to 800 combinations of tile and split over the
-// products of 320 / 640 / 1280 channels with 16 to 8192 rows and cold weights, where the choice is 0.6 % from the best on average, at worst
-// 10 %.  One workgroup runs per CU; a round of 256 pays for its rows (16 rows of 320 channels 0.66), for the LDS traffic of its units
-// (2 RT + 4 CT KB a wave and stage of 64 channels) and for the stages a wave goes through; what all workgroups read of the weights comes on top.
-struct NormChoice { const NormTile* tile; int per; };
-static NormChoice choose(const NormGemmArgs& a) {
-    static const short kPer[] = {1, 2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 40, 64, 80};
-    const int rows = a.B * a.Ma, NK = a.K / 64, KM = a.K / 320;
-    NormChoice c{nullptr, 1}; double best = 1e30;
-    for (const NormTile& t : kTiles) {
-        if (t.K != a.K || t.geglu != (a.geglu != 0) || !table_fits(a, t.rt)) continue;
-        if (a.src == NG_MAP_GN && 16 * t.rt * (640 * KM + 136) + NG_WAVES * t.nd * t.ct * 2048 + 2 * a.K * 8 > NG_LDS_MAX) continue;
-        const int units = a.N / (a.geglu ? 16 : 16 * t.ct), gx = ceil_div(rows, 16 * t.rt);
-        for (const int per : kPer) {
-            if (per > units) break;
-            const long long wgs = (long long)gx * ceil_div(units, per);
-            const int ks = waves_per_unit(KM, t.ct, per), stages = ks ? (NK + (1 << ks) - 1) >> ks : ceil_div(per, NG_WAVES) * NK;
-            const double us = 1.8 + (double)((wgs + 255) / 256) * (2.0 + 0.66 * t.rt * KM + 0.0031 * per * NK * (2 * t.rt + 4 * t.ct) + 0.026 * stages + (ks ? 0.26 : 0.0)) +
-                              0.024e-3 * wgs * per * NK * t.ct + 0.12 * NK * (t.ct - 1) / (1 << ks);
-            if (us < best) { best = us; c = {&t, per}; }
-        }
-    }
-    return c;
-}
+#define FISE_NORM_LAUNCH(K, GEGLU, RT, CT, ND) launch_cfg<K / 320, RT, CT, ND, GEGLU != 0>,
+static int (*const kNormLaunch[])(NormGemmDev, int, hipStream_t) = {FISE_NORM_TILES(FISE_NORM_LAUNCH)};
+#undef FISE_NORM_LAUNCH
 
 bool norm_gemm_takes(int src, int K, int B, int Ma, int H, int W) {
     if ((K != 320 && K != 640 && K != 1280) || Ma < 1) return false;
@@ -473,9 +427,9 @@ int launch_norm_gemm(const NormGemmArgs& a, hipStream_t st) {
     g.trans4 = a.Ma % 4 == 0 && (a.tile_idx ? a.tile % 4 == 0 && a.Wo % 4 == 0 : a.Ho * a.Wo % 4 == 0);
     g.d_Ma = fast_div(a.Ma); g.d_tt = fast_div(a.tile * a.tile); g.d_tile = fast_div(a.tile); g.d_tiles_w = fast_div(a.tiles_w);
     g.d_cpg = fast_div(a.src == NG_MAP_GN ? a.K / a.G : 1);
-    const NormChoice c = choose(a);
-    if (!c.tile) return fail(FISE_ERR_SHAPE, "norm gemm: no tile");
-    return c.tile->launch(g, c.per, st);
+    const NormChoice c = choose_norm_tile({a.B, a.Ma, a.K, a.N, a.geglu != 0, a.src == NG_MAP_GN});
+    if (c.tile < 0) return fail(FISE_ERR_SHAPE, "norm gemm: no tile");
+    return kNormLaunch[c.tile](g, c.per, st);
 }
 
 }  // namespace fise

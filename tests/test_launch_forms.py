@@ -18,6 +18,14 @@ int main() {
     int what, v[9];
     while (std::scanf("%%d %%d %%d", &what, &v[0], &v[1]) == 3) {       // 0 rows N: a linear of many rows
         if (what == 0) { std::printf("%%d\n", 32 * linear_tile(v[0], v[1])); continue; }
+        if (what == 2) {                                 // 2 B rows K N geglu gn: a product behind a normalisation, rows of a batch element
+            for (int i = 2; i < 6; ++i) if (std::scanf("%%d", &v[i]) != 1) return 1;
+            const NormChoice c = choose_norm_tile({v[0], v[1], v[2], v[3], v[4] != 0, v[5] != 0});
+            if (c.tile < 0) { std::puts("none"); continue; }
+            const NormTile& t = kNormTiles[c.tile];
+            std::printf("%%d%%s %%dx%%d%%s\n", t.K, t.geglu ? " gated" : "", 16 * t.rt, 16 * t.ct, waves_per_unit(v[2] / 320, t.ct, c.per) ? " in parts" : "");
+            continue;
+        }
         for (int i = 2; i < 9; ++i) if (std::scanf("%%d", &v[i]) != 1) return 1;     // 1 rows N K K2 tile geglu patches one_map scratch
         const GemmShape g{v[0], v[1], v[2], v[3], v[4], v[5] != 0, v[6] != 0, v[7] != 0};
         const TileChoice c = choose_tile(g, v[8] ? IGEMM_PARTIAL_BYTES : 0);
@@ -98,3 +106,20 @@ def test_transformer_cases(ask):
             assert (rows, *ask([rows_gemm(rows, 3 * C, C), rows_gemm(rows, 4 * C, C, geglu=1)])) == GENERAL[name], name
         seen.add(name)
     assert seen == set(LINEARS) | set(GENERAL)
+
+
+def norm_products(B, Ma, C):
+    """1x1 in, query product, queries + keys + values, gated product of a block."""
+    first = [(2, B, Ma, C, C, 0, 1)] if B == 1 or Ma >= (16 if C == 1280 else 32) else []      # fewer rows: another kernel
+    return first + [(2, B, Ma, C, C, 0, 0), (2, B, Ma, C, 3 * C, 0, 0), (2, B, Ma, C, 4 * C, 1, 0)]
+
+
+def test_products_behind_a_normalisation(ask):
+    """Every tile, with K dealt out among the waves and without, that any number of rows reaches is one that a transformer block of the GPU tests runs."""
+    rows = sorted({int(1.02 ** i) for i in range(462)})                                        # 1 to 9200
+    reached = set(ask([q for C in (320, 640, 1280) for B in (1, 2, 4) for Ma in rows for q in norm_products(B, Ma, C)]))
+    tested = set()
+    for case in blocks.TR_CASES:
+        if case[3] in (320, 640, 1280):
+            tested |= set(ask(norm_products(2, blocks.tr_inputs(case, blocks.tr_rng(case))[3].size * case[4] ** 2, case[3])))
+    assert len(reached) >= 19 and tested == reached, (reached - tested, tested - reached)
