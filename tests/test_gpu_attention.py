@@ -63,6 +63,8 @@ ACTIVE = [
     # with last splits of one partial key block
     (2, 700, 800, 640, 8, 1, 1),      # six splits fit, one is used
     (2, 576, 576, 1280, 8, 1, 1),     # four, one
+    (2, 600, 120, 256, 8, 1, 1),      # d = 32
+    (2, 520, 120, 768, 8, 1, 1),      # d = 96
     (1, 130, 2000, 256, 4, 0, 16),    # sixteen, all
     (1, 700, 1500, 416, 4, 0, 6),     # twelve, six
     (2, 384, 4033, 320, 8, 0, 5),     # fourteen, five, the last block one key

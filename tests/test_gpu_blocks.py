@@ -149,6 +149,7 @@ TR_CASES = [
     # widths that the one-launch products do not take: QKV and the gated product on the tiles of wave_gemm.hip (test_launch_forms.py says which)
     ("general-192", 24, 24, 192, 4, 0.3),
     ("general-384", 32, 24, 384, 4, 0.7),
+    ("general-416-few-rows", 8, 8, 416, 1, 0.1),         # 32-channel pieces: the staged kernel of igemm.hip, the gated product with split K
 ]
 
 
@@ -170,7 +171,7 @@ def tr_rng(case):
 @pytest.mark.parametrize("case", TR_CASES, ids=[c[0] for c in TR_CASES])
 def test_transformer_block(fb, case):
     name, H, W, C, t, frac = case
-    B, G, heads, cd, n_ctx, n = 2, 32, 8, 768, 77, "t"
+    B, G, heads, cd, n_ctx, n = 2, 32, 8 if C % 64 == 0 else 4, 768, 77, "t"
     rng = tr_rng(case)
     P, x_old, x_new, idx = tr_inputs(case, rng)
     full = fo.full_index(H, W, t)

@@ -72,8 +72,8 @@ CASES = [
     ("scalar-cin4-ds", 2, 16, 16, 4, 0, 32, 3, 2, 0, 4, False, 0, False, False, 0.2),          # generic scalar kernel
     ("deep-1280-few-rows", 2, 8, 8, 1280, 1280, 1280, 3, 1, 0, 1, True, 1, True, False, 0.2),     # long K, split over workgroups
     ("deep-16x16", 2, 16, 16, 1280, 640, 1280, 3, 1, 0, 2, True, 1, True, False, 0.2),
-    # no prologue and channel counts in multiples of 64: the LDS-direct kernel (zero fill at the borders, two
-    # sources, ragged rows and columns, long split K)
+    # no prologue and channel counts in multiples of 64: wave_gemm.hip (zero fill at the borders, two sources, ragged rows and
+    # columns, long split K)
     ("direct-concat-temb-res", 2, 16, 16, 64, 128, 192, 3, 1, 0, 2, False, 0, True, True, 0.2),
     ("direct-c1-concat", 2, 16, 16, 128, 64, 64, 1, 1, 0, 4, False, 0, False, True, 0.15),
     ("direct-ragged-n", 1, 16, 16, 64, 0, 72, 3, 1, 0, 4, False, 0, False, True, 0.1),
@@ -81,6 +81,13 @@ CASES = [
     ("direct-deep", 2, 8, 8, 1280, 1280, 1280, 3, 1, 0, 1, False, 0, True, True, 0.2),
     ("direct-ds-concat", 2, 32, 32, 64, 64, 128, 3, 2, 0, 4, False, 0, False, False, 0.1),
     ("direct-us-256", 2, 8, 8, 256, 0, 256, 3, 1, 1, 4, False, 0, False, False, 0.1),
+    # what wave_gemm.hip does not take, on the tiles of igemm.hip (the active tiles, then all): widths that are no multiple of 4 on 32 x 128, 64 x 64 and
+    # 64 x 128 tiles of the LDS-direct kernel, 32-channel pieces and GroupNorm prologues of 4096 rows on 64 x 128 tiles of the staged one
+    ("odd-width-66", 1, 16, 16, 64, 0, 66, 3, 1, 0, 2, False, 0, True, True, 0.02),
+    ("odd-width-130-dense", 1, 64, 64, 64, 64, 130, 3, 1, 0, 8, False, 0, True, True, 0.1),
+    ("32-channels-dense", 1, 64, 64, 32, 0, 128, 3, 1, 0, 8, False, 0, False, True, 0.1),
+    ("gn-96-channels-dense", 1, 64, 64, 96, 0, 128, 3, 1, 0, 8, True, 1, True, False, 0.1),
+    ("gn-64-channels-dense", 1, 64, 64, 64, 0, 128, 1, 1, 0, 8, True, 1, False, True, 0.1),
     # rectangular h x w blocks (adaptive block-size selection): LDS-direct, GroupNorm-prologue, scalar and resampling paths
     ("rect-2x8-direct", 2, 16, 16, 64, 64, 128, 3, 1, 0, (2, 8), False, 0, True, True, 0.15),
     ("rect-8x2-gn", 2, 16, 32, 64, 0, 96, 3, 1, 0, (8, 2), True, 1, True, False, 0.15),

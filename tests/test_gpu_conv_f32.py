@@ -15,11 +15,13 @@ CASES = [
     # name, B, H(out), W(out), Cin, Cout, k, stride, ups, tile, tiles, temb, res
     ("one-row-two-units", 1, 8, 8, 16, 4, 1, 1, 0, 1, 1, False, False),               # six of eight waves without work
     ("33-rows-ragged-columns", 1, 8, 8, 48, 36, 3, 1, 0, 1, 33, True, True),           # 54 units: batches end inside
-    ("border-tiles", 2, 8, 8, 64, 64, 3, 1, 0, 4, 4, False, True),                     # 72 units, one more than a batch of eight waves
+    ("border-tiles", 2, 8, 8, 64, 64, 3, 1, 0, 4, 4, False, True),                     # 72 units: one batch of nine for each of eight waves
+    ("a-batch-and-a-unit", 1, 8, 8, 592, 40, 1, 1, 0, 2, 9, True, False),              # 74 units: two waves take a tenth
     ("stride-2", 2, 8, 8, 128, 32, 3, 2, 0, 2, 5, True, False),
     ("upsample", 1, 16, 16, 32, 68, 3, 1, 1, 4, 7, False, False),
     ("256-tiles", 2, 64, 32, 16, 64, 3, 1, 0, 8, 32, False, False),                    # 128 x 2 tiles: the last launch shape of this kernel
-    ("258-tiles", 1, 64, 72, 16, 36, 3, 1, 0, 4, 258, False, True),                    # the staged kernel
+    ("258-tiles", 1, 64, 72, 16, 36, 3, 1, 0, 4, 258, False, True),                    # the staged kernel, 16 channels of a tap at a time
+    ("258-tiles-32-channels", 1, 64, 72, 32, 36, 3, 1, 0, 4, 258, True, False),        # and 32
 ]
 
 

@@ -191,7 +191,8 @@ def test_otsu_and_accumulate_and_apsc(fb):
 
 
 @pytest.mark.parametrize("dtype,shape,G,two", [("f32", (1, 32, 32, 64), 32, False), ("bf16", (2, 64, 64, 320), 32, False),
-                                               ("bf16", (2, 16, 16, 1280), 32, True), ("bf16", (2, 10, 6, 96), 4, True)])
+                                               ("bf16", (2, 16, 16, 1280), 32, True), ("bf16", (2, 10, 6, 96), 4, True),
+                                               ("bf16", (2, 10, 6, 36), 6, False)])      # channels that are no multiple of eight
 def test_groupnorm_stats(fb, dtype, shape, G, two):
     rng = np.random.default_rng(3001)
     B, H, W, C = shape
