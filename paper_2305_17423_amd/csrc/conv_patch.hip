@@ -305,7 +305,16 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const IgemmArgs a) {
             y[c] = u32x2_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
 #pragma unroll
             for (int v = 0; v < 2; ++v)
-                if (v < a.nview) u[v][c] = view_act4(y[c], __builtin_bit_cast(f32x4_t, ss[v][c][0]), __builtin_bit_cast(f32x4_t, ss[v][c][1]), a.view[v].silu);
+                if (v < a.nview) {                       // as put_views4
+                    float z[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        z[q] = view_scale(q & 1 ? hi16(y[c][q >> 1]) : lo16(y[c][q >> 1]), __uint_as_float(ss[v][c][q >> 1][(q & 1) * 2]), __uint_as_float(ss[v][c][q >> 1][(q & 1) * 2 + 1]));
+                    if (a.view[v].silu)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) z[q] = silu_f(z[q]);
+                    u[v][c] = u32x2_t{f2bf2(z[0], z[1]), f2bf2(z[2], z[3])};
+                }
         }
         if (pos.y >= 0)
 #pragma unroll

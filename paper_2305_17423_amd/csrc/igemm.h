@@ -81,39 +81,42 @@ struct BlockDerived {
 
 #if defined(__HIPCC__)
 __device__ __forceinline__ unsigned fdiv(unsigned n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
+// A view of a value as stored, before its SiLU: the one expression behind every normalised copy, so that they agree bit for bit.
+__device__ __forceinline__ float view_scale(float stored, float scale, float shift) { return fmaf(stored, scale, shift); }
 // Four consecutive channels col .. col + 3 of pixel `pix` (batch element b): every view gets its activation.
 // In two halves, so that an epilogue can request the table entries of all its items together with its other
 // operands and use them later (loaded where they are used, each item pays a round trip of its own in front of
 // its stores): view_ss_load fetches the four (scale, shift) pairs per view, put_views4 applies them.
-struct ViewSS { f32x4_t s[2][2]; };      // (scale, shift) of two channels each
+struct ViewSS { float s[2][8]; };
 __device__ __forceinline__ void view_ss_load(const GnView* view, int nview, int b, int col, ViewSS& o) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        o.s[i][0] = o.s[i][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        f32x4_t s01 = {0.f, 0.f, 0.f, 0.f}, s23 = s01;
         if (i < nview) {
             const GnView w = view[i];
             auto sp = (const FISE_AS1 f32x4_t*)(w.ss + (size_t)b * w.dstC + w.c_off + col);
-            o.s[i][0] = sp[0]; o.s[i][1] = sp[1];
+            s01 = sp[0]; s23 = sp[1];
         }
-    }
-}
-// One view of four channels, from the values as stored.
-__device__ __forceinline__ u32x2_t view_act4(u32x2_t stored, f32x4_t ss01, f32x4_t ss23, int silu) {
-    float u[4] = {fmaf(lo16(stored[0]), ss01[0], ss01[1]), fmaf(hi16(stored[0]), ss01[2], ss01[3]), fmaf(lo16(stored[1]), ss23[0], ss23[1]),
-                  fmaf(hi16(stored[1]), ss23[2], ss23[3])};
-    if (silu) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) u[q] = silu_f(u[q]);
+        for (int q = 0; q < 4; ++q) { o.s[i][q] = s01[q]; o.s[i][4 + q] = s23[q]; }
     }
-    return u32x2_t{f2bf2(u[0], u[1]), f2bf2(u[2], u[3])};
 }
 __device__ __forceinline__ void put_views4(const GnView* view, int nview, unsigned pix, int col, const float (&v)[4], const ViewSS& ss) {
-    const u32x2_t stored = {f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
+    const unsigned p01 = f2bf2(v[0], v[1]), p23 = f2bf2(v[2], v[3]);      // the values as stored
+    const float x[4] = {lo16(p01), hi16(p01), lo16(p23), hi16(p23)};
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         if (i >= nview) break;
         const GnView w = view[i];
-        *(FISE_AS1 u32x2_t*)(w.dst + (size_t)pix * w.dstC + w.c_off + col) = view_act4(stored, ss.s[i][0], ss.s[i][1], w.silu);
+        float u[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = view_scale(x[q], ss.s[i][2 * q], ss.s[i][2 * q + 1]);
+        if (w.silu) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) u[q] = silu_f(u[q]);
+        }
+        auto dp = (FISE_AS1 u32x2_t*)(w.dst + (size_t)pix * w.dstC + w.c_off + col);
+        *dp = u32x2_t{f2bf2(u[0], u[1]), f2bf2(u[2], u[3])};
     }
 }
 __device__ __forceinline__ void put_views4(const GnView* view, int nview, int b, unsigned pix, int col, const float (&v)[4]) {
@@ -129,7 +132,7 @@ __device__ __forceinline__ void put_views1(const GnView* view, int nview, int b,
         if (i >= nview) break;
         const GnView w = view[i];
         const float2 s = w.ss[(size_t)b * w.dstC + w.c_off + col];
-        float u = fmaf(x, s.x, s.y);
+        float u = view_scale(x, s.x, s.y);
         if (w.silu) u = silu_f(u);
         w.dst[pix * w.dstC + w.c_off + col] = f2bf(u);
     }

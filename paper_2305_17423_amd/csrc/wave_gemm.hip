@@ -676,8 +676,19 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
                 y[it] = u32x2_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
-                    if (i < a.nview)
-                        yv[it][i] = view_act4(y[it], __builtin_bit_cast(f32x4_t, e_ss[it][i][0]), __builtin_bit_cast(f32x4_t, e_ss[it][i][1]), a.view[i].silu);
+                    if (i < a.nview) {                  // as put_views4
+                        float u[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const u32x4_t& ss = e_ss[it][i][q >> 1];
+                            u[q] = view_scale(q & 1 ? hi16(y[it][q >> 1]) : lo16(y[it][q >> 1]), __uint_as_float(ss[(q & 1) * 2]), __uint_as_float(ss[(q & 1) * 2 + 1]));
+                        }
+                        if (a.view[i].silu) {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) u[q] = silu_f(u[q]);
+                        }
+                        yv[it][i] = u32x2_t{f2bf2(u[0], u[1]), f2bf2(u[2], u[3])};
+                    }
             }
             if (grp + 1 < GROUPS) fetch_operands(grp + 1);
 #pragma unroll
@@ -740,7 +751,9 @@ __device__ __forceinline__ void wave_gemm_tile(const IgemmArgs& a, const Product
             if (!GEGLU && a.nview) {
                 ViewSS ss;
 #pragma unroll
-                for (int i = 0; i < 2; ++i) { ss.s[i][0] = __builtin_bit_cast(f32x4_t, e_ss[gi][i][0]); ss.s[i][1] = __builtin_bit_cast(f32x4_t, e_ss[gi][i][1]); }
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) { ss.s[i][q] = __uint_as_float(e_ss[gi][i][0][q]); ss.s[i][4 + q] = __uint_as_float(e_ss[gi][i][1][q]); }
                 put_views4(a.view, a.nview, e_pix[it], scol, x, ss);
             }
         }
