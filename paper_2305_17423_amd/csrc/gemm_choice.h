@@ -96,7 +96,7 @@ inline int linear_tile(int rows, int N) {
 }
 
 // ---- norm_gemm.hip
-constexpr int NG_WAVES = 8, NG_LDS_MAX = 160 * 1024;
+constexpr int NG_WAVES = 8, NG_LDS_MAX = 160 * 1024, NG_BIAS = 5120;      // bytes of bias of a workgroup: 80 units of 32 columns
 
 // Logarithm of the waves that share a unit: all there are, where their sums find room in the place of the rows (320 channels of 32 columns: not).  1280 channels,
 // 24 rows: one product 8.1 -> 7.0 us, queries, keys and values 10.1 -> 8.5; 640 channels 384 rows 7.5 -> 7.2.
@@ -124,6 +124,7 @@ struct NormChoice { int tile, per; };                      // in kNormTiles (-1:
 // (2 RT + 4 CT KB a wave and stage of 64 channels) and for the stages a wave goes through; what all workgroups read of the weights comes on top.
 inline NormChoice choose_norm_tile(const NormShape& a) {
     constexpr int kPer[] = {1, 2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 40, 64, 80};
+    static_assert(kPer[14] * 32 * 2 <= NG_BIAS, "bias of a workgroup");
     auto up = [](int n, int d) { return (n + d - 1) / d; };
     const int rows = a.B * a.Ma, NK = a.K / 64, KM = a.K / 320;
     NormChoice c{-1, 1}; double best = 1e30;
@@ -132,7 +133,7 @@ inline NormChoice choose_norm_tile(const NormShape& a) {
         if (t.K != a.K || t.geglu != (int)a.geglu) continue;
         // the table holds two batch elements, and the smallest row tile is 32 (16 at 1280 channels)
         if (a.gn && a.B > 1 && a.Ma < 16 * t.rt) continue;
-        if (a.gn && 16 * t.rt * (640 * KM + 136) + NG_WAVES * t.nd * t.ct * 2048 + 2 * a.K * 8 > NG_LDS_MAX) continue;
+        if (a.gn && 16 * t.rt * (640 * KM + 136) + NG_WAVES * t.nd * t.ct * 2048 + NG_BIAS + 2 * a.K * 8 > NG_LDS_MAX) continue;
         const int units = a.N / (a.geglu ? 16 : 16 * t.ct), gx = up(rows, 16 * t.rt);
         for (const int per : kPer) {
             if (per > units) break;

@@ -9,6 +9,10 @@
 //  - Every wave owns 16*CT columns at a time and streams their weights through an LDS ring of its own (LDS-direct loads, eight rows of 128 bytes
 //    each, ND stages of 64 channels): behind the barrier of the rows there is none.  The ring runs on over the end of a column
 //    tile, so the next tile's weights travel under the epilogue.
+//  - Where the rows come from is part of the kernel's type, the touched lines are a fixed number of loads and the bias waits in LDS: the
+//    compiler then counts the loads in flight exactly.  With a run-time source, a loop of touches and the bias in registers it waited for every load,
+//    the first stages of cold weights among them, in front of the normalisation and of each column tile (rows normalised after 4.2 us of an 8 us launch,
+//    7.2 of 15 with GEGLU at 96 rows): steps of 12 of 64 and 43 of 144 tiles 2277 -> 2250 and 4226 -> 4174 us, dense pass 5047 -> 4975.
 //  - 16 x 16 x 32 products: a lane ends up with four consecutive columns of a row, or, with the operands exchanged, four consecutive
 //    rows of a column (the transposed values); results go from registers to memory, there is no sum over waves.
 // Bound by the LDS (operands of both sides, 2 RT + 4 CT KB a wave and stage) and the rate of LDS-direct loads for many rows, by its start, the rows and the
@@ -55,18 +59,22 @@ template <int N> __device__ __forceinline__ float ng_sum(float x) {
 // so that sixteen rows' operand reads meet no bank twice; then the rows' positions; then (GroupNorm) the scale / shift table.
 template <int KM> constexpr int ng_pitch() { return 640 * KM + (KM == 1 ? 0 : 128); }
 
-template <int KM, int RT, int CT, int ND, bool GEGLU>
+template <int KM, int RT, int CT, int ND, bool GEGLU, int SRC>
 __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormGemmDev g) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int NW = NG_WAVES, K = 320 * KM, BM = 16 * RT, PITCH = ng_pitch<KM>(), LPR = 16 * KM, RPW = 64 / LPR, P = BM / (NW * RPW);
     constexpr int OC = GEGLU ? 16 : 16 * CT, NK = 5 * KM;      // output columns of a unit, stages of 64 channels
+    constexpr unsigned OOB = 0x80000000u;                 // beyond every descriptor: no traffic
+    constexpr int NG_TOUCH = 2;                           // lines a lane touches at most
     static_assert(P >= 1 && BM % (NW * RPW) == 0 && (!GEGLU || CT == 2), "rows per wave");
     const NormGemmArgs& a = g.a;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     int2* const rowpos = reinterpret_cast<int2*>(lds + BM * PITCH);
     constexpr int WST = CT * 2048;                        // bytes of a stage of weights in LDS
     unsigned char* const wring = lds + BM * PITCH + BM * 8;
-    float2* const table = reinterpret_cast<float2*>(wring + NW * ND * WST);
+    constexpr bool BIAS = GEGLU || SRC == NG_MAP_GN || SRC == NG_MAP_RAW;
+    unsigned char* const lbias = wring + NW * ND * WST;
+    float2* const table = reinterpret_cast<float2*>(lbias + NG_BIAS);
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // consecutive workgroups go round-robin to the 8 XCDs: each gets a contiguous run of (columns, rows), rows fastest
@@ -90,7 +98,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
     if (g.pixels)
 #pragma unroll
         for (int p = 0; p < P; ++p) rt[p] = (unsigned)((const FISE_AS1 int*)a.tile_idx)[fdiv(rm[p], g.d_tt)];
-    if (a.src == NG_ROWS_LN)
+    if constexpr (SRC == NG_ROWS_LN)
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             const FISE_AS1 f32x4_t* q = (const FISE_AS1 f32x4_t*)((const float*)a.x + (size_t)(rb[p] * (unsigned)a.Ma + rm[p]) * K) + l;
@@ -105,7 +113,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
         }
         if (l == 0) rowpos[p * (NW * RPW) + wave * RPW + lane / LPR] = make_int2((int)rb[p], (int)rm[p]);
     }
-    if (a.src != NG_ROWS_LN)
+    if constexpr (SRC != NG_ROWS_LN)
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             const FISE_AS1 u32x2_t* q = (const FISE_AS1 u32x2_t*)((const bf16_t*)a.x + ((size_t)rb[p] * (a.Ho * a.Wo) + rm[p]) * K) + l;
@@ -113,7 +121,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
             for (int j = 0; j < 5; ++j) { const u32x2_t u = q[j * LPR]; v[p][j] = f32x4_t{__uint_as_float(u.x), __uint_as_float(u.y), 0.f, 0.f}; }
         }
     u32x2_t gam[5], bet[5];
-    if (a.src == NG_ROWS_LN || a.src == NG_MAP_LN)
+    if constexpr (SRC == NG_ROWS_LN || SRC == NG_MAP_LN)
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             gam[j] = ((const FISE_AS1 u32x2_t*)a.gamma)[j * LPR + l];
@@ -144,26 +152,26 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
                                                      q & 1 ? vd1 : vd0, wrow + (q < 2 ? 0u : GEGLU ? (unsigned)a.N * (2u * K) : 16u * (2u * K)), 0, 0);
         wrow += 128u;
     };
-    auto load_bias = [&](int t, u32x2_t (&o)[CT]) {
-        const __amdgpu_buffer_rsrc_t rs = buf(a.bias, a.bias && t < t1 ? (unsigned)((GEGLU ? 2 : 1) * a.N) * 2u : 0u);
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-            o[c] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, (unsigned)(t * OC + lq * 4) * 2u + (c == 0 ? 0u : GEGLU ? 2u * a.N : 32u), 0, 0));
-    };
+    // the bias of this workgroup's columns (GEGLU: of the values, then of the gates), 16 bytes a thread, on its way to LDS
+    u32x4_t bias16 = u32x4_t{0, 0, 0, 0};
+    if constexpr (BIAS) {
+        const __amdgpu_buffer_rsrc_t rs = buf(a.bias, a.bias ? (unsigned)((GEGLU ? 2 : 1) * a.N) * 2u : 0u);
+        const int half = g.per * OC / 8;                 // pieces of the values
+        bias16 = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (unsigned)(t0 * OC + (GEGLU && tid >= half ? a.N - half * 8 : 0) + tid * 8) * 2u, 0, 0));
+    }
     // Row tiles that share a slice of the weights walk it in step, so each of its lines is cold for all of them at once: they first touch
-    // the slice, each a share of its lines (one dword a line, into the ring before it is filled).  512 x 10240 x 1280 38 -> 30.4 us, 96 rows
+    // the slice, each a share of its lines (one dword a line, into the ring before it is filled; NG_TOUCH x 512 lines a row tile at most).  512 x 10240 x 1280 38 -> 30.4 us, 96 rows
     // 18.4 -> 16.0; slices under 200 KB or two row tiles lose 0.3 - 1 us.
-    if (g.touch) {
+    {
         const int col0 = t0 * OC, s = GEGLU ? 0 : (col0 >= a.sect_n) + (col0 >= 2 * a.sect_n), n = GEGLU ? 32 * (t1 - t0) : min(t1 * OC, (s + 1) * a.sect_n) - col0;
-        const __amdgpu_buffer_rsrc_t rs = buf(s == 0 ? a.w[0] : s == 1 ? a.w[1] : a.w[2], (unsigned)((GEGLU ? 2 * a.N : a.sect_n) * (2 * K)));
-        for (int q = (bx * NW + wave) * 64 + lane; q < n * NK; q += g.gx * NW * 64) {
-            const int r = q / NK, row = GEGLU ? (r & 1 ? a.N : 0) + col0 + (r >> 1) : col0 - s * a.sect_n + r;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)my_ring, 4, (unsigned)row * (2u * K) + (unsigned)(q - r * NK) * 128u, 0, 0, 0);
+        const __amdgpu_buffer_rsrc_t rs = buf(s == 0 ? a.w[0] : s == 1 ? a.w[1] : a.w[2], g.touch ? (unsigned)((GEGLU ? 2 * a.N : a.sect_n) * (2 * K)) : 0u);
+#pragma unroll
+        for (int k = 0; k < NG_TOUCH; ++k) {
+            const int q = ((k * g.gx + bx) * NW + wave) * 64 + lane, r = q / NK, row = GEGLU ? (r & 1 ? a.N : 0) + col0 + (r >> 1) : col0 - s * a.sect_n + r;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)my_ring, 4, q < n * NK ? (unsigned)row * (2u * K) + (unsigned)(q - r * NK) * 128u : OOB, 0, 0, 0);
         }
     }
     int t = t0 + (wave >> g.ks);
-    u32x2_t bias[CT], bias_next[CT];
-    load_bias(t, bias_next);
     set_unit(t);
 #pragma unroll
     for (int u = 0; u < ND; ++u) {
@@ -174,7 +182,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- normalise into LDS
-    if (a.src == NG_MAP_GN) {                             // (scale, shift) of the tile's batch elements (two at most: Ma >= BM)
+    if constexpr (SRC == NG_MAP_GN) {                     // (scale, shift) of the tile's batch elements (two at most: Ma >= BM)
         for (int e = tid; e < 2 * K; e += 64 * NW) {
             const int bb = min(a.B - 1, b_first + (e >= K)), c = e >= K ? e - K : e, gi = bb * a.G + (int)fdiv((unsigned)c, g.d_cpg);
             const float sc = a.gn_rstd[gi] * bf2f(a.gamma[c]);
@@ -189,18 +197,18 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             x[j] = v[p][j];
-            if (a.src != NG_ROWS_LN) {
+            if constexpr (SRC != NG_ROWS_LN) {
                 const unsigned w0 = __float_as_uint(v[p][j].x), w1 = __float_as_uint(v[p][j].y);
                 x[j] = f32x4_t{lo16(w0), hi16(w0), lo16(w1), hi16(w1)};
             }
         }
-        if (a.src == NG_MAP_GN) {
+        if constexpr (SRC == NG_MAP_GN) {
             const float2* ss = table + ((int)fdiv((unsigned)min(m0 + r, rows - 1), g.d_Ma) - b_first) * K;
 #pragma unroll
             for (int j = 0; j < 5; ++j)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) { const float2 s = ss[(j * LPR + l) * 4 + q]; x[j][q] = x[j][q] * s.x + s.y; }
-        } else if (a.src != NG_MAP_RAW) {
+        } else if constexpr (SRC != NG_MAP_RAW) {
             float s = 0.f;
 #pragma unroll
             for (int j = 0; j < 5; ++j) s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
@@ -227,6 +235,8 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
                 u32x2_t{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
         }
     }
+    if constexpr (BIAS)
+        if (tid < NG_BIAS / 16) *reinterpret_cast<u32x4_t*>(lbias + tid * 16) = bias16;
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // not the loads of the weights
 
     // ---- column tiles
@@ -238,9 +248,6 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
         for (int i = 0; i < RT; ++i)
 #pragma unroll
             for (int c = 0; c < CT; ++c) acc[i][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < CT; ++c) bias[c] = bias_next[c];
-        load_bias(t + step, bias_next);
         const int col = t * OC, sect = GEGLU ? 0 : (col >= a.sect_n) + (col >= 2 * a.sect_n);
         const int mode = GEGLU ? OUT_COMPACT : sect == 0 ? a.mode[0] : sect == 1 ? a.mode[1] : a.mode[2];
         auto run = [&]() {
@@ -309,6 +316,12 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
                     for (int c = 0; c < CT; ++c) acc[i][c] += sums[((wave + o) * (RT * CT) + i * CT + c) * 64 + lane];
         }
         place();
+        u32x2_t bias[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            bias[c] = u32x2_t{0, 0};
+            if constexpr (BIAS) bias[c] = *reinterpret_cast<const u32x2_t*>(lbias + ((t - t0) * OC + eq * 4 + (c == 0 ? 0 : GEGLU ? g.per * OC : c * 16)) * 2);
+        }
         if constexpr (GEGLU) {
             const float bv[4] = {lo16(bias[0].x), hi16(bias[0].x), lo16(bias[0].y), hi16(bias[0].y)};
             const float bg[4] = {lo16(bias[1].x), hi16(bias[1].x), lo16(bias[1].y), hi16(bias[1].y)};
@@ -377,36 +390,49 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
 // host side
 // ---------------------------------------------------------------------------
 template <int KM, int RT, int CT, int ND> constexpr int ng_lds(bool table) {
-    return 16 * RT * (ng_pitch<KM>() + 8) + NG_WAVES * ND * CT * 2048 + (table ? 2 * 320 * KM * 8 : 0);
+    return 16 * RT * (ng_pitch<KM>() + 8) + NG_WAVES * ND * CT * 2048 + NG_BIAS + (table ? 2 * 320 * KM * 8 : 0);
 }
 
-template <int KM, int RT, int CT, int ND, bool GEGLU>
+template <int KM, int RT, int CT, int ND, bool GEGLU, int SRC>
 static int launch_cfg(NormGemmDev g, int per, hipStream_t st) {
     const NormGemmArgs& a = g.a;
-    constexpr int lds_max = ng_lds<KM, RT, CT, ND>(true) <= NG_LDS_MAX ? ng_lds<KM, RT, CT, ND>(true) : ng_lds<KM, RT, CT, ND>(false);
-    static_assert(lds_max <= NG_LDS_MAX, "LDS of a CU");
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&norm_gemm_kernel<KM, RT, CT, ND, GEGLU>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
-    if (attr != hipSuccess) return fail(FISE_ERR_HIP, "norm gemm: cannot raise the dynamic LDS limit");
-    const int rows = a.B * a.Ma;
-    g.gx = ceil_div(rows, 16 * RT); g.units = a.N / (GEGLU ? 16 : 16 * CT); g.per = per;
-    g.t_tokens = a.mode[a.N / a.sect_n - 1] == OUT_TOKENS_T ? (a.N - a.sect_n) / (16 * CT) : g.units;
-    g.touch = g.gx >= 3 && per * CT * KM * 10 >= 200;      // kernel comment
-    g.ks = waves_per_unit(KM, CT, per);
-    g.d_gx = fast_div(g.gx);
-    {
-        const double K = 320.0 * KM, ncols = GEGLU ? 2.0 * a.N : a.N;
-        ProfileScope prof(GEGLU ? PROF_IGEMM_GEGLU : PROF_ROWS_GEMM, 2.0 * rows * ncols * K,
-                          2.0 * (ncols * K + (double)rows * a.N) + (a.src == NG_ROWS_LN ? 4.0 : 2.0) * rows * K, st);
-        hipLaunchKernelGGL((norm_gemm_kernel<KM, RT, CT, ND, GEGLU>), dim3((unsigned)(g.gx * ceil_div(g.units, per))), dim3(64 * NG_WAVES),
-                           (ng_lds<KM, RT, CT, ND>(a.src == NG_MAP_GN)), st, g);
+    constexpr int lds = ng_lds<KM, RT, CT, ND>(SRC == NG_MAP_GN);
+    if constexpr (lds > NG_LDS_MAX) {                    // never chosen: no room for the table
+        return fail(FISE_ERR_SHAPE, "norm gemm: LDS of a CU");
+    } else {
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&norm_gemm_kernel<KM, RT, CT, ND, GEGLU, SRC>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (attr != hipSuccess) return fail(FISE_ERR_HIP, "norm gemm: cannot raise the dynamic LDS limit");
+        const int rows = a.B * a.Ma;
+        g.gx = ceil_div(rows, 16 * RT); g.units = a.N / (GEGLU ? 16 : 16 * CT); g.per = per;
+        g.t_tokens = a.mode[a.N / a.sect_n - 1] == OUT_TOKENS_T ? (a.N - a.sect_n) / (16 * CT) : g.units;
+        g.touch = g.gx >= 3 && per * CT * KM * 10 >= 200;      // kernel comment
+        g.ks = waves_per_unit(KM, CT, per);
+        g.d_gx = fast_div(g.gx);
+        {
+            const double K = 320.0 * KM, ncols = GEGLU ? 2.0 * a.N : a.N;
+            ProfileScope prof(GEGLU ? PROF_IGEMM_GEGLU : PROF_ROWS_GEMM, 2.0 * rows * ncols * K,
+                              2.0 * (ncols * K + (double)rows * a.N) + (SRC == NG_ROWS_LN ? 4.0 : 2.0) * rows * K, st);
+            hipLaunchKernelGGL((norm_gemm_kernel<KM, RT, CT, ND, GEGLU, SRC>), dim3((unsigned)(g.gx * ceil_div(g.units, per))), dim3(64 * NG_WAVES), lds, st, g);
+        }
+        FISE_CHECK_LAUNCH("norm gemm");
+        return FISE_OK;
     }
-    FISE_CHECK_LAUNCH("norm gemm");
-    return FISE_OK;
 }
 
-#define FISE_NORM_LAUNCH(K, GEGLU, RT, CT, ND) launch_cfg<K / 320, RT, CT, ND, GEGLU != 0>,
-static int (*const kNormLaunch[])(NormGemmDev, int, hipStream_t) = {FISE_NORM_TILES(FISE_NORM_LAUNCH)};
+// the gate rides on the LayerNorm of the residual stream only
+template <int KM, int RT, int CT, int ND, bool GEGLU>
+static int launch_src(const NormGemmDev& g, int per, hipStream_t st) {
+    if constexpr (!GEGLU) {
+        if (g.a.src == NG_MAP_LN) return launch_cfg<KM, RT, CT, ND, false, NG_MAP_LN>(g, per, st);
+        if (g.a.src == NG_MAP_GN) return launch_cfg<KM, RT, CT, ND, false, NG_MAP_GN>(g, per, st);
+        if (g.a.src == NG_MAP_RAW) return launch_cfg<KM, RT, CT, ND, false, NG_MAP_RAW>(g, per, st);
+    }
+    return launch_cfg<KM, RT, CT, ND, GEGLU, NG_ROWS_LN>(g, per, st);
+}
+
+#define FISE_NORM_LAUNCH(K, GEGLU, RT, CT, ND) launch_src<K / 320, RT, CT, ND, GEGLU != 0>,
+static int (*const kNormLaunch[])(const NormGemmDev&, int, hipStream_t) = {FISE_NORM_TILES(FISE_NORM_LAUNCH)};
 #undef FISE_NORM_LAUNCH
 
 bool norm_gemm_takes(int src, int K, int B, int Ma, int H, int W) {
@@ -421,7 +447,7 @@ int launch_norm_gemm(const NormGemmArgs& a, hipStream_t st) {
     const int nsect = a.N / a.sect_n;
     bool map = a.src != NG_ROWS_LN, tokens = false;
     for (int s = 0; s < nsect; ++s) { map |= a.mode[s] == OUT_MAP; tokens |= a.mode[s] == OUT_TOKENS_T; if (a.mode[s] == OUT_TOKENS_T && s + 1 < nsect) return fail(FISE_ERR_SHAPE, "norm gemm: a transposed section is the last one"); }
-    if (!norm_gemm_takes(a.src, a.K, a.B, a.Ma, a.Ho, a.Wo) || a.sect_n % 32 || nsect * a.sect_n != a.N || nsect > 3 || (a.geglu && nsect != 1) || (a.bias && nsect != 1))
+    if (!norm_gemm_takes(a.src, a.K, a.B, a.Ma, a.Ho, a.Wo) || a.sect_n % 32 || nsect * a.sect_n != a.N || nsect > 3 || (a.geglu && (nsect != 1 || a.src != NG_ROWS_LN)) || (a.bias && nsect != 1))
         return fail(FISE_ERR_SHAPE, "norm gemm: %d channels, %d columns in sections of %d", a.K, a.N, a.sect_n);
     g.pixels = a.tile_idx && (map || tokens);
     g.trans4 = a.Ma % 4 == 0 && (a.tile_idx ? a.tile % 4 == 0 && a.Wo % 4 == 0 : a.Ho * a.Wo % 4 == 0);

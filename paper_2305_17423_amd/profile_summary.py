@@ -53,7 +53,7 @@ def kind_of(name: str):
     """The fise_profile_read kind (as bench.py names it) a profiler kernel name belongs to, or None."""
     n = short(name)
     wave = re.search(r"wave_gemm_(?:group_)?kernel<\d+, \d+, \d+, \d+, (\d), (true|false), ", n)      # A operand, GEGLU
-    norm = re.search(r"norm_gemm_kernel<\d+, \d+, \d+, \d+, (true|false)>", n)                      # GEGLU
+    norm = re.search(r"norm_gemm_kernel<\d+, \d+, \d+, \d+, (true|false), \d+>", n)                      # GEGLU
     if wave and wave[2] == "true" or norm and norm[1] == "true" or "igemm_dma_kernel<64, 128, 2, 2" in n or "igemm_dma_kernel<32, 256" in n:
         return "norm_gemm_kernel<*,GEGLU> / wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>"
     if norm or "wave_gemm_group" in n or wave and wave[1] == "0":
