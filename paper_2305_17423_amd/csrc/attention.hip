@@ -292,6 +292,295 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
     }
 }
 
+// The same for long key ranges of heads of 40, 80 and 160: a turn of 64 (160: 32) keys at a time, with the products of other turns issued between the
+// vector instructions of this turn's softmax: those of the values of the turn before, then the scores of the next turn, into the registers of this
+// turn's as they are used up.  Operands come through LDS-direct loads, two or three turns ahead, and one barrier a turn.
+// Bound by the instructions a wave issues (one in ~5 cycles: 172 vector, 14 matrix, 14 LDS and ~50 scalar ones a turn of 8 x 40; attention_kernel has
+// 190, 14, 26 and ~70) and, with many queries, by power: the clock falls from 2.2 to 1.7 - 2.1 GHz under this kernel, so what the matrix units
+// multiply counts too, and value rows past the head dim are read as zeros (left as they come, 2 x 2752 queries, 9216 keys 131 -> 136 us).
+// us, attention_kernel and this one: 2 x 2752 queries, 9216 keys of 8 x 40 151 -> 141, 2 x 4096 x 4096 92 -> 84, 2 x 768 x 4096 32.0 -> 31.0; 2 x 1376 x 2304 of
+// 8 x 80 48.7 -> 48.0; 2 x 576 x 576 of 8 x 160 22.6 -> 21.7.
+// Products issued when the vector work of slot s of a turn starts.  Slots: the maximum, from `weights` on the probabilities (eight slots a 32-key block), from
+// `rescale` on the rescaling.  The values' (DB a 16-key step) go out before the probabilities of their keys are overwritten and before the
+// rescaling; the scores of a 32-key block of the next turn behind the last use of this turn's, whose registers they take.
+constexpr int at_issued(int s, int slots, int weights, int NB, int DB, int KD) {
+    const int values = 2 * NB * DB, rescale = weights + 8 * NB, v_end = NB == 2 ? weights + 8 : rescale;
+    if (s < v_end) {
+        const int even = (values * (s + 1) + v_end - 1) / v_end, need = s < weights ? 0 : DB * ((s - weights) / 4 + 1);
+        return even > need ? even : need;
+    }
+    if (s < rescale) return values + (KD * (s + 1 - v_end) + 7) / 8;
+    return values + (NB - 1) * KD + (KD * (s + 1 - rescale) + slots - rescale - 1) / (slots - rescale);
+}
+// Registers that a turn's operands go round in, `ahead` of them requested before they are needed: the first ones of the next turn must not meet the last of this.
+constexpr int at_ring(int n, int ahead) {
+    for (int r = ahead + 1;; ++r) {
+        bool ok = true;
+        for (int i = 0; i < ahead; ++i)
+            for (int j = n - ahead + i + 1; j < n; ++j) ok = ok && j % r != i;
+        if (ok) return r;
+    }
+}
+template <int N, typename F> __device__ __forceinline__ void at_static_for(F&& f) {
+    if constexpr (N > 0) { at_static_for<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void attention_turns_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ K,
+                                                           const bf16_t* __restrict__ Vt, int B, int M, int n_keys, int n_stride,
+                                                           int C, float scale_log2e, int splits, int per, int nqt, int heads,
+                                                           FastDiv d_nqt, FastDiv d_heads, FastDiv d_splits,
+                                                           bf16_t* __restrict__ out, float* __restrict__ part_o, float* __restrict__ part_ml) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    using T = AtTile<D>;
+    constexpr int KD = T::KD, d = D, DB = T::DB, NB = T::NB, BK = T::BK, PITCH = T::PITCH, VPITCH = T::VPITCH, KL = T::KL, VL = T::VL, LPW = T::LPW;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // [VR][VB] values, [KR][KB] keys, zeros, what nobody reads
+
+    const int tid = threadIdx.x, lane = tid & 63, hl = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Workgroup -> (query tile qt, head h, batch element b, key split sp).  The grid is one-dimensional
+    // and consecutive workgroups go round-robin to the 8 XCDs (one L2 each): workgroup w takes position
+    // (w % 8) * (total / 8) + w / 8 of the (b, sp, h, qt) order, qt fastest, so the query tiles that
+    // stream the same K / V slice run on one XCD and the slice is fetched from HBM once, not eight times.
+    int qt, h, b, sp;
+    {
+        const int total = nqt * heads * B * splits, chunk = total >> 3;
+        int w = blockIdx.x;
+        if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
+        const int t = (int)fdiv(w, d_nqt), u = (int)fdiv(t, d_heads);
+        qt = w - t * nqt; h = t - u * heads;
+        b = (int)fdiv(u, d_splits); sp = u - b * splits;
+    }
+    const int qrow = qt * AT_BQ + wave * AT_QW + l32;
+    const bool qok = qrow < M;
+    // turns of this split: `per` key blocks of 64, in turns of BK
+    const int t0 = sp * per * (AT_BKV / BK), t1 = min((n_keys + BK - 1) / BK, t0 + per * (AT_BKV / BK)), turns = t1 - t0;
+
+    // query fragments: B operand of S^T = K Q^T (column = query, 8 consecutive head-dim elements)
+    bf16x8_t qf[KD];
+#pragma unroll
+    for (int ks = 0; ks < KD; ++ks) {
+        const int c = ks * 16 + hl * 8;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (qok && c < d) v = *reinterpret_cast<const uint4*>(q + ((size_t)b * M + qrow) * C + h * d + c);
+        qf[ks] = *reinterpret_cast<bf16x8_t*>(&v);
+    }
+
+    // ---- loads: KL of keys, VL of values, wave w takes every fourth from the w-th on.  K: LDS row r of a turn holds key
+    // (r & 3) + 4 (r / 8 % 2) + 8 (r / 4 % 2) + 16 (r / 16), so that a lane's eight scores of a 16-key step are eight consecutive
+    // keys, the operand of the second product as they stand; piece p of row r at r PITCH + p.  V^T: piece p (eight keys) of row r at
+    // slot p ^ swizzle(r) of the row.  All of them unconditional: pieces that do not exist are read where one of the same
+    // key or row exists (attention_keys.h), and behind the last turn the last one is read again.
+    const unsigned char* src[LPW]; unsigned off[LPW];    // address of the next load: base, lane's offset from there
+    unsigned put[LPW];                                   // its place
+    const int partial = t1 * BK > n_keys ? t1 - 1 : -1;  // the turn that has fewer than BK keys
+    auto load_of = [&](int t) { return min(wave + 4 * t, KL + VL - 1); };      // the last one several times over
+    auto place = [&](int t, bool whole) {                // offsets in a turn of BK keys, in the partial one
+        const int l = load_of(t), last = whole ? BK - 1 : n_keys - 1 - partial * BK;
+        off[t] = l < KL ? T::key_offset(l * 64 + lane, last, C) : T::value_offset(l - KL, lane, last, n_stride);
+    };
+#pragma unroll
+    for (int t = 0; t < LPW; ++t) {
+        const int l = load_of(t);
+        src[t] = reinterpret_cast<const unsigned char*>(l < KL ? K + ((size_t)b * n_keys + t0 * BK) * C + h * d : Vt + ((size_t)b * C + h * d + T::value_row(l - KL)) * n_stride + t0 * BK);
+        put[t] = l < KL ? T::KEYS + l * 1024 : (l - KL) * 1024;
+        place(t, t0 != partial);
+    }
+    // keys of turn `next` (behind the last one: that one again), values of the turn before (the first time: none)
+    int next = t0;
+    auto load = [&](bool first) {
+#pragma unroll
+        for (int t = 0; t < LPW; ++t)
+            if (!first || load_of(t) < KL) __builtin_amdgcn_global_load_lds((const FISE_AS1 void*)(src[t] + off[t]), (FISE_AS3 void*)(lds + put[t]), 16, 0, 0);
+#pragma unroll
+        for (int t = 0; t < LPW; ++t) {
+            const bool keys = load_of(t) < KL;
+            src[t] += at_next_turn(keys, first, next) < t1 ? (keys ? (long long)C * (2 * BK) : 2ll * BK) : 0ll;
+        }
+        if (next + 1 == partial || (!first && next == partial)) {
+            asm volatile("");                            // a branch, not selects
+#pragma unroll
+            for (int t = 0; t < LPW; ++t)
+                if (at_next_turn(load_of(t) < KL, first, next) == partial) place(t, false);
+        }
+        ++next;
+#pragma unroll
+        for (int t = 0; t < LPW; ++t) {
+            const bool keys = load_of(t) < KL;
+            if (keys || !first) put[t] += keys ? T::KB : T::VB;
+            if (put[t] >= (keys ? T::ZERO : T::KEYS)) put[t] -= keys ? T::KR * T::KB : T::VR * T::VB;
+        }
+    };
+
+    f32x16_t oacc[DB];
+#pragma unroll
+    for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[i][e] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;                // l: of this lane's half of the keys until the end
+
+    if (turns > 0) {
+        // zeros: what a head's last pieces are short of, and the values in front of the first turn
+        if (tid < (T::LDS - T::ZERO) / 16) *reinterpret_cast<uint4*>(lds + T::ZERO + tid * 16) = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < T::VB / 16; e += 256)
+            if (e + tid < T::VB / 16) *reinterpret_cast<uint4*>(lds + (T::VR - 1) * T::VB + (e + tid) * 16) = make_uint4(0, 0, 0, 0);
+        load(true);
+#pragma unroll
+        for (int g = 0; g < T::AHEAD; ++g) load(false);
+        // the query fragments have arrived before the loop: the compiler would otherwise wait for every load in flight in front of each turn's scores
+#pragma unroll
+        for (int ks = 0; ks < KD; ++ks) asm volatile("" ::"v"(qf[ks]));
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(T::AHEAD * LPW) : "memory");
+
+        constexpr int NV = 2 * NB * DB, NM = NV + NB * KD, RA = 3, RING = at_ring(NM, RA);
+        constexpr int WEIGHTS = 2 * NB + 1, RESCALE = WEIGHTS + 8 * NB, SLOTS = RESCALE + KD;
+        // A turn's operands: piece 2 ks + hl of key row l32 (past the head dim: zeros), piece 2 u + hl of value row l32, behind a base that is
+        // worked out once a turn.
+        constexpr int VU = VPITCH % 2 ? 1 : 2 * NB;
+        unsigned kget = T::KEYS, vget = (T::VR - 1) * T::VB, kat, vat[VU], vtail[VU];
+        auto keys_at = [&]() { kat = kget + (unsigned)(l32 * PITCH + hl) * 16; };
+        auto values_at = [&]() {
+#pragma unroll
+            for (int u = 0; u < VU; ++u) {
+                vat[u] = vget + (unsigned)(l32 * VPITCH + (VPITCH % 2 ? hl : (2 * u + hl) ^ T::swizzle(l32))) * 16;
+                if (T::TAIL) vtail[u] = l32 < T::TAIL ? vat[u] : (unsigned)(T::ZERO - (DB - 1) * (32 * VPITCH * 16));
+            }
+        };
+        auto read_k = [&](int kb, int ks) {
+            const unsigned step = (unsigned)(kb * (32 * PITCH * 16) + ks * 32);
+            const bool past = ks == KD - 1 && T::PAD && hl;
+            return *reinterpret_cast<const bf16x8_t*>(lds + (past ? (unsigned)T::ZERO - step : kat) + step);
+        };
+        auto read_v = [&](int u, int i) { return *reinterpret_cast<const bf16x8_t*>(lds + (T::TAIL && i == DB - 1 ? vtail : vat)[VU == 1 ? 0 : u] + (VU == 1 ? u * 32 : 0) + i * (32 * VPITCH * 16)); };
+        bf16x8_t frag[RING];
+        f32x16_t s[NB];
+        uint4 p[2 * NB];                                 // probabilities of the turn before: eight a 16-key step
+#pragma unroll
+        for (int u = 0; u < 2 * NB; ++u) p[u] = make_uint4(0, 0, 0, 0);
+        keys_at();
+        values_at();
+#pragma unroll
+        for (int kb = 0; kb < NB; ++kb) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[kb][e] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KD; ++ks) s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k(kb, ks), qf[ks], s[kb], 0, 0, 0);
+        }
+        kget = T::KEYS + T::KB;
+#pragma unroll
+        for (int m = 0; m < RA; ++m) frag[m] = read_v(m / DB, m % DB);
+
+        for (int t = t0; t < t1; ++t) {
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((T::AHEAD - 1) * LPW) : "memory");
+            load(false);
+            if (__builtin_amdgcn_readfirstlane(t == partial)) {
+                const int left = n_keys - t * BK - hl * 8;
+#pragma unroll
+                for (int kb = 0; kb < NB; ++kb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (kb * 32 + (e >> 3) * 16 + (e & 7) >= left) s[kb][e] = -INFINITY;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            float mraw = -INFINITY, mx = 0.f, alpha = 0.f, psum = 0.f;
+            at_static_for<SLOTS>([&](auto slot_) {
+                constexpr int slot = decltype(slot_)::value, m0 = slot ? at_issued(slot - 1, SLOTS, WEIGHTS, NB, DB, KD) : 0, m1 = at_issued(slot, SLOTS, WEIGHTS, NB, DB, KD);
+                at_static_for<m1 - m0>([&](auto m_) {
+                    constexpr int m = m0 + decltype(m_)::value, r = (m + RA) % NM;
+                    if constexpr (m < NV) {
+                        oacc[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[m % RING], *reinterpret_cast<bf16x8_t*>(&p[m / DB]), oacc[m % DB], 0, 0, 0);
+                    } else {
+                        constexpr int kb = (m - NV) / KD, ks = (m - NV) % KD;
+                        if constexpr (ks == 0)
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) s[kb][e] = 0.f;
+                        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[m % RING], qf[ks], s[kb], 0, 0, 0);
+                    }
+                    if constexpr (m + RA == NM) {
+                        vget = vget == (T::VR - 1) * T::VB ? 0u : vget + T::VB;
+                        values_at();
+                    }
+                    if constexpr (m + RA == NV) keys_at();
+                    if constexpr (r < NV) frag[r % RING] = read_v(r / DB, r % DB);
+                    else frag[r % RING] = read_k((r - NV) / KD, (r - NV) % KD);
+                });
+                if constexpr (slot < 2 * NB) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) mraw = fmaxf(mraw, s[slot / 2][slot % 2 * 8 + e]);
+                } else if constexpr (slot < WEIGHTS) {
+                    const float2 mh = at_halves(mraw);
+                    mx = fmaxf(m_run, fmaxf(mh.x, mh.y) * scale_log2e);
+                    alpha = __builtin_amdgcn_exp2f(m_run - mx);      // first turn: exp2(-inf) = 0
+                    m_run = mx;
+                } else if constexpr (slot < RESCALE) {
+                    constexpr int g = slot - WEIGHTS, kb = g / 8, e = g % 8 * 2;
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][e], scale_log2e, -mx)), p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][e + 1], scale_log2e, -mx));      // v_exp_f32: results below 2^-126 flush to 0
+                    psum += p0; psum += p1;
+                    const unsigned w = f2bf2(p0, p1);
+                    uint4& pu = p[g / 4];
+                    if constexpr (g % 4 == 0) pu.x = w; else if constexpr (g % 4 == 1) pu.y = w; else if constexpr (g % 4 == 2) pu.z = w; else pu.w = w;
+                } else {
+                    constexpr int j = slot - RESCALE;    // rows past the head dim are not stored
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) oacc[j / 2][j % 2 * 8 + e] *= alpha;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            l_run = l_run * alpha + psum;
+            kget = kget == T::ZERO - T::KB ? T::KEYS : kget + T::KB;
+        }
+        // values of the last turn; those of absent keys may be anything
+#pragma unroll
+        for (int m = 0; m < NV; ++m) {
+            uint4 v = *reinterpret_cast<uint4*>(&frag[m % RING]);
+            if (m + RA < NV) frag[(m + RA) % RING] = read_v((m + RA) / DB, (m + RA) % DB);
+            if (partial >= 0) {
+                const int left = n_keys - partial * BK - m / DB * 16 - hl * 8;
+                auto keep = [&](unsigned w, int t) { return left > t + 1 ? w : left > t ? w & 0xffffu : 0u; };
+                v = make_uint4(keep(v.x, 0), keep(v.y, 2), keep(v.z, 4), keep(v.w, 6));
+            }
+            oacc[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<bf16x8_t*>(&v), *reinterpret_cast<bf16x8_t*>(&p[m / DB]), oacc[m % DB], 0, 0, 0);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // loads behind the last turn still write the ring
+    }
+
+    // ---- store: lane holds query l32, head-dim rows i*32 + (e/4)*8 + hl*4 + e%4: four consecutive elements of e are
+    // four consecutive channels (d is a multiple of 8, so a group of four is inside the head or outside it as a whole)
+    const float2 lh = at_halves(l_run);
+    l_run = lh.x + lh.y;
+    if (!qok) return;
+    if (splits == 1) {
+        const float inv = 1.0f / l_run;
+        bf16_t* o = out + ((size_t)b * M + qrow) * C + h * d;
+#pragma unroll
+        for (int i = 0; i < DB; ++i)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const int r = i * 32 + q4 * 8 + hl * 4;
+                if (r < d)
+                    *reinterpret_cast<uint2*>(o + r) = make_uint2(f2bf2(oacc[i][4 * q4] * inv, oacc[i][4 * q4 + 1] * inv),
+                                                                  f2bf2(oacc[i][4 * q4 + 2] * inv, oacc[i][4 * q4 + 3] * inv));
+            }
+    } else {
+        // unnormalised partial of this key range: O[sp][b][qrow][h*d + r], (m, l)[sp][b][h][qrow]
+        float* po = part_o + (((size_t)sp * B + b) * M + qrow) * C + h * d;
+#pragma unroll
+        for (int i = 0; i < DB; ++i)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const int r = i * 32 + q4 * 8 + hl * 4;
+                if (r < d)
+                    *reinterpret_cast<float4*>(po + r) = make_float4(oacc[i][4 * q4], oacc[i][4 * q4 + 1], oacc[i][4 * q4 + 2], oacc[i][4 * q4 + 3]);
+            }
+        if (hl == 0) {
+            float* pm = part_ml + ((((size_t)sp * B + b) * heads + h) * M + qrow) * 2;
+            pm[0] = m_run; pm[1] = l_run;
+        }
+    }
+#endif
+}
+
 // Few queries: a workgroup of eight waves takes 32 queries of one (batch, head), and the waves deal the keys out among themselves, 32 at
 // a time, so 256 keys are one trip to memory for all of them and no second launch merges key splits.  Nothing is shared between
 // the waves before the end: each brings its keys into LDS of its own (LDS-direct loads, rows of 2 d contiguous bytes) and reads its values straight
@@ -531,6 +820,20 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
     *reinterpret_cast<uint2*>(out + ((size_t)b * M + m) * C + c) = make_uint2(f2bf2(num.x * inv, num.y * inv), f2bf2(num.z * inv, num.w * inv));
 }
 
+template <int D>
+static int launch_turns(const void* q, const void* K, const void* Vt, int B, int M, int n_keys, int n_stride, int C, int heads, float scale, int splits,
+                        void* out, float* part_o, float* part_ml, hipStream_t st) {
+    constexpr int lds = AtTile<D>::LDS;
+    static_assert(lds <= 80 * 1024, "two workgroups per CU");
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_turns_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return fail(FISE_ERR_HIP, "attention: cannot raise the dynamic LDS limit");
+    const int nqt = ceil_div(M, AT_BQ);
+    hipLaunchKernelGGL((attention_turns_kernel<D>), dim3((unsigned)(nqt * heads * B * splits)), dim3(256), lds, st, (const bf16_t*)q, (const bf16_t*)K,
+                       (const bf16_t*)Vt, B, M, n_keys, n_stride, C, scale * 1.4426950408889634f, splits, ceil_div(ceil_div(n_keys, AT_BKV), splits), nqt, heads,
+                       fast_div(nqt), fast_div(heads), fast_div(splits), (bf16_t*)out, part_o, part_ml);
+    return FISE_OK;
+}
+
 template <int KD, int DB, bool EXACT>
 static void launch_at(const void* q, const void* K, const void* Vt, int B, int M, int n_keys, int n_stride, int C, int heads,
                       int d, float scale, int splits, void* out, float* part_o, float* part_ml, hipStream_t st) {
@@ -568,7 +871,13 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
                       2.0 * ((double)B * n_keys * C * 2 + 2.0 * B * M * C), st);
 #define FISE_AT(KDV, DBV) launch_at<KDV, DBV, false>(q, K, Vt, B, M, n_keys, n_stride, C, heads, d, scale, splits, out, part_o, part_ml, st)
 #define FISE_AT_EXACT(KDV, DBV) launch_at<KDV, DBV, true>(q, K, Vt, B, M, n_keys, n_stride, C, heads, d, scale, splits, out, part_o, part_ml, st)
-    if (kd <= 1) FISE_AT(1, 1);
+#define FISE_AT_TURNS(DV) { if (int e = launch_turns<DV>(q, K, Vt, B, M, n_keys, n_stride, C, heads, scale, splits, out, part_o, part_ml, st)) return e; }
+    if (attention_turns(n_keys, n_stride, d, splits)) {
+        if (d == 40) FISE_AT_TURNS(40)
+        else if (d == 80) FISE_AT_TURNS(80)
+        else FISE_AT_TURNS(160)
+    }
+    else if (kd <= 1) FISE_AT(1, 1);
     else if (kd == 2) FISE_AT(2, 1);
     else if (kd == 3) FISE_AT(3, 2);
     else if (kd == 4) FISE_AT(4, 2);
@@ -581,6 +890,7 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
     else return fail(FISE_ERR_SHAPE, "attention: head dim %d > 160", d);
 #undef FISE_AT
 #undef FISE_AT_EXACT
+#undef FISE_AT_TURNS
     }
     FISE_CHECK_LAUNCH("attention");
     if (splits > 1) {

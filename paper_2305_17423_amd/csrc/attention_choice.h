@@ -63,6 +63,13 @@ inline bool attention_few(int B, int M, int n_keys, int n_stride, int C, int hea
     return few < attention_us(B, M, n_keys, C, heads, splits);
 }
 
+// Whether a launch in `splits` parts runs on attention_turns_kernel: from eight key blocks a part on, below which its longer set-up (1.1 us) costs more than its
+// turns save (a quarter of their cycles): 2 x 4096 queries of 8 x 40, 256 keys 10.1 and 10.8 us, 512 keys 16.0 and 15.5.  Heads of 104 and 128 would lose (2 x 700 x 1500 of 4 x
+// 104 31 and 33 us).  Its offsets reach over sixteen value rows in 32 bits.
+inline bool attention_turns(int n_keys, int n_stride, int d, int splits) {
+    return splits > 0 && (d == 40 || d == 80 || d == 160) && at_ceil(at_ceil(n_keys, AT_BKV), splits) >= 8 && n_stride < 1 << 27;
+}
+
 // Form of a launch: 0 attention_few_kernel (one launch whatever the key range), else the key splits of attention_kernel.
 inline int attention_form(int B, int M, int n_keys, int n_stride, int C, int heads, bool scratch) {
     const int most = scratch ? attention_splits(B, M, n_keys, C, heads) : 1;         // what the scratch is laid out for

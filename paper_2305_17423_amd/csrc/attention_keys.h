@@ -14,6 +14,38 @@ constexpr int AT_BKV = 64;        // keys per block
 constexpr int at_key_shift(int k0, int last, int key) { return k0 + (last < key ? last - key : 0); }
 constexpr int at_value_shift(int k0, int last, int key) { return at_key_shift(k0, last & ~7, key); }
 
+// ---- attention_turns_kernel: turns of 64 keys (wide heads: 32), brought into LDS by loads of 64 pieces of 16 bytes.  D: the head dim.
+template <int D> struct AtTile {
+    static constexpr int KD = (D + 15) / 16, DB = (D + 31) / 32, NB = KD <= 5 ? 2 : 1, BK = 32 * NB;      // 16-wide steps and 32-row blocks of the head dim, 32-key blocks and keys of a turn
+    // Pieces of 16 bytes of a key's and of a value row in LDS.  Odd numbers: sixteen rows meet no bank twice (value rows of wider heads, which leave no
+    // room for that, are swizzled).
+    static constexpr int PITCH = D / 8 | 1, VPITCH = KD <= 3 ? 4 * NB + 1 : 4 * NB;
+    static constexpr int swizzle(int r) { return NB == 2 ? r >> 1 & 7 : r >> 2 & 3; }          // slot p of a value row holds piece p ^ swizzle
+    static constexpr int KL = (BK * PITCH + 63) / 64, VL = (D * VPITCH + 63) / 64;             // loads of 64 pieces of a turn's keys, values
+    static constexpr int KB = KL * 1024, VB = VL * 1024, LPW = (KL + VL + 3) / 4;              // LDS of a turn's keys, values; loads of a wave
+    static constexpr int AHEAD = KD <= 3 ? 3 : 2, KR = AHEAD + 1, VR = AHEAD + 2;              // turns whose loads are in flight; ring slots
+    // Zeros behind the rings: the head's last 16-wide step where half of it lies past the head, value rows past the head.
+    static constexpr int PAD = D % 16, TAIL = D % 32, KEYS = VR * VB, ZERO = KEYS + KR * KB, LDS = ZERO + (TAIL ? 64 * NB : 0);
+
+    // What a lane reads, in bytes from the load's base (head h of the turn's first key; row value_row of the head at that key), `last` the turn's last
+    // existing key.  LDS row r of a turn holds key (r & 3) + 4 (r / 8 % 2) + 8 (r / 4 % 2) + 16 (r / 16): a lane's eight scores of a 16-key
+    // step are eight consecutive keys, the operand of the second product as they stand.
+    static constexpr int low(int a, int b) { return a < b ? a : b; }
+    static constexpr unsigned key_offset(int slot, int last, int C) {
+        const int r = low(slot / PITCH, BK - 1), c = low(slot % PITCH, D / 8 - 1), key = (r & 3) + 4 * (r >> 3 & 1) + 8 * (r >> 2 & 1) + (r & ~15);
+        return (unsigned)((key + at_key_shift(0, last, key)) * C + c * 8) * 2u;
+    }
+    static constexpr int value_row(int load) { return low(load * 64 / VPITCH, D - 1); }
+    static constexpr unsigned value_offset(int load, int lane, int last, int n_stride) {
+        const int slot = load * 64 + lane, r = slot / VPITCH, c = slot % VPITCH, key = (VPITCH % 2 ? low(c, 4 * NB - 1) : c ^ swizzle(r)) * 8;
+        return (unsigned)(low(r, D - 1) - value_row(load)) * (unsigned)n_stride * 2u + (unsigned)(key + at_value_shift(0, last, key)) * 2u;
+    }
+};
+// Turn that a load reads next, `next` being that of the keys now: they run one turn ahead of the values, of which the first group of loads has none.
+// (Past the last one: the last one again.)
+constexpr int AT_STAYS = 1 << 30;
+constexpr int at_next_turn(bool keys, bool first, int next) { return keys ? next + 1 : first ? AT_STAYS : next; }
+
 // ---- attention_few_kernel: blocks of 32 keys, read through buffer descriptors.  What a lane reads is its own offset behind the descriptor's base,
 // with no scalar offset: a load is dropped (zeros) where the lane offset is not below the descriptor's size, and how a scalar offset takes part
 // in that comparison, above all one that is past the size by itself, need not be known.  Bytes; h: the head; d: its channels.

@@ -70,7 +70,7 @@ def kind_of(name: str):
         return "igemm_kernel<...> (GroupNorm prologue)"
     if "attention_merge" in n:
         return "attention_merge_kernel"
-    if "attention_kernel" in n or "attention_few_kernel" in n:
+    if "attention_kernel" in n or "attention_few_kernel" in n or "attention_turns_kernel" in n:
         return "attention_kernel / attention_few_kernel"
     return None
 

@@ -71,3 +71,19 @@ def test_forms_of_the_partial_key_blocks(forms):
         for N in attention.PARTIAL_N:
             assert of(520, 8, d, N) == 1, (d, N)
         assert of(35, 2, d, 65) == 0 and of(35, 2, d, 120) == 0 and (d == 160 or of(35, 2, d, 9) == 0), d
+
+
+def test_long_key_ranges_run_in_turns(tmp_path):
+    """attention_turns_kernel has the cases of test_attention_long_key_ranges, in one part and in several, and nothing of other heads or of few key blocks."""
+    (tmp_path / "turns.cpp").write_text('#include <cstdio>\n#include "%s/attention_choice.h"\nint main() { int M, n, d; while (std::scanf("%%d %%d %%d", &M, &n, &d) == 3) for (int ws = 0; ws < 2; ++ws) {'
+                                        ' const int s = fise::attention_form(2, M, n, (n + 7) / 8 * 8, 8 * d, 8, ws); std::printf("%%d %%d\\n", s, fise::attention_turns(n, (n + 7) / 8 * 8, d, s)); } }' % build.CSRC)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(tmp_path / "turns"), str(tmp_path / "turns.cpp")], check=True)
+
+    def run(shapes):
+        r = subprocess.run([str(tmp_path / "turns")], input="\n".join(f"{M} {N} {d}" for d, N, M in shapes), check=True, capture_output=True, text=True)
+        return [tuple(map(int, l.split())) for l in r.stdout.splitlines()]
+    forms = run(attention.TURNS)
+    for d in (40, 80, 160):
+        of = [f for t, pair in zip(attention.TURNS, zip(forms[::2], forms[1::2])) if t[0] == d for f in pair]
+        assert (1, 1) in of and any(s > 1 and turns for s, turns in of), (d, of)
+    assert not any(turns for _, turns in run([(d, 447, 600) for d in (40, 80, 160)] + [(d, 2000, 600) for d in (32, 64, 104, 128, 152)]))

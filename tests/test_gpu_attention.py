@@ -114,6 +114,27 @@ def test_attention_partial_key_blocks(fb, d, N, M, heads):
     assert rel_err(host(out), want) <= TOL["bf16"]
 
 
+# Long key ranges of heads of 40, 80 and 160 (attention_turns_kernel; test_attention_splits.py says so), in one part and in several: whole turns, a last turn of
+# one key, of one more than a 32-key block and of all but one; queries on both sides of a tile of 128.
+TURNS = [(40, 512, 513), (40, 513, 1500), (40, 545, 1500), (40, 2199, 600), (40, 4160, 257), (80, 512, 640), (80, 513, 513), (80, 545, 600), (80, 1087, 700),
+         (160, 512, 513), (160, 513, 640), (160, 545, 600), (160, 1087, 700), (160, 2199, 513)]
+
+
+@pytest.mark.parametrize("d,N,M", TURNS)
+def test_attention_long_key_ranges(fb, d, N, M):
+    rng = np.random.default_rng(4070 + d + N)
+    B, heads = 2, 8
+    C = d * heads
+    q = wl.normal(rng, (B, M, C), 1.0, "bf16"); K = wl.normal(rng, (B, N, C), 1.0, "bf16"); V = wl.normal(rng, (B, N, C), 1.0, "bf16")
+    want = fo.attention_active(q, K, V, heads)
+    Vd = vt_dev(V, (N + 7) // 8 * 8 + 8, poison=True)
+    for scratch in (False, True):
+        ws = torch.full((max(fb.fise_attention_active_workspace_bytes(B, M, N, C, heads), 256),), 0x7F, dtype=torch.uint8, device=DEV) if scratch else None
+        out = torch.zeros((B, M, C), dtype=torch.bfloat16, device=DEV)
+        fb.fise_attention_active(dev(q, "bf16"), dev(K, "bf16"), Vd, heads, 1 / math.sqrt(d), out, n_keys=N, workspace=ws)
+        assert rel_err(host(out), want) <= TOL["bf16"], scratch
+
+
 def test_attention_closed_forms_on_device(fb):
     rng = np.random.default_rng(4100)
     B, M, N, C, heads = 1, 40, 300, 320, 8
