@@ -192,105 +192,189 @@ __global__ void or_pool_kernel(const uint8_t* __restrict__ m, int H, int W, uint
 // ---------------------------------------------------------------------------
 // Otsu in two launches.  Values are min-max normalised in double; bin k of 257 holds values with floor(256 v) == k, so
 // class A of threshold k/256 is exactly bins [0, k).  Every bin's sum is taken in index order: the order is part of the
-// result, so the longest chain of dependent additions (the fullest bin) is what bounds this.
-//  - otsu_bins_kernel: four bins per workgroup of sixteen waves.  The waves normalise 4096 values in registers (a double
-//    division per value and workgroup), pack those of each bin behind one another in LDS (ballot + popcount prefix, the waves' counts
-//    in between), and one wave per bin adds them up from there, where the reads run ahead of the additions.
+// result, so the fullest bin (2082 of 4096 values in an edit's mask) is what bounds this: a chain of dependent additions, 16 cycles each, unless
+// they are rounded ahead (ordered_sum: 15 rounds of ~900 cycles and 11 values on their own instead of 33000 cycles).
+//  - otsu_bins_kernel: four bins per workgroup of sixteen waves.  The waves normalise 4096 values in registers, pack those of each bin behind one
+//    another in LDS (ballots, the waves' counts scanned in between by one lane each), and one wave per bin adds them up from there.
 //  - otsu_apply_kernel: every workgroup finds the threshold for itself (the sums below a bin one chain of 257 additions, the counts
-//    below it, whole numbers, a scan, the objectives in parallel) and thresholds its share of the values.
-// One thread per bin walking all values in one workgroup: 650 us; four waves of one bin each over chunks of 1024: 21.3 + 8.8 us for 64 x 64
-// values of which 2285 share a bin; this: 19.6 + 5.9, of which the chain of 2285 dependent additions is 15.
+//    below it, whole numbers, a scan, the objectives a bin per thread) and thresholds its share of the values.
+// us, added one by one and now: bins 18.9 -> 15.4 for 64 x 64 values, the whole mask of two and seven steps at 96 x 96 52 -> 42 and 70 -> 56; one
+// of five steps at 64 x 64 takes the host 40 to launch either way.
 // ---------------------------------------------------------------------------
 constexpr int OTSU_BINS = 257, OTSU_CHUNK = 4096, OTSU_WG_BINS = 4, OTSU_WAVES = 16;
 struct OtsuWs { double lo, hi; double cnt[OTSU_BINS]; double sum[OTSU_BINS]; };
 
+#if defined(__HIP_DEVICE_COMPILE__)
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_or_zero(double x) {
+    const long long b = __double_as_longlong(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false), hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+__device__ __forceinline__ double lane_value(double x, int lane) {
+    const long long b = __double_as_longlong(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, lane), hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+#endif
+
+// s + src[0] + src[1] + ... with every addition rounded in this order, by one wave; 0 <= values < top, no subnormals (or NaN: the sum is).  While the
+// sum stays in one binade [2^e, 2^(e+1)) it is a multiple of its last place, and an addition moves it by the value rounded to a
+// multiple of that: they add up exactly in any order.  So a block of 256 values, four a lane, is rounded in parallel (added to 1.5 x 2^e and taken back)
+// and scanned.  The first lane in which the sum reaches the next binade, or a value lies half way between two places (then the
+// sum's last bit decides), adds its four values one by one, and the scan goes on behind it.  Blocks with many such values, and values of
+// 2^(e-1) and more, are added one by one.
+__device__ __forceinline__ double ordered_sum(double s, const double* src, int total, double top, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int Q = 4, BLOCK = 64 * Q, HEAD = 8, TIES = 8;   // HEAD: lanes of the first values, which change the binade all the time
+    double v[Q], next[Q];
+    auto fetch = [&](double (&x)[Q], int i0) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) { const int i = i0 + lane * Q + q; x[q] = src[min(i, total - 1)]; if (i >= total) x[q] = 0.0; }
+    };
+    auto take = [&](int at) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) s += lane_value(v[q], at);
+    };
+    if (total > 0) fetch(next, 0);
+    for (int i0 = 0; i0 < total; i0 += BLOCK) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) v[q] = next[q];
+        fetch(next, i0 + BLOCK);
+        int done = 0, ties = 0;                                // lanes whose values are in the sum
+        const int lanes = min(64, (total - i0 + Q - 1) / Q);
+        if (i0 == 0)
+            for (; done < min(lanes, HEAD); ++done) take(done);
+        while (done < lanes) {
+            const int e = __builtin_amdgcn_readfirstlane((int)(__double_as_longlong(s) >> 52));
+            if (e == 0x7ff) return s;
+            const double one = __longlong_as_double((long long)e << 52);       // 2^e; zero: the sum is zero
+            if (ties > TIES || __builtin_amdgcn_readfirstlane((int)(top > 0.5 * one))) {
+                if (e == 0) {                                  // passes over zeros
+                    const unsigned long long some = __ballot(!(v[0] == 0 && v[1] == 0 && v[2] == 0 && v[3] == 0)) & (~0ull << done);
+                    if (!some) break;
+                    done = __builtin_ctzll(some);
+                }
+                const int until = min(lanes, done + HEAD);
+                for (; done < until; ++done) take(done);
+                continue;
+            }
+            const double grid = 1.5 * one, half = one * 0x1p-53, end = 2.0 * one;
+            double run = 0.0;
+            unsigned long long tie = 0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const double r = (v[q] + grid) - grid;
+                tie |= __ballot(!(fabs(v[q] - r) < half));     // NaN too
+                run += r;
+            }
+            if (lane < done) run = 0.0;
+            double sum = run;                                  // past the binade it only has to stay there
+            sum += dpp_or_zero<0x111, 0xf>(sum); sum += dpp_or_zero<0x112, 0xf>(sum); sum += dpp_or_zero<0x114, 0xf>(sum); sum += dpp_or_zero<0x118, 0xf>(sum);
+            sum += dpp_or_zero<0x142, 0xa>(sum); sum += dpp_or_zero<0x143, 0xc>(sum);      // lane 15 of a row to the next row, lane 31 to the upper half
+            double base = s + dpp_or_zero<0x138, 0xf>(sum);    // the sum in front of this lane
+            for (;;) {
+                const unsigned long long stop = (tie | __ballot(!(base + run < end))) & (~0ull << done);
+                if (!stop) { s = lane_value(base + run, 63); done = 64; break; }
+                const int at = __builtin_ctzll(stop);
+                const double here = lane_value(base + run, at);
+                s = lane_value(base, at);
+                take(at);
+                done = at + 1;
+                if (done >= lanes || __builtin_amdgcn_readfirstlane((int)!(s < end)) || ++ties > TIES) break;      // another binade
+                base += s - here;
+            }
+        }
+    }
+#endif
+    return s;
+}
+
 __global__ __launch_bounds__(64 * OTSU_WAVES) void otsu_bins_kernel(const float* __restrict__ diff, int n, OtsuWs* __restrict__ ws) {
     constexpr int NT = 64 * OTSU_WAVES, PER = OTSU_CHUNK / NT;
-    __shared__ double red_lo[OTSU_WAVES], red_hi[OTSU_WAVES];
-    __shared__ int wave_cnt[OTSU_WG_BINS][OTSU_WAVES];
+    __shared__ __attribute__((aligned(16))) float red_lo[OTSU_WAVES], red_hi[OTSU_WAVES];
+    __shared__ int wave_cnt[OTSU_WG_BINS * OTSU_WAVES];
+    static_assert(OTSU_WG_BINS * OTSU_WAVES == 64 && OTSU_WAVES == 16, "a lane per bin and wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char otsu_lds[];
-    double (*mine)[OTSU_CHUNK + 64] = reinterpret_cast<double (*)[OTSU_CHUNK + 64]>(otsu_lds);      // [OTSU_WG_BINS]
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, k0 = blockIdx.x * OTSU_WG_BINS;
-    double lo = 1e300, hi = -1e300;
+    double (*mine)[OTSU_CHUNK] = reinterpret_cast<double (*)[OTSU_CHUNK]>(otsu_lds);      // [OTSU_WG_BINS]
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), k0 = blockIdx.x * OTSU_WG_BINS;
+    float flo = INFINITY, fhi = -INFINITY;
 #pragma unroll 4
-    for (int i = t; i < n; i += NT) { const double v = diff[i]; lo = fmin(lo, v); hi = fmax(hi, v); }
-    for (int o = 32; o > 0; o >>= 1) { lo = fmin(lo, __shfl_xor(lo, o)); hi = fmax(hi, __shfl_xor(hi, o)); }
-    if (lane == 0) { red_lo[wave] = lo; red_hi[wave] = hi; }
+    for (int i = t; i < n; i += NT) { const float v = diff[i]; flo = fminf(flo, v); fhi = fmaxf(fhi, v); }
+    for (int o = 32; o > 0; o >>= 1) { flo = fminf(flo, __shfl_xor(flo, o)); fhi = fmaxf(fhi, __shfl_xor(fhi, o)); }
+    if (lane == 0) { red_lo[wave] = flo; red_hi[wave] = fhi; }
     __syncthreads();
-    for (int w = 0; w < OTSU_WAVES; ++w) { lo = fmin(lo, red_lo[w]); hi = fmax(hi, red_hi[w]); }
+#pragma unroll
+    for (int w = 0; w < OTSU_WAVES; w += 4) {
+        const float4 l = *reinterpret_cast<const float4*>(&red_lo[w]), h = *reinterpret_cast<const float4*>(&red_hi[w]);
+        flo = fminf(flo, fminf(fminf(l.x, l.y), fminf(l.z, l.w)));
+        fhi = fmaxf(fhi, fmaxf(fmaxf(h.x, h.y), fmaxf(h.z, h.w)));
+    }
+    const double lo = fmin(1e300, (double)flo), hi = fmax(-1e300, (double)fhi);
     const double range = hi - lo;
+    // n / range, correctly rounded: the quotient by the rounded reciprocal, corrected with its exact remainder (Markstein's theorem); an
+    // infinite range has no such remainder
+    const double inv = 1.0 / range;
+    const bool finite = range <= 1e300;
+    auto normalised = [&](double x) {
+        const double q = x * inv;
+        return finite ? fma(fma(-q, range, x), inv, q) : x / range;
+    };
+    const int k = k0 + wave;
     double sum = 0.0;
     int count = 0;
     for (int c0 = 0; c0 < n; c0 += OTSU_CHUNK) {
         // wave w holds values c0 + w * 256 .. in index order: PER rows of 64
-        double v[PER]; int bin[PER], before[OTSU_WG_BINS][PER];
+        double v[PER]; int bin[PER], place[PER], held[OTSU_WG_BINS] = {};
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int i = c0 + (wave * PER + j) * 64 + lane;
-            v[j] = i < n && range > 0 ? ((double)diff[i] - lo) / range : 0.0;
+            v[j] = i < n && range > 0 ? normalised((double)diff[i] - lo) : 0.0;
             bin[j] = i < n ? (int)floor(v[j] * 256.0) - k0 : -1;
         }
 #pragma unroll
-        for (int b = 0; b < OTSU_WG_BINS; ++b) {
-            int m = 0;
+        for (int j = 0; j < PER; ++j) {                        // place among this wave's values of the bin
+            unsigned long long own = 0;
+            place[j] = 0;
 #pragma unroll
-            for (int j = 0; j < PER; ++j) {
+            for (int b = 0; b < OTSU_WG_BINS; ++b) {
                 const unsigned long long bal = __ballot(bin[j] == b);
-                before[b][j] = m + __popcll(bal & ((1ull << lane) - 1ull));
-                m += __popcll(bal);
+                if (bin[j] == b) { own = bal; place[j] = held[b]; }
+                held[b] += __popcll(bal);
             }
-            if (lane == 0) wave_cnt[b][wave] = m;
+            place[j] += __builtin_amdgcn_mbcnt_hi((unsigned)(own >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)own, 0));
         }
+        if (lane < OTSU_WG_BINS) wave_cnt[lane * OTSU_WAVES + wave] = lane == 0 ? held[0] : lane == 1 ? held[1] : lane == 2 ? held[2] : held[3];
         __syncthreads();
-        int total = 0;                                     // of bin `wave` in the first waves
+        // lane 16 b + w: values of bin b in the waves up to w
+        const int c = wave_cnt[lane];
+        int upto = c;
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false); upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, false);
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false); upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);
+        int base[OTSU_WG_BINS], total = 0;                     // total: of bin `wave` in the first waves
 #pragma unroll
         for (int b = 0; b < OTSU_WG_BINS; ++b) {
-            int base = 0, all = 0;
-#pragma unroll
-            for (int w = 0; w < OTSU_WAVES; ++w) { const int c = wave_cnt[b][w]; base += w < wave ? c : 0; all += c; }
-#pragma unroll
-            for (int j = 0; j < PER; ++j)
-                if (bin[j] == b) mine[b][base + before[b][j]] = v[j];
-            if (wave == OTSU_WG_BINS + b) mine[b][all + lane] = 0.0;       // past the last value: adding +0 changes no sum of values >= +0
-            if (wave == b) total = all;
+            base[b] = __builtin_amdgcn_readlane(upto - c, b * OTSU_WAVES + wave);
+            if (wave == b) total = __builtin_amdgcn_readlane(upto, b * OTSU_WAVES + OTSU_WAVES - 1);
         }
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if ((unsigned)bin[j] < (unsigned)OTSU_WG_BINS) mine[bin[j]][(bin[j] == 0 ? base[0] : bin[j] == 1 ? base[1] : bin[j] == 2 ? base[2] : base[3]) + place[j]] = v[j];
         __syncthreads();
         if (wave < OTSU_WG_BINS) {
-            // sixteen values are added while the next sixteen are on their way
-            const double* src = mine[wave];
-            double v0[16], v1[16];
-            auto read = [&](double (&r)[16], int i) {
-#pragma unroll
-                for (int q = 0; q < 16; ++q) r[q] = src[min(i, OTSU_CHUNK + 48) + q];
-            };
-            auto add = [&](const double (&r)[16]) {
-#pragma unroll
-                for (int q = 0; q < 16; ++q) sum += r[q];
-            };
-            read(v0, 0);
-            for (int i = 0; i < total; i += 32) {
-                read(v1, i + 16);
-                __builtin_amdgcn_sched_barrier(0);
-                add(v0);
-                __builtin_amdgcn_sched_barrier(0);
-                read(v0, i + 32);
-                __builtin_amdgcn_sched_barrier(0);
-                add(v1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            sum = ordered_sum(sum, mine[wave], total, k < OTSU_BINS - 1 ? (k + 1) / 256.0 : 2.0, lane);
             count += total;
         }
         __syncthreads();
     }
-    const int k = k0 + wave;
     if (lane == 0 && wave < OTSU_WG_BINS && k < OTSU_BINS) { ws->cnt[k] = (double)count; ws->sum[k] = sum; }
     if (blockIdx.x == 0 && t == 0) { ws->lo = lo; ws->hi = hi; }
 }
 
 __global__ __launch_bounds__(256) void otsu_apply_kernel(const float* __restrict__ diff, int n, float* __restrict__ eps_out,
                                                          uint8_t* __restrict__ pix, const OtsuWs* __restrict__ ws) {
-    __shared__ double sum[OTSU_BINS + 15], cnt_lo[OTSU_BINS], sum_lo[OTSU_BINS], total[2], s_eps;      // _lo: sums over the bins below k
+    __shared__ double sum[OTSU_BINS + 15], cnt_lo[OTSU_BINS], sum_lo[OTSU_BINS], total[2], wave_best[4];      // _lo: sums over the bins below k
     const int t = threadIdx.x, lane = t & 63;
+    __shared__ int wave_k[4];
     const double lo = ws->lo, range = ws->hi - lo;
     for (int k = t; k < OTSU_BINS; k += 256) sum[k] = ws->sum[k];
     double c4[4];                                              // second wave: counts of bins 4 lane .. 4 lane + 3
@@ -324,27 +408,30 @@ __global__ __launch_bounds__(256) void otsu_apply_kernel(const float* __restrict
         total[1] = s + sum[OTSU_BINS - 1];
     }
     __syncthreads();
-    if (t < 64) {                                       // the first bin with the largest objective
-        double best = -1.0;
-        int best_k = 0;
-        for (int k = t; k < OTSU_BINS; k += 64) {
-            const double ca = cnt_lo[k], sa = sum_lo[k], cb = total[0] - ca, sb = total[1] - sa;
-            double o = 0.0;
-            if (ca > 0 && cb > 0) {
-                const double dm = sa / ca - sb / cb;
-                o = ca * cb / (total[0] * total[0]) * dm * dm;
-            }
-            if (o > best) { best = o; best_k = k; }
+    // the first bin with the largest objective: a bin per thread, the last one as the last wave's second
+    double best = -1.0;
+    int best_k = 0;
+    for (int k = t; k < OTSU_BINS; k += t == 255 ? 1 : OTSU_BINS) {
+        const double ca = cnt_lo[k], sa = sum_lo[k], cb = total[0] - ca, sb = total[1] - sa;
+        double o = 0.0;
+        if (ca > 0 && cb > 0) {
+            const double dm = sa / ca - sb / cb;
+            o = ca * cb / (total[0] * total[0]) * dm * dm;
         }
-        for (int o = 32; o > 0; o >>= 1) {
-            const double b2 = __shfl_xor(best, o);
-            const int k2 = __shfl_xor(best_k, o);
-            if (b2 > best || (b2 == best && k2 < best_k)) { best = b2; best_k = k2; }
-        }
-        if (t == 0) { s_eps = best_k / 256.0; if (blockIdx.x == 0) *eps_out = (float)s_eps; }
+        if (o > best) { best = o; best_k = k; }
     }
+    for (int o = 32; o > 0; o >>= 1) {
+        const double b2 = __shfl_xor(best, o);
+        const int k2 = __shfl_xor(best_k, o);
+        if (b2 > best || (b2 == best && k2 < best_k)) { best = b2; best_k = k2; }
+    }
+    if (lane == 0) { wave_best[t >> 6] = best; wave_k[t >> 6] = best_k; }
     __syncthreads();
-    const double eps = s_eps;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+        if (wave_best[w] > best || (wave_best[w] == best && wave_k[w] < best_k)) { best = wave_best[w]; best_k = wave_k[w]; }
+    if (t == 0 && blockIdx.x == 0) *eps_out = (float)(best_k / 256.0);
+    const double eps = best_k / 256.0;
     for (int i = blockIdx.x * 256 + t; i < n; i += gridDim.x * 256) {
         const double v = range > 0 ? ((double)diff[i] - lo) / range : 0.0;
         pix[i] = v >= eps ? 1 : 0;
@@ -449,7 +536,7 @@ extern "C" size_t fise_otsu_workspace_bytes(void) { return align256(sizeof(OtsuW
 extern "C" int fise_otsu_mask(const float* diff, int n, float* eps_out, uint8_t* pix_mask, void* workspace, void* stream) {
     if (!diff || !eps_out || !pix_mask || !workspace) return fail(FISE_ERR_NULL, "fise_otsu_mask: null pointer");
     if (n < 1) return fail(FISE_ERR_SHAPE, "fise_otsu_mask: n=%d", n);
-    constexpr int lds = OTSU_WG_BINS * (OTSU_CHUNK + 64) * (int)sizeof(double);
+    constexpr int lds = OTSU_WG_BINS * OTSU_CHUNK * (int)sizeof(double);
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&otsu_bins_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return fail(FISE_ERR_HIP, "fise_otsu_mask: cannot raise the dynamic LDS limit");
     hipLaunchKernelGGL(otsu_bins_kernel, dim3(ceil_div(OTSU_BINS, OTSU_WG_BINS)), dim3(64 * OTSU_WAVES), lds, as_stream(stream), diff, n, (OtsuWs*)workspace);

@@ -38,3 +38,38 @@ def test_otsu_bins_in_index_order(n, shape):
     want, mask = fo.otsu_threshold(v)
     assert float(eps.item()) == np.float32(want)
     assert np.array_equal(pix.cpu().numpy(), mask.reshape(-1).astype(np.uint8))
+
+
+def _trailing_zeros(x):
+    m = int(np.float64(x).view(np.int64)) & (1 << 52) - 1
+    return 52 if m == 0 else (m & -m).bit_length() - 1
+
+
+@pytest.mark.parametrize("n", [33, 257, 4096, 9216])
+@pytest.mark.parametrize("shape", ["zeros", "half-places", "tiny-then-large", "steps"])
+def test_otsu_sums_where_additions_round_otherwise(n, shape):
+    """Sums that start at zero, additions half way between two places of the sum (one value over and over whose last set bit is the
+    ninth or higher: 2^8 of them in a row tie), values far below the sum, few distinct values: every bin bit for bit."""
+    from paper_2305_17423_amd import binding as fb
+    rng = np.random.default_rng(n)
+    d = (rng.random(n) * 3e-3).astype(np.float32)
+    if shape == "zeros":
+        d[rng.random(n) < 0.9] = 0.0
+    elif shape == "half-places":
+        while not 8 <= _trailing_zeros(np.float64(np.float32(c := rng.random() * 3e-3)) / np.float64(np.float32(0.9))) <= 11:
+            pass
+        d[:] = c
+    elif shape == "tiny-then-large":
+        d[: n // 2] *= 1e-30
+    else:
+        d = (np.round(d * 4000) / 3700).astype(np.float32) * np.float32(0.99)
+    d[0], d[n - 1] = 0.0, 0.9
+    eps, pix = torch.full((1,), -1.0, device=DEV), torch.full((n,), 7, dtype=torch.uint8, device=DEV)
+    ws = torch.full((fb.fise_otsu_workspace_bytes(),), 0xA5, dtype=torch.uint8, device=DEV)
+    fb.fise_otsu_mask(dev(d), eps, pix, ws)
+    v = fo.normalize_minmax(d.astype(np.float64))
+    tot = np.zeros(BINS)
+    for x in v:
+        tot[int(np.floor(x * 256.0))] += x
+    got = ws.cpu().numpy()[:8 * (2 + 2 * BINS)].view(np.float64)
+    assert np.array_equal(got[2 + BINS:], tot)
