@@ -95,6 +95,22 @@ inline int linear_tile(int rows, int N) {
     return (rows + 63) / 64 * columns <= 256 ? 2 : 4;
 }
 
+// ---- rows_group.hip: row tiles of 32 a workgroup takes, 0: the tiles of wave_gemm.hip.  One workgroup runs per CU; a round costs its start and epilogue (as
+// much as the operands of 290 rows of stages) and the rows of both operands that it loads.  The smaller tiles of wave_gemm.hip fill the chip where
+// there are few columns: their time goes with the number of columns, a round's does not (24960 columns, 154 rows: 24.0 and 15.5 us).
+constexpr int GROUP_UNITS = 7;               // units of 16 columns of a workgroup
+inline int group_tile(int rows, int cols) {
+    constexpr int kTiles[] = {1, 2, 3, 5, 7};
+    const long long groups = (cols / 16 + GROUP_UNITS - 1) / GROUP_UNITS;
+    int best = 0; double least = 1e30;
+    for (const int rt : kTiles) {
+        const long long wgs = (rows + 32 * rt - 1) / (32 * rt) * groups;
+        const double t = (double)((wgs + 255) / 256) * (290 + 32 * rt + 16 * GROUP_UNITS);
+        if (t < least) { least = t; best = rt; }
+    }
+    return groups >= 160 ? best : 0;
+}
+
 // ---- norm_gemm.hip
 constexpr int NG_WAVES = 8, NG_LDS_MAX = 160 * 1024, NG_BIAS = 5120;      // bytes of bias of a workgroup: 80 units of 32 columns
 

@@ -146,6 +146,9 @@ constexpr int GEMM_GROUP = 32;           // products of one launch
 struct GemmGroup { int first[GEMM_GROUP], N[GEMM_GROUP], mode[GEMM_GROUP]; const bf16_t* w[GEMM_GROUP]; bf16_t* out[GEMM_GROUP]; };    // first: column tile where a product starts
 // base: compact rows, K and geometry; its weights, width and destinations are the products'.  One launch where the sizes allow it.
 int launch_igemm_group(const IgemmArgs& base, const GemmProduct* p, int n, hipStream_t st);
+// The same on tiles of up to 160 rows x 112 columns that may straddle products (rows_group.hip).
+bool rows_group_takes(const IgemmArgs& base, const GemmProduct* p, int n);
+int launch_rows_group(const IgemmArgs& base, const GemmProduct* p, int n, hipStream_t st);
 bool wave_gemm_takes(const IgemmArgs& a);
 int launch_wave_gemm(IgemmArgs a, const IgemmWorkspace* ws, hipStream_t st);
 // 3x3 convolution on tiles of 32 * tm rows x 80 columns (conv_patch.hip; tm 2 or 4, tiles of edge 4 or 8, N a multiple of 80); called with the launcher's fields set.

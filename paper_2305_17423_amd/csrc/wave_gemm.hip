@@ -881,8 +881,8 @@ static int launch_patches(const IgemmArgs& a, int tm, int tn, hipStream_t st) {
 }
 
 // The products of a group as one launch (no K split).  One by one they are a few dozen workgroups each that wait for one another's
-// launch: keys and values of 154 context tokens for 16 blocks (24960 columns) 85.3 -> 24.0 us, queries,
-// keys and values of 640 rows of 320 channels three launches of 4.7 -> one of 6.
+// launch: queries, keys and values of 640 rows of 320 channels three launches of 4.7 -> one of 6.  Many columns (keys and values of a prompt for all
+// blocks) belong to rows_group.hip.
 template <int TM, int TN, int NST, bool SHARED>
 static int launch_group_tile(const IgemmArgs& a, const GemmGroup& g, hipStream_t st) {
     constexpr int NW = 4, lds = (SHARED ? 1 : NW) * NST * (32 * TM + 32 * TN) * 128;
@@ -916,6 +916,7 @@ int launch_igemm_group(const IgemmArgs& base, const GemmProduct* p, int n, hipSt
         }
         return FISE_OK;
     }
+    if (rows_group_takes(a, p, n)) return launch_rows_group(a, p, n, st);
     a.N = cols;
     const TileChoice c = choose_tile(a, nullptr);
     GemmGroup g{};
