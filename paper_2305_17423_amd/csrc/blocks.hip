@@ -208,15 +208,21 @@ int run_transformer(const fise_transformer_args* a, void* workspace, const Igemm
     IgemmArgs o1 = lin(ob, C, a->o1_w, a->o1_b, C); into_h(o1); with_ln(o1, a->ln2_g, a->ln2_b);
     if (int e = launch_igemm(o1, iw, st)) return e;
     // cross-attention against the context K/V
-    if (fused) {
-        if (int e = launch_norm_gemm(normed(a->ln2_g, a->ln2_b, a->q2_w, C, qb), st)) return e;
+    if (fused && cross_takes(C, a->heads, a->n_ctx, a->n_ctx_stride, B, Ma, H * W)) {
+        const CrossArgs c{hb, hb, (const bf16_t*)a->ln2_g, (const bf16_t*)a->ln2_b, (const bf16_t*)a->q2_w, (const bf16_t*)a->o2_w, (const bf16_t*)a->o2_b,
+                          (const bf16_t*)a->K_ctx, (const bf16_t*)a->Vt_ctx, 1e-5f, a->n_ctx, a->n_ctx_stride, B, Ma, nullptr, 0, 0, 0, 0};
+        if (int e = launch_cross(c, st)) return e;
     } else {
-        IgemmArgs q2 = lin(nb, C, a->q2_w, nullptr, C); q2.out[0] = qb;
-        if (int e = launch_igemm(q2, iw, st)) return e;
+        if (fused) {
+            if (int e = launch_norm_gemm(normed(a->ln2_g, a->ln2_b, a->q2_w, C, qb), st)) return e;
+        } else {
+            IgemmArgs q2 = lin(nb, C, a->q2_w, nullptr, C); q2.out[0] = qb;
+            if (int e = launch_igemm(q2, iw, st)) return e;
+        }
+        if (int e = launch_attention(qb, a->K_ctx, a->Vt_ctx, B, Ma, a->n_ctx, a->n_ctx_stride, C, a->heads, scale, ob, nullptr, 0, st)) return e;
+        IgemmArgs o2 = lin(ob, C, a->o2_w, a->o2_b, C); into_h(o2); with_ln(o2, a->ln3_g, a->ln3_b);
+        if (int e = launch_igemm(o2, iw, st)) return e;
     }
-    if (int e = launch_attention(qb, a->K_ctx, a->Vt_ctx, B, Ma, a->n_ctx, a->n_ctx_stride, C, a->heads, scale, ob, nullptr, 0, st)) return e;
-    IgemmArgs o2 = lin(ob, C, a->o2_w, a->o2_b, C); into_h(o2); with_ln(o2, a->ln3_g, a->ln3_b);
-    if (int e = launch_igemm(o2, iw, st)) return e;
     // feed-forward: LN -> first GEMM with the GEGLU gate in its epilogue -> second GEMM + residual
     if (fused) {
         NormGemmArgs g = normed(a->ln3_g, a->ln3_b, a->ff1_w, 4 * C, fb);
@@ -358,6 +364,11 @@ extern "C" int fise_masked_attention(const void* x, const void* ln_gamma, const 
     bf16_t* nbuf = (bf16_t*)ws; bf16_t* qbuf = (bf16_t*)(ws + buf); bf16_t* obuf = (bf16_t*)(ws + 2 * buf);
     const float scale = 1.0f / sqrtf((float)d);
 
+    if (!self && cross_takes(C, heads, n_ctx, n_ctx_stride, B, Ma, H * W)) {
+        const CrossArgs c{x, y_cache, (const bf16_t*)ln_gamma, (const bf16_t*)ln_beta, (const bf16_t*)Wq, (const bf16_t*)Wo, (const bf16_t*)bo, (const bf16_t*)K_ctx,
+                          (const bf16_t*)Vt_ctx, 1e-5f, n_ctx, n_ctx_stride, B, Ma, tile_idx, tile, W / tile, W, H * W};
+        return launch_cross(c, st);
+    }
     const GemmProduct qkv[3] = {{(const bf16_t*)Wq, C, qbuf, OUT_COMPACT}, {(const bf16_t*)Wk, C, (bf16_t*)K_cache, OUT_MAP}, {(const bf16_t*)Wv, C, (bf16_t*)Vt_cache, OUT_TOKENS_T}};
     const int nprod = self ? 3 : 1;
     if (norm_gemm_takes(NG_MAP_LN, C, B, Ma, H, W)) {

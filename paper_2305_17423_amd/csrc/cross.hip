@@ -1,0 +1,366 @@
+// Cross-attention sub-layer of 320 channels and eight heads over the few keys of a prompt, as one launch:
+//
+//   y = x + Wo attention(Wq LN(x), K, V) + bo
+//
+// Everything behind the LayerNorm belongs to one row, so a workgroup takes 32 rows of a batch element from the normalisation to the sum, and nothing of
+// it goes through memory.  Eight waves, a head each:
+//  - The rows are normalised into LDS as bf16, every wave four of them.
+//  - A wave multiplies its head's 40 rows of Wq with them, then 40 rows of Wo with the heads' outputs: ten stages of 64 channels through a ring of
+//    its own (LDS-direct loads of eight rows of 128 bytes), so that the rows of Wo travel under the attention.  No barrier in between.
+//  - Queries, probabilities and outputs never leave the wave's registers: 16 x 16 x 32 products whose rows are numbered so that a result is the next
+//    product's operand (row r of a pair of tiles is channel, or key, 8 (r / 4) + r % 4, and that + 4).  Keys, values and the residual are requested up
+//    front.
+//  - The heads' outputs meet in the place of the normalised rows (the two barriers beside the one behind the normalisation).
+// Bound by the 500 KB a workgroup brings in (410 of weights at the ~60 GB/s that loads of eight rows get a CU, keys, values and residual in pieces of 64
+// bytes); first touches of the later stages' lines are worth 1.3 us with cold weights.  Against the three launches it stands for (normalisation and
+// queries, attention over 77 keys, product and sum), us: 640 rows of a map 15.5 -> 14.2, 1536 float rows 18.5 -> 14.4, 5504 27 -> 14.7, 8192 28 ->
+// 15.5; steps of 12 of 64 tiles 2247 -> 2214, 43 of 144 4152 -> 4112, dense pass 4950 -> 4878.
+#include <cmath>
+#include <type_traits>
+#include "igemm.h"
+#include "profile.h"
+
+namespace fise {
+
+struct CrossDev {
+    CrossArgs a;
+    int gx; float scale_log2e;
+    FastDiv d_gx, d_tt, d_tile, d_tiles_w;
+};
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// over the four lanes l16, l16 + 16, + 32, + 48
+__device__ __forceinline__ float quad_max(float x) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+template <int CTRL> __device__ __forceinline__ float row_dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_sum(float x) {        // over aligned groups of 16 lanes
+    x += row_dpp<0xB1>(x); x += row_dpp<0x4E>(x); x += row_dpp<0x141>(x); x += row_dpp<0x140>(x);
+    return x;
+}
+#endif
+
+// MAP: rows are pixels of bf16 maps (in and out), else compact float rows, updated in place.
+template <bool MAP>
+__global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int C = CROSS_C, D = C / CROSS_HEADS, BM = 32, PITCH = 2 * C, ND = 3, PIECES = D / 8, STAGE = D * 128, NT = CROSS_KEYS / 16, TOUCH = 2;
+    constexpr unsigned OOB = 0x80000000u;
+    static_assert(D == 40 && NT == 5, "numbering of rows and keys");
+    const CrossArgs& a = g.a;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    unsigned char* const ring = lds + BM * PITCH;
+    int* const rowpix = reinterpret_cast<int*>(ring + CROSS_HEADS * ND * STAGE);
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // every XCD gets a contiguous run of row tiles
+    const int chunk = (int)gridDim.x >> 3;
+    int w = blockIdx.x;
+    if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
+    const int b = (int)fdiv((unsigned)w, g.d_gx), m0 = (w - b * g.gx) * BM;
+
+    // ---- rows: sixteen lanes a row, five pieces of four channels each
+    const int row = wave * 4 + lq;
+    const unsigned i_row = (unsigned)min(m0 + row, a.Ma - 1);
+    f32x4_t v[5];
+    if constexpr (MAP) {
+        const unsigned t = fdiv(i_row, g.d_tt), rp = i_row - t * (unsigned)(a.tile * a.tile), id = (unsigned)((const FISE_AS1 int*)a.tile_idx)[t];
+        const unsigned py = fdiv(rp, g.d_tile), ty = fdiv(id, g.d_tiles_w);
+        const unsigned pix = (ty * a.tile + py) * (unsigned)a.W + (id - ty * a.tiles_w) * a.tile + (rp - py * a.tile);
+        if (l16 == 0) rowpix[row] = (int)pix;
+        const FISE_AS1 u32x2_t* q = (const FISE_AS1 u32x2_t*)((const bf16_t*)a.x + ((size_t)b * a.HW + pix) * C) + l16;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) { const u32x2_t u = q[j * 16]; v[j] = f32x4_t{__uint_as_float(u.x), __uint_as_float(u.y), 0.f, 0.f}; }
+    } else {
+        const FISE_AS1 f32x4_t* q = (const FISE_AS1 f32x4_t*)((const float*)a.x + ((size_t)b * a.Ma + i_row) * C) + l16;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) v[j] = q[j * 16];
+    }
+    u32x2_t gam[5], bet[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+        gam[j] = ((const FISE_AS1 u32x2_t*)a.gamma)[j * 16 + l16];
+        bet[j] = ((const FISE_AS1 u32x2_t*)a.beta)[j * 16 + l16];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- weights: stages 0 - 4 are this head's rows of Wq, 5 - 9 as many of Wo.  Slot p of row r holds segment p ^ ((r >> 1) & 7).
+    const unsigned seg = (unsigned)((lane & 7) ^ (lane >> 4)) * 16u, vd = (unsigned)(lane >> 3) * PITCH;
+    unsigned char* const my_ring = ring + wave * (ND * STAGE);
+    auto load = [&](int s) {
+        const __amdgpu_buffer_rsrc_t rs = buf(s < 5 ? a.wq : a.wo, C * PITCH);
+#pragma unroll
+        for (int p = 0; p < PIECES; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (FISE_AS3 void*)(my_ring + (s % ND) * STAGE + p * 1024), 16, vd + (p & 1 ? seg ^ 64u : seg),
+                                                     (unsigned)((wave * D + p * 8) * PITCH + (s % 5) * 128), 0, 0);
+    };
+    // Later stages' lines are cold for all workgroups of an XCD at once: they touch them first, each a share (one dword a line, into the ring before it is filled).
+    {
+        constexpr int LINES = C * 2 + C * 5;               // stages 3 and 4 of Wq, then Wo
+        const int per_xcd = max(1, chunk), me = chunk ? w % chunk : 0;
+#pragma unroll
+        for (int k = 0; k < TOUCH; ++k) {
+            const int q = ((k * per_xcd + me) * CROSS_HEADS + wave) * 64 + lane;
+            const bool o = q >= C * 2;
+            const int r = o ? q - C * 2 : q;
+            const unsigned at = o ? (unsigned)r * 128u : (unsigned)((r >> 1) * PITCH + (3 + (r & 1)) * 128);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(buf(a.wq, C * PITCH), (FISE_AS3 void*)my_ring, 4, o ? OOB : at, 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(buf(a.wo, C * PITCH), (FISE_AS3 void*)my_ring, 4, o && q < LINES ? at : OOB, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < ND; ++s) load(s);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- LayerNorm
+    {
+        f32x4_t x[5];
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            x[j] = v[j];
+            if constexpr (MAP) {
+                const unsigned w0 = __float_as_uint(v[j].x), w1 = __float_as_uint(v[j].y);
+                x[j] = f32x4_t{lo16(w0), hi16(w0), lo16(w1), hi16(w1)};
+            }
+            s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
+        }
+        const float mu = row_sum(s) / C;
+        float q = 0.f;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            const f32x4_t d = x[j] - mu;
+            q += (d.x * d.x + d.y * d.y) + (d.z * d.z + d.w * d.w);
+        }
+        const float rs = rsqrtf(row_sum(q) / C + a.eps);
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            x[j].x = (x[j].x - mu) * rs * lo16(gam[j].x) + lo16(bet[j].x);
+            x[j].y = (x[j].y - mu) * rs * hi16(gam[j].x) + hi16(bet[j].x);
+            x[j].z = (x[j].z - mu) * rs * lo16(gam[j].y) + lo16(bet[j].y);
+            x[j].w = (x[j].w - mu) * rs * hi16(gam[j].y) + hi16(bet[j].y);
+            const int c4 = j * 16 + l16, sg = c4 >> 1;       // piece of four channels, 16-byte segment
+            *reinterpret_cast<u32x2_t*>(lds + row * PITCH + (sg >> 3) * 128 + ((sg & 7) ^ ((row >> 1) & 7)) * 16 + (c4 & 1) * 8) =
+                u32x2_t{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // not the loads in flight
+
+    // ---- keys (row r of tile 2p + h is key 32 p + 8 (r / 4) + 4 h + r % 4; of the last tile 64 + r) and values: keys that do not exist are zeros
+    u32x4_t k16[NT], v16[3][2]; u32x2_t k8[NT], v8[3];
+    auto fetch_keys = [&]() {
+        const __amdgpu_buffer_rsrc_t rk = buf(a.K + (size_t)b * a.n_ctx * C, (unsigned)(a.n_ctx * PITCH)), rv = buf(a.Vt + (size_t)b * C * a.n_stride, (unsigned)(C * a.n_stride) * 2u);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int key = t < NT - 1 ? 32 * (t >> 1) + 8 * (l16 >> 2) + 4 * (t & 1) + (l16 & 3) : 64 + l16;
+            const unsigned off = key < a.n_ctx ? (unsigned)(key * PITCH + wave * (2 * D)) : OOB;
+            k16[t] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rk, off + lq * 16u, 0, 0));
+            k8[t] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rk, lq < 2 ? off + 64u + lq * 8u : OOB, 0, 0));
+        }
+#pragma unroll
+        for (int dt = 0; dt < 3; ++dt) {
+            const int d = dt * 16 + l16;
+            const unsigned off = (unsigned)((wave * D + d) * a.n_stride) * 2u;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) v16[dt][p] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rv, d < D && 32 * p + 8 * lq < a.n_ctx ? off + (unsigned)(64 * p + 16 * lq) : OOB, 0, 0));
+            v8[dt] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rv, d < D && 64 + 4 * lq < a.n_ctx ? off + (unsigned)(128 + 8 * lq) : OOB, 0, 0));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+
+    // ---- product of 48 rows of a head's weights (the last eight twice) and the 32 rows in LDS over five stages
+    const unsigned rx = (unsigned)(l16 * PITCH + ((lq ^ ((l16 >> 1) & 7)) * 16));
+    auto product = [&](auto first, f32x4_t (&acc)[3][2], const int (&wrow)[3], auto behind_first) {
+        constexpr int S0 = decltype(first)::value;
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) acc[u][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            constexpr int AFTER = (ND - 1) * PIECES, KV = 2 * NT + 9, EPI = 9;
+            const int s = S0 + k;
+            // younger loads: two stages; behind those of stage 3 came the keys and values, behind those of stage 7 bias and residual
+            if (s == 0 || s == 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AFTER) : "memory");
+            else if (s < 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AFTER + KV) : "memory");
+            else if (s < 8) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AFTER + EPI) : "memory");
+            else if (s == 8) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PIECES) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const unsigned char* const stage = my_ring + (s % ND) * STAGE;
+            bf16x8_t fw[2][3], fx[2][2];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                for (int u = 0; u < 3; ++u) fw[ks][u] = *reinterpret_cast<const bf16x8_t*>(stage + wrow[u] * 128 + (((lq + 4 * ks) ^ ((wrow[u] >> 1) & 7)) * 16));
+#pragma unroll
+                for (int i = 0; i < 2; ++i) fx[ks][i] = *reinterpret_cast<const bf16x8_t*>(lds + (rx ^ (ks ? 64u : 0u)) + i * 16 * PITCH + k * 128);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (s + ND < 10) load(s + ND);
+            if (k == 0) behind_first();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int u = 0; u < 3; ++u)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) acc[u][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ks][u], fx[ks][i], acc[u][i], 0, 0, 0);
+        }
+    };
+    auto pack8 = [](const f32x4_t& x, const f32x4_t& y) { return __builtin_bit_cast(bf16x8_t, u32x4_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), f2bf2(y[0], y[1]), f2bf2(y[2], y[3])}); };
+    // Four of a lane's eight elements, the rest zeros.  (Not 16 x 16 x 16 products: where a 16 x 16 x 32 product goes on with their sums the compiler leaves
+    // too few wait states, and the last two elements of a lane were those of the registers' former contents.)
+    auto pack4 = [](const f32x4_t& x) { return __builtin_bit_cast(bf16x8_t, u32x4_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), 0, 0}); };
+    auto half = [](const u32x2_t& x) { return __builtin_bit_cast(bf16x8_t, u32x4_t{x.x, x.y, 0, 0}); };
+    f32x4_t acc[3][2];
+    {
+        const int wrow[3] = {8 * (l16 >> 2) + (l16 & 3), 8 * (l16 >> 2) + 4 + (l16 & 3), 32 + (l16 & 7)};
+        product(std::integral_constant<int, 0>(), acc, wrow, fetch_keys);
+    }
+
+    // ---- attention of this head: lane = row l16 of both row tiles, keys 32 p + 8 lq + 0 .. 7 and 64 + 4 lq + 0 .. 3
+    f32x4_t o[3][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const bf16x8_t q32 = pack8(acc[0][i], acc[1][i]);
+        const bf16x8_t q8 = pack4(acc[2][i]);               // channels 32 + 4 lq ..; from 40 on the keys hold zeros
+        f32x4_t s[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(half(k8[t]), q8, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, k16[t]), q32, s[t], 0, 0, 0);
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int key = t < NT - 1 ? 32 * (t >> 1) + 8 * lq + 4 * (t & 1) + e : 64 + 4 * lq + e;
+                s[t][e] = key < a.n_ctx ? s[t][e] : -INFINITY;
+                mx = fmaxf(mx, s[t][e]);
+            }
+        mx = quad_max(mx) * g.scale_log2e;
+        float sum = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], g.scale_log2e, -mx)); sum += s[t][e]; }
+        const float inv = 1.0f / quad_sum(sum);
+        const bf16x8_t p0 = pack8(s[0], s[1]), p1 = pack8(s[2], s[3]);
+        const bf16x8_t p2 = pack4(s[4]);
+        auto live = [&](unsigned w, int key) { return key + 1 < a.n_ctx ? w : key < a.n_ctx ? w & 0xffffu : 0u; };       // a word of two keys
+#pragma unroll
+        for (int dt = 0; dt < 3; ++dt) {
+            if (i == 0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { v16[dt][0][e] = live(v16[dt][0][e], 8 * lq + 2 * e); v16[dt][1][e] = live(v16[dt][1][e], 32 + 8 * lq + 2 * e); }
+                v8[dt].x = live(v8[dt].x, 64 + 4 * lq); v8[dt].y = live(v8[dt].y, 66 + 4 * lq);
+            }
+            f32x4_t x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v16[dt][0]), p0, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v16[dt][1]), p1, x, 0, 0, 0);
+            x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(half(v8[dt]), p2, x, 0, 0, 0);
+            o[dt][i] = x * inv;
+        }
+    }
+    // what the epilogue adds, under the hand-over and the second product
+    const int pix[2] = {MAP ? rowpix[l16] : m0 + l16, MAP ? rowpix[16 + l16] : m0 + 16 + l16};
+    u32x2_t bias[3]; f32x4_t res[3][2];
+    {
+        const __amdgpu_buffer_rsrc_t rb = buf(a.bias, a.bias ? 2u * C : 0u);
+        const __amdgpu_buffer_rsrc_t rr = MAP ? buf((const bf16_t*)a.x + (size_t)b * a.HW * C, (unsigned)(a.HW * C) * 2u) : buf((const float*)a.x + (size_t)b * a.Ma * C, (unsigned)(a.Ma * C) * 4u);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const int col = wave * D + u * 16 + lq * 4;
+            bias[u] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rb, (unsigned)col * 2u, 0, 0));
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const unsigned no = m0 + i * 16 + l16 < a.Ma && (u < 2 || lq < 2) ? 0u : OOB, at = (unsigned)(pix[i] * C + col);
+                if constexpr (MAP) {
+                    const u32x2_t r = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rr, (at * 2u) | no, 0, 0));
+                    res[u][i] = f32x4_t{__uint_as_float(r.x), __uint_as_float(r.y), 0.f, 0.f};
+                } else {
+                    res[u][i] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rr, (at * 4u) | no, 0, 0));
+                }
+            }
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // the normalised rows have been read
+#pragma unroll
+    for (int dt = 0; dt < 3; ++dt)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int col = wave * D + dt * 16 + lq * 4, r = i * 16 + l16, sg = col >> 3;
+            if (dt < 2 || lq < 2)
+                *reinterpret_cast<u32x2_t*>(lds + r * PITCH + (sg >> 3) * 128 + ((sg & 7) ^ ((r >> 1) & 7)) * 16 + (col & 4) * 2) =
+                    u32x2_t{f2bf2(o[dt][i][0], o[dt][i][1]), f2bf2(o[dt][i][2], o[dt][i][3])};
+        }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    f32x4_t y[3][2];
+    {
+        const int wrow[3] = {l16, 16 + l16, 32 + (l16 & 7)};
+        product(std::integral_constant<int, 5>(), y, wrow, []() {});
+    }
+
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+        const int col = wave * D + u * 16 + lq * 4;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int m = m0 + i * 16 + l16;
+            if (m >= a.Ma || (u == 2 && lq >= 2)) continue;
+            if constexpr (MAP) {
+                const unsigned w0 = __float_as_uint(res[u][i].x), w1 = __float_as_uint(res[u][i].y);
+                res[u][i] = f32x4_t{lo16(w0), hi16(w0), lo16(w1), hi16(w1)};
+            }
+            const f32x4_t z = y[u][i] + f32x4_t{lo16(bias[u].x), hi16(bias[u].x), lo16(bias[u].y), hi16(bias[u].y)} + res[u][i];
+            if constexpr (MAP) *(FISE_AS1 u32x2_t*)((bf16_t*)a.out + ((size_t)b * a.HW + pix[i]) * C + col) = u32x2_t{f2bf2(z[0], z[1]), f2bf2(z[2], z[3])};
+            else *(FISE_AS1 f32x4_t*)((float*)a.out + ((size_t)b * a.Ma + m) * C + col) = z;
+        }
+    }
+#endif
+}
+
+// From twenty workgroups on.  With fewer the three launches spread their weights over more CUs, which with cold weights counts for more than two launches: step of
+// 64 x 64 with 8 workgroups 1766 us, here 1778, with 16 1875 and 1876, with 24 1969 and 1960, with 48 2247 and 2214.
+bool cross_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW) {
+    return C == CROSS_C && heads == CROSS_HEADS && n_ctx >= 1 && n_ctx <= CROSS_KEYS && n_stride < 1 << 20 && Ma >= 1 && (long long)B * ceil_div(Ma, 32) >= 20 && Ma < 1 << 20 && HW < 1 << 21 && (long long)B * Ma < 1 << 24 && (long long)B * HW < 1 << 24;
+}
+
+template <bool MAP> static int launch(const CrossDev& g, hipStream_t st) {
+    constexpr int lds = 32 * 2 * CROSS_C + CROSS_HEADS * 3 * (CROSS_C / CROSS_HEADS) * 128 + 32 * 4;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&cross_attention_kernel<MAP>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return fail(FISE_ERR_HIP, "cross attention: cannot raise the dynamic LDS limit");
+    const CrossArgs& a = g.a;
+    {
+        const double rows = (double)a.B * a.Ma, el = MAP ? 2.0 : 4.0;
+        ProfileScope prof(PROF_ROWS_GEMM, rows * CROSS_C * 4.0 * (CROSS_C + a.n_ctx), 4.0 * CROSS_C * (CROSS_C + (double)a.B * a.n_ctx) + 2 * el * rows * CROSS_C, st);
+        hipLaunchKernelGGL((cross_attention_kernel<MAP>), dim3((unsigned)(g.gx * a.B)), dim3(512), lds, st, g);
+    }
+    FISE_CHECK_LAUNCH("cross attention");
+    return FISE_OK;
+}
+
+int launch_cross(const CrossArgs& a, hipStream_t st) {
+    CrossDev g{};
+    g.a = a;
+    g.gx = ceil_div(a.Ma, 32); g.scale_log2e = 1.4426950408889634f / sqrtf((float)(CROSS_C / CROSS_HEADS));
+    g.d_gx = fast_div(g.gx);
+    if (a.tile_idx) { g.d_tt = fast_div(a.tile * a.tile); g.d_tile = fast_div(a.tile); g.d_tiles_w = fast_div(a.tiles_w); }
+    return a.tile_idx ? launch<true>(g, st) : launch<false>(g, st);
+}
+
+}  // namespace fise

@@ -169,6 +169,15 @@ struct NormGemmArgs {
     const bf16_t* w[3]; const bf16_t* bias; int N, sect_n, geglu;
     bf16_t* out[3]; int mode[3];
 };
+// Cross-attention sub-layer as one launch (cross.hip): out = x + Wo attention(Wq LN(x), K, V) + bias.  tile_idx: x and out are bf16 maps of HW pixels and the
+// rows pixels of active tiles; null: compact float rows, which out may be.
+constexpr int CROSS_C = 320, CROSS_HEADS = 8, CROSS_KEYS = 80;
+struct CrossArgs {
+    const void* x; void* out; const bf16_t *gamma, *beta, *wq, *wo, *bias, *K, *Vt; float eps;
+    int n_ctx, n_stride, B, Ma; const int* tile_idx; int tile, tiles_w, W, HW;
+};
+bool cross_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW);
+int launch_cross(const CrossArgs& a, hipStream_t st);
 bool norm_gemm_takes(int src, int K, int B, int Ma, int H, int W);
 int launch_norm_gemm(const NormGemmArgs& a, hipStream_t st);
 size_t igemm_workspace_bytes();

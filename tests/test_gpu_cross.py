@@ -1,0 +1,45 @@
+"""GPU parity of the cross-attention layer over map pixels where its one-launch form ends: key counts around its tiles of 16 and 32 keys and past the last
+one, row tiles that end inside a batch element, tiles whose pixels are no runs of four, one batch element and three.  The float rows of a transformer block
+have their cases in test_gpu_blocks.py."""
+import pytest
+import torch
+
+from helpers import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,H,W,tile,n_ctx", [(2, 64, 64, 8, 77), (2, 24, 24, 3, 77), (1, 36, 20, 4, 1), (3, 16, 16, 2, 8), (2, 20, 20, 1, 31), (1, 64, 40, 8, 32),
+                                              (2, 24, 24, 4, 33), (2, 32, 16, 4, 48), (1, 32, 24, 4, 63), (2, 24, 24, 4, 64), (2, 24, 24, 4, 65), (2, 24, 24, 4, 72),
+                                              (2, 24, 24, 4, 80), (2, 24, 24, 4, 81)])
+def test_cross_attention_layer_of_320_channels(B, H, W, tile, n_ctx):
+    from paper_2305_17423_amd import binding as fb
+    C, heads, stride = 320, 8, (n_ctx + 7) // 8 * 8 + 8
+    g = torch.Generator(device=DEV).manual_seed(n_ctx + H)
+    normal = lambda *shape, std=1.0: (torch.randn(*shape, generator=g, device=DEV) * std).bfloat16()      # noqa: E731
+    x, y = normal(B, H, W, C), normal(B, H, W, C)
+    gam, bet, wq, wo, bo = 1 + normal(C, std=0.1), normal(C, std=0.1), normal(C, C, std=0.08), normal(C, C, std=0.05), normal(C, std=0.1)
+    K, V = normal(B, n_ctx, C), torch.full((B, C, stride), float("nan"), dtype=torch.bfloat16, device=DEV)      # the columns past the last key hold anything
+    V[:, :, :n_ctx] = normal(B, C, n_ctx)
+    tiles = (H // tile) * (W // tile)
+    idx = torch.randperm(tiles, generator=g, device=DEV)[: max(1, tiles - 3)].sort().values.to(torch.int32)
+    active = torch.zeros(tiles, dtype=torch.bool, device=DEV)
+    active[idx.long()] = True
+    active = active.reshape(H // tile, W // tile).repeat_interleave(tile, 0).repeat_interleave(tile, 1)
+    before = y.clone()
+    ws = torch.zeros(int(fb.fise_masked_attention_workspace_bytes(B, C, idx.numel(), tile)), dtype=torch.uint8, device=DEV)
+    fb.fise_masked_attention(x, gam, bet, wq, None, None, wo, bo, heads, None, None, K, V, n_ctx, idx, idx.numel(), tile, y, ws)
+    f = lambda t: t.float().cpu().double()                                                               # noqa: E731
+    ln = torch.nn.functional.layer_norm(f(x).reshape(B, H * W, C), (C,), f(gam), f(bet), 1e-5)
+    q = (ln @ f(wq).t()).reshape(B, -1, heads, C // heads).transpose(1, 2).contiguous()
+    k = f(K).reshape(B, n_ctx, heads, -1).permute(0, 2, 3, 1).contiguous()
+    v = f(V[:, :, :n_ctx]).reshape(B, heads, -1, n_ctx).transpose(2, 3).contiguous()
+    o = ((q @ k) * (C // heads) ** -0.5).softmax(-1) @ v
+    update = o.transpose(1, 2).reshape(B, H * W, C) @ f(wo).t() + f(bo)
+    want = (f(x).reshape(B, H * W, C) + update).reshape(B, H, W, C)
+    err = (f(y) - want)[:, active.cpu()]
+    # the sum is stored in bf16 (2^-9 relative); normalised rows, queries, probabilities and outputs are rounded to bf16 on the way: 2^-8 of the update, twice
+    rms = float(update.pow(2).mean().sqrt())
+    assert bool((err.abs() <= want[:, active.cpu()].abs() * 2.0 ** -8 + rms * 0.1).all())
+    assert float(err.pow(2).mean().sqrt()) <= 2.0 ** -9 * float(want.pow(2).mean().sqrt()) + rms * 2.0 ** -7
+    assert torch.equal(y[:, ~active], before[:, ~active])
