@@ -208,18 +208,23 @@ int run_transformer(const fise_transformer_args* a, void* workspace, const Igemm
     IgemmArgs o1 = lin(ob, C, a->o1_w, a->o1_b, C); into_h(o1); with_ln(o1, a->ln2_g, a->ln2_b);
     if (int e = launch_igemm(o1, iw, st)) return e;
     // cross-attention against the context K/V
+    CrossArgs cross{hb, hb, (const bf16_t*)a->ln2_g, (const bf16_t*)a->ln2_b, (const bf16_t*)a->q2_w, (const bf16_t*)a->o2_w, (const bf16_t*)a->o2_b,
+                    (const bf16_t*)a->K_ctx, (const bf16_t*)a->Vt_ctx, 1e-5f, a->n_ctx, a->n_ctx_stride, B, Ma, nullptr, 0, 0, 0, 0};
     if (fused && cross_takes(C, a->heads, a->n_ctx, a->n_ctx_stride, B, Ma, H * W)) {
-        const CrossArgs c{hb, hb, (const bf16_t*)a->ln2_g, (const bf16_t*)a->ln2_b, (const bf16_t*)a->q2_w, (const bf16_t*)a->o2_w, (const bf16_t*)a->o2_b,
-                          (const bf16_t*)a->K_ctx, (const bf16_t*)a->Vt_ctx, 1e-5f, a->n_ctx, a->n_ctx_stride, B, Ma, nullptr, 0, 0, 0, 0};
-        if (int e = launch_cross(c, st)) return e;
+        if (int e = launch_cross(cross, st)) return e;
     } else {
-        if (fused) {
-            if (int e = launch_norm_gemm(normed(a->ln2_g, a->ln2_b, a->q2_w, C, qb), st)) return e;
+        if (fused && query_attention_takes(C, a->heads, a->n_ctx, a->n_ctx_stride, B, Ma, H * W)) {
+            cross.out = ob;
+            if (int e = launch_query_attention(cross, C, st)) return e;
         } else {
-            IgemmArgs q2 = lin(nb, C, a->q2_w, nullptr, C); q2.out[0] = qb;
-            if (int e = launch_igemm(q2, iw, st)) return e;
+            if (fused) {
+                if (int e = launch_norm_gemm(normed(a->ln2_g, a->ln2_b, a->q2_w, C, qb), st)) return e;
+            } else {
+                IgemmArgs q2 = lin(nb, C, a->q2_w, nullptr, C); q2.out[0] = qb;
+                if (int e = launch_igemm(q2, iw, st)) return e;
+            }
+            if (int e = launch_attention(qb, a->K_ctx, a->Vt_ctx, B, Ma, a->n_ctx, a->n_ctx_stride, C, a->heads, scale, ob, nullptr, 0, st)) return e;
         }
-        if (int e = launch_attention(qb, a->K_ctx, a->Vt_ctx, B, Ma, a->n_ctx, a->n_ctx_stride, C, a->heads, scale, ob, nullptr, 0, st)) return e;
         IgemmArgs o2 = lin(ob, C, a->o2_w, a->o2_b, C); into_h(o2); with_ln(o2, a->ln3_g, a->ln3_b);
         if (int e = launch_igemm(o2, iw, st)) return e;
     }
@@ -364,30 +369,33 @@ extern "C" int fise_masked_attention(const void* x, const void* ln_gamma, const 
     bf16_t* nbuf = (bf16_t*)ws; bf16_t* qbuf = (bf16_t*)(ws + buf); bf16_t* obuf = (bf16_t*)(ws + 2 * buf);
     const float scale = 1.0f / sqrtf((float)d);
 
-    if (!self && cross_takes(C, heads, n_ctx, n_ctx_stride, B, Ma, H * W)) {
-        const CrossArgs c{x, y_cache, (const bf16_t*)ln_gamma, (const bf16_t*)ln_beta, (const bf16_t*)Wq, (const bf16_t*)Wo, (const bf16_t*)bo, (const bf16_t*)K_ctx,
-                          (const bf16_t*)Vt_ctx, 1e-5f, n_ctx, n_ctx_stride, B, Ma, tile_idx, tile, W / tile, W, H * W};
-        return launch_cross(c, st);
-    }
-    const GemmProduct qkv[3] = {{(const bf16_t*)Wq, C, qbuf, OUT_COMPACT}, {(const bf16_t*)Wk, C, (bf16_t*)K_cache, OUT_MAP}, {(const bf16_t*)Wv, C, (bf16_t*)Vt_cache, OUT_TOKENS_T}};
-    const int nprod = self ? 3 : 1;
-    if (norm_gemm_takes(NG_MAP_LN, C, B, Ma, H, W)) {
-        NormGemmArgs g{};
-        g.x = x; g.src = NG_MAP_LN; g.K = C; g.gamma = (const bf16_t*)ln_gamma; g.beta = (const bf16_t*)ln_beta; g.eps = 1e-5f;
-        g.tile_idx = tile_idx; g.tile = tile; g.tiles_w = W / tile; g.Ho = H; g.Wo = W; g.B = B; g.Ma = Ma;
-        g.N = nprod * C; g.sect_n = C;
-        for (int i = 0; i < nprod; ++i) { g.w[i] = qkv[i].w; g.out[i] = qkv[i].out; g.mode[i] = qkv[i].mode; }
-        if (int e = launch_norm_gemm(g, st)) return e;
+    CrossArgs cross{x, y_cache, (const bf16_t*)ln_gamma, (const bf16_t*)ln_beta, (const bf16_t*)Wq, (const bf16_t*)Wo, (const bf16_t*)bo, (const bf16_t*)K_ctx,
+                    (const bf16_t*)Vt_ctx, 1e-5f, n_ctx, n_ctx_stride, B, Ma, tile_idx, tile, W / tile, W, H * W};
+    if (!self && cross_takes(C, heads, n_ctx, n_ctx_stride, B, Ma, H * W)) return launch_cross(cross, st);
+    if (!self && query_attention_takes(C, heads, n_ctx, n_ctx_stride, B, Ma, H * W)) {
+        cross.out = obuf;
+        if (int e = launch_query_attention(cross, C, st)) return e;
     } else {
-        if (int e = launch_ln_rows(x, 0, rows, C, ln_gamma, ln_beta, 1e-5f, nbuf, tile_idx, tile, W / tile, H, W, Ma, st)) return e;
-        IgemmArgs g = linear_args(nbuf, Ma, B, C, Wq, nullptr, C);
-        g.tile_idx = tile_idx; g.tile = tile; g.tiles_w = W / tile; g.Ho = H; g.Wo = W;
-        if (int e = launch_igemm_group(g, qkv, nprod, st)) return e;
-    }
-    if (self) {
-        if (int e = launch_attention(qbuf, K_cache, Vt_cache, B, Ma, H * W, H * W, C, heads, scale, obuf, ws + 3 * buf, workspace_bytes - 3 * buf, st)) return e;
-    } else {
-        if (int e = launch_attention(qbuf, K_ctx, Vt_ctx, B, Ma, n_ctx, n_ctx_stride, C, heads, scale, obuf, nullptr, 0, st)) return e;
+        const GemmProduct qkv[3] = {{(const bf16_t*)Wq, C, qbuf, OUT_COMPACT}, {(const bf16_t*)Wk, C, (bf16_t*)K_cache, OUT_MAP}, {(const bf16_t*)Wv, C, (bf16_t*)Vt_cache, OUT_TOKENS_T}};
+        const int nprod = self ? 3 : 1;
+        if (norm_gemm_takes(NG_MAP_LN, C, B, Ma, H, W)) {
+            NormGemmArgs g{};
+            g.x = x; g.src = NG_MAP_LN; g.K = C; g.gamma = (const bf16_t*)ln_gamma; g.beta = (const bf16_t*)ln_beta; g.eps = 1e-5f;
+            g.tile_idx = tile_idx; g.tile = tile; g.tiles_w = W / tile; g.Ho = H; g.Wo = W; g.B = B; g.Ma = Ma;
+            g.N = nprod * C; g.sect_n = C;
+            for (int i = 0; i < nprod; ++i) { g.w[i] = qkv[i].w; g.out[i] = qkv[i].out; g.mode[i] = qkv[i].mode; }
+            if (int e = launch_norm_gemm(g, st)) return e;
+        } else {
+            if (int e = launch_ln_rows(x, 0, rows, C, ln_gamma, ln_beta, 1e-5f, nbuf, tile_idx, tile, W / tile, H, W, Ma, st)) return e;
+            IgemmArgs g = linear_args(nbuf, Ma, B, C, Wq, nullptr, C);
+            g.tile_idx = tile_idx; g.tile = tile; g.tiles_w = W / tile; g.Ho = H; g.Wo = W;
+            if (int e = launch_igemm_group(g, qkv, nprod, st)) return e;
+        }
+        if (self) {
+            if (int e = launch_attention(qbuf, K_cache, Vt_cache, B, Ma, H * W, H * W, C, heads, scale, obuf, ws + 3 * buf, workspace_bytes - 3 * buf, st)) return e;
+        } else {
+            if (int e = launch_attention(qbuf, K_ctx, Vt_ctx, B, Ma, n_ctx, n_ctx_stride, C, heads, scale, obuf, nullptr, 0, st)) return e;
+        }
     }
     IgemmArgs o = linear_args(obuf, Ma, B, C, Wo, bo, C);
     o.tile_idx = tile_idx; o.tile = tile; o.tiles_w = W / tile; o.Ho = H; o.Wo = W;

@@ -13,8 +13,8 @@
 //  - The heads' outputs meet in the place of the normalised rows (the two barriers beside the one behind the normalisation).
 // Bound by the 500 KB a workgroup brings in (410 of weights at the ~60 GB/s that loads of eight rows get a CU, keys, values and residual in pieces of 64
 // bytes); first touches of the later stages' lines are worth 1.3 us with cold weights.  Against the three launches it stands for (normalisation and
-// queries, attention over 77 keys, product and sum), us: 640 rows of a map 15.5 -> 14.2, 1536 float rows 18.5 -> 14.4, 5504 27 -> 14.7, 8192 28 ->
-// 15.5; steps of 12 of 64 tiles 2247 -> 2214, 43 of 144 4152 -> 4112, dense pass 4950 -> 4878.
+// queries, attention over 77 keys, product and sum), us: 1536 float rows 18.5 -> 14.4, 5504 27 -> 14.7, 8192 28 -> 15.5; steps of 12 of 64 tiles 2247 ->
+// 2214, 43 of 144 4152 -> 4112, dense pass 4950 -> 4878.
 #include <cmath>
 #include <type_traits>
 #include "igemm.h"
@@ -25,7 +25,7 @@ namespace fise {
 struct CrossDev {
     CrossArgs a;
     int gx; float scale_log2e;
-    FastDiv d_gx, d_tt, d_tile, d_tiles_w;
+    FastDiv d_gx, d_tiles, d_tt, d_tile, d_tiles_w;
 };
 
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -334,10 +334,232 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
 #endif
 }
 
-// From twenty workgroups on.  With fewer the three launches spread their weights over more CUs, which with cold weights counts for more than two launches: step of
-// 64 x 64 with 8 workgroups 1766 us, here 1778, with 16 1875 and 1876, with 24 1969 and 1960, with 48 2247 and 2214.
+// The same up to the product with Wo, out = attention(Wq LN(x), K, V) as compact bf16 rows, a workgroup per head and 32 rows: 640 channels, whose weights
+// are too many for one workgroup, and few rows of 320.  A wave per 64 channels:
+//  - it brings that stage of the head's weights into LDS (all of them in flight together, under the normalisation) and multiplies it with the
+//    rows; the waves' sums meet in the place of the weights, in wave order, and become queries;
+//  - the last two waves hold keys and values and finish sixteen rows each, numbered as above.
+// Bound by its start, the rows and 100 KB of weights.  Against a launch each for the queries and the attention, us: transformer block of 160 rows x 640 65.9
+// -> 63.1, of 512 82.7 -> 78.5, of 2048 134.0 -> 133.3; attention layer of 128 rows x 320 36.0 -> 32.0; step of 2 of 70 tiles 1787 -> 1755, 12 of 64 2217 -> 2198.
+template <int C> struct QueryTile {
+    static constexpr int NW = C / 64, D = C / CROSS_HEADS, U = (D + 15) / 16, BM = 32, PITCH = 2 * C + (C % 128 ? 0 : 128), REGION = D * 128 > U * 2048 ? D * 128 : U * 2048,
+                         QC = (D + 31) / 32, QPITCH = QC * 64 + 16, LDS = BM * PITCH + NW * REGION;      // QC: 32-wide steps over the head dim
+    static_assert(BM * QPITCH <= BM * PITCH, "queries lie in the place of the rows");
+};
+
+template <int C, bool MAP>
+__global__ __launch_bounds__(C, 1) void query_attention_kernel(const CrossDev g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    using T = QueryTile<C>;
+    constexpr int NW = T::NW, D = T::D, U = T::U, BM = T::BM, PITCH = T::PITCH, NT = CROSS_KEYS / 16, QUADS = BM / 4, PASSES = (QUADS + NW - 1) / NW;
+    constexpr unsigned OOB = 0x80000000u;
+    const CrossArgs& a = g.a;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    unsigned char* const regions = lds + BM * PITCH;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    unsigned char* const mine = regions + wave * T::REGION;
+    // every XCD gets a contiguous run of (head, row tile), row tiles fastest: the weights of a head are pulled into one L2
+    const int chunk = (int)gridDim.x >> 3;
+    int w = blockIdx.x;
+    if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
+    const int tiles = g.gx * a.B, h = (int)fdiv((unsigned)w, g.d_tiles), rt = w - h * tiles, b = (int)fdiv((unsigned)rt, g.d_gx), m0 = (rt - b * g.gx) * BM;
+
+    // ---- rows: sixteen lanes a row, NW pieces of four channels each
+    f32x4_t v[PASSES][NW];
+    u32x2_t gam[NW], bet[NW];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int quad = p * NW + wave;
+        if (quad >= QUADS) continue;
+        const unsigned i_row = (unsigned)min(m0 + quad * 4 + lq, a.Ma - 1);
+        if constexpr (MAP) {
+            const unsigned t = fdiv(i_row, g.d_tt), rp = i_row - t * (unsigned)(a.tile * a.tile), id = (unsigned)((const FISE_AS1 int*)a.tile_idx)[t];
+            const unsigned py = fdiv(rp, g.d_tile), ty = fdiv(id, g.d_tiles_w);
+            const unsigned pix = (ty * a.tile + py) * (unsigned)a.W + (id - ty * a.tiles_w) * a.tile + (rp - py * a.tile);
+            const FISE_AS1 u32x2_t* q = (const FISE_AS1 u32x2_t*)((const bf16_t*)a.x + ((size_t)b * a.HW + pix) * C) + l16;
+#pragma unroll
+            for (int j = 0; j < NW; ++j) { const u32x2_t u = q[j * 16]; v[p][j] = f32x4_t{__uint_as_float(u.x), __uint_as_float(u.y), 0.f, 0.f}; }
+        } else {
+            const FISE_AS1 f32x4_t* q = (const FISE_AS1 f32x4_t*)((const float*)a.x + ((size_t)b * a.Ma + i_row) * C) + l16;
+#pragma unroll
+            for (int j = 0; j < NW; ++j) v[p][j] = q[j * 16];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+        gam[j] = ((const FISE_AS1 u32x2_t*)a.gamma)[j * 16 + l16];
+        bet[j] = ((const FISE_AS1 u32x2_t*)a.beta)[j * 16 + l16];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- this wave's stage of the weights: slot p of row r holds segment p ^ ((r >> 1) & 7)
+    {
+        const unsigned seg = (unsigned)((lane & 7) ^ (lane >> 4)) * 16u, vd = (unsigned)(lane >> 3) * (2u * C);
+        const __amdgpu_buffer_rsrc_t rs = buf(a.wq, 2u * C * C);
+#pragma unroll
+        for (int p = 0; p < D / 8; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (FISE_AS3 void*)(mine + p * 1024), 16, vd + (p & 1 ? seg ^ 64u : seg), (unsigned)((h * D + p * 8) * (2 * C) + wave * 128), 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- LayerNorm
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int quad = p * NW + wave, row = quad * 4 + lq;
+        if (quad >= QUADS) continue;
+        f32x4_t x[NW];
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            x[j] = v[p][j];
+            if constexpr (MAP) {
+                const unsigned w0 = __float_as_uint(v[p][j].x), w1 = __float_as_uint(v[p][j].y);
+                x[j] = f32x4_t{lo16(w0), hi16(w0), lo16(w1), hi16(w1)};
+            }
+            s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
+        }
+        const float mu = row_sum(s) / C;
+        float q = 0.f;
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            const f32x4_t d = x[j] - mu;
+            q += (d.x * d.x + d.y * d.y) + (d.z * d.z + d.w * d.w);
+        }
+        const float rs = rsqrtf(row_sum(q) / C + a.eps);
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            x[j].x = (x[j].x - mu) * rs * lo16(gam[j].x) + lo16(bet[j].x);
+            x[j].y = (x[j].y - mu) * rs * hi16(gam[j].x) + hi16(bet[j].x);
+            x[j].z = (x[j].z - mu) * rs * lo16(gam[j].y) + lo16(bet[j].y);
+            x[j].w = (x[j].w - mu) * rs * hi16(gam[j].y) + hi16(bet[j].y);
+            const int c4 = j * 16 + l16, sg = c4 >> 1;       // piece of four channels, 16-byte segment
+            *reinterpret_cast<u32x2_t*>(lds + row * PITCH + (sg >> 3) * 128 + ((sg & 7) ^ ((row >> 1) & 7)) * 16 + (c4 & 1) * 8) =
+                u32x2_t{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+    // ---- this wave's 64 channels of the product (past the last row of the weights: the last eight again)
+    {
+        f32x4_t acc[U][2];
+        bf16x8_t fw[2][U], fx[2][2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int r = u * 16 + (u * 16 + 16 <= D ? l16 : l16 & 7);
+                fw[ks][u] = *reinterpret_cast<const bf16x8_t*>(mine + r * 128 + (((lq + 4 * ks) ^ ((r >> 1) & 7)) * 16));
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) fx[ks][i] = *reinterpret_cast<const bf16x8_t*>(lds + (i * 16 + l16) * PITCH + wave * 128 + (((lq + 4 * ks) ^ ((l16 >> 1) & 7)) * 16));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                acc[u][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[0][u], fx[0][i], f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                acc[u][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[1][u], fx[1][i], acc[u][i], 0, 0, 0);
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4_t*>(mine + ((u * 2 + i) * 64 + lane) * 16) = acc[u][i];
+    }
+    // ---- keys and values of the two waves that go on, under the sums (keys that do not exist are zeros)
+    u32x4_t k16[NT][T::QC], v16[U][2]; u32x2_t v8[U];
+    const int tile = wave - (NW - 2);                          // their row tile
+    if (tile >= 0) {
+        const __amdgpu_buffer_rsrc_t rk = buf(a.K + (size_t)b * a.n_ctx * C, (unsigned)(a.n_ctx * C) * 2u), rv = buf(a.Vt + (size_t)b * C * a.n_stride, (unsigned)(C * a.n_stride) * 2u);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int key = t < NT - 1 ? 32 * (t >> 1) + 8 * (l16 >> 2) + 4 * (t & 1) + (l16 & 3) : 64 + l16;
+#pragma unroll
+            for (int c = 0; c < T::QC; ++c)
+                k16[t][c] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rk, key < a.n_ctx && c * 32 + lq * 8 < D ? (unsigned)((key * C + h * D + c * 32 + lq * 8) * 2) : OOB, 0, 0));
+        }
+#pragma unroll
+        for (int dt = 0; dt < U; ++dt) {
+            const int d = dt * 16 + l16;
+            const unsigned off = (unsigned)((h * D + d) * a.n_stride) * 2u;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) v16[dt][p] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rv, d < D && 32 * p + 8 * lq < a.n_ctx ? off + (unsigned)(64 * p + 16 * lq) : OOB, 0, 0));
+            v8[dt] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rv, d < D && 64 + 4 * lq < a.n_ctx ? off + (unsigned)(128 + 8 * lq) : OOB, 0, 0));
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    // ---- queries: a wave sums a tile of 16 channels x 16 rows in wave order; channels past the head dim are zeros
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int id = e * NW + wave;
+        if (id >= 2 * T::QC * 2) continue;
+        const int u = id >> 1, i = id & 1;
+        f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+        if (u < U)
+#pragma unroll
+            for (int o = 0; o < NW; ++o) s += *reinterpret_cast<const f32x4_t*>(regions + o * T::REGION + (id * 64 + lane) * 16);
+        if (u * 16 + lq * 4 >= D) s = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        *reinterpret_cast<u32x2_t*>(lds + (i * 16 + l16) * T::QPITCH + (u * 16 + lq * 4) * 2) = u32x2_t{f2bf2(s[0], s[1]), f2bf2(s[2], s[3])};
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (tile < 0) return;
+
+    // ---- attention: lane = row l16 of the tile, keys 32 p + 8 lq + 0 .. 7 and 64 + 4 lq + 0 .. 3
+    auto pack8 = [](const f32x4_t& x, const f32x4_t& y) { return __builtin_bit_cast(bf16x8_t, u32x4_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), f2bf2(y[0], y[1]), f2bf2(y[2], y[3])}); };
+    bf16x8_t q[T::QC];
+#pragma unroll
+    for (int c = 0; c < T::QC; ++c) q[c] = *reinterpret_cast<const bf16x8_t*>(lds + (tile * 16 + l16) * T::QPITCH + c * 64 + lq * 16);
+    f32x4_t s[NT];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        s[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < T::QC; ++c) s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, k16[t][c]), q[c], s[t], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int key = t < NT - 1 ? 32 * (t >> 1) + 8 * lq + 4 * (t & 1) + e : 64 + 4 * lq + e;
+            s[t][e] = key < a.n_ctx ? s[t][e] : -INFINITY;
+            mx = fmaxf(mx, s[t][e]);
+        }
+    mx = quad_max(mx) * g.scale_log2e;
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], g.scale_log2e, -mx)); sum += s[t][e]; }
+    const float inv = 1.0f / quad_sum(sum);
+    const bf16x8_t p0 = pack8(s[0], s[1]), p1 = pack8(s[2], s[3]), p2 = pack8(s[4], f32x4_t{0.f, 0.f, 0.f, 0.f});
+    auto live = [&](unsigned x, int key) { return key + 1 < a.n_ctx ? x : key < a.n_ctx ? x & 0xffffu : 0u; };       // a word of two keys
+    const int m = m0 + tile * 16 + l16;
+    bf16_t* const out = (bf16_t*)a.out + ((size_t)b * a.Ma + m) * C + h * D + lq * 4;
+#pragma unroll
+    for (int dt = 0; dt < U; ++dt) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v16[dt][0][e] = live(v16[dt][0][e], 8 * lq + 2 * e); v16[dt][1][e] = live(v16[dt][1][e], 32 + 8 * lq + 2 * e); }
+        const u32x4_t tail = {live(v8[dt].x, 64 + 4 * lq), live(v8[dt].y, 66 + 4 * lq), 0, 0};
+        f32x4_t x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v16[dt][0]), p0, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v16[dt][1]), p1, x, 0, 0, 0);
+        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, tail), p2, x, 0, 0, 0) * inv;
+        if (m < a.Ma && dt * 16 + lq * 4 < D) *(FISE_AS1 u32x2_t*)(out + dt * 16) = u32x2_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
+    }
+#endif
+}
+
+static bool takes(int heads, int n_ctx, int n_stride, int B, int Ma, int HW) {
+    return heads == CROSS_HEADS && n_ctx >= 1 && n_ctx <= CROSS_KEYS && n_stride < 1 << 20 && Ma >= 1 && Ma < 1 << 20 && HW < 1 << 21 && (long long)B * Ma < 1 << 24 && (long long)B * HW < 1 << 24;
+}
+// From forty workgroups on: with fewer, a workgroup per head and a product behind it spread the weights over more CUs.  Step of 64 x 64 with 24 workgroups
+// 1952 us here and 1939, with 48 2199 and 2206, with 96 2726 and 2761; attention layer of 640 rows (20) 44.8 and 43.0, of 1280 (40) 50.7 and 51.2, of
+// 4096 (128) 81.3 and 89.2.
 bool cross_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW) {
-    return C == CROSS_C && heads == CROSS_HEADS && n_ctx >= 1 && n_ctx <= CROSS_KEYS && n_stride < 1 << 20 && Ma >= 1 && (long long)B * ceil_div(Ma, 32) >= 20 && Ma < 1 << 20 && HW < 1 << 21 && (long long)B * Ma < 1 << 24 && (long long)B * HW < 1 << 24;
+    return C == CROSS_C && takes(heads, n_ctx, n_stride, B, Ma, HW) && (long long)B * ceil_div(Ma, 32) >= 40;
+}
+// 640 channels: two rounds of the CUs (2048 rows 134.0 -> 133.3 us, a transformer block); in five the rows are normalised too often (4608 rows 277.6 -> 281.7).
+bool query_attention_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW) {
+    return (C == 320 || (C == 640 && (long long)B * ceil_div(Ma, 32) * CROSS_HEADS <= 512)) && takes(heads, n_ctx, n_stride, B, Ma, HW);
 }
 
 template <bool MAP> static int launch(const CrossDev& g, hipStream_t st) {
@@ -354,13 +576,39 @@ template <bool MAP> static int launch(const CrossDev& g, hipStream_t st) {
     return FISE_OK;
 }
 
-int launch_cross(const CrossArgs& a, hipStream_t st) {
+template <int C, bool MAP> static int launch_query(const CrossDev& g, hipStream_t st) {
+    constexpr int lds = QueryTile<C>::LDS;
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&query_attention_kernel<C, MAP>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return fail(FISE_ERR_HIP, "query attention: cannot raise the dynamic LDS limit");
+    const CrossArgs& a = g.a;
+    {
+        const double rows = (double)a.B * a.Ma, el = MAP ? 2.0 : 4.0;
+        ProfileScope prof(PROF_ROWS_GEMM, rows * C * (2.0 * C + 4.0 * a.n_ctx), 2.0 * C * (C + 2.0 * a.B * a.n_ctx) + (el + 2.0) * rows * C, st);
+        hipLaunchKernelGGL((query_attention_kernel<C, MAP>), dim3((unsigned)(g.gx * a.B * CROSS_HEADS)), dim3(C), lds, st, g);
+    }
+    FISE_CHECK_LAUNCH("query attention");
+    return FISE_OK;
+}
+
+static CrossDev device_args(const CrossArgs& a, int C) {
     CrossDev g{};
     g.a = a;
-    g.gx = ceil_div(a.Ma, 32); g.scale_log2e = 1.4426950408889634f / sqrtf((float)(CROSS_C / CROSS_HEADS));
-    g.d_gx = fast_div(g.gx);
+    g.gx = ceil_div(a.Ma, 32); g.scale_log2e = 1.4426950408889634f / sqrtf((float)(C / CROSS_HEADS));
+    g.d_gx = fast_div(g.gx); g.d_tiles = fast_div(g.gx * a.B);
     if (a.tile_idx) { g.d_tt = fast_div(a.tile * a.tile); g.d_tile = fast_div(a.tile); g.d_tiles_w = fast_div(a.tiles_w); }
+    return g;
+}
+
+int launch_cross(const CrossArgs& a, hipStream_t st) {
+    const CrossDev g = device_args(a, CROSS_C);
     return a.tile_idx ? launch<true>(g, st) : launch<false>(g, st);
+}
+
+int launch_query_attention(const CrossArgs& a, int C, hipStream_t st) {
+    const CrossDev g = device_args(a, C);
+    if (C == 320) return a.tile_idx ? launch_query<320, true>(g, st) : launch_query<320, false>(g, st);
+    return a.tile_idx ? launch_query<640, true>(g, st) : launch_query<640, false>(g, st);
 }
 
 }  // namespace fise

@@ -178,6 +178,9 @@ struct CrossArgs {
 };
 bool cross_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW);
 int launch_cross(const CrossArgs& a, hipStream_t st);
+// The same without the last product and sum, 320 or 640 channels: out = attention(Wq LN(x), K, V), compact bf16 rows.
+bool query_attention_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW);
+int launch_query_attention(const CrossArgs& a, int C, hipStream_t st);
 bool norm_gemm_takes(int src, int K, int B, int Ma, int H, int W);
 int launch_norm_gemm(const NormGemmArgs& a, hipStream_t st);
 size_t igemm_workspace_bytes();

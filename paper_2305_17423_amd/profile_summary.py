@@ -56,7 +56,7 @@ def kind_of(name: str):
     norm = re.search(r"norm_gemm_kernel<\d+, \d+, \d+, \d+, (true|false), \d+>", n)                      # GEGLU
     if wave and wave[2] == "true" or norm and norm[1] == "true" or "igemm_dma_kernel<64, 128, 2, 2" in n or "igemm_dma_kernel<32, 256" in n:
         return "norm_gemm_kernel<*,GEGLU> / wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>"
-    if norm or "wave_gemm_group" in n or "rows_group_kernel" in n or "cross_attention_kernel" in n or wave and wave[1] == "0":
+    if norm or "wave_gemm_group" in n or "rows_group_kernel" in n or "cross_attention_kernel" in n or "query_attention_kernel" in n or wave and wave[1] == "0":
         return "norm_gemm_kernel / wave_gemm_kernel<*,A_ROWS>"
     if wave or "conv_patch_kernel" in n or "igemm_dma_kernel<64, 64, 2, 2" in n:
         return "wave_gemm_kernel<*,A_MAP> / conv_patch_kernel / igemm_dma_kernel<64,64,*>"

@@ -1,5 +1,6 @@
-"""GPU parity of the cross-attention layer over map pixels where its one-launch form ends: key counts around its tiles of 16 and 32 keys and past the last
-one, row tiles that end inside a batch element, tiles whose pixels are no runs of four, one batch element and three.  The float rows of a transformer block
+"""GPU parity of the cross-attention layer over map pixels where its forms of few launches end: key counts around its tiles of 16 and 32 keys and past the last
+one, row tiles that end inside a batch element, tiles whose pixels are no runs of four, one batch element and three, few rows and many (one launch for the layer
+from forty workgroups of 32 rows on, below and at 640 channels a workgroup per head and the product behind it).  The float rows of a transformer block
 have their cases in test_gpu_blocks.py."""
 import pytest
 import torch
@@ -9,16 +10,19 @@ from helpers import DEV
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,H,W,tile,n_ctx", [(2, 64, 64, 8, 77), (2, 24, 24, 3, 77), (1, 36, 20, 4, 1), (3, 16, 16, 2, 8), (2, 20, 20, 1, 31), (1, 64, 40, 8, 32),
-                                              (2, 24, 24, 4, 33), (2, 32, 16, 4, 48), (1, 32, 24, 4, 63), (2, 24, 24, 4, 64), (2, 24, 24, 4, 65), (2, 24, 24, 4, 72),
-                                              (2, 24, 24, 4, 80), (2, 24, 24, 4, 81)])
-def test_cross_attention_layer_of_320_channels(B, H, W, tile, n_ctx):
+MANY = [(2, 64, 64, 8, 77), (2, 36, 36, 3, 77), (1, 36, 40, 4, 1), (3, 24, 20, 2, 8), (2, 28, 26, 1, 31), (1, 64, 40, 8, 32), (2, 28, 28, 4, 33), (2, 32, 24, 4, 48), (1, 48, 32, 4, 63),
+        (2, 28, 28, 4, 64), (2, 28, 28, 4, 65), (2, 28, 28, 4, 72), (2, 28, 28, 4, 80), (2, 28, 28, 4, 81)]
+FEW = [(1, 8, 8, 1, 77), (2, 12, 12, 3, 77), (1, 20, 16, 4, 1), (3, 10, 10, 2, 8), (2, 12, 8, 4, 31), (2, 16, 16, 4, 33), (1, 32, 24, 8, 63), (2, 12, 12, 2, 64), (2, 12, 12, 4, 65), (2, 12, 20, 4, 80), (1, 12, 12, 4, 81)]
+
+
+@pytest.mark.parametrize("C,B,H,W,tile,n_ctx", [(320, *c) for c in MANY + FEW] + [(640, *c) for c in FEW + MANY[:3]])
+def test_cross_attention_layer(C, B, H, W, tile, n_ctx):
     from paper_2305_17423_amd import binding as fb
-    C, heads, stride = 320, 8, (n_ctx + 7) // 8 * 8 + 8
+    heads, stride = 8, (n_ctx + 7) // 8 * 8 + 8
     g = torch.Generator(device=DEV).manual_seed(n_ctx + H)
     normal = lambda *shape, std=1.0: (torch.randn(*shape, generator=g, device=DEV) * std).bfloat16()      # noqa: E731
     x, y = normal(B, H, W, C), normal(B, H, W, C)
-    gam, bet, wq, wo, bo = 1 + normal(C, std=0.1), normal(C, std=0.1), normal(C, C, std=0.08), normal(C, C, std=0.05), normal(C, std=0.1)
+    gam, bet, wq, wo, bo = 1 + normal(C, std=0.1), normal(C, std=0.1), normal(C, C, std=1.4 * C ** -0.5), normal(C, C, std=0.9 * C ** -0.5), normal(C, std=0.1)
     K, V = normal(B, n_ctx, C), torch.full((B, C, stride), float("nan"), dtype=torch.bfloat16, device=DEV)      # the columns past the last key hold anything
     V[:, :, :n_ctx] = normal(B, C, n_ctx)
     tiles = (H // tile) * (W // tile)
