@@ -2,6 +2,7 @@
 // multiples of 32 go to the MFMA implicit GEMM; float maps and odd channel counts
 // (e.g. the 4-channel latent) use the scalar kernel below, one output element per
 // thread, same gather rules.
+#include <type_traits>
 #include "igemm.h"
 
 namespace fise {
@@ -234,56 +235,62 @@ __global__ __launch_bounds__(256) void conv_f32_tile_kernel(const float* __restr
 }
 
 // The same product for a few tiles, where its chain of stages and barriers is all the time there is: eight waves share the K
-// range of one 32 x 32 tile in units of (tap, 8 channels), operands go from memory into the matrix registers (a lane
-// loads four consecutive channels of its row and of its column, the two halves of a wave eight), a batch of nine units
-// is requested at once, and the waves' sums meet in LDS.  One barrier.  What bounds it is the round trips of its batches (32-byte
-// pieces); nine a batch are the one trip that 64 channels under 3x3 need (80 rows x 64 x 576: 9.0 -> 8.3 us, 19.4 on the staged kernel).
+// range of one E x E tile in units of 256 / E channels of a tap, operands go from memory into the matrix registers (a lane
+// loads four consecutive channels of its row and of its column), a batch of nine (five) units
+// is requested at once, and the waves' sums meet in LDS.  One barrier.  What bounds it is the round trips of its batches; a batch is the one trip
+// that 64 channels under 3x3 need (80 rows x 64 x 576: 9.0 -> 8.3 us, 19.4 on the staged kernel).  Tiles of 16 x 16 bring half the bytes into a CU
+// in pieces of 64 instead of 32 and take its matrix units a quarter as long as 32 x 32: for launches that leave most CUs idle.
+template <int E>
 __global__ __launch_bounds__(512) void conv_f32_wave_kernel(const float* __restrict__ x, int Cin, int B, int Hin, int Win,
                                                             const float* __restrict__ w, const float* __restrict__ bias, int Cout,
                                                             int ksize, int stride, int ups, const float* __restrict__ temb,
                                                             const float* residual, const int* __restrict__ tile_idx, int Ma, int tile,
                                                             int tile_w, int Ho, int Wo, FastDiv d_units, float* y) {
-    constexpr int NW = 8, BATCH = 9;
-    __shared__ float part[NW][32][33];
-    __shared__ int rb[32], rpix[32];
-    const int t = threadIdx.x, lane = t & 63, l32 = lane & 31, hl = lane >> 5, rows = B * Ma;
+    constexpr int NW = 8, UNIT = 256 / E, BATCH = E == 32 ? 9 : 5;       // UNIT: channels of a unit
+    __shared__ float part[NW][E][E + 1];
+    __shared__ int rb[E], rpix[E];
+    const int t = threadIdx.x, lane = t & 63, le = lane & (E - 1), hl = lane / E, rows = B * Ma;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
-    const bool row_ok = m0 + l32 < rows;
-    const int gm = row_ok ? m0 + l32 : 0, b = gm / Ma;
+    const int m0 = blockIdx.x * E, n0 = blockIdx.y * E;
+    const bool row_ok = m0 + le < rows;
+    const int gm = row_ok ? m0 + le : 0, b = gm / Ma;
     int oy, ox;
     active_pixel(tile_idx, gm - b * Ma, tile, tile_w, Wo / tile_w, oy, ox);
-    if (t < 32) { rb[t] = row_ok ? b : -1; rpix[t] = (b * Ho + oy) * Wo + ox; }
-    const int pad = ksize >> 1, units = Cin / 8, total = ksize * ksize * units;       // units of a tap, of all taps
+    if (t < E) { rb[t] = row_ok ? b : -1; rpix[t] = (b * Ho + oy) * Wo + ox; }
+    const int pad = ksize >> 1, units = Cin / UNIT, total = ksize * ksize * units;       // units of a tap, of all taps
     const int hh = ups ? 2 * Hin : Hin, ww = ups ? 2 * Win : Win;
-    const float* const wrow = w + (size_t)min(n0 + l32, Cout - 1) * ksize * ksize * Cin + hl * 4;     // columns past Cout are not stored
-    f32x16v acc = {};
+    const float* const wrow = w + (size_t)min(n0 + le, Cout - 1) * ksize * ksize * Cin + hl * 4;     // columns past Cout are not stored
+    typename std::conditional<E == 32, f32x16v, f32x4_t>::type acc = {};
+    auto multiply = [&](float p, float q) {
+        if constexpr (E == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(p, q, acc, 0, 0, 0);
+        else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(p, q, acc, 0, 0, 0);
+    };
     for (int u0 = wave; u0 < total; u0 += NW * BATCH) {
         float4 av[BATCH], bv[BATCH]; bool ok[BATCH];
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
-            const int u = min(u0 + i * NW, total - 1), tap = (int)fdiv((unsigned)u, d_units), c = (u - tap * units) * 8;
+            const int u = min(u0 + i * NW, total - 1), tap = (int)fdiv((unsigned)u, d_units), c = (u - tap * units) * UNIT;
             const int ky = ksize == 1 ? 0 : (tap * 11) >> 5, kx = tap - ky * ksize;
             const int iy = oy * (ups ? 1 : stride) + ky - pad, ix = ox * (ups ? 1 : stride) + kx - pad;
             ok[i] = row_ok && u0 + i * NW < total && (unsigned)iy < (unsigned)hh && (unsigned)ix < (unsigned)ww;
             const size_t pix = ok[i] ? ((size_t)b * Hin + (ups ? iy >> 1 : iy)) * Win + (ups ? ix >> 1 : ix) : 0;      // absent: any pixel
             av[i] = *reinterpret_cast<const float4*>(x + pix * Cin + c + hl * 4);
-            bv[i] = *reinterpret_cast<const float4*>(wrow + (size_t)u * 8);
+            bv[i] = *reinterpret_cast<const float4*>(wrow + (size_t)u * UNIT);
         }
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
             if (u0 + i * NW >= total) break;            // uniform in a wave
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ok[i] ? av[i].x : 0.f, bv[i].x, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ok[i] ? av[i].y : 0.f, bv[i].y, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ok[i] ? av[i].z : 0.f, bv[i].z, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ok[i] ? av[i].w : 0.f, bv[i].w, acc, 0, 0, 0);
+            multiply(ok[i] ? av[i].x : 0.f, bv[i].x);
+            multiply(ok[i] ? av[i].y : 0.f, bv[i].y);
+            multiply(ok[i] ? av[i].z : 0.f, bv[i].z);
+            multiply(ok[i] ? av[i].w : 0.f, bv[i].w);
         }
     }
 #pragma unroll
-    for (int e = 0; e < 16; ++e) part[wave][(e >> 2) * 8 + hl * 4 + (e & 3)][l32] = acc[e];
+    for (int e = 0; e < E * E / 64; ++e) part[wave][(e >> 2) * 8 + hl * 4 + (e & 3)][le] = acc[e];
     __syncthreads();
-    if (t >= 256) return;
-    const int r = t >> 3, c = (t & 7) * 4, col = n0 + c;
+    if (t >= E * E / 4) return;
+    const int r = t / (E / 4), c = t % (E / 4) * 4, col = n0 + c;
     if (col >= Cout || rb[r] < 0) return;                // Cout % 4 == 0: a group of four is inside or outside as a whole
     const size_t o = (size_t)rpix[r] * Cout + col;
     float v[4];
@@ -365,15 +372,20 @@ int conv_dispatch(const fise_conv_args* a, void* workspace, size_t workspace_byt
         if (nview && a->dtype != FISE_BF16) return fail(FISE_ERR_DTYPE, "fise_masked_conv: normalised copies need bf16 maps");
         if (a->dtype == FISE_F32 && a->C1 == 0 && !a->gn_mean && a->C0 % 16 == 0 && a->Cout % 4 == 0) {
             const int Ma = a->n_active * a->tile * tile_cols(a), rows = a->B * Ma;
-            const dim3 grid(ceil_div(rows, 32), ceil_div(a->Cout, 64)), wgrid(ceil_div(rows, 32), ceil_div(a->Cout, 32));
+            const dim3 grid(ceil_div(rows, 32), ceil_div(a->Cout, 64)), wgrid(ceil_div(rows, 32), ceil_div(a->Cout, 32)), sgrid(ceil_div(rows, 16), ceil_div(a->Cout, 16));
+            constexpr long long F32_SMALL = 512;     // tiles of 16 x 16 up to two for each CU (comment below)
             // Up to one 32 x 32 tile per CU it is the faster one at every size measured (8 - 256 tiles; us here / staged at 256): 3x3 of 16
             // channels 5.3 / 8.8, 64 9.2 / 20.1, 320 27 / 84, 1280 101 / 324; 1x1 of 16 4.3 / 4.4, 64 5.2 / 5.7, 1280 15 / 39.  A second tile per CU
             // costs a second round: at 320 tiles 1x1 of 64 channels 7.3 / 5.8, of 128 7.7 / 7.5, though 3x3 of 64 still 15 / 20.
+            // Of its two tiles 16 x 16 while there are at most two for each CU (detection and convolution alone, us, 32 x 32 and 16 x 16): 40 tiles of 64 channels
+            // 29.1, 26.4; 256 of 128 channels 33.5, 28.4; 512 of 64 29.2, 27.9; 960 of 64 29.4, 32.1.
             // Pixel numbers of the output have 32 bits.
             if ((long long)wgrid.x * wgrid.y <= 256 && (long long)a->B * Ho * Wo < (1ll << 31)) {
-                hipLaunchKernelGGL(conv_f32_wave_kernel, wgrid, dim3(512), 0, st, (const float*)a->x0, a->C0, a->B, a->H, a->W, (const float*)a->w,
-                                   (const float*)a->bias, a->Cout, a->ksize, a->stride, a->upsample ? 1 : 0, a->temb, (const float*)a->residual,
-                                   a->tile_idx, Ma, a->tile, tile_cols(a), Ho, Wo, fast_div(a->C0 / 8), (float*)a->y_cache);
+#define FISE_F32_WAVE(E, GRID) hipLaunchKernelGGL(conv_f32_wave_kernel<E>, GRID, dim3(512), 0, st, (const float*)a->x0, a->C0, a->B, a->H, a->W, (const float*)a->w, \
+                               (const float*)a->bias, a->Cout, a->ksize, a->stride, a->upsample ? 1 : 0, a->temb, (const float*)a->residual,                  \
+                               a->tile_idx, Ma, a->tile, tile_cols(a), Ho, Wo, fast_div(a->C0 / (256 / E)), (float*)a->y_cache)
+                if ((long long)sgrid.x * sgrid.y <= F32_SMALL) FISE_F32_WAVE(16, sgrid); else FISE_F32_WAVE(32, wgrid);
+#undef FISE_F32_WAVE
                 FISE_CHECK_LAUNCH("fise_masked_conv(fp32, few tiles)");
                 return FISE_OK;
             }

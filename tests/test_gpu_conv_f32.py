@@ -44,3 +44,18 @@ def test_conv_f32_few_tiles(case):
     fb.fise_masked_conv(fb.conv_args(xd, wd, bd, ixd, n, t, y, ksize=k, stride=stride, upsample=ups, temb=tembd, residual=resd), None)
     # K <= 1152 float products and sums: K 2^-24 = 7e-5 of the largest term at worst, 1e-5 as the sums here go
     check_map(host(y), want, cache.astype(np.float64), active_mask(ix, t, Ho, Wo), 1e-5, name)
+
+
+FORMS = [
+    # tiles of 16 x 16 up to 512 of them, 32 x 32 up to 256 of those: both sides of the rule, rows and columns that end inside a tile, batches that end inside
+    ("16-row-tiles-17-rows", 1, 8, 8, 80, 20, 3, 1, 0, 1, 17, True, True),                # 45 units of 16 channels: two batches of five for five of eight waves
+    ("16-row-tiles-512", 1, 64, 64, 32, 32, 3, 1, 0, 8, 64, False, True),
+    ("32-row-tiles-4001-rows", 1, 64, 64, 48, 36, 3, 1, 0, 1, 4001, True, True),          # 252 tiles of 32 x 32
+    ("32-row-tiles-a-batch-and-a-unit", 1, 64, 64, 592, 68, 1, 1, 0, 1, 2700, True, False),
+    ("32-row-tiles-stride-2", 2, 64, 32, 32, 64, 3, 2, 0, 8, 32, False, True),
+]
+
+
+@pytest.mark.parametrize("case", FORMS, ids=[c[0] for c in FORMS])
+def test_conv_f32_forms_of_the_wave_kernel(case):
+    test_conv_f32_few_tiles(case)
