@@ -18,6 +18,8 @@ FISE_F32, FISE_BF16 = 0, 1
 FISE_STATS_CACHED, FISE_STATS_FRESH = 0, 1
 FISE_MAX_LEVELS = 8
 _lib = None
+_initialized = torch.cuda.is_initialized
+_raw_stream, _device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))      # absent in a build of torch without GPUs
 
 vp, i32, f32, sz, i64 = C.c_void_p, C.c_int, C.c_float, C.c_size_t, C.c_int64
 
@@ -144,24 +146,27 @@ def _p(t):
     """Device (or host) address of a tensor, None -> NULL."""
     if t is None:
         return None
-    if not hasattr(t, "data_ptr"):          # a bare number here would reach a kernel as an address
-        raise TypeError(f"expected a tensor or None where a buffer is passed, got {type(t).__name__}")
-    return t.data_ptr()
+    try:
+        return t.data_ptr()
+    except AttributeError:                  # a bare number here would reach a kernel as an address
+        raise TypeError(f"expected a tensor or None where a buffer is passed, got {type(t).__name__}") from None
 
 
 def _dt(t):
-    if t.dtype == torch.float32:
-        return FISE_F32
-    if t.dtype == torch.bfloat16:
+    d = t.dtype
+    if d is torch.bfloat16:
         return FISE_BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    if d is torch.float32:
+        return FISE_F32
+    raise TypeError(f"unsupported dtype {d}")
 
 
 def _stream(stream):
     if stream is None:
-        # the handle alone: the Stream object around it costs 2.9 us a call, more than the launch (a mask detection 6.9 -> 4 us)
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        # the handle alone: the Stream object around it costs 2.9 us a call, more than the launch (a mask detection 6.9 -> 4 us), and
+        # torch.cuda.current_device() twice the call that it ends in
+        if _initialized():
+            return _raw_stream(_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 
