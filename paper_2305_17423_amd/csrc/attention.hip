@@ -791,33 +791,45 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
 }
 
 // out[b,m,c] = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max_s m_s), splits visited in index order.
-// One thread per four channels (d is a multiple of 8: the four share a head, hence the weights).
+// One thread per four channels (d is a multiple of 8: the four share a head, hence the weights).  Bound by its launch and its trips to memory: the parts
+// of up to MERGE_AHEAD splits are requested together with their weights, one trip instead of two, and the positions come from 32-bit divisions.
+constexpr int MERGE_AHEAD = 6;
 __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                              int B, int M, int C, int heads, int d, int splits,
+                                                              int B, int M, int C, int heads, FastDiv d_C4, FastDiv d_M, FastDiv d_d, int splits,
                                                               bf16_t* __restrict__ out) {
-    const int C4 = C / 4;
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long long)B * M * C4) return;
-    const int c = (int)(i % C4) * 4, m = (int)((i / C4) % M), b = (int)(i / ((long long)C4 * M));
-    const int h = c / d;
+    const unsigned i = blockIdx.x * 256u + threadIdx.x, row = fdiv(i, d_C4);
+    if (row >= (unsigned)B * (unsigned)M) return;
+    const int c = (int)(i - row * (unsigned)(C / 4)) * 4, b = (int)fdiv(row, d_M), m = (int)row - b * M;
+    const int h = (int)fdiv((unsigned)c, d_d);
     const size_t ml_stride = (size_t)B * heads * M * 2, o_stride = (size_t)B * M * C;
     const float* ml0 = part_ml + (((size_t)b * heads + h) * M + m) * 2;
-    const float* o0 = part_o + ((size_t)b * M + m) * C + c;
+    const float* o0 = part_o + (size_t)row * C + c;
+    float2 ml[MERGE_AHEAD]; float4 o[MERGE_AHEAD];
+#pragma unroll
+    for (int s = 0; s < MERGE_AHEAD; ++s) {                    // past the last split: the last one again, not used
+        const int sp = min(s, splits - 1);
+        ml[s] = *reinterpret_cast<const float2*>(ml0 + sp * ml_stride);
+        o[s] = *reinterpret_cast<const float4*>(o0 + sp * o_stride);
+    }
     float mx = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < MERGE_AHEAD; ++s) mx = fmaxf(mx, ml[s].x);
 #pragma unroll 8
-    for (int s = 0; s < splits; ++s) mx = fmaxf(mx, ml0[s * ml_stride]);     // unrolled: the loads go out together, not one round trip each
+    for (int s = MERGE_AHEAD; s < splits; ++s) mx = fmaxf(mx, ml0[s * ml_stride]);       // unrolled: the loads go out together, not one round trip each
     float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
     float den = 0.f;
-#pragma unroll 4
-    for (int s = 0; s < splits; ++s) {
-        const float2 ml = *reinterpret_cast<const float2*>(ml0 + s * ml_stride);
-        const float4 o = *reinterpret_cast<const float4*>(o0 + s * o_stride);
+    auto add = [&](const float2& ml, const float4& o) {
         const float w = __builtin_amdgcn_exp2f(ml.x - mx);  // an empty split has m = -inf: weight 0
         num.x += w * o.x; num.y += w * o.y; num.z += w * o.z; num.w += w * o.w;
         den += w * ml.y;
-    }
+    };
+#pragma unroll
+    for (int s = 0; s < MERGE_AHEAD; ++s)
+        if (s < splits) add(ml[s], o[s]);
+#pragma unroll 4
+    for (int s = MERGE_AHEAD; s < splits; ++s) add(*reinterpret_cast<const float2*>(ml0 + s * ml_stride), *reinterpret_cast<const float4*>(o0 + s * o_stride));
     const float inv = 1.0f / den;
-    *reinterpret_cast<uint2*>(out + ((size_t)b * M + m) * C + c) = make_uint2(f2bf2(num.x * inv, num.y * inv), f2bf2(num.z * inv, num.w * inv));
+    *reinterpret_cast<uint2*>(out + (size_t)row * C + c) = make_uint2(f2bf2(num.x * inv, num.y * inv), f2bf2(num.z * inv, num.w * inv));
 }
 
 template <int D>
@@ -897,7 +909,7 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
         const long long n = (long long)B * M * (C / 4);
         ProfileScope prof(PROF_ATTENTION_MERGE, 0.0, (double)splits * B * M * C * 4.0 + 2.0 * B * M * C, st);
         hipLaunchKernelGGL(attention_merge_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part_o, part_ml, B, M, C,
-                           heads, d, splits, (bf16_t*)out);
+                           heads, fast_div(C / 4), fast_div(M), fast_div(d), splits, (bf16_t*)out);      // fewer than 2^23 threads: a split launch has at most 640 workgroups' queries
         FISE_CHECK_LAUNCH("attention merge");
     }
     return FISE_OK;
