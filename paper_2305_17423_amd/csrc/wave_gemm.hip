@@ -2,7 +2,7 @@
 //
 //   out[row, n] = epilogue( sum_k A[row, k] * W[n, k]  (+ sum_k A2[row, k] * W2[n, k]) )      (see igemm.h)
 //
-// What bounds the masked step is not bandwidth or MFMA rate but the fixed cost of 222 dependent launches (114 of them this
+// What bounds the masked step is not bandwidth or MFMA rate but the fixed cost of some 200 dependent launches (half of them this
 // kernel), and inside a launch the round trips to memory.  So this kernel is built around them.  What a CU gets through LDS-direct
 // loads depends on who else is at it (operand bytes over time, tiles of 32 x 32 to 64 x 160): 71 - 88 GB/s over a launch with all
 // 256 CUs busy (18 - 22 TB/s together), 110 in the K loop of 240 workgroups whose lines are in L2 (85 where they are not), 125

@@ -66,7 +66,7 @@ def kind_of(name: str):
         return "igemm_dma_kernel<32,128,1,4,3,*>"
     if "igemm_reduce" in n:
         return "igemm_reduce_kernel"
-    if "igemm_kernel" in n:
+    if "igemm_kernel" in n or "conv_out_kernel" in n:
         return "igemm_kernel<...> (GroupNorm prologue)"
     if "attention_merge" in n:
         return "attention_merge_kernel"

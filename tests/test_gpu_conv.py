@@ -239,3 +239,20 @@ def test_apsc_selected_blocks_end_to_end(fb, seed, frac):
     act = active_mask(idx_o, (h, w_), H, W)
     assert act[pix.astype(bool)].all()                                   # the chosen blocks cover every masked pixel
     check_map(host(y), want, cache.astype(np.float64), act, TOL[dt], f"apsc {h}x{w_}")
+
+
+# GroupNorm, SiLU and four output channels (one launch of 4 x 4 pixels a workgroup): one, two and several batches of the waves' pieces, fewer pieces than waves
+# times a batch, groups of two channels, tiles of one and of nine workgroups, patches past every border, normalisation alone, one width past the last
+NARROW = [
+    ("narrow-32", 1, 12, 20, 32, 0, 4, 3, 1, 0, 4, True, 1, False, False, 0.4),
+    ("narrow-96", 2, 24, 24, 96, 0, 4, 3, 1, 0, 12, True, 1, False, False, 0.3),
+    ("narrow-320-tile8", 2, 32, 24, 320, 0, 4, 3, 1, 0, 8, True, 1, False, False, 0.3),
+    ("narrow-384", 1, 16, 16, 384, 0, 4, 3, 1, 0, 4, True, 0, False, False, 0.3),
+    ("narrow-640", 2, 16, 8, 640, 0, 4, 3, 1, 0, 8, True, 1, False, False, 0.5),
+    ("narrow-672", 1, 16, 16, 672, 0, 4, 3, 1, 0, 8, True, 1, False, False, 0.5),
+]
+
+
+@pytest.mark.parametrize("case", NARROW, ids=[c[0] for c in NARROW])
+def test_bf16_conv_of_four_columns(fb, case):
+    test_bf16_conv_variants(fb, case)
