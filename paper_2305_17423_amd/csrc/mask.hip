@@ -245,7 +245,7 @@ __device__ __forceinline__ double ordered_sum(double s, const double* src, int t
         if (i0 == 0)
             for (; done < min(lanes, HEAD); ++done) take(done);
         while (done < lanes) {
-            const int e = __builtin_amdgcn_readfirstlane((int)(__double_as_longlong(s) >> 52));
+            const int e = __builtin_amdgcn_readfirstlane((int)(__double_as_longlong(s) >> 52)) & 0x7ff;        // of a NaN whatever its sign
             if (e == 0x7ff) return s;
             const double one = __longlong_as_double((long long)e << 52);       // 2^e; zero: the sum is zero
             if (ties > TIES || __builtin_amdgcn_readfirstlane((int)(top > 0.5 * one))) {
