@@ -65,8 +65,8 @@ __global__ __launch_bounds__(256) void conv_scalar_kernel(const T* __restrict__ 
 // SiLU(GroupNorm(x)) under a 3x3 kernel with four output channels (the UNet's output convolution).  Four columns leave a matrix tile of the general
 // product 15/16 empty and its K range is then split and summed by a second launch; here a workgroup takes 4 x 4 pixels: their 6 x 6 patch is
 // normalised into LDS once, every wave multiplies a quarter of the 32-channel pieces of the nine taps, whose weights it requested up front.
-// Bound by two trips to memory and its barriers.  1536 pixels of 320 channels, with the sum, 17.5 -> 7.9 us, 8192 30.7 -> 8.7; from 640 channels on the patch no longer
-// fits the 64 KB of LDS that a launch has without asking.
+// Bound by two trips to memory and its barriers.  1536 pixels of 320 channels, with the sum, 17.5 -> 7.9 us, 8192 30.7 -> 8.7.  Up to 640
+// channels, whose patch is 47 of the 64 KB of LDS that a launch has without asking (896 do not fit).
 constexpr int CO_PATCH = 36, CO_MAX_C = 640;
 __global__ __launch_bounds__(256) void conv_out_kernel(const bf16_t* __restrict__ x, int C, int H, int W, const bf16_t* __restrict__ w, const bf16_t* __restrict__ bias,
                                                        const float* __restrict__ mean, const float* __restrict__ rstd, const bf16_t* __restrict__ gamma,

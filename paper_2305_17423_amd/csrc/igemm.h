@@ -146,7 +146,7 @@ constexpr int GEMM_GROUP = 32;           // products of one launch
 struct GemmGroup { int first[GEMM_GROUP], N[GEMM_GROUP], mode[GEMM_GROUP]; const bf16_t* w[GEMM_GROUP]; bf16_t* out[GEMM_GROUP]; };    // first: column tile where a product starts
 // base: compact rows, K and geometry; its weights, width and destinations are the products'.  One launch where the sizes allow it.
 int launch_igemm_group(const IgemmArgs& base, const GemmProduct* p, int n, hipStream_t st);
-// The same on tiles of up to 160 rows x 112 columns that may straddle products (rows_group.hip).
+// The same on tiles of up to 224 rows x 112 columns that may straddle products (rows_group.hip).
 bool rows_group_takes(const IgemmArgs& base, const GemmProduct* p, int n);
 int launch_rows_group(const IgemmArgs& base, const GemmProduct* p, int n, hipStream_t st);
 bool wave_gemm_takes(const IgemmArgs& a);
@@ -208,7 +208,7 @@ int launch_gn_scale_shift(const float* mean, const float* rstd, const void* gamm
 int launch_gn_act_halo(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, const float* mean, const float* rstd,
                        const void* gamma, const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act,
                        hipStream_t st, const IgemmWorkspace* iw = nullptr);
-// The same with fresh statistics, in two launches: those of x0 | x1 to mean / rstd (and the scale / shift table ss [B, C], if given), and act with them
+// The same with fresh statistics, in two launches (one for a small map that is active as a whole): those of x0 | x1 to mean / rstd (and the scale / shift table ss [B, C], if given), and act with them
 // (workspace as for fise_groupnorm_stats).
 int launch_gn_stats_act(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, float eps, float* mean, float* rstd, const void* gamma,
                         const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act, float2* ss, void* workspace,

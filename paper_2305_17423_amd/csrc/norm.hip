@@ -274,6 +274,106 @@ __global__ __launch_bounds__(256) void gn_finish_act_kernel(const ActMap a, cons
     act_tile<false>(a, [&](int g) { return stats[g]; }, blockIdx.z, H, W, t, tile, d_side, d_tiles_w);
 }
 
+// The whole of it as one launch, for small maps of which every pixel is active: a workgroup owns a slab of whole groups (a multiple of 8 channels) over
+// all pixels, keeps its values in registers between the sums and the activation, and nothing waits for another workgroup.  A lane holds one piece of eight
+// channels of every PS-th pixel; it adds pairs of values in float, the pairs in double.  Bound by its start, one trip to memory and two barriers.
+// Two batch elements of 16 x 16 x 1280, sums and activation as two launches and this, us: 4.7 + 5.7 -> 4.9; 2560 channels 8.0.  Dense pass of 64 x 64 4867 -> 4757.
+constexpr int GM_THREADS = 512, GM_MAX_J = 8, GM_MAX_GROUPS = GM_THREADS / 64;      // a wave finishes a group
+struct GnMapArgs {
+    ActMap a; int HW, P, gps, slabs; double count; float eps; float* mean; float* rstd; int* zero; int n_zero;      // P: pieces of a slab, gps: its groups
+    FastDiv d_P;
+};
+template <int J>
+__global__ __launch_bounds__(GM_THREADS) void gn_map_kernel(const GnMapArgs g) {
+    constexpr int NT = GM_THREADS;
+    __shared__ double2 sums[2][NT];
+    __shared__ float2 stats[GM_MAX_GROUPS];
+    const ActMap& a = g.a;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.y, C = a.C0 + a.C1;
+    for (int i = (b * gridDim.x + blockIdx.x) * NT + tid; i < g.n_zero; i += gridDim.x * gridDim.y * NT) g.zero[i] = 0;
+    // neighbouring slabs, which share cache lines, on one XCD
+    const int chunk = g.slabs >> 3;
+    int w = blockIdx.x;
+    if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
+    const int ps = (int)fdiv((unsigned)tid, g.d_P), PS = (int)fdiv((unsigned)NT, g.d_P), cc = tid - ps * g.P;
+    const int c = w * g.gps * a.cpg + cc * 8;
+    const bool live = ps < PS;
+    const bf16_t* const src = c < a.C0 ? a.x0 + (size_t)b * g.HW * a.C0 + c : a.x1 + (size_t)b * g.HW * a.C1 + (c - a.C0);
+    const size_t pitch = c < a.C0 ? a.C0 : a.C1;
+    uint4 v[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int p = ps + j * PS;
+        v[j] = live && p < g.HW ? *reinterpret_cast<const uint4*>(src + (size_t)p * pitch) : make_uint4(0, 0, 0, 0);
+    }
+    const uint4 gv = *reinterpret_cast<const uint4*>(a.gamma + c), bv = *reinterpret_cast<const uint4*>(a.beta + c);
+    // a piece lies in one group or straddles one boundary: its channels from `edge` on belong to the next
+    const int gl = (int)fdiv((unsigned)(cc * 8), a.d_cpg), edge = (gl + 1) * a.cpg - cc * 8;
+    {
+        double2 lo = make_double2(0, 0), hi = make_double2(0, 0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            double s = 0, q = 0;
+#pragma unroll
+            for (int j = 0; j < J; j += 2) {
+                float x[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const unsigned word = e < 2 ? v[j + k].x : e < 4 ? v[j + k].y : e < 6 ? v[j + k].z : v[j + k].w;
+                    x[k] = e & 1 ? hi16(word) : lo16(word);
+                }
+                s += (double)(x[0] + x[1]); q += (double)(x[0] * x[0] + x[1] * x[1]);
+            }
+            if (e < edge) { lo.x += s; lo.y += q; } else { hi.x += s; hi.y += q; }
+        }
+        sums[0][tid] = lo; sums[1][tid] = hi;
+    }
+    __syncthreads();
+    if (wave < g.gps) {
+        double s = 0, q = 0;
+        for (int i = lane; i < PS * g.P; i += 64) {
+            const int r = (int)fdiv((unsigned)i, g.d_P), first = (int)fdiv((unsigned)((i - r * g.P) * 8), a.d_cpg);
+            if (first == wave || first + 1 == wave) { const double2 u = sums[first == wave ? 0 : 1][i]; s += u.x; q += u.y; }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) { s += __shfl_xor(s, off); q += __shfl_xor(q, off); }
+        const double m = s / g.count;
+        double var = q / g.count - m * m;
+        if (var < 0) var = 0;
+        if (lane == 0) {
+            const float2 st = make_float2((float)m, (float)(1.0 / sqrt(var + (double)g.eps)));
+            const int i = b * a.G + w * g.gps + wave;
+            stats[wave] = st; g.mean[i] = st.x; g.rstd[i] = st.y;
+        }
+    }
+    __syncthreads();
+    if (!live) return;
+    const float2 st0 = stats[gl], st1 = stats[min(gl + 1, g.gps - 1)];
+    const unsigned gw[4] = {gv.x, gv.y, gv.z, gv.w}, bw[4] = {bv.x, bv.y, bv.z, bv.w};
+    float sc[8], sh[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float2 st = e < edge ? st0 : st1;
+        sc[e] = st.y * (e & 1 ? hi16(gw[e >> 1]) : lo16(gw[e >> 1]));
+        sh[e] = fmaf(-st.x, sc[e], e & 1 ? hi16(bw[e >> 1]) : lo16(bw[e >> 1]));
+        if (a.ss && ps == 0) a.ss[(size_t)b * C + c + e] = make_float2(sc[e], sh[e]);
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int p = ps + j * PS;
+        if (p >= g.HW) break;
+        const unsigned xw[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+        unsigned o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float u0 = fmaf(lo16(xw[e]), sc[2 * e], sh[2 * e]), u1 = fmaf(hi16(xw[e]), sc[2 * e + 1], sh[2 * e + 1]);
+            if (a.silu) { u0 = silu_f(u0); u1 = silu_f(u1); }
+            o[e] = f2bf2(u0, u1);
+        }
+        *reinterpret_cast<uint4*>(a.act + ((size_t)b * g.HW + p) * C + c) = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+}
+
 __global__ void gn_scale_shift_kernel(const float* __restrict__ mean, const float* __restrict__ rstd, const bf16_t* __restrict__ gamma,
                                       const bf16_t* __restrict__ beta, int B, int C, int G, float2* __restrict__ ss) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -501,6 +601,22 @@ static int gn_stats_check(const char* fn, const void* x, const void* x1, int dty
     return FISE_OK;
 }
 
+// Slab of gn_map_kernel: the fewest whole groups whose channels are a multiple of 8.
+struct GnSlab { int groups, pieces; };
+static GnSlab gn_slab(int C, int G) {
+    const int cpg = C / G, unit = cpg % 8 == 0 ? 1 : cpg % 4 == 0 ? 2 : cpg % 2 == 0 ? 4 : 8;
+    if (cpg < 8 || G % unit) return {0, 0};
+    return {unit, unit * cpg / 8};
+}
+// Pieces a lane of gn_map_kernel holds, 0: two launches.  Up to eight: 32 workgroups of eight 9.5 us (two launches 10.4), of twelve 10.6 (10.1) with 512 lanes
+// as with 1024, 64 of twelve 12.6 (12).  Fewer than 32
+// workgroups were not measured.  Channels: what the statistics' launch takes.
+static int gn_map_values(const GnSlab& s, int B, int HW, int C, int G) {
+    if (!s.groups || C * sizeof(double2) > 64 * 1024 || s.pieces > GM_THREADS || (long long)B * (G / s.groups) < 32) return 0;
+    const int n = ceil_div(HW, GM_THREADS / s.pieces);
+    return n <= GM_MAX_J ? n : 0;
+}
+
 int fise::launch_gn_stats_act(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, float eps, float* mean, float* rstd, const void* gamma,
                               const void* beta, int G, int silu, const int* tile_idx, int n_active, int tile, void* act, float2* ss, void* workspace,
                               hipStream_t st, const IgemmWorkspace* iw) {
@@ -512,12 +628,26 @@ int fise::launch_gn_stats_act(const void* x0, const void* x1, int C0, int C1, in
         if (int e = gn_stats_run(fn, x0, x1, FISE_BF16, B, H, W, C0, C1, G, eps, mean, rstd, (double2*)workspace, st, ss ? gamma : nullptr, ss ? beta : nullptr, ss)) return e;
         return launch_gn_act_halo(x0, x1, C0, C1, B, H, W, mean, rstd, gamma, beta, G, silu, tile_idx, n_active, tile, act, st, iw);
     }
+    const bool zero = iw && iw->counters && !iw->counters_zeroed;
+    const GnSlab slab = gn_slab(C, G);
+    const int values = gn_map_values(slab, B, H * W, C, G);
+    if ((long long)n_active * tile * tile == (long long)H * W && C0 % 8 == 0 && C1 % 8 == 0 && values && aligned16(x0) && (C1 == 0 || aligned16(x1))) {
+        GnMapArgs m{};
+        m.a = act_map(x0, x1, C0, C1, mean, rstd, gamma, beta, G, silu, tile, false, act, ss);
+        m.HW = H * W; m.P = slab.pieces; m.gps = slab.groups; m.slabs = G / slab.groups; m.count = (double)H * W * (C / G); m.eps = eps; m.mean = mean; m.rstd = rstd;
+        m.zero = zero ? iw->counters : nullptr; m.n_zero = zero ? IGEMM_COUNTERS : 0; m.d_P = fast_div(slab.pieces);
+        const dim3 grid(m.slabs, B);
+        if (values <= 4) hipLaunchKernelGGL(gn_map_kernel<4>, grid, dim3(GM_THREADS), 0, st, m);
+        else hipLaunchKernelGGL(gn_map_kernel<GM_MAX_J>, grid, dim3(GM_THREADS), 0, st, m);
+        FISE_CHECK_LAUNCH("gn statistics and activation of a map");
+        if (zero) iw->counters_zeroed = true;
+        return FISE_OK;
+    }
     if (int e = gn_stats_run(fn, x0, x1, FISE_BF16, B, H, W, C0, C1, G, eps, mean, rstd, (double2*)workspace, st, nullptr, nullptr, nullptr, false)) return e;
     ActMap a = act_map(x0, x1, C0, C1, mean, rstd, gamma, beta, G, silu, tile, false, act, ss);
     a.z = std::max(1, std::min(a.z, 1024 / (n_active * B)));      // each workgroup reads the partial sums: four to a CU at most
     int log_gp = 0;
     while ((1 << log_gp) < G) ++log_gp;
-    const bool zero = iw && iw->counters && !iw->counters_zeroed;
     hipLaunchKernelGGL(gn_finish_act_kernel, dim3(n_active, B, a.z), dim3(256), 0, st, a, (const double2*)workspace, ceil_div(H * W, GS_PIX), log_gp,
                        (double)H * W * (C / G), eps, mean, rstd, H, W, tile_idx, tile, fast_div(tile + 2), fast_div(W / tile), zero ? iw->counters : nullptr,
                        zero ? IGEMM_COUNTERS : 0);

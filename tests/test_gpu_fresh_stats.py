@@ -52,3 +52,11 @@ def test_resnet_block_with_fresh_statistics(fb, B, H, W, C, G, tile, tiles):
     act = active_mask(idx, tile, H, W)
     check_map(host(h1), want["r.h1"], h_old, act, TOL[DT], "h1")
     check_map(host(out), want["r.out"], out_old, act, TOL[DT], "out")
+
+
+# every pixel of a small map active: pieces of 8 channels inside a group and across its edge, 1 to 8 pieces a lane, pixels that leave lanes idle,
+# three batch elements; the last two are maps that are too large for one launch
+@pytest.mark.parametrize("B,H,W,C,G,tile,tiles", [(2, 16, 16, 256, 32, 4, 16), (2, 8, 8, 640, 32, 2, 16), (3, 16, 24, 384, 32, 8, 6), (2, 24, 24, 640, 32, 8, 9),
+                                                  (8, 16, 24, 288, 32, 8, 6), (2, 24, 34, 640, 32, 2, 204), (2, 28, 32, 640, 32, 4, 56), (8, 24, 24, 288, 32, 8, 9)])
+def test_resnet_block_with_fresh_statistics_of_an_active_map(fb, B, H, W, C, G, tile, tiles):
+    test_resnet_block_with_fresh_statistics(fb, B, H, W, C, G, tile, tiles)
