@@ -4,6 +4,7 @@
 // adaptive block-size choice.
 #include <algorithm>
 #include "common.h"
+#include "ordered_sum.h"
 
 namespace fise {
 
@@ -210,84 +211,32 @@ template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_or_zero(doub
     const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false), hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
     return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
 }
-__device__ __forceinline__ double lane_value(double x, int lane) {
-    const long long b = __double_as_longlong(x);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, lane), hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
-}
-#endif
-
-// s + src[0] + src[1] + ... with every addition rounded in this order, by one wave; 0 <= values < top, no subnormals (or NaN: the sum is).  While the
-// sum stays in one binade [2^e, 2^(e+1)) it is a multiple of its last place, and an addition moves it by the value rounded to a
-// multiple of that: they add up exactly in any order.  So a block of 256 values, four a lane, is rounded in parallel (added to 1.5 x 2^e and taken back)
-// and scanned.  The first lane in which the sum reaches the next binade, or a value lies half way between two places (then the
-// sum's last bit decides), adds its four values one by one, and the scan goes on behind it.  Blocks with many such values, and values of
-// 2^(e-1) and more, are added one by one.
-__device__ __forceinline__ double ordered_sum(double s, const double* src, int total, double top, int lane) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int Q = 4, BLOCK = 64 * Q, HEAD = 8, TIES = 8;   // HEAD: lanes of the first values, which change the binade all the time
-    double v[Q], next[Q];
-    auto fetch = [&](double (&x)[Q], int i0) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) { const int i = i0 + lane * Q + q; x[q] = src[min(i, total - 1)]; if (i >= total) x[q] = 0.0; }
-    };
-    auto take = [&](int at) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) s += lane_value(v[q], at);
-    };
-    if (total > 0) fetch(next, 0);
-    for (int i0 = 0; i0 < total; i0 += BLOCK) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) v[q] = next[q];
-        fetch(next, i0 + BLOCK);
-        int done = 0, ties = 0;                                // lanes whose values are in the sum
-        const int lanes = min(64, (total - i0 + Q - 1) / Q);
-        if (i0 == 0)
-            for (; done < min(lanes, HEAD); ++done) take(done);
-        while (done < lanes) {
-            const int e = __builtin_amdgcn_readfirstlane((int)(__double_as_longlong(s) >> 52)) & 0x7ff;        // of a NaN whatever its sign
-            if (e == 0x7ff) return s;
-            const double one = __longlong_as_double((long long)e << 52);       // 2^e; zero: the sum is zero
-            if (ties > TIES || __builtin_amdgcn_readfirstlane((int)(top > 0.5 * one))) {
-                if (e == 0) {                                  // passes over zeros
-                    const unsigned long long some = __ballot(!(v[0] == 0 && v[1] == 0 && v[2] == 0 && v[3] == 0)) & (~0ull << done);
-                    if (!some) break;
-                    done = __builtin_ctzll(some);
-                }
-                const int until = min(lanes, done + HEAD);
-                for (; done < until; ++done) take(done);
-                continue;
-            }
-            const double grid = 1.5 * one, half = one * 0x1p-53, end = 2.0 * one;
-            double run = 0.0;
-            unsigned long long tie = 0;
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const double r = (v[q] + grid) - grid;
-                tie |= __ballot(!(fabs(v[q] - r) < half));     // NaN too
-                run += r;
-            }
-            if (lane < done) run = 0.0;
-            double sum = run;                                  // past the binade it only has to stay there
-            sum += dpp_or_zero<0x111, 0xf>(sum); sum += dpp_or_zero<0x112, 0xf>(sum); sum += dpp_or_zero<0x114, 0xf>(sum); sum += dpp_or_zero<0x118, 0xf>(sum);
-            sum += dpp_or_zero<0x142, 0xa>(sum); sum += dpp_or_zero<0x143, 0xc>(sum);      // lane 15 of a row to the next row, lane 31 to the upper half
-            double base = s + dpp_or_zero<0x138, 0xf>(sum);    // the sum in front of this lane
-            for (;;) {
-                const unsigned long long stop = (tie | __ballot(!(base + run < end))) & (~0ull << done);
-                if (!stop) { s = lane_value(base + run, 63); done = 64; break; }
-                const int at = __builtin_ctzll(stop);
-                const double here = lane_value(base + run, at);
-                s = lane_value(base, at);
-                take(at);
-                done = at + 1;
-                if (done >= lanes || __builtin_amdgcn_readfirstlane((int)!(s < end)) || ++ties > TIES) break;      // another binade
-                base += s - here;
-            }
-        }
+// A wavefront for ordered_sum.
+struct Wavefront {
+    using Lanes = double;
+    static __device__ __forceinline__ int lane() { return __lane_id(); }
+    static __device__ __forceinline__ double zero() { return 0.0; }
+    static __device__ __forceinline__ double abs(double x) { return fabs(x); }
+    static __device__ __forceinline__ unsigned long long ballot(bool c) { return __ballot(c); }
+    static __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+    static __device__ __forceinline__ double at(double x, int lane) {
+        const long long b = __double_as_longlong(x);
+        const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, lane), hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+        return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
     }
+    static __device__ __forceinline__ double from(double x, int first) { return lane() < first ? 0.0 : x; }
+    static __device__ __forceinline__ double before(double x) { return dpp_or_zero<0x138, 0xf>(x); }
+    static __device__ __forceinline__ double scan(double x) {
+        x += dpp_or_zero<0x111, 0xf>(x); x += dpp_or_zero<0x112, 0xf>(x); x += dpp_or_zero<0x114, 0xf>(x); x += dpp_or_zero<0x118, 0xf>(x);
+        x += dpp_or_zero<0x142, 0xa>(x); x += dpp_or_zero<0x143, 0xc>(x);      // lane 15 of a row to the next row, lane 31 to the upper half
+        return x;
+    }
+    static __device__ __forceinline__ void load(double (&x)[4], const double* src, int i0, int total) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { const int i = i0 + lane() * 4 + q; x[q] = src[min(i, total - 1)]; if (i >= total) x[q] = 0.0; }
+    }
+};
 #endif
-    return s;
-}
 
 __global__ __launch_bounds__(64 * OTSU_WAVES) void otsu_bins_kernel(const float* __restrict__ diff, int n, OtsuWs* __restrict__ ws) {
     constexpr int NT = 64 * OTSU_WAVES, PER = OTSU_CHUNK / NT;
@@ -361,7 +310,9 @@ __global__ __launch_bounds__(64 * OTSU_WAVES) void otsu_bins_kernel(const float*
             if ((unsigned)bin[j] < (unsigned)OTSU_WG_BINS) mine[bin[j]][(bin[j] == 0 ? base[0] : bin[j] == 1 ? base[1] : bin[j] == 2 ? base[2] : base[3]) + place[j]] = v[j];
         __syncthreads();
         if (wave < OTSU_WG_BINS) {
-            sum = ordered_sum(sum, mine[wave], total, k < OTSU_BINS - 1 ? (k + 1) / 256.0 : 2.0, lane);
+#if defined(__HIP_DEVICE_COMPILE__)
+            sum = ordered_sum<Wavefront>(sum, mine[wave], total, k < OTSU_BINS - 1 ? (k + 1) / 256.0 : 2.0);
+#endif
             count += total;
         }
         __syncthreads();
