@@ -194,7 +194,7 @@ __global__ void or_pool_kernel(const uint8_t* __restrict__ m, int H, int W, uint
 // Otsu in two launches.  Values are min-max normalised in double; bin k of 257 holds values with floor(256 v) == k, so
 // class A of threshold k/256 is exactly bins [0, k).  Every bin's sum is taken in index order: the order is part of the
 // result, so the fullest bin (2082 of 4096 values in an edit's mask) is what bounds this: a chain of dependent additions, 16 cycles each, unless
-// they are rounded ahead (ordered_sum: 15 rounds of ~900 cycles and 11 values on their own instead of 33000 cycles).
+// they are rounded ahead (ordered_sum.h: 15 rounds of ~900 cycles and 11 values on their own instead of 33000 cycles).
 //  - otsu_bins_kernel: four bins per workgroup of sixteen waves.  The waves normalise 4096 values in registers, pack those of each bin behind one
 //    another in LDS (ballots, the waves' counts scanned in between by one lane each), and one wave per bin adds them up from there.
 //  - otsu_apply_kernel: every workgroup finds the threshold for itself (the sums below a bin one chain of 257 additions, the counts
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(64 * OTSU_WAVES) void otsu_bins_kernel(const float*
     __shared__ int wave_cnt[OTSU_WG_BINS * OTSU_WAVES];
     static_assert(OTSU_WG_BINS * OTSU_WAVES == 64 && OTSU_WAVES == 16, "a lane per bin and wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char otsu_lds[];
-    double (*mine)[OTSU_CHUNK] = reinterpret_cast<double (*)[OTSU_CHUNK]>(otsu_lds);      // [OTSU_WG_BINS]
+    double (*mine)[OTSU_CHUNK + 64] = reinterpret_cast<double (*)[OTSU_CHUNK + 64]>(otsu_lds);      // [OTSU_WG_BINS], zeros behind a bin's values
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), k0 = blockIdx.x * OTSU_WG_BINS;
     float flo = INFINITY, fhi = -INFINITY;
 #pragma unroll 4
@@ -303,7 +303,9 @@ __global__ __launch_bounds__(64 * OTSU_WAVES) void otsu_bins_kernel(const float*
 #pragma unroll
         for (int b = 0; b < OTSU_WG_BINS; ++b) {
             base[b] = __builtin_amdgcn_readlane(upto - c, b * OTSU_WAVES + wave);
-            if (wave == b) total = __builtin_amdgcn_readlane(upto, b * OTSU_WAVES + OTSU_WAVES - 1);
+            const int all = __builtin_amdgcn_readlane(upto, b * OTSU_WAVES + OTSU_WAVES - 1);
+            if (wave == b) total = all;
+            if (wave == OTSU_WG_BINS + b) mine[b][all + lane] = 0.0;
         }
 #pragma unroll
         for (int j = 0; j < PER; ++j)
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(64 * OTSU_WAVES) void otsu_bins_kernel(const float*
         __syncthreads();
         if (wave < OTSU_WG_BINS) {
 #if defined(__HIP_DEVICE_COMPILE__)
-            sum = ordered_sum<Wavefront>(sum, mine[wave], total, k < OTSU_BINS - 1 ? (k + 1) / 256.0 : 2.0);
+            sum = ordered_sum<Wavefront>(sum, static_cast<const double*>(mine[wave]), total);
 #endif
             count += total;
         }
@@ -487,7 +489,7 @@ extern "C" size_t fise_otsu_workspace_bytes(void) { return align256(sizeof(OtsuW
 extern "C" int fise_otsu_mask(const float* diff, int n, float* eps_out, uint8_t* pix_mask, void* workspace, void* stream) {
     if (!diff || !eps_out || !pix_mask || !workspace) return fail(FISE_ERR_NULL, "fise_otsu_mask: null pointer");
     if (n < 1) return fail(FISE_ERR_SHAPE, "fise_otsu_mask: n=%d", n);
-    constexpr int lds = OTSU_WG_BINS * OTSU_CHUNK * (int)sizeof(double);
+    constexpr int lds = OTSU_WG_BINS * (OTSU_CHUNK + 64) * (int)sizeof(double);
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&otsu_bins_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return fail(FISE_ERR_HIP, "fise_otsu_mask: cannot raise the dynamic LDS limit");
     hipLaunchKernelGGL(otsu_bins_kernel, dim3(ceil_div(OTSU_BINS, OTSU_WG_BINS)), dim3(64 * OTSU_WAVES), lds, as_stream(stream), diff, n, (OtsuWs*)workspace);

@@ -24,18 +24,21 @@ Lanes operator+(const Lanes& a, const Lanes& b) { return each([&](int i) { retur
 Lanes operator-(const Lanes& a, const Lanes& b) { return each([&](int i) { return a.x[i] - b.x[i]; }); }
 Lanes operator+(const Lanes& a, double b) { return each([&](int i) { return a.x[i] + b; }); }
 Lanes operator-(const Lanes& a, double b) { return each([&](int i) { return a.x[i] - b; }); }
+Flags operator<=(const Lanes& a, double b) { return where([&](int i) { return a.x[i] <= b; }); }
 Flags operator<(const Lanes& a, double b) { return where([&](int i) { return a.x[i] < b; }); }
 Flags operator==(const Lanes& a, double b) { return where([&](int i) { return a.x[i] == b; }); }
 Flags operator!(Flags a) { return {~a.m}; }
 Flags operator&(Flags a, Flags b) { return {a.m & b.m}; }
 Flags operator|(Flags a, Flags b) { return {a.m | b.m}; }
+long long walked;                                        // values read one by one
+struct Values { const double* v; double operator[](int i) const { ++walked; return v[i]; } };
 struct Wave {
     using Lanes = ::Lanes;
     static Lanes zero() { return each([](int) { return 0.0; }); }
     static Lanes abs(const Lanes& a) { return each([&](int i) { return std::fabs(a.x[i]); }); }
     static u64 ballot(Flags a) { return a.m; }
     static int uniform(int x) { return x; }
-    static double at(const Lanes& a, int lane) { return a.x[lane]; }
+    static double at(const Lanes& a, int lane) { ++walked; return a.x[lane]; }
     static Lanes from(const Lanes& a, int first) { return each([&](int i) { return i < first ? 0.0 : a.x[i]; }); }
     static Lanes before(const Lanes& a) { return each([&](int i) { return i ? a.x[i - 1] : 0.0; }); }
     static Lanes scan(Lanes a) {                         // rows of 16, then their last lanes, as the wavefront's moves do it
@@ -43,18 +46,20 @@ struct Wave {
         a = a + each([&](int i) { return i / 16 %% 2 ? a.x[i / 16 * 16 - 1] : 0.0; });
         return a + each([&](int i) { return i >= 32 ? a.x[31] : 0.0; });
     }
-    static void load(Lanes (&x)[4], const double* src, int i0, int total) {
-        for (int q = 0; q < 4; ++q) x[q] = each([&](int i) { const int at = i0 + 4 * i + q; return at < total ? src[at] : 0.0; });
+    static void load(Lanes (&x)[4], const Values& src, int i0, int total) {
+        for (int q = 0; q < 4; ++q) x[q] = each([&](int i) { const int at = i0 + 4 * i + q; return at < total ? src.v[at] : 0.0; });
     }
 };
 int main(int, char** argv) {
     const std::string_view shape = argv[1];
+    const bool one_by_one_counts = argv[3][0] == '1';                  // long sums in chunks of the kernel's size
     int bad = 0, runs = std::atoi(argv[2]);
+    long long all = 0;
     for (int seed = 0; seed < runs; ++seed) {
         std::mt19937_64 g(seed);
         auto unit = [&] { return (g() >> 11) * 0x1p-53; };
-        const int bin = shape == "edge" ? 0 : shape == "nan" ? (int)(g() %% 4) * 64 : (int)(g() %% 257);
-        const double low = bin / 256.0, top = bin < 256 ? (bin + 1) / 256.0 : 2.0;
+        const int bin = shape == "edge" || one_by_one_counts ? 0 : shape == "nan" ? (int)(g() %% 4) * 64 : (int)(g() %% 257);
+        const double low = bin / 256.0;
         std::vector<double> v;
         if (shape == "edge") {                           // up to a few places below 2, then ties and whole places across it
             v.assign(1023, 0x1p-9);
@@ -64,7 +69,7 @@ int main(int, char** argv) {
             v.resize((v.size() + 255) / 256 * 256);
             for (int i = 0; i < 256; ++i) v.push_back((g() %% 8 ? 0 : 1 + g() %% 6) * (g() %% 3 ? 0x1p-53 : 0x1p-52));
         } else {
-            const int n = 1 + g() %% 1500;
+            const int n = one_by_one_counts ? 4096 + (int)(g() %% 5000) : 1 + g() %% 1500;
             const double c = low + unit() / 256;
             for (int i = 0; i < n; ++i) {
                 double x = low + unit() / 256;
@@ -80,15 +85,18 @@ int main(int, char** argv) {
         }
         // in chunks, as the kernel hands them over
         double want = 0, got = 0;
-        const int chunk = g() %% 2 ? 4096 : 700;
+        all += v.size();
+        const int chunk = g() %% 2 || one_by_one_counts ? 4096 : 700;
         for (size_t i = 0; i < v.size(); i += chunk) {
             const int n = (int)std::min<size_t>(chunk, v.size() - i);
             for (int j = 0; j < n; ++j) want += v[i + j];
-            got = fise::ordered_sum<Wave>(got, v.data() + i, n, top);
+            std::vector<double> part(v.begin() + i, v.begin() + i + n);
+            part.resize(n + 16);
+            got = fise::ordered_sum<Wave>(got, Values{part.data()}, n);
         }
         if (std::memcmp(&want, &got, 8) && !(want != want && got != got) && ++bad < 4) std::printf("seed %%d: %%a, in order %%a\n", seed, got, want);
     }
-    std::printf("%%d of %%d differ\n", bad, runs);
+    std::printf("%%d of %%d differ, %%.0f %%%% one by one\n", bad, runs, 100.0 * walked / all);
 }
 """
 
@@ -97,11 +105,22 @@ int main(int, char** argv) {
 def program(tmp_path_factory):
     d = tmp_path_factory.mktemp("ordered_sum")
     (d / "sum.cpp").write_text(PROGRAM % os.path.join(build.CSRC, "ordered_sum.h"))
-    subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-Wno-unknown-pragmas", "-o", str(d / "sum"), str(d / "sum.cpp")], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-g", "-D_GLIBCXX_ASSERTIONS", "-ffp-contract=off", "-Wno-unknown-pragmas", "-o", str(d / "sum"), str(d / "sum.cpp")], check=True)
     return str(d / "sum")
+
+
+def run(program, shape, runs, long=0):
+    out = subprocess.run([program, shape, str(runs), str(long)], check=True, capture_output=True, text=True).stdout
+    assert out.startswith(f"0 of {runs} differ"), out
+    return int(out.split(", ")[1].split()[0])
 
 
 @pytest.mark.parametrize("shape,runs", [("edge", 20000), ("uniform", 1500), ("sparse", 1500), ("tiny", 1500), ("mixed", 1500), ("ties", 1500), ("equal", 1500), ("nan", 500)])
 def test_sums_in_index_order(program, shape, runs):
-    out = subprocess.run([program, shape, str(runs)], check=True, capture_output=True, text=True).stdout
-    assert out == f"0 of {runs} differ\n", out
+    run(program, shape, runs)
+
+
+@pytest.mark.parametrize("shape", ["uniform", "sparse", "tiny", "mixed", "equal"])
+def test_long_sums_are_scanned(program, shape):
+    """4096 and more values of the lowest bin, zeros, tiny and equal ones among them: few are added one by one (32 at the head, four a stop of the scan)."""
+    assert run(program, shape, 200, 1) <= 15
