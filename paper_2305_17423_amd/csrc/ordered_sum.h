@@ -22,7 +22,7 @@ namespace fise {
 // 30.5, 17.2; 9216 57.4, 27.8 (68 and 186 with every sum below 2^-7 added one by one in registers); all equal 61.9, 39.8; ties throughout, 1024 values 16.7, 18.1, 4096 32.2, 30.5.
 // Wave: Lanes, a double for each lane, with arithmetic and comparisons; ballot of a comparison; at(x, lane); from(x, lane): x in this lane and those behind it, else zero; scan: sums
 // over the lanes up to each, of which those that a binade holds are exact; before(x): the lane in front's; load(src, i, total): src[i + 4 lane + 0 .. 3], zeros behind `total`;
-// uniform: a value that all lanes agree on.  Src: the values, and 16 zeros behind them.
+// uniform: a value that all lanes agree on.  Src: the values, 16 zeros behind them and 8 more that can be read.
 template <class Wave, class Src>
 FISE_OS_FN double ordered_sum(double s, Src src, int total) {
     using Lanes = typename Wave::Lanes;
