@@ -31,7 +31,7 @@ Flags operator!(Flags a) { return {~a.m}; }
 Flags operator&(Flags a, Flags b) { return {a.m & b.m}; }
 Flags operator|(Flags a, Flags b) { return {a.m | b.m}; }
 long long walked;                                        // values read one by one
-struct Values { const double* v; double operator[](int i) const { ++walked; return v[i]; } };
+struct Values { const double* v; int n; double operator[](int i) const { if (i < 0 || i >= n) std::abort(); ++walked; return v[i]; } };
 struct Wave {
     using Lanes = ::Lanes;
     static Lanes zero() { return each([](int) { return 0.0; }); }
@@ -92,7 +92,7 @@ int main(int, char** argv) {
             for (int j = 0; j < n; ++j) want += v[i + j];
             std::vector<double> part(v.begin() + i, v.begin() + i + n);
             part.resize(n + 24);
-            got = fise::ordered_sum<Wave>(got, Values{part.data()}, n);
+            got = fise::ordered_sum<Wave>(got, Values{part.data(), n + 24}, n);
         }
         if (std::memcmp(&want, &got, 8) && !(want != want && got != got) && ++bad < 4) std::printf("seed %%d: %%a, in order %%a\n", seed, got, want);
     }
@@ -105,7 +105,7 @@ int main(int, char** argv) {
 def program(tmp_path_factory):
     d = tmp_path_factory.mktemp("ordered_sum")
     (d / "sum.cpp").write_text(PROGRAM % os.path.join(build.CSRC, "ordered_sum.h"))
-    subprocess.run(["g++", "-std=c++17", "-O2", "-fsanitize=address", "-ffp-contract=off", "-Wno-unknown-pragmas", "-o", str(d / "sum"), str(d / "sum.cpp")], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-Wno-unknown-pragmas", "-o", str(d / "sum"), str(d / "sum.cpp")], check=True)
     return str(d / "sum")
 
 
