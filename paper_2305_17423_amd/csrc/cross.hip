@@ -51,6 +51,22 @@ __device__ __forceinline__ float row_sum(float x) {        // over aligned group
 }
 #endif
 
+#if defined(__HIP_DEVICE_COMPILE__)
+// Eight probabilities as a bf16 operand, and what its rounding left of them as another: the product with the values has both.  One softmax over all keys has one
+// weight that is exactly one; of three launches the middle one had one for every 32 keys, so rounded probabilities cost more here.  Layer of 128 rows x
+// 320 channels, error against 64 bits: those 1.738e-3, this with one operand 1.743e-3, with both 1.724e-3 (1536 rows 1.748, 1.748, 1.733), for 0.1 - 0.25 us of 9 - 14.
+struct Probabilities { bf16x8_t high, low; };
+__device__ __forceinline__ Probabilities probabilities(const f32x4_t& x, const f32x4_t& y) {
+    const u32x4_t h = {f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
+    const u32x4_t l = {f2bf2(x[0] - lo16(h.x), x[1] - hi16(h.x)), f2bf2(x[2] - lo16(h.y), x[3] - hi16(h.y)), f2bf2(y[0] - lo16(h.z), y[1] - hi16(h.z)), f2bf2(y[2] - lo16(h.w), y[3] - hi16(h.w))};
+    return {__builtin_bit_cast(bf16x8_t, h), __builtin_bit_cast(bf16x8_t, l)};
+}
+__device__ __forceinline__ f32x4_t weighted(const u32x4_t& v, const Probabilities& p, const f32x4_t& sum) {
+    const bf16x8_t x = __builtin_bit_cast(bf16x8_t, v);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, p.high, __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, p.low, sum, 0, 0, 0), 0, 0, 0);
+}
+#endif
+
 // MAP: rows are pixels of bf16 maps (in and out), else compact float rows, updated in place.
 template <bool MAP>
 __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev g) {
@@ -259,8 +275,7 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
 #pragma unroll
             for (int e = 0; e < 4; ++e) { s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], g.scale_log2e, -mx)); sum += s[t][e]; }
         const float inv = 1.0f / quad_sum(sum);
-        const bf16x8_t p0 = pack8(s[0], s[1]), p1 = pack8(s[2], s[3]);
-        const bf16x8_t p2 = pack4(s[4]);
+        const Probabilities p0 = probabilities(s[0], s[1]), p1 = probabilities(s[2], s[3]), p2 = probabilities(s[4], f32x4_t{0.f, 0.f, 0.f, 0.f});
         auto live = [&](unsigned w, int key) { return key + 1 < a.n_ctx ? w : key < a.n_ctx ? w & 0xffffu : 0u; };       // a word of two keys
 #pragma unroll
         for (int dt = 0; dt < 3; ++dt) {
@@ -269,10 +284,7 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
                 for (int e = 0; e < 4; ++e) { v16[dt][0][e] = live(v16[dt][0][e], 8 * lq + 2 * e); v16[dt][1][e] = live(v16[dt][1][e], 32 + 8 * lq + 2 * e); }
                 v8[dt].x = live(v8[dt].x, 64 + 4 * lq); v8[dt].y = live(v8[dt].y, 66 + 4 * lq);
             }
-            f32x4_t x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v16[dt][0]), p0, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-            x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v16[dt][1]), p1, x, 0, 0, 0);
-            x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(half(v8[dt]), p2, x, 0, 0, 0);
-            o[dt][i] = x * inv;
+            o[dt][i] = weighted(u32x4_t{v8[dt].x, v8[dt].y, 0, 0}, p2, weighted(v16[dt][1], p1, weighted(v16[dt][0], p0, f32x4_t{0.f, 0.f, 0.f, 0.f}))) * inv;
         }
     }
     // what the epilogue adds, under the hand-over and the second product
@@ -504,7 +516,6 @@ __global__ __launch_bounds__(C, 1) void query_attention_kernel(const CrossDev g)
     if (tile < 0) return;
 
     // ---- attention: lane = row l16 of the tile, keys 32 p + 8 lq + 0 .. 7 and 64 + 4 lq + 0 .. 3
-    auto pack8 = [](const f32x4_t& x, const f32x4_t& y) { return __builtin_bit_cast(bf16x8_t, u32x4_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), f2bf2(y[0], y[1]), f2bf2(y[2], y[3])}); };
     bf16x8_t q[T::QC];
 #pragma unroll
     for (int c = 0; c < T::QC; ++c) q[c] = *reinterpret_cast<const bf16x8_t*>(lds + (tile * 16 + l16) * T::QPITCH + c * 64 + lq * 16);
@@ -531,7 +542,7 @@ __global__ __launch_bounds__(C, 1) void query_attention_kernel(const CrossDev g)
 #pragma unroll
         for (int e = 0; e < 4; ++e) { s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], g.scale_log2e, -mx)); sum += s[t][e]; }
     const float inv = 1.0f / quad_sum(sum);
-    const bf16x8_t p0 = pack8(s[0], s[1]), p1 = pack8(s[2], s[3]), p2 = pack8(s[4], f32x4_t{0.f, 0.f, 0.f, 0.f});
+    const Probabilities p0 = probabilities(s[0], s[1]), p1 = probabilities(s[2], s[3]), p2 = probabilities(s[4], f32x4_t{0.f, 0.f, 0.f, 0.f});
     auto live = [&](unsigned x, int key) { return key + 1 < a.n_ctx ? x : key < a.n_ctx ? x & 0xffffu : 0u; };       // a word of two keys
     const int m = m0 + tile * 16 + l16;
     bf16_t* const out = (bf16_t*)a.out + ((size_t)b * a.Ma + m) * C + h * D + lq * 4;
@@ -540,9 +551,7 @@ __global__ __launch_bounds__(C, 1) void query_attention_kernel(const CrossDev g)
 #pragma unroll
         for (int e = 0; e < 4; ++e) { v16[dt][0][e] = live(v16[dt][0][e], 8 * lq + 2 * e); v16[dt][1][e] = live(v16[dt][1][e], 32 + 8 * lq + 2 * e); }
         const u32x4_t tail = {live(v8[dt].x, 64 + 4 * lq), live(v8[dt].y, 66 + 4 * lq), 0, 0};
-        f32x4_t x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v16[dt][0]), p0, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v16[dt][1]), p1, x, 0, 0, 0);
-        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, tail), p2, x, 0, 0, 0) * inv;
+        const f32x4_t x = weighted(tail, p2, weighted(v16[dt][1], p1, weighted(v16[dt][0], p0, f32x4_t{0.f, 0.f, 0.f, 0.f}))) * inv;
         if (m < a.Ma && dt * 16 + lq * 4 < D) *(FISE_AS1 u32x2_t*)(out + dt * 16) = u32x2_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
     }
 #endif
