@@ -77,4 +77,21 @@ inline int attention_form(int B, int M, int n_keys, int n_stride, int C, int hea
     return attention_few(B, M, n_keys, n_stride, C, heads, splits) ? 0 : splits;
 }
 
+// ---- cross.hip: a cross-attention sub-layer over the few keys of a prompt, `Ma` rows of a batch element of maps of HW pixels.  CROSS_LAYER: one launch;
+// CROSS_QUERIES: one launch up to the last product; CROSS_STEPS: a launch each for queries, attention and product.
+constexpr int CROSS_C = 320, CROSS_HEADS = 8, CROSS_KEYS = 80, CROSS_ROWS = 32;
+enum { CROSS_STEPS = 0, CROSS_QUERIES = 1, CROSS_LAYER = 2 };
+inline int cross_form(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW) {
+    if (heads != CROSS_HEADS || n_ctx < 1 || n_ctx > CROSS_KEYS || Ma < 1) return CROSS_STEPS;
+    if (n_stride >= 1 << 20 || Ma >= 1 << 20 || HW >= 1 << 21 || (long long)B * Ma >= 1 << 24 || (long long)B * HW >= 1 << 24) return CROSS_STEPS;       // 32-bit offsets
+    const long long tiles = (long long)B * at_ceil(Ma, CROSS_ROWS);
+    // From forty workgroups on: with fewer, a workgroup per head and a product behind it spread the weights over more CUs.  Step of 64 x 64 with 24 workgroups
+    // 1952 us as one launch and 1939 as two, with 48 2199 and 2206, with 96 2726 and 2761; attention layer of 640 rows (20) 44.8 and 43.0, of 1280 (40) 50.7 and 51.2,
+    // of 4096 (128) 81.3 and 89.2.
+    if (C == CROSS_C) return tiles >= 40 ? CROSS_LAYER : CROSS_QUERIES;
+    // A workgroup per head and tile: one round of the CUs.  In a second one the rows are normalised too often (layer as three launches and as two, us: 992 rows
+    // 22.5, 17.3, 1056 22.8, 24.4, 1536 24.9, 26.3, 2048 28.7 both; 64 batch elements of nine rows 20.7, 22.5).
+    return C == 2 * CROSS_C && tiles * CROSS_HEADS <= 256 ? CROSS_QUERIES : CROSS_STEPS;
+}
+
 }  // namespace fise

@@ -2,6 +2,7 @@
 // sub-layer and the context K/V projection: host-side sequencing of the gathered
 // GEMM, row LayerNorm and active-query attention kernels on the caller's stream.
 #include <cmath>
+#include "attention_choice.h"
 #include "igemm.h"
 
 namespace fise {
@@ -210,10 +211,11 @@ int run_transformer(const fise_transformer_args* a, void* workspace, const Igemm
     // cross-attention against the context K/V
     CrossArgs cross{hb, hb, (const bf16_t*)a->ln2_g, (const bf16_t*)a->ln2_b, (const bf16_t*)a->q2_w, (const bf16_t*)a->o2_w, (const bf16_t*)a->o2_b,
                     (const bf16_t*)a->K_ctx, (const bf16_t*)a->Vt_ctx, 1e-5f, a->n_ctx, a->n_ctx_stride, B, Ma, nullptr, 0, 0, 0, 0};
-    if (fused && cross_takes(C, a->heads, a->n_ctx, a->n_ctx_stride, B, Ma, H * W)) {
+    const int form = fused ? cross_form(C, a->heads, a->n_ctx, a->n_ctx_stride, B, Ma, H * W) : CROSS_STEPS;
+    if (form == CROSS_LAYER) {
         if (int e = launch_cross(cross, st)) return e;
     } else {
-        if (fused && query_attention_takes(C, a->heads, a->n_ctx, a->n_ctx_stride, B, Ma, H * W)) {
+        if (form == CROSS_QUERIES) {
             cross.out = ob;
             if (int e = launch_query_attention(cross, C, st)) return e;
         } else {
@@ -371,8 +373,9 @@ extern "C" int fise_masked_attention(const void* x, const void* ln_gamma, const 
 
     CrossArgs cross{x, y_cache, (const bf16_t*)ln_gamma, (const bf16_t*)ln_beta, (const bf16_t*)Wq, (const bf16_t*)Wo, (const bf16_t*)bo, (const bf16_t*)K_ctx,
                     (const bf16_t*)Vt_ctx, 1e-5f, n_ctx, n_ctx_stride, B, Ma, tile_idx, tile, W / tile, W, H * W};
-    if (!self && cross_takes(C, heads, n_ctx, n_ctx_stride, B, Ma, H * W)) return launch_cross(cross, st);
-    if (!self && query_attention_takes(C, heads, n_ctx, n_ctx_stride, B, Ma, H * W)) {
+    const int form = self ? CROSS_STEPS : cross_form(C, heads, n_ctx, n_ctx_stride, B, Ma, H * W);
+    if (form == CROSS_LAYER) return launch_cross(cross, st);
+    if (form == CROSS_QUERIES) {
         cross.out = obuf;
         if (int e = launch_query_attention(cross, C, st)) return e;
     } else {

@@ -17,6 +17,7 @@
 // 2214, 43 of 144 4152 -> 4112, dense pass 4950 -> 4878.
 #include <cmath>
 #include <type_traits>
+#include "attention_choice.h"
 #include "igemm.h"
 #include "profile.h"
 
@@ -352,7 +353,7 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
 //    rows; the waves' sums meet in the place of the weights, in wave order, and become queries;
 //  - the last two waves hold keys and values and finish sixteen rows each, numbered as above.
 // Bound by its start, the rows and 100 KB of weights.  Against a launch each for the queries and the attention, us: transformer block of 160 rows x 640 65.9
-// -> 63.1, of 512 82.7 -> 78.5, of 2048 134.0 -> 133.3; attention layer of 128 rows x 320 36.0 -> 32.0; step of 2 of 70 tiles 1787 -> 1755, 12 of 64 2217 -> 2198.
+// -> 63.1, of 512 82.7 -> 78.5; attention layer of 128 rows x 320 36.0 -> 32.0; step of 2 of 70 tiles 1787 -> 1755, 12 of 64 2217 -> 2198.
 template <int C> struct QueryTile {
     static constexpr int NW = C / 64, D = C / CROSS_HEADS, U = (D + 15) / 16, BM = 32, PITCH = 2 * C + (C % 128 ? 0 : 128), REGION = D * 128 > U * 2048 ? D * 128 : U * 2048,
                          QC = (D + 31) / 32, QPITCH = QC * 64 + 16, LDS = BM * PITCH + NW * REGION;      // QC: 32-wide steps over the head dim
@@ -555,20 +556,6 @@ __global__ __launch_bounds__(C, 1) void query_attention_kernel(const CrossDev g)
         if (m < a.Ma && dt * 16 + lq * 4 < D) *(FISE_AS1 u32x2_t*)(out + dt * 16) = u32x2_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
     }
 #endif
-}
-
-static bool takes(int heads, int n_ctx, int n_stride, int B, int Ma, int HW) {
-    return heads == CROSS_HEADS && n_ctx >= 1 && n_ctx <= CROSS_KEYS && n_stride < 1 << 20 && Ma >= 1 && Ma < 1 << 20 && HW < 1 << 21 && (long long)B * Ma < 1 << 24 && (long long)B * HW < 1 << 24;
-}
-// From forty workgroups on: with fewer, a workgroup per head and a product behind it spread the weights over more CUs.  Step of 64 x 64 with 24 workgroups
-// 1952 us here and 1939, with 48 2199 and 2206, with 96 2726 and 2761; attention layer of 640 rows (20) 44.8 and 43.0, of 1280 (40) 50.7 and 51.2, of
-// 4096 (128) 81.3 and 89.2.
-bool cross_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW) {
-    return C == CROSS_C && takes(heads, n_ctx, n_stride, B, Ma, HW) && (long long)B * ceil_div(Ma, 32) >= 40;
-}
-// 640 channels: two rounds of the CUs (2048 rows 134.0 -> 133.3 us, a transformer block); in five the rows are normalised too often (4608 rows 277.6 -> 281.7).
-bool query_attention_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW) {
-    return (C == 320 || (C == 640 && (long long)B * ceil_div(Ma, 32) * CROSS_HEADS <= 512)) && takes(heads, n_ctx, n_stride, B, Ma, HW);
 }
 
 template <bool MAP> static int launch(const CrossDev& g, hipStream_t st) {

@@ -170,16 +170,13 @@ struct NormGemmArgs {
     bf16_t* out[3]; int mode[3];
 };
 // Cross-attention sub-layer as one launch (cross.hip): out = x + Wo attention(Wq LN(x), K, V) + bias.  tile_idx: x and out are bf16 maps of HW pixels and the
-// rows pixels of active tiles; null: compact float rows, which out may be.
-constexpr int CROSS_C = 320, CROSS_HEADS = 8, CROSS_KEYS = 80;
+// rows pixels of active tiles; null: compact float rows, which out may be.  Where it and the next one run: cross_form in attention_choice.h.
 struct CrossArgs {
     const void* x; void* out; const bf16_t *gamma, *beta, *wq, *wo, *bias, *K, *Vt; float eps;
     int n_ctx, n_stride, B, Ma; const int* tile_idx; int tile, tiles_w, W, HW;
 };
-bool cross_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW);
 int launch_cross(const CrossArgs& a, hipStream_t st);
 // The same without the last product and sum, 320 or 640 channels: out = attention(Wq LN(x), K, V), compact bf16 rows.
-bool query_attention_takes(int C, int heads, int n_ctx, int n_stride, int B, int Ma, int HW);
 int launch_query_attention(const CrossArgs& a, int C, hipStream_t st);
 bool norm_gemm_takes(int src, int K, int B, int Ma, int H, int W);
 int launch_norm_gemm(const NormGemmArgs& a, hipStream_t st);

@@ -5,6 +5,7 @@ import subprocess
 import pytest
 
 import test_gpu_attention as attention
+import test_gpu_cross as cross
 from paper_2305_17423_amd import binding as fb, build
 
 
@@ -87,3 +88,20 @@ def test_long_key_ranges_run_in_turns(tmp_path):
         of = [f for t, pair in zip(attention.TURNS, zip(forms[::2], forms[1::2])) if t[0] == d for f in pair]
         assert (1, 1) in of and any(s > 1 and turns for s, turns in of), (d, of)
     assert not any(turns for _, turns in run([(d, 447, 600) for d in (40, 80, 160)] + [(d, 2000, 600) for d in (32, 64, 104, 128, 152)]))
+
+
+def test_forms_of_the_cross_attention(tmp_path):
+    """One launch, two or three for a layer: the cases of test_gpu_cross.py have each at every width that has it, and 640 channels stop at one round of the CUs."""
+    (tmp_path / "cross.cpp").write_text('#include <cstdio>\n#include "%s/attention_choice.h"\nint main() { int C, h, n, B, Ma, HW; while (std::scanf("%%d %%d %%d %%d %%d %%d", &C, &h, &n, &B, &Ma, &HW) == 6)'
+                                        ' std::printf("%%d\\n", fise::cross_form(C, h, n, (n + 7) / 8 * 8, B, Ma, HW)); }' % build.CSRC)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(tmp_path / "cross"), str(tmp_path / "cross.cpp")], check=True)
+
+    def forms(shapes):                                   # (channels, heads, keys, batch, rows of an element, pixels)
+        r = subprocess.run([str(tmp_path / "cross")], input="\n".join(" ".join(map(str, s)) for s in shapes), check=True, capture_output=True, text=True)
+        return [int(v) for v in r.stdout.split()]
+    cases = [c for p in cross.test_cross_attention_layer.pytestmark if p.name == "parametrize" for c in p.args[1]]
+    got = forms([(C, 8, n, B, max(1, (H // t) * (W // t) - 3) * t * t, H * W) for C, B, H, W, t, n in cases])
+    assert {(c[0], f) for c, f in zip(cases, got)} == {(320, 0), (320, 1), (320, 2), (640, 0), (640, 1)}
+    assert all(f == 0 for c, f in zip(cases, got) if c[-1] > 80)
+    assert forms([(640, 8, 77, 1, 1024, 4096), (640, 8, 77, 1, 1025, 4096), (640, 8, 77, 32, 9, 256), (640, 8, 77, 33, 9, 256), (640, 8, 77, 2, 1024, 4096)]) == [1, 0, 1, 0, 0]
+    assert forms([(320, 8, 77, 1, 1248, 4096), (320, 8, 77, 1, 1249, 4096), (320, 4, 77, 1, 1249, 4096), (1280, 8, 77, 1, 32, 64)]) == [1, 2, 0, 0]
