@@ -792,8 +792,10 @@ __global__ __launch_bounds__(64 * AF_WAVES, 2) void attention_few_kernel(const b
 
 // out[b,m,c] = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max_s m_s), splits visited in index order.
 // One thread per four channels (d is a multiple of 8: the four share a head, hence the weights).  Bound by its launch and its trips to memory: the parts
-// of up to MERGE_AHEAD splits are requested together with their weights, one trip instead of two, and the positions come from 32-bit divisions.
-constexpr int MERGE_AHEAD = 6;
+// of all splits, N at most, are requested together with their weights, one trip, and the positions come from 32-bit divisions.  us with the attention in
+// front: weights and parts one behind the other; six together and the others in rounds of eight weights and four parts; this: 2 x 32 queries, 4096 keys of
+// 8 x 40 (16 splits) 11.9, 12.7, 10.5; 9216 keys (29) 19.3, 19.6, 16.5; 2 x 96 x 2304 of 8 x 80 (12) 15.1, 15.7, 13.4; 2 x 192 x 9216 of 8 x 40 (16) 24.9, 25.9, 23.9.
+template <int N>
 __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                                               int B, int M, int C, int heads, FastDiv d_C4, FastDiv d_M, FastDiv d_d, int splits,
                                                               bf16_t* __restrict__ out) {
@@ -804,30 +806,25 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
     const size_t ml_stride = (size_t)B * heads * M * 2, o_stride = (size_t)B * M * C;
     const float* ml0 = part_ml + (((size_t)b * heads + h) * M + m) * 2;
     const float* o0 = part_o + (size_t)row * C + c;
-    float2 ml[MERGE_AHEAD]; float4 o[MERGE_AHEAD];
+    float2 ml[N]; float4 o[N];
 #pragma unroll
-    for (int s = 0; s < MERGE_AHEAD; ++s) {                    // past the last split: the last one again, not used
+    for (int s = 0; s < N; ++s) {                        // past the last split: the last one again, not used
         const int sp = min(s, splits - 1);
         ml[s] = *reinterpret_cast<const float2*>(ml0 + sp * ml_stride);
         o[s] = *reinterpret_cast<const float4*>(o0 + sp * o_stride);
     }
     float mx = -INFINITY;
 #pragma unroll
-    for (int s = 0; s < MERGE_AHEAD; ++s) mx = fmaxf(mx, ml[s].x);
-#pragma unroll 8
-    for (int s = MERGE_AHEAD; s < splits; ++s) mx = fmaxf(mx, ml0[s * ml_stride]);       // unrolled: the loads go out together, not one round trip each
+    for (int s = 0; s < N; ++s) mx = fmaxf(mx, ml[s].x);
     float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
     float den = 0.f;
-    auto add = [&](const float2& ml, const float4& o) {
-        const float w = __builtin_amdgcn_exp2f(ml.x - mx);  // an empty split has m = -inf: weight 0
-        num.x += w * o.x; num.y += w * o.y; num.z += w * o.z; num.w += w * o.w;
-        den += w * ml.y;
-    };
 #pragma unroll
-    for (int s = 0; s < MERGE_AHEAD; ++s)
-        if (s < splits) add(ml[s], o[s]);
-#pragma unroll 4
-    for (int s = MERGE_AHEAD; s < splits; ++s) add(*reinterpret_cast<const float2*>(ml0 + s * ml_stride), *reinterpret_cast<const float4*>(o0 + s * o_stride));
+    for (int s = 0; s < N; ++s)
+        if (s < splits) {
+            const float w = __builtin_amdgcn_exp2f(ml[s].x - mx);  // an empty split has m = -inf: weight 0
+            num.x += w * o[s].x; num.y += w * o[s].y; num.z += w * o[s].z; num.w += w * o[s].w;
+            den += w * ml[s].y;
+        }
     const float inv = 1.0f / den;
     *reinterpret_cast<uint2*>(out + (size_t)row * C + c) = make_uint2(f2bf2(num.x * inv, num.y * inv), f2bf2(num.z * inv, num.w * inv));
 }
@@ -908,8 +905,17 @@ int launch_attention(const void* q, const void* K, const void* Vt, int B, int M,
     if (splits > 1) {
         const long long n = (long long)B * M * (C / 4);
         ProfileScope prof(PROF_ATTENTION_MERGE, 0.0, (double)splits * B * M * C * 4.0 + 2.0 * B * M * C, st);
-        hipLaunchKernelGGL(attention_merge_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part_o, part_ml, B, M, C,
-                           heads, fast_div(C / 4), fast_div(M), fast_div(d), splits, (bf16_t*)out);      // fewer than 2^23 threads: a split launch has at most 640 workgroups' queries
+        // fewer than 2^23 threads: a split launch has at most 640 workgroups' queries
+#define FISE_MERGE(N) hipLaunchKernelGGL(attention_merge_kernel<N>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part_o, part_ml, B, M, C, \
+                                         heads, fast_div(C / 4), fast_div(M), fast_div(d), splits, (bf16_t*)out)
+        switch (at_merge(splits)) {
+            case 6: FISE_MERGE(6); break;
+            case 8: FISE_MERGE(8); break;
+            case 12: FISE_MERGE(12); break;
+            case 16: FISE_MERGE(16); break;
+            default: FISE_MERGE(AT_MAX_SPLITS);
+        }
+#undef FISE_MERGE
         FISE_CHECK_LAUNCH("attention merge");
     }
     return FISE_OK;

@@ -8,6 +8,7 @@
 namespace fise {
 
 constexpr int AT_BQ = 128, AF_BQ = 32;        // queries of a workgroup of attention_kernel, of attention_few_kernel
+constexpr int AT_MAX_SPLITS = 32;
 constexpr int at_ceil(int a, int b) { return (a + b - 1) / b; }
 
 // Key splits that the scratch of a launch is laid out for; how many it uses is attention_launch_splits' choice.  A split pays a second launch for the
@@ -21,8 +22,11 @@ inline int attention_splits(int B, int M, int n_keys, int C, int heads) {
     if (nblocks < 6 || (nblocks < 8 && (long long)B * M * C > (C / heads - 64) * 7000LL)) return 1;
     int s = at_ceil(640, wgs);
     s = std::min(s, nblocks / 2);
-    return std::max(1, std::min(s, 32));
+    return std::max(1, std::min(s, AT_MAX_SPLITS));
 }
+
+// Parts that the merge of `splits` requests at once (loads past the last split go to that one again: not many more than there are).
+constexpr int at_merge(int splits) { return splits <= 6 ? 6 : splits <= 8 ? 8 : splits <= 12 ? 12 : splits <= 16 ? 16 : AT_MAX_SPLITS; }
 
 // What a launch costs in us, by lines fitted to 500 of them (32 to 4096 queries, 128 to 9216 keys, heads of 40, 80 and 160, cold keys, every
 // split that the scratch allows); d = head dim.  A workgroup spends 0.52 + 0.009 d on each of its key blocks and 0.44 more for every further

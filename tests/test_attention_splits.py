@@ -64,6 +64,17 @@ def test_forms_of_the_gpu_cases(forms):
     assert split >= {40, 64, 80, 104, 128, 160}, sorted(split)
 
 
+def test_merges_of_the_gpu_cases(forms, tmp_path):
+    """Every number of parts that a merge requests at once has a case at that many splits; what is requested covers the splits."""
+    assert forms([c[:5] for c in attention.MERGES]) == [c[5:] for c in attention.MERGES]
+    (tmp_path / "merge.cpp").write_text('#include <cstdio>\n#include "%s/attention_choice.h"\nint main() { for (int s = 2; s <= fise::AT_MAX_SPLITS; ++s) std::printf("%%d ", fise::at_merge(s)); }' % build.CSRC)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(tmp_path / "merge"), str(tmp_path / "merge.cpp")], check=True)
+    parts = dict(enumerate(map(int, subprocess.run([str(tmp_path / "merge")], check=True, capture_output=True, text=True).stdout.split()), 2))
+    assert len(parts) == 31 and all(p >= s for s, p in parts.items())
+    tested = {c[6] for c in attention.ACTIVE + attention.MERGES}
+    assert set(parts.values()) <= tested, (set(parts.values()), tested)
+
+
 def test_forms_of_the_partial_key_blocks(forms):
     """The kernel for many queries has a partial block at every head dim, as the first one and behind a whole one; so has the one for few."""
     def of(M, heads, d, N):

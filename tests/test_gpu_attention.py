@@ -135,6 +135,15 @@ def test_attention_long_key_ranges(fb, d, N, M):
         assert rel_err(host(out), want) <= TOL["bf16"], scratch
 
 
+# The same columns as ACTIVE: splits on both sides of the numbers of parts that a merge requests at once, the most there are among them.
+MERGES = [(1, 30, 1100, 160, 1, 0, 9), (2, 70, 1500, 40, 1, 0, 12), (1, 36, 2226, 80, 2, 0, 12), (1, 20, 3000, 128, 2, 0, 16), (1, 20, 5000, 80, 2, 0, 27), (1, 20, 4096, 80, 2, 0, 32)]
+
+
+@pytest.mark.parametrize("B,M,N,C,heads", [c[:5] for c in MERGES])
+def test_attention_merges(fb, B, M, N, C, heads):
+    test_attention_active(fb, B, M, N, C, heads)
+
+
 def test_attention_closed_forms_on_device(fb):
     rng = np.random.default_rng(4100)
     B, M, N, C, heads = 1, 40, 300, 320, 8
