@@ -328,14 +328,16 @@ __global__ __launch_bounds__(256) void conv_f32_tile_kernel(const float* __restr
 // loads four consecutive channels of its row and of its column), a batch of nine (five) units
 // is requested at once, and the waves' sums meet in LDS.  One barrier.  What bounds it is the round trips of its batches; a batch is the one trip
 // that 64 channels under 3x3 need (80 rows x 64 x 576: 9.0 -> 8.3 us, 19.4 on the staged kernel).  Tiles of 16 x 16 bring half the bytes into a CU
-// in pieces of 64 instead of 32 and take its matrix units a quarter as long as 32 x 32: for launches that leave most CUs idle.
+// in pieces of 64 instead of 32 and take its matrix units a quarter as long as 32 x 32: for launches that leave most CUs idle.  Their waves have half the
+// units each, of four channels a product: with one accumulator a chain of additions is twice that of a wave of a 32 x 32 tile and its error up to 11 % larger (512 rows, K = 64, against 64
+// bits: 8.05e-8, 8.75e-8), with four a half of it (7.25e-8; 16 rows, K = 11520: 6.4e-7, 6.7e-7, 3.4e-7), for 0 - 0.1 us.
 template <int E>
 __global__ __launch_bounds__(512) void conv_f32_wave_kernel(const float* __restrict__ x, int Cin, int B, int Hin, int Win,
                                                             const float* __restrict__ w, const float* __restrict__ bias, int Cout,
                                                             int ksize, int stride, int ups, const float* __restrict__ temb,
                                                             const float* residual, const int* __restrict__ tile_idx, int Ma, int tile,
                                                             int tile_w, int Ho, int Wo, FastDiv d_units, float* y) {
-    constexpr int NW = 8, UNIT = 256 / E, BATCH = E == 32 ? 9 : 5;       // UNIT: channels of a unit
+    constexpr int NW = 8, UNIT = 256 / E, BATCH = E == 32 ? 9 : 5, SUMS = E == 32 ? 1 : 4;       // UNIT: channels of a unit; SUMS: accumulators of a wave
     __shared__ float part[NW][E][E + 1];
     __shared__ int rb[E], rpix[E];
     const int t = threadIdx.x, lane = t & 63, le = lane & (E - 1), hl = lane / E, rows = B * Ma;
@@ -349,10 +351,11 @@ __global__ __launch_bounds__(512) void conv_f32_wave_kernel(const float* __restr
     const int pad = ksize >> 1, units = Cin / UNIT, total = ksize * ksize * units;       // units of a tap, of all taps
     const int hh = ups ? 2 * Hin : Hin, ww = ups ? 2 * Win : Win;
     const float* const wrow = w + (size_t)min(n0 + le, Cout - 1) * ksize * ksize * Cin + hl * 4;     // columns past Cout are not stored
-    typename std::conditional<E == 32, f32x16v, f32x4_t>::type acc = {};
-    auto multiply = [&](float p, float q) {
-        if constexpr (E == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(p, q, acc, 0, 0, 0);
-        else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(p, q, acc, 0, 0, 0);
+    typename std::conditional<E == 32, f32x16v, f32x4_t>::type acc[SUMS] = {};
+    auto multiply = [&](int k, float p, float q) {
+        auto& a = acc[k % SUMS];
+        if constexpr (E == 32) a = __builtin_amdgcn_mfma_f32_32x32x2f32(p, q, a, 0, 0, 0);
+        else a = __builtin_amdgcn_mfma_f32_16x16x4f32(p, q, a, 0, 0, 0);
     };
     for (int u0 = wave; u0 < total; u0 += NW * BATCH) {
         float4 av[BATCH], bv[BATCH]; bool ok[BATCH];
@@ -369,14 +372,18 @@ __global__ __launch_bounds__(512) void conv_f32_wave_kernel(const float* __restr
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
             if (u0 + i * NW >= total) break;            // uniform in a wave
-            multiply(ok[i] ? av[i].x : 0.f, bv[i].x);
-            multiply(ok[i] ? av[i].y : 0.f, bv[i].y);
-            multiply(ok[i] ? av[i].z : 0.f, bv[i].z);
-            multiply(ok[i] ? av[i].w : 0.f, bv[i].w);
+            multiply(0, ok[i] ? av[i].x : 0.f, bv[i].x);
+            multiply(1, ok[i] ? av[i].y : 0.f, bv[i].y);
+            multiply(2, ok[i] ? av[i].z : 0.f, bv[i].z);
+            multiply(3, ok[i] ? av[i].w : 0.f, bv[i].w);
         }
     }
 #pragma unroll
-    for (int e = 0; e < E * E / 64; ++e) part[wave][(e >> 2) * 8 + hl * 4 + (e & 3)][le] = acc[e];
+    for (int e = 0; e < E * E / 64; ++e) {
+        float sum = acc[0][e];
+        if constexpr (SUMS == 4) sum = (sum + acc[1][e]) + (acc[2][e] + acc[3][e]);
+        part[wave][(e >> 2) * 8 + hl * 4 + (e & 3)][le] = sum;
+    }
     __syncthreads();
     if (t >= E * E / 4) return;
     const int r = t / (E / 4), c = t % (E / 4) * 4, col = n0 + c;

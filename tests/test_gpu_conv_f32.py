@@ -5,10 +5,11 @@ import zlib
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import fise_oracle as fo
 from paper_2305_17423_amd import workloads as wl
-from helpers import dev, host, idx_dev, active_mask, check_map
+from helpers import DEV, dev, host, idx_dev, active_mask, check_map
 
 pytestmark = pytest.mark.gpu
 CASES = [
@@ -59,3 +60,22 @@ FORMS = [
 @pytest.mark.parametrize("case", FORMS, ids=[c[0] for c in FORMS])
 def test_conv_f32_forms_of_the_wave_kernel(case):
     test_conv_f32_few_tiles(case)
+
+
+@pytest.mark.parametrize("C,co,tiles", [(64, 64, 16), (320, 64, 4), (1280, 64, 1), (320, 68, 3)])
+def test_conv_f32_of_few_tiles_is_as_close_to_64_bits_as_its_chains_of_additions(C, co, tiles):
+    """Tiles of 16 x 16: eight waves of four accumulators share K, so a chain is K / 32 additions, whose roundings of 2^-24 / sqrt(3) in the mean leave
+    sqrt(K / 64) of them, and the 32 sums about five.  A chain of K / 8 is over it."""
+    from paper_2305_17423_amd import binding as fb
+    B, H, W, t = 1, 32, 32, 4
+    g = torch.Generator(device=DEV).manual_seed(C)
+    x, w = torch.randn(B, H, W, C, generator=g, device=DEV), torch.randn(co, 3, 3, C, generator=g, device=DEV) * (9 * C) ** -0.5
+    idx = torch.randperm((H // t) * (W // t), generator=g, device=DEV)[:tiles].sort().values.to(torch.int32)
+    active = torch.zeros((H // t) * (W // t), dtype=torch.bool, device=DEV)
+    active[idx.long()] = True
+    active = active.reshape(H // t, W // t).repeat_interleave(t, 0).repeat_interleave(t, 1).cpu()
+    y = torch.zeros(B, H, W, co, device=DEV)
+    fb.fise_masked_conv(fb.conv_args(x, w, None, idx, tiles, t, y), None)
+    want = torch.nn.functional.conv2d(x.cpu().double().permute(0, 3, 1, 2), w.cpu().double().permute(0, 3, 1, 2), padding=1).permute(0, 2, 3, 1)[:, active]
+    err = float((y.cpu().double()[:, active] - want).norm() / want.norm())
+    assert err <= 2.0 ** -24 / 3 ** 0.5 * (9 * C / 64 + 5) ** 0.5, err
