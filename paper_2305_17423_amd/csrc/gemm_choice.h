@@ -97,18 +97,22 @@ inline int linear_tile(int rows, int N) {
 
 // ---- rows_group.hip: row tiles of 32 a workgroup takes, 0: the tiles of wave_gemm.hip.  One workgroup runs per CU; a round costs its start and epilogue (as
 // much as the operands of 290 rows of stages) and the rows of both operands that it loads.  The smaller tiles of wave_gemm.hip fill the chip where
-// there are few columns: their time goes with the number of columns, a round's does not (24960 columns, 154 rows: 24.0 and 15.5 us).
+// there are few columns: their time goes with the number of columns, a round's does not (24960 columns, 154 rows: 24.0 and 15.5 us).  With several rounds the two
+// are held against each other, us at 24960 columns of 768 channels: 6.5 and 3.7 + 1.5 rt a round; 12.7 and 3.83 for every 64 rows, where a batch element's rows are a
+// multiple of four (`fours`: transposed columns go out four rows at a time), else 15 and 4.75.  There and here: 240 rows 28.2, 28.9, 264 30.1, 28.6, 448
+// 38.6, 36.2, 512 43.1, 48.9, 576 46.5, 49.5; no fours 226 33.7, 29.0, 520 57.1, 49.1.
 constexpr int GROUP_UNITS = 7;               // units of 16 columns of a workgroup
-inline int group_tile(int rows, int cols) {
+inline int group_tile(int rows, int cols, bool fours) {
     constexpr int kTiles[] = {1, 2, 3, 5, 7};
     const long long groups = (cols / 16 + GROUP_UNITS - 1) / GROUP_UNITS;
-    int best = 0; double least = 1e30;
+    int best = 0; double least = 1e30; long long rounds = 0;
     for (const int rt : kTiles) {
-        const long long wgs = (rows + 32 * rt - 1) / (32 * rt) * groups;
-        const double t = (double)((wgs + 255) / 256) * (290 + 32 * rt + 16 * GROUP_UNITS);
-        if (t < least) { least = t; best = rt; }
+        const long long n = ((rows + 32 * rt - 1) / (32 * rt) * groups + 255) / 256;
+        const double t = (double)n * (290 + 32 * rt + 16 * GROUP_UNITS);
+        if (t < least) { least = t; best = rt; rounds = n; }
     }
-    return groups >= 160 ? best : 0;
+    const double here = 6.5 + rounds * (3.7 + 1.5 * best), there = (fours ? 12.7 + 3.83 * ((rows + 63) / 64) : 15 + 4.75 * ((rows + 63) / 64)) * (cols / 24960.0);
+    return groups >= 160 && (rounds == 1 || here <= there) ? best : 0;
 }
 
 // ---- norm_gemm.hip

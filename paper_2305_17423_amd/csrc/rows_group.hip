@@ -169,7 +169,7 @@ bool rows_group_takes(const IgemmArgs& a, const GemmProduct* p, int n) {
         if (p[i].mode != OUT_COMPACT && p[i].mode != OUT_TOKENS_T) return false;
         cols += p[i].N;
     }
-    return !a.tile_idx && a.Ho == 1 && a.ksize == 1 && a.C1 == 0 && a.K == a.C0 && a.K % 64 == 0 && group_tile(a.B * a.Ma, cols) > 0;
+    return !a.tile_idx && a.Ho == 1 && a.ksize == 1 && a.C1 == 0 && a.K == a.C0 && a.K % 64 == 0 && group_tile(a.B * a.Ma, cols, a.Ma % 4 == 0) > 0;
 }
 
 int launch_rows_group(const IgemmArgs& b, const GemmProduct* p, int n, hipStream_t st) {
@@ -181,7 +181,7 @@ int launch_rows_group(const IgemmArgs& b, const GemmProduct* p, int n, hipStream
         a.g.w[i] = p[i].w; a.g.out[i] = p[i].out; a.g.N[i] = p[i].N; a.g.mode[i] = p[i].mode;
         a.units += p[i].N / 16;
     }
-    const int rt = group_tile(a.rows, a.units * 16);
+    const int rt = group_tile(a.rows, a.units * 16, a.Ma % 4 == 0);
     a.gx = ceil_div(a.rows, 32 * rt); a.d_gx = fast_div(a.gx); a.d_Ma = fast_div(a.Ma);
     const int cols = a.units * 16;
     return rt == 1 ? launch_rows<1>(a, cols, st) : rt == 2 ? launch_rows<2>(a, cols, st) : rt == 3 ? launch_rows<3>(a, cols, st) : rt == 5 ? launch_rows<5>(a, cols, st) : launch_rows<7>(a, cols, st);

@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 import test_gpu_blocks as blocks
+import test_gpu_rows_group as group
 import test_gpu_wave_gemm as gemm
 from paper_2305_17423_amd import build
 
@@ -24,6 +25,11 @@ int main() {
             if (c.tile < 0) { std::puts("none"); continue; }
             const NormTile& t = kNormTiles[c.tile];
             std::printf("%%d%%s %%dx%%d%%s\n", t.K, t.geglu ? " gated" : "", 16 * t.rt, 16 * t.ct, waves_per_unit(v[2] / 320, t.ct, c.per) ? " in parts" : "");
+            continue;
+        }
+        if (what == 3) {                                 // 3 rows columns fours: a group of products
+            if (std::scanf("%%d", &v[2]) != 1) return 1;
+            std::printf("%%d\n", 32 * group_tile(v[0], v[1], v[2] != 0));
             continue;
         }
         for (int i = 2; i < 9; ++i) if (std::scanf("%%d", &v[i]) != 1) return 1;     // 1 rows N K K2 tile geglu patches one_map scratch
@@ -123,3 +129,15 @@ def test_products_behind_a_normalisation(ask):
         if case[3] in (320, 640, 1280):
             tested |= set(ask(norm_products(2, blocks.tr_inputs(case, blocks.tr_rng(case))[3].size * case[4] ** 2, case[3])))
     assert len(reached) >= 19 and tested == reached, (reached - tested, tested - reached)
+
+
+def test_groups_over_many_columns(ask):
+    """Every row tile has a case; where a second or further round would be the slower form, the smaller tiles have the launch."""
+    cases = [c for p in group.test_context_keys_and_values_of_many_layers.pytestmark if p.name == "parametrize" for c in p.args[1]]
+    columns = 11 * 2 * 1280                              # of its eleven layers
+    got = ask([(3, B * n, columns, n % 4 == 0) for B, n, _ in cases])
+    assert set(got) >= {"32", "64", "96", "160", "224"}, got
+    sd15 = 2 * (5 * 320 + 5 * 640 + 6 * 1280)
+    rows = {(154, 0): 160, (224, 1): 224, (226, 0): 160, (240, 1): 0, (256, 1): 0, (264, 1): 160, (448, 1): 224, (512, 1): 0, (520, 0): 224, (576, 1): 0, (616, 0): 224, (896, 1): 224}
+    assert ask([(3, r, sd15, f) for r, f in rows]) == [str(t) for t in rows.values()]
+    assert ask([(3, 154, 17808, 0), (3, 154, 17824, 0)]) == ["0", "160"]
