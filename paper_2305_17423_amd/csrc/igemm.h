@@ -159,8 +159,10 @@ bool linear_wide_takes(const IgemmArgs& a);
 int launch_linear_wide(const IgemmArgs& a, hipStream_t st);
 // Normalised rows times weights (norm_gemm.hip).  Rows of K channels: compact float rows under a LayerNorm, or the active pixels of a bf16 map
 // [B, Ho*Wo, K] under a LayerNorm, under a GroupNorm with given statistics, or as they are.  N columns in sections of sect_n, section s with
-// weights w[s] [sect_n, K] to out[s] (only the last one transposed; geglu: one section, w[0] [2N, K]); a bias belongs to one section.
+// weights w[s] [sect_n, K] to out[s] (only the last one transposed; geglu: one section, w[0] [2N, K], compact float rows).  A bias belongs to one section, and to a gate or to rows without a
+// LayerNorm: the launcher refuses it elsewhere.
 enum { NG_ROWS_LN = 0, NG_MAP_LN = 1, NG_MAP_GN = 2, NG_MAP_RAW = 3 };
+constexpr bool norm_gemm_has_bias(bool geglu, int src) { return geglu || src == NG_MAP_GN || src == NG_MAP_RAW; }
 struct NormGemmArgs {
     const void* x; int src, K;
     const bf16_t* gamma; const bf16_t* beta; float eps;

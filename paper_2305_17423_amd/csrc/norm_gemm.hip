@@ -72,7 +72,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
     int2* const rowpos = reinterpret_cast<int2*>(lds + BM * PITCH);
     constexpr int WST = CT * 2048;                        // bytes of a stage of weights in LDS
     unsigned char* const wring = lds + BM * PITCH + BM * 8;
-    constexpr bool BIAS = GEGLU || SRC == NG_MAP_GN || SRC == NG_MAP_RAW;
+    constexpr bool BIAS = norm_gemm_has_bias(GEGLU, SRC);
     unsigned char* const lbias = wring + NW * ND * WST;
     float2* const table = reinterpret_cast<float2*>(lbias + NG_BIAS);
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
@@ -449,6 +449,7 @@ int launch_norm_gemm(const NormGemmArgs& a, hipStream_t st) {
     for (int s = 0; s < nsect; ++s) { map |= a.mode[s] == OUT_MAP; tokens |= a.mode[s] == OUT_TOKENS_T; if (a.mode[s] == OUT_TOKENS_T && s + 1 < nsect) return fail(FISE_ERR_SHAPE, "norm gemm: a transposed section is the last one"); }
     if (!norm_gemm_takes(a.src, a.K, a.B, a.Ma, a.Ho, a.Wo) || a.sect_n % 32 || nsect * a.sect_n != a.N || nsect > 3 || (a.geglu && (nsect != 1 || a.src != NG_ROWS_LN)) || (a.bias && nsect != 1))
         return fail(FISE_ERR_SHAPE, "norm gemm: %d channels, %d columns in sections of %d", a.K, a.N, a.sect_n);
+    if (a.bias && !norm_gemm_has_bias(a.geglu != 0, a.src)) return fail(FISE_ERR_SHAPE, "norm gemm: a bias behind a LayerNorm without a gate");
     g.pixels = a.tile_idx && (map || tokens);
     g.trans4 = a.Ma % 4 == 0 && (a.tile_idx ? a.tile % 4 == 0 && a.Wo % 4 == 0 : a.Ho * a.Wo % 4 == 0);
     g.d_Ma = fast_div(a.Ma); g.d_tt = fast_div(a.tile * a.tile); g.d_tile = fast_div(a.tile); g.d_tiles_w = fast_div(a.tiles_w);
