@@ -74,7 +74,7 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
     unsigned char* const wring = lds + BM * PITCH + BM * 8;
     constexpr bool BIAS = norm_gemm_has_bias(GEGLU, SRC);
     unsigned char* const lbias = wring + NW * ND * WST;
-    float2* const table = reinterpret_cast<float2*>(lbias + NG_BIAS);
+    float2* const table = reinterpret_cast<float2*>(lbias + (BIAS ? NG_BIAS : 0));
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // consecutive workgroups go round-robin to the 8 XCDs: each gets a contiguous run of (columns, rows), rows fastest
@@ -389,15 +389,16 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-template <int KM, int RT, int CT, int ND> constexpr int ng_lds(bool table) {
-    return 16 * RT * (ng_pitch<KM>() + 8) + NG_WAVES * ND * CT * 2048 + NG_BIAS + (table ? 2 * 320 * KM * 8 : 0);
+template <int KM, int RT, int CT, int ND> constexpr int ng_lds(bool bias, bool table) {
+    return 16 * RT * (ng_pitch<KM>() + 8) + NG_WAVES * ND * CT * 2048 + (bias ? NG_BIAS : 0) + (table ? 2 * 320 * KM * 8 : 0);
 }
 
 template <int KM, int RT, int CT, int ND, bool GEGLU, int SRC>
 static int launch_cfg(NormGemmDev g, int per, hipStream_t st) {
     const NormGemmArgs& a = g.a;
-    constexpr int lds = ng_lds<KM, RT, CT, ND>(SRC == NG_MAP_GN);
-    if constexpr (lds > NG_LDS_MAX) {                    // never chosen: no room for the table
+    constexpr int lds = ng_lds<KM, RT, CT, ND>(norm_gemm_has_bias(GEGLU, SRC), SRC == NG_MAP_GN);
+    static_assert(SRC == NG_MAP_GN || lds <= NG_LDS_MAX, "LDS of a CU");
+    if constexpr (lds > NG_LDS_MAX) {                    // a table that finds no room: choose_norm_tile passes the tile by
         return fail(FISE_ERR_SHAPE, "norm gemm: LDS of a CU");
     } else {
         static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&norm_gemm_kernel<KM, RT, CT, ND, GEGLU, SRC>),
