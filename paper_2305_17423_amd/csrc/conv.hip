@@ -3,6 +3,7 @@
 // (e.g. the 4-channel latent) use the scalar kernel below, one output element per
 // thread, same gather rules.
 #include <type_traits>
+#include "conv_choice.h"
 #include "igemm.h"
 #include "profile.h"
 
@@ -65,9 +66,8 @@ __global__ __launch_bounds__(256) void conv_scalar_kernel(const T* __restrict__ 
 // SiLU(GroupNorm(x)) under a 3x3 kernel with four output channels (the UNet's output convolution).  Four columns leave a matrix tile of the general
 // product 15/16 empty and its K range is then split and summed by a second launch; here a workgroup takes 4 x 4 pixels: their 6 x 6 patch is
 // normalised into LDS once, every wave multiplies a quarter of the 32-channel pieces of the nine taps, whose weights it requested up front.
-// Bound by two trips to memory and its barriers.  1536 pixels of 320 channels, with the sum, 17.5 -> 7.9 us, 8192 30.7 -> 8.7.  Up to 640
-// channels, whose patch is 47 of the 64 KB of LDS that a launch has without asking (896 do not fit).
-constexpr int CO_PATCH = 36, CO_MAX_C = 640;
+// Bound by two trips to memory and its barriers.  1536 pixels of 320 channels, with the sum, 17.5 -> 7.9 us, 8192 30.7 -> 8.7.
+constexpr int CO_PATCH = 36;
 __global__ __launch_bounds__(256) void conv_out_kernel(const bf16_t* __restrict__ x, int C, int H, int W, const bf16_t* __restrict__ w, const bf16_t* __restrict__ bias,
                                                        const float* __restrict__ mean, const float* __restrict__ rstd, const bf16_t* __restrict__ gamma,
                                                        const bf16_t* __restrict__ beta, int G, int silu, const int* __restrict__ tile_idx, int tile, FastDiv d_subs,
@@ -468,19 +468,13 @@ int conv_dispatch(const fise_conv_args* a, void* workspace, size_t workspace_byt
         if (nview && a->dtype != FISE_BF16) return fail(FISE_ERR_DTYPE, "fise_masked_conv: normalised copies need bf16 maps");
         if (a->dtype == FISE_F32 && a->C1 == 0 && !a->gn_mean && a->C0 % 16 == 0 && a->Cout % 4 == 0) {
             const int Ma = a->n_active * a->tile * tile_cols(a), rows = a->B * Ma;
-            const dim3 grid(ceil_div(rows, 32), ceil_div(a->Cout, 64)), wgrid(ceil_div(rows, 32), ceil_div(a->Cout, 32)), sgrid(ceil_div(rows, 16), ceil_div(a->Cout, 16));
-            constexpr long long F32_SMALL = 512;     // tiles of 16 x 16 up to two for each CU (comment below)
-            // Up to one 32 x 32 tile per CU it is the faster one at every size measured (8 - 256 tiles; us here / staged at 256): 3x3 of 16
-            // channels 5.3 / 8.8, 64 9.2 / 20.1, 320 27 / 84, 1280 101 / 324; 1x1 of 16 4.3 / 4.4, 64 5.2 / 5.7, 1280 15 / 39.  A second tile per CU
-            // costs a second round: at 320 tiles 1x1 of 64 channels 7.3 / 5.8, of 128 7.7 / 7.5, though 3x3 of 64 still 15 / 20.
-            // Of its two tiles 16 x 16 while there are at most two for each CU (detection and convolution alone, us, 32 x 32 and 16 x 16): 40 tiles of 64 channels
-            // 29.1, 26.4; 256 of 128 channels 33.5, 28.4; 512 of 64 29.2, 27.9; 960 of 64 29.4, 32.1.
-            // Pixel numbers of the output have 32 bits.
-            if ((long long)wgrid.x * wgrid.y <= 256 && (long long)a->B * Ho * Wo < (1ll << 31)) {
-#define FISE_F32_WAVE(E, GRID) hipLaunchKernelGGL(conv_f32_wave_kernel<E>, GRID, dim3(512), 0, st, (const float*)a->x0, a->C0, a->B, a->H, a->W, (const float*)a->w, \
+            const int edge = conv_f32_edge(rows, a->Cout, (long long)a->B * Ho * Wo);
+            const dim3 grid(ceil_div(rows, edge ? edge : 32), ceil_div(a->Cout, edge ? edge : 64));
+            if (edge) {
+#define FISE_F32_WAVE(E) hipLaunchKernelGGL(conv_f32_wave_kernel<E>, grid, dim3(512), 0, st, (const float*)a->x0, a->C0, a->B, a->H, a->W, (const float*)a->w, \
                                (const float*)a->bias, a->Cout, a->ksize, a->stride, a->upsample ? 1 : 0, a->temb, (const float*)a->residual,                  \
                                a->tile_idx, Ma, a->tile, tile_cols(a), Ho, Wo, fast_div(a->C0 / (256 / E)), (float*)a->y_cache)
-                if ((long long)sgrid.x * sgrid.y <= F32_SMALL) FISE_F32_WAVE(16, sgrid); else FISE_F32_WAVE(32, wgrid);
+                if (edge == 16) FISE_F32_WAVE(16); else FISE_F32_WAVE(32);
 #undef FISE_F32_WAVE
                 FISE_CHECK_LAUNCH("fise_masked_conv(fp32, few tiles)");
                 return FISE_OK;
@@ -498,8 +492,7 @@ int conv_dispatch(const fise_conv_args* a, void* workspace, size_t workspace_byt
         FISE_CHECK_LAUNCH("fise_masked_conv(scalar)");
         return FISE_OK;
     }
-    if (a->gn_mean && a->C1 == 0 && a->Cout == 4 && a->ksize == 3 && a->stride == 1 && !a->upsample && !a->temb && !a->residual && !nview && a->C0 <= CO_MAX_C &&
-        a->tile % 4 == 0 && tile_cols(a) == a->tile && (long long)a->n_active * (a->tile / 4) * (a->tile / 4) < 1 << 24) {
+    if (conv_out_takes({a->C0, a->C1, a->Cout, a->ksize, a->stride, a->tile, tile_cols(a), a->n_active, a->upsample != 0, a->gn_mean != nullptr, a->temb || a->residual || nview})) {
         const int edge = a->tile / 4, lds = CO_PATCH * (2 * a->C0 + 16);
         ProfileScope prof(PROF_IGEMM_STAGED, 2.0 * a->B * a->n_active * a->tile * a->tile * 36.0 * a->C0, 2.0 * (36.0 * a->C0 + (double)a->B * a->n_active * a->tile * a->tile * (a->C0 + 4.0)), st);
         hipLaunchKernelGGL(conv_out_kernel, dim3((unsigned)(a->n_active * edge * edge), a->B), dim3(256), lds, st, (const bf16_t*)a->x0, a->C0, a->H, a->W, (const bf16_t*)a->w,

@@ -3,6 +3,7 @@
 // token buffers.
 #include <algorithm>
 #include <mutex>
+#include "conv_choice.h"
 #include "igemm.h"
 
 namespace fise {
@@ -278,7 +279,6 @@ __global__ __launch_bounds__(256) void gn_finish_act_kernel(const ActMap a, cons
 // all pixels, keeps its values in registers between the sums and the activation, and nothing waits for another workgroup.  A lane holds one piece of eight
 // channels of every PS-th pixel; it adds pairs of values in float, the pairs in double.  Bound by its start, one trip to memory and two barriers.
 // Two batch elements of 16 x 16 x 1280, sums and activation as two launches and this, us: 4.7 + 5.7 -> 4.9; 2560 channels 8.0.  Dense pass of 64 x 64 4867 -> 4757.
-constexpr int GM_THREADS = 512, GM_MAX_J = 8, GM_MAX_GROUPS = GM_THREADS / 64;      // a wave finishes a group
 struct GnMapArgs {
     ActMap a; int HW, P, gps, slabs; double count; float eps; float* mean; float* rstd; int* zero; int n_zero;      // P: pieces of a slab, gps: its groups
     FastDiv d_P;
@@ -599,22 +599,6 @@ static int gn_stats_check(const char* fn, const void* x, const void* x1, int dty
     if (C1 < 0 || (C1 > 0 && !x1)) return fail(FISE_ERR_NULL, "%s: second source missing", fn);
     if (B < 1 || H < 1 || W < 1 || C0 < 1 || G < 1 || (C0 + C1) % G) return fail(FISE_ERR_SHAPE, "%s: B%d H%d W%d C%d G%d", fn, B, H, W, C0 + C1, G);
     return FISE_OK;
-}
-
-// Slab of gn_map_kernel: the fewest whole groups whose channels are a multiple of 8.
-struct GnSlab { int groups, pieces; };
-static GnSlab gn_slab(int C, int G) {
-    const int cpg = C / G, unit = cpg % 8 == 0 ? 1 : cpg % 4 == 0 ? 2 : cpg % 2 == 0 ? 4 : 8;
-    if (cpg < 8 || G % unit) return {0, 0};
-    return {unit, unit * cpg / 8};
-}
-// Pieces a lane of gn_map_kernel holds, 0: two launches.  Up to eight: 32 workgroups of eight 9.5 us (two launches 10.4), of twelve 10.6 (10.1) with 512 lanes
-// as with 1024, 64 of twelve 12.6 (12).  Fewer than 32
-// workgroups were not measured.  Channels: what the statistics' launch takes.
-static int gn_map_values(const GnSlab& s, int B, int HW, int C, int G) {
-    if (!s.groups || C * sizeof(double2) > 64 * 1024 || s.pieces > GM_THREADS || (long long)B * (G / s.groups) < 32) return 0;
-    const int n = ceil_div(HW, GM_THREADS / s.pieces);
-    return n <= GM_MAX_J ? n : 0;
 }
 
 int fise::launch_gn_stats_act(const void* x0, const void* x1, int C0, int C1, int B, int H, int W, float eps, float* mean, float* rstd, const void* gamma,

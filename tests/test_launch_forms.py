@@ -6,12 +6,16 @@ import subprocess
 import pytest
 
 import test_gpu_blocks as blocks
+import test_gpu_conv as bf16
+import test_gpu_conv_f32 as f32
+import test_gpu_fresh_stats as fresh
 import test_gpu_rows_group as group
 import test_gpu_wave_gemm as gemm
 from paper_2305_17423_amd import build
 
 PROGRAM = r"""
 #include <cstdio>
+#include "%s/conv_choice.h"
 #include "%s/gemm_choice.h"
 using namespace fise;
 int main() {
@@ -32,6 +36,18 @@ int main() {
             std::printf("%%d\n", 32 * group_tile(v[0], v[1], v[2] != 0));
             continue;
         }
+        if (what == 4) { std::printf("%%d\n", conv_f32_edge(v[0], v[1], 1 << 20)); continue; }       // 4 rows N: an fp32 convolution
+        if (what == 5) {                                 // 5 C0 C1 N k stride upsample groupnorm adds tile tile_w n: is it four columns behind a GroupNorm
+            int w[9];
+            for (int& x : w) if (std::scanf("%%d", &x) != 1) return 1;
+            std::printf("%%d\n", conv_out_takes({v[0], v[1], w[0], w[1], w[2], w[6], w[7], w[8], w[3] != 0, w[4] != 0, w[5] != 0}));
+            continue;
+        }
+        if (what == 6) {                                 // 6 B pixels C G: pieces of eight channels that a lane holds for fresh statistics
+            for (int i = 2; i < 4; ++i) if (std::scanf("%%d", &v[i]) != 1) return 1;
+            std::printf("%%d\n", gn_map_values(gn_slab(v[2], v[3]), v[0], v[1], v[2], v[3]));
+            continue;
+        }
         for (int i = 2; i < 9; ++i) if (std::scanf("%%d", &v[i]) != 1) return 1;     // 1 rows N K K2 tile geglu patches one_map scratch
         const GemmShape g{v[0], v[1], v[2], v[3], v[4], v[5] != 0, v[6] != 0, v[7] != 0};
         const TileChoice c = choose_tile(g, v[8] ? IGEMM_PARTIAL_BYTES : 0);
@@ -46,7 +62,7 @@ int main() {
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
     d = tmp_path_factory.mktemp("forms")
-    (d / "forms.cpp").write_text(PROGRAM % build.CSRC)
+    (d / "forms.cpp").write_text(PROGRAM % (build.CSRC, build.CSRC))
     subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(d / "forms"), str(d / "forms.cpp")], check=True)
 
     def run(questions):
@@ -141,3 +157,31 @@ def test_groups_over_many_columns(ask):
     rows = {(154, 0): 160, (224, 1): 224, (226, 0): 160, (240, 1): 0, (256, 1): 0, (264, 1): 160, (448, 1): 224, (512, 1): 0, (520, 0): 224, (576, 1): 0, (616, 0): 224, (896, 1): 224}
     assert ask([(3, r, sd15, f) for r, f in rows]) == [str(t) for t in rows.values()]
     assert ask([(3, 154, 17808, 0), (3, 154, 17824, 0)]) == ["0", "160"]
+
+
+def test_fp32_convolution_cases(ask):
+    """Tiles of 16 x 16 and of 32 x 32, both sides of the lines between them and behind them."""
+    got = dict(zip((c[0] for c in f32.CASES + f32.FORMS), ask([(4, c[1] * c[10] * c[9] ** 2, c[5]) for c in f32.CASES + f32.FORMS])))
+    assert set(got.values()) == {"16", "32", "0"} and all(got[c[0]] == c[0].split("-")[0] for c in f32.FORMS), got
+    assert ask([(4, 512, 256), (4, 513, 256), (4, 4096, 64), (4, 4097, 64)]) == ["16", "32", "32", "0"]
+
+
+def test_four_column_cases(ask):
+    def question(case):
+        name, B, H, W, C0, C1, Co, k, stride, ups, t, use_gn, silu, use_temb, use_res, frac = case
+        th, tw = t if isinstance(t, tuple) else (t, t)
+        return 5, C0, C1, Co, k, stride, ups, use_gn, use_temb or use_res, th, tw, 4
+    assert ask([question(c) for c in bf16.NARROW]) == ["1"] * (len(bf16.NARROW) - 1) + ["0"]      # the last one is a width past the last
+    taken = [c[0] for c, f in zip(bf16.CASES, ask([question(c) for c in bf16.CASES])) if f == "1"]
+    assert taken == ["narrow-out"]                       # and nothing of other widths, strides, sources or additions
+    assert ask([(5, 320, 0, 4, 3, 1, 0, 1, 0, 8, 8, 1 << 22), (5, 320, 0, 4, 3, 1, 0, 1, 0, 8, 4, 4), (5, 320, 0, 4, 3, 1, 0, 1, 0, 2, 2, 4)]) == ["0", "0", "0"]
+
+
+def test_fresh_statistics_cases(ask):
+    """A lane's four registers' worth of pieces, its eight, and maps too large for one launch."""
+    cases = [c for p in fresh.test_resnet_block_with_fresh_statistics_of_an_active_map.pytestmark if p.name == "parametrize" for c in p.args[1]]
+    for B, H, W, C, G, tile, tiles in cases:
+        assert tiles * tile * tile == H * W
+    got = [int(v) for v in ask([(6, B, H * W, C, G) for B, H, W, C, G, *_ in cases])]
+    assert got[-2:] == [0, 0] and min(got[:-2]) == 1 and {1, 2, 3, 4} & set(got) and 8 in got, got
+    assert ask([(6, 2, 64, 320, 40), (6, 1, 64, 256, 32), (6, 1, 64, 256, 16), (6, 2, 64, 96, 24), (6, 2, 64, 4104, 27)]) == ["1", "1", "0", "0", "0"]
