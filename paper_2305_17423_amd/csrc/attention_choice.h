@@ -28,8 +28,8 @@ inline int attention_splits(int B, int M, int n_keys, int C, int heads) {
 // Parts that the merge of `splits` requests at once (loads past the last split go to that one again: not many more than there are).
 constexpr int at_merge(int splits) { return splits <= 6 ? 6 : splits <= 8 ? 8 : splits <= 12 ? 12 : splits <= 16 ? 16 : AT_MAX_SPLITS; }
 
-// What a launch costs in us, by lines fitted to 500 of them (32 to 4096 queries, 128 to 9216 keys, heads of 40, 80 and 160, cold keys, every
-// split that the scratch allows); d = head dim.  A workgroup spends 0.52 + 0.009 d on each of its key blocks and 0.44 more for every further
+// What a launch costs in us, by lines fitted to 500 of attention_kernel (32 to 4096 queries, 128 to 9216 keys, heads of 40, 80 and 160, cold keys, every
+// split that the scratch allows), before its turns and the present merge; d = head dim.  A workgroup spends 0.52 + 0.009 d on each of its key blocks and 0.44 more for every further
 // workgroup on its CU, which holds three of heads up to 64 and two of wider ones; more workgroups than that go round again.  A split costs
 // 3.5 for the merge and 2.6 per million parked elements (rows x channels x splits).
 inline double attention_us(int B, int M, int n_keys, int C, int heads, int splits) {
@@ -42,10 +42,10 @@ inline double attention_us(int B, int M, int n_keys, int C, int heads, int split
            (splits > 1 ? 3.5 + 2.6e-6 * splits * B * M * C : 0.0);
 }
 
-// Splits of a launch, of the `most` that its scratch holds (2.5 workgroups per CU): as many as pay for what they park.  1.1 % from the best
-// one on average over 90 shapes, 12 % at worst; all of `most` 11 % and 43 %.  2 x 1024 queries and keys of 8 x 80 channels: 5 splits 30.0
-// us, none 22.2; of 8 x 40 5 splits 22.1, two 17.5; 2 x 384 x 1024 keys of 8 x 80 8 splits 21.1, four 17.0; 2 x 4096 x 4096 of 8 x 40 two
-// splits 101, none 95; 2 x 2752 x 9216 stays at two.
+// Splits of a launch, of the `most` that its scratch holds (2.5 workgroups per CU): as many as pay for what they park.  With the kernels as they are the form
+// chosen here and in attention_few is 1.3 % from the best one on average over 98 shapes (one to four batch elements, 32 to 4096 queries, 512 to 9216 keys, heads of 40, 80 and 160), 19 % at worst:
+// 2 x 1376 queries, 2304 keys of 8 x 80 46.6 us in three, 39.4 in one; 4096 keys 67.5 in three, 57.0 in four; 2304 keys of 8 x 160 76.5 in three, 65.3 in two.  All
+// of `most` was 11 % and 43 %.
 inline int attention_launch_splits(int B, int M, int n_keys, int C, int heads, int most) {
     int best = 1;
     double us = attention_us(B, M, n_keys, C, heads, 1);
@@ -67,11 +67,12 @@ inline bool attention_few(int B, int M, int n_keys, int n_stride, int C, int hea
     return few < attention_us(B, M, n_keys, C, heads, splits);
 }
 
-// Whether a launch in `splits` parts runs on attention_turns_kernel: from eight key blocks a part on, below which its longer set-up (1.1 us) costs more than its
-// turns save (a quarter of their cycles): 2 x 4096 queries of 8 x 40, 256 keys 10.1 and 10.8 us, 512 keys 16.0 and 15.5.  Heads of 104 and 128 would lose (2 x 700 x 1500 of 4 x
-// 104 31 and 33 us).  Its offsets reach over sixteen value rows in 32 bits.
+// Whether a launch in `splits` parts runs on attention_turns_kernel: from twelve key blocks a part on (heads of 160: eight), below which its longer set-up (1.1 us) costs more
+// than its turns save.  Its time over attention_kernel's at 8, 10, 12, 16 and 20 blocks a part: heads of 40, one workgroup on a CU 1.03, 1.02, 1.00, 0.98, 0.97,
+// more 1.02, 1.00, 1.00, 0.98, 0.97; of 80 1.05, 1.03, 1.00, 0.98, 0.965, more 1.00, 0.985, 0.98, 0.96, 0.95; of 160 0.97 at eight and 0.95 at ten.  Heads of
+// 104 and 128 would lose (2 x 700 x 1500 of 4 x 104 31 and 33 us).  Its offsets reach over sixteen value rows in 32 bits.
 inline bool attention_turns(int n_keys, int n_stride, int d, int splits) {
-    return splits > 0 && (d == 40 || d == 80 || d == 160) && at_ceil(at_ceil(n_keys, AT_BKV), splits) >= 8 && n_stride < 1 << 27;
+    return splits > 0 && (d == 40 || d == 80 || d == 160) && at_ceil(at_ceil(n_keys, AT_BKV), splits) >= (d == 160 ? 8 : 12) && n_stride < 1 << 27;
 }
 
 // Form of a launch: 0 attention_few_kernel (one launch whatever the key range), else the key splits of attention_kernel.

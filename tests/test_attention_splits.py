@@ -98,6 +98,9 @@ def test_long_key_ranges_run_in_turns(tmp_path):
     for d in (40, 80, 160):
         of = [f for t, pair in zip(attention.TURNS, zip(forms[::2], forms[1::2])) if t[0] == d for f in pair]
         assert (1, 1) in of and any(s > 1 and turns for s, turns in of), (d, of)
+        for ends in (0, 1, 33, 63):                      # keys behind the last whole turn of 64
+            assert any(N % 64 == ends and f == (1, 1) for (_, N, _), f in zip((t for t in attention.TURNS if t[0] == d for _ in (0, 1)), of)) or (d == 160 and ends == 63), (d, ends, of)
+    assert run([(40, 705, 2000), (40, 704, 2000), (80, 705, 2000), (80, 704, 2000), (160, 449, 2000), (160, 448, 2000)])[::2] == [(1, 1), (1, 0)] * 3
     assert not any(turns for _, turns in run([(d, 447, 600) for d in (40, 80, 160)] + [(d, 2000, 600) for d in (32, 64, 104, 128, 152)]))
 
 

@@ -117,7 +117,9 @@ def test_attention_partial_key_blocks(fb, d, N, M, heads):
 # Long key ranges of heads of 40, 80 and 160 (attention_turns_kernel; test_attention_splits.py says so), in one part and in several: whole turns, a last turn of
 # one key, of one more than a 32-key block and of all but one; queries on both sides of a tile of 128.
 TURNS = [(40, 512, 513), (40, 513, 1500), (40, 545, 1500), (40, 2199, 600), (40, 4160, 257), (80, 512, 640), (80, 513, 513), (80, 545, 600), (80, 1087, 700),
-         (160, 512, 513), (160, 513, 640), (160, 545, 600), (160, 1087, 700), (160, 2199, 513)]
+         (160, 512, 513), (160, 513, 640), (160, 545, 600), (160, 1087, 700), (160, 2199, 513),
+         # heads of 40 and 80 from twelve key blocks a part on: the same ends
+         (40, 768, 1500), (40, 769, 1500), (40, 801, 1500), (40, 895, 1500), (40, 4161, 700), (80, 768, 1500), (80, 769, 1500), (80, 801, 1500), (80, 895, 1500), (80, 4127, 700)]
 
 
 @pytest.mark.parametrize("d,N,M", TURNS)
