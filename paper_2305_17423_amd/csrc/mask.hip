@@ -194,7 +194,7 @@ __global__ void or_pool_kernel(const uint8_t* __restrict__ m, int H, int W, uint
 // Otsu in two launches.  Values are min-max normalised in double; bin k of 257 holds values with floor(256 v) == k, so
 // class A of threshold k/256 is exactly bins [0, k).  Every bin's sum is taken in index order: the order is part of the
 // result, so the fullest bin (2082 of 4096 values in an edit's mask) is what bounds this: a chain of dependent additions, 16 cycles each, unless
-// they are rounded ahead (ordered_sum.h: 15 rounds of ~900 cycles and 11 values on their own instead of 33000 cycles).
+// they are rounded ahead (ordered_sum.h: a round of ~900 cycles for 256 of them instead of 4100).
 //  - otsu_bins_kernel: four bins per workgroup of sixteen waves.  The waves normalise 4096 values in registers, pack those of each bin behind one
 //    another in LDS (ballots, the waves' counts scanned in between by one lane each), and one wave per bin adds them up from there.
 //  - otsu_apply_kernel: every workgroup finds the threshold for itself (the sums below a bin one chain of 257 additions, the counts
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(64 * OTSU_WAVES) void otsu_bins_kernel(const float*
         __syncthreads();
         if (wave < OTSU_WG_BINS) {
 #if defined(__HIP_DEVICE_COMPILE__)
-            sum = ordered_sum<Wavefront>(sum, static_cast<const double*>(mine[wave]), total);
+            sum = ordered_sum<Wavefront>(sum, static_cast<const double*>(mine[wave]), total, k < OTSU_BINS - 1 ? (k + 1) / 256.0 : 1.0);
 #endif
             count += total;
         }

@@ -59,7 +59,7 @@ int main(int, char** argv) {
         std::mt19937_64 g(seed);
         auto unit = [&] { return (g() >> 11) * 0x1p-53; };
         const int bin = shape == "edge" || one_by_one_counts ? 0 : shape == "nan" ? (int)(g() %% 4) * 64 : (int)(g() %% 257);
-        const double low = bin / 256.0;
+        const double low = bin / 256.0, top = bin < 256 ? (bin + 1) / 256.0 : 1.0;
         std::vector<double> v;
         if (shape == "edge") {                           // up to a few places below 2, then ties and whole places across it
             v.assign(1023, 0x1p-9);
@@ -92,7 +92,7 @@ int main(int, char** argv) {
             for (int j = 0; j < n; ++j) want += v[i + j];
             std::vector<double> part(v.begin() + i, v.begin() + i + n);
             part.resize(n + 24);
-            got = fise::ordered_sum<Wave>(got, Values{part.data(), n + 24}, n);
+            got = fise::ordered_sum<Wave>(got, Values{part.data(), n + 24}, n, top);
         }
         if (std::memcmp(&want, &got, 8) && !(want != want && got != got) && ++bad < 4) std::printf("seed %%d: %%a, in order %%a\n", seed, got, want);
     }
