@@ -36,6 +36,19 @@ __device__ __forceinline__ float2 at_halves(float x) {
 #endif
 }
 
+// Workgroup -> (query tile qt, head h, batch element b, key split sp).  The grid is one-dimensional
+// and consecutive workgroups go round-robin to the 8 XCDs (one L2 each): workgroup w takes position
+// (w % 8) * (total / 8) + w / 8 of the (b, sp, h, qt) order, qt fastest, so the query tiles that
+// stream the same K / V slice run on one XCD and the slice is fetched from HBM once, not eight times.
+struct AtPlace { int qt, h, b, sp; };
+__device__ __forceinline__ AtPlace at_place(int nqt, int heads, int B, int splits, FastDiv d_nqt, FastDiv d_heads, FastDiv d_splits) {
+    const int total = nqt * heads * B * splits, chunk = total >> 3;
+    int w = blockIdx.x;
+    if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
+    const int t = (int)fdiv(w, d_nqt), u = (int)fdiv(t, d_heads), b = (int)fdiv(u, d_splits);
+    return {w - t * nqt, t - u * heads, b, u - b * splits};
+}
+
 // KD: 16-wide steps over the head dim; DB: 32-row blocks of the output head dim; EXACT: the head dim is 16 KD (80, 160: the set-up
 // of a short launch is instructions, and most of its conditions and address terms are constants then).
 // What bounds it: few queries, the round trips of the key blocks (~0.9 us each with two blocks in flight, heads up to 96; ~2 us
@@ -58,19 +71,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
     __shared__ __attribute__((aligned(16))) bf16_t Vs[DB * 32][VP];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hl = lane >> 5, l32 = lane & 31;
-    // Workgroup -> (query tile qt, head h, batch element b, key split sp).  The grid is one-dimensional
-    // and consecutive workgroups go round-robin to the 8 XCDs (one L2 each): workgroup w takes position
-    // (w % 8) * (total / 8) + w / 8 of the (b, sp, h, qt) order, qt fastest, so the query tiles that
-    // stream the same K / V slice run on one XCD and the slice is fetched from HBM once, not eight times.
-    int qt, h, b, sp;
-    {
-        const int total = nqt * heads * B * splits, chunk = total >> 3;
-        int w = blockIdx.x;
-        if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
-        const int t = (int)fdiv(w, d_nqt), u = (int)fdiv(t, d_heads);
-        qt = w - t * nqt; h = t - u * heads;
-        b = (int)fdiv(u, d_splits); sp = u - b * splits;
-    }
+    const auto [qt, h, b, sp] = at_place(nqt, heads, B, splits, d_nqt, d_heads, d_splits);
     const int qrow = qt * AT_BQ + wave * AT_QW + l32;
     const bool qok = qrow < M;
     const int d = EXACT ? DP : d_arg, dchunks = d / 8;
@@ -338,19 +339,7 @@ __global__ __launch_bounds__(256, 2) void attention_turns_kernel(const bf16_t* _
 
     const int tid = threadIdx.x, lane = tid & 63, hl = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Workgroup -> (query tile qt, head h, batch element b, key split sp).  The grid is one-dimensional
-    // and consecutive workgroups go round-robin to the 8 XCDs (one L2 each): workgroup w takes position
-    // (w % 8) * (total / 8) + w / 8 of the (b, sp, h, qt) order, qt fastest, so the query tiles that
-    // stream the same K / V slice run on one XCD and the slice is fetched from HBM once, not eight times.
-    int qt, h, b, sp;
-    {
-        const int total = nqt * heads * B * splits, chunk = total >> 3;
-        int w = blockIdx.x;
-        if (w < (chunk << 3)) w = (w & 7) * chunk + (w >> 3);
-        const int t = (int)fdiv(w, d_nqt), u = (int)fdiv(t, d_heads);
-        qt = w - t * nqt; h = t - u * heads;
-        b = (int)fdiv(u, d_splits); sp = u - b * splits;
-    }
+    const auto [qt, h, b, sp] = at_place(nqt, heads, B, splits, d_nqt, d_heads, d_splits);
     const int qrow = qt * AT_BQ + wave * AT_QW + l32;
     const bool qok = qrow < M;
     // turns of this split: `per` key blocks of 64, in turns of BK

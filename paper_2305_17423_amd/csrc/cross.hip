@@ -43,13 +43,6 @@ __device__ __forceinline__ float quad_sum(float x) {
     const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
-template <int CTRL> __device__ __forceinline__ float row_dpp(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float row_sum(float x) {        // over aligned groups of 16 lanes
-    x += row_dpp<0xB1>(x); x += row_dpp<0x4E>(x); x += row_dpp<0x141>(x); x += row_dpp<0x140>(x);
-    return x;
-}
 #endif
 
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -143,7 +136,6 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
     // ---- LayerNorm
     {
         f32x4_t x[5];
-        float s = 0.f;
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
             x[j] = v[j];
@@ -151,26 +143,9 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
                 const unsigned w0 = __float_as_uint(v[j].x), w1 = __float_as_uint(v[j].y);
                 x[j] = f32x4_t{lo16(w0), hi16(w0), lo16(w1), hi16(w1)};
             }
-            s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
         }
-        const float mu = row_sum(s) / C;
-        float q = 0.f;
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            const f32x4_t d = x[j] - mu;
-            q += (d.x * d.x + d.y * d.y) + (d.z * d.z + d.w * d.w);
-        }
-        const float rs = rsqrtf(row_sum(q) / C + a.eps);
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            x[j].x = (x[j].x - mu) * rs * lo16(gam[j].x) + lo16(bet[j].x);
-            x[j].y = (x[j].y - mu) * rs * hi16(gam[j].x) + hi16(bet[j].x);
-            x[j].z = (x[j].z - mu) * rs * lo16(gam[j].y) + lo16(bet[j].y);
-            x[j].w = (x[j].w - mu) * rs * hi16(gam[j].y) + hi16(bet[j].y);
-            const int c4 = j * 16 + l16, sg = c4 >> 1;       // piece of four channels, 16-byte segment
-            *reinterpret_cast<u32x2_t*>(lds + row * PITCH + (sg >> 3) * 128 + ((sg & 7) ^ ((row >> 1) & 7)) * 16 + (c4 & 1) * 8) =
-                u32x2_t{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
-        }
+        layer_norm<16>(x, gam, bet, a.eps);
+        put_row<16>(lds + row * PITCH, row, l16, x);
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // not the loads in flight
 
@@ -421,7 +396,6 @@ __global__ __launch_bounds__(C, 1) void query_attention_kernel(const CrossDev g)
         const int quad = p * NW + wave, row = quad * 4 + lq;
         if (quad >= QUADS) continue;
         f32x4_t x[NW];
-        float s = 0.f;
 #pragma unroll
         for (int j = 0; j < NW; ++j) {
             x[j] = v[p][j];
@@ -429,26 +403,9 @@ __global__ __launch_bounds__(C, 1) void query_attention_kernel(const CrossDev g)
                 const unsigned w0 = __float_as_uint(v[p][j].x), w1 = __float_as_uint(v[p][j].y);
                 x[j] = f32x4_t{lo16(w0), hi16(w0), lo16(w1), hi16(w1)};
             }
-            s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
         }
-        const float mu = row_sum(s) / C;
-        float q = 0.f;
-#pragma unroll
-        for (int j = 0; j < NW; ++j) {
-            const f32x4_t d = x[j] - mu;
-            q += (d.x * d.x + d.y * d.y) + (d.z * d.z + d.w * d.w);
-        }
-        const float rs = rsqrtf(row_sum(q) / C + a.eps);
-#pragma unroll
-        for (int j = 0; j < NW; ++j) {
-            x[j].x = (x[j].x - mu) * rs * lo16(gam[j].x) + lo16(bet[j].x);
-            x[j].y = (x[j].y - mu) * rs * hi16(gam[j].x) + hi16(bet[j].x);
-            x[j].z = (x[j].z - mu) * rs * lo16(gam[j].y) + lo16(bet[j].y);
-            x[j].w = (x[j].w - mu) * rs * hi16(gam[j].y) + hi16(bet[j].y);
-            const int c4 = j * 16 + l16, sg = c4 >> 1;       // piece of four channels, 16-byte segment
-            *reinterpret_cast<u32x2_t*>(lds + row * PITCH + (sg >> 3) * 128 + ((sg & 7) ^ ((row >> 1) & 7)) * 16 + (c4 & 1) * 8) =
-                u32x2_t{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
-        }
+        layer_norm<16>(x, gam, bet, a.eps);
+        put_row<16>(lds + row * PITCH, row, l16, x);
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 

@@ -157,6 +157,59 @@ int launch_conv_patch(const IgemmArgs& a, int tm, hipStream_t st);
 // Linears of many compact rows into float rows (linear_wide.hip).
 bool linear_wide_takes(const IgemmArgs& a);
 int launch_linear_wide(const IgemmArgs& a, hipStream_t st);
+#if defined(__HIP_DEVICE_COMPILE__)
+// Sum over aligned groups of 16, 32 or 64 lanes, in every lane of the group (data paths of the vector unit: a shuffle through the LDS costs
+// ~130 cycles a step, and a row's mean and variance are ten to twelve of them in a row).
+template <int CTRL> __device__ __forceinline__ float group_dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int N> __device__ __forceinline__ float group_sum(float x) {
+    x += group_dpp<0xB1>(x);                                 // quad_perm 1 0 3 2
+    x += group_dpp<0x4E>(x);                                 // quad_perm 2 3 0 1
+    x += group_dpp<0x141>(x);                                // row_half_mirror
+    x += group_dpp<0x140>(x);                                // row_mirror
+    if constexpr (N >= 32) {
+        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+    if constexpr (N >= 64) {
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+    return x;
+}
+// LayerNorm of a row that LPR lanes hold, N pieces of four channels each.
+template <int LPR, int N> __device__ __forceinline__ void layer_norm(f32x4_t (&x)[N], const u32x2_t (&gam)[N], const u32x2_t (&bet)[N], float eps) {
+    constexpr int C = LPR * N * 4;
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < N; ++j) s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
+    const float mu = group_sum<LPR>(s) / C;
+    float q = 0.f;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const f32x4_t d = x[j] - mu;
+        q += (d.x * d.x + d.y * d.y) + (d.z * d.z + d.w * d.w);
+    }
+    const float rs = rsqrtf(group_sum<LPR>(q) / C + eps);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        x[j].x = (x[j].x - mu) * rs * lo16(gam[j].x) + lo16(bet[j].x);
+        x[j].y = (x[j].y - mu) * rs * hi16(gam[j].x) + hi16(bet[j].x);
+        x[j].z = (x[j].z - mu) * rs * lo16(gam[j].y) + lo16(bet[j].y);
+        x[j].w = (x[j].w - mu) * rs * hi16(gam[j].y) + hi16(bet[j].y);
+    }
+}
+// Those pieces as bf16 into row r of an operand in LDS: 16-byte segment p of its 128 bytes at slot p ^ ((r >> 1) & 7).
+template <int LPR, int N> __device__ __forceinline__ void put_row(unsigned char* row, int r, int l, const f32x4_t (&x)[N]) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int c4 = j * LPR + l, seg = c4 >> 1;       // piece of four channels, 16-byte segment
+        *reinterpret_cast<u32x2_t*>(row + (seg >> 3) * 128 + ((seg & 7) ^ ((r >> 1) & 7)) * 16 + (c4 & 1) * 8) = u32x2_t{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
+    }
+}
+#endif
+
 // Normalised rows times weights (norm_gemm.hip).  Rows of K channels: compact float rows under a LayerNorm, or the active pixels of a bf16 map
 // [B, Ho*Wo, K] under a LayerNorm, under a GroupNorm with given statistics, or as they are.  N columns in sections of sect_n, section s with
 // weights w[s] [sect_n, K] to out[s] (only the last one transposed; geglu: one section, w[0] [2N, K], compact float rows).  A bias belongs to one section, and to a gate or to rows without a

@@ -32,29 +32,6 @@ struct NormGemmDev {
     FastDiv d_gx, d_Ma, d_tt, d_tile, d_tiles_w, d_cpg;
 };
 
-#if defined(__HIP_DEVICE_COMPILE__)
-// Sum over aligned groups of 16, 32 or 64 lanes, in every lane of the group (data paths of the vector unit: a shuffle through the LDS costs
-// ~130 cycles a step, and a row's mean and variance are ten to twelve of them in a row).
-template <int CTRL> __device__ __forceinline__ float ng_dpp(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-template <int N> __device__ __forceinline__ float ng_sum(float x) {
-    x += ng_dpp<0xB1>(x);                                 // quad_perm 1 0 3 2
-    x += ng_dpp<0x4E>(x);                                 // quad_perm 2 3 0 1
-    x += ng_dpp<0x141>(x);                                // row_half_mirror
-    x += ng_dpp<0x140>(x);                                // row_mirror
-    if constexpr (N >= 32) {
-        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-        x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    }
-    if constexpr (N >= 64) {
-        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-        x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    }
-    return x;
-}
-#endif
-
 // LDS of a workgroup: rows of K bf16 whose 16-byte segments are XOR-swizzled with (row >> 1) & 7, at a pitch of 128 bytes modulo 256,
 // so that sixteen rows' operand reads meet no bank twice; then the rows' positions; then (GroupNorm) the scale / shift table.
 template <int KM> constexpr int ng_pitch() { return 640 * KM + (KM == 1 ? 0 : 128); }
@@ -209,31 +186,9 @@ __global__ __launch_bounds__(64 * NG_WAVES, 2) void norm_gemm_kernel(const NormG
 #pragma unroll
                 for (int q = 0; q < 4; ++q) { const float2 s = ss[(j * LPR + l) * 4 + q]; x[j][q] = x[j][q] * s.x + s.y; }
         } else if constexpr (SRC != NG_MAP_RAW) {
-            float s = 0.f;
-#pragma unroll
-            for (int j = 0; j < 5; ++j) s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
-            const float mu = ng_sum<LPR>(s) / K;
-            float q = 0.f;
-#pragma unroll
-            for (int j = 0; j < 5; ++j) {
-                const f32x4_t d = x[j] - mu;
-                q += (d.x * d.x + d.y * d.y) + (d.z * d.z + d.w * d.w);
-            }
-            const float rs = rsqrtf(ng_sum<LPR>(q) / K + a.eps);
-#pragma unroll
-            for (int j = 0; j < 5; ++j) {
-                x[j].x = (x[j].x - mu) * rs * lo16(gam[j].x) + lo16(bet[j].x);
-                x[j].y = (x[j].y - mu) * rs * hi16(gam[j].x) + hi16(bet[j].x);
-                x[j].z = (x[j].z - mu) * rs * lo16(gam[j].y) + lo16(bet[j].y);
-                x[j].w = (x[j].w - mu) * rs * hi16(gam[j].y) + hi16(bet[j].y);
-            }
+            layer_norm<LPR>(x, gam, bet, a.eps);
         }
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            const int c4 = j * LPR + l, seg = c4 >> 1;   // piece of four channels, 16-byte segment
-            *reinterpret_cast<u32x2_t*>(lds + r * PITCH + (seg >> 3) * 128 + ((seg & 7) ^ ((r >> 1) & 7)) * 16 + (c4 & 1) * 8) =
-                u32x2_t{f2bf2(x[j].x, x[j].y), f2bf2(x[j].z, x[j].w)};
-        }
+        put_row<LPR>(lds + r * PITCH, r, l, x);
     }
     if constexpr (BIAS)
         if (tid < NG_BIAS / 16) *reinterpret_cast<u32x4_t*>(lbias + tid * 16) = bias16;
