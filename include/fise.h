@@ -463,11 +463,12 @@ int fise_masked_attention_restricted(const void* x, const void* ln_gamma, const 
  * and the number of launches recorded for `kind`:
  *   0 gathered GEMM over maps (and over 2048 - 4095 compact rows of one output)
  *   1 gathered GEMM with the GEGLU epilogue
- *   2 attention (main kernel)           3 gathered GEMM, 64x128 tiles (>= 4096 compact rows)
+ *   2 attention (main kernels)          3 gathered GEMM, 64x128 tiles (>= 4096 compact rows)
  *   4 split-K reduce launches           5 gathered GEMM, 32x128 tiles (<= 32 rows of odd widths)
  *   6 gathered GEMM with the GroupNorm prologue / 32-wide K steps
  *   7 attention merge launches          8 empty brackets (fise_profile_calibrate)
- *   9 gathered GEMM over compact rows (fewer than 2048, or several outputs)
+ *   9 gathered GEMM over compact rows (fewer than 2048, or several outputs), and cross-attention
+ *     that is one launch with the products beside it
  * kind = -1 clears the log.  fise_profile_calibrate records n brackets with no
  * launch inside on `stream`: their average is what a bracket itself adds to every
  * figure above.  All pointers host.  Not thread safe.

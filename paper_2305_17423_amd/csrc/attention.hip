@@ -299,7 +299,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
 // Bound by the instructions a wave issues (one in ~5 cycles: 172 vector, 14 matrix, 14 LDS and ~50 scalar ones a turn of 8 x 40; attention_kernel has
 // 190, 14, 26 and ~70) and, with many queries, by power: the clock falls from 2.2 to 1.7 - 2.1 GHz under this kernel, so what the matrix units
 // multiply counts too, and value rows past the head dim are read as zeros (left as they come, 4 % slower at 2 x 2752 queries, 9216 keys).
-// us, attention_kernel and this one: 2 x 2752 queries, 9216 keys of 8 x 40 154 -> 142, 2 x 4096 x 4096 99 -> 88, 2 x 768 x 4096 29.6 -> 29.0; 2 x 2048 x 2304 of
+// us with the merge, attention_kernel and this one: 2 x 2752 queries, 9216 keys of 8 x 40 154 -> 142, 2 x 4096 x 4096 99 -> 88, 2 x 768 x 4096 29.6 -> 29.0; 2 x 2048 x 2304 of
 // 8 x 80 44.3 -> 41.0; 2 x 576 x 576 of 8 x 160 23.0 -> 22.1.
 // Products issued when the vector work of slot s of a turn starts.  Slots: the maximum, from `weights` on the probabilities (eight slots a 32-key block), from
 // `rescale` on the rescaling.  The values' (DB a 16-key step) go out before the probabilities of their keys are overwritten and before the

@@ -13,8 +13,8 @@
 //  - The heads' outputs meet in the place of the normalised rows (the two barriers beside the one behind the normalisation).
 // Bound by the 500 KB a workgroup brings in (410 of weights at the ~60 GB/s that loads of eight rows get a CU, keys, values and residual in pieces of 64
 // bytes); first touches of the later stages' lines are worth 1.3 us with cold weights.  Against the three launches it stands for (normalisation and
-// queries, attention over 77 keys, product and sum), us: 1536 float rows 18.5 -> 14.4, 5504 27 -> 14.7, 8192 28 -> 15.5; steps of 12 of 64 tiles 2247 ->
-// 2214, 43 of 144 4152 -> 4112, dense pass 4950 -> 4878.
+// queries, attention over 77 keys, product and sum), us: 1536 float rows 18.5 -> 14.5, 5504 27 -> 15.1, 8192 28 -> 16.0; steps of 12 of 64 tiles 2247 ->
+// 2214, 43 of 144 4152 -> 4112, dense pass 4950 -> 4878 (before the second half of the probabilities, 0.15 - 0.5 a launch).
 #include <cmath>
 #include <type_traits>
 #include "attention_choice.h"

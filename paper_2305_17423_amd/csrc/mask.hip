@@ -199,7 +199,7 @@ __global__ void or_pool_kernel(const uint8_t* __restrict__ m, int H, int W, uint
 //    another in LDS (ballots, the waves' counts scanned in between by one lane each), and one wave per bin adds them up from there.
 //  - otsu_apply_kernel: every workgroup finds the threshold for itself (the sums below a bin one chain of 257 additions, the counts
 //    below it, whole numbers, a scan, the objectives a bin per thread) and thresholds its share of the values.
-// us, added one by one and now: bins 18.9 -> 15.4 for 64 x 64 values, the whole mask of two and seven steps at 96 x 96 52 -> 42 and 70 -> 56; one
+// us, added one by one and now: bins 18.9 -> 16.0 for 64 x 64 values; with the threshold, five steps of 64 x 64 25.9 -> 21.3, of 96 x 96 48.1 -> 34.1; a whole mask
 // of five steps at 64 x 64 takes the host 40 to launch either way.
 // ---------------------------------------------------------------------------
 constexpr int OTSU_BINS = 257, OTSU_CHUNK = 4096, OTSU_WG_BINS = 4, OTSU_WAVES = 16;

@@ -8,9 +8,9 @@ into the summaries).  Only library kernels (`fise::`) of masked steps in the ste
   NAME_kernel_trace.md    per-kernel launches per step / average duration (from --kernel-trace)
   NAME_hbm_traffic.md     per-kernel HBM bytes per launch (FETCH_SIZE, WRITE_SIZE scaled by a plain copy kernel)
   NAME_traffic.json       the same per fise_profile_read kind, with the sha1 of the kernel sources measured
-  NAME_mfma_counters.md   MFMA busy cycles / MFMA ops / GPU-active cycles per kernel (--pmc run)
+  NAME_mfma_counters.md   MFMA busy cycles / MFMA ops / GPU-active cycles per kernel (--pmc run; average times from --trace of the same call)
 
-The JSON is what bench.py quotes as `roofline.traffic`; it refuses the figure when the kernel sources changed.
+Every file names the sha1 of the kernel sources at hand when it is written: run it at the sources that were measured.  The JSON is what bench.py quotes as `roofline.traffic`; it refuses the figure when the kernel sources changed.
 """
 from __future__ import annotations
 
@@ -41,6 +41,10 @@ def kernel_sources_sha1() -> str:
             h.update(f.encode())
             h.update(open(os.path.join(CSRC, f), "rb").read())
     return h.hexdigest()
+
+
+def _sources():
+    return f"Kernel sources at sha1 `{kernel_sources_sha1()}` (of their names and contents, in name order)."
 
 
 def short(name: str) -> str:
@@ -109,7 +113,7 @@ def summarize_trace(d, out):
     total, n_lib = sum(v[1] for v in agg.values()) / ns, round(sum(v[0] for v in agg.values()) / ns)
     lines = ["# Masked UNet step (SD-1.5 shapes, batch 2, 64x64 latent, 10 % blob = 12 of 64 tiles): per-kernel times", "",
              "Command (on the MI355X box, from the repository root, after `cd /tmp && export TMPDIR=/tmp`):", "", "```", TRACE_CMD.format(d=os.path.normpath(d)), "```", "",
-             f"Steady state: {ns} consecutive masked steps of `run_kernel_trace.csv`, {n_lib} library launches per step "
+             _sources(), "", f"Steady state: {ns} consecutive masked steps of `run_kernel_trace.csv`, {n_lib} library launches per step "
              f"(mask detection + UNet step; {n_launch - n_lib} torch launches of the sampler update between two steps are left out), summed kernel durations {total / 1e3:.3f} ms per step, start-to-start "
              f"{span / ns / 1e3:.3f} ms per step under the profiler.", "",
              "| kernel | launches/step | average us | min us | max us | ms/step | % of step |", "|---|---:|---:|---:|---:|---:|---:|"]
@@ -179,7 +183,7 @@ def summarize_traffic(df, dw, out):
     lines = ["# HBM traffic of the masked UNet step's kernels (SD-1.5 shapes, 10 % blob): FETCH_SIZE / WRITE_SIZE", "",
              "Commands (two runs, one counter each; on the MI355X box, from the repository root, after `cd /tmp && export TMPDIR=/tmp`):", "", "```",
              PMC_CMD.format(c="FETCH_SIZE", d=os.path.normpath(df)), PMC_CMD.format(c="WRITE_SIZE", d=os.path.normpath(dw)), "```", "",
-             "bench.py ends with `fise_calibrate_peaks`, whose plain copy kernel (`fise::calib_copy_kernel`) reads 1 GiB and writes 1 GiB per "
+             _sources(), "", "bench.py ends with `fise_calibrate_peaks`, whose plain copy kernel (`fise::calib_copy_kernel`) reads 1 GiB and writes 1 GiB per "
              f"launch: the counters are scaled by what they read for it (FETCH_SIZE x {factors['FETCH_SIZE']:.3f}, WRITE_SIZE x "
              f"{factors['WRITE_SIZE']:.3f}).  Steady-state masked steps ({nsteps}), scaled, per launch and per step:", "",
              "| kernel | launches/step | fetched KiB/launch | written KiB/launch | fetched MiB/step | written MiB/step |", "|---|---:|---:|---:|---:|---:|"]
@@ -231,7 +235,7 @@ def summarize_mfma(d, out, avg_us):
     lines = ["# MFMA counters of the masked UNet step's kernels (SD-1.5 shapes, 10 % blob)", "",
              "Command (its own run: counters only; on the MI355X box, from the repository root, after `cd /tmp && export TMPDIR=/tmp`):", "", "```",
              PMC_CMD.format(c="MfmaUtil SQ_INSTS_VALU_MFMA_MOPS_BF16 GRBM_GUI_ACTIVE", d=os.path.normpath(d)), "```", "",
-             f"Per launch, averaged over {nsteps} steady-state masked steps.  `MfmaUtil` is the profiler's derived counter "
+             _sources(), "", f"Per launch, averaged over {nsteps} steady-state masked steps.  `MfmaUtil` is the profiler's derived counter "
              "100 x SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE x SIMDs): the share of SIMD-cycles, while the kernel had the GPU, in which a "
              "matrix unit was executing.  `MFMA GFLOP` = SQ_INSTS_VALU_MFMA_MOPS_BF16 x 512 / 1e9: the bf16 matrix operations actually issued "
              "(tile padding included).  `TFLOP/s` divides it by the kernel's average duration in the kernel-trace run (the counter run "
