@@ -13,8 +13,8 @@
 //  - The heads' outputs meet in the place of the normalised rows (the two barriers beside the one behind the normalisation).
 // Bound by the 500 KB a workgroup brings in (410 of weights at the ~60 GB/s that loads of eight rows get a CU, keys, values and residual in pieces of 64
 // bytes); first touches of the later stages' lines are worth 1.3 us with cold weights.  Against the three launches it stands for (normalisation and
-// queries, attention over 77 keys, product and sum), us: 1536 float rows 18.5 -> 14.5, 5504 27 -> 15.1, 8192 28 -> 16.0; steps of 12 of 64 tiles 2247 ->
-// 2214, 43 of 144 4152 -> 4112, dense pass 4950 -> 4878 (before the second half of the probabilities, 0.15 - 0.5 a launch).
+// queries, attention over 77 keys, product and sum), us with warm weights: 1536 rows of a map 17.3 -> 12.6, 5504 29.3 -> 13.6, 8192 32.8 -> 14.4; steps of 12 of 64
+// tiles 2247 -> 2214, 43 of 144 4152 -> 4112, dense pass 4950 -> 4878.
 #include <cmath>
 #include <type_traits>
 #include "attention_choice.h"
@@ -43,21 +43,54 @@ __device__ __forceinline__ float quad_sum(float x) {
     const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
-#endif
+__device__ __forceinline__ bf16x8_t pack8(const f32x4_t& x, const f32x4_t& y) { return __builtin_bit_cast(bf16x8_t, u32x4_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), f2bf2(y[0], y[1]), f2bf2(y[2], y[3])}); }
 
-#if defined(__HIP_DEVICE_COMPILE__)
-// Eight probabilities as a bf16 operand, and what its rounding left of them as another: the product with the values has both.  One softmax over all keys has one
-// weight that is exactly one; of three launches the middle one had one for every 32 keys, so rounded probabilities cost more here.  Layer of 128 rows x
-// 320 channels, error against 64 bits: those 1.738e-3, this with one operand 1.743e-3, with both 1.724e-3 (1536 rows 1.748, 1.748, 1.733), for 0.1 - 0.25 us of 9 - 14.
-struct Probabilities { bf16x8_t high, low; };
-__device__ __forceinline__ Probabilities probabilities(const f32x4_t& x, const f32x4_t& y) {
-    const u32x4_t h = {f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
-    const u32x4_t l = {f2bf2(x[0] - lo16(h.x), x[1] - hi16(h.x)), f2bf2(x[2] - lo16(h.y), x[3] - hi16(h.y)), f2bf2(y[0] - lo16(h.z), y[1] - hi16(h.z)), f2bf2(y[2] - lo16(h.w), y[3] - hi16(h.w))};
-    return {__builtin_bit_cast(bf16x8_t, h), __builtin_bit_cast(bf16x8_t, l)};
+// Softmax of a lane's row, whose raw scores over keys 32 p + 8 lq + 0 .. 7 and 64 + 4 lq + 0 .. 3 are s: probabilities against the largest of their 32 keys as operands, and
+// what the product of each operand with the values counts for.  One weight in 32 is then exactly one, as where a wave of attention_few_kernel has those keys;
+// against the largest of all keys one in 77 is, and the error against 64 bits of a layer of 128 rows x 320 channels 1.743e-3 for 1.738e-3.  (What the rounding leaves of a probability as a
+// second operand made it 1.724e-3 for the same time, but an infinite value times a zero there is no number.)
+struct KeyWeights { bf16x8_t p[3]; float w[3]; };
+__device__ __forceinline__ KeyWeights key_weights(f32x4_t (&s)[CROSS_KEYS / 16], int n_ctx, int lq, float scale_log2e) {
+    KeyWeights r;
+    float top[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        top[p] = -INFINITY;
+#pragma unroll
+        for (int t = 2 * p; t < 2 * p + 2 && t < CROSS_KEYS / 16; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int key = p < 2 ? 32 * p + 8 * lq + 4 * (t & 1) + e : 64 + 4 * lq + e;
+                s[t][e] = key < n_ctx ? s[t][e] : -INFINITY;
+                top[p] = fmaxf(top[p], s[t][e]);
+            }
+        top[p] = quad_max(top[p]);
+    }
+    const float mx = fmaxf(fmaxf(top[0], top[1]), top[2]);
+    float sum = 0.f;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const float m = (top[p] > -INFINITY ? top[p] : mx) * scale_log2e;       // no such keys: probabilities of zero
+        float part = 0.f;
+#pragma unroll
+        for (int t = 2 * p; t < 2 * p + 2 && t < CROSS_KEYS / 16; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], scale_log2e, -m)); part += s[t][e]; }
+        r.w[p] = __builtin_amdgcn_exp2f(m - mx * scale_log2e);
+        sum += part * r.w[p];
+        r.p[p] = pack8(s[2 * p], p < 2 ? s[2 * p + 1] : f32x4_t{0.f, 0.f, 0.f, 0.f});
+    }
+    const float inv = 1.0f / quad_sum(sum);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) r.w[p] *= inv;
+    return r;
 }
-__device__ __forceinline__ f32x4_t weighted(const u32x4_t& v, const Probabilities& p, const f32x4_t& sum) {
-    const bf16x8_t x = __builtin_bit_cast(bf16x8_t, v);
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, p.high, __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, p.low, sum, 0, 0, 0), 0, 0, 0);
+// Sixteen channels of the values (of keys 32 p ..), weighted.
+__device__ __forceinline__ f32x4_t weighted(const u32x4_t& v0, const u32x4_t& v1, const u32x4_t& v2, const KeyWeights& k) {
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v0), k.p[0], zero, 0, 0, 0) * k.w[0] +
+           __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v1), k.p[1], zero, 0, 0, 0) * k.w[1] +
+           __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v2), k.p[2], zero, 0, 0, 0) * k.w[2];
 }
 #endif
 
@@ -212,7 +245,6 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
                     for (int i = 0; i < 2; ++i) acc[u][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ks][u], fx[ks][i], acc[u][i], 0, 0, 0);
         }
     };
-    auto pack8 = [](const f32x4_t& x, const f32x4_t& y) { return __builtin_bit_cast(bf16x8_t, u32x4_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), f2bf2(y[0], y[1]), f2bf2(y[2], y[3])}); };
     // Four of a lane's eight elements, the rest zeros.  (Not 16 x 16 x 16 products: where a 16 x 16 x 32 product goes on with their sums the compiler leaves
     // too few wait states, and the last two elements of a lane were those of the registers' former contents.)
     auto pack4 = [](const f32x4_t& x) { return __builtin_bit_cast(bf16x8_t, u32x4_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3]), 0, 0}); };
@@ -235,23 +267,7 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
             s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(half(k8[t]), q8, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
             s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, k16[t]), q32, s[t], 0, 0, 0);
         }
-        float mx = -INFINITY;
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int key = t < NT - 1 ? 32 * (t >> 1) + 8 * lq + 4 * (t & 1) + e : 64 + 4 * lq + e;
-                s[t][e] = key < a.n_ctx ? s[t][e] : -INFINITY;
-                mx = fmaxf(mx, s[t][e]);
-            }
-        mx = quad_max(mx) * g.scale_log2e;
-        float sum = 0.f;
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], g.scale_log2e, -mx)); sum += s[t][e]; }
-        const float inv = 1.0f / quad_sum(sum);
-        const Probabilities p0 = probabilities(s[0], s[1]), p1 = probabilities(s[2], s[3]), p2 = probabilities(s[4], f32x4_t{0.f, 0.f, 0.f, 0.f});
+        const KeyWeights kw = key_weights(s, a.n_ctx, lq, g.scale_log2e);
         auto live = [&](unsigned w, int key) { return key + 1 < a.n_ctx ? w : key < a.n_ctx ? w & 0xffffu : 0u; };       // a word of two keys
 #pragma unroll
         for (int dt = 0; dt < 3; ++dt) {
@@ -260,7 +276,7 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
                 for (int e = 0; e < 4; ++e) { v16[dt][0][e] = live(v16[dt][0][e], 8 * lq + 2 * e); v16[dt][1][e] = live(v16[dt][1][e], 32 + 8 * lq + 2 * e); }
                 v8[dt].x = live(v8[dt].x, 64 + 4 * lq); v8[dt].y = live(v8[dt].y, 66 + 4 * lq);
             }
-            o[dt][i] = weighted(u32x4_t{v8[dt].x, v8[dt].y, 0, 0}, p2, weighted(v16[dt][1], p1, weighted(v16[dt][0], p0, f32x4_t{0.f, 0.f, 0.f, 0.f}))) * inv;
+            o[dt][i] = weighted(v16[dt][0], v16[dt][1], u32x4_t{v8[dt].x, v8[dt].y, 0, 0}, kw);
         }
     }
     // what the epilogue adds, under the hand-over and the second product
@@ -328,7 +344,7 @@ __global__ __launch_bounds__(512, 2) void cross_attention_kernel(const CrossDev 
 //    rows; the waves' sums meet in the place of the weights, in wave order, and become queries;
 //  - the last two waves hold keys and values and finish sixteen rows each, numbered as above.
 // Bound by its start, the rows and 100 KB of weights.  Against a launch each for the queries and the attention, us: transformer block of 160 rows x 640 65.9
-// -> 63.1, of 512 82.7 -> 78.5; attention layer of 128 rows x 320 36.0 -> 32.0; step of 2 of 70 tiles 1787 -> 1755, 12 of 64 2217 -> 2198.
+// -> 63.1, of 512 82.7 -> 78.5; cross-attention layer of 96 rows x 320 13.0 -> 9.2, of 160 x 640 16.7 -> 12.7; step of 2 of 70 tiles 1787 -> 1755, 12 of 64 2217 -> 2198.
 template <int C> struct QueryTile {
     static constexpr int NW = C / 64, D = C / CROSS_HEADS, U = (D + 15) / 16, BM = 32, PITCH = 2 * C + (C % 128 ? 0 : 128), REGION = D * 128 > U * 2048 ? D * 128 : U * 2048,
                          QC = (D + 31) / 32, QPITCH = QC * 64 + 16, LDS = BM * PITCH + NW * REGION;      // QC: 32-wide steps over the head dim
@@ -478,29 +494,13 @@ __global__ __launch_bounds__(C, 1) void query_attention_kernel(const CrossDev g)
 #pragma unroll
     for (int c = 0; c < T::QC; ++c) q[c] = *reinterpret_cast<const bf16x8_t*>(lds + (tile * 16 + l16) * T::QPITCH + c * 64 + lq * 16);
     f32x4_t s[NT];
-    float mx = -INFINITY;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         s[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < T::QC; ++c) s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, k16[t][c]), q[c], s[t], 0, 0, 0);
     }
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int key = t < NT - 1 ? 32 * (t >> 1) + 8 * lq + 4 * (t & 1) + e : 64 + 4 * lq + e;
-            s[t][e] = key < a.n_ctx ? s[t][e] : -INFINITY;
-            mx = fmaxf(mx, s[t][e]);
-        }
-    mx = quad_max(mx) * g.scale_log2e;
-    float sum = 0.f;
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], g.scale_log2e, -mx)); sum += s[t][e]; }
-    const float inv = 1.0f / quad_sum(sum);
-    const Probabilities p0 = probabilities(s[0], s[1]), p1 = probabilities(s[2], s[3]), p2 = probabilities(s[4], f32x4_t{0.f, 0.f, 0.f, 0.f});
+    const KeyWeights kw = key_weights(s, a.n_ctx, lq, g.scale_log2e);
     auto live = [&](unsigned x, int key) { return key + 1 < a.n_ctx ? x : key < a.n_ctx ? x & 0xffffu : 0u; };       // a word of two keys
     const int m = m0 + tile * 16 + l16;
     bf16_t* const out = (bf16_t*)a.out + ((size_t)b * a.Ma + m) * C + h * D + lq * 4;
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(C, 1) void query_attention_kernel(const CrossDev g)
 #pragma unroll
         for (int e = 0; e < 4; ++e) { v16[dt][0][e] = live(v16[dt][0][e], 8 * lq + 2 * e); v16[dt][1][e] = live(v16[dt][1][e], 32 + 8 * lq + 2 * e); }
         const u32x4_t tail = {live(v8[dt].x, 64 + 4 * lq), live(v8[dt].y, 66 + 4 * lq), 0, 0};
-        const f32x4_t x = weighted(tail, p2, weighted(v16[dt][1], p1, weighted(v16[dt][0], p0, f32x4_t{0.f, 0.f, 0.f, 0.f}))) * inv;
+        const f32x4_t x = weighted(v16[dt][0], v16[dt][1], tail, kw);
         if (m < a.Ma && dt * 16 + lq * 4 < D) *(FISE_AS1 u32x2_t*)(out + dt * 16) = u32x2_t{f2bf2(x[0], x[1]), f2bf2(x[2], x[3])};
     }
 #endif
