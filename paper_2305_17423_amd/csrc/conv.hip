@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void conv_scalar_kernel(const T* __restrict__ 
 // SiLU(GroupNorm(x)) under a 3x3 kernel with four output channels (the UNet's output convolution).  Four columns leave a matrix tile of the general
 // product 15/16 empty and its K range is then split and summed by a second launch; here a workgroup takes 4 x 4 pixels: their 6 x 6 patch is
 // normalised into LDS once, every wave multiplies a quarter of the 32-channel pieces of the nine taps, whose weights it requested up front.
-// Bound by two trips to memory and its barriers.  1536 pixels of 320 channels, with the sum, 17.5 -> 7.9 us, 8192 30.7 -> 8.7.
+// Bound by two trips to memory and its barriers.  Warm, 1536 pixels of 320 channels, with the sum, 14.8 -> 6.1 us, 8192 29.4 -> 8.4.
 constexpr int CO_PATCH = 36;
 __global__ __launch_bounds__(256) void conv_out_kernel(const bf16_t* __restrict__ x, int C, int H, int W, const bf16_t* __restrict__ w, const bf16_t* __restrict__ bias,
                                                        const float* __restrict__ mean, const float* __restrict__ rstd, const bf16_t* __restrict__ gamma,
@@ -91,6 +91,8 @@ __global__ __launch_bounds__(256) void conv_out_kernel(const bf16_t* __restrict_
         }
     };
     request(wave);
+    const int nothing = 2 * C;                          // behind the first pixel's channels: zeros, which the weights past the last piece meet (an infinite activation would make them no number)
+    if (tid == 0) *reinterpret_cast<uint4*>(lds + nothing) = make_uint4(0, 0, 0, 0);
     // scale and shift of this thread's eight channels
     const int pieces = C / 8, per = (int)fdiv(256u, d_pieces), p0 = (int)fdiv((unsigned)tid, d_pieces), c = (tid - p0 * pieces) * 8;
     float sc[8], sh[8];
@@ -128,14 +130,15 @@ __global__ __launch_bounds__(256) void conv_out_kernel(const bf16_t* __restrict_
         }
     __syncthreads();
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    const int mine = ((l16 >> 2) * 6 + (l16 & 3)) * pitch + lq * 16;
     for (int k0 = wave; k0 < total; k0 += 4 * CO_BATCH) {
         if (k0 != wave) request(k0);
+        // lane i works out where the pixels of the i-th piece lie (a division for each piece on its own: 0.2 - 0.4 us more)
+        const int k = k0 + lane * 4, tap = (int)fdiv((unsigned)k, d_c32), ky = (tap * 11) >> 5, any = k < total ? -1 : 0;
+        const int at = k < total ? (ky * 6 + tap - ky * 3) * pitch + (k - tap * (C / 32)) * 64 : nothing;
 #pragma unroll
-        for (int i = 0; i < CO_BATCH; ++i) {
-            const int k = min(k0 + i * 4, total - 1), tap = (int)fdiv((unsigned)k, d_c32), ky = (tap * 11) >> 5;       // past the last piece: weights are zeros
-            const unsigned char* const q = lds + (((l16 >> 2) + ky) * 6 + (l16 & 3) + tap - ky * 3) * pitch + (k - tap * (C / 32)) * 64 + lq * 16;
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fw[i]), *reinterpret_cast<const bf16x8_t*>(q), acc, 0, 0, 0);
-        }
+        for (int i = 0; i < CO_BATCH; ++i)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fw[i]), *reinterpret_cast<const bf16x8_t*>(lds + ((mine & __builtin_amdgcn_readlane(any, i)) + __builtin_amdgcn_readlane(at, i))), acc, 0, 0, 0);
     }
     if (lq == 0) part[wave][l16] = acc;
     __syncthreads();

@@ -256,3 +256,25 @@ NARROW = [
 @pytest.mark.parametrize("case", NARROW, ids=[c[0] for c in NARROW])
 def test_bf16_conv_of_four_columns(fb, case):
     test_bf16_conv_variants(fb, case)
+
+
+@pytest.mark.parametrize("C", [64, 320, 640])
+def test_four_columns_infinite_activation(fb, C):
+    """An infinite activation in the last channels makes the pixels around it infinite, by the sign of the weight that it meets, and no other."""
+    B, H, W, t = 1, 8, 8, 4
+    rng = np.random.default_rng(C)
+    x, w = wl.normal(rng, (B, H, W, C), 1.0, "bf16"), wl.normal(rng, (4, 3, 3, C), 1 / math.sqrt(9 * C), "bf16")
+    x[0, 5, 3, C - 1] = np.inf
+    w[..., C - 1] = np.where(w[..., C - 1] < 0, -1, 1)
+    gn = dict(mean=dev(np.zeros((B, 32)), "f32"), rstd=dev(np.ones((B, 32)), "f32"), gamma=dev(np.ones(C), "bf16"), beta=dev(np.zeros(C), "bf16"), groups=32)
+    idx, y = idx_dev(fo.full_index(H, W, t)), dev(np.zeros((B, H, W, 4)), "bf16")
+    args = fb.conv_args(dev(x, "bf16"), dev(w, "bf16"), None, idx, idx.numel(), t, y, gn=gn, gn_silu=1)
+    ws = torch.zeros(int(fb.fise_masked_conv_workspace_bytes(args)), dtype=torch.uint8, device=DEV)
+    fb.fise_masked_conv(args, ws)
+    got = host(y)
+    want = np.zeros((H, W, 4))
+    for ky in range(3):
+        for kx in range(3):
+            want[5 + 1 - ky, 3 + 1 - kx] = w[:, ky, kx, C - 1] * np.inf
+    assert np.array_equal(got[0][want != 0], want[want != 0])
+    assert np.isfinite(got[0][want == 0]).all()
