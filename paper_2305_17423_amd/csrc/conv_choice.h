@@ -38,7 +38,7 @@ inline GnSlab gn_slab(int C, int G) {
 // Pieces a lane of gn_map_kernel holds, 0: two launches.  Up to eight: 32 workgroups of eight 9.5 us (two launches 10.4), of twelve 10.6 (10.1) with 512 lanes
 // as with 1024, 64 of twelve 12.6 (12).  Fewer than 32 workgroups were not measured.  Channels: what the statistics' launch takes.
 inline int gn_map_values(const GnSlab& s, int B, int HW, int C, int G) {
-    if (!s.groups || C * 16 > 64 * 1024 || s.pieces > GM_THREADS || (long long)B * (G / s.groups) < 32) return 0;
+    if (!s.groups || C > 64 * 1024 / 16 || s.pieces > GM_THREADS || (long long)B * (G / s.groups) < 32) return 0;
     const int lanes = GM_THREADS / s.pieces, n = (HW + lanes - 1) / lanes;
     return n <= GM_MAX_J ? n : 0;
 }
