@@ -49,6 +49,53 @@ __device__ __forceinline__ AtPlace at_place(int nqt, int heads, int B, int split
     return {w - t * nqt, t - u * heads, b, u - b * splits};
 }
 
+// What both kernels of many queries begin and end with.  Query fragments: B operand of S^T = K Q^T (column = query, 8 consecutive head-dim elements)
+template <int KD> __device__ __forceinline__ void at_queries(bf16x8_t (&qf)[KD], const bf16_t* __restrict__ q, int M, int C, int b, int h, int qrow, bool qok, int hl, int d) {
+#pragma unroll
+    for (int ks = 0; ks < KD; ++ks) {
+        const int c = ks * 16 + hl * 8;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (qok && c < d) v = *reinterpret_cast<const uint4*>(q + ((size_t)b * M + qrow) * C + h * d + c);
+        qf[ks] = *reinterpret_cast<bf16x8_t*>(&v);
+    }
+}
+// Store: lane holds query l32, head-dim rows i*32 + (e/4)*8 + hl*4 + e%4: four consecutive elements of e are
+// four consecutive channels (d is a multiple of 8, so a group of four is inside the head or outside it as a whole)
+template <int DB> __device__ __forceinline__ void at_store(const f32x16_t (&oacc)[DB], float m_run, float l_run, bool qok, int splits, int B, int M, int C, int heads, int b, int h, int sp,
+                                                           int qrow, int hl, int d, bf16_t* __restrict__ out, float* __restrict__ part_o, float* __restrict__ part_ml) {
+    const float2 lh = at_halves(l_run);
+    l_run = lh.x + lh.y;
+    if (!qok) return;
+    if (splits == 1) {
+        const float inv = 1.0f / l_run;
+        bf16_t* o = out + ((size_t)b * M + qrow) * C + h * d;
+#pragma unroll
+        for (int i = 0; i < DB; ++i)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const int r = i * 32 + q4 * 8 + hl * 4;
+                if (r < d)
+                    *reinterpret_cast<uint2*>(o + r) = make_uint2(f2bf2(oacc[i][4 * q4] * inv, oacc[i][4 * q4 + 1] * inv),
+                                                                  f2bf2(oacc[i][4 * q4 + 2] * inv, oacc[i][4 * q4 + 3] * inv));
+            }
+    } else {
+        // unnormalised partial of this key range: O[sp][b][qrow][h*d + r], (m, l)[sp][b][h][qrow]
+        float* po = part_o + (((size_t)sp * B + b) * M + qrow) * C + h * d;
+#pragma unroll
+        for (int i = 0; i < DB; ++i)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const int r = i * 32 + q4 * 8 + hl * 4;
+                if (r < d)
+                    *reinterpret_cast<float4*>(po + r) = make_float4(oacc[i][4 * q4], oacc[i][4 * q4 + 1], oacc[i][4 * q4 + 2], oacc[i][4 * q4 + 3]);
+            }
+        if (hl == 0) {
+            float* pm = part_ml + ((((size_t)sp * B + b) * heads + h) * M + qrow) * 2;
+            pm[0] = m_run; pm[1] = l_run;
+        }
+    }
+}
+
 // KD: 16-wide steps over the head dim; DB: 32-row blocks of the output head dim; EXACT: the head dim is 16 KD (80, 160: the set-up
 // of a short launch is instructions, and most of its conditions and address terms are constants then).
 // What bounds it: few queries, the round trips of the key blocks (~0.9 us each with two blocks in flight, heads up to 96; ~2 us
@@ -81,15 +128,8 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
     const int per = (nblocks + splits - 1) / splits;
     const int blk0 = sp * per, blk1 = min(nblocks, blk0 + per);
 
-    // query fragments: B operand of S^T = K Q^T (column = query, 8 consecutive head-dim elements)
     bf16x8_t qf[KD];
-#pragma unroll
-    for (int ks = 0; ks < KD; ++ks) {
-        const int c = ks * 16 + hl * 8;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (qok && c < d) v = *reinterpret_cast<const uint4*>(q + ((size_t)b * M + qrow) * C + h * d + c);
-        qf[ks] = *reinterpret_cast<bf16x8_t*>(&v);
-    }
+    at_queries(qf, q, M, C, b, h, qrow, qok, hl, d);
 
     f32x16_t oacc[DB];
 #pragma unroll
@@ -258,39 +298,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
       }
     }
 
-    // ---- store: lane holds query l32, head-dim rows i*32 + (e/4)*8 + hl*4 + e%4: four consecutive elements of e are
-    // four consecutive channels (d is a multiple of 8, so a group of four is inside the head or outside it as a whole)
-    const float2 lh = at_halves(l_run);
-    l_run = lh.x + lh.y;
-    if (!qok) return;
-    if (splits == 1) {
-        const float inv = 1.0f / l_run;
-        bf16_t* o = out + ((size_t)b * M + qrow) * C + h * d;
-#pragma unroll
-        for (int i = 0; i < DB; ++i)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int r = i * 32 + q4 * 8 + hl * 4;
-                if (r < d)
-                    *reinterpret_cast<uint2*>(o + r) = make_uint2(f2bf2(oacc[i][4 * q4] * inv, oacc[i][4 * q4 + 1] * inv),
-                                                                  f2bf2(oacc[i][4 * q4 + 2] * inv, oacc[i][4 * q4 + 3] * inv));
-            }
-    } else {
-        // unnormalised partial of this key range: O[sp][b][qrow][h*d + r], (m, l)[sp][b][h][qrow]
-        float* po = part_o + (((size_t)sp * B + b) * M + qrow) * C + h * d;
-#pragma unroll
-        for (int i = 0; i < DB; ++i)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int r = i * 32 + q4 * 8 + hl * 4;
-                if (r < d)
-                    *reinterpret_cast<float4*>(po + r) = make_float4(oacc[i][4 * q4], oacc[i][4 * q4 + 1], oacc[i][4 * q4 + 2], oacc[i][4 * q4 + 3]);
-            }
-        if (hl == 0) {
-            float* pm = part_ml + ((((size_t)sp * B + b) * heads + h) * M + qrow) * 2;
-            pm[0] = m_run; pm[1] = l_run;
-        }
-    }
+    at_store(oacc, m_run, l_run, qok, splits, B, M, C, heads, b, h, sp, qrow, hl, d, out, part_o, part_ml);
 }
 
 // The same for long key ranges of heads of 40, 80 and 160: a turn of 64 (160: 32) keys at a time, with the products of other turns issued between the
@@ -345,15 +353,8 @@ __global__ __launch_bounds__(256, 2) void attention_turns_kernel(const bf16_t* _
     // turns of this split: `per` key blocks of 64, in turns of BK
     const int t0 = sp * per * (AT_BKV / BK), t1 = min((n_keys + BK - 1) / BK, t0 + per * (AT_BKV / BK)), turns = t1 - t0;
 
-    // query fragments: B operand of S^T = K Q^T (column = query, 8 consecutive head-dim elements)
     bf16x8_t qf[KD];
-#pragma unroll
-    for (int ks = 0; ks < KD; ++ks) {
-        const int c = ks * 16 + hl * 8;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (qok && c < d) v = *reinterpret_cast<const uint4*>(q + ((size_t)b * M + qrow) * C + h * d + c);
-        qf[ks] = *reinterpret_cast<bf16x8_t*>(&v);
-    }
+    at_queries(qf, q, M, C, b, h, qrow, qok, hl, d);
 
     // ---- loads: KL of keys, VL of values, wave w takes every fourth from the w-th on.  K: LDS row r of a turn holds key
     // (r & 3) + 4 (r / 8 % 2) + 8 (r / 4 % 2) + 16 (r / 16), so that a lane's eight scores of a 16-key step are eight consecutive
@@ -534,39 +535,7 @@ __global__ __launch_bounds__(256, 2) void attention_turns_kernel(const bf16_t* _
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // loads behind the last turn still write the ring
     }
 
-    // ---- store: lane holds query l32, head-dim rows i*32 + (e/4)*8 + hl*4 + e%4: four consecutive elements of e are
-    // four consecutive channels (d is a multiple of 8, so a group of four is inside the head or outside it as a whole)
-    const float2 lh = at_halves(l_run);
-    l_run = lh.x + lh.y;
-    if (!qok) return;
-    if (splits == 1) {
-        const float inv = 1.0f / l_run;
-        bf16_t* o = out + ((size_t)b * M + qrow) * C + h * d;
-#pragma unroll
-        for (int i = 0; i < DB; ++i)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int r = i * 32 + q4 * 8 + hl * 4;
-                if (r < d)
-                    *reinterpret_cast<uint2*>(o + r) = make_uint2(f2bf2(oacc[i][4 * q4] * inv, oacc[i][4 * q4 + 1] * inv),
-                                                                  f2bf2(oacc[i][4 * q4 + 2] * inv, oacc[i][4 * q4 + 3] * inv));
-            }
-    } else {
-        // unnormalised partial of this key range: O[sp][b][qrow][h*d + r], (m, l)[sp][b][h][qrow]
-        float* po = part_o + (((size_t)sp * B + b) * M + qrow) * C + h * d;
-#pragma unroll
-        for (int i = 0; i < DB; ++i)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int r = i * 32 + q4 * 8 + hl * 4;
-                if (r < d)
-                    *reinterpret_cast<float4*>(po + r) = make_float4(oacc[i][4 * q4], oacc[i][4 * q4 + 1], oacc[i][4 * q4 + 2], oacc[i][4 * q4 + 3]);
-            }
-        if (hl == 0) {
-            float* pm = part_ml + ((((size_t)sp * B + b) * heads + h) * M + qrow) * 2;
-            pm[0] = m_run; pm[1] = l_run;
-        }
-    }
+    at_store(oacc, m_run, l_run, qok, splits, B, M, C, heads, b, h, sp, qrow, hl, d, out, part_o, part_ml);
 #endif
 }
 
