@@ -30,9 +30,9 @@ HBM_PEAK_GBS = 8000.0
 # 64x128 from there on, where linear_wide does not take them; its other tiles for odd widths only)
 KIND_NAMES = {0: "wave_gemm_kernel<*,A_MAP> / conv_patch_kernel / igemm_dma_kernel<64,64,*>",
               1: "norm_gemm_kernel<*,GEGLU> / wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>",
-              2: "attention_kernel / attention_few_kernel", 3: "linear_wide_kernel / igemm_dma_kernel<64,128,2,4,3,*>", 4: "igemm_reduce_kernel",
-              5: "igemm_dma_kernel<32,128,1,4,3,*>", 6: "igemm_kernel<...> (GroupNorm prologue)", 7: "attention_merge_kernel",
-              8: "(empty bracket)", 9: "norm_gemm_kernel / wave_gemm_kernel<*,A_ROWS>"}
+              2: "attention_kernel / attention_turns_kernel / attention_few_kernel", 3: "linear_wide_kernel / igemm_dma_kernel<64,128,2,4,3,*>", 4: "igemm_reduce_kernel",
+              5: "igemm_dma_kernel<32,128,1,4,3,*>", 6: "conv_out_kernel / igemm_kernel<...>", 7: "attention_merge_kernel",
+              8: "(empty bracket)", 9: "norm_gemm_kernel / wave_gemm_kernel<*,A_ROWS> / cross_attention_kernel / query_attention_kernel / rows_group_kernel"}
 # HBM bytes per launch (read + written) of the library's kernels from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of
 # this bench on the headline workload: profiles/masked_unet_step_sd15_10pct_traffic.json, written by
 # `python -m paper_2305_17423_amd.profile_summary` together with the sha1 of the kernel sources it was measured

@@ -465,7 +465,8 @@ int fise_masked_attention_restricted(const void* x, const void* ln_gamma, const 
  *   1 gathered GEMM with the GEGLU epilogue
  *   2 attention (main kernels)          3 gathered GEMM, 64x128 tiles (>= 4096 compact rows)
  *   4 split-K reduce launches           5 gathered GEMM, 32x128 tiles (<= 32 rows of odd widths)
- *   6 gathered GEMM with the GroupNorm prologue / 32-wide K steps
+ *   6 gathered GEMM with the GroupNorm prologue / 32-wide K steps, and four columns under a 3x3
+ *     kernel behind a GroupNorm
  *   7 attention merge launches          8 empty brackets (fise_profile_calibrate)
  *   9 gathered GEMM over compact rows (fewer than 2048, or several outputs), and cross-attention
  *     that is one launch with the products beside it

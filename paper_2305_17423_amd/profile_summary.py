@@ -61,7 +61,7 @@ def kind_of(name: str):
     if wave and wave[2] == "true" or norm and norm[1] == "true" or "igemm_dma_kernel<64, 128, 2, 2" in n or "igemm_dma_kernel<32, 256" in n:
         return "norm_gemm_kernel<*,GEGLU> / wave_gemm_kernel<*,GEGLU> / igemm_dma_kernel<64,128,2,2,3,*>"
     if norm or "wave_gemm_group" in n or "rows_group_kernel" in n or "cross_attention_kernel" in n or "query_attention_kernel" in n or wave and wave[1] == "0":
-        return "norm_gemm_kernel / wave_gemm_kernel<*,A_ROWS>"
+        return "norm_gemm_kernel / wave_gemm_kernel<*,A_ROWS> / cross_attention_kernel / query_attention_kernel / rows_group_kernel"
     if wave or "conv_patch_kernel" in n or "igemm_dma_kernel<64, 64, 2, 2" in n:
         return "wave_gemm_kernel<*,A_MAP> / conv_patch_kernel / igemm_dma_kernel<64,64,*>"
     if "linear_wide_kernel" in n or "igemm_dma_kernel<64, 128, 2, 4" in n:
@@ -71,11 +71,11 @@ def kind_of(name: str):
     if "igemm_reduce" in n:
         return "igemm_reduce_kernel"
     if "igemm_kernel" in n or "conv_out_kernel" in n:
-        return "igemm_kernel<...> (GroupNorm prologue)"
+        return "conv_out_kernel / igemm_kernel<...>"
     if "attention_merge" in n:
         return "attention_merge_kernel"
     if "attention_kernel" in n or "attention_few_kernel" in n or "attention_turns_kernel" in n:
-        return "attention_kernel / attention_few_kernel"
+        return "attention_kernel / attention_turns_kernel / attention_few_kernel"
     return None
 
 
